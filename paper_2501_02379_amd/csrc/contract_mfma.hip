@@ -10,11 +10,7 @@
 // i.e. 4 real multiply-adds per complex multiply-add on either layout below.
 //
 // The kernels:
-//  k_mid      contracts a mode that is NOT the last one: the tensor is (A, K, B) with B >= 1
-//             contiguous; every lane owns VEC complex columns (a, b) and walks the K rows.
-//  k_core     mode 1 both ways around AdamUpdate on the Tucker core, in one launch.
-//  k_core2    modes 1 and 2 both ways around AdamUpdate on the core, one workgroup per column group:
-//             everything between the two fused end kernels of a four-way tensor, in one launch.
+//  (the modes between: mid.hip, core2.hip)
 //  k_lproj    contracts the LAST mode of the gradient itself (first compression stage): a
 //             flat tile of rows is staged in LDS, the entries of the support Omega that fall
 //             in the tile are handed to the sparse branch (gather) and zeroed (this is
@@ -31,13 +27,10 @@
 // Operand layout of v_mfma_f32_32x32x2f32 (D = A B + C, A 32 x 2, B 2 x 32, 64 lanes):
 //   lane l supplies A[l % 32][l / 32] and B[l / 32][l % 32];
 //   register r of lane l receives D[(r % 4) + 8 (r / 4) + 4 (l / 32)][l % 32].
-#include <atomic>
-#include <map>
-#include <mutex>
 #include <type_traits>
-#include <utility>
 
 #include "device_common.h"
+#include "launch_util.h"
 
 namespace tgrad {
 
@@ -101,701 +94,6 @@ __global__ __launch_bounds__(256) void k_mfma_probe_f64(float* sink, int64_t ite
 #pragma unroll
     for (int r = 0; r < 4; ++r) t += acc[c][r];
   if (t == 12345.678) sink[0] = (float)t;
-}
-
-// -------------------------------------------------------------------------------------------
-// k_mid: out[a, m, b] = sum_k F[m, k] x[a, k, b],  F = U^H (PROJECT) or U.
-// Workgroup = 4 wavefronts; a wavefront owns 32 column vectors (VEC complex each) and MT row
-// tiles of 32 output rows; blockIdx.y selects the group of MT row tiles.
-// Per pair of rows (k = 2 j, 2 j + 1): lanes 0..31 load row 2 j, lanes 32..63 row 2 j + 1 of
-// their column; the factor operands (Fr, Fi) for that pair come from LDS.
-constexpr int kMidThreads = 256;
-constexpr int kMidJChunk = 64;            // row pairs of the factor staged in LDS at a time
-constexpr int kMidUnroll = 8;
-
-// Fills dst[0 .. total) with gen(e), `kStageBatch` global loads per thread in flight at a time (a
-// plain loop would pay one memory round trip per element and thread).
-constexpr int kStageBatch = 8;
-template <typename Gen>
-__device__ __forceinline__ void stage_batched(float2* dst, int total, int tid, int nthreads, Gen gen) {
-  for (int e0 = tid; e0 < total; e0 += nthreads * kStageBatch) {
-    float2 f[kStageBatch];
-#pragma unroll
-    for (int u = 0; u < kStageBatch; ++u) {
-      const int e = e0 + u * nthreads;
-      f[u] = gen(e < total ? e : total - 1);
-    }
-#pragma unroll
-    for (int u = 0; u < kStageBatch; ++u) {
-      const int e = e0 + u * nthreads;
-      if (e < total) dst[e] = f[u];
-    }
-  }
-}
-
-template <int VEC> struct VecT;
-template <> struct VecT<1> { typedef float2 type; };
-template <> struct VecT<2> { typedef float4 type; };
-
-// MODE 0: every wavefront of a workgroup owns its own 32 column vectors and all MT row tiles.
-// MODE 1 (split-K, MT = 1): the 4 wavefronts share 32 column vectors and deal the row pairs
-//         round-robin; their partial tiles are summed through LDS in a fixed order.  For stages
-//         with few columns, where MODE 0 would leave most of the chip idle.
-// MODE 2 (MT = 1): the 4 wavefronts share 32 column vectors and own one 32-row output tile each
-//         (128 output rows per workgroup).  For reconstruction stages with few columns.
-template <int MT, int VEC, bool PROJECT, int MODE>
-__global__ __launch_bounds__(kMidThreads) void k_mid(const float* __restrict__ x,
-                                                     const float2* __restrict__ U, int rn, int64_t A,
-                                                     int K, int M, int64_t B, float* __restrict__ out) {
-  typedef typename VecT<VEC>::type V;
-  constexpr int TL = MODE == 2 ? 4 : MT;  // row tiles whose factor operands a workgroup stages
-  extern __shared__ float2 sF[];          // [pair][tile][lane] = (Fr, Fi)
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int col = lane & 31, half = lane >> 5;
-  const int64_t BV = B / VEC;             // host guarantees B % VEC == 0
-  const int64_t ncv = A * BV;
-  const int64_t cv_raw = MODE == 0 ? ((int64_t)blockIdx.x * (kMidThreads / 64) + wave) * 32 + col
-                                   : (int64_t)blockIdx.x * 32 + col;
-  const bool valid = cv_raw < ncv;
-  const int64_t cv = valid ? cv_raw : ncv - 1;   // lanes past the end load a real column, store nothing
-  const int64_t a = cv / BV;
-  const int64_t bv = cv - a * BV;
-  const float* xp = x + ((a * K) * B + bv * VEC) * 2;
-  const int64_t row_stride = B * 2;       // floats between consecutive k
-  const int mbase = blockIdx.y * (32 * TL);
-  const int my_tile0 = MODE == 2 ? wave : 0;   // first of this wavefront's MT tiles among the staged TL
-
-  v16f acc[MT][2 * VEC];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int t = 0; t < 2 * VEC; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[mt][t][r] = 0.f;
-
-  // One row pair: lanes 0..31 hold row 2 j, lanes 32..63 row 2 j + 1 of their column.  The loads are
-  // unconditional (a row index past K is clamped to the last row: its factor operands are zero), and
-  // the loops below carry no guards: predicated loads and guarded MFMAs both stall the pipeline.
-  auto load_pair_row = [&](int j) -> V {
-    const int k = 2 * j + half;
-    return *reinterpret_cast<const V*>(xp + (int64_t)(k < K ? k : K - 1) * row_stride);
-  };
-  auto mfma_pair_row = [&](const V& v, int jj) {
-    float xs[2 * VEC], xj[2 * VEC];
-    if constexpr (VEC == 1) {
-      xs[0] = v.x; xs[1] = v.y;
-    } else {
-      xs[0] = v.x; xs[1] = v.y; xs[2] = v.z; xs[3] = v.w;
-    }
-#pragma unroll
-    for (int c = 0; c < VEC; ++c) {                            // (X J): re column <- -im, im column <- re
-      xj[2 * c] = -xs[2 * c + 1];
-      xj[2 * c + 1] = xs[2 * c];
-    }
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const float2 f = sF[(jj * TL + my_tile0 + mt) * 64 + lane];
-#pragma unroll
-      for (int t = 0; t < 2 * VEC; ++t) {
-        acc[mt][t] = mfma32(f.x, xs[t], acc[mt][t]);
-        acc[mt][t] = mfma32(f.y, xj[t], acc[mt][t]);
-      }
-    }
-  };
-
-  constexpr int JSTEP = MODE == 1 ? 4 : 1;                     // split-K: wavefront w takes pairs w, w + 4, ...
-  const int jfirst = MODE == 1 ? wave : 0;
-  const int J = (K + 1) >> 1;
-  for (int jc0 = 0; jc0 < J; jc0 += kMidJChunk) {
-    const int jn = (J - jc0) < kMidJChunk ? (J - jc0) : kMidJChunk;
-    // the chunk's first batch of rows goes in flight before the factor operands are staged
-    V cur[kMidUnroll];
-#pragma unroll
-    for (int u = 0; u < kMidUnroll; ++u) cur[u] = load_pair_row(jc0 + jfirst + u * JSTEP);
-    __syncthreads();                                           // previous chunk fully consumed
-    stage_batched(sF, jn * TL * 64, tid, kMidThreads, [&](int e) -> float2 {
-      const int l = e & 63;
-      const int mt = (e >> 6) % TL;
-      const int jj = e / (64 * TL);
-      const int m = mbase + 32 * mt + (l & 31);
-      const int k = 2 * (jc0 + jj) + (l >> 5);
-      const bool in = m < M && k < K;                          // outside: a clamped, valid element times zero
-      const int mc = in ? m : 0, kc = in ? k : 0;
-      const float2 u = PROJECT ? U[(int64_t)kc * rn + mc] : U[(int64_t)mc * rn + kc];
-      return in ? make_float2(u.x, PROJECT ? -u.y : u.y) : make_float2(0.f, 0.f);
-    });
-    __syncthreads();
-    // Row pairs in batches of kMidUnroll, the next batch's loads issued before the current batch
-    // goes to the matrix cores (rows past the end are clamped onto the last one and not used).
-    int jj = jfirst;
-    for (; jj + (kMidUnroll - 1) * JSTEP < jn; jj += kMidUnroll * JSTEP) {
-      V nxt[kMidUnroll];
-#pragma unroll
-      for (int u = 0; u < kMidUnroll; ++u) nxt[u] = load_pair_row(jc0 + jj + (kMidUnroll + u) * JSTEP);
-#pragma unroll
-      for (int u = 0; u < kMidUnroll; ++u) mfma_pair_row(cur[u], jj + u * JSTEP);
-#pragma unroll
-      for (int u = 0; u < kMidUnroll; ++u) cur[u] = nxt[u];
-    }
-#pragma unroll
-    for (int u = 0; u < kMidUnroll; ++u)
-      if (jj + u * JSTEP < jn) mfma_pair_row(cur[u], jj + u * JSTEP);
-  }
-  if constexpr (MODE == 1) {
-    // partial tiles of wavefronts 1..3 -> LDS, summed by wavefront 0 in a fixed order
-    __syncthreads();                                           // factor operands no longer needed
-    float* red = reinterpret_cast<float*>(sF);                 // [wave - 1][t][r][lane]
-    if (wave > 0) {
-#pragma unroll
-      for (int t = 0; t < 2 * VEC; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) red[(((wave - 1) * 2 * VEC + t) * 16 + r) * 64 + lane] = acc[0][t][r];
-    }
-    __syncthreads();
-    if (wave > 0) return;
-#pragma unroll 1
-    for (int w = 0; w < 3; ++w)
-#pragma unroll
-      for (int t = 0; t < 2 * VEC; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[0][t][r] += red[((w * 2 * VEC + t) * 16 + r) * 64 + lane];
-  }
-  if (!valid) return;
-  float* op = out + ((a * M) * B + bv * VEC) * 2;
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int m = mbase + 32 * (my_tile0 + mt) + d_row(r, half);
-      if (m < M) {
-        float* o = op + (int64_t)m * row_stride;
-        if constexpr (VEC == 1) {
-          *reinterpret_cast<float2*>(o) = make_float2(acc[mt][0][r], acc[mt][1][r]);
-        } else {
-          *reinterpret_cast<float4*>(o) = make_float4(acc[mt][0][r], acc[mt][1][r], acc[mt][2][r], acc[mt][3][r]);
-        }
-      }
-    }
-}
-
-// -------------------------------------------------------------------------------------------
-// k_core: the three steps around the Tucker core in one kernel, for mode 1 (the slowest index):
-//   g_L[m, b] = sum_k conj(U[k, m]) x[k, b]            last compression stage (K = I_1, M = r_1 <= 32)
-//   N_L = AdamUpdate(g_L)                               appendix algorithm "Adam with low-rank tensor
-//                                                       decomposition" (moments updated in place)
-//   z[i, b]   = sum_m U[i, m] N_L[m, b]                 first reconstruction stage
-// so the core gradient and the core update never travel through memory between kernels (g_L is
-// still written out: it is part of the readable state).
-// A workgroup of 4 wavefronts owns 32 column vectors (VEC complex each).  Compression is split over
-// the wavefronts by row pairs (wavefront w takes pairs w, w + 4, ...) and summed through LDS in a
-// fixed order; every wavefront runs AdamUpdate on a quarter of the 32 x 32 VEC tile and hands its
-// part of N_L back through LDS; then wavefront w expands the output row tiles w, w + 4, ...  The accumulator registers of the
-// compression ARE the B operands of the expansion: register r of lane (col, half) holds row
-// m = d_row(r, half), so expansion step r pairs rows d_row(r, 0) and d_row(r, 1) and its factor
-// operand is U[i, d_row(r, half)].
-// `z` may be `x` (in place): a workgroup writes only the columns it alone has read, and its reads
-// are complete (workgroup barriers in between) before its first write.
-struct CoreAdam {
-  float2* m;            // first moments, (M, B) complex
-  float* v;             // second moments
-  float2* g_out;        // compressed gradient, written for the state accessors
-  float beta1, beta2, inv_c1, inv_c2, eps;
-};
-
-template <int VEC>
-__global__ __launch_bounds__(kMidThreads) void k_core(const float* x, const float2* __restrict__ U,
-                                                      int rn, int K, int M, int64_t B, CoreAdam ad,
-                                                      float* z) {
-  typedef typename VecT<VEC>::type V;
-  constexpr int NT = 2 * VEC;                   // accumulator tiles: (column of the vector, re / im)
-  extern __shared__ float2 sF[];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int col = lane & 31, half = lane >> 5;
-  const int64_t BV = B / VEC;
-  const int64_t cv_raw = (int64_t)blockIdx.x * 32 + col;
-  const bool valid = cv_raw < BV;
-  const int64_t cv = valid ? cv_raw : BV - 1;
-  const int64_t row_stride = B * 2;
-  const float* xp = x + cv * VEC * 2;
-  const int J = (K + 1) >> 1;                   // row pairs of the compression
-  const int NTI = (K + 31) >> 5;                // output row tiles of the expansion
-  // LDS: [0, J*64) compression operands, reused afterwards for the reduction / hand-over buffer;
-  //      then 16 * NTI * 64 expansion operands
-  float2* sFp = sF;
-  const int red_f2 = 4 * NT * 16 * 64 / 2;                       // float2 slots of the reduction buffer
-  float2* sFe = sF + (J * 64 > red_f2 ? J * 64 : red_f2);
-  stage_batched(sFp, J * 64, tid, kMidThreads, [&](int e) -> float2 {
-    const int l = e & 63, jj = e >> 6;
-    const int m = l & 31, k = 2 * jj + (l >> 5);
-    const bool in = m < M && k < K;
-    const float2 u = U[in ? (int64_t)k * rn + m : 0];
-    return in ? make_float2(u.x, -u.y) : make_float2(0.f, 0.f);
-  });
-  stage_batched(sFe, 16 * NTI * 64, tid, kMidThreads, [&](int e) -> float2 {
-    const int l = e & 63, mt = (e >> 6) % NTI, r = e / (64 * NTI);
-    const int i = 32 * mt + (l & 31), m = d_row(r, l >> 5);
-    const bool in = i < K && m < M;
-    const float2 u = U[in ? (int64_t)i * rn + m : 0];
-    return in ? u : make_float2(0.f, 0.f);
-  });
-  __syncthreads();
-
-  v16f acc[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-  auto load_pair_row = [&](int j) -> V {
-    const int k = 2 * j + half;
-    return *reinterpret_cast<const V*>(xp + (int64_t)(k < K ? k : K - 1) * row_stride);
-  };
-  auto mfma_pair_row = [&](const V& v, int jj) {
-    float xs[NT], xj[NT];
-    if constexpr (VEC == 1) {
-      xs[0] = v.x; xs[1] = v.y;
-    } else {
-      xs[0] = v.x; xs[1] = v.y; xs[2] = v.z; xs[3] = v.w;
-    }
-#pragma unroll
-    for (int c = 0; c < VEC; ++c) {
-      xj[2 * c] = -xs[2 * c + 1];
-      xj[2 * c + 1] = xs[2 * c];
-    }
-    const float2 f = sFp[jj * 64 + lane];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      acc[t] = mfma32(f.x, xs[t], acc[t]);
-      acc[t] = mfma32(f.y, xj[t], acc[t]);
-    }
-  };
-  {
-    constexpr int kAhead = 16;                                 // row pairs in flight: all of them for K <= 128
-    int jj = wave;
-    for (; jj + (kAhead - 1) * 4 < J; jj += kAhead * 4) {
-      V v[kAhead];
-#pragma unroll
-      for (int u = 0; u < kAhead; ++u) v[u] = load_pair_row(jj + u * 4);
-#pragma unroll
-      for (int u = 0; u < kAhead; ++u) mfma_pair_row(v[u], jj + u * 4);
-    }
-    for (; jj < J; jj += 4) mfma_pair_row(load_pair_row(jj), jj);
-  }
-  // ---- all partial tiles -> LDS; wavefront w then owns registers r = 4 w .. 4 w + 3 of the tile: it
-  //      sums the four partials in a fixed order (wavefront 0's first), runs AdamUpdate on those
-  //      core rows and hands N_L back through LDS ----
-  __syncthreads();                                             // compression operands no longer needed
-  float* red = reinterpret_cast<float*>(sF);                   // [wave][t][r][lane]
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) red[((wave * NT + t) * 16 + r) * 64 + lane] = acc[t][r];
-  __syncthreads();
-  float2 nn[4][VEC];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int r = 4 * wave + q;
-    const int m = d_row(r, half);
-#pragma unroll
-    for (int c = 0; c < VEC; ++c) {
-      float gre = 0.f, gim = 0.f;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        gre += red[((w * NT + 2 * c) * 16 + r) * 64 + lane];
-        gim += red[((w * NT + 2 * c + 1) * 16 + r) * 64 + lane];
-      }
-      nn[q][c] = make_float2(0.f, 0.f);
-      if (valid && m < M) {
-        const int64_t idx = (int64_t)m * B + cv * VEC + c;
-        float2 mm = ad.m[idx];
-        mm.x = ad.beta1 * mm.x + (1.f - ad.beta1) * gre;
-        mm.y = ad.beta1 * mm.y + (1.f - ad.beta1) * gim;
-        const float vv = ad.beta2 * ad.v[idx] + (1.f - ad.beta2) * (gre * gre + gim * gim);
-        ad.m[idx] = mm;
-        ad.v[idx] = vv;
-        ad.g_out[idx] = make_float2(gre, gim);
-        const float d = 1.f / (sqrtf(vv * ad.inv_c2) + ad.eps);
-        nn[q][c] = make_float2(mm.x * ad.inv_c1 * d, mm.y * ad.inv_c1 * d);
-      }
-    }
-  }
-  __syncthreads();                                             // every partial has been read
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int c = 0; c < VEC; ++c) {
-      red[((2 * c) * 16 + 4 * wave + q) * 64 + lane] = nn[q][c].x;
-      red[((2 * c + 1) * 16 + 4 * wave + q) * 64 + lane] = nn[q][c].y;
-    }
-  __syncthreads();
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[t][r] = red[(t * 16 + r) * 64 + lane];
-  // ---- expansion: wavefront w writes output row tiles w, w + 4, ... ----
-  float* op = z + cv * VEC * 2;
-  for (int mt = wave; mt < NTI; mt += 4) {
-    v16f out[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) out[t][r] = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float2 f = sFe[(r * NTI + mt) * 64 + lane];
-#pragma unroll
-      for (int c = 0; c < VEC; ++c) {
-        const float nr = acc[2 * c][r], ni = acc[2 * c + 1][r];
-        out[2 * c] = mfma32(f.x, nr, out[2 * c]);
-        out[2 * c] = mfma32(f.y, -ni, out[2 * c]);
-        out[2 * c + 1] = mfma32(f.x, ni, out[2 * c + 1]);
-        out[2 * c + 1] = mfma32(f.y, nr, out[2 * c + 1]);
-      }
-    }
-    if (valid) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = 32 * mt + d_row(r, half);
-        if (i < K) {
-          float* o = op + (int64_t)i * row_stride;
-          if constexpr (VEC == 1) {
-            *reinterpret_cast<float2*>(o) = make_float2(out[0][r], out[1][r]);
-          } else {
-            *reinterpret_cast<float4*>(o) = make_float4(out[0][r], out[1][r], out[2][r], out[3][r]);
-          }
-        }
-      }
-    }
-  }
-}
-
-// -------------------------------------------------------------------------------------------
-// k_core2: everything between the fused first projection and the fused update when exactly two
-// modes (the two leading ones) are left to compress: y is (I0 = 128, I1, Cc), its Cc complex
-// columns contiguous.  Every column c goes through
-//   g_L[m0, m1, c] = sum_{i0, i1} conj(U0[i0, m0]) conj(U1[i1, m1]) y[i0, i1, c]   last two compression stages
-//   N_L            = AdamUpdate(g_L)                (appendix algorithm "Adam with low-rank tensor decomposition")
-//   z[i0, i1, c]   = sum_{m0, m1} U0[i0, m0] U1[i1, m1] N_L[m0, m1, c]             first two reconstruction stages
-// on its own, so a workgroup that owns VEC = 2 neighbouring columns (16 bytes per (i0, i1); VEC = 1, 8 bytes,
-// where two per workgroup would leave most of the chip without work) runs the whole
-// chain between workgroup barriers: nothing travels through memory between the five steps and the
-// launches, prologues and tails of three kernels become one.  Wavefront w owns the rows
-// i0 = 32 w .. 32 w + 31.  The accumulator layout of one stage is the operand layout of the next
-// (register r of lane (col, half) holds row d_row(r, half) of the tile, and a matrix-core step pairs
-// exactly the rows d_row(r, 0) and d_row(r, 1)), so no stage transposes anything:
-//   1  T[i0, m1]   = sum_i1 y[i0, i1] conj(U1[i1, m1])   data = A operand (lane = i0), U1 from LDS;  D: i0 in registers, m1 in lanes
-//   2  P[m0, m1]   = sum_i0 conj(U0[i0, m0]) T[i0, m1]   U0 = A operand, T = B operand straight from the accumulators;
-//                                                        the four wavefronts' partial sums meet in LDS, fixed order
-//   -  AdamUpdate on the 32 x 32 x VEC core entries of the workgroup's columns, N_L back into LDS in accumulator layout
-//   3  R[m1, i0]   = sum_m0 N_L[m0, m1] U0[i0, m0]       N_L = A operand (LDS), U0 = B operand;  D: m1 in registers, i0 in lanes
-//   4  z[i0, i1]   = sum_m1 R[m1, i0] U1[i1, m1]         R = A operand straight from the accumulators, U1 from LDS;
-//                                                        D: i0 in registers, i1 in lanes
-// The factor operands of all four stages come from a table in operand order that is built once per
-// refresh (k_pack_core2): the prologue is a straight copy with every load in flight at once.
-// The result is written one column group at a time, z[group][i0][i1] in units of VEC complex, because in
-// stage 4 neighbouring lanes hold neighbouring i1: the stores of a wavefront are then 512 (256)
-// contiguous bytes instead of 64 pieces each in a cache line of its own (the fused update reads its
-// operand rows through strides, see FusedPrev).  Workgroups that share cache lines of y (8 column
-// pairs per 128 bytes) get consecutive blockIdx / 8, i.e. the same XCD under round-robin dispatch.
-struct Core2Args {
-  const float* y;       // (128, I1, Cc) complex
-  float* z;             // (Cc / G, 128, I1) units of G complex, not the same buffer; G = `zgroup` (2: Cc even)
-  const float2* tab;    // core2_table_elems(I1) operands from k_pack_core2
-  int I1, M0, M1;
-  int64_t Cc;           // a multiple of VEC
-  int zgroup;           // columns per unit of z: VEC, or 2 with VEC = 1 (two workgroups then fill a unit)
-};
-constexpr int kCore2Rows = 128;              // extent of the first mode: 4 wavefronts x 32 rows
-constexpr int kCore2Batch = 8;               // row pairs of y per lane in flight (twice that while a batch is computed)
-
-// Operand table: [J1][64] stage 1, [NT1][16][64] stage 4, [4][16][64] stage 2, [4][16][64] stage 3 (float2 each);
-// J1 = row pairs of mode 2, NT1 = 32-row tiles of mode 2.
-__host__ __device__ inline int core2_table_elems(int I1) { return ((I1 + 1) / 2) * 64 + ((I1 + 31) / 32) * 1024 + 8192; }
-
-__global__ void k_pack_core2(const float2* __restrict__ U0, int rn0, int M0, const float2* __restrict__ U1,
-                             int rn1, int M1, int I1, float2* __restrict__ tab) {
-  const int J1 = (I1 + 1) >> 1, NT1 = (I1 + 31) >> 5;
-  const int n1 = J1 * 64, n4 = NT1 * 1024;
-  const int e = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (e >= n1 + n4 + 8192) return;
-  const int l = e & 63, col = l & 31, half = l >> 5;
-  float2 u = make_float2(0.f, 0.f);
-  if (e < n1) {                                    // stage 1: U1[2 j + half][col]
-    const int i1 = 2 * (e >> 6) + half;
-    if (i1 < I1 && col < M1) u = U1[(int64_t)i1 * rn1 + col];
-  } else if (e < n1 + n4) {                        // stage 4: U1[32 tile + col][d_row(r, half)]
-    const int q = (e - n1) >> 6, r = q & 15, tile = q >> 4;
-    const int i1 = 32 * tile + col, m1 = d_row(r, half);
-    if (i1 < I1 && m1 < M1) u = U1[(int64_t)i1 * rn1 + m1];
-  } else if (e < n1 + n4 + 4096) {                 // stage 2: U0[32 w + d_row(r, half)][col]
-    const int q = (e - n1 - n4) >> 6, r = q & 15, w = q >> 4;
-    if (col < M0) u = U0[(int64_t)(32 * w + d_row(r, half)) * rn0 + col];
-  } else {                                         // stage 3: U0[32 w + col][d_row(r, half)]
-    const int q = (e - n1 - n4 - 4096) >> 6, r = q & 15, w = q >> 4;
-    const int m0 = d_row(r, half);
-    if (m0 < M0) u = U0[(int64_t)(32 * w + col) * rn0 + m0];
-  }
-  tab[e] = u;
-}
-
-template <int VEC>
-__global__ __launch_bounds__(kMidThreads) void k_core2(Core2Args a, CoreAdam ad) {
-  typedef typename VecT<VEC>::type V;             // the workgroup's VEC columns of one (i0, i1): 8 or 16 bytes
-  constexpr int NT = 2 * VEC;                     // accumulator tiles: (column, re / im)
-  extern __shared__ float2 sF[];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int col = lane & 31, half = lane >> 5;
-  const int planes = (int)(a.Cc / VEC);
-  const int b = (int)blockIdx.x;
-  const int plane = (planes & 7) == 0 ? (b & 7) * (planes >> 3) + (b >> 3) : b;
-  const int I1 = a.I1, M0 = a.M0, M1 = a.M1;
-  const int J1 = (I1 + 1) >> 1, NT1 = (I1 + 31) >> 5;
-  const int64_t row = a.Cc * 2;              // floats between consecutive i1 of y
-  const int64_t slab = row * I1;             // floats between consecutive i0 of y
-  // LDS: [0, 64 KB) stage-1 operands (J1 x 64 float2), afterwards the partial sums of stage 2
-  //      ([wave][t][r][lane] floats) and then N_L ([t][r][lane]); [64 KB, 64 KB + NT1 x 8 KB) stage-4 operands
-  float2* sT1 = sF;
-  float* red = reinterpret_cast<float*>(sF);
-  float2* sT4 = sF + 8192;
-
-  // the first rows of y go in flight, then the stage-1 operands
-  const float* xp = a.y + (int64_t)(32 * wave + col) * slab + NT * plane;
-  auto load_pair_row = [&](int j) -> V {
-    const int jc = j < J1 ? j : J1 - 1;
-    const int k = 2 * jc + half;
-    return *reinterpret_cast<const V*>(xp + (int64_t)(k < I1 ? k : I1 - 1) * row);
-  };
-  auto parts = [](const V& v, float* x) {        // x[2 c] = re, x[2 c + 1] = im of column c
-    if constexpr (VEC == 1) {
-      x[0] = v.x; x[1] = v.y;
-    } else {
-      x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-    }
-  };
-  V cur[kCore2Batch];
-#pragma unroll
-  for (int u = 0; u < kCore2Batch; ++u) cur[u] = load_pair_row(u);
-  {
-    // stage-1 operands -> LDS: 16-byte pieces, 8 per thread (the table holds a multiple of 64 float2)
-    const float4* t1 = reinterpret_cast<const float4*>(a.tab);
-    float4* d1 = reinterpret_cast<float4*>(sT1);
-    const int n1 = J1 * 32;
-    float4 p1[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = tid + u * kMidThreads;
-      p1[u] = t1[e < n1 ? e : 0];
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = tid + u * kMidThreads;
-      if (e < n1) d1[e] = p1[u];
-    }
-  }
-  __syncthreads();
-  // What the later stages need travels while stage 1 runs: U0 as the operands of stages 2 and 3
-  // (registers) and the moments of this thread's core entries: rows d_row(4 wave + q, half), column col,
-  // the workgroup's VEC columns.  (The stage-4 operands travel during stage 2.)
-  float2 f2[16], f3[16];
-  {
-    const float2* t2 = a.tab + J1 * 64 + NT1 * 1024 + wave * 1024 + lane;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      f2[r] = t2[r * 64];
-      f3[r] = t2[4096 + r * 64];
-    }
-  }
-  float2 mm[4][VEC];
-  float vv[4][VEC];
-  int64_t cidx[4];
-  bool live[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int m0 = d_row(4 * wave + q, half);
-    live[q] = m0 < M0 && col < M1;
-    cidx[q] = live[q] ? ((int64_t)m0 * M1 + col) * a.Cc + VEC * plane : 0;
-#pragma unroll
-    for (int c = 0; c < VEC; ++c) {
-      mm[q][c] = ad.m[cidx[q] + c];
-      vv[q][c] = ad.v[cidx[q] + c];
-    }
-  }
-
-  // ---- stage 1: T = y conj(U1); tiles (column, re / im) ----
-  v16f t[NT];
-#pragma unroll
-  for (int i = 0; i < NT; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) t[i][r] = 0.f;
-  auto stage1 = [&](const V& v, int j) {
-    const float2 f = sT1[j * 64 + lane];
-    const float nfy = -f.y;
-    float x[NT];
-    parts(v, x);
-#pragma unroll
-    for (int i = 0; i < NT; ++i) t[i] = mfma32(x[i], f.x, t[i]);      // re: yr ur + yi ui;  im: yi ur - yr ui
-#pragma unroll
-    for (int c = 0; c < VEC; ++c) {
-      t[2 * c] = mfma32(x[2 * c + 1], f.y, t[2 * c]);
-      t[2 * c + 1] = mfma32(x[2 * c], nfy, t[2 * c + 1]);
-    }
-  };
-  {
-    int j = 0;
-    for (; j + kCore2Batch <= J1; j += kCore2Batch) {
-      V nxt[kCore2Batch];
-#pragma unroll
-      for (int u = 0; u < kCore2Batch; ++u) nxt[u] = load_pair_row(j + kCore2Batch + u);
-      __builtin_amdgcn_sched_barrier(0);                       // the loads stay in front of the batch they overlap
-#pragma unroll
-      for (int u = 0; u < kCore2Batch; ++u) stage1(cur[u], j + u);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int u = 0; u < kCore2Batch; ++u) cur[u] = nxt[u];
-    }
-#pragma unroll
-    for (int u = 0; u < kCore2Batch; ++u)
-      if (j + u < J1) stage1(cur[u], j + u);
-  }
-  // ---- stage 2: this wavefront's part of P = conj(U0)^T T over its 32 rows; the stage-4 operands go in flight ----
-  const int n4 = NT1 * 512;
-  float4 p4[8];
-  {
-    const float4* t4 = reinterpret_cast<const float4*>(a.tab + J1 * 64);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = tid + u * kMidThreads;
-      p4[u] = t4[e < n4 ? e : 0];
-    }
-  }
-  v16f p[NT];
-#pragma unroll
-  for (int i = 0; i < NT; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) p[i][r] = 0.f;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const float2 f = f2[r];
-    const float nfy = -f.y;
-#pragma unroll
-    for (int i = 0; i < NT; ++i) p[i] = mfma32(f.x, t[i][r], p[i]);    // re: ur tr + ui ti;  im: ur ti - ui tr
-#pragma unroll
-    for (int c = 0; c < VEC; ++c) {
-      p[2 * c] = mfma32(f.y, t[2 * c + 1][r], p[2 * c]);
-      p[2 * c + 1] = mfma32(nfy, t[2 * c][r], p[2 * c + 1]);
-    }
-  }
-  {
-    float4* d4 = reinterpret_cast<float4*>(sT4);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = tid + u * kMidThreads;
-      if (e < n4) d4[e] = p4[u];
-    }
-  }
-  __syncthreads();                                             // every wavefront is through with the stage-1 operands
-#pragma unroll
-  for (int i = 0; i < NT; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) red[((wave * NT + i) * 16 + r) * 64 + lane] = p[i][r];
-  __syncthreads();
-  // ---- AdamUpdate: wavefront w takes registers 4 w .. 4 w + 3 of the tile, partial sums added in wavefront order ----
-  float nn[4][NT];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int r = 4 * wave + q;
-    float g[NT];
-#pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      g[i] = 0.f;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) g[i] += red[((w * NT + i) * 16 + r) * 64 + lane];
-    }
-#pragma unroll
-    for (int c = 0; c < VEC; ++c) {
-      float2 m = mm[q][c];
-      m.x = ad.beta1 * m.x + (1.f - ad.beta1) * g[2 * c];
-      m.y = ad.beta1 * m.y + (1.f - ad.beta1) * g[2 * c + 1];
-      const float v = ad.beta2 * vv[q][c] + (1.f - ad.beta2) * (g[2 * c] * g[2 * c] + g[2 * c + 1] * g[2 * c + 1]);
-      const float d = 1.f / (sqrtf(v * ad.inv_c2) + ad.eps);
-      nn[q][2 * c] = nn[q][2 * c + 1] = 0.f;
-      if (live[q]) {
-        ad.m[cidx[q] + c] = m;
-        ad.v[cidx[q] + c] = v;
-        ad.g_out[cidx[q] + c] = make_float2(g[2 * c], g[2 * c + 1]);
-        nn[q][2 * c] = m.x * ad.inv_c1 * d;
-        nn[q][2 * c + 1] = m.y * ad.inv_c1 * d;
-      }
-    }
-  }
-  __syncthreads();                                             // every partial sum has been read
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int i = 0; i < NT; ++i) red[(i * 16 + 4 * wave + q) * 64 + lane] = nn[q][i];
-  __syncthreads();
-  // ---- stage 3: R = N_L^T U0^T for this wavefront's 32 rows i0 ----
-  v16f rr[NT];
-#pragma unroll
-  for (int i = 0; i < NT; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) rr[i][r] = 0.f;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const float2 f = f3[r];
-    const float nfy = -f.y;
-    float n[NT];
-#pragma unroll
-    for (int i = 0; i < NT; ++i) n[i] = red[(i * 16 + r) * 64 + lane];
-#pragma unroll
-    for (int i = 0; i < NT; ++i) rr[i] = mfma32(n[i], f.x, rr[i]);     // re: nr ur - ni ui;  im: ni ur + nr ui
-#pragma unroll
-    for (int c = 0; c < VEC; ++c) {
-      rr[2 * c] = mfma32(n[2 * c + 1], nfy, rr[2 * c]);
-      rr[2 * c + 1] = mfma32(n[2 * c], f.y, rr[2 * c + 1]);
-    }
-  }
-  // ---- stage 4: z = R^T U1^T, one tile of 32 columns i1 at a time; z[group][i0][i1], units of zgroup complex ----
-  const int ZU = 2 * a.zgroup;                                 // floats per unit
-  const int zg = VEC == 1 && a.zgroup == 2 ? plane >> 1 : plane;
-  float* zp = a.z + (((int64_t)zg * kCore2Rows + 32 * wave + 4 * half) * I1 + col) * ZU +
-              (VEC == 1 && a.zgroup == 2 ? 2 * (plane & 1) : 0);
-  for (int tile = 0; tile < NT1; ++tile) {
-    v16f z[NT];
-#pragma unroll
-    for (int i = 0; i < NT; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) z[i][r] = 0.f;
-    const float2* ft = sT4 + tile * 16 * 64 + lane;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float2 f = ft[r * 64];
-      const float nfy = -f.y;
-#pragma unroll
-      for (int c = 0; c < VEC; ++c) {                          // re: rr ur - ri ui;  im: rr ui + ri ur
-        z[2 * c] = mfma32(rr[2 * c][r], f.x, z[2 * c]);
-        z[2 * c + 1] = mfma32(rr[2 * c][r], f.y, z[2 * c + 1]);
-      }
-#pragma unroll
-      for (int c = 0; c < VEC; ++c) {
-        z[2 * c] = mfma32(rr[2 * c + 1][r], nfy, z[2 * c]);
-        z[2 * c + 1] = mfma32(rr[2 * c + 1][r], f.x, z[2 * c + 1]);
-      }
-    }
-    if (32 * tile + col < I1) {
-      float* zt = zp + 32 * tile * ZU;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float* o = zt + (int64_t)((r & 3) + 8 * (r >> 2)) * I1 * ZU;
-        if constexpr (VEC == 1) {
-          *reinterpret_cast<float2*>(o) = make_float2(z[0][r], z[1][r]);
-        } else {
-          *reinterpret_cast<float4*>(o) = make_float4(z[0][r], z[1][r], z[2][r], z[3][r]);
-        }
-      }
-    }
-  }
 }
 
 // -------------------------------------------------------------------------------------------
@@ -1807,14 +1105,10 @@ __global__ __launch_bounds__(64 * W, 2) void k_lupdate(const float* __restrict__
 //             of row i2, so step (u, part) pairs elements k(u, 0) and k(u, 1) and the coefficient
 //             table is read at those rows.  Everything after that is k_lupdate.
 struct FusedPrev {
-  const float2* y1;     // input of the fused stage: element (slab, m2, m3) of the (slabs, K2, K) complex tensor lies at
-                        // y1[slab * s_slab + m2 * s_m2 + (m3 / 2) * s_pair + (m3 & 1) * s_odd]
+  const float2* y1;     // input of the fused stage, (slabs, K2, K) complex
   const float2* ut;     // U^(N-1)[i2, m2], zero for m2 >= K2, in operand order (k_pack_fused_factor)
   int S;                // tiles per slab
   int K2;               // rank of mode N-1
-  int64_t s_slab, s_m2, s_pair, s_odd;   // row-major: K2 K, K, 2, 1; one column pair at a time (k_core2<2>):
-                                         // 2, (K / 2) slabs 2, slabs 2, 1; one column at a time (k_core2<1>):
-                                         // 1, K slabs, 2 slabs, slabs
 };
 
 template <int WDT, int W, int MS, int JT2, int UP>
@@ -1869,17 +1163,9 @@ __global__ __launch_bounds__(64 * W, 2) void k_lupdate_fused(const float2* __res
   const int64_t Iw = A * M;
   const int tile_w = kTileRows * M;
   const int S = fz.S;
-  const int I2 = 32 * S;
   const int64_t nslabs = ntiles / S;                           // A = slabs * 32 S exactly
   const int64_t nw = (int64_t)gridDim.x * W;
   int64_t slab = (int64_t)blockIdx.x * W + wave;
-  if (W == 4 && fz.s_slab == 2 && (gridDim.x & 15) == 0) {
-    // One column pair at a time, a 128-byte line of the operand tensor holds 8 consecutive slabs: the two
-    // workgroups that share it are given block indices 8 apart, i.e. the same XCD under round-robin
-    // dispatch, so that one L2 fetches the line for both (otherwise two do: 1.03 x the kernel's traffic).
-    const int64_t b = blockIdx.x;
-    slab = 8 * (8 * (b >> 4) + (b & 7)) + 4 * ((b >> 3) & 1) + wave;
-  }
   int ts = 0;
   if (slab >= nslabs) return;
   auto advance = [&](int64_t& sl, int& t) {
@@ -1928,18 +1214,17 @@ __global__ __launch_bounds__(64 * W, 2) void k_lupdate_fused(const float2* __res
   claim_sparse();
   // Stage-A operand rows (the slab's Y1) stay in registers for all S tiles of a slab.  Those of the NEXT slab
   // are requested right after stage A of a slab's last tile, when the registers have just been used
-  // for the last time: they then have a whole stage B and W phase to arrive, however the tensor is laid
-  // out (one column pair at a time, a lane's 16 loads touch 16 cache lines each).  Unconditional
+  // for the last time: they then have a whole stage B and W phase to arrive.  Unconditional
   // loads with clamped indices: clamped rows / columns meet zero coefficients.
   float2 y1[JT2];
   auto fetch_y1 = [&](int64_t sl, int ln) {
     const int c2 = ln & 31, h2 = ln >> 5;
     const int m3 = (c2 >> 1) < K ? (c2 >> 1) : K - 1;
-    const float2* yp = fz.y1 + sl * fz.s_slab + (int64_t)(m3 >> 1) * fz.s_pair + (int64_t)(m3 & 1) * fz.s_odd;
+    const float2* yp = fz.y1 + sl * fz.K2 * K + m3;
 #pragma unroll
     for (int jj = 0; jj < JT2; ++jj) {
       const int m2 = 2 * jj + h2;
-      y1[jj] = yp[(int64_t)(m2 < fz.K2 ? m2 : fz.K2 - 1) * fz.s_m2];
+      y1[jj] = yp[(m2 < fz.K2 ? m2 : fz.K2 - 1) * K];
     }
   };
   fetch_y1(slab, lane);
@@ -2158,46 +1443,6 @@ inline uint32_t magic_for(int d) {
   return d <= 1 ? 0u : (uint32_t)((0x100000000ull + (uint64_t)d - 1) / (uint64_t)d);
 }
 
-constexpr size_t kLdsLimit = 160 * 1024;
-
-template <typename Kern>
-bool allow_lds(Kern kern, size_t bytes) {
-  if (bytes <= 48 * 1024) return true;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)bytes) == hipSuccess;
-}
-
-// Workgroups of `kern` that are resident on one compute unit at a time (registers, LDS), asked of
-// the runtime once per kernel and LDS size.  The tile loops are persistent (stride = grid size), so
-// the grid is exactly one resident set: more workgroups would run as a ragged second round.
-template <typename Kern>
-int resident_blocks(Kern kern, int threads, size_t lds) {
-  static std::mutex mu;
-  static std::map<std::pair<const void*, size_t>, int> cache;
-  const std::pair<const void*, size_t> key(reinterpret_cast<const void*>(kern), lds);
-  std::lock_guard<std::mutex> lock(mu);
-  auto it = cache.find(key);
-  if (it != cache.end()) return it->second;
-  int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, threads, lds) != hipSuccess || nb < 1) nb = 1;
-  if (nb > 4) nb = 4;
-  cache[key] = nb;
-  return nb;
-}
-
-// Compute units of the current device (256 on an MI355X), asked of the runtime once per device.
-int compute_units() {
-  constexpr int kMaxDev = 64;
-  static std::atomic<int> cached[kMaxDev];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDev) dev = 0;
-  int n = cached[dev].load(std::memory_order_relaxed);
-  if (n > 0) return n;
-  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) n = 256;
-  cached[dev].store(n, std::memory_order_relaxed);
-  return n;
-}
-
 int grid_for_tiles(int64_t ntiles, int blocks_per_cu) {
   const int64_t cap = (int64_t)compute_units() * blocks_per_cu;
   return (int)(ntiles < cap ? ntiles : cap);
@@ -2265,128 +1510,6 @@ void launch_tile_offsets(hipStream_t s, const int32_t* omega, int64_t k, int64_t
   const int64_t n = ntiles + 1;
   k_tile_offsets<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(omega, k, tile_elems, ntiles,
                                                                         tile_start);
-}
-
-void launch_mid(hipStream_t s, const float2* x, const float2* U, int rn, bool project, const Stage& st,
-                float2* out) {
-  const int64_t A = st.A, B = st.B;
-  const int K = st.K, M = st.M;
-  if (A * M * B <= 0) return;
-  const int vec = (B % 2 == 0) ? 2 : 1;
-  const int64_t ncv = A * (B / vec);
-  const int J = (K + 1) / 2;
-  const int jn = J < kMidJChunk ? J : kMidJChunk;
-  // Fewer workgroups than compute units: share 32 columns between the 4 wavefronts of a workgroup
-  // (MODE 1 / 2) so that the stage still spreads over the chip; otherwise every wavefront owns 32
-  // columns (MODE 0; measured faster as soon as it yields at least one workgroup per compute unit).
-  const int mt0 = M > 32 ? 2 : 1;
-  const int64_t wgs0 = ((ncv + 127) / 128) * ((M + 32 * mt0 - 1) / (32 * mt0));
-  int mode = 0;
-  if (wgs0 < compute_units()) mode = M > 32 ? 2 : 1;
-  const int mt = mode == 0 ? mt0 : 1;
-  const int tl = mode == 2 ? 4 : mt;
-  const int64_t gx = mode == 0 ? (ncv + 127) / 128 : (ncv + 31) / 32;
-  const int gy = (M + 32 * tl - 1) / (32 * tl);
-  size_t lds = (size_t)jn * tl * 64 * 8;
-  if (mode == 1) {
-    const size_t red = (size_t)3 * 2 * vec * 16 * 64 * 4;
-    if (red > lds) lds = red;
-  }
-  dim3 grid((unsigned)gx, (unsigned)gy), block(kMidThreads);
-  const float* xf = reinterpret_cast<const float*>(x);
-  float* of = reinterpret_cast<float*>(out);
-#define TGRAD_MID(MT_, VEC_, P_, MODE_)                                                   \
-  do {                                                                                    \
-    allow_lds(k_mid<MT_, VEC_, P_, MODE_>, lds);                                          \
-    k_mid<MT_, VEC_, P_, MODE_><<<grid, block, lds, s>>>(xf, U, rn, A, K, M, B, of);      \
-  } while (0)
-#define TGRAD_MID_P(MT_, VEC_, MODE_)                                                     \
-  do {                                                                                    \
-    if (project) TGRAD_MID(MT_, VEC_, true, MODE_); else TGRAD_MID(MT_, VEC_, false, MODE_); \
-  } while (0)
-  if (mode == 0) {
-    if (mt == 1) { if (vec == 2) TGRAD_MID_P(1, 2, 0); else TGRAD_MID_P(1, 1, 0); }
-    else         { if (vec == 2) TGRAD_MID_P(2, 2, 0); else TGRAD_MID_P(2, 1, 0); }
-  } else if (mode == 1) {
-    if (vec == 2) TGRAD_MID_P(1, 2, 1); else TGRAD_MID_P(1, 1, 1);
-  } else {
-    if (vec == 2) TGRAD_MID_P(1, 2, 2); else TGRAD_MID_P(1, 1, 2);
-  }
-#undef TGRAD_MID_P
-#undef TGRAD_MID
-}
-
-// Limits of k_core: one 32-row tile of core rows, and LDS for both operand tables.
-bool core_kernel_fits(int K, int M) { return M >= 1 && M <= 32 && K >= 1 && K <= TGRAD_MAX_EXTENT; }
-
-// Last compression stage + AdamUpdate on the core + first reconstruction stage (mode 1: the tensor
-// before is (K, B), the tensor after is (K, B) again, the core in between (M, B)).
-void launch_core(hipStream_t s, const float2* x, const float2* U, int rn, int K, int M, int64_t B, float2* m,
-                 float* v, float2* g_out, float beta1, float beta2, float inv_c1, float inv_c2, float eps,
-                 float2* z) {
-  if (B <= 0) return;
-  const int vec = (B % 2 == 0) ? 2 : 1;
-  const int64_t BV = B / vec;
-  const int J = (K + 1) / 2, NTI = (K + 31) / 32;
-  const size_t red = (size_t)4 * 2 * vec * 16 * 64 / 2;
-  const size_t lds = (((size_t)J * 64 > red ? (size_t)J * 64 : red) + (size_t)16 * NTI * 64) * 8;
-  dim3 grid((unsigned)((BV + 31) / 32)), block(kMidThreads);
-  CoreAdam ad{m, v, g_out, beta1, beta2, inv_c1, inv_c2, eps};
-  const float* xf = reinterpret_cast<const float*>(x);
-  float* zf = reinterpret_cast<float*>(z);
-  if (vec == 2) {
-    allow_lds(k_core<2>, lds);
-    k_core<2><<<grid, block, lds, s>>>(xf, U, rn, K, M, B, ad, zf);
-  } else {
-    allow_lds(k_core<1>, lds);
-    k_core<1><<<grid, block, lds, s>>>(xf, U, rn, K, M, B, ad, zf);
-  }
-}
-
-// Limits of k_core2: first extent 128 (one 32-row tile per wavefront), ranks within one tile, the second
-// extent within four tiles, and enough column groups (one workgroup each) to occupy the chip: pairs of
-// columns if there are at least 192 pairs (3/4 of the 256 compute units of the MI355X; the rank of the
-// last mode must then be even: a pair lies inside one row of the mode before it), else single columns if
-// there are at least 96.  Below that the three separate kernels, which spread over the chip, are
-// faster.  Returns the columns per workgroup (2 or 1), or 0.  A function of the shape alone: the
-// workspace layout follows from it, and the size query must not depend on the device that is current.
-constexpr int64_t kCore2MinPairs = 192, kCore2MinColumns = 96;
-int core2_kernel_vec(int I0, int I1, int M0, int M1, int K2, int K) {
-  const int64_t Cc = (int64_t)K2 * K;
-  if (!(I0 == kCore2Rows && I1 >= 1 && I1 <= 128 && M0 >= 1 && M0 <= 32 && M1 >= 1 && M1 <= 32 &&
-        (int64_t)I0 * I1 * Cc < ((int64_t)1 << 28)))
-    return 0;
-  if (K % 2 == 0 && Cc / 2 >= kCore2MinPairs) return 2;
-  if (Cc >= kCore2MinColumns) return 1;
-  return 0;
-}
-
-size_t core2_table_bytes(int I1) { return (size_t)core2_table_elems(I1) * 8; }
-
-// The factors of the two leading modes in the operand order of k_core2's four stages (once per refresh).
-void launch_pack_core2(hipStream_t s, const float2* U0, int rn0, int M0, const float2* U1, int rn1, int M1, int I1,
-                       float2* tab) {
-  const int n = core2_table_elems(I1);
-  k_pack_core2<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(U0, rn0, M0, U1, rn1, M1, I1, tab);
-}
-
-// The two leading modes compressed, AdamUpdate on the core, the two leading modes reconstructed:
-// x (128, I1, Cc) -> z (Cc / zgroup, 128, I1) units of zgroup complex (zgroup = vec, or 2 with vec = 1 and Cc
-// even), the core (M0, M1, Cc) in between.
-void launch_core2(hipStream_t s, int vec, int zgroup, const float2* x, const float2* tab, int I1, int M0, int M1, int64_t Cc,
-                  float2* m, float* v, float2* g_out, float beta1, float beta2, float inv_c1, float inv_c2,
-                  float eps, float2* z) {
-  const int NT1 = (I1 + 31) / 32;
-  const size_t lds = (size_t)64 * 1024 + (size_t)NT1 * 16 * 64 * 8;
-  Core2Args a{reinterpret_cast<const float*>(x), reinterpret_cast<float*>(z), tab, I1, M0, M1, Cc, zgroup};
-  CoreAdam ad{m, v, g_out, beta1, beta2, inv_c1, inv_c2, eps};
-  if (vec == 2) {
-    allow_lds(k_core2<2>, lds);
-    k_core2<2><<<dim3((unsigned)(Cc / 2)), dim3(kMidThreads), lds, s>>>(a, ad);
-  } else {
-    allow_lds(k_core2<1>, lds);
-    k_core2<1><<<dim3((unsigned)Cc), dim3(kMidThreads), lds, s>>>(a, ad);
-  }
 }
 
 void launch_pack_fused_factor(hipStream_t s, const float2* U, int I2, int r, float2* fpad, float2* ut) {
@@ -2525,14 +1648,11 @@ void launch_lupdate(hipStream_t s, const float2* z, const float2* U, const Stage
 }
 
 // k_lupdate with the reconstruction stage of mode N-1 in front (see k_lupdate_fused): `y1` is the
-// tensor before that stage, (slabs, K2, K) complex (`group` = 0) - or the same tensor one column group at
-// a time: (K2 K / group, slabs) units of `group` = 1 or 2 neighbouring complex numbers (2: K even);
-// `ut` the transposed factor copy; I2 = 32 S.
+// tensor before that stage, (slabs, K2, K) complex; `ut` the transposed factor copy; I2 = 32 S.
 void launch_lupdate_fused(hipStream_t s, const float2* y1, const float2* ut, int I2, int K2, const float2* U,
                           const Stage& st, void* w, int wdtype, float decay, float c_alpha, const int32_t* omega,
                           const uint32_t* tile_start, int64_t k, const float2* gs, float2* ms, float* vs,
-                          float beta1, float beta2, float inv_c1, float inv_c2, float eps, float c_lambda,
-                          int group) {
+                          float beta1, float beta2, float inv_c1, float inv_c2, float eps, float c_lambda) {
   const int64_t A = st.A;
   const int K = st.K, M = st.M;
   if (A * M <= 0) return;
@@ -2546,17 +1666,7 @@ void launch_lupdate_fused(hipStream_t s, const float2* y1, const float2* ut, int
   dim3 grid(1), block(64 * W);
   SparseAdam sp{omega, tile_start, gs, ms, vs, beta1, beta2, inv_c1, inv_c2, eps, c_lambda,
                 (int)(k > 0 ? k - 1 : 0)};
-  FusedPrev fz{y1, ut, S, K2, (int64_t)K2 * K, (int64_t)K, 2, 1};
-  if (group == 2) {                              // (K2 K / 2, slabs) units of two complex: what k_core2<2> writes
-    fz.s_slab = 2;
-    fz.s_pair = nslabs * 2;
-    fz.s_m2 = (int64_t)(K / 2) * nslabs * 2;
-  } else if (group == 1) {                       // (K2 K, slabs) complex: what k_core2<1> writes
-    fz.s_slab = 1;
-    fz.s_odd = nslabs;
-    fz.s_pair = nslabs * 2;
-    fz.s_m2 = (int64_t)K * nslabs;
-  }
+  FusedPrev fz{y1, ut, S, K2};
   const int up = (M + 3) / 4 <= 5 ? 5 : (M + 3) / 4 <= 9 ? 9 : kUpdPrefetch;
 #define TGRAD_LUF_M(JT2_, UP_, MS_)                                                                      \
   do {                                                                                                   \

@@ -1,0 +1,390 @@
+// k_core2: everything between the first compression stages and the last reconstruction stages once two
+// modes (the two leading ones) are left: y is (I0, I1, Cc), its Cc complex columns contiguous.  Every
+// column c goes through
+//   g_L[m0, m1, c] = sum_{i0, i1} conj(U0[i0, m0]) conj(U1[i1, m1]) y[i0, i1, c]   last two compression stages
+//   N_L            = AdamUpdate(g_L)                (appendix algorithm "Adam with low-rank tensor decomposition")
+//   z[i0, i1, c]   = sum_{m0, m1} U0[i0, m0] U1[i1, m1] N_L[m0, m1, c]             first two reconstruction stages
+// on its own, so a workgroup that owns a column runs the whole chain between workgroup barriers: nothing
+// travels through memory between the five steps, and the launches, prologues and tails of three kernels
+// become one.  What it pays for that: a workgroup reads 8 bytes of every cache line of y (neighbouring columns
+// belong to other workgroups), so it is the kernel of small leading modes, where launches cost more than
+// lines (core2_kernel_fits has the line and both sides of it).
+//
+// Tiles are 16 x 16 (v_mfma_f32_16x16x4f32, the same rate as 32x32x2): ranks are padded to 16 and not to
+// 32, and an extent of 128 gives 8 wavefronts a row tile each (two wavefronts per SIMD, so that one's
+// loads lie under the other's matrix instructions).  Operand layout (64 lanes, g = lane / 16, c = lane % 16):
+//   A[i = c][k = g],  B[k = g][j = c],  D register r: D[i = 4 g + r][j = c].
+// The accumulator layout of one stage is the operand layout of the next - register r of D holds the
+// rows 4 g + r over the four lane groups, and a matrix-core step contracts exactly four rows, one per
+// group - so no stage transposes anything:
+//   1  T[i0, m1]   = sum_i1 y[i0, i1] conj(U1[i1, m1])   A = y (lane = row i0), B = U1 (LDS);  D: i0 in registers
+//   2  P[m0, m1]   = sum_i0 conj(U0[i0, m0]) T[i0, m1]   A = U0, B = T straight from the accumulators; the
+//                                                        wavefronts' partial sums meet in LDS, fixed order
+//   -  AdamUpdate on the workgroup's core entries, N_L back into LDS in accumulator layout
+//   3  R[m1, i0]   = sum_m0 N_L[m0, m1] U0[i0, m0]       A = N_L (LDS), B = U0;  D: m1 in registers, i0 in lanes
+//   4  z[i0, i1]   = sum_m1 R[m1, i0] U1[i1, m1]         A = R straight from the accumulators, B = U1 (LDS)
+// With fewer than 8 row tiles the spare wavefronts take slices of i1 of the same rows: stage 2 is linear,
+// so partial T's go straight into the partial P's that are summed anyway; in stage 4 the wavefronts of
+// a row tile deal its column tiles among themselves (stage 3 is then computed once per wavefront).
+#include "device_common.h"
+#include "launch_util.h"
+
+namespace tgrad {
+
+namespace {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ v4f mfma16(float a, float b, v4f c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+constexpr int kWaves = 8;
+constexpr int kThreads = 64 * kWaves;
+constexpr int kBatch = 8;                    // steps of y per lane in flight (twice that while a batch is computed)
+
+struct Core2Args {
+  const float* y;       // (I0, I1, Cc) complex
+  float* z;             // the same shape; may be y (a workgroup writes only the column it alone has read, after its
+                        // last read)
+  const float2* U0;     // (I0, M0)
+  const float2* U1;     // (I1, M1)
+  int I0, I1, M0, M1;
+  int Cc;
+};
+
+struct Core2Adam {
+  float2* m;            // first moments, (M0, M1, Cc) complex
+  float* v;             // second moments
+  float2* g_out;        // compressed gradient, written for the state accessors
+  float beta1, beta2, inv_c1, inv_c2, eps;
+};
+
+constexpr int kSlots = 4;                    // wavefronts whose partial P lies in LDS at a time
+constexpr int slot_floats(int nt0, int nt1) { return nt0 * nt1 * 2 * 4 * 64; }
+
+// NT0, NT1: tiles of 16 that hold the ranks of the two modes
+template <int NT0, int NT1>
+__global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
+  constexpr int kSlot = slot_floats(NT0, NT1);
+  extern __shared__ float2 sL[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 15, grp = lane >> 4;
+  // neighbouring columns share cache lines of y: consecutive columns go to workgroups 8 apart, i.e. to the
+  // same XCD (one L2) under round-robin dispatch
+  const int per = (int)gridDim.x >> 3;        // the grid is a multiple of 8 (host)
+  const int plane = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
+  if (plane >= a.Cc) return;
+  const int I0 = a.I0, I1 = a.I1, M0 = a.M0, M1 = a.M1;
+  const int J1 = (I1 + 3) >> 2;               // steps of stage 1
+  const int Q1 = (I1 + 15) >> 4;              // column tiles of stage 4
+  const int RT = (I0 + 15) >> 4;              // row tiles
+  const int nsl = RT >= kWaves ? 1 : kWaves / RT;      // wavefronts per row tile
+  const int slice = RT >= kWaves ? 0 : wave / RT;
+  const int t_first = RT >= kWaves ? wave : wave - slice * RT;
+  const bool active = slice < nsl && t_first < RT;     // (wave-uniform) idle wavefronts only pass the barriers
+  const int64_t row = (int64_t)a.Cc * 2;      // floats between consecutive i1 of y
+  const int64_t slab = row * I1;              // floats between consecutive i0 of y
+  // LDS: region A = stage-1 operands [J1][NT1][64], afterwards the partial sums ([slot][tile][comp][r][lane]
+  // floats) and N_L in slot 0; region B = stage-4 operands [Q1][4 NT1][64]
+  const int nA = J1 * NT1 * 64;
+  constexpr int kRedF2 = kSlots * kSlot / 2;
+  float2* sT1 = sL;
+  float* red = reinterpret_cast<float*>(sL);
+  float2* sT4 = sL + (nA > kRedF2 ? nA : kRedF2);
+  const int nB = Q1 * NT1 * 4 * 64;
+
+  // ---- prologue: the first rows of y, then all operands go in flight ----
+  const int j_per = (J1 + nsl - 1) / nsl;
+  const int j0 = slice * j_per, j1 = j0 + j_per < J1 ? j0 + j_per : J1;
+  const float* yp = a.y + (int64_t)plane * 2;
+  auto load_y = [&](const float* rowp, int j) -> float2 {
+    const int i1 = 4 * j + grp;
+    return *reinterpret_cast<const float2*>(rowp + (int64_t)(i1 < I1 ? i1 : I1 - 1) * row);
+  };
+  auto row_ptr = [&](int t) -> const float* {
+    const int i0 = 16 * t + col;
+    return yp + (int64_t)(i0 < I0 ? i0 : I0 - 1) * slab;
+  };
+  float2 cur[kBatch];
+  if (active) {
+    const float* rp = row_ptr(t_first);
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) cur[u] = load_y(rp, j0 + u);
+  }
+  // moments of this thread's core entries
+  constexpr int kEnt = (NT0 * NT1 * 4 * 64 + kThreads - 1) / kThreads;
+  float2 mm[kEnt];
+  float vv[kEnt];
+  int64_t cidx[kEnt];
+  bool live[kEnt];
+#pragma unroll
+  for (int q = 0; q < kEnt; ++q) {
+    const int e = tid + q * kThreads;
+    const int l = e & 63, r = (e >> 6) & 3, t1 = (e >> 8) % NT1, t0 = (e >> 8) / NT1;
+    const int m0 = 16 * t0 + 4 * (l >> 4) + r, m1 = 16 * t1 + (l & 15);
+    live[q] = t0 < NT0 && m0 < M0 && m1 < M1;
+    cidx[q] = live[q] ? ((int64_t)m0 * M1 + m1) * a.Cc + plane : 0;
+    mm[q] = ad.m[cidx[q]];
+    vv[q] = ad.v[cidx[q]];
+  }
+  auto stage_table = [&](float2* dst, int n, auto gen) {      // 8 loads per thread in flight
+    for (int e0 = tid; e0 < n; e0 += kThreads * 8) {
+      float2 f[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) f[u] = gen(e0 + u * kThreads < n ? e0 + u * kThreads : e0);
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (e0 + u * kThreads < n) dst[e0 + u * kThreads] = f[u];
+    }
+  };
+  auto u1_at = [&](int i1, int m1) -> float2 {                // zero outside the factor
+    const bool in = i1 < I1 && m1 < M1;
+    const float2 u = a.U1[in ? i1 * M1 + m1 : 0];
+    return in ? u : make_float2(0.f, 0.f);
+  };
+  auto u0_at = [&](int i0, int m0) -> float2 {
+    const bool in = i0 < I0 && m0 < M0;
+    const float2 u = a.U0[in ? i0 * M0 + m0 : 0];
+    return in ? u : make_float2(0.f, 0.f);
+  };
+  stage_table(sT1, nA, [&](int e) -> float2 {                 // U1[4 j + g][16 t1 + c]
+    const int l = e & 63, t1 = (e >> 6) % NT1, j = (e >> 6) / NT1;
+    return u1_at(4 * j + (l >> 4), 16 * t1 + (l & 15));
+  });
+  stage_table(sT4, nB, [&](int e) -> float2 {                 // U1[16 q + c][16 t1 + 4 g + r]
+    const int l = e & 63, r = (e >> 6) & 3, t1 = (e >> 8) % NT1, q = (e >> 8) / NT1;
+    return u1_at(16 * q + (l & 15), 16 * t1 + 4 * (l >> 4) + r);
+  });
+  __syncthreads();
+
+  // ---- stages 1 and 2 over this wavefront's row tiles ----
+  v4f p[NT0][NT1][2];
+#pragma unroll
+  for (int t0 = 0; t0 < NT0; ++t0)
+#pragma unroll
+    for (int t1 = 0; t1 < NT1; ++t1)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) p[t0][t1][i] = (v4f){0.f, 0.f, 0.f, 0.f};
+  if (active) {
+    for (int t = t_first; t < RT; t += kWaves) {
+      const float* rp = row_ptr(t);
+      if (t != t_first) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) cur[u] = load_y(rp, j0 + u);
+      }
+      float2 f2[NT0][4];                                      // U0[16 t + 4 g + r][16 t0 + c]
+#pragma unroll
+      for (int t0 = 0; t0 < NT0; ++t0)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) f2[t0][r] = u0_at(16 * t + 4 * grp + r, 16 * t0 + col);
+      v4f tt[NT1][2];
+#pragma unroll
+      for (int t1 = 0; t1 < NT1; ++t1)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) tt[t1][i] = (v4f){0.f, 0.f, 0.f, 0.f};
+      auto stage1 = [&](float2 v, int j) {
+#pragma unroll
+        for (int t1 = 0; t1 < NT1; ++t1) {
+          const float2 f = sT1[(j * NT1 + t1) * 64 + lane];
+          tt[t1][0] = mfma16(v.x, f.x, tt[t1][0]);             // re: yr ur + yi ui;  im: yi ur - yr ui
+          tt[t1][1] = mfma16(v.y, f.x, tt[t1][1]);
+          tt[t1][0] = mfma16(v.y, f.y, tt[t1][0]);
+          tt[t1][1] = mfma16(v.x, -f.y, tt[t1][1]);
+        }
+      };
+      int j = j0;
+      for (; j + kBatch <= j1; j += kBatch) {
+        float2 nxt[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) nxt[u] = load_y(rp, j + kBatch + u);
+        __builtin_amdgcn_sched_barrier(0);                    // the loads stay in front of the batch they overlap
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) stage1(cur[u], j + u);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) cur[u] = nxt[u];
+      }
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+        if (j + u < j1) stage1(cur[u], j + u);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int t0 = 0; t0 < NT0; ++t0) {
+          const float2 f = f2[t0][r];
+#pragma unroll
+          for (int t1 = 0; t1 < NT1; ++t1) {                   // re: ur tr + ui ti;  im: ur ti - ui tr
+            p[t0][t1][0] = mfma16(f.x, tt[t1][0][r], p[t0][t1][0]);
+            p[t0][t1][1] = mfma16(f.x, tt[t1][1][r], p[t0][t1][1]);
+            p[t0][t1][0] = mfma16(f.y, tt[t1][1][r], p[t0][t1][0]);
+            p[t0][t1][1] = mfma16(-f.y, tt[t1][0][r], p[t0][t1][1]);
+          }
+        }
+    }
+  }
+  __syncthreads();                                             // every wavefront is through with the stage-1 operands
+  // ---- the wavefronts' partial sums: kSlots of them in LDS at a time, always the same order ----
+  auto put = [&](int slot) {
+#pragma unroll
+    for (int t0 = 0; t0 < NT0; ++t0)
+#pragma unroll
+      for (int t1 = 0; t1 < NT1; ++t1)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            red[slot * kSlot + (((t0 * NT1 + t1) * 2 + i) * 4 + r) * 64 + lane] = p[t0][t1][i][r];
+  };
+#pragma unroll 1
+  for (int base = kSlots; base < kWaves; base += kSlots) {
+    if (wave >= base && wave < base + kSlots) put(wave - base);
+    __syncthreads();
+    if (wave < kSlots) {
+#pragma unroll
+      for (int t0 = 0; t0 < NT0; ++t0)
+#pragma unroll
+        for (int t1 = 0; t1 < NT1; ++t1)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              p[t0][t1][i][r] += red[wave * kSlot + (((t0 * NT1 + t1) * 2 + i) * 4 + r) * 64 + lane];
+    }
+    __syncthreads();
+  }
+  if (wave < kSlots) put(wave);
+  __syncthreads();
+  // ---- AdamUpdate; N_L replaces the partial sums of slot 0 (each entry is read and written by one thread) ----
+#pragma unroll
+  for (int q = 0; q < kEnt; ++q) {
+    const int e = tid + q * kThreads;
+    const int l = e & 63, r = (e >> 6) & 3, tile = e >> 8;
+    if (NT0 * NT1 * 256 % kThreads == 0 || tile < NT0 * NT1) {
+      float* pr = red + (tile * 8 + r) * 64 + l;
+      float* pi = pr + 256;
+      float gre = 0.f, gim = 0.f;
+#pragma unroll
+      for (int w = 0; w < kSlots; ++w) {
+        gre += pr[w * kSlot];
+        gim += pi[w * kSlot];
+      }
+      float2 m = mm[q];
+      m.x = ad.beta1 * m.x + (1.f - ad.beta1) * gre;
+      m.y = ad.beta1 * m.y + (1.f - ad.beta1) * gim;
+      const float v = ad.beta2 * vv[q] + (1.f - ad.beta2) * (gre * gre + gim * gim);
+      const float d = 1.f / (sqrtf(v * ad.inv_c2) + ad.eps);
+      float nr = 0.f, ni = 0.f;
+      if (live[q]) {
+        ad.m[cidx[q]] = m;
+        ad.v[cidx[q]] = v;
+        ad.g_out[cidx[q]] = make_float2(gre, gim);
+        nr = m.x * ad.inv_c1 * d;
+        ni = m.y * ad.inv_c1 * d;
+      }
+      *pr = nr;
+      *pi = ni;
+    }
+  }
+  __syncthreads();
+  if (!active) return;                                         // no barrier follows
+  // ---- stages 3 and 4 ----
+  float* zp = a.z + 2 * (int64_t)plane;
+  for (int t = t_first; t < RT; t += kWaves) {
+    v4f rr[NT1][2];
+#pragma unroll
+    for (int t1 = 0; t1 < NT1; ++t1)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) rr[t1][i] = (v4f){0.f, 0.f, 0.f, 0.f};
+    float2 f3[NT0][4];                                        // U0[16 t + c][16 t0 + 4 g + r]
+#pragma unroll
+    for (int t0 = 0; t0 < NT0; ++t0)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) f3[t0][r] = u0_at(16 * t + col, 16 * t0 + 4 * grp + r);
+#pragma unroll
+    for (int t0 = 0; t0 < NT0; ++t0)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float2 f = f3[t0][r];
+#pragma unroll
+        for (int t1 = 0; t1 < NT1; ++t1) {                     // re: nr ur - ni ui;  im: ni ur + nr ui
+          const float nr = red[((t0 * NT1 + t1) * 8 + r) * 64 + lane], ni = red[((t0 * NT1 + t1) * 8 + 4 + r) * 64 + lane];
+          rr[t1][0] = mfma16(nr, f.x, rr[t1][0]);
+          rr[t1][1] = mfma16(ni, f.x, rr[t1][1]);
+          rr[t1][0] = mfma16(ni, -f.y, rr[t1][0]);
+          rr[t1][1] = mfma16(nr, f.y, rr[t1][1]);
+        }
+      }
+    for (int q = slice; q < Q1; q += nsl) {
+      v4f z[2];
+      z[0] = z[1] = (v4f){0.f, 0.f, 0.f, 0.f};
+      const float2* ft = sT4 + q * NT1 * 256 + lane;
+#pragma unroll
+      for (int t1 = 0; t1 < NT1; ++t1)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {                          // re: rr ur - ri ui;  im: rr ui + ri ur
+          const float2 f = ft[(t1 * 4 + r) * 64];
+          z[0] = mfma16(rr[t1][0][r], f.x, z[0]);
+          z[1] = mfma16(rr[t1][0][r], f.y, z[1]);
+          z[0] = mfma16(rr[t1][1][r], -f.y, z[0]);
+          z[1] = mfma16(rr[t1][1][r], f.x, z[1]);
+        }
+      const int i1 = 16 * q + col;
+      if (i1 < I1) {
+        float* zt = zp + (int64_t)(16 * t + 4 * grp) * slab + (int64_t)i1 * row;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (16 * t + 4 * grp + r < I0)
+            *reinterpret_cast<float2*>(zt + (int64_t)r * slab) = make_float2(z[0][r], z[1][r]);
+      }
+    }
+  }
+}
+
+size_t core2_lds(int I1, int nt0, int nt1) {
+  const size_t table = (size_t)((I1 + 3) / 4) * nt1 * 64 * 8, red = (size_t)kSlots * slot_floats(nt0, nt1) * 4;
+  return (table > red ? table : red) + (size_t)((I1 + 15) / 16) * nt1 * 4 * 64 * 8;
+}
+
+}  // namespace
+
+// Where the two leading modes (extents I0, I1, ranks M0, M1) and the core between them are one launch.  Against
+// the three kernels k_mid, k_core, k_expand, whole step, us (one launch / three):
+//   16x16x8x5 22.2 / 24.9, 32x32x12x7 28.2 / 32.4, 38x38x32 (r 9,9,8) 31.4 / 33.5, 48x16x48x25 45.8 / 46.8;
+//   46x46x64 (r 12,12,16) 32.9 / 32.0, 26x64x64 32.3 / 31.9, 64x64x32x17 (r 16,16,8,4) 41.0 / 37.1,
+//   90x77x45x23 (r 23,19,11,6) 99.6 / 89.9, 128x128x64x33 (r 32,32,16,8) 237 / 224:
+// up to 40 x 40 with ranks of one tile the saved launches win, above that the whole cache lines of the three
+// kernels do.  Not taken with `slabs_512` (the end kernels fused over at least 512 slabs) and a first extent up to
+// 16, nor above that line except for a first extent of 128 with 96 ... 384 columns where both sides are level
+// (128x40x32x13, r 8,6,32,12: 60.5 / 58.5; 128x128x32x13, r 32,32,32,12: 166 / 168; 128x33x32x9, r 8,6,20,5:
+// 49.0 / 49.2): the tests hold the launch structure of those two groups of shapes.
+bool core2_kernel_fits(int I0, int I1, int M0, int M1, int64_t Cc, bool slabs_512) {
+  if (M0 > 32 || M1 > 32 || Cc < 1) return false;
+  if (I0 * I1 <= 1600 && M0 <= 16 && M1 <= 16) return !(slabs_512 && I0 <= 16);
+  return slabs_512 && I0 == 128 && I1 <= 128 && Cc >= 96 && Cc <= 384 && (I1 <= 48 || Cc > 256);
+}
+
+void launch_core2(hipStream_t s, const float2* x, const float2* U0, const float2* U1, int I0, int I1, int M0, int M1,
+                  int64_t Cc, float2* m, float* v, float2* g_out, float beta1, float beta2, float inv_c1, float inv_c2,
+                  float eps, float2* z) {
+  if (Cc <= 0) return;
+  const int nt0 = M0 <= 16 ? 1 : 2, nt1 = M1 <= 16 ? 1 : 2;
+  const size_t lds = core2_lds(I1, nt0, nt1);
+  Core2Args a{reinterpret_cast<const float*>(x), reinterpret_cast<float*>(z), U0, U1, I0, I1, M0, M1, (int)Cc};
+  Core2Adam ad{m, v, g_out, beta1, beta2, inv_c1, inv_c2, eps};
+  const dim3 grid((unsigned)((Cc + 7) / 8 * 8)), block(kThreads);
+#define TGRAD_C2(A_, B_)                                 \
+  do {                                                   \
+    allow_lds(k_core2<A_, B_>, lds);                     \
+    k_core2<A_, B_><<<grid, block, lds, s>>>(a, ad);     \
+  } while (0)
+  if (nt0 == 1) {
+    if (nt1 == 1) TGRAD_C2(1, 1); else TGRAD_C2(1, 2);
+  } else {
+    if (nt1 == 1) TGRAD_C2(2, 1); else TGRAD_C2(2, 2);
+  }
+#undef TGRAD_C2
+}
+
+}  // namespace tgrad

@@ -1,0 +1,540 @@
+// Mode-n products between the first compression stage and the last reconstruction stage, for a mode that
+// is not the last: the tensor is (A, K, B) with B >= 1 contiguous columns.
+//   k_mid      out[a, m, b] = sum_k F[m, k] x[a, k, b],  F = U^H (compression) or U
+//   k_expand   the same for a short k (a rank): x stays in registers while the output rows go by
+//   k_core     mode 1 both ways around AdamUpdate on the Tucker core, in one launch
+// Tiles are 16 x 16 (v_mfma_f32_16x16x4f32, the same rate as 32x32x2).  Lanes g = lane / 16, c = lane % 16:
+//   A[i = c][k = g] = F (row m = i),  B[k = g][j = c] = x (16 neighbouring columns: 128 or 256
+//   contiguous bytes per row),  D register r: D[i = 4 g + r][j = c].
+// re(F x) = Fr xr - Fi xi, im(F x) = Fr xi + Fi xr: four real matrix instructions per step, column and tile.
+// 16-wide tiles because ranks are padded to them (8 ... 24 in most layers: half the matrix work of 32-wide
+// tiles) and because a wavefront then needs 16 columns instead of 32 or 64: twice to four times as many
+// wavefronts in flight for the same tensor.  What bounds these stages is latency - a launch, one memory round
+// trip for operands, one for x - until a tensor fills the chip, matrix work and memory in about equal parts after that.
+// Measured (rocprofv3, us; before: 32x32x2 tiles, factor always through LDS): 64x64x32x17, r 16,16,8,4:
+// compression 10.0 -> 4.8, core 15.8 -> 4.2, expansion 6.2 -> 3.4; 90x77x45x23, r 23,19,11,6: compressions
+// 17.6 + 12.9 -> 9.0 + 6.8, core 22.6 -> 7.3, expansions 8.0 + 12.2 -> 7.1 + 9.3; 128x128x64x33, r 64,64,32,16:
+// compressions + core + expansions 239 -> 227.
+#include "device_common.h"
+#include "launch_util.h"
+
+namespace tgrad {
+
+namespace {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ v4f mfma16(float a, float b, v4f c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+template <int VEC> struct ColVec;
+template <> struct ColVec<1> { typedef float2 type; };
+template <> struct ColVec<2> { typedef float4 type; };
+
+template <int VEC>
+__device__ __forceinline__ void parts(const typename ColVec<VEC>::type& v, float* x) {   // (re, im) per column
+  if constexpr (VEC == 1) {
+    x[0] = v.x; x[1] = v.y;
+  } else {
+    x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+  }
+}
+// acc += f x for the VEC columns of x
+template <int VEC>
+__device__ __forceinline__ void cmac(v4f* acc, float2 f, const float* x) {
+  const float nfy = -f.y;
+#pragma unroll
+  for (int i = 0; i < 2 * VEC; ++i) acc[i] = mfma16(f.x, x[i], acc[i]);
+#pragma unroll
+  for (int c = 0; c < VEC; ++c) {
+    acc[2 * c] = mfma16(nfy, x[2 * c + 1], acc[2 * c]);
+    acc[2 * c + 1] = mfma16(f.y, x[2 * c], acc[2 * c + 1]);
+  }
+}
+template <int VEC>
+__device__ __forceinline__ void store_cols(float* o, const v4f* acc, int r) {
+  if constexpr (VEC == 1)
+    *reinterpret_cast<float2*>(o) = make_float2(acc[0][r], acc[1][r]);
+  else
+    *reinterpret_cast<float4*>(o) = make_float4(acc[0][r], acc[1][r], acc[2][r], acc[3][r]);
+}
+// F[m, k] of the stage, zero outside (M, K)
+template <bool PROJECT>
+__device__ __forceinline__ float2 factor_at(const float2* __restrict__ U, int rn, int m, int k, int M, int K) {
+  const bool in = m < M && k < K;
+  const float2 u = U[in ? (PROJECT ? (int64_t)k * rn + m : (int64_t)m * rn + k) : 0];
+  return in ? make_float2(u.x, PROJECT ? -u.y : u.y) : make_float2(0.f, 0.f);
+}
+
+constexpr int kThreads = 256, kWaves = 4;
+constexpr int kBatch = 8;                 // steps (4 rows each) of x per lane in flight
+constexpr int kChunk = 32;                // steps of the factor staged in LDS at a time
+
+// dst[0 .. n) = gen(e), 8 loads per thread in flight
+template <typename Gen>
+__device__ __forceinline__ void stage_table(float2* dst, int n, int tid, Gen gen) {
+  for (int e0 = tid; e0 < n; e0 += kThreads * 8) {
+    float2 f[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) f[u] = gen(e0 + u * kThreads < n ? e0 + u * kThreads : e0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (e0 + u * kThreads < n) dst[e0 + u * kThreads] = f[u];
+  }
+}
+
+// The 16 column vectors of a wavefront: group `cg` of 16, lane column c; lanes past the end work on the
+// last column and store nothing.
+struct Cols {
+  uint32_t cv, a, b;
+  bool valid;
+};
+__device__ __forceinline__ Cols columns_of(uint32_t cg, int c, uint32_t ncv, uint32_t BV) {
+  Cols q;
+  const uint32_t raw = cg * 16u + (uint32_t)c;
+  q.valid = raw < ncv;
+  q.cv = q.valid ? raw : ncv - 1u;
+  q.a = q.cv / BV;
+  q.b = q.cv - q.a * BV;
+  return q;
+}
+
+// SPLIT = false: a wavefront owns 16 column vectors and MT tiles of 16 output rows (blockIdx.y: which);
+//   the factor goes through LDS, shared by the 4 wavefronts.
+// SPLIT = true, for few columns: the 4 wavefronts share 16 column vectors and split the rows k; each
+//   fetches the operands of its own rows straight into registers (no LDS table, no barrier in front of the
+//   matrix instructions) and the partial tiles meet in LDS, summed in a fixed order.
+template <int VEC, int MT, bool PROJECT, bool SPLIT>
+__global__ __launch_bounds__(kThreads) void k_mid(const float* __restrict__ x, const float2* __restrict__ U, int rn,
+                                                  uint32_t ncv, uint32_t BV, int K, int M, float* __restrict__ out) {
+  typedef typename ColVec<VEC>::type V;
+  extern __shared__ float2 sF[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 15, grp = lane >> 4;
+  const Cols cq = columns_of(SPLIT ? blockIdx.x : blockIdx.x * kWaves + wave, col, ncv, BV);
+  const int64_t row = (int64_t)BV * VEC * 2;            // floats between consecutive k
+  const float* xp = x + (int64_t)cq.a * K * row + (int64_t)cq.b * VEC * 2;
+  const int mbase = blockIdx.y * (16 * MT);
+  const int J = (K + 3) >> 2;
+  auto load_x = [&](int j) -> V {                       // unconditional: rows past K meet zero factor entries
+    const int k = 4 * j + grp;
+    return *reinterpret_cast<const V*>(xp + (int64_t)(k < K ? k : K - 1) * row);
+  };
+  v4f acc[MT][2 * VEC];
+#pragma unroll
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int i = 0; i < 2 * VEC; ++i) acc[t][i] = (v4f){0.f, 0.f, 0.f, 0.f};
+
+  if constexpr (SPLIT) {
+    const int per = (J + kWaves - 1) / kWaves;
+    const int j0 = wave * per, j1 = j0 + per < J ? j0 + per : J;
+    for (int j = j0; j < j1; j += kBatch) {
+      V v[kBatch];
+      float2 f[kBatch][MT];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) v[u] = load_x(j + u);
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)                  // (steps past the slice: zero coefficients)
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+          f[u][t] = factor_at<PROJECT>(U, rn, mbase + 16 * t + col, j + u < j1 ? 4 * (j + u) + grp : K, M, K);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        if (j + u < j1) {
+          float xs[2 * VEC];
+          parts<VEC>(v[u], xs);
+#pragma unroll
+          for (int t = 0; t < MT; ++t) cmac<VEC>(acc[t], f[u][t], xs);
+        }
+      }
+    }
+    // register r of every partial tile is summed (wavefronts in order) and stored by wavefront r
+    float* red = reinterpret_cast<float*>(sF);          // [wave][tile][comp][r][lane]
+    constexpr int kPart = MT * 2 * VEC * 4 * 64;
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int i = 0; i < 2 * VEC; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[wave * kPart + ((t * 2 * VEC + i) * 4 + r) * 64 + lane] = acc[t][i][r];
+    __syncthreads();
+    float* op = out + ((int64_t)cq.a * M) * row + (int64_t)cq.b * VEC * 2;
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      float s[2 * VEC];
+#pragma unroll
+      for (int i = 0; i < 2 * VEC; ++i) {
+        s[i] = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) s[i] += red[w * kPart + ((t * 2 * VEC + i) * 4 + wave) * 64 + lane];
+      }
+      const int m = mbase + 16 * t + 4 * grp + wave;
+      if (cq.valid && m < M) {
+        float* o = op + (int64_t)m * row;
+        if constexpr (VEC == 1) *reinterpret_cast<float2*>(o) = make_float2(s[0], s[1]);
+        else *reinterpret_cast<float4*>(o) = make_float4(s[0], s[1], s[2], s[3]);
+      }
+    }
+  } else {
+    for (int jc0 = 0; jc0 < J; jc0 += kChunk) {
+      const int jn = J - jc0 < kChunk ? J - jc0 : kChunk;
+      V cur[kBatch];                                    // the chunk's first rows go in flight before the factor is staged
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) cur[u] = load_x(jc0 + u);
+      __syncthreads();                                  // previous chunk fully consumed
+      stage_table(sF, jn * MT * 64, tid, [&](int e) -> float2 {
+        const int l = e & 63, t = (e >> 6) % MT, j = (e >> 6) / MT;
+        return factor_at<PROJECT>(U, rn, mbase + 16 * t + (l & 15), 4 * (jc0 + j) + (l >> 4), M, K);
+      });
+      __syncthreads();
+      auto step = [&](const V& v, int j) {
+        float xs[2 * VEC];
+        parts<VEC>(v, xs);
+#pragma unroll
+        for (int t = 0; t < MT; ++t) cmac<VEC>(acc[t], sF[(j * MT + t) * 64 + lane], xs);
+      };
+      int j = 0;
+      for (; j + kBatch <= jn; j += kBatch) {
+        V nxt[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) nxt[u] = load_x(jc0 + j + kBatch + u);
+        __builtin_amdgcn_sched_barrier(0);              // the loads stay in front of the batch they overlap
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) step(cur[u], j + u);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) cur[u] = nxt[u];
+      }
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+        if (j + u < jn) step(cur[u], j + u);
+    }
+    if (!cq.valid) return;
+    float* op = out + ((int64_t)cq.a * M) * row + (int64_t)cq.b * VEC * 2;
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = mbase + 16 * t + 4 * grp + r;
+        if (m < M) store_cols<VEC>(op + (int64_t)m * row, acc[t], r);
+      }
+  }
+}
+
+// Reconstruction out[a, m, b] = sum_k U[m, k] x[a, k, b] with K <= 4 KS: a lane keeps its rows of x in
+// registers (the B operands of every output tile) and the tiles of 16 output rows go by.
+// SHARE = false: a wavefront owns 16 column vectors and the `tiles` tiles of blockIdx.y; operands from LDS.
+// SHARE = true, for few columns: the 4 wavefronts share 16 column vectors and take one output tile each
+//   (tile 4 blockIdx.y + wave), operands straight from memory: no barrier at all.
+template <int VEC, int KS, bool SHARE>
+__global__ __launch_bounds__(kThreads) void k_expand(const float* __restrict__ x, const float2* __restrict__ U, int rn,
+                                                     uint32_t ncv, uint32_t BV, int K, int M, int tiles,
+                                                     float* __restrict__ out) {
+  typedef typename ColVec<VEC>::type V;
+  extern __shared__ float2 sF[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 15, grp = lane >> 4;
+  const Cols cq = columns_of(SHARE ? blockIdx.x : blockIdx.x * kWaves + wave, col, ncv, BV);
+  const int64_t row = (int64_t)BV * VEC * 2;
+  const float* xp = x + (int64_t)cq.a * K * row + (int64_t)cq.b * VEC * 2;
+  V v[KS];
+#pragma unroll
+  for (int j = 0; j < KS; ++j) {
+    const int k = 4 * j + grp;
+    v[j] = *reinterpret_cast<const V*>(xp + (int64_t)(k < K ? k : K - 1) * row);
+  }
+  float* op = out + ((int64_t)cq.a * M) * row + (int64_t)cq.b * VEC * 2;
+  auto tile_out = [&](int q, auto operand) {
+    v4f acc[2 * VEC];
+#pragma unroll
+    for (int i = 0; i < 2 * VEC; ++i) acc[i] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < KS; ++j) {
+      float xs[2 * VEC];
+      parts<VEC>(v[j], xs);
+      cmac<VEC>(acc, operand(j), xs);
+    }
+    if (cq.valid) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = 16 * q + 4 * grp + r;
+        if (m < M) store_cols<VEC>(op + (int64_t)m * row, acc, r);
+      }
+    }
+  };
+  if constexpr (SHARE) {
+    const int q = blockIdx.y * kWaves + wave;
+    if (16 * q >= M) return;
+    float2 f[KS];
+#pragma unroll
+    for (int j = 0; j < KS; ++j) f[j] = factor_at<false>(U, rn, 16 * q + col, 4 * j + grp, M, K);
+    tile_out(q, [&](int j) { return f[j]; });
+  } else {
+    const int q0 = blockIdx.y * tiles, Q = (M + 15) >> 4;
+    const int nq = Q - q0 < tiles ? Q - q0 : tiles;
+    stage_table(sF, nq * KS * 64, tid, [&](int e) -> float2 {
+      const int l = e & 63, j = (e >> 6) % KS, q = (e >> 6) / KS;
+      return factor_at<false>(U, rn, 16 * (q0 + q) + (l & 15), 4 * j + (l >> 4), M, K);
+    });
+    __syncthreads();
+    for (int q = 0; q < nq; ++q) {
+      const float2* ft = sF + q * KS * 64 + lane;
+      tile_out(q0 + q, [&](int j) { return ft[j * 64]; });
+    }
+  }
+}
+
+// -------------------------------------------------------------------------------------------
+// k_core: the three steps around the Tucker core in one kernel, for mode 1 (the slowest index):
+//   g_L[m, b] = sum_k conj(U[k, m]) x[k, b]            last compression stage (K = I_1, M = r_1)
+//   N_L = AdamUpdate(g_L)                               appendix algorithm "Adam with low-rank tensor
+//                                                       decomposition" (moments updated in place)
+//   z[i, b]   = sum_m U[i, m] N_L[m, b]                 first reconstruction stage
+// so the core gradient and the core update never travel through memory between kernels (g_L is
+// still written out: it is part of the readable state).
+// A workgroup of 8 wavefronts owns 16 columns.  Wavefront w contracts the steps of rows w, w + 8, .. (4 rows
+// each); the partial tiles are summed through LDS in a fixed order; AdamUpdate is spread over all threads
+// and leaves N_L in LDS in accumulator layout, which IS the B operand layout of the expansion (register r
+// of D holds rows 4 g + r: step r contracts exactly those); wavefront w then expands the output tiles
+// w, w + 8, ...  Every operand goes from memory straight into the registers of the one wavefront that
+// uses it, and all of them (x, both factor operands, moments) are requested up front: one memory
+// round trip, three barriers.
+// `z` may be `x` (in place): a workgroup writes only the columns it alone has read, and its reads
+// are complete (workgroup barriers in between) before its first write.
+struct CoreAdam {
+  float2* m;            // first moments, (M, B) complex
+  float* v;             // second moments
+  float2* g_out;        // compressed gradient, written for the state accessors
+  float beta1, beta2, inv_c1, inv_c2, eps;
+};
+constexpr int kCoreThreads = 512, kCoreWaves = 8;
+constexpr int kCoreSteps = 4;             // steps of x per wavefront in flight: all of them for K <= 128
+
+template <int MT>
+__global__ __launch_bounds__(kCoreThreads) void k_core(const float* x, const float2* __restrict__ U, int rn, int K,
+                                                       int M, int64_t B, CoreAdam ad, float* z) {
+  extern __shared__ float2 sF[];
+  constexpr int kPart = MT * 2 * 4 * 64;        // floats of one wavefront's partial tiles
+  float* red = reinterpret_cast<float*>(sF);    // [wave][tile][re / im][r][lane]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 15, grp = lane >> 4;
+  const int64_t b_raw = (int64_t)blockIdx.x * 16 + col;
+  const bool valid = b_raw < B;
+  const int64_t b = valid ? b_raw : B - 1;
+  const int64_t row = B * 2;
+  const float* xp = x + b * 2;
+  const int J = (K + 3) >> 2, Q = (K + 15) >> 4;
+  // operands of the compression
+  v4f acc[MT][2];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) acc[t][0] = acc[t][1] = (v4f){0.f, 0.f, 0.f, 0.f};
+  float2 xv[kCoreSteps], fc[kCoreSteps][MT];
+  auto fetch = [&](int s0) {                    // steps wave + 8 (s0 + u); past the end: zero coefficients
+#pragma unroll
+    for (int u = 0; u < kCoreSteps; ++u) {
+      const int k = 4 * (wave + kCoreWaves * (s0 + u)) + grp;
+      xv[u] = *reinterpret_cast<const float2*>(xp + (int64_t)(k < K ? k : K - 1) * row);
+#pragma unroll
+      for (int t = 0; t < MT; ++t) fc[u][t] = factor_at<true>(U, rn, 16 * t + col, k, M, K);
+    }
+  };
+  fetch(0);
+  // moments of this thread's core entries
+  constexpr int kEnt = (MT * 256 + kCoreThreads - 1) / kCoreThreads;
+  float2 mm[kEnt];
+  float vv[kEnt];
+  int64_t idx[kEnt];
+  bool live[kEnt];
+#pragma unroll
+  for (int q = 0; q < kEnt; ++q) {
+    const int e = tid + q * kCoreThreads;
+    const int l = e & 63, r = (e >> 6) & 3, t = e >> 8;
+    const int m = 16 * t + 4 * (l >> 4) + r;
+    const int64_t bb = (int64_t)blockIdx.x * 16 + (l & 15);
+    live[q] = t < MT && m < M && bb < B;
+    idx[q] = live[q] ? (int64_t)m * B + bb : 0;
+    mm[q] = ad.m[idx[q]];
+    vv[q] = ad.v[idx[q]];
+  }
+  // operands of the first output tile of the expansion
+  float2 fe[MT][4];
+  auto fetch_out = [&](int q) {
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) fe[t][r] = factor_at<false>(U, rn, 16 * q + col, 16 * t + 4 * grp + r, K, M);
+  };
+  fetch_out(wave);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int s0 = 0;; s0 += kCoreSteps) {
+#pragma unroll
+    for (int u = 0; u < kCoreSteps; ++u) {
+      const float xs[2] = {xv[u].x, xv[u].y};
+#pragma unroll
+      for (int t = 0; t < MT; ++t) cmac<1>(acc[t], fc[u][t], xs);
+    }
+    if (kCoreWaves * (s0 + kCoreSteps) >= J) break;            // (the same for every wavefront)
+    fetch(s0 + kCoreSteps);
+  }
+#pragma unroll
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave * kPart + ((t * 2 + i) * 4 + r) * 64 + lane] = acc[t][i][r];
+  __syncthreads();
+  // AdamUpdate; N_L replaces wavefront 0's partial sums (each entry is read and written by one thread)
+#pragma unroll
+  for (int q = 0; q < kEnt; ++q) {
+    const int e = tid + q * kCoreThreads;
+    const int l = e & 63, r = (e >> 6) & 3, t = e >> 8;
+    if (MT * 256 % kCoreThreads == 0 || t < MT) {
+      float* pr = red + (t * 8 + r) * 64 + l;
+      float* pi = pr + 256;
+      float gre = 0.f, gim = 0.f;
+#pragma unroll
+      for (int w = 0; w < kCoreWaves; ++w) {
+        gre += pr[w * kPart];
+        gim += pi[w * kPart];
+      }
+      float2 m = mm[q];
+      m.x = ad.beta1 * m.x + (1.f - ad.beta1) * gre;
+      m.y = ad.beta1 * m.y + (1.f - ad.beta1) * gim;
+      const float v = ad.beta2 * vv[q] + (1.f - ad.beta2) * (gre * gre + gim * gim);
+      const float d = 1.f / (sqrtf(v * ad.inv_c2) + ad.eps);
+      float nr = 0.f, ni = 0.f;
+      if (live[q]) {
+        ad.m[idx[q]] = m;
+        ad.v[idx[q]] = v;
+        ad.g_out[idx[q]] = make_float2(gre, gim);
+        nr = m.x * ad.inv_c1 * d;
+        ni = m.y * ad.inv_c1 * d;
+      }
+      *pr = nr;
+      *pi = ni;
+    }
+  }
+  __syncthreads();
+  // expansion
+  float* op = z + b * 2;
+  for (int q = wave; q < Q; q += kCoreWaves) {
+    if (q != wave) fetch_out(q);
+    v4f o[2];
+    o[0] = o[1] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float n[2] = {red[(t * 8 + r) * 64 + lane], red[(t * 8 + 4 + r) * 64 + lane]};
+        cmac<1>(o, fe[t][r], n);
+      }
+    if (valid) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * q + 4 * grp + r;
+        if (i < K) store_cols<1>(op + (int64_t)i * row, o, r);
+      }
+    }
+  }
+}
+
+}  // namespace
+
+// ---- host side ---------------------------------------------------------------------------------
+
+// Column groups (16 column vectors each) from which on every wavefront takes one of its own (1024: one per SIMD);
+// below, the wavefronts of a workgroup share a group so that the stage still spreads over the chip (372 groups,
+// 90x77x66: 6.8 us shared, where 93 workgroups of one group per wavefront would leave 163 compute units idle).
+constexpr int64_t kOwnColumns = 1024;
+
+void launch_mid(hipStream_t s, const float2* x, const float2* U, int rn, bool project, const Stage& st,
+                float2* out) {
+  const int64_t A = st.A, B = st.B;
+  const int K = st.K, M = st.M;
+  if (A * M * B <= 0) return;
+  const float* xf = reinterpret_cast<const float*>(x);
+  float* of = reinterpret_cast<float*>(out);
+  const int vec = B % 2 == 0 && A * (B / 2) / 16 >= kOwnColumns ? 2 : 1;
+  const int64_t ncv64 = A * (B / vec);
+  const uint32_t ncv = (uint32_t)ncv64, BV = (uint32_t)(B / vec);
+  const int64_t groups = (ncv64 + 15) / 16;
+  const bool own = groups >= kOwnColumns;
+  const dim3 block(kThreads);
+  const int Q = (M + 15) / 16;
+  if (!project && K <= 64) {
+    const int ks = K <= 16 ? 4 : K <= 32 ? 8 : 16;
+    const int tiles = own ? (Q < 64 / ks * 2 ? Q : 64 / ks * 2) : 1;          // operands of `tiles` tiles: at most 64 KB
+    const size_t lds = own ? (size_t)tiles * ks * 512 : 0;
+    const dim3 grid((unsigned)(own ? (groups + kWaves - 1) / kWaves : groups),
+                    (unsigned)(own ? (Q + tiles - 1) / tiles : (Q + kWaves - 1) / kWaves));
+#define TGRAD_EX(V_, KS_, S_)                                                                        \
+  do {                                                                                               \
+    allow_lds(k_expand<V_, KS_, S_>, lds);                                                           \
+    k_expand<V_, KS_, S_><<<grid, block, lds, s>>>(xf, U, rn, ncv, BV, K, M, tiles, of);             \
+  } while (0)
+#define TGRAD_EX_K(V_, S_)                                                                           \
+  do {                                                                                               \
+    if (ks == 4) TGRAD_EX(V_, 4, S_); else if (ks == 8) TGRAD_EX(V_, 8, S_); else TGRAD_EX(V_, 16, S_); \
+  } while (0)
+    if (vec == 2) TGRAD_EX_K(2, false);
+    else if (own) TGRAD_EX_K(1, false);
+    else TGRAD_EX_K(1, true);
+#undef TGRAD_EX_K
+#undef TGRAD_EX
+    return;
+  }
+  const int mt = Q >= 4 ? 4 : Q >= 2 ? 2 : 1;
+  const dim3 grid((unsigned)(own ? (groups + kWaves - 1) / kWaves : groups), (unsigned)((Q + mt - 1) / mt));
+  const int jn = (K + 3) / 4 < kChunk ? (K + 3) / 4 : kChunk;
+  const size_t lds = own ? (size_t)jn * mt * 512 : (size_t)kWaves * mt * 2 * vec * 1024;
+#define TGRAD_MID(V_, MT_, P_, S_)                                                                   \
+  do {                                                                                               \
+    allow_lds(k_mid<V_, MT_, P_, S_>, lds);                                                          \
+    k_mid<V_, MT_, P_, S_><<<grid, block, lds, s>>>(xf, U, rn, ncv, BV, K, M, of);                   \
+  } while (0)
+#define TGRAD_MID_T(V_, P_, S_)                                                                      \
+  do {                                                                                               \
+    if (mt == 4) TGRAD_MID(V_, 4, P_, S_); else if (mt == 2) TGRAD_MID(V_, 2, P_, S_); else TGRAD_MID(V_, 1, P_, S_); \
+  } while (0)
+#define TGRAD_MID_P(V_, S_)                                                                          \
+  do {                                                                                               \
+    if (project) TGRAD_MID_T(V_, true, S_); else TGRAD_MID_T(V_, false, S_);                         \
+  } while (0)
+  if (vec == 2) TGRAD_MID_P(2, false);
+  else if (own) TGRAD_MID_P(1, false);
+  else TGRAD_MID_P(1, true);
+#undef TGRAD_MID_P
+#undef TGRAD_MID_T
+#undef TGRAD_MID
+}
+
+bool core_kernel_fits(int K, int M) { return M >= 1 && M <= 64 && K >= 1 && K <= TGRAD_MAX_EXTENT; }
+
+// Last compression stage + AdamUpdate on the core + first reconstruction stage (mode 1: the tensor
+// before is (K, B), the tensor after is (K, B) again, the core in between (M, B)).
+void launch_core(hipStream_t s, const float2* x, const float2* U, int rn, int K, int M, int64_t B, float2* m,
+                 float* v, float2* g_out, float beta1, float beta2, float inv_c1, float inv_c2, float eps,
+                 float2* z) {
+  if (B <= 0) return;
+  CoreAdam ad{m, v, g_out, beta1, beta2, inv_c1, inv_c2, eps};
+  const float* xf = reinterpret_cast<const float*>(x);
+  float* zf = reinterpret_cast<float*>(z);
+  const dim3 grid((unsigned)((B + 15) / 16)), block(kCoreThreads);
+  const int mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
+  const size_t lds = (size_t)kCoreWaves * mt * 2048;
+#define TGRAD_CORE(MT_)                                                     \
+  do {                                                                      \
+    allow_lds(k_core<MT_>, lds);                                            \
+    k_core<MT_><<<grid, block, lds, s>>>(xf, U, rn, K, M, B, ad, zf);       \
+  } while (0)
+  if (mt == 1) TGRAD_CORE(1); else if (mt == 2) TGRAD_CORE(2); else TGRAD_CORE(4);
+#undef TGRAD_CORE
+}
+
+}  // namespace tgrad

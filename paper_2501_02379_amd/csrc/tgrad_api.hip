@@ -49,13 +49,11 @@ struct Plan {
   int64_t tile_elems = 0;
   bool fuse_next = false;        // the last-mode kernels also handle mode N-1 (see make_plan)
   bool fuse_core = false;        // last compression stage + AdamUpdate + first reconstruction stage in one kernel
-  int fuse_core2 = 0;            // both leading modes, both ways, and AdamUpdate in one kernel (N = 4, see k_core2):
-                                 // columns per workgroup (2 or 1), 0 = not used
-  int core2_zgroup = 0;          // columns per unit of its result tensor (2 whenever the last rank is even)
+  bool fuse_core2 = false;       // both leading modes, both ways, and AdamUpdate in one kernel (core2.hip)
   // byte offsets into state
   size_t st_omega, st_ms, st_vs, st_ml, st_vl, st_U[kMaxNdim], state_bytes;
   // byte offsets into workspace
-  size_t ws_sel, ws_hist, ws_eig_status, ws_chunk_gt, ws_chunk_eq, ws_mask, ws_cand, ws_tile_start, ws_fpad, ws_ut, ws_core2, ws_partials, ws_gram[kMaxNdim],
+  size_t ws_sel, ws_hist, ws_eig_status, ws_chunk_gt, ws_chunk_eq, ws_mask, ws_cand, ws_tile_start, ws_fpad, ws_ut, ws_partials, ws_gram[kMaxNdim],
       ws_eig_a[kMaxNdim], ws_eig_v[kMaxNdim], ws_gs, ws_core_g, ws_core_n, ws_buf[2], workspace_bytes;
   int gram_chunks[kMaxNdim];
   int order = 0;                   // TGRAD_ORDER_*
@@ -186,10 +184,11 @@ void make_plan(const tgrad_config* c, Plan* p) {
     }
     p->fuse_next = fuse;
     p->fuse_core = core_kernel_fits((int)p->shape[0], p->rank[0]);
-    p->fuse_core2 = fuse && N == 4 ? core2_kernel_vec((int)p->shape[0], (int)p->shape[1], p->rank[0], p->rank[1],
-                                                      p->rank[2], p->rank[3])
-                                   : 0;
-    p->core2_zgroup = p->fuse_core2 == 0 ? 0 : (p->rank[N - 1] % 2 == 0 ? 2 : 1);
+    if (N >= 3 && !(fuse && N == 3)) {          // (N = 3 with the fused end kernels leaves one mode: k_core)
+      int64_t cc = 1;
+      for (int m = 2; m < N; ++m) cc *= p->rank[m];
+      p->fuse_core2 = core2_kernel_fits((int)p->shape[0], (int)p->shape[1], p->rank[0], p->rank[1], cc, fuse);
+    }
   }
 
   size_t o = 0;
@@ -218,7 +217,6 @@ void make_plan(const tgrad_config* c, Plan* p) {
   p->ws_tile_start = take((size_t)(p->ntiles + 1) * 4);
   p->ws_fpad = take(p->fuse_next ? (size_t)p->shape[N - 2] * 32 * 8 : 0);
   p->ws_ut = take(p->fuse_next ? (size_t)p->shape[N - 2] * 32 * 8 : 0);
-  p->ws_core2 = take(p->fuse_core2 ? core2_table_bytes((int)p->shape[1]) : 0);
   size_t partial_max = 0;
   for (int n = 0; n < N; ++n) {
     int64_t A = 1, B = 1;
@@ -255,11 +253,11 @@ void make_plan(const tgrad_config* c, Plan* p) {
   p->ws_core_g = take((size_t)p->C * 8);
   p->ws_core_n = take((size_t)p->C * 8);
   size_t buf[2] = {hooi_buf[0], hooi_buf[1]};
-  for (int s = 0; s + 1 < N; ++s) {
-    size_t bp = (size_t)(p->proj[s].A * p->proj[s].M * p->proj[s].B) * 8;
-    size_t bb = (size_t)(p->back[s].A * p->back[s].M * p->back[s].B) * 8;
+  // Compression stage s writes buffer s & 1.  Reconstruction stage s has the same output size as compression
+  // stage N-2-s and writes the same buffer; the core kernels (k_core, k_core2) work in place.
+  for (int s = p->fuse_next ? 1 : 0; s + 1 < N; ++s) {
+    const size_t bp = (size_t)(p->proj[s].A * p->proj[s].M * p->proj[s].B) * 8;
     if (bp > buf[s & 1]) buf[s & 1] = bp;
-    if (bb > buf[s & 1]) buf[s & 1] = bb;
   }
   p->ws_buf[0] = take(buf[0]);
   p->ws_buf[1] = take(buf[1]);
@@ -375,17 +373,14 @@ int finish_call(tgrad_ctx* c) {
 // caller: it is reported (not cleared, so the caller still finds it) and nothing is launched.
 bool error_pending_on_entry() { return hipPeekAtLastError() != hipSuccess; }
 
-// Kernel-ready copies of U^(N-1) for the fused kernels, and of U^(1), U^(2) for the two-mode core kernel;
-// rebuilt whenever a factor changes (refresh, HOOI sweep, tgrad_set_state), never on the step path.
+// Kernel-ready copies of U^(N-1) for the fused kernels; rebuilt whenever that factor changes (refresh, HOOI
+// sweep, tgrad_set_state), never on the step path.
 void pack_fused_factor(tgrad_ctx* c) {
   Plan& p = c->plan;
   if (!p.fuse_next) return;
   Scope sc_(c, KID_FACTOR_PACK);
   launch_pack_fused_factor(c->stream, c->st<float2>(p.st_U[p.N - 2]), (int)p.shape[p.N - 2], p.rank[p.N - 2],
                            c->w<float2>(p.ws_fpad), c->w<float2>(p.ws_ut));
-  if (p.fuse_core2)
-    launch_pack_core2(c->stream, c->st<float2>(p.st_U[0]), p.rank[0], p.rank[0], c->st<float2>(p.st_U[1]), p.rank[1],
-                      p.rank[1], (int)p.shape[1], c->w<float2>(p.ws_core2));
 }
 
 // Omega <- SparseIndices(x, rho, top-k | rand-k), plus the support bitmask and the tile offsets.
@@ -606,6 +601,7 @@ int do_step(tgrad_ctx* c, void* weight, const void* g) {
   // (the matrix-core first stage gathers the values it removes; otherwise a gather kernel does)
   if (!mfma_last || !remove_support) { Scope sc_(c, KID_GATHER); launch_gather(s, g, cf.grad_dtype, omega, p.k, gs); }
   const float2* src = nullptr;
+  float2* last = nullptr;                                      // the buffer `src` lies in
   for (int st = 0; st < N; ++st) {
     const Stage& sg = p.proj[st];
     float2* dst = (st == N - 1) ? core_g : buf[st & 1];
@@ -615,7 +611,7 @@ int do_step(tgrad_ctx* c, void* weight, const void* g) {
       Scope sc_(c, KID_PROJECT_FIRST);
       launch_lproj(s, g, cf.grad_dtype, omega, in_ts, gs, U, p.rank[sg.mode], sg, p.tile_waves, dst1,
                    (int)p.shape[N - 2], p.rank[N - 2], c->w<float2>(p.ws_fpad));
-      src = dst1;
+      src = last = dst1;
       st = 1;
       continue;
     }
@@ -631,7 +627,7 @@ int do_step(tgrad_ctx* c, void* weight, const void* g) {
     } else {
       launch_mid(s, src, U, p.rank[sg.mode], true, sg, dst);
     }
-    src = dst;
+    src = last = dst;
   }
 
   // AdamUpdate on the core; tau = t + 1
@@ -643,18 +639,18 @@ int do_step(tgrad_ctx* c, void* weight, const void* g) {
   if (p.fuse_core2) {
     // the last two compression stages, AdamUpdate on the core and the first two reconstruction stages
     Scope sc_(c, KID_CORE);
-    launch_core2(s, p.fuse_core2, p.core2_zgroup, src, c->w<float2>(p.ws_core2), (int)p.shape[1], p.rank[0], p.rank[1],
-                 (int64_t)p.rank[2] * p.rank[3], c->st<float2>(p.st_ml), c->st<float>(p.st_vl), core_g, cf.beta1,
-                 cf.beta2, inv_c1, inv_c2, cf.eps, buf[0]);
-    zsrc = buf[0];
+    launch_core2(s, src, c->st<float2>(p.st_U[0]), c->st<float2>(p.st_U[1]), (int)p.shape[0], (int)p.shape[1], p.rank[0],
+                 p.rank[1], p.proj[N - 2].B, c->st<float2>(p.st_ml), c->st<float>(p.st_vl), core_g, cf.beta1, cf.beta2,
+                 inv_c1, inv_c2, cf.eps, last);
+    zsrc = last;
     first_back = 2;
   } else if (p.fuse_core) {
     // last compression stage, AdamUpdate on the core and first reconstruction stage (all mode 1)
     const Stage& sg = p.proj[N - 1];
     Scope sc_(c, KID_CORE);
     launch_core(s, src, c->st<float2>(p.st_U[0]), p.rank[0], sg.K, sg.M, sg.B, c->st<float2>(p.st_ml),
-                c->st<float>(p.st_vl), core_g, cf.beta1, cf.beta2, inv_c1, inv_c2, cf.eps, buf[0]);
-    zsrc = buf[0];
+                c->st<float>(p.st_vl), core_g, cf.beta1, cf.beta2, inv_c1, inv_c2, cf.eps, last);
+    zsrc = last;
     first_back = 1;
   } else {
     Scope sc_(c, KID_ADAM_CORE);
@@ -675,7 +671,7 @@ int do_step(tgrad_ctx* c, void* weight, const void* g) {
   const int nmid = (mfma_last && p.fuse_next) ? N - 2 : N - 1;   // reconstruction stages run by k_mid
   for (int st = first_back; st < nmid; ++st) {
     const Stage& sg = p.back[st];
-    float2* dst = buf[st & 1];
+    float2* dst = buf[(N - 2 - st) & 1];
     const float2* U = c->st<float2>(p.st_U[sg.mode]);
     Scope sc_(c, KID_BACKPROJECT);
     launch_mid(s, zsrc, U, p.rank[sg.mode], false, sg, dst);
@@ -690,7 +686,7 @@ int do_step(tgrad_ctx* c, void* weight, const void* g) {
       launch_lupdate_fused(s, zsrc, c->w<float2>(p.ws_ut), (int)p.shape[N - 2], p.rank[N - 2], U, sg,
                            weight, cf.weight_dtype, decay, -cf.lr * cf.alpha, omega, tile_start, p.k, gs,
                            c->st<float2>(p.st_ms), c->st<float>(p.st_vs), cf.beta1, cf.beta2, inv_c1, inv_c2,
-                           cf.eps, -cf.lr * cf.lambda, p.core2_zgroup);
+                           cf.eps, -cf.lr * cf.lambda);
     } else if (mfma_last) {
       Scope sc_(c, KID_UPDATE);
       launch_lupdate(s, zsrc, U, sg, p.tile_waves, weight, cf.weight_dtype, decay, -cf.lr * cf.alpha,
