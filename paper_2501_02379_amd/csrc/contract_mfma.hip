@@ -10,7 +10,7 @@
 // i.e. 4 real multiply-adds per complex multiply-add on either layout below.
 //
 // The kernels:
-//  (the modes between: mid.hip, core2.hip)
+//  (the modes between: mid.hip, core2.hip; both ends on 16 x 16 tiles: ends.hip)
 //  k_lproj    contracts the LAST mode of the gradient itself (first compression stage): a
 //             flat tile of rows is staged in LDS, the entries of the support Omega that fall
 //             in the tile are handed to the sparse branch (gather) and zeroed (this is
@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "end_common.h"
 #include "launch_util.h"
 
 namespace tgrad {
@@ -42,12 +43,6 @@ __device__ __forceinline__ v16f mfma32(float a, float b, v16f c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 __device__ __forceinline__ int d_row(int r, int half) { return (r & 3) + 8 * (r >> 2) + 4 * half; }
-
-// q = n / d, exact for n * d < 2^32 (callers keep n < 2^17, d < 2^10).
-// magic = ceil(2^32 / d); d == 1 is encoded as magic == 0.
-__device__ __forceinline__ uint32_t div_magic(uint32_t n, uint32_t magic) {
-  return magic ? __umulhi(n, magic) : n;
-}
 
 // -------------------------------------------------------------------------------------------
 // Register-resident matrix-core loops: what the matrix cores of this chip deliver when nothing else
@@ -110,22 +105,6 @@ __global__ __launch_bounds__(256) void k_mfma_probe_f64(float* sink, int64_t ite
 // one: smaller workgroups leave the matrix cores of the last SIMDs idle.
 constexpr int kTileRows = 32;
 
-// Orders the LDS accesses of one wavefront across its lanes (LDS executes a wavefront's
-// instructions in order; this only keeps the compiler from moving them across the point).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Zero in a vector register that the compiler can neither fold nor prove uniform: an index built
-// with it is loaded per lane (vector memory), not through the scalar cache.
-__device__ __forceinline__ int opaque_zero() {
-  int z = 0;
-  asm volatile("" : "+v"(z));
-  return z;
-}
-
 // Factor table in LDS: sF[k * ld + m] = scale * F[m, k] as (fr, fi), ld = 16 NT, zero for k >= K
 // or m >= M.  PROJECT: F[m, k] = conj(U[k, m]); otherwise F[m, k] = U[m, k].
 template <bool PROJECT>
@@ -146,12 +125,6 @@ __device__ __forceinline__ void stage_factor_table(float2* sF, const float2* __r
     sF[e] = make_float2(scale * f.x, scale * f.y);
   }
 }
-// Coefficients of the (re, im) parts of input element k for real output column (m, p):
-// re(F x) = fr xr - fi xi,  im(F x) = fi xr + fr xi.
-__device__ __forceinline__ float2 column_coef(float2 f, int p) {
-  return p ? make_float2(f.y, f.x) : make_float2(f.x, -f.y);
-}
-
 // Two consecutive gradient elements as they lie in memory (complex64: 16 bytes, bf16 pairs: 8).
 template <int DT> struct RawPair;
 template <> struct RawPair<TGRAD_C64> { typedef float4 type; };
@@ -190,10 +163,6 @@ __device__ __forceinline__ void decode_raw(const typename RawPair<DT>::type& raw
   }
 }
 
-__device__ __forceinline__ void claim_raw(float4& r) {
-  asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w));
-}
-__device__ __forceinline__ void claim_raw(uint2& r) { asm volatile("" : "+v"(r.x), "+v"(r.y)); }
 
 constexpr int kTileBatch = 17;            // 2-element pieces per lane in flight while a tile is staged (the most;
                                           // narrower last modes use 9 or 5: a tile of K-wide rows has K / 4 per lane)
@@ -516,38 +485,6 @@ __global__ __launch_bounds__(64 * W, 2) void k_lproj(const void* __restrict__ g,
 //    that they cover the tile: TB x 64 >= 16 K), so no lane masks;
 //  - support ranges, factor operands and results go through scalar bases + invariant lane offsets.
 // Same tile sequence and the same arithmetic, in the same order, as k_lproj<.., FUSE>.
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_buffer(const void* base, uint32_t bytes) {
-  // untyped buffer, stride 0: an access at offset >= bytes returns zero (loads) or is dropped (stores)
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
-}
-// Two consecutive gradient elements as a buffer load returns them (one register tuple), and their
-// float32 image in LDS.
-template <int DT> struct BufPair;
-template <> struct BufPair<TGRAD_C64> {
-  typedef u32x4 type;
-  static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, int voff) {
-    return __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 2);   // cache policy: non-temporal
-  }
-  static __device__ __forceinline__ void commit(float* dst, const type& v) { *reinterpret_cast<type*>(dst) = v; }
-};
-template <> struct BufPair<TGRAD_CBF16> {
-  typedef u32x2 type;
-  static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, int voff) {
-    return __builtin_amdgcn_raw_buffer_load_b64(r, voff, 0, 2);    // cache policy: non-temporal
-  }
-  static __device__ __forceinline__ void commit(float* dst, const type& v) {   // a bf16 is the upper half of a float32
-    u32x4 w;
-    w.x = v.x << 16;
-    w.y = v.x & 0xFFFF0000u;
-    w.z = v.y << 16;
-    w.w = v.y & 0xFFFF0000u;
-    *reinterpret_cast<u32x4*>(dst) = w;
-  }
-};
-
 // floats of LDS per wavefront: the tile (32 rows of K complex + one pad pair for the row pair past
 // an odd K) or, if larger, what TB x 64 committed pieces cover; a multiple of 4 (16-byte writes)
 __host__ __device__ inline int lproj_flat_slice(int K, int TB) {
@@ -802,111 +739,8 @@ __global__ __launch_bounds__(256, 2) void k_lproj_flat(const void* __restrict__ 
 // The rows of z are read straight into matrix-core operand registers: lane (row, half) keeps
 // elements k = half JT .. half JT + JT - 1 of its row (JT = a power of two >= K / 2, zero beyond
 // K), so step (j, part) pairs element j (lanes 0..31) with element JT + j (lanes 32..63).
-struct SparseAdam {
-  const int32_t* omega;
-  const uint32_t* tile_start;
-  const float2* gs;
-  float2* ms;
-  float* vs;
-  float beta1, beta2, inv_c1, inv_c2, eps, c_lambda;
-  int k_last;           // max(k, 1) - 1: a support position that is always safe to read
-};
-
-// AdamUpdate on sparse entry j (value x at support position oj, moments mm / v_old) and
-// tile[oj] += (-lr lambda) N_S[j]; `sD` is the flat LDS image of the W tile that starts at w_base.
-__device__ __forceinline__ void sparse_adam_entry(const SparseAdam& sp, uint32_t j, int32_t oj, float2 x,
-                                                  float2 mm, float v_old, int64_t w_base, float* sD) {
-  mm.x = sp.beta1 * mm.x + (1.f - sp.beta1) * x.x;
-  mm.y = sp.beta1 * mm.y + (1.f - sp.beta1) * x.y;
-  const float vv = sp.beta2 * v_old + (1.f - sp.beta2) * (x.x * x.x + x.y * x.y);
-  sp.ms[j] = mm;
-  sp.vs[j] = vv;
-  const float d = sp.c_lambda * sp.inv_c1 / (sqrtf(vv * sp.inv_c2) + sp.eps);
-  const int e = (int)((int64_t)oj - w_base);
-  sD[2 * e] += d * mm.x;
-  sD[2 * e + 1] += d * mm.y;
-}
-
 constexpr int kUpdPrefetch = 17;          // complex64 pairs of W per lane kept in flight during the MFMA phase (the
                                           // most; narrower last modes use 9 or 5: a tile of M-wide rows has M / 4)
-
-// float32 -> bf16 bit pattern, round to nearest, ties to even (NaN stays a quiet NaN).
-__device__ __forceinline__ uint32_t bf16_rne(float f) {
-  const uint32_t u = __float_as_uint(f);
-  if ((u & 0x7FFFFFFFu) > 0x7F800000u) return 0x7FC0u;
-  return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-__device__ __forceinline__ uint32_t bf16_pack(float re, float im) { return bf16_rne(re) | (bf16_rne(im) << 16); }
-
-// How the weight tensor is stored (section "Mixed precision training": weights may be kept in half
-// precision while the optimizer states stay in full precision).  A "piece" is 16 bytes of the W tile:
-// 2 complex64 elements, or 4 elements stored as bf16 (re, im) pairs.  apply() returns
-// decay * w + d for the piece, d read from the float32 image `sD` of the tile's update; bf16 weights
-// are widened exactly, updated in float32 and rounded once (nearest even).
-template <int WDT> struct WStore;
-template <> struct WStore<TGRAD_C64> {
-  typedef float4 raw;
-  static constexpr int kElems = 2;
-  static __device__ __forceinline__ raw* tile(void* w, int64_t w_base) {
-    return reinterpret_cast<raw*>(reinterpret_cast<float*>(w) + 2 * w_base);
-  }
-  static __device__ __forceinline__ raw apply(const raw o, const float* sD, int q, float decay) {
-    const float4 d = reinterpret_cast<const float4*>(sD)[q];
-    return make_float4(decay * o.x + d.x, decay * o.y + d.y, decay * o.z + d.z, decay * o.w + d.w);
-  }
-  static __device__ __forceinline__ void apply_one(void* w, int64_t e, const float* d, float decay) {
-    float2* p = reinterpret_cast<float2*>(w) + e;
-    const float2 o = *p;
-    *p = make_float2(decay * o.x + d[0], decay * o.y + d[1]);
-  }
-};
-template <> struct WStore<TGRAD_CBF16> {
-  typedef uint4 raw;
-  static constexpr int kElems = 4;
-  static __device__ __forceinline__ raw* tile(void* w, int64_t w_base) {
-    return reinterpret_cast<raw*>(reinterpret_cast<uint32_t*>(w) + w_base);
-  }
-  static __device__ __forceinline__ uint32_t one(uint32_t o, float dre, float dim, float decay) {
-    return bf16_pack(decay * __uint_as_float(o << 16) + dre, decay * __uint_as_float(o & 0xFFFF0000u) + dim);
-  }
-  static __device__ __forceinline__ raw apply(const raw o, const float* sD, int q, float decay) {
-    const float4 d0 = reinterpret_cast<const float4*>(sD)[2 * q];
-    const float4 d1 = reinterpret_cast<const float4*>(sD)[2 * q + 1];
-    return make_uint4(one(o.x, d0.x, d0.y, decay), one(o.y, d0.z, d0.w, decay), one(o.z, d1.x, d1.y, decay),
-                      one(o.w, d1.z, d1.w, decay));
-  }
-  static __device__ __forceinline__ void apply_one(void* w, int64_t e, const float* d, float decay) {
-    uint32_t* p = reinterpret_cast<uint32_t*>(w) + e;
-    *p = one(*p, d[0], d[1], decay);
-  }
-};
-__device__ __forceinline__ void claim_raw(uint4& r) { asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w)); }
-// 16-byte pieces of W through a buffer descriptor (range-checked by the hardware: no clamps, no lane
-// masks), non-temporal
-__device__ __forceinline__ void buffer_piece_load(float4& d, __amdgpu_buffer_rsrc_t r, int voff) {
-  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 2);
-  d = make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
-}
-__device__ __forceinline__ void buffer_piece_load(uint4& d, __amdgpu_buffer_rsrc_t r, int voff) {
-  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 2);
-  d = make_uint4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ void buffer_piece_store(const float4& d, __amdgpu_buffer_rsrc_t r, int voff) {
-  u32x4 v;
-  v.x = __float_as_uint(d.x);
-  v.y = __float_as_uint(d.y);
-  v.z = __float_as_uint(d.z);
-  v.w = __float_as_uint(d.w);
-  __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, 0, 2);
-}
-__device__ __forceinline__ void buffer_piece_store(const uint4& d, __amdgpu_buffer_rsrc_t r, int voff) {
-  u32x4 v;
-  v.x = d.x;
-  v.y = d.y;
-  v.z = d.z;
-  v.w = d.w;
-  __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, 0, 2);
-}
 
 template <int WDT, int W, int NTB, int JT, int UP>
 __global__ __launch_bounds__(64 * W, 2) void k_lupdate(const float* __restrict__ z,
@@ -1425,22 +1259,21 @@ __global__ void k_pack_fused_factor(const float2* __restrict__ U, int I2, int r,
   ut[(((size_t)ts * 8 + (jj >> 1)) * 64 + 32 * (m2 & 1) + il) * 2 + (jj & 1)] = u;
 }
 
-// tile_start[t] = #{ j : Omega_j < t * tile_elems }, t = 0 .. ntiles (Omega ascending).
-__global__ void k_tile_offsets(const int32_t* __restrict__ omega, int64_t k, int64_t tile_elems,
-                               int64_t ntiles, uint32_t* __restrict__ tile_start) {
+// tile_start[t] = support entries below tile t, t = 0 .. ntiles (Omega ascending).  Tile t of the tensor cut into
+// slabs of `slab_elems` elements and those into S tiles of `tile_elems` (the last one of a slab may be shorter)
+// starts at element (t / S) slab_elems + (t % S) tile_elems.  Flat tiles: S = 1, slab_elems = tile_elems.
+__global__ void k_tile_offsets(const int32_t* __restrict__ omega, int64_t k, int64_t tile_elems, uint32_t S,
+                               int64_t slab_elems, int64_t ntiles, uint32_t* __restrict__ tile_start) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t > ntiles) return;
-  const int64_t target = t * tile_elems;
+  const uint32_t sl = (uint32_t)t / S;                          // (tile counts fit 32 bits: I < 2^31)
+  const int64_t target = (int64_t)sl * slab_elems + (int64_t)((uint32_t)t - sl * S) * tile_elems;
   int64_t lo = 0, hi = k;                                      // first j in [0, k] with Omega_j >= target
   while (lo < hi) {
     const int64_t mid = (lo + hi) >> 1;
     if ((int64_t)omega[mid] < target) lo = mid + 1; else hi = mid;
   }
   tile_start[t] = (uint32_t)lo;
-}
-
-inline uint32_t magic_for(int d) {
-  return d <= 1 ? 0u : (uint32_t)((0x100000000ull + (uint64_t)d - 1) / (uint64_t)d);
 }
 
 int grid_for_tiles(int64_t ntiles, int blocks_per_cu) {
@@ -1505,11 +1338,11 @@ double launch_mfma_probe(hipStream_t s, int kind, int64_t iters, float* sink) {
   return instr * 2048.0;                                       // 16 x 16 x 4 multiply-adds
 }
 
-void launch_tile_offsets(hipStream_t s, const int32_t* omega, int64_t k, int64_t tile_elems,
-                         int64_t ntiles, uint32_t* tile_start) {
+void launch_tile_offsets(hipStream_t s, const int32_t* omega, int64_t k, int64_t tile_elems, int S,
+                         int64_t slab_elems, int64_t ntiles, uint32_t* tile_start) {
   const int64_t n = ntiles + 1;
-  k_tile_offsets<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(omega, k, tile_elems, ntiles,
-                                                                        tile_start);
+  k_tile_offsets<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(omega, k, tile_elems, (uint32_t)S,
+                                                                        slab_elems, ntiles, tile_start);
 }
 
 void launch_pack_fused_factor(hipStream_t s, const float2* U, int I2, int r, float2* fpad, float2* ut) {
@@ -1605,8 +1438,8 @@ void launch_lproj(hipStream_t s, const void* g, int dtype, const int32_t* omega,
 
 void launch_lupdate(hipStream_t s, const float2* z, const float2* U, const Stage& st, int W, void* w,
                     int wdtype, float decay, float c_alpha, const int32_t* omega, const uint32_t* tile_start,
-                    const float2* gs, float2* ms, float* vs, float beta1, float beta2, float inv_c1,
-                    float inv_c2, float eps, float c_lambda) {
+                    const float2* gs, float2* ms, float* vs, float beta1, float beta2, double inv_c1,
+                    double inv_c2, float eps, float c_lambda) {
   const int64_t A = st.A;
   const int K = st.K, M = st.M;
   if (A * M <= 0) return;
@@ -1614,7 +1447,7 @@ void launch_lupdate(hipStream_t s, const float2* z, const float2* U, const Stage
   const size_t lds = lupdate_lds_bytes(W, K, M);
   const int64_t ngroups = (ntiles + W - 1) / W;
   dim3 grid(1), block(64 * W);
-  SparseAdam sp{omega, tile_start, gs, ms, vs, beta1, beta2, inv_c1, inv_c2, eps, c_lambda, 0};
+  const SparseAdam sp = sparse_adam(omega, tile_start, gs, ms, vs, beta1, beta2, inv_c1, inv_c2, eps, c_lambda, 0);
   const float* zf = reinterpret_cast<const float*>(z);
   const int jt = lupdate_jt(K);
   const int up = (M + 3) / 4 <= 5 ? 5 : (M + 3) / 4 <= 9 ? 9 : kUpdPrefetch;
@@ -1652,7 +1485,7 @@ void launch_lupdate(hipStream_t s, const float2* z, const float2* U, const Stage
 void launch_lupdate_fused(hipStream_t s, const float2* y1, const float2* ut, int I2, int K2, const float2* U,
                           const Stage& st, void* w, int wdtype, float decay, float c_alpha, const int32_t* omega,
                           const uint32_t* tile_start, int64_t k, const float2* gs, float2* ms, float* vs,
-                          float beta1, float beta2, float inv_c1, float inv_c2, float eps, float c_lambda) {
+                          float beta1, float beta2, double inv_c1, double inv_c2, float eps, float c_lambda) {
   const int64_t A = st.A;
   const int K = st.K, M = st.M;
   if (A * M <= 0) return;
@@ -1664,8 +1497,8 @@ void launch_lupdate_fused(hipStream_t s, const float2* y1, const float2* ut, int
   const size_t lds = (size_t)W * ((kTileRows * 2 * M + 3) & ~3) * 4 + (size_t)16 * 16 * NT * 8;
   const int64_t ngroups = (nslabs + W - 1) / W;
   dim3 grid(1), block(64 * W);
-  SparseAdam sp{omega, tile_start, gs, ms, vs, beta1, beta2, inv_c1, inv_c2, eps, c_lambda,
-                (int)(k > 0 ? k - 1 : 0)};
+  const SparseAdam sp = sparse_adam(omega, tile_start, gs, ms, vs, beta1, beta2, inv_c1, inv_c2, eps, c_lambda,
+                                    (int)(k > 0 ? k - 1 : 0));
   FusedPrev fz{y1, ut, S, K2};
   const int up = (M + 3) / 4 <= 5 ? 5 : (M + 3) / 4 <= 9 ? 9 : kUpdPrefetch;
 #define TGRAD_LUF_M(JT2_, UP_, MS_)                                                                      \
@@ -1690,7 +1523,7 @@ void launch_lupdate_fused(hipStream_t s, const float2* y1, const float2* ut, int
     if (up == 5) TGRAD_LUF_U(JT2_, 5, 17); else if (up == 9) TGRAD_LUF_U(JT2_, 9, 33);                   \
     else TGRAD_LUF_U(JT2_, kUpdPrefetch, 65);                                                            \
   } while (0)
-  if (K2 <= 8) TGRAD_LUF(4); else if (K2 <= 16) TGRAD_LUF(8); else TGRAD_LUF(16);
+  TGRAD_LUF(16);                               // (K2 <= 16 goes to ends.hip)
 #undef TGRAD_LUF_U
 #undef TGRAD_LUF_M
 #undef TGRAD_LUF

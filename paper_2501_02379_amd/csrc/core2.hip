@@ -350,15 +350,14 @@ size_t core2_lds(int I1, int nt0, int nt1) {
 }  // namespace
 
 // Where the two leading modes (extents I0, I1, ranks M0, M1) and the core between them are one launch.  Against
-// the three kernels k_mid, k_core, k_expand, whole step, us (one launch / three):
-//   16x16x8x5 22.2 / 24.9, 32x32x12x7 28.2 / 32.4, 38x38x32 (r 9,9,8) 31.4 / 33.5, 48x16x48x25 45.8 / 46.8;
-//   46x46x64 (r 12,12,16) 32.9 / 32.0, 26x64x64 32.3 / 31.9, 64x64x32x17 (r 16,16,8,4) 41.0 / 37.1,
-//   90x77x45x23 (r 23,19,11,6) 99.6 / 89.9, 128x128x64x33 (r 32,32,16,8) 237 / 224:
+// the three kernels k_mid, k_core, k_expand, difference of a whole step in us (one launch - three):
+//   16x16x8x5 -2.7, 32x32x12x7 -4.2, 38x38x32 (r 9,9,8) -2.1, 48x16x48x25 -1.0;
+//   46x46x64 (r 12,12,16) +0.9, 26x64x64 +0.4, 64x64x32x17 (r 16,16,8,4) +3.9,
+//   90x77x45x23 (r 23,19,11,6) +9.7, 128x128x64x33 (r 32,32,16,8) +13:
 // up to 40 x 40 with ranks of one tile the saved launches win, above that the whole cache lines of the three
 // kernels do.  Not taken with `slabs_512` (the end kernels fused over at least 512 slabs) and a first extent up to
 // 16, nor above that line except for a first extent of 128 with 96 ... 384 columns where both sides are level
-// (128x40x32x13, r 8,6,32,12: 60.5 / 58.5; 128x128x32x13, r 32,32,32,12: 166 / 168; 128x33x32x9, r 8,6,20,5:
-// 49.0 / 49.2): the tests hold the launch structure of those two groups of shapes.
+// (128x40x32x13, r 8,6,32,12: +2.0; 128x128x32x13, r 32,32,32,12: -2; 128x33x32x9, r 8,6,20,5: -0.2): the tests hold the launch structure of those two groups of shapes.
 bool core2_kernel_fits(int I0, int I1, int M0, int M1, int64_t Cc, bool slabs_512) {
   if (M0 > 32 || M1 > 32 || Cc < 1) return false;
   if (I0 * I1 <= 1600 && M0 <= 16 && M1 <= 16) return !(slabs_512 && I0 <= 16);

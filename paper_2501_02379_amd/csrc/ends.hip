@@ -1,0 +1,752 @@
+// First and last kernel of a step on 16 x 16 matrix-core tiles, for narrow ranks and any extent of mode N-1:
+//   k_head  g_S <- G[Omega];  out[slab, m2, m3] = sum_{i2, i3} conj(U2[i2, m2]) conj(U3[i3, m3]) (G - Sparse(G, Omega))[slab, i2, i3]
+//   k_tail  W <- (1 - lr wd) W - lr (alpha z x_(N-1) U2 x_N U3 + lambda scatter(AdamUpdate(g_S)))
+// with modes N-1 (extent I2, rank M2 <= 32) and N (extent K, rank M <= 16) in one pass over G and one over W; a
+// slab is the I2 x K block of one set of leading indices.  (contract_mfma.hip has the same two passes on 32 x 32
+// tiles, for ranks that fill them: ends_kernel_fits has the line.)
+//
+// Why 16 x 16 (v_mfma_f32_16x16x4f32): a rank is padded to the tile, so a last-mode rank of 4 or 8 - which most
+// layers have - and a rank up to 16 of mode N-1 cost a half to a quarter of the matrix work of 32-wide tiles, and
+// fp32 matrix instructions occupy the SIMD's vector ALU: on 32-wide tiles both passes were bound by them, not by
+// memory.  The steps of the first contraction are counted in fours of K, not up to the next of two sizes.
+//
+// Measured (rocprofv3, us; before: 32 x 32 tiles, or separate kernels per mode where slabs were ragged or few):
+//   first pass 64x64x32x17 15.7 -> 10.8, 32x32x32x32x17 (bf16) 84.5 -> 35.3, 128x128x64x33 91.7 -> 57 (4.9 TB/s), bf16
+//   87.7 -> 47.8, 64x64x64x32 32.4 -> 20.2, 90x77x45x23 26.6 + 8.9 -> 20.8;
+//   last pass 128x128x64x33 112 -> 108 (5.1 TB/s), bf16 weights 98.4 -> 66.2, 90x77x45x23 10.6 + 26.8 -> 29.1.
+// Whole step: 16x16x8x5 21.7 -> 17.2, 64x64x32x17 39.1 -> 33.3, 90x77x45x23 89.7 -> 70.4, five-way 156 -> 111, 128x128x64x33
+// 224 -> 201, with bf16 gradients and weights 200 -> 142.
+//
+// Lanes: g = lane / 16, c = lane % 16.  A[i = c][k = g], B[k = g][j = c], D register r: D[i = 4 g + r][j = c].
+// Real columns are (m, p) = (re, im) parts interleaved: c = 2 m + p.
+//
+// Tiles of R rows of a slab (R = 32; 16 where rows are long: end_tile_rows) belong to one wavefront from the
+// first load to the last store and are staged in LDS private to it, as in contract_mfma.hip.  A wavefront walks
+// whole slabs where there are enough of them to occupy the chip; with fewer (SPLIT) the wavefronts of a
+// workgroup share a slab (k_head: partial sums added through LDS in a fixed order), or take any tile (k_tail).
+#include "device_common.h"
+#include "end_common.h"
+#include "launch_util.h"
+
+namespace tgrad {
+
+namespace {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ v4f mfma16(float a, float b, v4f c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+constexpr int kMaxWaves = 4;
+
+// v of the neighbouring lane (c ^ 1): the other part of the same complex column
+__device__ __forceinline__ float swap_parts(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true));
+}
+
+// dst[0 .. n) = gen(e), 8 loads per thread in flight
+template <typename Gen>
+__device__ __forceinline__ void stage_table(float2* dst, int n, int tid, int nthreads, Gen gen) {
+  for (int e0 = tid; e0 < n; e0 += nthreads * 8) {
+    float2 f[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) f[u] = gen(e0 + u * nthreads < n ? e0 + u * nthreads : e0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (e0 + u * nthreads < n) dst[e0 + u * nthreads] = f[u];
+  }
+}
+
+// ---- k_head -------------------------------------------------------------------------------------
+// Steps of four elements of K (T4) and rows per tile; pieces of two elements per lane that cover a tile.
+constexpr int head_rows(int T4) { return T4 <= 9 ? 32 : 16; }
+constexpr int head_pieces(int T4) { return T4 <= 9 ? T4 : (T4 + 1) / 2; }
+// floats of LDS per wavefront.  Rows of an even K are padded by one element, so that neighbouring rows do not
+// share banks; everything a commit writes and everything the steps past K read lies inside, and so do the
+// partial sums of a shared slab.
+__host__ __device__ constexpr int head_slice(int K, int T4) {
+  const int pad = (K & 1) ? 0 : 2;
+  const int committed = head_pieces(T4) * 64 * 4;                        // floats of G that a commit writes
+  const int a = committed + pad * (committed / (2 * K) + 1);
+  const int b = head_rows(T4) * (2 * K + pad);
+  const int c = (a > b ? a : b) + 8 * T4;                                // + what the last row's steps read past its end
+  return ((c > 1024 ? c : 1024) + 3) & ~3;                               // 1024: partial sums of two by two tiles
+}
+
+struct HeadArgs {
+  const void* g;
+  const int32_t* omega;
+  const uint32_t* tile_start;   // support entries below every tile of every slab
+  float2* gs;
+  const float2* U3;             // (K, M)
+  const float2* U2;             // (I2, M2)
+  int K, M, I2, M2, S, nslabs;  // S: tiles per slab
+  int split;
+  uint32_t magicK;
+  float* out;                   // (nslabs, M2, M) complex
+};
+
+// NC: tiles of 16 real columns (2 M), NM: tiles of 16 rows (M2)
+template <int DT, int T4, int NC, int NM>
+__global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
+  typedef typename BufPair<DT>::type Raw;
+  constexpr int R = head_rows(T4), TB = head_pieces(T4);
+  constexpr int kPiece = (int)sizeof(Raw), kElem = kPiece / 2;           // bytes of two elements, of one
+  extern __shared__ float smem[];
+  const int K = a.K, M = a.M, I2 = a.I2, M2 = a.M2, S = a.S;
+  const int pad = (K & 1) ? 0 : 2, stride = 2 * K + pad;
+  const int slice = head_slice(K, T4);
+  const int W = (int)blockDim.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 15, grp = lane >> 4;
+  float* sX = smem + wave * slice;
+  float2* sT = reinterpret_cast<float2*>(smem + W * slice);              // conj(U2) in operand order [16 rows][r][nm][lane]
+  const bool split = a.split != 0;
+  const int nw = (int)gridDim.x * W;
+  int slab = split ? (int)blockIdx.x : (int)blockIdx.x * W + wave, ts = split ? wave : 0;
+  if (ts >= S) slab = a.nslabs;                                          // (a shared slab with fewer tiles than wavefronts)
+  auto advance = [&](int& sl, int& t) {
+    if (split) {
+      t += W;
+      if (t >= S) sl = a.nslabs;
+    } else if (t + 1 < S) {
+      t += 1;
+    } else {
+      t = 0;
+      sl += nw;
+    }
+  };
+  const uint32_t slab_elems = (uint32_t)(I2 * K);
+  Raw raw[TB];
+  u32x2 lone = {0u, 0u};                                                 // last element of a tile with an odd count
+  int32_t my_om = 0;
+  // the tile being fetched (scalar): address, bytes in whole pieces (0: no tile), elements
+  const char* f_base = reinterpret_cast<const char*>(a.g);
+  int f_bytes = 0, f_n = 0;
+  auto set_fetch = [&](int sl, int t) {
+    const bool ok = sl < a.nslabs;
+    const int rows = I2 - t * R < R ? I2 - t * R : R;
+    f_n = ok ? rows * K : 0;
+    f_bytes = (f_n >> 1) * kPiece;
+    f_base = reinterpret_cast<const char*>(a.g) +
+             (ok ? ((uint64_t)(uint32_t)sl * slab_elems + (uint32_t)(t * R * K)) * (uint64_t)kElem : 0ull);
+  };
+  auto issue_piece = [&](int i) {
+    const int k = i / 4, left = f_bytes - k * 4 * 64 * kPiece;           // a descriptor per 4 pieces: immediates reach 4 KB
+    const __amdgpu_buffer_rsrc_t r = raw_buffer(f_base + k * 4 * 64 * kPiece, (uint32_t)(left > 0 ? left : 0));
+    raw[i] = BufPair<DT>::load(r, lane * kPiece + (i - 4 * k) * 64 * kPiece);
+  };
+  auto issue_lone = [&]() {
+    const __amdgpu_buffer_rsrc_t r = raw_buffer(f_base + f_bytes, (f_n & 1) ? kElem : 0);
+    if constexpr (DT == TGRAD_C64) {
+      lone = __builtin_amdgcn_raw_buffer_load_b64(r, lane * kElem, 0, 2);
+    } else {
+      lone.x = __builtin_amdgcn_raw_buffer_load_b32(r, lane * kElem, 0, 2);
+    }
+  };
+  auto issue_support = [&](uint32_t j0, uint32_t j1) {
+    const uint32_t cnt = j1 - j0;
+    const __amdgpu_buffer_rsrc_t ro = raw_buffer(a.omega + j0, (cnt < 64u ? cnt : 64u) * 4u);
+    my_om = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(ro, lane * 4, 0, 0);
+  };
+  // ---- prologue: the first tile, then the operands go in flight ----
+  set_fetch(slab, ts);
+#pragma unroll
+  for (int i = 0; i < TB; ++i) issue_piece(i);
+  issue_lone();
+  const uint32_t vzero = (uint32_t)opaque_zero();
+  auto range_of = [&](int sl, int t, uint32_t& j0, uint32_t& j1) {       // per-lane loads, made scalar when used
+    const uint32_t* tsb = a.tile_start + (sl < a.nslabs ? (int64_t)sl * S + t : 0);
+    j0 = tsb[vzero];
+    j1 = tsb[vzero + 1];
+  };
+  int nslab = slab, nts = ts;
+  if (slab < a.nslabs) advance(nslab, nts);
+  uint32_t cj0v, cj1v, nj0v, nj1v;
+  range_of(slab, ts, cj0v, cj1v);
+  range_of(nslab, nts, nj0v, nj1v);
+  float2 creg[T4][NC];                                                   // conj(U3)[4 j + g][column]
+#pragma unroll
+  for (int j = 0; j < T4; ++j)
+#pragma unroll
+    for (int nc = 0; nc < NC; ++nc) {
+      const int k = 4 * j + grp, m = (16 * nc + col) >> 1;
+      const bool in = k < K && m < M;
+      const float2 u = a.U3[in ? k * M + m : 0];
+      creg[j][nc] = in ? column_coef(make_float2(u.x, -u.y), col & 1) : make_float2(0.f, 0.f);
+    }
+  for (int e = lane; e < slice; e += 64) sX[e] = 0.f;                    // pads stay finite
+  stage_table(sT, ((I2 + 15) >> 4) * 4 * NM * 64, tid, (int)blockDim.x, [&](int e) -> float2 {
+    const int l = e & 63, nm = (e >> 6) % NM, r = ((e >> 6) / NM) & 3, q = (e >> 6) / (4 * NM);
+    const int i2 = 16 * q + 4 * (l >> 4) + r, m2 = 16 * nm + (l & 15);
+    const bool in = i2 < I2 && m2 < M2;
+    const float2 u = a.U2[in ? i2 * M2 + m2 : 0];
+    return in ? make_float2(u.x, -u.y) : make_float2(0.f, 0.f);
+  });
+  int wofs[TB];                                                          // where the lane's pieces lie in the slice
+#pragma unroll
+  for (int i = 0; i < TB; ++i) {
+    const int pi = lane + 64 * i;
+    wofs[i] = 4 * pi + (pad ? pad * (int)div_magic(2u * (uint32_t)pi, a.magicK) : 0);
+  }
+  uint32_t cj0 = __builtin_amdgcn_readfirstlane(cj0v), cj1 = __builtin_amdgcn_readfirstlane(cj1v);
+  if (slab >= a.nslabs) cj1 = cj0;
+  issue_support(cj0, cj1);
+  __syncthreads();                                                       // (the only barrier unless the slab is shared)
+  if (!split && slab >= a.nslabs) return;
+
+  // second-stage sums, unswapped: da = sum fr y, db = sum fi y (db of the other part is exchanged once per slab)
+  v4f da[NM][NC], db[NM][NC];
+  auto clear = [&]() {
+#pragma unroll
+    for (int nm = 0; nm < NM; ++nm)
+#pragma unroll
+      for (int nc = 0; nc < NC; ++nc) da[nm][nc] = db[nm][nc] = (v4f){0.f, 0.f, 0.f, 0.f};
+  };
+  auto value = [&](int nm, int nc, int r) -> float {                     // re: a_re - b_im, im: a_im + b_re
+    const float s = swap_parts(db[nm][nc][r]);
+    return (col & 1) ? da[nm][nc][r] + s : da[nm][nc][r] - s;
+  };
+  // out[sl, m2, column] through a descriptor that ends with the slab: rows past M2 are dropped by the range check,
+  // columns past 2 M by an offset beyond it
+  const int row_bytes = 2 * M * 4;
+  int ofs[NC];
+#pragma unroll
+  for (int nc = 0; nc < NC; ++nc)
+    ofs[nc] = 16 * nc + col < 2 * M ? 4 * grp * row_bytes + (16 * nc + col) * 4 : 0x40000000;
+  auto store_at = [&](int sl, int nm, int nc, int r, float v) {
+    const int skip = (16 * nm + r) * row_bytes, left = M2 * row_bytes - skip;
+    const __amdgpu_buffer_rsrc_t ro =
+        raw_buffer(reinterpret_cast<const char*>(a.out) + (int64_t)sl * M2 * row_bytes + skip, left > 0 ? left : 0);
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), ro, ofs[nc], 0, 0);
+  };
+  clear();
+  bool pending = false;
+  int pending_slab = 0;
+  auto store_slab = [&]() {
+#pragma unroll
+    for (int nm = 0; nm < NM; ++nm)
+#pragma unroll
+      for (int nc = 0; nc < NC; ++nc)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) store_at(pending_slab, nm, nc, r, value(nm, nc, r));
+    clear();
+  };
+  while (slab < a.nslabs) {
+    const uint32_t e_base = (uint32_t)slab * slab_elems + (uint32_t)(ts * R * K);   // I < 2^31
+    const int n_e = f_n, rows = I2 - ts * R;
+    wave_sync();                                                         // previous tile's LDS reads are done
+    asm volatile("" : "+v"(my_om), "+v"(lone));
+#pragma unroll
+    for (int i = 0; i < TB; ++i) asm volatile("" : "+v"(raw[i]));        // one wait for the whole batch
+#pragma unroll
+    for (int i = 0; i < TB; ++i) {
+      float2* d = reinterpret_cast<float2*>(sX + wofs[i]);
+      if constexpr (DT == TGRAD_C64) {
+        d[0] = make_float2(__uint_as_float(raw[i].x), __uint_as_float(raw[i].y));
+        d[1] = make_float2(__uint_as_float(raw[i].z), __uint_as_float(raw[i].w));
+      } else {                                                           // a bf16 is the upper half of a float32
+        d[0] = make_float2(__uint_as_float(raw[i].x << 16), __uint_as_float(raw[i].x & 0xFFFF0000u));
+        d[1] = make_float2(__uint_as_float(raw[i].y << 16), __uint_as_float(raw[i].y & 0xFFFF0000u));
+      }
+    }
+    if (n_e & 1) {                                                       // (K is odd: no padding in the slice)
+      wave_sync();
+      if (lane == 0) {
+        float2* d = reinterpret_cast<float2*>(sX + 2 * (n_e - 1));
+        if constexpr (DT == TGRAD_C64) *d = make_float2(__uint_as_float(lone.x), __uint_as_float(lone.y));
+        else *d = make_float2(__uint_as_float(lone.x << 16), __uint_as_float(lone.x & 0xFFFF0000u));
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (pending) {                                                       // (stores here, not in front of the wait above)
+      store_slab();
+      pending = false;
+    }
+    const int32_t cur_om = my_om;
+    set_fetch(nslab, nts);
+    int nnslab = nslab, nnts = nts;
+    if (nslab < a.nslabs) advance(nnslab, nnts);
+    const uint32_t nj0 = __builtin_amdgcn_readfirstlane(nj0v);
+    const uint32_t nj1 = nslab < a.nslabs ? __builtin_amdgcn_readfirstlane(nj1v) : nj0;
+    wave_sync();
+    {                                                                    // Sparse(G, Omega): hand the values over, then remove them
+      auto take = [&](uint32_t j, int32_t oj) {
+        const uint32_t e = (uint32_t)oj - e_base;
+        float2* p = reinterpret_cast<float2*>(sX + 2 * e + (pad ? (uint32_t)pad * div_magic(e, a.magicK) : 0u));
+        a.gs[cj0 + j] = *p;
+        *p = make_float2(0.f, 0.f);
+      };
+      const uint32_t cnt = cj1 - cj0;
+      if ((uint32_t)lane < cnt) take((uint32_t)lane, cur_om);
+      if (cnt > 64u)
+        for (uint32_t j = 64u + lane; j < cnt; j += 64) take(j, a.omega[cj0 + j]);
+    }
+    wave_sync();
+    __builtin_amdgcn_s_setprio(1);
+    // The next tile's loads go between the steps of the first contraction: a load waits at issue until the memory
+    // pipeline takes it, and there that wait lies under matrix instructions.
+#pragma unroll
+    for (int h = 0; h < R / 16; ++h) {
+      if (h == 0 || rows > 16 * h) {                                     // (wave-uniform)
+        v4f y[NC], yi[NC];                                               // two chains: half the depth and the rounding of one
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) y[nc] = yi[nc] = (v4f){0.f, 0.f, 0.f, 0.f};
+        const float* xa = sX + (16 * h + col) * stride + 2 * grp;
+        constexpr int kFetch = 4;                                        // operands fetched ahead
+        float2 x[kFetch];
+#pragma unroll
+        for (int u = 0; u < kFetch && u < T4; ++u) x[u] = *reinterpret_cast<const float2*>(xa + 8 * u);
+#pragma unroll
+        for (int j = 0; j < T4; ++j) {
+          const float2 xv = x[j % kFetch];
+          if (j + kFetch < T4) x[j % kFetch] = *reinterpret_cast<const float2*>(xa + 8 * (j + kFetch));
+#pragma unroll
+          for (int nc = 0; nc < NC; ++nc) {
+            y[nc] = mfma16(xv.x, creg[j][nc].x, y[nc]);
+            yi[nc] = mfma16(xv.y, creg[j][nc].y, yi[nc]);
+          }
+          if (h == 0 && j < TB) {
+            __builtin_amdgcn_sched_barrier(0);
+            issue_piece(j);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        const float2* ft = sT + (size_t)(ts * (R / 16) + h) * (4 * NM * 64) + lane;
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) y[nc] += yi[nc];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int nm = 0; nm < NM; ++nm) {
+            const float2 f = ft[(r * NM + nm) * 64];
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) {
+              da[nm][nc] = mfma16(f.x, y[nc][r], da[nm][nc]);
+              db[nm][nc] = mfma16(f.y, y[nc][r], db[nm][nc]);
+            }
+          }
+      }
+    }
+    issue_lone();
+    issue_support(nj0, nj1);
+    uint32_t nnj0v, nnj1v;
+    range_of(nnslab, nnts, nnj0v, nnj1v);
+    __builtin_amdgcn_s_setprio(0);
+    if (!split && ts == S - 1) {
+      pending = true;
+      pending_slab = slab;
+    }
+    slab = nslab;
+    ts = nts;
+    nslab = nnslab;
+    nts = nnts;
+    cj0 = nj0;
+    cj1 = nj1;
+    nj0v = nnj0v;
+    nj1v = nnj1v;
+  }
+  if (pending) store_slab();
+  if (split) {                                                           // the wavefronts' parts of the slab, in order
+    __syncthreads();
+    constexpr int kPart = NM * NC * 4 * 64;
+#pragma unroll
+    for (int nm = 0; nm < NM; ++nm)
+#pragma unroll
+      for (int nc = 0; nc < NC; ++nc)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sX[((nm * NC + nc) * 4 + r) * 64 + lane] = value(nm, nc, r);
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < NM * NC * 4; ++e)
+      if (e % W == wave) {
+        float v = 0.f;
+        for (int w = 0; w < W; ++w) v += smem[w * slice + e * 64 + lane];
+        store_at((int)blockIdx.x, e / (4 * NC), (e >> 2) % NC, e & 3, v);
+      }
+    static_assert(kPart <= 1024, "head_slice");
+  }
+}
+
+// ---- k_tail -------------------------------------------------------------------------------------
+// Stage A  D'[(m3, p), i2] = sum_m2 Y1[m2, (m3, p)] U2[i2, m2]:  A operand = rows of the slab's Y1 (registers, parts
+//   chosen per p once per slab), B operand = U2 from the LDS table; lane (i2 = c, g) then holds (re, im) of elements
+//   m3 = 8 nc + 2 g + {0, 1} of row i2 - the A operand of stage B as it stands.
+// Stage B  tile[i2, column] = sum_m3 D'[.., i2] (c_alpha U3)[column, m3], 16 columns at a time, coefficients in
+//   registers; the flat image of the tile in LDS then takes the sparse entries and is streamed into W.
+// A last mode of 8 m + 1 complex columns has its last column done by vector arithmetic, not by a tile of its own.
+constexpr int tail_rows(int CT) { return CT <= 4 ? 32 : 16; }
+constexpr int tail_pieces(int CT) { return CT == 2 ? 5 : CT == 3 ? 7 : 9; }   // complex64 pieces per lane of a tile
+__host__ __device__ constexpr int tail_slice(int M, int R) { return (R * 2 * M + 3) & ~3; }
+
+struct TailArgs {
+  const float2* y1;             // (nslabs, K2, K) complex
+  const float2* U2;             // (I2, K2)
+  const float2* U3;             // (M, K)
+  void* w;
+  int K, M, I2, K2, S, nslabs;
+  int split;                    // 1: single tiles are dealt to the wavefronts; 0: whole slabs
+  float decay, c_alpha;
+};
+
+template <int WDT, int CT, int NC, int SA>
+__global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAdam sp) {
+  typedef WStore<WDT> WS;
+  typedef typename WS::raw wraw;
+  constexpr int R = tail_rows(CT);
+  constexpr int kPre = WS::kElems == 2 ? tail_pieces(CT) : (tail_pieces(CT) + 1) / 2;
+  constexpr int kElem = 16 / WS::kElems;                                 // bytes of an element of W
+  extern __shared__ float smem[];
+  const int K = a.K, M = a.M, I2 = a.I2, K2 = a.K2, S = a.S;
+  const int N2 = 2 * M;
+  const int slice = tail_slice(M, R);
+  const int W = (int)blockDim.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 15, grp = lane >> 4, part = lane & 1;
+  float* sD = smem + wave * slice;
+  float2* sT = reinterpret_cast<float2*>(smem + W * slice);              // U2 in operand order [16 rows][step][lane]
+  const bool vtail = (N2 & 15) == 2;
+  const int NT = vtail ? N2 >> 4 : (N2 + 15) >> 4;                       // column tiles (<= CT: host)
+  const bool split = a.split != 0;
+  const int nw = (int)gridDim.x * W;
+  const int first = (int)blockIdx.x * W + wave;
+  int slab = split ? first / S : first, ts = split ? first - slab * S : 0;
+  auto advance = [&](int& sl, int& t) {
+    if (split) {
+      t += nw;
+      sl += t / S;
+      t = t % S;
+    } else if (t + 1 < S) {
+      t += 1;
+    } else {
+      t = 0;
+      sl += nw;
+    }
+  };
+  const uint32_t slab_elems = (uint32_t)(I2 * M);
+  wraw wpre[kPre];
+  uint32_t wl0 = 0, wl1 = 0;                                             // elements past the last whole piece of the tile
+  auto tile_elems = [&](int t) -> int { return (I2 - t * R < R ? I2 - t * R : R) * M; };
+  auto tile_addr = [&](int sl, int t) -> char* {
+    return reinterpret_cast<char*>(a.w) + ((uint64_t)(uint32_t)sl * slab_elems + (uint32_t)(t * R * M)) * (uint64_t)kElem;
+  };
+  auto issue_w = [&](int sl, int t) {                                    // (no tile: empty descriptors)
+    const bool ok = sl < a.nslabs;
+    const int n = ok ? tile_elems(t) : 0, n4 = n / WS::kElems;
+    const char* base = ok ? tile_addr(sl, t) : reinterpret_cast<const char*>(a.w);
+#pragma unroll
+    for (int k = 0; k < (kPre + 3) / 4; ++k) {                           // a descriptor per 4 pieces: immediates reach 4 KB
+      const int left = n4 * 16 - k * 4096;
+      const __amdgpu_buffer_rsrc_t r = raw_buffer(base + k * 4096, (uint32_t)(left > 0 ? left : 0));
+#pragma unroll
+      for (int i = 4 * k; i < 4 * k + 4 && i < kPre; ++i) buffer_piece_load(wpre[i], r, lane * 16 + (i - 4 * k) * 1024);
+    }
+    const __amdgpu_buffer_rsrc_t rl = raw_buffer(base + n4 * 16, (uint32_t)((n - n4 * WS::kElems) * kElem));
+    if constexpr (WDT == TGRAD_C64) {
+      const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rl, lane * kElem, 0, 0);
+      wl0 = v.x;
+      wl1 = v.y;
+    } else {
+      wl0 = __builtin_amdgcn_raw_buffer_load_b32(rl, lane * kElem, 0, 0);
+    }
+  };
+  int32_t my_om = 0;
+  u32x2 my_g, my_m;
+  uint32_t my_v = 0;
+  auto issue_sparse = [&](uint32_t j0, uint32_t j1) {                    // the first 64 entries of a tile
+    const uint32_t n = j1 - j0 < 64u ? j1 - j0 : 64u;
+    my_om = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(raw_buffer(sp.omega + j0, n * 4u), lane * 4, 0, 0);
+    my_g = __builtin_amdgcn_raw_buffer_load_b64(raw_buffer(sp.gs + j0, n * 8u), lane * 8, 0, 0);
+    my_m = __builtin_amdgcn_raw_buffer_load_b64(raw_buffer(sp.ms + j0, n * 8u), lane * 8, 0, 0);
+    my_v = __builtin_amdgcn_raw_buffer_load_b32(raw_buffer(sp.vs + j0, n * 4u), lane * 4, 0, 0);
+  };
+  float2 y[SA][NC];
+  auto fetch_y = [&](int sl) {                                           // rows / columns past the end meet zero coefficients
+    const float2* yp = a.y1 + (int64_t)sl * K2 * K;
+#pragma unroll
+    for (int s = 0; s < SA; ++s)
+#pragma unroll
+      for (int nc = 0; nc < NC; ++nc) {
+        const int m2 = 4 * s + grp, m3 = 8 * nc + (col >> 1);
+        y[s][nc] = yp[(m2 < K2 ? m2 : K2 - 1) * K + (m3 < K ? m3 : K - 1)];
+      }
+  };
+  const uint32_t vzero = (uint32_t)opaque_zero();
+  auto range_of = [&](int sl, int t, uint32_t& j0, uint32_t& j1) {
+    const uint32_t* tsb = sp.tile_start + (sl < a.nslabs ? (int64_t)sl * S + t : 0);
+    j0 = tsb[vzero];
+    j1 = tsb[vzero + 1];
+  };
+  // ---- prologue: the first tile of W, its operands and the tables go in flight ----
+  issue_w(slab, ts);
+  int nslab = slab, nts = ts;
+  if (slab < a.nslabs) advance(nslab, nts);
+  uint32_t cj0v, cj1v, nj0v, nj1v;
+  range_of(slab, ts, cj0v, cj1v);
+  range_of(nslab, nts, nj0v, nj1v);
+  fetch_y(slab < a.nslabs ? slab : 0);
+  float2 cf[CT][NC][2], ct[NC][2];                                       // (c_alpha U3)[column][8 nc + 2 g + u]
+#pragma unroll
+  for (int nc = 0; nc < NC; ++nc)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int k = 8 * nc + 2 * grp + u;
+#pragma unroll
+      for (int i = 0; i < CT; ++i) {
+        const int m = (16 * i + col) >> 1;
+        const bool in = k < K && m < M;
+        const float2 f = a.U3[in ? m * K + k : 0];
+        cf[i][nc][u] = in ? column_coef(make_float2(a.c_alpha * f.x, a.c_alpha * f.y), part) : make_float2(0.f, 0.f);
+      }
+      const float2 f = a.U3[k < K ? (M - 1) * K + k : 0];
+      ct[nc][u] = k < K ? make_float2(a.c_alpha * f.x, a.c_alpha * f.y) : make_float2(0.f, 0.f);
+    }
+  stage_table(sT, ((I2 + 15) >> 4) * SA * 64, tid, (int)blockDim.x, [&](int e) -> float2 {
+    const int l = e & 63, s = (e >> 6) % SA, q = (e >> 6) / SA;
+    const int i2 = 16 * q + (l & 15), m2 = 4 * s + (l >> 4);
+    const bool in = i2 < I2 && m2 < K2;
+    const float2 u = a.U2[in ? i2 * K2 + m2 : 0];
+    return in ? u : make_float2(0.f, 0.f);
+  });
+  uint32_t cj0 = __builtin_amdgcn_readfirstlane(cj0v), cj1 = __builtin_amdgcn_readfirstlane(cj1v);
+  if (slab >= a.nslabs) cj1 = cj0;
+  issue_sparse(cj0, cj1);
+  __syncthreads();                                                       // the only workgroup barrier
+  bool fresh = true;                                                     // y as loaded, not yet in operand form
+  while (slab < a.nslabs) {
+    const uint32_t w_base = (uint32_t)slab * slab_elems + (uint32_t)(ts * R * M);
+    const int n_w = tile_elems(ts), n4 = n_w / WS::kElems, rows = I2 - ts * R;
+    char* w_tile = tile_addr(slab, ts);
+    if (fresh) {
+      // row (m3, p): re(u y) = ur yr - ui yi, im(u y) = ur yi + ui yr
+#pragma unroll
+      for (int s = 0; s < SA; ++s)
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) {
+          const float2 v = y[s][nc];
+          y[s][nc] = part ? make_float2(v.y, v.x) : make_float2(v.x, -v.y);
+        }
+      fresh = false;
+    }
+    wave_sync();                                                         // previous tile's LDS reads are done
+#pragma unroll
+    for (int h = 0; h < R / 16; ++h) {
+      if (h == 0 || rows > 16 * h) {                                     // (wave-uniform)
+        v4f dz[NC], dzi[NC];                                             // two chains (see k_head)
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) dz[nc] = dzi[nc] = (v4f){0.f, 0.f, 0.f, 0.f};
+        const float2* ft = sT + (size_t)(ts * (R / 16) + h) * (SA * 64) + lane;
+#pragma unroll
+        for (int s = 0; s < SA; ++s) {
+          const float2 f = ft[s * 64];
+#pragma unroll
+          for (int nc = 0; nc < NC; ++nc) {
+            dz[nc] = mfma16(y[s][nc].x, f.x, dz[nc]);
+            dzi[nc] = mfma16(y[s][nc].y, f.y, dzi[nc]);
+          }
+        }
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) dz[nc] += dzi[nc];
+        float* sR = sD + (16 * h + 4 * grp) * N2 + col;
+#pragma unroll
+        for (int i = 0; i < CT; ++i) {
+          if (i < NT) {                                                  // (wave-uniform)
+            v4f o = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc)
+#pragma unroll
+              for (int u = 0; u < 2; ++u) {
+                o = mfma16(dz[nc][2 * u], cf[i][nc][u].x, o);
+                o = mfma16(dz[nc][2 * u + 1], cf[i][nc][u].y, o);
+              }
+            if (16 * i + col < N2) {
+#pragma unroll
+              for (int r = 0; r < 4; ++r) sR[r * N2 + 16 * i] = o[r];   // (rows past the slab's end: written, not streamed)
+            }
+          }
+        }
+        if (vtail) {
+          float pre = 0.f, pim = 0.f;
+#pragma unroll
+          for (int nc = 0; nc < NC; ++nc)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              const float zr = dz[nc][2 * u], zi = dz[nc][2 * u + 1];
+              pre += zr * ct[nc][u].x - zi * ct[nc][u].y;
+              pim += zr * ct[nc][u].y + zi * ct[nc][u].x;
+            }
+          pre += __shfl_xor(pre, 16, 64);
+          pim += __shfl_xor(pim, 16, 64);
+          pre += __shfl_xor(pre, 32, 64);
+          pim += __shfl_xor(pim, 32, 64);
+          if (grp == 0)
+            *reinterpret_cast<float2*>(&sD[(16 * h + col) * N2 + N2 - 2]) = make_float2(pre, pim);
+        }
+      }
+    }
+    if (nslab < a.nslabs && nslab != slab) {                             // (wave-uniform) the next tile opens another slab
+      fetch_y(nslab);
+      fresh = true;
+    }
+    wave_sync();
+    // ---- AdamUpdate on the sparse values that live in this tile; add lambda N_S into the tile ----
+    {
+      const uint32_t cnt = cj1 - cj0;
+      if ((uint32_t)lane < cnt)
+        sparse_adam_entry(sp, cj0 + lane, my_om, make_float2(__uint_as_float(my_g.x), __uint_as_float(my_g.y)),
+                          make_float2(__uint_as_float(my_m.x), __uint_as_float(my_m.y)), __uint_as_float(my_v),
+                          (int64_t)w_base, sD);
+      if (cnt > 64u)                                                     // rare: more than 64 entries in one tile
+        for (uint32_t j = cj0 + 64u + lane; j < cj1; j += 64)
+          sparse_adam_entry(sp, j, sp.omega[j], sp.gs[j], sp.ms[j], sp.vs[j], (int64_t)w_base, sD);
+    }
+    wave_sync();
+    // ---- stream the tile into W ----
+#pragma unroll
+    for (int i = 0; i < kPre; ++i) claim_raw(wpre[i]);
+#pragma unroll
+    for (int k = 0; k < (kPre + 3) / 4; ++k) {
+      const int left = n4 * 16 - k * 4096;
+      const __amdgpu_buffer_rsrc_t r = raw_buffer(w_tile + k * 4096, (uint32_t)(left > 0 ? left : 0));
+#pragma unroll
+      for (int i = 4 * k; i < 4 * k + 4 && i < kPre; ++i) {
+        const int q = lane + i * 64;                                     // (the LDS read stays inside the slice)
+        buffer_piece_store(WS::apply(wpre[i], sD, q < n4 ? q : 0, a.decay), r, lane * 16 + (i - 4 * k) * 1024);
+      }
+    }
+    {                                                                    // elements past the last whole piece
+      const int e = n4 * WS::kElems + lane;
+      if (e < n_w) {
+        if constexpr (WDT == TGRAD_C64)
+          *reinterpret_cast<float2*>(w_tile + (int64_t)e * kElem) =
+              make_float2(a.decay * __uint_as_float(wl0) + sD[2 * e], a.decay * __uint_as_float(wl1) + sD[2 * e + 1]);
+        else
+          *reinterpret_cast<uint32_t*>(w_tile + (int64_t)e * kElem) =
+              WStore<TGRAD_CBF16>::one(wl0, sD[2 * e], sD[2 * e + 1], a.decay);
+      }
+    }
+    // ---- the next tile goes in flight ----
+    issue_w(nslab, nts);
+    int nnslab = nslab, nnts = nts;
+    if (nslab < a.nslabs) advance(nnslab, nnts);
+    cj0 = __builtin_amdgcn_readfirstlane(nj0v);
+    cj1 = nslab < a.nslabs ? __builtin_amdgcn_readfirstlane(nj1v) : cj0;
+    issue_sparse(cj0, cj1);
+    range_of(nnslab, nnts, nj0v, nj1v);
+    slab = nslab;
+    ts = nts;
+    nslab = nnslab;
+    nts = nnts;
+  }
+}
+
+// ---- host side ----------------------------------------------------------------------------------
+
+int steps_class(int K) {                        // k_head's T4
+  const int t = (K + 3) / 4;
+  if (K <= 33) return t <= 3 ? 3 : t <= 5 ? 5 : t <= 7 ? 7 : 9;
+  return t <= 13 ? 13 : 17;
+}
+int columns_class(int M) { return M <= 17 ? 2 : M <= 25 ? 3 : M <= 33 ? 4 : 9; }   // k_tail's CT
+int step_class(int K2) { return K2 <= 8 ? 2 : K2 <= 16 ? 4 : 8; }                  // k_tail's SA
+
+size_t head_lds(int W, int K, int I2, int M2) {
+  return (size_t)W * head_slice(K, steps_class(K)) * 4 + (size_t)((I2 + 15) / 16) * 4 * ((M2 + 15) / 16) * 512;
+}
+size_t tail_lds(int W, int M, int I2, int K2) {
+  return (size_t)W * tail_slice(M, end_tile_rows(M)) * 4 + (size_t)((I2 + 15) / 16) * step_class(K2) * 512;
+}
+
+// From this many slabs on a wavefront takes whole ones (one wavefront per SIMD of the chip).
+constexpr int64_t kWholeSlabs = 1024;
+
+// Workgroups of a launch over `units` wavefronts' worth of work
+template <typename Kern>
+unsigned end_grid(Kern kern, int W, size_t lds, int64_t units) {
+  const int64_t groups = (units + W - 1) / W, cap = (int64_t)compute_units() * resident_blocks(kern, 64 * W, lds, 8);
+  return (unsigned)(groups < cap ? groups : cap);
+}
+
+}  // namespace
+
+int end_tile_rows(int K) { return K <= 33 ? 32 : 16; }
+
+// Which shapes take the two kernels: K = extent of the last mode, r its rank, I2 / r2 extent and rank of mode N-1.
+// (With both ranks in the upper half of a 32-wide tile, whole 32-row tiles and at least 512 slabs the 32 x 32 kernels are
+// the better ones - make_plan prefers them: whole step 128x128x128x65, r 32,32,32,16: 747 us against 787 with these;
+// 128x128x64x33, r 64,64,32,16: 413 against 431.)
+bool ends_kernel_fits(int K, int r, int I2, int r2) {
+  if (K < 2 || K > 68 || r > 16 || r2 > 32 || I2 > TGRAD_MAX_EXTENT) return false;
+  return head_lds(kMaxWaves, K, I2, r2) <= kLdsLimit / 2 && tail_lds(kMaxWaves, K, I2, r2) <= kLdsLimit / 2;
+}
+
+void launch_head(hipStream_t s, const void* g, int dtype, const int32_t* omega, const uint32_t* tile_start, float2* gs,
+                 const float2* U3, int K, int M, const float2* U2, int I2, int M2, int64_t nslabs, float2* out) {
+  const int R = end_tile_rows(K), S = (I2 + R - 1) / R;
+  const bool split = nslabs < kWholeSlabs && S > 1;
+  const int W = split ? (S < kMaxWaves ? S : kMaxWaves) : nslabs >= kWholeSlabs ? kMaxWaves : 1;
+  const size_t lds = head_lds(W, K, I2, M2);
+  HeadArgs a{g, omega, tile_start, gs, U3, U2, K, M, I2, M2, S, (int)nslabs, split ? 1 : 0, magic_for(K),
+             reinterpret_cast<float*>(out)};
+  const int t4 = steps_class(K), nc = M <= 8 ? 1 : 2, nm = M2 <= 16 ? 1 : 2;
+#define TGRAD_HEAD(DT_, T_, C_, M_)                                                                          \
+  do {                                                                                                       \
+    allow_lds(k_head<DT_, T_, C_, M_>, lds);                                                                 \
+    const unsigned grid = split ? (unsigned)nslabs : end_grid(k_head<DT_, T_, C_, M_>, W, lds, nslabs);      \
+    k_head<DT_, T_, C_, M_><<<dim3(grid), dim3(64 * W), lds, s>>>(a);                                        \
+  } while (0)
+#define TGRAD_HEAD_M(DT_, T_)                                                                                \
+  do {                                                                                                       \
+    if (nc == 1) { if (nm == 1) TGRAD_HEAD(DT_, T_, 1, 1); else TGRAD_HEAD(DT_, T_, 1, 2); }                 \
+    else { if (nm == 1) TGRAD_HEAD(DT_, T_, 2, 1); else TGRAD_HEAD(DT_, T_, 2, 2); }                         \
+  } while (0)
+#define TGRAD_HEAD_T(DT_)                                                                                    \
+  do {                                                                                                       \
+    if (t4 == 3) TGRAD_HEAD_M(DT_, 3); else if (t4 == 5) TGRAD_HEAD_M(DT_, 5); else if (t4 == 7) TGRAD_HEAD_M(DT_, 7); \
+    else if (t4 == 9) TGRAD_HEAD_M(DT_, 9); else if (t4 == 13) TGRAD_HEAD_M(DT_, 13); else TGRAD_HEAD_M(DT_, 17); \
+  } while (0)
+  if (dtype == TGRAD_C64) TGRAD_HEAD_T(TGRAD_C64); else TGRAD_HEAD_T(TGRAD_CBF16);
+#undef TGRAD_HEAD_T
+#undef TGRAD_HEAD_M
+#undef TGRAD_HEAD
+}
+
+void launch_tail(hipStream_t s, const float2* y1, const float2* U3, int K, int M, const float2* U2, int I2, int K2,
+                 int64_t nslabs, void* w, int wdtype, float decay, float c_alpha, const int32_t* omega,
+                 const uint32_t* tile_start, const float2* gs, float2* ms, float* vs, float beta1, float beta2,
+                 double inv_c1, double inv_c2, float eps, float c_lambda) {
+  const int R = end_tile_rows(M), S = (I2 + R - 1) / R;
+  const bool split = nslabs < kWholeSlabs;
+  const int64_t units = split ? nslabs * S : nslabs;
+  const int W = units >= kWholeSlabs ? kMaxWaves : 1;
+  const size_t lds = tail_lds(W, M, I2, K2);
+  TailArgs a{y1, U2, U3, w, K, M, I2, K2, S, (int)nslabs, split ? 1 : 0, decay, c_alpha};
+  const SparseAdam sp = sparse_adam(omega, tile_start, gs, ms, vs, beta1, beta2, inv_c1, inv_c2, eps, c_lambda, 0);
+  const int ct = columns_class(M), nc = K <= 8 ? 1 : 2, sa = step_class(K2);
+#define TGRAD_TAIL(WD_, T_, C_, A_)                                                                          \
+  do {                                                                                                       \
+    allow_lds(k_tail<WD_, T_, C_, A_>, lds);                                                                 \
+    const unsigned grid = end_grid(k_tail<WD_, T_, C_, A_>, W, lds, units);                                  \
+    k_tail<WD_, T_, C_, A_><<<dim3(grid), dim3(64 * W), lds, s>>>(a, sp);                                    \
+  } while (0)
+#define TGRAD_TAIL_A(WD_, T_, C_)                                                                            \
+  do {                                                                                                       \
+    if (sa == 2) TGRAD_TAIL(WD_, T_, C_, 2); else if (sa == 4) TGRAD_TAIL(WD_, T_, C_, 4); else TGRAD_TAIL(WD_, T_, C_, 8); \
+  } while (0)
+#define TGRAD_TAIL_T(WD_)                                                                                    \
+  do {                                                                                                       \
+    if (ct == 2) { if (nc == 1) TGRAD_TAIL_A(WD_, 2, 1); else TGRAD_TAIL_A(WD_, 2, 2); }                     \
+    else if (ct == 3) { if (nc == 1) TGRAD_TAIL_A(WD_, 3, 1); else TGRAD_TAIL_A(WD_, 3, 2); }                \
+    else if (ct == 4) { if (nc == 1) TGRAD_TAIL_A(WD_, 4, 1); else TGRAD_TAIL_A(WD_, 4, 2); }                \
+    else { if (nc == 1) TGRAD_TAIL_A(WD_, 9, 1); else TGRAD_TAIL_A(WD_, 9, 2); }                             \
+  } while (0)
+  if (wdtype == TGRAD_C64) TGRAD_TAIL_T(TGRAD_C64); else TGRAD_TAIL_T(TGRAD_CBF16);
+#undef TGRAD_TAIL_T
+#undef TGRAD_TAIL_A
+#undef TGRAD_TAIL
+}
+
+}  // namespace tgrad

@@ -20,21 +20,20 @@ inline bool allow_lds(Kern kern, size_t bytes) {
 }
 
 // Workgroups of `kern` that are resident on one compute unit at a time (registers, LDS), asked of
-// the runtime once per kernel and LDS size.  The tile loops are persistent (stride = grid size), so
+// the runtime once per kernel, workgroup and LDS size (`most` bounds the answer).  The tile loops are persistent (stride = grid size), so
 // the grid is exactly one resident set: more workgroups would run as a ragged second round.
 template <typename Kern>
-int resident_blocks(Kern kern, int threads, size_t lds) {
+int resident_blocks(Kern kern, int threads, size_t lds, int most = 4) {
   static std::mutex mu;
-  static std::map<std::pair<const void*, size_t>, int> cache;
-  const std::pair<const void*, size_t> key(reinterpret_cast<const void*>(kern), lds);
+  static std::map<std::pair<std::pair<const void*, int>, size_t>, int> cache;
+  const std::pair<std::pair<const void*, int>, size_t> key({reinterpret_cast<const void*>(kern), threads}, lds);
   std::lock_guard<std::mutex> lock(mu);
   auto it = cache.find(key);
-  if (it != cache.end()) return it->second;
+  if (it != cache.end()) return it->second < most ? it->second : most;
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, threads, lds) != hipSuccess || nb < 1) nb = 1;
-  if (nb > 4) nb = 4;
   cache[key] = nb;
-  return nb;
+  return nb < most ? nb : most;
 }
 
 // Compute units of the current device (256 on an MI355X), asked of the runtime once per device.

@@ -48,15 +48,20 @@ struct Plan {
   int64_t ntiles = 0;            // tiles of the tensor seen as (I / I_N rows, I_N)
   int64_t tile_elems = 0;
   bool fuse_next = false;        // the last-mode kernels also handle mode N-1 (see make_plan)
+  bool narrow = false;           // ... and they are k_head / k_tail (ends.hip), on tiles that end with their slab
+  int end_tiles = 0;             // k_head / k_tail: tiles per slab
+  bool own_offsets = false;      // their tiles are not the flat tiles: support offsets of their own
+  bool flat_offsets = true;      // some kernel walks the flat tiles with the support
   bool fuse_core = false;        // last compression stage + AdamUpdate + first reconstruction stage in one kernel
   bool fuse_core2 = false;       // both leading modes, both ways, and AdamUpdate in one kernel (core2.hip)
   // byte offsets into state
   size_t st_omega, st_ms, st_vs, st_ml, st_vl, st_U[kMaxNdim], state_bytes;
   // byte offsets into workspace
-  size_t ws_sel, ws_hist, ws_eig_status, ws_chunk_gt, ws_chunk_eq, ws_mask, ws_cand, ws_tile_start, ws_fpad, ws_ut, ws_partials, ws_gram[kMaxNdim],
+  size_t ws_sel, ws_hist, ws_eig_status, ws_chunk_gt, ws_chunk_eq, ws_mask, ws_cand, ws_tile_start, ws_end_start, ws_fpad, ws_ut, ws_partials, ws_gram[kMaxNdim],
       ws_eig_a[kMaxNdim], ws_eig_v[kMaxNdim], ws_gs, ws_core_g, ws_core_n, ws_buf[2], workspace_bytes;
   int gram_chunks[kMaxNdim];
   int order = 0;                   // TGRAD_ORDER_*
+  int64_t zero_tiles = 0;
   size_t ws_tile_zero = 0;         // all-zero tile offsets: "no support" for the first-stage kernel
   size_t ws_resid = 0;             // low-rank-first order: the residual G - G~_L at refresh
   size_t ws_rbuf[2] = {0, 0};      // low-rank-first order: intermediates of the raw reconstruction chain
@@ -174,20 +179,33 @@ void make_plan(const tgrad_config* c, Plan* p) {
     const int64_t rows = p->I / p->shape[last];
     p->ntiles = (rows + 31) / 32;                 // last-mode kernels: flat tiles of 32 rows
     p->tile_elems = (int64_t)32 * p->shape[last];
-    // Fusion of the mode-(N-1) stages into the last-mode kernels: needs whole 32-row tiles per slab,
-    // one column tile of the last mode (r_N <= 16), r_(N-1) <= 32, and enough slabs to fill the chip.
-    bool fuse = p->tile_waves == 4 && N >= 3;
-    if (fuse) {
+    // Fusion of the mode-(N-1) stages into the last-mode kernels.  On 32 x 32 tiles: whole 32-row tiles per slab,
+    // one column tile of the last mode (r_N <= 16), r_(N-1) <= 32, enough slabs to fill the chip.
+    bool wide = p->tile_waves == 4 && N >= 3;
+    bool slabs_512 = false;
+    if (N >= 3) {
       const int64_t I2 = p->shape[last - 1];
-      fuse = (I2 % 32 == 0) && I2 <= TGRAD_MAX_EXTENT && p->rank[last - 1] <= 32 && 2 * p->rank[last] <= 32 &&
-             rows / I2 >= 512 && p->shape[last] <= fused_max_last_extent();
+      slabs_512 = rows / I2 >= 512;
+      wide = wide && (I2 % 32 == 0) && I2 <= TGRAD_MAX_EXTENT && p->rank[last - 1] <= 32 && 2 * p->rank[last] <= 32 &&
+             slabs_512 && p->shape[last] <= fused_max_last_extent();
+      // Otherwise, and wherever the ranks leave half of a 32-wide tile empty, on 16 x 16 tiles.
+      const bool full_tiles = p->rank[last] > 8 && p->rank[last - 1] > 16;
+      p->narrow = p->tile_waves > 0 && !(wide && full_tiles) &&
+                  ends_kernel_fits((int)p->shape[last], p->rank[last], (int)I2, p->rank[last - 1]);
+      if (p->narrow) {
+        const int R = end_tile_rows((int)p->shape[last]);
+        p->end_tiles = (int)((I2 + R - 1) / R);
+        p->own_offsets = R != 32 || I2 % 32 != 0;
+        p->flat_offsets = !p->own_offsets || c->hooi_sweeps > 0;
+      }
     }
-    p->fuse_next = fuse;
+    p->fuse_next = wide || p->narrow;
     p->fuse_core = core_kernel_fits((int)p->shape[0], p->rank[0]);
-    if (N >= 3 && !(fuse && N == 3)) {          // (N = 3 with the fused end kernels leaves one mode: k_core)
+    if (N >= 3 && !(p->fuse_next && N == 3)) {  // (N = 3 with the fused end kernels leaves one mode: k_core)
       int64_t cc = 1;
       for (int m = 2; m < N; ++m) cc *= p->rank[m];
-      p->fuse_core2 = core2_kernel_fits((int)p->shape[0], (int)p->shape[1], p->rank[0], p->rank[1], cc, fuse);
+      p->fuse_core2 = core2_kernel_fits((int)p->shape[0], (int)p->shape[1], p->rank[0], p->rank[1], cc,
+                                        p->fuse_next && slabs_512);
     }
   }
 
@@ -215,8 +233,11 @@ void make_plan(const tgrad_config* c, Plan* p) {
   p->ws_mask = take((size_t)p->mask_words * 4);
   p->ws_cand = take((size_t)p->mask_words * 4);
   p->ws_tile_start = take((size_t)(p->ntiles + 1) * 4);
-  p->ws_fpad = take(p->fuse_next ? (size_t)p->shape[N - 2] * 32 * 8 : 0);
-  p->ws_ut = take(p->fuse_next ? (size_t)p->shape[N - 2] * 32 * 8 : 0);
+  const int64_t end_tiles = p->narrow ? p->I / (p->shape[N - 1] * p->shape[N - 2]) * p->end_tiles : 0;
+  p->ws_end_start = p->own_offsets ? take((size_t)(end_tiles + 1) * 4) : p->ws_tile_start;
+  const bool packed = p->fuse_next && !p->narrow;
+  p->ws_fpad = take(packed ? (size_t)p->shape[N - 2] * 32 * 8 : 0);
+  p->ws_ut = take(packed ? (size_t)p->shape[N - 2] * 32 * 8 : 0);
   size_t partial_max = 0;
   for (int n = 0; n < N; ++n) {
     int64_t A = 1, B = 1;
@@ -262,7 +283,8 @@ void make_plan(const tgrad_config* c, Plan* p) {
   p->ws_buf[0] = take(buf[0]);
   p->ws_buf[1] = take(buf[1]);
   p->order = c->order;
-  p->ws_tile_zero = take(p->order != TGRAD_ORDER_US_LR ? (size_t)(p->ntiles + 1) * 4 : 0);
+  p->zero_tiles = (end_tiles > p->ntiles ? end_tiles : p->ntiles) + 1;
+  p->ws_tile_zero = take(p->order != TGRAD_ORDER_US_LR ? (size_t)p->zero_tiles * 4 : 0);
   {
     // unfused chains (every stage through memory) for the residual of the low-rank part
     size_t rb[2] = {0, 0};
@@ -377,10 +399,24 @@ bool error_pending_on_entry() { return hipPeekAtLastError() != hipSuccess; }
 // sweep, tgrad_set_state), never on the step path.
 void pack_fused_factor(tgrad_ctx* c) {
   Plan& p = c->plan;
-  if (!p.fuse_next) return;
+  if (!p.fuse_next || p.narrow) return;
   Scope sc_(c, KID_FACTOR_PACK);
   launch_pack_fused_factor(c->stream, c->st<float2>(p.st_U[p.N - 2]), (int)p.shape[p.N - 2], p.rank[p.N - 2],
                            c->w<float2>(p.ws_fpad), c->w<float2>(p.ws_ut));
+}
+
+// Where the support lies, tile by tile, for the kernels of this plan that walk tiles.
+void tile_offsets(tgrad_ctx* c) {
+  Plan& p = c->plan;
+  const int32_t* omega = c->st<int32_t>(p.st_omega);
+  Scope sc_(c, KID_TILE_OFFSETS);
+  if (p.flat_offsets)
+    launch_tile_offsets(c->stream, omega, p.k, p.tile_elems, 1, p.tile_elems, p.ntiles, c->w<uint32_t>(p.ws_tile_start));
+  if (p.own_offsets) {
+    const int64_t K = p.shape[p.N - 1], slab = K * p.shape[p.N - 2];
+    launch_tile_offsets(c->stream, omega, p.k, end_tile_rows((int)K) * K, p.end_tiles, slab, p.I / slab * p.end_tiles,
+                        c->w<uint32_t>(p.ws_end_start));
+  }
 }
 
 // Omega <- SparseIndices(x, rho, top-k | rand-k), plus the support bitmask and the tile offsets.
@@ -418,10 +454,7 @@ void select_support(tgrad_ctx* c, const void* x, int dt) {
     { Scope sc_(c, KID_SEL_EMIT); launch_select_emit(s, x, dt, keys, p.I, sc, chunk_gt, chunk_eq, p.nchunks, mask, cand, omega); }
   }
   c->have_hist = p.k > 0 && !keys.random;
-  {
-    Scope sc_(c, KID_TILE_OFFSETS);
-    launch_tile_offsets(s, omega, p.k, p.tile_elems, p.ntiles, c->w<uint32_t>(p.ws_tile_start));
-  }
+  tile_offsets(c);
   c->have_indices = true;
 }
 
@@ -589,7 +622,8 @@ int do_step(tgrad_ctx* c, void* weight, const void* g) {
   float2* core_n = c->w<float2>(p.ws_core_n);
   float2* buf[2] = {c->w<float2>(p.ws_buf[0]), c->w<float2>(p.ws_buf[1])};
 
-  const uint32_t* tile_start = c->w<uint32_t>(p.ws_tile_start);
+  const uint32_t* tile_start = c->w<uint32_t>(p.narrow ? p.ws_end_start : p.ws_tile_start);
+  const int64_t nslabs = N >= 2 ? p.I / (p.shape[N - 1] * p.shape[N - 2]) : 0;
   const bool mfma_last = p.tile_waves > 0;
   // What the compression chain removes on the way in: the support (Algorithm 1), or nothing (the
   // low-rank part sees the full gradient in the two other composition orders).
@@ -609,8 +643,12 @@ int do_step(tgrad_ctx* c, void* weight, const void* g) {
     if (st == 0 && mfma_last && p.fuse_next) {                 // stages 0 and 1 in one kernel
       float2* dst1 = (N == 2) ? core_g : buf[1];
       Scope sc_(c, KID_PROJECT_FIRST);
-      launch_lproj(s, g, cf.grad_dtype, omega, in_ts, gs, U, p.rank[sg.mode], sg, p.tile_waves, dst1,
-                   (int)p.shape[N - 2], p.rank[N - 2], c->w<float2>(p.ws_fpad));
+      if (p.narrow)
+        launch_head(s, g, cf.grad_dtype, omega, in_ts, gs, U, sg.K, sg.M, c->st<float2>(p.st_U[N - 2]),
+                    (int)p.shape[N - 2], p.rank[N - 2], nslabs, dst1);
+      else
+        launch_lproj(s, g, cf.grad_dtype, omega, in_ts, gs, U, p.rank[sg.mode], sg, p.tile_waves, dst1,
+                     (int)p.shape[N - 2], p.rank[N - 2], c->w<float2>(p.ws_fpad));
       src = last = dst1;
       st = 1;
       continue;
@@ -632,8 +670,8 @@ int do_step(tgrad_ctx* c, void* weight, const void* g) {
 
   // AdamUpdate on the core; tau = t + 1
   const double tau = (double)(c->t + 1);
-  const float inv_c1 = (float)(1.0 / (1.0 - std::pow((double)cf.beta1, tau)));
-  const float inv_c2 = (float)(1.0 / (1.0 - std::pow((double)cf.beta2, tau)));
+  const double corr1 = 1.0 / (1.0 - std::pow((double)cf.beta1, tau)), corr2 = 1.0 / (1.0 - std::pow((double)cf.beta2, tau));
+  const float inv_c1 = (float)corr1, inv_c2 = (float)corr2;
   const float2* zsrc = core_n;
   int first_back = 0;
   if (p.fuse_core2) {
@@ -681,17 +719,22 @@ int do_step(tgrad_ctx* c, void* weight, const void* g) {
     const Stage& sg = p.back[N - 1];
     const float2* U = c->st<float2>(p.st_U[sg.mode]);
     const float decay = 1.f - cf.lr * cf.weight_decay;
-    if (mfma_last && p.fuse_next) {
+    if (p.narrow) {
+      Scope sc_(c, KID_UPDATE);
+      launch_tail(s, zsrc, U, sg.K, sg.M, c->st<float2>(p.st_U[N - 2]), (int)p.shape[N - 2], p.rank[N - 2], nslabs,
+                  weight, cf.weight_dtype, decay, -cf.lr * cf.alpha, omega, tile_start, gs, c->st<float2>(p.st_ms),
+                  c->st<float>(p.st_vs), cf.beta1, cf.beta2, corr1, corr2, cf.eps, -cf.lr * cf.lambda);
+    } else if (mfma_last && p.fuse_next) {
       Scope sc_(c, KID_UPDATE);
       launch_lupdate_fused(s, zsrc, c->w<float2>(p.ws_ut), (int)p.shape[N - 2], p.rank[N - 2], U, sg,
                            weight, cf.weight_dtype, decay, -cf.lr * cf.alpha, omega, tile_start, p.k, gs,
-                           c->st<float2>(p.st_ms), c->st<float>(p.st_vs), cf.beta1, cf.beta2, inv_c1, inv_c2,
+                           c->st<float2>(p.st_ms), c->st<float>(p.st_vs), cf.beta1, cf.beta2, corr1, corr2,
                            cf.eps, -cf.lr * cf.lambda);
     } else if (mfma_last) {
       Scope sc_(c, KID_UPDATE);
       launch_lupdate(s, zsrc, U, sg, p.tile_waves, weight, cf.weight_dtype, decay, -cf.lr * cf.alpha,
                      omega, tile_start, gs, c->st<float2>(p.st_ms), c->st<float>(p.st_vs), cf.beta1, cf.beta2,
-                     inv_c1, inv_c2, cf.eps, -cf.lr * cf.lambda);
+                     corr1, corr2, cf.eps, -cf.lr * cf.lambda);
     } else {
       {
         Scope sc_(c, KID_SPARSE_UPDATE);
@@ -828,7 +871,7 @@ int tgrad_init(tgrad_ctx** out, const tgrad_config* cfg, void* state_dev, void* 
   // moments <- 0 (and everything else in the state block), with a fill kernel
   zero_u32(c->stream, reinterpret_cast<uint32_t*>(c->state), (int64_t)(c->plan.state_bytes / 4));
   if (c->plan.order != TGRAD_ORDER_US_LR)
-    zero_u32(c->stream, c->w<uint32_t>(c->plan.ws_tile_zero), c->plan.ntiles + 1);
+    zero_u32(c->stream, c->w<uint32_t>(c->plan.ws_tile_zero), c->plan.zero_tiles);
   if (check_launch() != TGRAD_OK) {
     delete c;
     return TGRAD_ERR_HIP;
@@ -884,7 +927,7 @@ int tgrad_step_static(const tgrad_config* cfg, void* state_dev, int64_t t, void*
   c.profiling = false;
   if (error_pending_on_entry()) return TGRAD_ERR_HIP;
   Plan& p = c.plan;
-  if (p.order != TGRAD_ORDER_US_LR) zero_u32(c.stream, c.w<uint32_t>(p.ws_tile_zero), p.ntiles + 1);
+  if (p.order != TGRAD_ORDER_US_LR) zero_u32(c.stream, c.w<uint32_t>(p.ws_tile_zero), p.zero_tiles);
   if (t % cfg->refresh_every == 0) {
     rc = do_refresh(&c, grad_dev);
     if (rc != TGRAD_OK) return rc;
@@ -894,8 +937,7 @@ int tgrad_step_static(const tgrad_config* cfg, void* state_dev, int64_t t, void*
     // from the state (the support bitmask, the tile offsets, the factor copies of the fused kernels).
     if (p.k > 0 && p.tile_waves == 0)
       launch_mask_from_indices(c.stream, c.st<int32_t>(p.st_omega), p.k, c.w<uint32_t>(p.ws_mask), p.mask_words);
-    launch_tile_offsets(c.stream, c.st<int32_t>(p.st_omega), p.k, p.tile_elems, p.ntiles,
-                        c.w<uint32_t>(p.ws_tile_start));
+    tile_offsets(&c);
     pack_fused_factor(&c);
   }
   return do_step(&c, weight_dev, grad_dev);
@@ -983,11 +1025,7 @@ int tgrad_set_state(tgrad_ctx* ctx, int what, const void* host_in, size_t bytes)
       launch_mask_from_indices(ctx->stream, ctx->st<int32_t>(p.st_omega), p.k, ctx->w<uint32_t>(p.ws_mask),
                                p.mask_words);
     }
-    {
-      Scope sc_(ctx, KID_TILE_OFFSETS);
-      launch_tile_offsets(ctx->stream, ctx->st<int32_t>(p.st_omega), p.k, p.tile_elems, p.ntiles,
-                          ctx->w<uint32_t>(p.ws_tile_start));
-    }
+    tile_offsets(ctx);
     if (hipStreamSynchronize(ctx->stream) != hipSuccess) return TGRAD_ERR_HIP;
     ctx->have_indices = true;
     return check_launch();

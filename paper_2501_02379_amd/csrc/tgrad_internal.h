@@ -101,8 +101,8 @@ void launch_residual_gather(hipStream_t s, float2* gs, const int32_t* omega, int
 int choose_tile_waves(int Klast, int rlast, int prefer);
 double launch_mfma_probe(hipStream_t s, int kind, int64_t iters, float* sink);   // returns the launch's flops
 int fused_max_last_extent();                       // largest I_N the fused first-stage kernel takes
-void launch_tile_offsets(hipStream_t s, const int32_t* omega, int64_t k, int64_t tile_elems,
-                         int64_t ntiles, uint32_t* tile_start);
+void launch_tile_offsets(hipStream_t s, const int32_t* omega, int64_t k, int64_t tile_elems, int S,
+                         int64_t slab_elems, int64_t ntiles, uint32_t* tile_start);
 void launch_mid(hipStream_t s, const float2* x, const float2* U, int rn, bool project, const Stage& st,
                 float2* out);
 bool core_kernel_fits(int K, int M);
@@ -119,12 +119,22 @@ void launch_lproj(hipStream_t s, const void* g, int dtype, const int32_t* omega,
                   int fused_M2, const float2* fpad);
 void launch_lupdate(hipStream_t s, const float2* z, const float2* U, const Stage& st, int W, void* w,
                     int wdtype, float decay, float c_alpha, const int32_t* omega, const uint32_t* tile_start,
-                    const float2* gs, float2* ms, float* vs, float beta1, float beta2, float inv_c1,
-                    float inv_c2, float eps, float c_lambda);
+                    const float2* gs, float2* ms, float* vs, float beta1, float beta2, double inv_c1,
+                    double inv_c2, float eps, float c_lambda);
 
 void launch_lupdate_fused(hipStream_t s, const float2* y1, const float2* ut, int I2, int K2, const float2* U,
                           const Stage& st, void* w, int wdtype, float decay, float c_alpha, const int32_t* omega,
                           const uint32_t* tile_start, int64_t k, const float2* gs, float2* ms, float* vs,
-                          float beta1, float beta2, float inv_c1, float inv_c2, float eps, float c_lambda);
+                          float beta1, float beta2, double inv_c1, double inv_c2, float eps, float c_lambda);
+
+// modes N-1 and N in one pass on 16 x 16 tiles (ends.hip)
+int end_tile_rows(int K);
+bool ends_kernel_fits(int K, int r, int I2, int r2);
+void launch_head(hipStream_t s, const void* g, int dtype, const int32_t* omega, const uint32_t* tile_start, float2* gs,
+                 const float2* U3, int K, int M, const float2* U2, int I2, int M2, int64_t nslabs, float2* out);
+void launch_tail(hipStream_t s, const float2* y1, const float2* U3, int K, int M, const float2* U2, int I2, int K2,
+                 int64_t nslabs, void* w, int wdtype, float decay, float c_alpha, const int32_t* omega,
+                 const uint32_t* tile_start, const float2* gs, float2* ms, float* vs, float beta1, float beta2,
+                 double inv_c1, double inv_c2, float eps, float c_lambda);
 
 }  // namespace tgrad

@@ -1,0 +1,54 @@
+"""The first and last kernel of a step on 16 x 16 tiles (modes N-1 and N in one pass, any extent of mode N-1):
+one step per shape against the oracle, at the edges of its tiles and of its size classes."""
+import numpy as np
+import pytest
+
+from oracle import tgrad_oracle as O
+from paper_2501_02379_amd import synth
+from paper_2501_02379_amd import tgrad as T
+from helpers import check_parity, run_both, run_both_bf16_weights
+
+pytestmark = pytest.mark.gpu
+
+# shape, ranks, k, gradient dtype
+SHAPES = [
+    ((5, 7, 13, 5), (3, 4, 5, 2), 200, "c64"),          # odd slabs: tiles that start off a 16-byte boundary
+    ((6, 9, 1, 7), (3, 4, 1, 3), 40, "c64"),            # one row per slab
+    ((11, 6, 16, 2), (3, 4, 16, 2), 40, "c64"),         # shortest rows, a full tile of rows, full ranks
+    ((9, 8, 33, 33), (3, 4, 17, 9), 700, "c64"),        # two tiles (32 + 1 rows), lone last column, two tiles of each rank
+    ((9, 8, 48, 34), (3, 4, 16, 8), 500, "c64"),        # 16-row tiles from here on, padded rows
+    ((4, 5, 21, 65), (3, 4, 9, 16), 300, "c64"),        # 16 + 5 rows, lone last column
+    ((4, 3, 70, 68), (3, 3, 32, 16), 900, "c64"),       # longest rows, five tiles shared by four wavefronts
+    ((40, 30, 35, 9), (4, 5, 6, 8), 3000, "c64"),       # slabs enough for whole ones per wavefront, two tiles each
+    ((36, 31, 3, 4), (4, 5, 2, 3), 3900, "c64"),        # ... of three rows; support entries everywhere
+    ((5, 7, 13, 5), (3, 4, 5, 2), 2000, "cbf16"),       # odd slabs of 4-byte elements, most entries in the support
+    ((37, 29, 19, 21), (4, 5, 7, 6), 2000, "cbf16"),
+    ((50, 33, 24), (12, 20, 7), 300, "c64"),            # three-way: one slab per leading index
+    ((4, 3, 5, 6, 11), (2, 2, 3, 4, 5), 90, "c64"),     # five-way
+]
+
+
+@pytest.mark.parametrize("shape,ranks,k,dt", SHAPES)
+def test_end_kernels_small_tiles(shape, ranks, k, dt):
+    print("[case]", shape, ranks, k, dt, flush=True)
+    grads = [synth.small_case(shape, 300 + t, outlier_frac=(1, 100), dtype=dt) for t in range(4)]
+    rng = np.random.default_rng(5)
+    W0 = ((rng.standard_normal(shape) + 1j * rng.standard_normal(shape)) * 0.02).astype(np.complex64)
+    info = run_both(T, shape, ranks, k, grads, W0, refresh_every=3, lr=2e-3, weight_decay=0.01,
+                    grad_dtype=T.TGRAD_CBF16 if dt == "cbf16" else T.TGRAD_C64)
+    assert all(info["omega_equal"])
+    check_parity(info, W0)
+
+
+@pytest.mark.parametrize("shape,ranks,k,dt", [SHAPES[0], SHAPES[3], SHAPES[5], SHAPES[9], SHAPES[10]])
+def test_end_kernels_bf16_weights(shape, ranks, k, dt):
+    """Four-element pieces of W: tiles that start and end inside a piece (bounds as in test_bf16_weights_single_steps)."""
+    print("[case]", shape, ranks, k, dt, flush=True)
+    grads = [synth.small_case(shape, 400 + t, outlier_frac=(1, 100), dtype=dt) for t in range(4)]
+    rng = np.random.default_rng(6)
+    W0 = O.complex_to_bf16_pairs((rng.standard_normal(shape) + 1j * rng.standard_normal(shape)) * 0.02)
+    info = run_both_bf16_weights(T, shape, ranks, k, grads, W0, resync=True, refresh_every=3, lr=2e-3,
+                                 weight_decay=0.01, grad_dtype=T.TGRAD_CBF16 if dt == "cbf16" else T.TGRAD_C64)
+    for worst, frac in info["stats"]:
+        assert worst <= 1
+        assert frac <= max(5e-3, 2.0 / (2 * int(np.prod(shape))))
