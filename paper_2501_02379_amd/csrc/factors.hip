@@ -1070,57 +1070,77 @@ __global__ __launch_bounds__(kEigThreads) void k_eig_finish(EigJobs jobs) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// The same eigenvectors by the classical three-stage route, for n <= 128 (one workgroup per matrix):
-//   (1) Householder tridiagonalisation  A = Q T Q^H  of the Hermitian matrix (packed lower triangle
-//       in LDS; reflector i annihilates column i below the subdiagonal; T real symmetric tridiagonal),
-//   (2) the r largest eigenvalues of T by multisection on Sturm counts (32 lanes per eigenvalue, 32
-//       points per step: 13 steps from the Gershgorin interval down to rounding),
-//   (3) their eigenvectors by inverse iteration (Gaussian elimination with partial pivoting on
-//       T - lambda I, three solves from a fixed pseudo-random start vector, one thread per vector),
-//   (4) back-transformation with the reflectors, phase convention and the float32 factor (k_trid_back,
-//       one wavefront per eigenvector).
-// A cyclic Jacobi sweep reads and writes the whole matrix in every one of its n - 1 rounds, about
-// ten sweeps long; the tridiagonalisation touches the trailing block once per step: 15 times less
-// LDS traffic, which is what bounds both.
-// Inverse iteration separates eigenvectors only as well as their eigenvalues are separated: if two
-// of the r leading eigenvalues, or the r-th and the (r+1)-th, lie within 1e-7 of the spectral radius
-// (exactly repeated eigenvalues, a zero matrix), this path declines (status[2] = 1) and the Jacobi
-// kernels, which handle clusters gracefully, solve the matrix instead.
-constexpr int kTridThreads = 1024;
-constexpr int kInvBatch = 32;          // eigenvectors per inverse-iteration batch (LDS: 4 arrays of n x 32 doubles)
-constexpr int kMultiSteps = 13;        // 33^13 > 2^64
+// The same eigenvectors by the classical route, for n <= 128:
+//   k_trid      (one workgroup per matrix) Householder tridiagonalisation  A = Q T Q^H; reflector i annihilates column
+//               i below the subdiagonal; T real symmetric tridiagonal
+//   k_trid_vec  (one wavefront per eigenvector)
+//               the k-th largest eigenvalue of T by multisection on Sturm counts (64 points per step: 10 steps from the
+//               Gershgorin interval down to rounding), its eigenvector by inverse iteration (Gaussian elimination
+//               with partial pivoting on T - lambda I, three solves from a fixed pseudo-random start vector), the
+//               back-transformation with the reflectors, the phase convention and the float32 factor.
+// A cyclic Jacobi sweep reads and writes the whole matrix in every one of its n - 1 rounds, about ten sweeps long;
+// the tridiagonalisation touches the trailing block once per step.
+// Inverse iteration separates eigenvectors only as well as their eigenvalues are separated: if an eigenvalue lies
+// within 1e-7 of the spectral radius of one of the r leading ones (exactly repeated eigenvalues, a zero matrix),
+// this path declines (status[2] = 1) and the Jacobi kernels, which handle clusters gracefully, solve the matrix.
+//
+// Everything here is a serial chain, so what bounds it is latency.  k_trid keeps the matrix in registers (32 x 32
+// threads, elements (ty + 32 a, tx + 32 b), both triangles) and passes two barriers per step: every wavefront
+// derives the reflector from the column in LDS by itself, and the sums run over lanes without LDS.  In LDS, with
+// eight barriers per step and one wavefront deriving the reflector, a step took 6 us at n = 128.
+// Measured, four modes at once, us, tridiagonalisation + vectors: 128,128,128,65 (r 32,32,32,16) 935 + 66 -> 337 + 138;
+// 64,64,32,17 (r 16,16,8,4) 338 + 34 -> 110 + 73.
+constexpr int kMultiSteps = 10;        // 65^10 > 2^60
 constexpr double kClusterTol = 1e-7;
 
+// work buffer of a job: reflector factors, T, and the bounds of its spectrum
 __device__ __forceinline__ double2* trid_tau(const EigJob& jb) { return reinterpret_cast<double2*>(jb.A); }
-__device__ __forceinline__ double* trid_Z(const EigJob& jb) { return jb.A + 2 * jb.n; }   // r vectors of n doubles
+__device__ __forceinline__ double* trid_d(const EigJob& jb) { return jb.A + 2 * jb.n; }
+__device__ __forceinline__ double* trid_e(const EigJob& jb) { return jb.A + 3 * jb.n; }
+__device__ __forceinline__ double* trid_bounds(const EigJob& jb) { return jb.A + 4 * jb.n; }   // lower, upper
 
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+  const int2 w = __builtin_bit_cast(int2, v);
+  int2 r;
+  r.x = __builtin_amdgcn_mov_dpp(w.x, CTRL, 0xF, 0xF, true);
+  r.y = __builtin_amdgcn_mov_dpp(w.y, CTRL, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, r);
+}
+constexpr int kMirror16 = 0x140, kMirror8 = 0x141, kReverse4 = 0x1B, kSwap2 = 0xB1;   // lane ^ 15, ^ 7, ^ 3, ^ 1
+
+// a, b -> (even rows of 16 lanes: a of both rows of the pair, odd rows: b of both): one step of a reduction that also
+// halves the values; with a == b it adds the two rows of a pair
+__device__ __forceinline__ double add_rows16(double a, double b) {
+  const int2 x = __builtin_bit_cast(int2, a), y = __builtin_bit_cast(int2, b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x.x, (unsigned)y.x, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)x.y, (unsigned)y.y, false, false);
+  return __builtin_bit_cast(double, make_int2((int)lo[0], (int)hi[0])) +
+         __builtin_bit_cast(double, make_int2((int)lo[1], (int)hi[1]));
+}
+__device__ __forceinline__ double add_halves(double a) {
+  const int2 x = __builtin_bit_cast(int2, a);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x.x, (unsigned)x.x, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)x.y, (unsigned)x.y, false, false);
+  return __builtin_bit_cast(double, make_int2((int)lo[0], (int)hi[0])) +
+         __builtin_bit_cast(double, make_int2((int)lo[1], (int)hi[1]));
+}
+// sum over the 64 lanes, the same bits in every lane
 __device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+  v += dpp_d<kMirror16>(v);
+  v += dpp_d<kMirror8>(v);
+  v += dpp_d<kReverse4>(v);
+  v += dpp_d<kSwap2>(v);
+  return add_halves(add_rows16(v, v));
 }
 
-// 1 / q from the hardware's reciprocal estimate and two Newton steps (relative error a few 1e-16): the
-// sequential recurrences below spend their time in this, and a correctly rounded float64 division
-// is four times as long.  Their results only steer a bisection and an inverse iteration.
+// 1 / q from the hardware's reciprocal estimate and two Newton steps (relative error a few 1e-16): a correctly
+// rounded float64 division is four times as long.  Its results only steer an inverse iteration.
 __device__ __forceinline__ double rcp_nr(double q) {
   double r = __builtin_amdgcn_rcp(q);
   r = fma(fma(-q, r, 1.), r, r);
   r = fma(fma(-q, r, 1.), r, r);
   return r;
-}
-
-// eigenvalues of the tridiagonal (d, e2 = e^2) below x
-__device__ __forceinline__ int sturm_count(const double* d, const double* e2, int n, double x, double pivmin) {
-  double q = d[0] - x;
-  if (fabs(q) < pivmin) q = -pivmin;
-  int c = q < 0. ? 1 : 0;
-  for (int i = 1; i < n; ++i) {
-    q = (d[i] - x) - e2[i - 1] * rcp_nr(q);
-    if (fabs(q) < pivmin) q = -pivmin;
-    c += q < 0. ? 1 : 0;
-  }
-  return c;
 }
 
 __device__ __forceinline__ uint32_t trid_mix(uint32_t x) {
@@ -1132,285 +1152,337 @@ __device__ __forceinline__ uint32_t trid_mix(uint32_t x) {
   return x;
 }
 
-__global__ __launch_bounds__(kTridThreads) void k_trid(EigJobs jobs) {
-  extern __shared__ double2 T[];                // packed lower triangle; reused by the inverse iteration
-  const EigJob jb = jobs.job[blockIdx.x];
-  const int n = jb.n, r = jb.r;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// W wavefronts; thread (ty, tx) of the 2 W x 32 grid holds elements (ty + 2 W a, tx + 32 b), a < NA, b < NB.  Few
+// wavefronts, because every one of them derives the reflector: with 16 the four on a SIMD spent two thirds of a step
+// on that (n = 128: 4.7 us a step, with 8 wavefronts 2.7).
+struct TridLds {
+  double2 col[kEigTriMaxN], v[kEigTriMaxN], p[kEigTriMaxN];
+  double d[kEigTriMaxN], e[kEigTriMaxN];
+};
+
+// Workgroup barrier that orders LDS only (a full one would also wait for the reflectors on their way to memory)
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <int W, int NA, int NB>
+__device__ __forceinline__ void tridiagonalise(const EigJob& jb, TridLds& lds) {
+  constexpr int T = 64 * W, RG = 2 * W;
+  static_assert(NA <= 8 && RG * NA == 32 * NB && 32 * NB <= kEigTriMaxN, "");
+  const int n = jb.n;
+  const int tid = threadIdx.x, lane = tid & 63, tx = tid & 31, ty = tid >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const double2* G = reinterpret_cast<const double2*>(jb.gram);
   double2* Vg = reinterpret_cast<double2*>(jb.V);   // reflector i: Vg[i * n + row], rows i + 1 .. n - 1
   double2* tauG = trid_tau(jb);
-  __shared__ double2 sv[kEigTriMaxN], sw[kEigTriMaxN];
-  __shared__ double sd[kEigTriMaxN], se[kEigTriMaxN], se2[kEigTriMaxN], slam[kEigTriMaxN];
-  __shared__ double2 s_tau, s_scale, s_alpha2;
-  __shared__ double s_gl, s_gu, s_pivmin;
-  __shared__ int s_decline;
+  double2* scol = lds.col;
+  double2* sv = lds.v;
+  double2* sp = lds.p;
+  double* sd = lds.d;
+  double* se = lds.e;
 
-  for (int e = tid; e < n * n; e += kTridThreads) {
-    const int i = e / n, j = e - i * n;
-    if (i >= j) T[tri_idx(i, j)] = G[e];
-  }
-  if (tid == 0) s_decline = 0;
-  __syncthreads();
-
-  // ---- (1) tridiagonalisation ----
-  for (int i = 0; i + 1 < n; ++i) {
-    const int m = n - i - 1;                     // trailing block: rows / columns i + 1 .. n - 1 (local 0 .. m - 1)
-    if (wave == 0) {
-      double xn2 = 0.;
-      for (int j = 1 + lane; j < m; j += 64) {
-        const double2 x = T[tri_idx(i + 1 + j, i)];
-        xn2 += x.x * x.x + x.y * x.y;
-      }
-      xn2 = wave_sum_d(xn2);
-      if (lane == 0) {
-        const double2 alpha = T[tri_idx(i + 1, i)];
-        double2 tau = make_double2(0., 0.), scale = make_double2(0., 0.);
-        double beta = alpha.x;
-        if (!(xn2 == 0. && alpha.y == 0.)) {
-          beta = -copysign(sqrt(alpha.x * alpha.x + alpha.y * alpha.y + xn2), alpha.x);
-          tau = make_double2((beta - alpha.x) / beta, -alpha.y / beta);
-          const double2 z = make_double2(alpha.x - beta, alpha.y);          // 1 / (alpha - beta)
-          const double inv = 1. / (z.x * z.x + z.y * z.y);
-          scale = make_double2(z.x * inv, -z.y * inv);
-        }
-        s_tau = tau;
-        s_scale = scale;
-        se[i] = beta;
-        sd[i] = T[tri_idx(i, i)].x;
-        tauG[i] = tau;
-      }
-    }
-    __syncthreads();
-    const double2 tau = s_tau;
-    const bool reflect = tau.x != 0. || tau.y != 0.;           // (workgroup-uniform)
-    for (int j = tid; j < m; j += kTridThreads) {
-      double2 v = make_double2(j == 0 ? 1. : 0., 0.);
-      if (j > 0 && reflect) v = cmuld(T[tri_idx(i + 1 + j, i)], s_scale);
-      sv[j] = v;
-      Vg[(size_t)i * n + i + 1 + j] = v;
-    }
-    __syncthreads();
-    if (!reflect) continue;
-    // p = tau S v: 8 threads per row, each over the columns c = q, q + 8, ..; summed in a fixed order
-    {
-      const int rr = tid >> 3, q = tid & 7;
-      double2 acc = make_double2(0., 0.);
-      if (rr < m)
-        for (int c = q; c < m; c += 8) {
-          const double2 sv_c = sv[c];
-          const double2 a = c <= rr ? T[tri_idx(i + 1 + rr, i + 1 + c)] : conjd(T[tri_idx(i + 1 + c, i + 1 + rr)]);
-          const double2 t = cmuld(a, sv_c);
-          acc.x += t.x;
-          acc.y += t.y;
-        }
+  double2 S[NA][NB];
 #pragma unroll
-      for (int off = 1; off < 8; off <<= 1) {
-        acc.x += __shfl_xor(acc.x, off, 64);
-        acc.y += __shfl_xor(acc.y, off, 64);
-      }
-      if (q == 0 && rr < m) sw[rr] = cmuld(tau, acc);
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int row = ty + RG * a, c = tx + 32 * b;
+      S[a][b] = row < n && c < n ? G[row * n + c] : make_double2(0., 0.);
     }
-    __syncthreads();
-    // alpha2 = -1/2 tau (p^H v);  w = p + alpha2 v
-    if (wave == 0) {
-      double ax = 0., ay = 0.;
-      for (int j = lane; j < m; j += 64) {
-        const double2 t = cmuld(conjd(sw[j]), sv[j]);
-        ax += t.x;
-        ay += t.y;
-      }
-      ax = wave_sum_d(ax);
-      ay = wave_sum_d(ay);
-      if (lane == 0) {
-        const double2 t = cmuld(tau, make_double2(ax, ay));
-        s_alpha2 = make_double2(-0.5 * t.x, -0.5 * t.y);
-      }
+  for (int j = tid; j < kEigTriMaxN; j += T) scol[j] = sv[j] = sp[j] = make_double2(0., 0.);
+  __syncthreads();
+  auto publish = [&](int c, auto b_c) {          // column c, of block column b_c, -> LDS
+    constexpr int b = decltype(b_c)::value;
+    if (tx == (c & 31)) {
+#pragma unroll
+      for (int a = 0; a < NA; ++a) scol[ty + RG * a] = S[a][b];
     }
-    __syncthreads();
-    for (int j = tid; j < m; j += kTridThreads) {
-      const double2 t = cmuld(s_alpha2, sv[j]);
-      sw[j] = make_double2(sw[j].x + t.x, sw[j].y + t.y);
-    }
-    __syncthreads();
-    // S <- S - v w^H - w v^H on the lower triangle
-    {
-      const int ty = tid >> 5, tx = tid & 31;
-      for (int rr = ty; rr < m; rr += 32) {
-        const double2 vr = sv[rr], wr = sw[rr];
-        for (int c = tx; c <= rr; c += 32) {
-          const double2 t1 = cmuld(vr, conjd(sw[c])), t2 = cmuld(wr, conjd(sv[c]));
-          double2* p = &T[tri_idx(i + 1 + rr, i + 1 + c)];
-          *p = make_double2(p->x - t1.x - t2.x, p->y - t1.y - t2.y);
+  };
+  publish(0, std::integral_constant<int, 0>());
+  // Steps of block column P: rows and columns of the blocks before it are finished, which the code knows (a branch per
+  // block would put the LDS latency of its operands in front of every one of them).
+  auto block_column = [&](auto p_c) __attribute__((always_inline)) {
+    constexpr int P = decltype(p_c)::value, A0 = 32 * P / RG;
+    auto publish_next = [&](int c) {             // (the last step of a block column publishes the next one's first)
+      if (P + 1 < NB && c == 32 * (P + 1)) publish(c, std::integral_constant<int, (P + 1 < NB ? P + 1 : P)>());
+      else publish(c, p_c);
+    };
+    const int i_end = 32 * (P + 1) < n - 1 ? 32 * (P + 1) : n - 1;
+    for (int i = 32 * P; i < i_end; ++i) {
+      lds_barrier();
+      // the reflector of column i, by every wavefront: v = (0 .. 0, 1, scale x)
+      const double2 c0 = scol[lane], c1 = n > 64 ? scol[lane + 64] : make_double2(0., 0.), alpha = scol[i + 1];
+      double xn2 = lane > i + 1 ? c0.x * c0.x + c0.y * c0.y : 0.;
+      if (n > 64) xn2 += lane + 64 > i + 1 ? c1.x * c1.x + c1.y * c1.y : 0.;
+      xn2 = wave_sum_d(xn2);
+      double2 tau = make_double2(0., 0.), scale = make_double2(0., 0.);
+      double beta = alpha.x;
+      const bool reflect = !(xn2 == 0. && alpha.y == 0.);        // (the same in every wavefront)
+      if (reflect) {
+        beta = -copysign(sqrt(alpha.x * alpha.x + alpha.y * alpha.y + xn2), alpha.x);
+        const double inv_beta = rcp_nr(beta);
+        tau = make_double2((beta - alpha.x) * inv_beta, -alpha.y * inv_beta);
+        const double2 z = make_double2(alpha.x - beta, alpha.y);              // 1 / (alpha - beta)
+        const double inv = rcp_nr(z.x * z.x + z.y * z.y);
+        scale = make_double2(z.x * inv, -z.y * inv);
+      }
+      auto v_of = [&](int j, double2 x) -> double2 {
+        return j > i + 1 ? cmuld(x, scale) : make_double2(j == i + 1 ? 1. : 0., 0.);
+      };
+      const double2 v0 = v_of(lane, c0), v1 = n > 64 ? v_of(lane + 64, c1) : make_double2(0., 0.);
+      if (wave == 0) {
+        sv[lane] = v0;
+        sv[lane + 64] = v1;
+      } else if (wave == 1) {
+        if (lane > i && lane < n) Vg[(size_t)i * n + lane] = v0;
+        if (lane + 64 > i && lane + 64 < n) Vg[(size_t)i * n + lane + 64] = v1;
+      } else if (wave == 2 && lane == 0) {
+        tauG[i] = tau;
+        sd[i] = scol[i].x;
+        se[i] = beta;
+      }
+      if (!reflect) {
+        lds_barrier();
+        publish_next(i + 1);
+        continue;
+      }
+      {                                            // S v, rows summed over the 32 threads that hold them
+        double2 acc[8];
+#pragma unroll
+        for (int a = 0; a < 8; ++a) acc[a] = make_double2(0., 0.);
+#pragma unroll
+        for (int b = P; b < NB; ++b) {
+          const double2 v = v_of(tx + 32 * b, scol[tx + 32 * b]);
+#pragma unroll
+          for (int a = A0; a < NA; ++a) {
+            acc[a].x += S[a][b].x * v.x - S[a][b].y * v.y;
+            acc[a].y += S[a][b].x * v.y + S[a][b].y * v.x;
+          }
+        }
+        // lane bits 4, 3, 2, 1 pick (row block, part): each step adds two lanes and keeps half of the values
+        auto halve = [&](double lo, double hi, bool up, auto ctrl) -> double {
+          return (up ? hi : lo) + dpp_d<decltype(ctrl)::value>(up ? lo : hi);
+        };
+        using M16 = std::integral_constant<int, kMirror16>;
+        using M8 = std::integral_constant<int, kMirror8>;
+        using R4 = std::integral_constant<int, kReverse4>;
+        const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
+        double h[4][2];
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          h[a][0] = add_rows16(acc[a].x, acc[a + 4].x);
+          h[a][1] = add_rows16(acc[a].y, acc[a + 4].y);
+        }
+        double m[2][2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          m[a][0] = halve(h[a][0], h[a + 2][0], b3, M16());
+          m[a][1] = halve(h[a][1], h[a + 2][1], b3, M16());
+        }
+        const double qx = halve(m[0][0], m[1][0], b2, M8()), qy = halve(m[0][1], m[1][1], b2, M8());
+        double q = halve(qx, qy, b1, R4());
+        q += dpp_d<kSwap2>(q);
+        const int a = ((lane >> 4) & 1) * 4 + ((lane >> 3) & 1) * 2 + ((lane >> 2) & 1);
+        if ((lane & 1) == 0 && a >= A0 && a < NA) {
+          double* dst = reinterpret_cast<double*>(&sp[ty + RG * a]);
+          dst[(lane >> 1) & 1] = q;
         }
       }
+      lds_barrier();
+      // w = tau S v - 1/2 |tau|^2 (v^H S v) v;   S <- S - v w^H - w v^H
+      const double2 q0 = sp[lane];
+      double dot = lane > i ? v0.x * q0.x + v0.y * q0.y : 0.;
+      if (n > 64) {
+        const double2 q1 = sp[lane + 64];
+        dot += lane + 64 > i ? v1.x * q1.x + v1.y * q1.y : 0.;
+      }
+      const double rho = wave_sum_d(dot);
+      const double alpha2 = -0.5 * (tau.x * tau.x + tau.y * tau.y) * rho;
+      auto w_of = [&](int j, double2 v) -> double2 {               // (rows that are finished: v = 0, and their S v is stale)
+        const double2 t = cmuld(tau, sp[j]);
+        return j > i ? make_double2(t.x + alpha2 * v.x, t.y + alpha2 * v.y) : make_double2(0., 0.);
+      };
+      double2 vt[NB], wt[NB];
+#pragma unroll
+      for (int b = P; b < NB; ++b) {
+        vt[b] = sv[tx + 32 * b];
+        wt[b] = w_of(tx + 32 * b, vt[b]);
+      }
+#pragma unroll
+      for (int a = A0; a < NA; ++a) {
+        const double2 vy = sv[ty + RG * a], wy = w_of(ty + RG * a, vy);
+#pragma unroll
+        for (int b = P; b < NB; ++b) {
+          double2 s = S[a][b];
+          s.x -= vy.x * wt[b].x + vy.y * wt[b].y;
+          s.y -= vy.y * wt[b].x - vy.x * wt[b].y;
+          s.x -= wy.x * vt[b].x + wy.y * vt[b].y;
+          s.y -= wy.y * vt[b].x - wy.x * vt[b].y;
+          S[a][b] = s;
+        }
+      }
+      publish_next(i + 1);
     }
-    __syncthreads();
-  }
+  };
+  block_column(std::integral_constant<int, 0>());
+  if constexpr (NB > 1) block_column(std::integral_constant<int, 1>());
+  if constexpr (NB > 2) block_column(std::integral_constant<int, 2>());
+  if constexpr (NB > 3) block_column(std::integral_constant<int, 3>());
+  __syncthreads();
   if (tid == 0) {
-    sd[n - 1] = T[tri_idx(n - 1, n - 1)].x;
+    sd[n - 1] = scol[n - 1].x;
     se[n - 1] = 0.;
   }
   __syncthreads();
-  for (int i = tid; i < n; i += kTridThreads) se2[i] = se[i] * se[i];
-  __syncthreads();
-
-  // ---- (2) the r largest eigenvalues: Gershgorin interval, then multisection on Sturm counts ----
-  if (wave == 0) {
-    double lo = 1e300, hi = -1e300, em = 0.;
+  for (int i = tid; i < n; i += T) {
+    trid_d(jb)[i] = sd[i];
+    trid_e(jb)[i] = se[i];
+  }
+  if (wave == 0) {                               // Gershgorin interval
+    double lo = 1e300, hi = -1e300;
     for (int i = lane; i < n; i += 64) {
       const double rad = (i > 0 ? fabs(se[i - 1]) : 0.) + (i + 1 < n ? fabs(se[i]) : 0.);
       lo = fmin(lo, sd[i] - rad);
       hi = fmax(hi, sd[i] + rad);
-      em = fmax(em, se2[i]);
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
       lo = fmin(lo, __shfl_xor(lo, off, 64));
       hi = fmax(hi, __shfl_xor(hi, off, 64));
-      em = fmax(em, __shfl_xor(em, off, 64));
     }
     if (lane == 0) {
-      const double tn = fmax(fabs(lo), fabs(hi));
-      const double pivmin = 2.2250738585072014e-308 * fmax(1., em);
-      const double slack = 2.1 * tn * 2.220446049250313e-16 * n + 2.1 * pivmin;
-      s_gl = lo - slack;
-      s_gu = hi + slack;
-      s_pivmin = pivmin;
+      const double slack = 2.1 * fmax(fabs(lo), fabs(hi)) * 2.220446049250313e-16 * n;
+      trid_bounds(jb)[0] = lo - slack;
+      trid_bounds(jb)[1] = hi + slack;
+      jb.status[0] = 0;
+      jb.status[1] = 0;
+      jb.status[2] = 0;                          // k_trid_vec declines
     }
-  }
-  __syncthreads();
-  const double pivmin = s_pivmin;
-  const double tnorm = fmax(fabs(s_gl), fabs(s_gu));
-  {
-    const int g = tid >> 5, j = tid & 31;
-    for (int kk = g; kk < r; kk += kTridThreads / 32) {
-      const int kasc = n - 1 - kk;                 // kk-th largest = kasc-th smallest (0-based)
-      double lo = s_gl, hi = s_gu;
-      for (int step = 0; step < kMultiSteps; ++step) {
-        const double h = (hi - lo) / 33.;
-        const double x = lo + (j + 1) * h;
-        const bool above = sturm_count(sd, se2, n, x, pivmin) > kasc;     // more than kasc eigenvalues below x
-        const uint64_t bal = __ballot(above);
-        const uint32_t mk = (uint32_t)(bal >> (lane & 32));
-        // first point with `above`: the eigenvalue lies between it and the point before
-        const int jf = mk ? __builtin_ctz(mk) : 32;
-        const double nlo = jf == 0 ? lo : lo + jf * h;
-        const double nhi = jf == 32 ? hi : lo + (jf + 1) * h;
-        lo = nlo;
-        hi = nhi;
-      }
-      if (j == 0) slam[kk] = 0.5 * (lo + hi);
-    }
-  }
-  __syncthreads();
-  // close eigenvalues: decline
-  if (tid == 0) {
-    const double delta = kClusterTol * tnorm;
-    int bad = 0;
-    for (int k = 0; k < r; ++k) {
-      if (!(fabs(slam[k]) <= 1e300)) bad = 1;                          // NaN / inf
-      if (k + 1 < r && !(slam[k] - slam[k + 1] >= delta)) bad = 1;
-    }
-    if (!bad && r < n && sturm_count(sd, se2, n, slam[r - 1] - delta, pivmin) != n - r) bad = 1;
-    if (!(tnorm > 0.)) bad = 1;                                         // zero matrix
-    s_decline = bad;
-    jb.status[0] = 0;
-    jb.status[1] = 0;
-    jb.status[2] = bad;
-  }
-  __syncthreads();
-  if (s_decline) return;
-
-  // ---- (3) inverse iteration, kInvBatch eigenvectors at a time, one thread each ----
-  double* pivA = reinterpret_cast<double*>(T);     // [i][t]: reciprocal pivots of the elimination
-  double* U1 = pivA + n * kInvBatch;               //         first super-diagonal of the upper factor
-  double* Y = U1 + n * kInvBatch;                  //         right-hand side after the forward sweep
-  double* Zv = Y + n * kInvBatch;                  //         current iterate
-  double* Zg = trid_Z(jb);
-  const double tol = 2.220446049250313e-16 * tnorm;
-  for (int b0 = 0; b0 < r; b0 += kInvBatch) {
-    const int t = tid;
-    if (t < kInvBatch && b0 + t < r) {
-      const int k = b0 + t;
-      const double lam = slam[k];
-      for (int i = 0; i < n; ++i) {
-        const uint32_t u = trid_mix((uint32_t)i * 0x9E3779B9u + (uint32_t)k * 0x85EBCA6Bu + 0x1234567u);
-        Zv[i * kInvBatch + t] = (double)u * (1. / 2147483648.) - 1.;
-      }
-      for (int it = 0; it < 3; ++it) {
-        uint64_t pv_lo = 0ull, pv_hi = 0ull;                           // bit i: rows interchanged at step i
-        // forward: elimination with partial pivoting and the forward substitution in one sweep
-        double a = sd[0] - lam, du = se[0], y = Zv[t];
-        for (int i = 0; i + 1 < n; ++i) {
-          const double sub = se[i], dn = sd[i + 1] - lam, en = i + 2 < n ? se[i + 1] : 0.;
-          const double rhs = Zv[(i + 1) * kInvBatch + t];
-          if (fabs(a) >= fabs(sub)) {
-            if (a == 0.) a = tol;
-            const double ra = rcp_nr(fabs(a) < tol ? (a < 0. ? -tol : tol) : a);
-            const double f = sub * ra;
-            pivA[i * kInvBatch + t] = ra;                              // reciprocal pivots: the back substitution multiplies
-            U1[i * kInvBatch + t] = du;
-            Y[i * kInvBatch + t] = y;
-            a = dn - f * du;
-            du = en;
-            y = rhs - f * y;
-          } else {
-            const double rs = rcp_nr(sub);                             // |sub| > |a| >= 0
-            const double f = a * rs;
-            if (i < 64) pv_lo |= 1ull << i; else pv_hi |= 1ull << (i - 64);
-            pivA[i * kInvBatch + t] = fabs(sub) < tol ? (sub < 0. ? -1. / tol : 1. / tol) : rs;
-            U1[i * kInvBatch + t] = dn;
-            Y[i * kInvBatch + t] = rhs;
-            a = du - f * dn;
-            du = -f * en;
-            y = y - f * rhs;
-          }
-        }
-        if (fabs(a) < tol) a = a < 0. ? -tol : tol;
-        pivA[(n - 1) * kInvBatch + t] = rcp_nr(a);
-        Y[(n - 1) * kInvBatch + t] = y;
-        // backward substitution; second super-diagonal: e[i + 1] where rows were interchanged
-        double z1 = 0., z2 = 0., zmax = 0.;
-        for (int i = n - 1; i >= 0; --i) {
-          const double rp = pivA[i * kInvBatch + t];
-          double sacc = Y[i * kInvBatch + t];
-          if (i + 1 < n) sacc -= U1[i * kInvBatch + t] * z1;
-          const bool swapped = i < 64 ? ((pv_lo >> i) & 1ull) : ((pv_hi >> (i - 64)) & 1ull);
-          if (i + 2 < n && swapped) sacc -= se[i + 1] * z2;
-          const double z = sacc * rp;
-          Zv[i * kInvBatch + t] = z;
-          zmax = fmax(zmax, fabs(z));
-          z2 = z1;
-          z1 = z;
-        }
-        const double sc = zmax > 0. ? 1. / zmax : 1.;
-        for (int i = 0; i < n; ++i) Zv[i * kInvBatch + t] *= sc;
-      }
-      double nrm2 = 0.;
-      for (int i = 0; i < n; ++i) nrm2 += Zv[i * kInvBatch + t] * Zv[i * kInvBatch + t];
-      const double inv = nrm2 > 0. ? rsqrt(nrm2) : 0.;
-      for (int i = 0; i < n; ++i) Zg[(size_t)k * n + i] = Zv[i * kInvBatch + t] * inv;
-    }
-    __syncthreads();
   }
 }
 
-// (4) U[:, k] = H_0 H_1 .. H_{n-2} z_k, the phase convention and the float32 factor: one wavefront per
-// eigenvector, the vector in registers (rows lane and lane + 64), the reflectors read kAheadRefl ahead.
-constexpr int kAheadRefl = 4;
-__global__ __launch_bounds__(64) void k_trid_back(EigJobs jobs) {
+// One workgroup per matrix; the code for its own extent.
+template <int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W / 4))) void k_trid(EigJobs jobs) {
+  __shared__ TridLds lds;
+  const EigJob jb = jobs.job[blockIdx.x];
+  constexpr int A = 16 / W;                      // row blocks per block of 32 columns
+  if (jb.n <= 32) tridiagonalise<W, A, 1>(jb, lds);
+  else if (jb.n <= 64) tridiagonalise<W, 2 * A, 2>(jb, lds);
+  else if constexpr (W == 8) {
+    if (jb.n <= 96) tridiagonalise<W, 3 * A, 3>(jb, lds);
+    else tridiagonalise<W, 4 * A, 4>(jb, lds);
+  }
+}
+
+// Eigenvector k of job blockIdx.y.  T is scaled by a power of two so that its spectral radius lies in [1, 2).
+// Sturm counts without divisions: p_(i+1) = (d_i - x) p_i - e_(i-1)^2 p_(i-1), one sign change per eigenvalue below x;
+// the chain is one multiply-add per row (a quotient recurrence has a reciprocal in it).  Every eighth row the pair is
+// brought back to order one; e^2 has a floor of 1e-60 so that no two consecutive p vanish: a pair then shrinks by at most
+// 1e-240 between two such rows.
+constexpr int kAheadRefl = 12;
+__global__ __launch_bounds__(64) void k_trid_vec(EigJobs jobs) {
   const EigJob jb = jobs.job[blockIdx.y];
   const int n = jb.n, r = jb.r;
   const int k = blockIdx.x;
-  if (k >= r || jb.status[2] != 0) return;
+  if (k >= r) return;
   const int lane = threadIdx.x;
+  __shared__ double2 de[kEigTriMaxN + 8];        // (d_i, e_(i-1)^2), scaled; past n: rows that change no sign
+  __shared__ double sd[kEigTriMaxN + 2], se[kEigTriMaxN + 2];
+  __shared__ double2 slu[kEigTriMaxN + 2][2];    // (1 / pivot, first super-diagonal), (second, multiplier)
+  __shared__ double sy[kEigTriMaxN + 2], sz[kEigTriMaxN + 2];
+  const double gl = trid_bounds(jb)[0], gu = trid_bounds(jb)[1];
+  const double tn = fmax(fabs(gl), fabs(gu));
+  if (!(tn > 0.) || !(tn <= 1e300) || gl != gl || gu != gu) {            // zero matrix, inf or NaN
+    if (lane == 0) jb.status[2] = 1;
+    return;
+  }
+  const int ex = -ilogb(tn);
+  auto scaled = [&](double v) { return ldexp(v, ex); };
+  for (int i = lane; i < kEigTriMaxN + 8; i += 64) {
+    const double d = i < n ? scaled(trid_d(jb)[i]) : 8.;                 // d - x > 0 and e = 0: p keeps its sign
+    const double e = i < n ? scaled(trid_e(jb)[i]) : 0.;
+    const double ep = i > 0 && i < n ? scaled(trid_e(jb)[i - 1]) : 0.;
+    de[i] = make_double2(d, i < n ? fmax(ep * ep, 1e-60) : 0.);
+    if (i < kEigTriMaxN + 2) {
+      sd[i] = i < n ? d : 0.;
+      se[i] = e;
+    }
+  }
+  __syncthreads();
+  auto sturm_count = [&](double x) -> int {      // eigenvalues below x
+    double p0 = 0., p1 = 1.;
+    int c = 0;
+    for (int i0 = 0; i0 < n; i0 += 8) {
+      double2 t[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) t[u] = de[i0 + u];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const double p2 = fma(t[u].x - x, p1, -(t[u].y * p0));
+        c += (int)((uint32_t)(__double2hiint(p2) ^ __double2hiint(p1)) >> 31);
+        p0 = p1;
+        p1 = p2;
+      }
+      const int e = -__builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
+      p0 = ldexp(p0, e);
+      p1 = ldexp(p1, e);
+    }
+    return c;
+  };
+  const double tnorm = scaled(tn);
+  const int kasc = n - 1 - k;                    // k-th largest = kasc-th smallest (0-based)
+  double lo = scaled(gl), hi = scaled(gu);
+  for (int step = 0; step < kMultiSteps; ++step) {
+    const double h = (hi - lo) * (1. / 65.);
+    const bool above = sturm_count(lo + (lane + 1) * h) > kasc;          // more than kasc eigenvalues below the point
+    const uint64_t bal = __ballot(above);
+    const int jf = bal ? __builtin_ctzll(bal) : 64;                      // the eigenvalue lies below point jf and not below jf - 1
+    const double nlo = jf == 0 ? lo : lo + jf * h;
+    const double nhi = jf == 64 ? hi : lo + (jf + 1) * h;
+    lo = nlo;
+    hi = nhi;
+  }
+  const double lam = 0.5 * (lo + hi);
+  // the next eigenvalue (also the one behind the last kept one) must be separated
+  if (!(fabs(lam) <= 1e300) || (k + 1 < n && sturm_count(lam - kClusterTol * tnorm) != kasc)) {
+    if (lane == 0) jb.status[2] = 1;
+    return;
+  }
+
+  // ---- inverse iteration: serial, every lane computes the same; lane 0 writes the arrays ----
+  const double tol = 2.220446049250313e-16 * tnorm;
+  uint64_t pv_lo = 0ull, pv_hi = 0ull;           // bit i: rows interchanged at step i
+  {
+    double a = sd[0] - lam, du = se[0];
+    double sub = se[0], dn = sd[1] - lam, en = se[1];
+    for (int i = 0; i + 1 < n; ++i) {            // elimination with partial pivoting; the next row is read one ahead
+      const double nsub = se[i + 1], ndn = sd[i + 2] - lam, nen = se[i + 2];
+      const bool swap = fabs(a) < fabs(sub);
+      double piv = swap ? sub : a;
+      if (fabs(piv) < tol) piv = piv < 0. ? -tol : tol;
+      const double rp = rcp_nr(piv);
+      const double f = (swap ? a : sub) * rp;
+      if (lane == 0) {
+        slu[i][0] = make_double2(rp, swap ? dn : du);
+        slu[i][1] = make_double2(swap ? en : 0., f);
+      }
+      if (i < 64) pv_lo |= (uint64_t)swap << i; else pv_hi |= (uint64_t)swap << (i - 64);
+      const double na = swap ? du - f * dn : dn - f * du;
+      du = swap ? -f * en : en;
+      a = na;
+      sub = nsub;
+      dn = ndn;
+      en = nen;
+    }
+    if (fabs(a) < tol) a = a < 0. ? -tol : tol;
+    if (lane == 0) {
+      slu[n - 1][0] = make_double2(rcp_nr(a), 0.);
+      slu[n - 1][1] = make_double2(0., 0.);
+    }
+  }
+  const int r0 = lane, r1 = lane + 64;
+  // the first reflectors of the back-transformation go in flight
   const double2* Vg = reinterpret_cast<const double2*>(jb.V);
   const double2* tauG = trid_tau(jb);
-  const double* Zg = trid_Z(jb);
-  const int r0 = lane, r1 = lane + 64;
-  double2 x0 = make_double2(r0 < n ? Zg[(size_t)k * n + r0] : 0., 0.);
-  double2 x1 = make_double2(r1 < n ? Zg[(size_t)k * n + r1] : 0., 0.);
   double2 pv0[kAheadRefl], pv1[kAheadRefl], ptau[kAheadRefl];
   auto issue = [&](int i, int slot) {
     const double2 zero = make_double2(0., 0.);
@@ -1421,6 +1493,58 @@ __global__ __launch_bounds__(64) void k_trid_back(EigJobs jobs) {
   };
 #pragma unroll
   for (int d = 0; d < kAheadRefl; ++d) issue(n - 2 - d, d);
+  auto start = [&](int i) -> double {
+    const uint32_t u = trid_mix((uint32_t)i * 0x9E3779B9u + (uint32_t)k * 0x85EBCA6Bu + 0x1234567u);
+    return (double)u * (1. / 2147483648.) - 1.;
+  };
+  double z0 = r0 < n ? start(r0) : 0., z1 = r1 < n ? start(r1) : 0.;
+  for (int it = 0; it < 3; ++it) {
+    __syncthreads();                             // (one wavefront: orders the LDS accesses)
+    sz[r0] = z0;
+    sz[r1] = z1;
+    __syncthreads();
+    double y = sz[0], f = slu[0][1].y, rhs = sz[1];
+    for (int i = 0; i + 1 < n; ++i) {            // forward substitution
+      const double nf = slu[i + 1][1].y, nrhs = sz[i + 2];
+      const bool swap = i < 64 ? (pv_lo >> i) & 1ull : (pv_hi >> (i - 64)) & 1ull;
+      const double keep = swap ? rhs : y;
+      y = swap ? y - f * rhs : rhs - f * y;
+      if (lane == 0) sy[i] = keep;
+      f = nf;
+      rhs = nrhs;
+    }
+    if (lane == 0) sy[n - 1] = y;
+    __syncthreads();
+    double zn1 = 0., zn2 = 0.;
+    double2 p = slu[n - 1][0];
+    double u2 = slu[n - 1][1].x, yi = sy[n - 1];
+    for (int i = n - 1; i >= 0; --i) {           // back substitution
+      const int j = i > 0 ? i - 1 : 0;
+      const double2 np = slu[j][0];
+      const double nu2 = slu[j][1].x, nyi = sy[j];
+      const double z = (yi - u2 * zn2 - p.y * zn1) * p.x;
+      if (lane == 0) sz[i] = z;
+      zn2 = zn1;
+      zn1 = z;
+      p = np;
+      u2 = nu2;
+      yi = nyi;
+    }
+    __syncthreads();
+    z0 = r0 < n ? sz[r0] : 0.;
+    z1 = r1 < n ? sz[r1] : 0.;
+    double zmax = fmax(fabs(z0), fabs(z1));
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) zmax = fmax(zmax, __shfl_xor(zmax, off, 64));
+    const double sc = zmax > 0. ? 1. / zmax : 1.;
+    z0 *= sc;
+    z1 *= sc;
+  }
+  const double nrm2 = wave_sum_d(z0 * z0 + z1 * z1);
+  const double inv = nrm2 > 0. ? rsqrt(nrm2) : 0.;
+
+  // ---- U[:, k] = H_0 H_1 .. H_(n-2) z, the reflectors read kAheadRefl ahead ----
+  double2 x0 = make_double2(z0 * inv, 0.), x1 = make_double2(z1 * inv, 0.);
   for (int base = n - 2; base >= 0; base -= kAheadRefl) {
 #pragma unroll
     for (int d = 0; d < kAheadRefl; ++d) {
@@ -1569,16 +1693,10 @@ void launch_eig_batch(hipStream_t s, int njobs, const double* const* gram, doubl
     if (use_fast) {
       int rmax = 1;
       for (int i = 0; i < nsmall; ++i) rmax = small.job[i].r > rmax ? small.job[i].r : rmax;
-      const size_t inv = (size_t)4 * nmax * kInvBatch * sizeof(double);
-      const size_t lds_t = lds > inv ? lds : inv;
-      static bool attr_t = false;
-      if (!attr_t) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_trid), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  kEigTriMaxN * (kEigTriMaxN + 1) / 2 * (int)sizeof(double2));
-        attr_t = true;
-      }
-      k_trid<<<dim3((unsigned)nsmall), dim3(kTridThreads), lds_t, s>>>(small);
-      k_trid_back<<<dim3((unsigned)rmax, (unsigned)nsmall), dim3(64), 0, s>>>(small);
+      const dim3 grid((unsigned)nsmall);
+      if (nmax <= 64) k_trid<4><<<grid, dim3(256), 0, s>>>(small);
+      else k_trid<8><<<grid, dim3(512), 0, s>>>(small);
+      k_trid_vec<<<dim3((unsigned)rmax, (unsigned)nsmall), dim3(64), 0, s>>>(small);
     }
     k_eig_tri<<<dim3((unsigned)nsmall), dim3(kEigThreads), lds, s>>>(small);
     k_eig_apply<<<dim3((unsigned)nmax, (unsigned)nsmall), dim3(64), 0, s>>>(small);
