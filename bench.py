@@ -349,6 +349,8 @@ def main():
         mm = model.get(name)
         if mm:
             lp = mm.get("launches_per_step", 1)
+            if name == "gram" and "eig_jacobi" in times:          # small tensors: all modes in one bracket
+                lp = max(1, round(v["launches"] / max(1, times["eig_jacobi"]["launches"])))
             gbs = mm["bytes"] / lp / (avg * 1e-3) / 1e9
             tfl = mm["flops"] / lp / (avg * 1e-3) / 1e12
             ent["GBps"] = round(gbs, 1)

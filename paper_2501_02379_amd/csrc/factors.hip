@@ -14,6 +14,7 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "launch_util.h"
 
 namespace tgrad {
 
@@ -255,25 +256,28 @@ __global__ __launch_bounds__(kGramThreads) void k_gram(const void* __restrict__ 
 }
 
 // -------------------------------------------------------------------------------------------------
-// k_gram128: the same Gram for extents In <= 128 - one super block, on the diagonal - which is every
-// mode of the FNO shapes.  Same staging scheme and the same arithmetic as k_gram's diagonal case (the
-// two LDS areas take turns, one barrier per staged tile of 16 columns); what differs is what runs
-// next to the f64 matrix instructions, which occupy the SIMD's vector ALU as well:
-//  * 8 wavefronts instead of 16 (256 registers each): the accumulators of 6 tiles and a fetched tile
-//    stay in registers with nothing spilled.  (A spill reload is a vector-memory load: it waits for
-//    every prefetch in flight and puts the memory latency back in front of the matrix phase.)
-//  * Fetch: the element and its support-mask word come through two buffer descriptors (the tile's
-//    first column as base, rebuilt in scalar registers per tile).  A lane's offset is invariant -
-//    row * B + column, plus the wrap into the next leading index - and lanes without an element
-//    (row >= In, column past the chunk) use an offset that the hardware range check answers with
-//    zero: no branches, no 64-bit vector arithmetic.  The mask is applied when the tile is
-//    committed to LDS, so nothing waits for the loads before the matrix phase.
-//  * Matrix phase: a wavefront's tiles are runs inside one tile ROW, so the row-side operands
-//    (xr | xi) and (xi | -xr) are fetched from LDS once per run and column pair (62 operand fetches
-//    per column pair instead of 108), three column pairs ahead of the matrix instructions that use
-//    them; the main loop exists once per shape of tile set, chosen outside the loop, so inside it
-//    the accumulators live in fixed registers.
-// With fewer than 8 tile rows (In <= 112) the tiles are dealt one by one as in k_gram.
+// k_gram128: the Gram for extents In <= 128 (every mode of the FNO shapes), up to four modes per launch (blockIdx.y).
+// A complex Hermitian product in THREE real ones.  With P1 = Xr Xr^T, P2 = Xi Xi^T and P3 = (Xr + Xi)(Xr - Xi)^T,
+//   Re = P1 + P2,   Im = Xi Xr^T - Xr Xi^T = P3 - P1 + P2,
+// so a 16 x 16 tile takes three matrix instructions per four tensor columns instead of four.  The products of
+// float32 numbers are exact in float64 and so, up to 29 bits of difference in exponent, are the sums Xr +- Xi; the
+// rounding of Im stays within that of P1 + P2, row norm times row norm, which is what the four-product form has.
+// What runs next to the f64 matrix instructions matters, because they occupy the SIMD's vector ALU:
+//  * RT tile rows (1, 2, 4 or 8) are held; a staged tile is 4096 elements whatever RT: 256 / RT columns, so a thread
+//    always has 8 loads in flight and a barrier is passed as rarely as the LDS allows.
+//  * LDS holds two planes (re, im) per staged tile, column by column, rows contiguous, an odd column stride: operand
+//    reads (16 rows x 4 columns) and commits are free of bank conflicts.  Xr +- Xi are formed in registers.
+//  * Fetch: the element and its support-mask word come through buffer descriptors (the tile's first column as
+//    base, scalar); lanes without an element use an offset that the range check answers with zero.
+//    The mask is applied at the commit, so nothing waits for the loads before the matrix phase.
+//  * RT = 8: the 36 tiles of the lower triangle over 8 wavefronts, runs inside one tile row (fewer than 8 tile rows
+//    present: dealt one by one).  RT <= 4: the wavefronts also split the columns of the staged tile - 10 tiles = 2 x 5,
+//    columns 4 ways; 3 or 1 tiles, columns 8 ways - and add their parts through LDS at the end: every SIMD has the
+//    same number of matrix instructions.
+//  * An extent of 16 RT + 1 (a half-spectrum mode) has its last row done by vector arithmetic, lane = column row:
+//    65 rows would need 15 tiles instead of 10.
+// Measured (rocprofv3, us per mode of 128x128x128x65; before: four products, 16-column tiles, 15 tiles for 65 rows):
+// 128 rows 1330 - 1385 -> 1010 (the matrix instructions alone: 765), 65 rows 1510 -> 707; a refresh 6558 -> 4809.
 struct GramRuns {                    // a wavefront's tiles when all 8 tile rows exist: run A = (ra, a0 .. a0 + na - 1),
   signed char ra, a0, na, rb, b0, nb;  // run B = (rb, b0 .. b0 + nb - 1), every run inside one tile row
 };
@@ -285,101 +289,110 @@ __constant__ GramRuns kGramRuns[8] = {
 
 constexpr int kGram128Threads = 512;
 
+struct GramJob {
+  const void* x;
+  const uint32_t* mask;
+  double* partials;
+  int64_t A, B, cols_per_chunk;
+  int In, nchunks;
+  uint32_t magicB;
+};
+struct GramJobs {
+  GramJob job[kMaxNdim];
+};
+
+__host__ __device__ constexpr int gram_cols(int RT) { return 256 / RT; }            // tensor columns per staged tile
+__host__ __device__ constexpr int gram_plane(int RT) { return gram_cols(RT) * (16 * RT + 1); }   // doubles
+
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t gram_buffer(const void* base, uint32_t bytes) {
   // untyped buffer, stride 0: a load at an offset >= bytes returns zero
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
 }
 
-template <int DT, bool SMALLB>
-__global__ __launch_bounds__(kGram128Threads) void k_gram128(const void* __restrict__ x,
-                                                             const uint32_t* __restrict__ mask, int64_t A, int In,
-                                                             int64_t B64, int64_t cols_per_chunk, uint32_t magicB,
-                                                             double* __restrict__ partials) {
+// tile t of the lower triangle of a tile grid
+__device__ constexpr int tri_row(int t) { int a = 0; while ((a + 1) * (a + 2) / 2 <= t) ++a; return a; }
+
+template <int DT, int RT>
+__global__ __launch_bounds__(kGram128Threads) void k_gram128(GramJobs jobs) {
   extern __shared__ double sG[];
+  const GramJob jb = jobs.job[blockIdx.y];
+  if ((int)blockIdx.x >= jb.nchunks) return;
+  constexpr int TC = gram_cols(RT), Q = 16 * RT + 1, PL = gram_plane(RT);
   constexpr int kEs = DT == TGRAD_C64 ? 8 : 4;        // bytes per element
   constexpr uint32_t kNowhere = 0xFFFFFFF0u;          // an offset beyond every descriptor: the load returns zero
-  double* buf0 = sG;
-  double* buf1 = sG + kSuper * kRowD;
-  const uint32_t B = (uint32_t)B64;                   // the host takes this kernel only when In * B < 2^28
-  const int64_t J = A * B64;
-  const int64_t c_begin = (int64_t)blockIdx.x * cols_per_chunk;
-  const int64_t c_end = c_begin + cols_per_chunk < J ? c_begin + cols_per_chunk : J;
+  constexpr int kTiles = RT == 8 ? 6 : RT == 4 ? 5 : RT == 2 ? 3 : 1;    // per wavefront
+  constexpr int CG = RT == 8 ? 1 : RT == 4 ? 4 : 8;   // wavefronts that share tiles and split the columns
+  const int In = jb.In;
+  const int64_t J = jb.A * jb.B;
+  const uint32_t B = (uint32_t)jb.B;                  // the host takes this kernel only when In * B < 2^28
+  const int64_t c_begin = (int64_t)blockIdx.x * jb.cols_per_chunk;
+  const int64_t c_end = c_begin + jb.cols_per_chunk < J ? c_begin + jb.cols_per_chunk : J;
   const bool empty = c_begin >= c_end;                // (workgroup-uniform) a trailing chunk without columns writes zeros
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int part = (lane >> 4) & 1, ccol = lane >> 5, lrow = lane & 15;
+  const int lrow = lane & 15, lcol = lane >> 4;
   const int ntr = (In + 15) >> 4;                     // tile rows present
+  const bool tail = RT < 8 && In == 16 * RT + 1;
 
-  // ---- staging: a thread owns kPer elements (il, cl) of every staged tile ----
-  constexpr int kPer = kSuper * kTC / kGram128Threads;   // 4
-  // lane-invariant offset (elements) of (il, cl) from the tile's first column, before any wrap of the
-  // column into the next leading index; rows that do not exist point nowhere
-  const uint32_t wrap_add = (uint32_t)(In - 1) * B;
-  uint32_t off0[kPer];
-  int cl[kPer], lds_slot[kPer];
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    const int e = tid + u * kGram128Threads;
-    int il;
-    if (B == 1) { il = e % kSuper; cl[u] = e / kSuper; } else { il = e / kTC; cl[u] = e % kTC; }
-    off0[u] = il < In ? (uint32_t)il * B + (uint32_t)cl[u] : kNowhere;
-    lds_slot[u] = il * kRowD + 4 * cl[u];
-  }
+  // ---- staging: thread's elements (il, cl) = first + u * step, u < 8; the ninth is the tail row's ----
+  constexpr int kPer = 4096 / kGram128Threads;
+  const bool last = B == 1;                           // the mode is the fastest index in memory: lanes along rows
+  const int il0 = last ? tid % (16 * RT) : tid / TC, cl0 = last ? tid / (16 * RT) : tid % TC;
+  const int ilstep = last ? 0 : kGram128Threads / TC, clstep = last ? 32 / RT : 0;
+  const uint32_t ustep = last ? (uint32_t)clstep * (uint32_t)In : (uint32_t)ilstep * B;   // elements between them
+  const int slot0 = cl0 * Q + il0, slotstep = clstep * Q + ilstep;
+  const uint32_t wrap_add = (uint32_t)(In - 1) * B;   // a column past B continues one leading index further
   const uint64_t total_bytes = (uint64_t)J * (uint64_t)In * kEs;
-  const __amdgpu_buffer_rsrc_t rmask = gram_buffer(mask, mask ? (uint32_t)((((uint64_t)J * In + 31) >> 5) * 4) : 0u);
-
-  // the tile being fetched: first column c = (a0, b0) (workgroup-uniform, scalar registers)
-  uint32_t pa0 = (uint32_t)(c_begin / B64), pb0 = (uint32_t)(c_begin - (int64_t)pa0 * B64);
-  uint32_t pre0[kPer], pre1[kPer];                    // the fetched elements as they lie in memory
-  uint32_t pre_m[kPer], pre_g[kPer];                  // their mask words and global element indices
+  const __amdgpu_buffer_rsrc_t rmask =
+      gram_buffer(jb.mask, jb.mask ? (uint32_t)((((uint64_t)J * In + 31) >> 5) * 4) : 0u);
+  uint32_t pa0 = (uint32_t)(c_begin / jb.B), pb0 = (uint32_t)(c_begin - (int64_t)pa0 * jb.B);   // tile being fetched
+  uint32_t pre0[kPer + 1], pre1[kPer + 1], pre_m[kPer + 1], pre_g[kPer + 1];
+  auto wraps = [&](uint32_t c) -> uint32_t {          // (b0 + column) / B
+    const uint32_t nn = pb0 + c;
+    return B >= (uint32_t)TC ? (nn >= B ? 1u : 0u) : jb.magicB ? __umulhi(nn, jb.magicB) : nn;
+  };
   auto fetch_tile = [&](int64_t c0) {                 // the tile that starts at column c0 = (pa0, pb0) -> pre
-    const uint64_t base_e = (uint64_t)pa0 * (uint64_t)In * B + pb0;          // < 2^31 elements
-    const uint64_t base_b = base_e * kEs;
-    const uint64_t left = total_bytes - base_b;       // bytes of the tensor from the tile's first element on
-    const __amdgpu_buffer_rsrc_t rx =
-        gram_buffer(reinterpret_cast<const char*>(x) + base_b, left > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)left);
-    const uint32_t lim = (uint32_t)(c_end - c0 < kTC ? c_end - c0 : kTC);    // columns of this tile inside the chunk
-    const uint32_t base32 = (uint32_t)base_e;
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      uint32_t off;
-      if constexpr (SMALLB) {                         // B < 16: (b0 + cl) / B wraps, b0 + cl < 32
-        const uint32_t n = pb0 + (uint32_t)cl[u];
-        const uint32_t q = magicB ? __umulhi(n, magicB) : n;
-        off = off0[u] + q * wrap_add;
-      } else {                                        // B >= 16: at most one wrap
-        off = off0[u] + ((pb0 + (uint32_t)cl[u] >= B) ? wrap_add : 0u);
-      }
-      if (off0[u] == kNowhere || (uint32_t)cl[u] >= lim) off = kNowhere;
-      const uint32_t gi = base32 + off;               // global element index (unused where off points nowhere)
+    const uint64_t base_e = (uint64_t)pa0 * (uint64_t)In * B + pb0;      // < 2^31 elements
+    const uint64_t left = total_bytes - base_e * kEs;
+    const __amdgpu_buffer_rsrc_t rx = gram_buffer(reinterpret_cast<const char*>(jb.x) + base_e * kEs,
+                                                  left > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)left);
+    const int lim = (int)(c_end - c0 < TC ? c_end - c0 : TC);            // columns of this tile inside the chunk
+    auto load = [&](int u, bool ok, uint32_t off) {
+      const uint32_t gi = (uint32_t)base_e + off;
       pre_g[u] = gi;
-      const uint32_t voff = off == kNowhere ? kNowhere : off * kEs;
+      const uint32_t voff = ok ? off * kEs : kNowhere;
       if constexpr (DT == TGRAD_C64) {
         typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-        const u2 r = __builtin_amdgcn_raw_buffer_load_b64(rx, voff, 0, 0);
-        pre0[u] = r.x;
-        pre1[u] = r.y;
+        const u2 rr = __builtin_amdgcn_raw_buffer_load_b64(rx, voff, 0, 0);
+        pre0[u] = rr.x;
+        pre1[u] = rr.y;
       } else {
         pre0[u] = __builtin_amdgcn_raw_buffer_load_b32(rx, voff, 0, 0);
         pre1[u] = 0u;
       }
-      pre_m[u] = __builtin_amdgcn_raw_buffer_load_b32(rmask, off == kNowhere ? kNowhere : ((gi >> 5) << 2), 0, 0);
-    }
+      pre_m[u] = __builtin_amdgcn_raw_buffer_load_b32(rmask, ok ? ((gi >> 5) << 2) : kNowhere, 0, 0);
+    };
+    const uint32_t first = last ? (uint32_t)(il0 + cl0 * In) : (uint32_t)il0 * B + (uint32_t)cl0 + wraps((uint32_t)cl0) * wrap_add;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+      load(u, il0 + u * ilstep < In && il0 + u * ilstep < 16 * RT && cl0 + u * clstep < lim, first + (uint32_t)u * ustep);
+    if (tail)
+      load(kPer, tid < lim, last ? (uint32_t)(tid * In + In - 1)
+                                 : (uint32_t)(In - 1) * B + (uint32_t)tid + wraps((uint32_t)tid) * wrap_add);
   };
   auto next_tile = [&]() {
-    pb0 += kTC;
-    if constexpr (SMALLB) {
-      const uint32_t q = magicB ? __umulhi(pb0, magicB) : pb0;
+    pb0 += TC;
+    if (B >= (uint32_t)TC) {
+      if (pb0 >= B) { pb0 -= B; pa0 += 1; }
+    } else {
+      const uint32_t q = jb.magicB ? __umulhi(pb0, jb.magicB) : pb0;
       pa0 += q;
       pb0 -= q * B;
-    } else {
-      if (pb0 >= B) { pb0 -= B; pa0 += 1; }
     }
   };
-  auto commit = [&](double* d) {                      // pre -> one staged tile, as (xr, xi, xi, -xr) per element
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
+  auto commit = [&](double* d) {                      // pre -> one staged tile: plane of re, plane of im
+    auto put = [&](int u, int slot) {
       float fr, fi;
       if constexpr (DT == TGRAD_C64) {
         fr = __uint_as_float(pre0[u]);
@@ -389,96 +402,135 @@ __global__ __launch_bounds__(kGram128Threads) void k_gram128(const void* __restr
         fi = __uint_as_float(pre0[u] & 0xFFFF0000u);
       }
       const bool masked = (pre_m[u] >> (pre_g[u] & 31u)) & 1u;
-      const double xr = (double)(masked ? 0.f : fr), xi = (double)(masked ? 0.f : fi);
-      double2* q = reinterpret_cast<double2*>(d + lds_slot[u]);
-      q[0] = make_double2(xr, xi);
-      q[1] = make_double2(xi, -xr);
-    }
-  };
-
-  // ---- this wavefront's tiles ----
-  constexpr int kMaxT = 6;
-  int ti[kMaxT], tj[kMaxT];
-  bool mine[kMaxT];
-  if (ntr == 8) {
-    const GramRuns g = kGramRuns[wave];
-#pragma unroll
-    for (int k = 0; k < kMaxT; ++k) {
-      const bool in_a = k < g.na;
-      mine[k] = k < g.na + g.nb;
-      ti[k] = in_a ? g.ra : g.rb;
-      tj[k] = !mine[k] ? 0 : in_a ? g.a0 + k : g.b0 + (k - g.na);
-    }
-  } else {                                            // fewer tile rows: tile t of the lower triangle to wavefront t % 8
-    const int ntl = ntr * (ntr + 1) / 2;
-#pragma unroll
-    for (int k = 0; k < kMaxT; ++k) {
-      const int t = wave + 8 * k;
-      int a = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
-      while (a * (a + 1) / 2 > t) --a;
-      while ((a + 1) * (a + 2) / 2 <= t) ++a;
-      mine[k] = t < ntl;
-      ti[k] = mine[k] ? a : 0;
-      tj[k] = mine[k] ? t - a * (a + 1) / 2 : 0;
-    }
-  }
-  v4d accRe[kMaxT], accIm[kMaxT];
-#pragma unroll
-  for (int k = 0; k < kMaxT; ++k) {
-    accRe[k] = (v4d){0., 0., 0., 0.};
-    accIm[k] = (v4d){0., 0., 0., 0.};
-  }
-  const int lane_off = lrow * kRowD + 4 * ccol + part;   // doubles, within a tile row of a staged area
-  // A run of NT tiles of one tile row in accumulator slots S0 ..: the row-side operands are fetched
-  // once per column pair for the whole run, kAhead - 1 column pairs ahead of the matrix instructions
-  // (an LDS fetch right in front of its use leaves the matrix core idle for the LDS latency whenever
-  // the SIMD's other wavefront is not ready).
-  constexpr int kAhead = 3;
-  auto multiply_run = [&](const double* b, auto s0_c, auto nt_c) {
-    constexpr int S0 = decltype(s0_c)::value;
-    constexpr int NT = decltype(nt_c)::value;
-    const double* pa = b + 16 * ti[S0] * kRowD + lane_off;
-    const double* pb[NT];
-#pragma unroll
-    for (int k = 0; k < NT; ++k) pb[k] = b + 16 * tj[S0 + k] * kRowD + lane_off;
-    double ar[kAhead], ai[kAhead], bo[kAhead][NT];
-    auto fetch_ops = [&](int s2) {                    // column 2 s2 + ccol: 4 doubles per column
-      const int slot = s2 % kAhead;
-      ar[slot] = pa[8 * s2];                          // part ? xi : xr
-      ai[slot] = pa[8 * s2 + 2];                      // part ? -xr : xi
-#pragma unroll
-      for (int k = 0; k < NT; ++k) bo[slot][k] = pb[k][8 * s2];
+      d[slot] = (double)(masked ? 0.f : fr);
+      d[PL + slot] = (double)(masked ? 0.f : fi);
     };
 #pragma unroll
-    for (int s2 = 0; s2 < kAhead - 1; ++s2) fetch_ops(s2);
+    for (int u = 0; u < kPer; ++u) put(u, slot0 + u * slotstep);
+    if (tail && tid < TC) put(kPer, tid * Q + 16 * RT);
+  };
+
+  v4d p1[kTiles], p2[kTiles], p3[kTiles];
 #pragma unroll
-    for (int s2 = 0; s2 < kTC / 2; ++s2) {
-      if (s2 + kAhead - 1 < kTC / 2) fetch_ops(s2 + kAhead - 1);
-      __builtin_amdgcn_sched_barrier(0);
-      const int slot = s2 % kAhead;
+  for (int k = 0; k < kTiles; ++k) p1[k] = p2[k] = p3[k] = (v4d){0., 0., 0., 0.};
+  double t_re = 0., t_im = 0., t_dd = 0.;             // tail row against this lane's row, and itself
+  int ti[kTiles], tj[kTiles];
+  bool mine[kTiles];
+  const int tg = RT == 4 ? wave >> 2 : 0, cg = RT == 8 ? 0 : RT == 4 ? wave & 3 : wave;
+  if constexpr (RT == 8) {
+    if (ntr == 8) {
+      const GramRuns g = kGramRuns[wave];
+#pragma unroll
+      for (int k = 0; k < kTiles; ++k) {
+        const bool in_a = k < g.na;
+        mine[k] = k < g.na + g.nb;
+        ti[k] = in_a ? g.ra : g.rb;
+        tj[k] = !mine[k] ? 0 : in_a ? g.a0 + k : g.b0 + (k - g.na);
+      }
+    } else {                                          // fewer tile rows: tile t of the lower triangle to wavefront t % 8
+      const int ntl = ntr * (ntr + 1) / 2;
+#pragma unroll
+      for (int k = 0; k < kTiles; ++k) {
+        const int t = wave + 8 * k;
+        int a = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
+        while (a * (a + 1) / 2 > t) --a;
+        while ((a + 1) * (a + 2) / 2 <= t) ++a;
+        mine[k] = t < ntl;
+        ti[k] = mine[k] ? a : 0;
+        tj[k] = mine[k] ? t - a * (a + 1) / 2 : 0;
+      }
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < kTiles; ++k) {
+      const int t = tg * kTiles + k, a = tri_row(t);
+      ti[k] = a;
+      tj[k] = t - a * (a + 1) / 2;
+      mine[k] = a < ntr;
+    }
+  }
+  const int lane_off = lcol * Q + lrow;
+  auto three = [&](int k, double ar, double ai, double br, double bi) {
+    p1[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, p1[k], 0, 0, 0);
+    p2[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, bi, p2[k], 0, 0, 0);
+    p3[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar + ai, br - bi, p3[k], 0, 0, 0);
+  };
+  // A run of NT tiles of one tile row in accumulator slots S0 ..: the row-side operands are fetched once per four
+  // columns for the whole run, one step ahead of the matrix instructions.
+  auto multiply_run = [&](const double* b, auto s0_c, auto nt_c) {
+    constexpr int S0 = decltype(s0_c)::value, NT = decltype(nt_c)::value, STEPS = TC / 4;
+    const double* pa = b + 16 * ti[S0] + lane_off;
+    const double* pb[NT];
+#pragma unroll
+    for (int k = 0; k < NT; ++k) pb[k] = b + 16 * tj[S0 + k] + lane_off;
+    double ar[2], ai[2], br[2][NT], bi[2][NT];
+    auto fetch_ops = [&](int s) {
+      const int slot = s & 1;
+      ar[slot] = pa[4 * s * Q];
+      ai[slot] = pa[4 * s * Q + PL];
 #pragma unroll
       for (int k = 0; k < NT; ++k) {
-        accRe[S0 + k] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[slot], bo[slot][k], accRe[S0 + k], 0, 0, 0);
-        accIm[S0 + k] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai[slot], bo[slot][k], accIm[S0 + k], 0, 0, 0);
+        br[slot][k] = pb[k][4 * s * Q];
+        bi[slot][k] = pb[k][4 * s * Q + PL];
+      }
+    };
+    fetch_ops(0);
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+      if (s + 1 < STEPS) fetch_ops(s + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 0; k < NT; ++k) three(S0 + k, ar[s & 1], ai[s & 1], br[s & 1][k], bi[s & 1][k]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto multiply_single = [&](const double* b) {       // tile by tile
+#pragma unroll
+    for (int k = 0; k < kTiles; ++k) {
+      if (mine[k]) {
+        const double* pa = b + 16 * ti[k] + lane_off;
+        const double* pb = b + 16 * tj[k] + lane_off;
+#pragma unroll
+        for (int s = 0; s < TC / 4; ++s) three(k, pa[4 * s * Q], pa[4 * s * Q + PL], pb[4 * s * Q], pb[4 * s * Q + PL]);
+      }
+    }
+  };
+  // RT <= 4: all tiles of group G on this wavefront's steps; every tile row's operands are read once per step
+  auto multiply_group = [&](const double* b, auto g_c) {
+    constexpr int G = decltype(g_c)::value, STEPS = TC / 4 / CG;
+    constexpr int NR = RT == 4 ? (G == 0 ? 3 : 4) : RT;                  // tile rows the group touches
+    const double* pa = b + cg * 4 * Q + lane_off;
+    double xr[2][NR], xi[2][NR];
+    auto fetch_ops = [&](int s) {
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        xr[s & 1][q] = pa[4 * CG * s * Q + 16 * q];
+        xi[s & 1][q] = pa[4 * CG * s * Q + 16 * q + PL];
+      }
+    };
+    fetch_ops(0);
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+      if (s + 1 < STEPS) fetch_ops(s + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 0; k < kTiles; ++k) {
+        constexpr int t0 = G * kTiles;
+        const int a = tri_row(t0 + k), c = t0 + k - a * (a + 1) / 2;     // (constants after unrolling)
+        if (a < ntr) three(k, xr[s & 1][a], xi[s & 1][a], xr[s & 1][c], xi[s & 1][c]);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  auto multiply_single = [&](const double* b) {       // fewer than 8 tile rows: tile by tile
+  auto tail_row = [&](const double* b) {              // row 16 RT against every row; columns wave, wave + 8, ..
+    const int jl = lane < 16 * RT ? lane : 16 * RT - 1;
 #pragma unroll
-    for (int k = 0; k < kMaxT; ++k) {
-      if (mine[k]) {
-        const double* pa = b + 16 * ti[k] * kRowD + lane_off;
-        const double* pb = b + 16 * tj[k] * kRowD + lane_off;
-#pragma unroll
-        for (int s2 = 0; s2 < kTC / 2; ++s2) {
-          const double aRe = pa[8 * s2];
-          const double aIm = pa[8 * s2 + 2];
-          const double bop = pb[8 * s2];
-          accRe[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(aRe, bop, accRe[k], 0, 0, 0);
-          accIm[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(aIm, bop, accIm[k], 0, 0, 0);
-        }
-      }
+    for (int c = 0; c < TC / 8; ++c) {
+      const double* col = b + (wave + 8 * c) * Q;
+      const double yr = col[16 * RT], yi = col[16 * RT + PL], xr = col[jl], xi = col[jl + PL];
+      t_re += yr * xr + yi * xi;
+      t_im += yi * xr - yr * xi;
+      t_dd += yr * yr + yi * yi;
     }
   };
   using I0 = std::integral_constant<int, 0>;
@@ -487,47 +539,109 @@ __global__ __launch_bounds__(kGram128Threads) void k_gram128(const void* __restr
   using I3 = std::integral_constant<int, 3>;
   using I4 = std::integral_constant<int, 4>;
 
-  // ---- main loop: while the wavefronts multiply tile t out of one LDS area, tile t + 1 is committed
-  // into the other (read last for tile t - 1, before the barrier that ended it) and tile t + 2 is
-  // fetched.  One instance of the loop per shape of a wavefront's tile set; every instance passes the
-  // same barriers. ----
-  auto main_loop = [&](auto na_c, auto nb_c) {        // (NA, NB): runs of NA and NB tiles; (0, 0): tile by tile
-    constexpr int NA = decltype(na_c)::value;
-    constexpr int NB = decltype(nb_c)::value;
+  // ---- main loop: while the wavefronts multiply tile t out of one LDS area, tile t + 1 is committed into the other
+  // (read last for tile t - 1, before the barrier that ended it) and tile t + 2 is fetched.  One instance of the loop
+  // per shape of a wavefront's tile set; every instance passes the same barriers. ----
+  auto main_loop = [&](auto multiply) {
+    double* buf0 = sG;
+    double* buf1 = sG + 2 * PL;
     fetch_tile(c_begin);
     commit(buf0);
-    if (c_begin + kTC < c_end) { next_tile(); fetch_tile(c_begin + kTC); }
+    if (c_begin + TC < c_end) { next_tile(); fetch_tile(c_begin + TC); }
     __syncthreads();
     int it = 0;
-    for (int64_t c0 = c_begin; c0 < c_end; c0 += kTC, ++it) {
+    for (int64_t c0 = c_begin; c0 < c_end; c0 += TC, ++it) {
       double* cur = (it & 1) ? buf1 : buf0;
       double* nxt = (it & 1) ? buf0 : buf1;
-      if (c0 + kTC < c_end) commit(nxt);
-      if (c0 + 2 * kTC < c_end) { next_tile(); fetch_tile(c0 + 2 * kTC); }
-      if constexpr (NA == 0) {
-        multiply_single(cur);
-      } else {
-        multiply_run(cur, I0{}, na_c);
-        if constexpr (NB > 0) multiply_run(cur, na_c, nb_c);
-      }
+      if (c0 + TC < c_end) commit(nxt);
+      if (c0 + 2 * TC < c_end) { next_tile(); fetch_tile(c0 + 2 * TC); }
+      multiply(cur);
+      if (tail) tail_row(cur);
       __syncthreads();
     }
   };
   if (!empty) {
-    if (ntr != 8) main_loop(I0{}, I0{});
-    else if (wave < 4) main_loop(I3{}, I2{});
-    else if (wave == 4) main_loop(I3{}, I1{});
-    else main_loop(I4{}, I0{});                        // both runs lie in one tile row: a run of 4
+    if constexpr (RT == 8) {
+      if (ntr != 8) main_loop([&](const double* b) { multiply_single(b); });
+      else if (wave < 4) main_loop([&](const double* b) { multiply_run(b, I0{}, I3{}); multiply_run(b, I3{}, I2{}); });
+      else if (wave == 4) main_loop([&](const double* b) { multiply_run(b, I0{}, I3{}); multiply_run(b, I3{}, I1{}); });
+      else main_loop([&](const double* b) { multiply_run(b, I0{}, I4{}); });   // both runs lie in one tile row: a run of 4
+    } else if constexpr (RT == 4) {
+      if (tg == 0) main_loop([&](const double* b) { multiply_group(b, I0{}); });
+      else main_loop([&](const double* b) { multiply_group(b, I1{}); });
+    } else {
+      main_loop([&](const double* b) { multiply_group(b, I0{}); });
+    }
   }
-  double2* out = reinterpret_cast<double2*>(partials) + (int64_t)blockIdx.x * In * In;
+  // Re = P1 + P2 and Im = P3 - P1 + P2 replace p1 and p2
 #pragma unroll
-  for (int k = 0; k < kMaxT; ++k) {
-    if (mine[k]) {
-      for (int r = 0; r < 4; ++r) {
-        const int i = 16 * ti[k] + 4 * r + (lane >> 4);
-        const int j = 16 * tj[k] + (lane & 15);
-        if (i < In && j < In) out[(int64_t)i * In + j] = make_double2(accRe[k][r], accIm[k][r]);
+  for (int k = 0; k < kTiles; ++k) {
+    const v4d re = p1[k] + p2[k];
+    p2[k] = p3[k] - p1[k] + p2[k];
+    p1[k] = re;
+  }
+  if constexpr (CG > 1) {
+    // the column groups' parts: upper half onto the lower one until one is left (RT = 4: one group at a time, they do
+    // not fit in pairs), always the same order
+    constexpr int kPart = kTiles * 8 * 64;
+    int hi = CG;
+#pragma unroll
+    for (int round = 0; round < 3; ++round) {
+      const int half = RT == 4 ? hi - 1 : hi / 2;
+      double* area = sG + (tg * (RT == 4 ? 1 : CG / 2) + (cg >= half ? cg - half : cg)) * kPart + lane;
+      if (cg >= half && cg < hi) {
+#pragma unroll
+        for (int k = 0; k < kTiles; ++k)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            area[(k * 8 + r) * 64] = p1[k][r];
+            area[(k * 8 + 4 + r) * 64] = p2[k][r];
+          }
       }
+      __syncthreads();
+      if (cg < hi - half) {
+#pragma unroll
+        for (int k = 0; k < kTiles; ++k)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            p1[k][r] += area[(k * 8 + r) * 64];
+            p2[k][r] += area[(k * 8 + 4 + r) * 64];
+          }
+      }
+      __syncthreads();
+      hi = half;
+    }
+  }
+  double2* out = reinterpret_cast<double2*>(jb.partials) + (int64_t)blockIdx.x * In * In;
+  if (cg == 0) {
+#pragma unroll
+    for (int k = 0; k < kTiles; ++k) {
+      if (mine[k]) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = 16 * ti[k] + 4 * r + (lane >> 4);
+          const int j = 16 * tj[k] + (lane & 15);
+          if (i < In && j < In && i < 16 * RT) out[(int64_t)i * In + j] = make_double2(p1[k][r], p2[k][r]);
+        }
+      }
+    }
+  }
+  if (tail) {                                         // the wavefronts' columns of the tail row, in order
+    double* area = sG + lane;
+    area[(wave * 3) * 64] = t_re;
+    area[(wave * 3 + 1) * 64] = t_im;
+    area[(wave * 3 + 2) * 64] = t_dd;
+    __syncthreads();
+    if (wave == 0) {
+      double re = 0., im = 0., dd = 0.;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) {
+        re += area[(w * 3) * 64];
+        im += area[(w * 3 + 1) * 64];
+        dd += area[(w * 3 + 2) * 64];
+      }
+      if (lane < 16 * RT) out[(int64_t)(16 * RT) * In + lane] = make_double2(re, im);
+      if (lane == 0) out[(int64_t)(16 * RT) * In + 16 * RT] = make_double2(dd, 0.);
     }
   }
 }
@@ -538,25 +652,33 @@ __global__ __launch_bounds__(kGram128Threads) void k_gram128(const void* __restr
 // order: the result does not depend on the launch, and 8 times as many loads are in flight.
 constexpr int kReduceSplit = 8;
 constexpr int kReduceElems = 256 / kReduceSplit;     // entries per workgroup
-__global__ __launch_bounds__(256) void k_gram_reduce(const double* __restrict__ partials, int nchunks, int In,
-                                                     double* __restrict__ gram) {
+struct ReduceJobs {
+  const double* partials[kMaxNdim];
+  double* gram[kMaxNdim];
+  int In[kMaxNdim], nchunks[kMaxNdim];
+};
+__global__ __launch_bounds__(256) void k_gram_reduce(ReduceJobs jobs) {
   __shared__ double2 part[kReduceSplit][kReduceElems];
+  const int In = jobs.In[blockIdx.y], nchunks = jobs.nchunks[blockIdx.y];
   const int el = threadIdx.x % kReduceElems, sub = threadIdx.x / kReduceElems;
   const int64_t e = (int64_t)blockIdx.x * kReduceElems + el;
   const int64_t n2 = (int64_t)In * In;
+  if ((int64_t)blockIdx.x * kReduceElems >= n2) return;
   const bool in = e < n2;
   const int i = in ? (int)(e / In) : 0, j = in ? (int)(e - (int64_t)i * In) : 0;
   const int64_t src = i >= j ? (int64_t)i * In + j : (int64_t)j * In + i;
   const int per = (nchunks + kReduceSplit - 1) / kReduceSplit;
   const int c0 = sub * per, c1 = c0 + per < nchunks ? c0 + per : nchunks;
-  const double2* p2 = reinterpret_cast<const double2*>(partials);
+  const double2* p2 = reinterpret_cast<const double2*>(jobs.partials[blockIdx.y]);
   double re = 0., im = 0.;
-  if (in)
+  if (in) {
+#pragma unroll 8
     for (int c = c0; c < c1; ++c) {
       const double2 v = p2[(int64_t)c * n2 + src];
       re += v.x;
       im += v.y;
     }
+  }
   part[sub][el] = make_double2(re, im);
   __syncthreads();
   if (sub == 0 && in) {
@@ -566,7 +688,7 @@ __global__ __launch_bounds__(256) void k_gram_reduce(const double* __restrict__ 
       sr += part[q][el].x;
       si += part[q][el].y;
     }
-    reinterpret_cast<double2*>(gram)[e] = make_double2(sr, i >= j ? si : -si);
+    reinterpret_cast<double2*>(jobs.gram[blockIdx.y])[e] = make_double2(sr, i > j ? si : i < j ? -si : 0.);
   }
 }
 
@@ -1604,54 +1726,111 @@ size_t eig_work_bytes(int n) {
   return sizeof(EigLogHeader) + (size_t)kEigMaxSweeps * (m - 1) * (m / 2) * sizeof(RotLog);
 }
 
+// Tile rows that k_gram128 holds for an extent (0: the kernel for larger extents), 16 RT + 1 included where that
+// row is done by vector arithmetic.  Its lane offsets reach two leading indices ahead: 2 In B elements of at most 8 bytes.
+static int gram_rows(int In, int64_t B) {
+  if (In > kSuper || (int64_t)In * B >= ((int64_t)1 << 28)) return 0;
+  return In <= 17 ? 1 : In <= 33 ? 2 : In <= 65 ? 4 : 8;
+}
+static int64_t gram_tiles(int64_t A, int In, int64_t B) {
+  const int rt = gram_rows(In, B), tc = rt ? gram_cols(rt) : kTC;
+  return (A * B + tc - 1) / tc;
+}
+
+// Runs of tensor columns that one mode's Gram is summed over by a workgroup each: one per compute unit.
 int gram_num_chunks(int64_t A, int In, int64_t B) {
-  (void)In;
-  const int64_t J = A * B;
-  const int64_t tiles = (J + kTC - 1) / kTC;
+  const int64_t tiles = gram_tiles(A, In, B);
   return (int)(tiles < 256 ? (tiles < 1 ? 1 : tiles) : 256);
 }
+// One launch per kernel variant for all modes of a small tensor: its Grams are a few staged tiles per compute unit, so
+// what counts is launches, the first round trip to memory and the partial sums (64x64x32x17: four Grams and four
+// reductions of 256 partials 187 us, now 85 us).  From 16 tiles per compute unit and mode on, a mode fills the
+// chip by itself.
+bool gram_batched(int64_t I) { return I <= (int64_t)256 * 16 * 4096; }
 
-void launch_gram(hipStream_t s, const void* g, int dtype, const uint32_t* mask, int64_t A, int In,
-                 int64_t B, int nchunks, double* partials) {
-  const int64_t J = A * B;
-  const int64_t tiles = (J + kTC - 1) / kTC;
-  const int64_t tiles_per_chunk = (tiles + nchunks - 1) / nchunks;
-  const int64_t cols_per_chunk = tiles_per_chunk * kTC;
-  const int nsup = (In + kSuper - 1) / kSuper;
-  const size_t lds = (size_t)2 * kSuper * kRowD * sizeof(double);   // 132 KB: more than the default limit
-  // One super block (every FNO extent) and lane offsets that fit 32 bits: the kernel with the lean fetch.
-  // Its offsets reach two leading indices ahead: 2 In B elements of at most 8 bytes.
-  if (nsup == 1 && (int64_t)In * B < ((int64_t)1 << 28)) {
-    dim3 grid((unsigned)nchunks), block(kGram128Threads);
-    const bool smallb = B < kTC;
-    const uint32_t magic = B <= 1 ? 0u : (uint32_t)((0x100000000ull + (uint64_t)B - 1) / (uint64_t)B);
-#define TGRAD_GRAM128(DT_, SB_)                                                                         \
-  do {                                                                                                  \
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_gram128<DT_, SB_>),                       \
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                    \
-    k_gram128<DT_, SB_><<<grid, block, lds, s>>>(g, mask, A, In, B, cols_per_chunk, magic, partials);   \
-  } while (0)
-    if (dtype == TGRAD_C64) { if (smallb) TGRAD_GRAM128(TGRAD_C64, true); else TGRAD_GRAM128(TGRAD_C64, false); }
-    else { if (smallb) TGRAD_GRAM128(TGRAD_CBF16, true); else TGRAD_GRAM128(TGRAD_CBF16, false); }
-#undef TGRAD_GRAM128
-    return;
+// Chunks of every mode where modes of one kernel variant share a launch: one workgroup per compute unit and launch, and
+// partial sums that take no more memory together than those of the largest mode alone would, one by one.
+void gram_num_chunks_batched(int njobs, const int64_t* A, const int* In, const int64_t* B, int* nchunks) {
+  double cap = 0., sum = 0.;
+  for (int i = 0; i < njobs; ++i) {
+    int sharing = 0;
+    for (int j = 0; j < njobs; ++j) sharing += gram_rows(In[j], B[j]) == gram_rows(In[i], B[i]) ? 1 : 0;
+    const int n = gram_num_chunks(A[i], In[i], B[i]), most = 256 / sharing;
+    nchunks[i] = n < most ? n : most;
+    const double tiles = (double)((A[i] * B[i] + 15) / 16);
+    cap = fmax(cap, fmin(tiles, 256.) * In[i] * In[i]);
+    sum += (double)nchunks[i] * In[i] * In[i];
   }
-  dim3 grid((unsigned)nchunks, (unsigned)(nsup * nsup)), block(kGramThreads);
-  if (dtype == TGRAD_C64) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_gram<TGRAD_C64>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    k_gram<TGRAD_C64><<<grid, block, lds, s>>>(g, mask, A, In, B, cols_per_chunk, partials);
-  } else {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_gram<TGRAD_CBF16>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    k_gram<TGRAD_CBF16><<<grid, block, lds, s>>>(g, mask, A, In, B, cols_per_chunk, partials);
+  if (sum > cap)
+    for (int i = 0; i < njobs; ++i) {
+      const int n = (int)(nchunks[i] * (cap / sum));
+      nchunks[i] = n > 1 ? n : 1;
+    }
+}
+
+// Partial Grams of several modes of one tensor, nchunks[i] runs of columns each.
+void launch_gram_batch(hipStream_t s, int njobs, const void* g, int dtype, const uint32_t* mask, const int64_t* A,
+                       const int* In, const int64_t* B, const int* nchunks, double* const* partials) {
+  const int variants[5] = {0, 1, 2, 4, 8};
+  for (int rt : variants) {
+    GramJobs jobs;
+    int n = 0, chunks = 0;
+    for (int i = 0; i < njobs; ++i) {
+      if (gram_rows(In[i], B[i]) != rt) continue;
+      const int tc = rt ? gram_cols(rt) : kTC;
+      const int64_t per = (gram_tiles(A[i], In[i], B[i]) + nchunks[i] - 1) / nchunks[i] * tc;
+      GramJob& jb = jobs.job[n];
+      jb = GramJob{g, mask, partials[i], A[i], B[i], per, In[i], nchunks[i],
+                   B[i] <= 1 ? 0u : (uint32_t)((0x100000000ull + (uint64_t)B[i] - 1) / (uint64_t)B[i])};
+      if (rt == 0) {
+        const int nsup = (In[i] + kSuper - 1) / kSuper;
+        const size_t lds = (size_t)2 * kSuper * kRowD * sizeof(double);   // 132 KB: more than the default limit
+        const dim3 grid((unsigned)nchunks[i], (unsigned)(nsup * nsup)), block(kGramThreads);
+        if (dtype == TGRAD_C64) {
+          allow_lds(k_gram<TGRAD_C64>, lds);
+          k_gram<TGRAD_C64><<<grid, block, lds, s>>>(g, mask, A[i], In[i], B[i], per, partials[i]);
+        } else {
+          allow_lds(k_gram<TGRAD_CBF16>, lds);
+          k_gram<TGRAD_CBF16><<<grid, block, lds, s>>>(g, mask, A[i], In[i], B[i], per, partials[i]);
+        }
+        continue;
+      }
+      chunks = nchunks[i] > chunks ? nchunks[i] : chunks;
+      ++n;
+    }
+    if (n == 0) continue;
+    const dim3 grid((unsigned)chunks, (unsigned)n), block(kGram128Threads);
+    const size_t lds = (size_t)4 * gram_plane(rt) * sizeof(double);
+#define TGRAD_GRAM128(DT_, RT_)                                     \
+  do {                                                              \
+    allow_lds(k_gram128<DT_, RT_>, lds);                            \
+    k_gram128<DT_, RT_><<<grid, block, lds, s>>>(jobs);             \
+  } while (0)
+#define TGRAD_GRAM128_DT(RT_)                                       \
+  do {                                                              \
+    if (dtype == TGRAD_C64) TGRAD_GRAM128(TGRAD_C64, RT_);          \
+    else TGRAD_GRAM128(TGRAD_CBF16, RT_);                           \
+  } while (0)
+    if (rt == 8) TGRAD_GRAM128_DT(8); else if (rt == 4) TGRAD_GRAM128_DT(4);
+    else if (rt == 2) TGRAD_GRAM128_DT(2); else TGRAD_GRAM128_DT(1);
+#undef TGRAD_GRAM128_DT
+#undef TGRAD_GRAM128
   }
 }
 
-void launch_gram_reduce(hipStream_t s, const double* partials, int nchunks, int In, double* gram) {
-  const int64_t n2 = (int64_t)In * In;
-  k_gram_reduce<<<dim3((unsigned)((n2 + kReduceElems - 1) / kReduceElems)), dim3(256), 0, s>>>(partials, nchunks, In,
-                                                                                          gram);
+void launch_gram_reduce(hipStream_t s, int njobs, const int* In, const int* nchunks, double* const* partials,
+                        double* const* gram) {
+  ReduceJobs jobs;
+  int64_t most = 1;
+  for (int i = 0; i < njobs; ++i) {
+    jobs.partials[i] = partials[i];
+    jobs.gram[i] = gram[i];
+    jobs.In[i] = In[i];
+    jobs.nchunks[i] = nchunks[i];
+    const int64_t n2 = (int64_t)In[i] * In[i];
+    most = n2 > most ? n2 : most;
+  }
+  k_gram_reduce<<<dim3((unsigned)((most + kReduceElems - 1) / kReduceElems), (unsigned)njobs), dim3(256), 0, s>>>(jobs);
 }
 
 void launch_eig_batch(hipStream_t s, int njobs, const double* const* gram, double* const* work_a,

@@ -59,7 +59,11 @@ struct Plan {
   // byte offsets into workspace
   size_t ws_sel, ws_hist, ws_eig_status, ws_chunk_gt, ws_chunk_eq, ws_mask, ws_cand, ws_tile_start, ws_end_start, ws_fpad, ws_ut, ws_partials, ws_gram[kMaxNdim],
       ws_eig_a[kMaxNdim], ws_eig_v[kMaxNdim], ws_gs, ws_core_g, ws_core_n, ws_buf[2], workspace_bytes;
-  int gram_chunks[kMaxNdim];
+  int gram_jobs = 0;               // the compressed modes, in order
+  int gram_mode[kMaxNdim], gram_In[kMaxNdim], gram_chunks[kMaxNdim];
+  int64_t gram_A[kMaxNdim], gram_B[kMaxNdim];
+  size_t gram_partial[kMaxNdim];   // byte offset of the mode's partial sums in ws_partials
+  bool gram_batch = false;         // all modes in shared launches
   int order = 0;                   // TGRAD_ORDER_*
   int64_t zero_tiles = 0;
   size_t ws_tile_zero = 0;         // all-zero tile offsets: "no support" for the first-stage kernel
@@ -238,15 +242,26 @@ void make_plan(const tgrad_config* c, Plan* p) {
   const bool packed = p->fuse_next && !p->narrow;
   p->ws_fpad = take(packed ? (size_t)p->shape[N - 2] * 32 * 8 : 0);
   p->ws_ut = take(packed ? (size_t)p->shape[N - 2] * 32 * 8 : 0);
+  // Partial Grams: of all modes side by side where they share launches, else of one mode at a time.
   size_t partial_max = 0;
+  p->gram_jobs = 0;
   for (int n = 0; n < N; ++n) {
-    int64_t A = 1, B = 1;
-    for (int m = 0; m < n; ++m) A *= p->shape[m];
-    for (int m = n + 1; m < N; ++m) B *= p->shape[m];
-    const bool compressed = p->rank[n] < p->shape[n];
-    p->gram_chunks[n] = compressed ? gram_num_chunks(A, (int)p->shape[n], B) : 0;
-    size_t bytes = (size_t)p->gram_chunks[n] * p->shape[n] * p->shape[n] * 16;
-    if (bytes > partial_max) partial_max = bytes;
+    if (p->rank[n] == p->shape[n]) continue;
+    const int j = p->gram_jobs++;
+    p->gram_mode[j] = n;
+    p->gram_In[j] = (int)p->shape[n];
+    p->gram_A[j] = 1;
+    for (int m = 0; m < n; ++m) p->gram_A[j] *= p->shape[m];
+    p->gram_B[j] = 1;
+    for (int m = n + 1; m < N; ++m) p->gram_B[j] *= p->shape[m];
+    p->gram_chunks[j] = gram_num_chunks(p->gram_A[j], p->gram_In[j], p->gram_B[j]);
+  }
+  p->gram_batch = gram_batched(p->I);
+  if (p->gram_batch) gram_num_chunks_batched(p->gram_jobs, p->gram_A, p->gram_In, p->gram_B, p->gram_chunks);
+  for (int j = 0; j < p->gram_jobs; ++j) {
+    const size_t bytes = (size_t)p->gram_chunks[j] * p->gram_In[j] * p->gram_In[j] * 16;
+    p->gram_partial[j] = p->gram_batch ? partial_max : 0;
+    partial_max = p->gram_batch ? partial_max + bytes : bytes > partial_max ? bytes : partial_max;
   }
   p->hooi_sweeps = c->hooi_sweeps;
   size_t hooi_buf[2] = {0, 0};
@@ -480,40 +495,39 @@ void compute_factors(tgrad_ctx* c, const void* g, const uint32_t* tile_start, co
   // Warm restart: the sweeps below start from the factors in place instead of from HOSVD.
   bool warm = c->cfg.warm_restart == 1 && p.hooi_sweeps > 0;
   for (int n = 0; n < p.N; ++n) warm = warm && c->have_factor[n];
-  const double* grams[kMaxNdim];
-  double* wa[kMaxNdim];
-  double* wv[kMaxNdim];
-  int In[kMaxNdim], rr[kMaxNdim];
-  float* Us[kMaxNdim];
-  int* stat[kMaxNdim];
-  int njobs = 0;
   for (int n = 0; n < p.N; ++n) {
-    float* U = c->st<float>(p.st_U[n]);
     if (p.rank[n] == p.shape[n]) {
       Scope sc_(c, KID_FACTOR_PACK);
-      launch_identity_factor(s, U, (int)p.shape[n]);
-    } else if (!warm) {
-      int64_t A = 1, B = 1;
-      for (int m = 0; m < n; ++m) A *= p.shape[m];
-      for (int m = n + 1; m < p.N; ++m) B *= p.shape[m];
-      double* partials = c->w<double>(p.ws_partials);
-      double* gram = c->w<double>(p.ws_gram[n]);
-      { Scope sc_(c, KID_GRAM); launch_gram(s, g, dt, use_mask, A, (int)p.shape[n], B, p.gram_chunks[n], partials); }
-      { Scope sc_(c, KID_GRAM_REDUCE); launch_gram_reduce(s, partials, p.gram_chunks[n], (int)p.shape[n], gram); }
-      grams[njobs] = gram;
-      wa[njobs] = c->w<double>(p.ws_eig_a[n]);
-      wv[njobs] = c->w<double>(p.ws_eig_v[n]);
-      In[njobs] = (int)p.shape[n];
-      rr[njobs] = p.rank[n];
-      Us[njobs] = U;
-      stat[njobs] = c->w<int>(p.ws_eig_status) + 4 * n;
-      ++njobs;
+      launch_identity_factor(s, c->st<float>(p.st_U[n]), (int)p.shape[n]);
     }
     c->have_factor[n] = true;
   }
-  if (njobs > 0) {
+  if (!warm && p.gram_jobs > 0) {
+    const double* grams[kMaxNdim];
+    double* gram_out[kMaxNdim];
+    double* partials[kMaxNdim];
+    double* wa[kMaxNdim];
+    double* wv[kMaxNdim];
+    int rr[kMaxNdim];
+    float* Us[kMaxNdim];
+    int* stat[kMaxNdim];
+    for (int j = 0; j < p.gram_jobs; ++j) {
+      const int n = p.gram_mode[j];
+      grams[j] = gram_out[j] = c->w<double>(p.ws_gram[n]);
+      partials[j] = c->w<double>(p.ws_partials + p.gram_partial[j]);
+      wa[j] = c->w<double>(p.ws_eig_a[n]);
+      wv[j] = c->w<double>(p.ws_eig_v[n]);
+      rr[j] = p.rank[n];
+      Us[j] = c->st<float>(p.st_U[n]);
+      stat[j] = c->w<int>(p.ws_eig_status) + 4 * n;
+    }
+    const int group = p.gram_batch ? p.gram_jobs : 1;
+    for (int j = 0; j < p.gram_jobs; j += group) {
+      { Scope sc_(c, KID_GRAM); launch_gram_batch(s, group, g, dt, use_mask, p.gram_A + j, p.gram_In + j, p.gram_B + j, p.gram_chunks + j, partials + j); }
+      { Scope sc_(c, KID_GRAM_REDUCE); launch_gram_reduce(s, group, p.gram_In + j, p.gram_chunks + j, partials + j, gram_out + j); }
+    }
     Scope sc_(c, KID_EIG);
-    launch_eig_batch(s, njobs, grams, wa, wv, In, rr, Us, stat, c->cfg.eig_max_sweeps);
+    launch_eig_batch(s, p.gram_jobs, grams, wa, wv, p.gram_In, rr, Us, stat, c->cfg.eig_max_sweeps);
   }
 
   // --- HOOI sweeps: mode n re-solved on the tensor compressed in every other mode ---
@@ -536,12 +550,13 @@ void compute_factors(tgrad_ctx* c, const void* g, const uint32_t* tile_start, co
       }
       double* partials = c->w<double>(p.ws_partials);
       double* gram = c->w<double>(p.ws_gram[n]);
-      { Scope sc_(c, KID_GRAM); launch_gram(s, src, TGRAD_C64, nullptr, ch.gram_A, (int)p.shape[n], ch.gram_B, p.hooi_gram_chunks[n], partials); }
-      { Scope sc_(c, KID_GRAM_REDUCE); launch_gram_reduce(s, partials, p.hooi_gram_chunks[n], (int)p.shape[n], gram); }
+      const int i1[1] = {(int)p.shape[n]};
+      { Scope sc_(c, KID_GRAM); launch_gram_batch(s, 1, src, TGRAD_C64, nullptr, &ch.gram_A, i1, &ch.gram_B, &p.hooi_gram_chunks[n], &partials); }
+      { Scope sc_(c, KID_GRAM_REDUCE); launch_gram_reduce(s, 1, i1, &p.hooi_gram_chunks[n], &partials, &gram); }
       const double* g1[1] = {gram};
       double* a1[1] = {c->w<double>(p.ws_eig_a[n])};
       double* v1[1] = {c->w<double>(p.ws_eig_v[n])};
-      int i1[1] = {(int)p.shape[n]}, r1[1] = {p.rank[n]};
+      const int r1[1] = {p.rank[n]};
       float* u1[1] = {c->st<float>(p.st_U[n])};
       int* s1[1] = {c->w<int>(p.ws_eig_status) + 4 * n};
       Scope sc_(c, KID_EIG);
