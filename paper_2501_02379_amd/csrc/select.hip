@@ -39,7 +39,6 @@ constexpr int kSelThreads = 256;
 constexpr int kWavesPerBlock = kSelThreads / kWave;
 constexpr int kPairsPerIter = kWave;                       // one pair (2 elements) per lane
 constexpr int kSegIters = kSegElems / (2 * kPairsPerIter); // 16 iterations of 128 elements
-constexpr int kChunkWords = kSelChunkElems / 32;           // mask words one wavefront counts / emits in order
 
 __device__ __forceinline__ uint32_t digit_of(uint32_t key, int pass) {
   return pass == 0 ? (key >> 20) : pass == 1 ? ((key >> 8) & 0xFFFu) : (key & 0xFFu);
@@ -249,21 +248,21 @@ __device__ __forceinline__ void classify_candidates(const KeySource& g, int64_t 
   }
 }
 
-// Per chunk of kChunkWords mask words (one wavefront each): entries above T and entries equal to T.
+// Per chunk of `chunk_words` mask words (one wavefront each): entries above T and entries equal to T.
 template <int DT>
 __global__ __launch_bounds__(kSelThreads) void k_select_count(const KeySource g,
                                                               const SelectScalars* __restrict__ sc,
                                                               const uint32_t* __restrict__ sure,
                                                               const uint32_t* __restrict__ cand, int64_t nwords,
-                                                              uint32_t* __restrict__ chunk_gt,
+                                                              int chunk_words, uint32_t* __restrict__ chunk_gt,
                                                               uint32_t* __restrict__ chunk_eq, int64_t nchunks) {
   const int lane = lane_id();
   const int64_t chunk = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x / kWave);
   if (chunk >= nchunks) return;
   const uint32_t T = sc->threshold;
   uint32_t ngt = 0, neq = 0;
-  for (int it = 0; it < kChunkWords / kWave; ++it) {
-    const int64_t w = chunk * kChunkWords + (int64_t)it * kWave + lane;
+  for (int it = 0; it < chunk_words / kWave; ++it) {
+    const int64_t w = chunk * chunk_words + (int64_t)it * kWave + lane;
     if (w < nwords) {
       uint32_t above, equal;
       classify_candidates<DT>(g, w, cand[w], T, above, equal);
@@ -341,15 +340,15 @@ __global__ __launch_bounds__(kSelThreads) void k_select_emit(const KeySource g,
                                                              const uint32_t* __restrict__ chunk_eq,
                                                              int64_t nchunks, uint32_t* __restrict__ sure,
                                                              const uint32_t* __restrict__ cand, int64_t nwords,
-                                                             int32_t* __restrict__ omega) {
+                                                             int chunk_words, int32_t* __restrict__ omega) {
   const int lane = lane_id();
   const int64_t chunk = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x / kWave);
   if (chunk >= nchunks) return;
   const uint32_t T = sc->threshold;
   const uint32_t need = sc->need_eq;
   uint32_t run_gt = chunk_gt[chunk], run_eq = chunk_eq[chunk];
-  for (int it = 0; it < kChunkWords / kWave; ++it) {
-    const int64_t w = chunk * kChunkWords + (int64_t)it * kWave + lane;
+  for (int it = 0; it < chunk_words / kWave; ++it) {
+    const int64_t w = chunk * chunk_words + (int64_t)it * kWave + lane;
     uint32_t take = 0u, equal = 0u;                   // bits taken for certain; bits equal to T
     if (w < nwords) {
       uint32_t above;
@@ -477,10 +476,11 @@ void zero_u32(hipStream_t s, uint32_t* p, int64_t n) {
     else KERN<TGRAD_CBF16><<<dim3(GRID), dim3(BLOCK), 0, s>>>(__VA_ARGS__);                           \
   } while (0)
 
+// At least 8192 elements per workgroup: every one of them adds its few hundred occupied bins to the same ones in memory
+// (64x64x32x17: 4096 workgroups 79 us, 272 of them 11; 128x128x128x65: 205 with 1024 or with 4096).
 void launch_select_hist(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I,
                         uint32_t* hist) {
-  int64_t npairs = I >> 1;
-  int64_t want = (npairs + kSelThreads - 1) / kSelThreads;
+  const int64_t want = (I + 8191) / 8192;
   unsigned grid = (unsigned)(want < 1 ? 1 : want > 4096 ? 4096 : want);
   const KeySource src{g, keys.s0, keys.s1};
   TGRAD_SEL_DISPATCH(k_select_hist, grid, kSelThreads, src, I, hist);
@@ -507,13 +507,22 @@ void launch_select_hist_cand(hipStream_t s, const void* g, int dtype, const Sele
   TGRAD_SEL_DISPATCH(k_select_hist_cand, grid, kSelThreads, src, pass, sc, cand, nwords, hist);
 }
 
+// Mask words per chunk, the run one wavefront walks in order: as few as keep the counts to be scanned at a few
+// thousand (64x64x32x17 in runs of 1024 words, 17 workgroups: count and emit 19 us each, in runs of 64 words 5).
+int select_chunk_words(int64_t I) {
+  int words = kWave;
+  while (words < 1024 && I > (int64_t)words * 32 * 4224) words *= 2;
+  return words;
+}
+
 void launch_select_count(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I,
                          const SelectScalars* sc, const uint32_t* sure, const uint32_t* cand,
                          uint32_t* chunk_gt, uint32_t* chunk_eq, int64_t nchunks) {
   const int64_t nwords = (I + 31) / 32;
   unsigned grid = (unsigned)((nchunks + kWavesPerBlock - 1) / kWavesPerBlock);
   const KeySource src{g, keys.s0, keys.s1};
-  TGRAD_SEL_DISPATCH(k_select_count, grid, kSelThreads, src, sc, sure, cand, nwords, chunk_gt, chunk_eq, nchunks);
+  TGRAD_SEL_DISPATCH(k_select_count, grid, kSelThreads, src, sc, sure, cand, nwords, select_chunk_words(I),
+                     chunk_gt, chunk_eq, nchunks);
 }
 
 void launch_select_scan(hipStream_t s, uint32_t* chunk_gt, uint32_t* chunk_eq, int64_t nchunks) {
@@ -527,7 +536,7 @@ void launch_select_emit(hipStream_t s, const void* g, int dtype, const SelectKey
   unsigned grid = (unsigned)((nchunks + kWavesPerBlock - 1) / kWavesPerBlock);
   const KeySource src{g, keys.s0, keys.s1};
   TGRAD_SEL_DISPATCH(k_select_emit, grid, kSelThreads, src, sc, chunk_gt, chunk_eq, nchunks, sure, cand, nwords,
-                     omega);
+                     select_chunk_words(I), omega);
 }
 #undef TGRAD_SEL_DISPATCH
 

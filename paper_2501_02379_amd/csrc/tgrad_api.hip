@@ -42,7 +42,7 @@ struct Plan {
   int rank[kMaxNdim];
   Stage proj[kMaxNdim];          // proj[s]: s-th projection stage; contracts mode N-1-s
   Stage back[kMaxNdim];          // back[s]: s-th reconstruction stage; expands mode s
-  int64_t nchunks = 0;           // selection: runs of kSelChunkElems elements counted / emitted by one wavefront
+  int64_t nchunks = 0;           // selection: runs of elements counted / emitted by one wavefront
   int64_t mask_words = 0;
   int tile_waves = 0;            // last-mode kernels: wavefronts per workgroup; 0 = generic kernels
   int64_t ntiles = 0;            // tiles of the tensor seen as (I / I_N rows, I_N)
@@ -174,7 +174,8 @@ void make_plan(const tgrad_config* c, Plan* p) {
     st.K = p->rank[s];
     st.M = (int)p->shape[s];
   }
-  p->nchunks = (p->I + kSelChunkElems - 1) / kSelChunkElems;
+  const int64_t chunk = (int64_t)select_chunk_words(p->I) * 32;
+  p->nchunks = (p->I + chunk - 1) / chunk;
   p->mask_words = (p->I + 31) / 32;
   {
     const int last = N - 1;

@@ -13,9 +13,8 @@ constexpr int kMaxNdim = TGRAD_MAX_NDIM;
 
 // ---- selection (Algorithm 1: SparseIndices) -------------------------------------------------
 // A "segment" is the run of consecutive elements one wavefront turns into mask bits; a "chunk" is
-// the run one wavefront counts and emits in order from the masks.
+// the run one wavefront counts and emits in order from the masks (select_chunk_words).
 constexpr int kSegElems = 2048;
-constexpr int kSelChunkElems = 32768;
 constexpr int kHistBins = 4096;            // 12-bit digits; the three digits are 12 + 12 + 8 bits
 
 struct SelectScalars {                     // lives in workspace, written by the pick kernel
@@ -60,6 +59,7 @@ void launch_select_split(hipStream_t s, const void* g, int dtype, const SelectKe
                          const SelectScalars* sc, uint32_t* sure, uint32_t* cand);
 void launch_select_hist_cand(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I,
                              int pass, const SelectScalars* sc, const uint32_t* cand, uint32_t* hist);
+int select_chunk_words(int64_t I);
 void launch_select_count(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I,
                          const SelectScalars* sc, const uint32_t* sure, const uint32_t* cand,
                          uint32_t* chunk_gt, uint32_t* chunk_eq, int64_t nchunks);
