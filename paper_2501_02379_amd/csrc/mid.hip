@@ -304,8 +304,11 @@ __global__ __launch_bounds__(kThreads) void k_expand(const float* __restrict__ x
 // w, w + 8, ...  Every operand goes from memory straight into the registers of the one wavefront that
 // uses it, and all of them (x, both factor operands, moments) are requested up front: one memory
 // round trip, three barriers.
-// `z` may be `x` (in place): a workgroup writes only the columns it alone has read, and its reads
-// are complete (workgroup barriers in between) before its first write.
+// A workgroup stays for several groups of columns where there are more of them than the chip holds: the factor operands
+// are then fetched once per workgroup instead of once per 16 columns (ranks up to 64: 128 KB each, which the L2 caches
+// delivered in 105 us for 128 x 32768 columns at rank 64, now 68), and a group's columns and moments arrive under the group before it.
+// `z` may be `x` (in place): a workgroup writes only the columns it alone reads, a group's writes come after its reads
+// (workgroup barriers in between), and what is fetched ahead are other columns.
 struct CoreAdam {
   float2* m;            // first moments, (M, B) complex
   float* v;             // second moments
@@ -317,52 +320,58 @@ constexpr int kCoreSteps = 4;             // steps of x per wavefront in flight:
 
 template <int MT>
 __global__ __launch_bounds__(kCoreThreads) void k_core(const float* x, const float2* __restrict__ U, int rn, int K,
-                                                       int M, int64_t B, CoreAdam ad, float* z) {
+                                                       int M, int64_t B, int groups, CoreAdam ad, float* z) {
   extern __shared__ float2 sF[];
   constexpr int kPart = MT * 2 * 4 * 64;        // floats of one wavefront's partial tiles
-  float* red = reinterpret_cast<float*>(sF);    // [wave][tile][re / im][r][lane]
+  constexpr int kArea = kCoreWaves * kPart;     // [wave][tile][re / im][r][lane]; two of them take turns
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, grp = lane >> 4;
-  const int64_t b_raw = (int64_t)blockIdx.x * 16 + col;
-  const bool valid = b_raw < B;
-  const int64_t b = valid ? b_raw : B - 1;
   const int64_t row = B * 2;
-  const float* xp = x + b * 2;
   const int J = (K + 3) >> 2, Q = (K + 15) >> 4;
-  // operands of the compression
-  v4f acc[MT][2];
-#pragma unroll
-  for (int t = 0; t < MT; ++t) acc[t][0] = acc[t][1] = (v4f){0.f, 0.f, 0.f, 0.f};
+  const bool once = J <= kCoreWaves * kCoreSteps;              // (K <= 128) one batch of steps, one output tile each
+  // operands of the compression: steps wave + 8 (s0 + u); past the end: zero coefficients
   float2 xv[kCoreSteps], fc[kCoreSteps][MT];
-  auto fetch = [&](int s0) {                    // steps wave + 8 (s0 + u); past the end: zero coefficients
+  auto fetch_x = [&](int g, int s0) {
+    const int64_t b_raw = (int64_t)g * 16 + col;
+    const float* xp = x + (b_raw < B ? b_raw : B - 1) * 2;
 #pragma unroll
     for (int u = 0; u < kCoreSteps; ++u) {
       const int k = 4 * (wave + kCoreWaves * (s0 + u)) + grp;
       xv[u] = *reinterpret_cast<const float2*>(xp + (int64_t)(k < K ? k : K - 1) * row);
+    }
+  };
+  auto fetch_in = [&](int s0) {
+#pragma unroll
+    for (int u = 0; u < kCoreSteps; ++u) {
+      const int k = 4 * (wave + kCoreWaves * (s0 + u)) + grp;
 #pragma unroll
       for (int t = 0; t < MT; ++t) fc[u][t] = factor_at<true>(U, rn, 16 * t + col, k, M, K);
     }
   };
-  fetch(0);
   // moments of this thread's core entries
   constexpr int kEnt = (MT * 256 + kCoreThreads - 1) / kCoreThreads;
   float2 mm[kEnt];
   float vv[kEnt];
-  int64_t idx[kEnt];
-  bool live[kEnt];
-#pragma unroll
-  for (int q = 0; q < kEnt; ++q) {
+  auto entry = [&](int g, int q, int64_t& idx) -> bool {
     const int e = tid + q * kCoreThreads;
     const int l = e & 63, r = (e >> 6) & 3, t = e >> 8;
     const int m = 16 * t + 4 * (l >> 4) + r;
-    const int64_t bb = (int64_t)blockIdx.x * 16 + (l & 15);
-    live[q] = t < MT && m < M && bb < B;
-    idx[q] = live[q] ? (int64_t)m * B + bb : 0;
-    mm[q] = ad.m[idx[q]];
-    vv[q] = ad.v[idx[q]];
-  }
-  // operands of the first output tile of the expansion
+    const int64_t bb = (int64_t)g * 16 + (l & 15);
+    const bool live = t < MT && m < M && bb < B;
+    idx = live ? (int64_t)m * B + bb : 0;
+    return live;
+  };
+  auto fetch_moments = [&](int g) {
+#pragma unroll
+    for (int q = 0; q < kEnt; ++q) {
+      int64_t idx;
+      entry(g, q, idx);
+      mm[q] = ad.m[idx];
+      vv[q] = ad.v[idx];
+    }
+  };
+  // operands of an output tile of the expansion
   float2 fe[MT][4];
   auto fetch_out = [&](int q) {
 #pragma unroll
@@ -370,75 +379,94 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(const float* x, const flo
 #pragma unroll
       for (int r = 0; r < 4; ++r) fe[t][r] = factor_at<false>(U, rn, 16 * q + col, 16 * t + 4 * grp + r, K, M);
   };
+  int g = blockIdx.x;
+  fetch_x(g, 0);
+  fetch_in(0);
+  fetch_moments(g);
   fetch_out(wave);
-  __builtin_amdgcn_sched_barrier(0);
-  for (int s0 = 0;; s0 += kCoreSteps) {
+  float* red = reinterpret_cast<float*>(sF);
+  for (int it = 0; g < groups; g += gridDim.x, ++it, red = reinterpret_cast<float*>(sF) + (it & 1) * kArea) {
+    v4f acc[MT][2];
 #pragma unroll
-    for (int u = 0; u < kCoreSteps; ++u) {
-      const float xs[2] = {xv[u].x, xv[u].y};
+    for (int t = 0; t < MT; ++t) acc[t][0] = acc[t][1] = (v4f){0.f, 0.f, 0.f, 0.f};
+    __builtin_amdgcn_sched_barrier(0);
+    for (int s0 = 0;; s0 += kCoreSteps) {
 #pragma unroll
-      for (int t = 0; t < MT; ++t) cmac<1>(acc[t], fc[u][t], xs);
-    }
-    if (kCoreWaves * (s0 + kCoreSteps) >= J) break;            // (the same for every wavefront)
-    fetch(s0 + kCoreSteps);
-  }
+      for (int u = 0; u < kCoreSteps; ++u) {
+        const float xs[2] = {xv[u].x, xv[u].y};
 #pragma unroll
-  for (int t = 0; t < MT; ++t)
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) red[wave * kPart + ((t * 2 + i) * 4 + r) * 64 + lane] = acc[t][i][r];
-  __syncthreads();
-  // AdamUpdate; N_L replaces wavefront 0's partial sums (each entry is read and written by one thread)
-#pragma unroll
-  for (int q = 0; q < kEnt; ++q) {
-    const int e = tid + q * kCoreThreads;
-    const int l = e & 63, r = (e >> 6) & 3, t = e >> 8;
-    if (MT * 256 % kCoreThreads == 0 || t < MT) {
-      float* pr = red + (t * 8 + r) * 64 + l;
-      float* pi = pr + 256;
-      float gre = 0.f, gim = 0.f;
-#pragma unroll
-      for (int w = 0; w < kCoreWaves; ++w) {
-        gre += pr[w * kPart];
-        gim += pi[w * kPart];
+        for (int t = 0; t < MT; ++t) cmac<1>(acc[t], fc[u][t], xs);
       }
-      float2 m = mm[q];
-      m.x = ad.beta1 * m.x + (1.f - ad.beta1) * gre;
-      m.y = ad.beta1 * m.y + (1.f - ad.beta1) * gim;
-      const float v = ad.beta2 * vv[q] + (1.f - ad.beta2) * (gre * gre + gim * gim);
-      const float d = 1.f / (sqrtf(v * ad.inv_c2) + ad.eps);
-      float nr = 0.f, ni = 0.f;
-      if (live[q]) {
-        ad.m[idx[q]] = m;
-        ad.v[idx[q]] = v;
-        ad.g_out[idx[q]] = make_float2(gre, gim);
-        nr = m.x * ad.inv_c1 * d;
-        ni = m.y * ad.inv_c1 * d;
-      }
-      *pr = nr;
-      *pi = ni;
+      if (kCoreWaves * (s0 + kCoreSteps) >= J) break;          // (the same for every wavefront)
+      fetch_x(g, s0 + kCoreSteps);
+      fetch_in(s0 + kCoreSteps);
     }
-  }
-  __syncthreads();
-  // expansion
-  float* op = z + b * 2;
-  for (int q = wave; q < Q; q += kCoreWaves) {
-    if (q != wave) fetch_out(q);
-    v4f o[2];
-    o[0] = o[1] = (v4f){0.f, 0.f, 0.f, 0.f};
+    const int gn = g + gridDim.x;
+    if (gn < groups) {                                         // the next group's columns go in flight
+      fetch_x(gn, 0);
+      if (!once) fetch_in(0);
+    }
 #pragma unroll
     for (int t = 0; t < MT; ++t)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float n[2] = {red[(t * 8 + r) * 64 + lane], red[(t * 8 + 4 + r) * 64 + lane]};
-        cmac<1>(o, fe[t][r], n);
-      }
-    if (valid) {
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = 16 * q + 4 * grp + r;
-        if (i < K) store_cols<1>(op + (int64_t)i * row, o, r);
+        for (int r = 0; r < 4; ++r) red[wave * kPart + ((t * 2 + i) * 4 + r) * 64 + lane] = acc[t][i][r];
+    __syncthreads();
+    // AdamUpdate; N_L replaces wavefront 0's partial sums (each entry is read and written by one thread)
+#pragma unroll
+    for (int q = 0; q < kEnt; ++q) {
+      const int e = tid + q * kCoreThreads;
+      const int l = e & 63, r = (e >> 6) & 3, t = e >> 8;
+      if (MT * 256 % kCoreThreads == 0 || t < MT) {
+        float* pr = red + (t * 8 + r) * 64 + l;
+        float* pi = pr + 256;
+        float gre = 0.f, gim = 0.f;
+#pragma unroll
+        for (int w = 0; w < kCoreWaves; ++w) {
+          gre += pr[w * kPart];
+          gim += pi[w * kPart];
+        }
+        float2 m = mm[q];
+        m.x = ad.beta1 * m.x + (1.f - ad.beta1) * gre;
+        m.y = ad.beta1 * m.y + (1.f - ad.beta1) * gim;
+        const float v = ad.beta2 * vv[q] + (1.f - ad.beta2) * (gre * gre + gim * gim);
+        const float d = 1.f / (sqrtf(v * ad.inv_c2) + ad.eps);
+        float nr = 0.f, ni = 0.f;
+        int64_t idx;
+        if (entry(g, q, idx)) {
+          ad.m[idx] = m;
+          ad.v[idx] = v;
+          ad.g_out[idx] = make_float2(gre, gim);
+          nr = m.x * ad.inv_c1 * d;
+          ni = m.y * ad.inv_c1 * d;
+        }
+        *pr = nr;
+        *pi = ni;
+      }
+    }
+    if (gn < groups) fetch_moments(gn);
+    __syncthreads();
+    // expansion
+    const int64_t b = (int64_t)g * 16 + col;
+    float* op = z + b * 2;
+    for (int q = wave; q < Q; q += kCoreWaves) {
+      if (!once && (q != wave || it > 0)) fetch_out(q);
+      v4f o[2];
+      o[0] = o[1] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float n[2] = {red[(t * 8 + r) * 64 + lane], red[(t * 8 + 4 + r) * 64 + lane]};
+          cmac<1>(o, fe[t][r], n);
+        }
+      if (b < B) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = 16 * q + 4 * grp + r;
+          if (i < K) store_cols<1>(op + (int64_t)i * row, o, r);
+        }
       }
     }
   }
@@ -525,13 +553,15 @@ void launch_core(hipStream_t s, const float2* x, const float2* U, int rn, int K,
   CoreAdam ad{m, v, g_out, beta1, beta2, inv_c1, inv_c2, eps};
   const float* xf = reinterpret_cast<const float*>(x);
   float* zf = reinterpret_cast<float*>(z);
-  const dim3 grid((unsigned)((B + 15) / 16)), block(kCoreThreads);
+  const int64_t groups = (B + 15) / 16;
+  const dim3 block(kCoreThreads);
   const int mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
-  const size_t lds = (size_t)kCoreWaves * mt * 2048;
-#define TGRAD_CORE(MT_)                                                     \
-  do {                                                                      \
-    allow_lds(k_core<MT_>, lds);                                            \
-    k_core<MT_><<<grid, block, lds, s>>>(xf, U, rn, K, M, B, ad, zf);       \
+  const size_t lds = (size_t)2 * kCoreWaves * mt * 2048;
+#define TGRAD_CORE(MT_)                                                                                      \
+  do {                                                                                                       \
+    allow_lds(k_core<MT_>, lds);                                                                             \
+    const int64_t cap = (int64_t)compute_units() * resident_blocks(k_core<MT_>, kCoreThreads, lds);          \
+    k_core<MT_><<<dim3((unsigned)(groups < cap ? groups : cap)), block, lds, s>>>(xf, U, rn, K, M, B, (int)groups, ad, zf); \
   } while (0)
   if (mt == 1) TGRAD_CORE(1); else if (mt == 2) TGRAD_CORE(2); else TGRAD_CORE(4);
 #undef TGRAD_CORE
