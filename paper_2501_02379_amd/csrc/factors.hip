@@ -1198,7 +1198,7 @@ __global__ __launch_bounds__(kEigThreads) void k_eig_finish(EigJobs jobs) {
 //   k_trid_vec  (one wavefront per eigenvector)
 //               the k-th largest eigenvalue of T by multisection on Sturm counts (64 points per step: 10 steps from the
 //               Gershgorin interval down to rounding), its eigenvector by inverse iteration (Gaussian elimination
-//               with partial pivoting on T - lambda I, three solves from a fixed pseudo-random start vector), the
+//               with partial pivoting on T - lambda I from both ends, three solves from a fixed pseudo-random vector), the
 //               back-transformation with the reflectors, the phase convention and the float32 factor.
 // A cyclic Jacobi sweep reads and writes the whole matrix in every one of its n - 1 rounds, about ten sweeps long;
 // the tridiagonalisation touches the trailing block once per step.
@@ -1210,8 +1210,8 @@ __global__ __launch_bounds__(kEigThreads) void k_eig_finish(EigJobs jobs) {
 // threads, elements (ty + 32 a, tx + 32 b), both triangles) and passes two barriers per step: every wavefront
 // derives the reflector from the column in LDS by itself, and the sums run over lanes without LDS.  In LDS, with
 // eight barriers per step and one wavefront deriving the reflector, a step took 6 us at n = 128.
-// Measured, four modes at once, us, tridiagonalisation + vectors: 128,128,128,65 (r 32,32,32,16) 935 + 66 -> 337 + 138;
-// 64,64,32,17 (r 16,16,8,4) 338 + 34 -> 110 + 73.
+// Measured, four modes at once, us, tridiagonalisation + vectors: 128,128,128,65 (r 32,32,32,16) 935 + 66 -> 337 + 106;
+// 64,64,32,17 (r 16,16,8,4) 338 + 34 -> 110 + 57.
 constexpr int kMultiSteps = 10;        // 65^10 > 2^60
 constexpr double kClusterTol = 1e-7;
 
@@ -1570,37 +1570,52 @@ __global__ __launch_bounds__(64) void k_trid_vec(EigJobs jobs) {
     return;
   }
 
-  // ---- inverse iteration: serial, every lane computes the same; lane 0 writes the arrays ----
+  // ---- inverse iteration: a serial chain, so it burns at both ends: lanes 0 .. 31 eliminate from the first row down,
+  // lanes 32 .. 63 from the last row up (the same code on the reversed matrix), a 2 x 2 system is left in the middle, and
+  // the substitution runs outwards on both sides.  Within a side every lane computes the same; one writes. ----
   const double tol = 2.220446049250313e-16 * tnorm;
-  uint64_t pv_lo = 0ull, pv_hi = 0ull;           // bit i: rows interchanged at step i
+  const int side = lane >> 5;
+  const bool writer = (lane & 31) == 0;
+  const int mt = (n - 1) >> 1, mh = side ? n - 2 - mt : mt;              // rows eliminated from the top, from this side
+  auto row_at = [&](int j) -> int { return side ? n - 1 - j : j; };
+  auto d_at = [&](int j) -> double { return sd[row_at(j)] - lam; };
+  auto e_at = [&](int j) -> double { return se[side ? n - 2 - j : j]; };  // couples rows j and j + 1 of this side
+  auto clamped = [&](double p) -> double { return fabs(p) < tol ? (p < 0. ? -tol : tol) : p; };
+  uint64_t swaps = 0ull;                         // bit j: rows interchanged at step j (mt <= 63)
+  double ca, cu;                                 // the side's last row: ca x[mh] + cu x[mh + 1]
   {
-    double a = sd[0] - lam, du = se[0];
-    double sub = se[0], dn = sd[1] - lam, en = se[1];
-    for (int i = 0; i + 1 < n; ++i) {            // elimination with partial pivoting; the next row is read one ahead
-      const double nsub = se[i + 1], ndn = sd[i + 2] - lam, nen = se[i + 2];
+    double a = d_at(0), du = e_at(0);
+    double sub = du, dn = n > 2 ? d_at(1) : 0., en = n > 2 ? e_at(1) : 0.;   // the next row is read one ahead
+    for (int j = 0; j < mt; ++j) {               // elimination with partial pivoting
+      const int jn = j + 2 < n - 1 ? j + 2 : n - 2;
+      const double ndn = d_at(jn), nen = e_at(jn);
       const bool swap = fabs(a) < fabs(sub);
-      double piv = swap ? sub : a;
-      if (fabs(piv) < tol) piv = piv < 0. ? -tol : tol;
-      const double rp = rcp_nr(piv);
+      const double rp = rcp_nr(clamped(swap ? sub : a));
       const double f = (swap ? a : sub) * rp;
-      if (lane == 0) {
-        slu[i][0] = make_double2(rp, swap ? dn : du);
-        slu[i][1] = make_double2(swap ? en : 0., f);
+      if (writer && j < mh) {
+        slu[row_at(j)][0] = make_double2(rp, swap ? dn : du);
+        slu[row_at(j)][1] = make_double2(swap ? en : 0., f);
       }
-      if (i < 64) pv_lo |= (uint64_t)swap << i; else pv_hi |= (uint64_t)swap << (i - 64);
-      const double na = swap ? du - f * dn : dn - f * du;
-      du = swap ? -f * en : en;
-      a = na;
-      sub = nsub;
+      if (j < mh) {
+        swaps |= (uint64_t)swap << j;
+        a = swap ? du - f * dn : dn - f * du;
+        du = swap ? -f * en : en;
+      }
+      sub = en;
       dn = ndn;
       en = nen;
     }
-    if (fabs(a) < tol) a = a < 0. ? -tol : tol;
-    if (lane == 0) {
-      slu[n - 1][0] = make_double2(rcp_nr(a), 0.);
-      slu[n - 1][1] = make_double2(0., 0.);
-    }
+    ca = a;
+    cu = du;
   }
+  // the middle: (top row) a1 xp + u1 xq = y1, (bottom row) u2 xp + a2 xq = y2, with pivoting
+  const double oa = __shfl_xor(ca, 32, 64), ou = __shfl_xor(cu, 32, 64);
+  const double a1 = side ? oa : ca, u1 = side ? ou : cu, a2 = side ? ca : oa, u2 = side ? cu : ou;
+  const bool mswap = fabs(a1) < fabs(u2);
+  const double mp = mswap ? u2 : a1, mu = mswap ? a2 : u1;               // the pivot row
+  const double mrp = rcp_nr(clamped(mp));
+  const double mf = (mswap ? a1 : u2) * mrp;
+  const double mrq = rcp_nr(clamped((mswap ? u1 : a2) - mf * mu));
   const int r0 = lane, r1 = lane + 64;
   // the first reflectors of the back-transformation go in flight
   const double2* Vg = reinterpret_cast<const double2*>(jb.V);
@@ -1619,37 +1634,50 @@ __global__ __launch_bounds__(64) void k_trid_vec(EigJobs jobs) {
     const uint32_t u = trid_mix((uint32_t)i * 0x9E3779B9u + (uint32_t)k * 0x85EBCA6Bu + 0x1234567u);
     return (double)u * (1. / 2147483648.) - 1.;
   };
-  double z0 = r0 < n ? start(r0) : 0., z1 = r1 < n ? start(r1) : 0.;
+  double z0 = 0., z1 = 0.;
   for (int it = 0; it < 3; ++it) {
     __syncthreads();                             // (one wavefront: orders the LDS accesses)
-    sz[r0] = z0;
-    sz[r1] = z1;
-    __syncthreads();
-    double y = sz[0], f = slu[0][1].y, rhs = sz[1];
-    for (int i = 0; i + 1 < n; ++i) {            // forward substitution
-      const double nf = slu[i + 1][1].y, nrhs = sz[i + 2];
-      const bool swap = i < 64 ? (pv_lo >> i) & 1ull : (pv_hi >> (i - 64)) & 1ull;
-      const double keep = swap ? rhs : y;
-      y = swap ? y - f * rhs : rhs - f * y;
-      if (lane == 0) sy[i] = keep;
-      f = nf;
-      rhs = nrhs;
+    double y;
+    if (it == 0) {                               // the first right-hand side is taken as already eliminated
+      if (r0 < n) sy[r0] = start(r0);
+      if (r1 < n) sy[r1] = start(r1);
+      y = start(row_at(mh));
+    } else {
+      if (r0 < n) sz[r0] = z0;
+      if (r1 < n) sz[r1] = z1;
+      __syncthreads();
+      y = sz[row_at(0)];
+      double f = slu[row_at(0)][1].y, rhs = sz[row_at(1)];
+      for (int j = 0; j < mt; ++j) {             // elimination of the right-hand side
+        const int jn = j + 2 < n ? j + 2 : n - 1;
+        const double nf = slu[row_at(j + 1)][1].y, nrhs = sz[row_at(jn)];
+        const bool swap = (swaps >> j) & 1ull;
+        if (writer && j < mh) sy[row_at(j)] = swap ? rhs : y;
+        if (j < mh) y = swap ? y - f * rhs : rhs - f * y;
+        f = nf;
+        rhs = nrhs;
+      }
     }
-    if (lane == 0) sy[n - 1] = y;
     __syncthreads();
-    double zn1 = 0., zn2 = 0.;
-    double2 p = slu[n - 1][0];
-    double u2 = slu[n - 1][1].x, yi = sy[n - 1];
-    for (int i = n - 1; i >= 0; --i) {           // back substitution
-      const int j = i > 0 ? i - 1 : 0;
-      const double2 np = slu[j][0];
-      const double nu2 = slu[j][1].x, nyi = sy[j];
-      const double z = (yi - u2 * zn2 - p.y * zn1) * p.x;
-      if (lane == 0) sz[i] = z;
+    const double oy = __shfl_xor(y, 32, 64);
+    const double y1 = side ? oy : y, y2 = side ? y : oy;
+    const double yp = mswap ? y2 : y1, yq = mswap ? y1 : y2;
+    const double xq = (yq - mf * yp) * mrq, xp = (yp - mu * xq) * mrp;
+    double zn1 = side ? xq : xp, zn2 = side ? xp : xq;
+    if (writer) sz[row_at(mh)] = zn1;
+    int j = mh - 1;
+    double2 p = slu[row_at(j > 0 ? j : 0)][0];
+    double s2 = slu[row_at(j > 0 ? j : 0)][1].x, yi = sy[row_at(j > 0 ? j : 0)];
+    for (int step = 0; step < mt; ++step, --j) { // back substitution, outwards
+      const int jn = j > 1 ? j - 1 : 0;
+      const double2 np = slu[row_at(jn)][0];
+      const double ns2 = slu[row_at(jn)][1].x, nyi = sy[row_at(jn)];
+      const double z = (yi - s2 * zn2 - p.y * zn1) * p.x;
+      if (writer && j >= 0) sz[row_at(j)] = z;
       zn2 = zn1;
       zn1 = z;
       p = np;
-      u2 = nu2;
+      s2 = ns2;
       yi = nyi;
     }
     __syncthreads();
