@@ -675,11 +675,13 @@ unsigned end_grid(Kern kern, int W, size_t lds, int64_t units) {
 int end_tile_rows(int K) { return K <= 33 ? 32 : 16; }
 
 // Which shapes take the two kernels: K = extent of the last mode, r its rank, I2 / r2 extent and rank of mode N-1.
+// Slabs of fewer than four rows would leave seven eighths of every tile empty (and need a support offset for every few
+// entries): they stay with the kernels that cut the tensor into tiles of 32 rows wherever a slab ends.
 // (With both ranks in the upper half of a 32-wide tile, whole 32-row tiles and at least 512 slabs the 32 x 32 kernels are
 // the better ones - make_plan prefers them: whole step 128x128x128x65, r 32,32,32,16: 747 us against 787 with these;
 // 128x128x64x33, r 64,64,32,16: 413 against 431.)
 bool ends_kernel_fits(int K, int r, int I2, int r2) {
-  if (K < 2 || K > 68 || r > 16 || r2 > 32 || I2 > TGRAD_MAX_EXTENT) return false;
+  if (K < 2 || K > 68 || r > 16 || r2 > 32 || I2 < 4 || I2 > TGRAD_MAX_EXTENT) return false;
   return head_lds(kMaxWaves, K, I2, r2) <= kLdsLimit / 2 && tail_lds(kMaxWaves, K, I2, r2) <= kLdsLimit / 2;
 }
 

@@ -290,6 +290,7 @@ __constant__ GramRuns kGramRuns[8] = {
 constexpr int kGram128Threads = 512;
 
 struct GramJob {
+  int rt;                            // tile rows held: the variant of the kernel
   const void* x;
   const uint32_t* mask;
   double* partials;
@@ -313,10 +314,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gram_buffer(const void* base, 
 __device__ constexpr int tri_row(int t) { int a = 0; while ((a + 1) * (a + 2) / 2 <= t) ++a; return a; }
 
 template <int DT, int RT>
-__global__ __launch_bounds__(kGram128Threads) void k_gram128(GramJobs jobs) {
-  extern __shared__ double sG[];
-  const GramJob jb = jobs.job[blockIdx.y];
-  if ((int)blockIdx.x >= jb.nchunks) return;
+__device__ __forceinline__ void gram_chunk(const GramJob& jb, double* sG) {
   constexpr int TC = gram_cols(RT), Q = 16 * RT + 1, PL = gram_plane(RT);
   constexpr int kEs = DT == TGRAD_C64 ? 8 : 4;        // bytes per element
   constexpr uint32_t kNowhere = 0xFFFFFFF0u;          // an offset beyond every descriptor: the load returns zero
@@ -644,6 +642,17 @@ __global__ __launch_bounds__(kGram128Threads) void k_gram128(GramJobs jobs) {
       if (lane == 0) out[(int64_t)(16 * RT) * In + 16 * RT] = make_double2(dd, 0.);
     }
   }
+}
+
+template <int DT>
+__global__ __launch_bounds__(kGram128Threads) void k_gram128(GramJobs jobs) {
+  extern __shared__ double sG[];
+  const GramJob jb = jobs.job[blockIdx.y];
+  if ((int)blockIdx.x >= jb.nchunks) return;
+  if (jb.rt == 8) gram_chunk<DT, 8>(jb, sG);
+  else if (jb.rt == 4) gram_chunk<DT, 4>(jb, sG);
+  else if (jb.rt == 2) gram_chunk<DT, 2>(jb, sG);
+  else gram_chunk<DT, 1>(jb, sG);
 }
 
 // gram[i, j] = sum over chunks of partials[chunk][i, j] for i >= j; the upper triangle is the
@@ -1770,21 +1779,27 @@ int gram_num_chunks(int64_t A, int In, int64_t B) {
   const int64_t tiles = gram_tiles(A, In, B);
   return (int)(tiles < 256 ? (tiles < 1 ? 1 : tiles) : 256);
 }
-// One launch per kernel variant for all modes of a small tensor: its Grams are a few staged tiles per compute unit, so
-// what counts is launches, the first round trip to memory and the partial sums (64x64x32x17: four Grams and four
-// reductions of 256 partials 187 us, now 85 us).  From 16 tiles per compute unit and mode on, a mode fills the
-// chip by itself.
+// One launch for all modes of a small tensor: its Grams are a few staged tiles per compute unit, so what counts is
+// launches, the first round trip to memory and the partial sums (64x64x32x17: four Grams and four reductions of 256
+// partials 187 us, one launch per kernel variant 85, one for all 82).  From 16 tiles per compute unit and mode on,
+// a mode fills the chip by itself.
 bool gram_batched(int64_t I) { return I <= (int64_t)256 * 16 * 4096; }
 
-// Chunks of every mode where modes of one kernel variant share a launch: one workgroup per compute unit and launch, and
-// partial sums that take no more memory together than those of the largest mode alone would, one by one.
+// Chunks of every mode where they share a launch: by their share of the work two workgroups per compute unit (of unequal
+// length, so that the last ones level it out), and partial sums that take no more memory together than those of the
+// largest mode alone would, one by one.
 void gram_num_chunks_batched(int njobs, const int64_t* A, const int* In, const int64_t* B, int* nchunks) {
-  double cap = 0., sum = 0.;
+  double cap = 0., sum = 0., work = 0.;
+  auto cost = [&](int i) -> double {               // staged tiles times their matrix instructions and their fetch
+    const int rt = gram_rows(In[i], B[i]);
+    return (double)gram_tiles(A[i], In[i], B[i]) * (rt == 8 ? 3. : rt == 4 ? 1.7 : 1.);
+  };
+  for (int i = 0; i < njobs; ++i) work += cost(i);
   for (int i = 0; i < njobs; ++i) {
-    int sharing = 0;
-    for (int j = 0; j < njobs; ++j) sharing += gram_rows(In[j], B[j]) == gram_rows(In[i], B[i]) ? 1 : 0;
-    const int n = gram_num_chunks(A[i], In[i], B[i]), most = 256 / sharing;
-    nchunks[i] = n < most ? n : most;
+    const int n = gram_num_chunks(A[i], In[i], B[i]);
+    int share = (int)(512. * cost(i) / work + 0.5);
+    if (share < 1) share = 1;
+    nchunks[i] = n < share ? n : share;
     const double tiles = (double)((A[i] * B[i] + 15) / 16);
     cap = fmax(cap, fmin(tiles, 256.) * In[i] * In[i]);
     sum += (double)nchunks[i] * In[i] * In[i];
@@ -1799,50 +1814,39 @@ void gram_num_chunks_batched(int njobs, const int64_t* A, const int* In, const i
 // Partial Grams of several modes of one tensor, nchunks[i] runs of columns each.
 void launch_gram_batch(hipStream_t s, int njobs, const void* g, int dtype, const uint32_t* mask, const int64_t* A,
                        const int* In, const int64_t* B, const int* nchunks, double* const* partials) {
-  const int variants[5] = {0, 1, 2, 4, 8};
-  for (int rt : variants) {
-    GramJobs jobs;
-    int n = 0, chunks = 0;
-    for (int i = 0; i < njobs; ++i) {
-      if (gram_rows(In[i], B[i]) != rt) continue;
-      const int tc = rt ? gram_cols(rt) : kTC;
-      const int64_t per = (gram_tiles(A[i], In[i], B[i]) + nchunks[i] - 1) / nchunks[i] * tc;
-      GramJob& jb = jobs.job[n];
-      jb = GramJob{g, mask, partials[i], A[i], B[i], per, In[i], nchunks[i],
-                   B[i] <= 1 ? 0u : (uint32_t)((0x100000000ull + (uint64_t)B[i] - 1) / (uint64_t)B[i])};
-      if (rt == 0) {
-        const int nsup = (In[i] + kSuper - 1) / kSuper;
-        const size_t lds = (size_t)2 * kSuper * kRowD * sizeof(double);   // 132 KB: more than the default limit
-        const dim3 grid((unsigned)nchunks[i], (unsigned)(nsup * nsup)), block(kGramThreads);
-        if (dtype == TGRAD_C64) {
-          allow_lds(k_gram<TGRAD_C64>, lds);
-          k_gram<TGRAD_C64><<<grid, block, lds, s>>>(g, mask, A[i], In[i], B[i], per, partials[i]);
-        } else {
-          allow_lds(k_gram<TGRAD_CBF16>, lds);
-          k_gram<TGRAD_CBF16><<<grid, block, lds, s>>>(g, mask, A[i], In[i], B[i], per, partials[i]);
-        }
-        continue;
+  GramJobs jobs;
+  int n = 0, chunks = 0;
+  size_t lds128 = 0;
+  for (int i = 0; i < njobs; ++i) {
+    const int rt = gram_rows(In[i], B[i]), tc = rt ? gram_cols(rt) : kTC;
+    const int64_t per = (gram_tiles(A[i], In[i], B[i]) + nchunks[i] - 1) / nchunks[i] * tc;
+    if (rt == 0) {
+      const int nsup = (In[i] + kSuper - 1) / kSuper;
+      const size_t lds = (size_t)2 * kSuper * kRowD * sizeof(double);   // 132 KB: more than the default limit
+      const dim3 grid((unsigned)nchunks[i], (unsigned)(nsup * nsup)), block(kGramThreads);
+      if (dtype == TGRAD_C64) {
+        allow_lds(k_gram<TGRAD_C64>, lds);
+        k_gram<TGRAD_C64><<<grid, block, lds, s>>>(g, mask, A[i], In[i], B[i], per, partials[i]);
+      } else {
+        allow_lds(k_gram<TGRAD_CBF16>, lds);
+        k_gram<TGRAD_CBF16><<<grid, block, lds, s>>>(g, mask, A[i], In[i], B[i], per, partials[i]);
       }
-      chunks = nchunks[i] > chunks ? nchunks[i] : chunks;
-      ++n;
+      continue;
     }
-    if (n == 0) continue;
-    const dim3 grid((unsigned)chunks, (unsigned)n), block(kGram128Threads);
+    jobs.job[n++] = GramJob{rt, g, mask, partials[i], A[i], B[i], per, In[i], nchunks[i],
+                            B[i] <= 1 ? 0u : (uint32_t)((0x100000000ull + (uint64_t)B[i] - 1) / (uint64_t)B[i])};
+    chunks = nchunks[i] > chunks ? nchunks[i] : chunks;
     const size_t lds = (size_t)4 * gram_plane(rt) * sizeof(double);
-#define TGRAD_GRAM128(DT_, RT_)                                     \
-  do {                                                              \
-    allow_lds(k_gram128<DT_, RT_>, lds);                            \
-    k_gram128<DT_, RT_><<<grid, block, lds, s>>>(jobs);             \
-  } while (0)
-#define TGRAD_GRAM128_DT(RT_)                                       \
-  do {                                                              \
-    if (dtype == TGRAD_C64) TGRAD_GRAM128(TGRAD_C64, RT_);          \
-    else TGRAD_GRAM128(TGRAD_CBF16, RT_);                           \
-  } while (0)
-    if (rt == 8) TGRAD_GRAM128_DT(8); else if (rt == 4) TGRAD_GRAM128_DT(4);
-    else if (rt == 2) TGRAD_GRAM128_DT(2); else TGRAD_GRAM128_DT(1);
-#undef TGRAD_GRAM128_DT
-#undef TGRAD_GRAM128
+    lds128 = lds > lds128 ? lds : lds128;
+  }
+  if (n == 0) return;
+  const dim3 grid((unsigned)chunks, (unsigned)n), block(kGram128Threads);
+  if (dtype == TGRAD_C64) {
+    allow_lds(k_gram128<TGRAD_C64>, lds128);
+    k_gram128<TGRAD_C64><<<grid, block, lds128, s>>>(jobs);
+  } else {
+    allow_lds(k_gram128<TGRAD_CBF16>, lds128);
+    k_gram128<TGRAD_CBF16><<<grid, block, lds128, s>>>(jobs);
   }
 }
 

@@ -233,11 +233,8 @@ void make_plan(const tgrad_config* c, Plan* p) {
   p->ws_hist = take(3 * kHistBins * 4);
   p->ws_eig_status = take(4 * kMaxNdim * sizeof(int));   // per mode: 1 if the last solve stopped at the sweep limit,
                                                          // Jacobi sweeps run, 1 if the tridiagonal path declined, spare
-  p->ws_chunk_gt = take((size_t)p->nchunks * 4);
-  p->ws_chunk_eq = take((size_t)p->nchunks * 4);
   p->ws_mask = take((size_t)p->mask_words * 4);
-  p->ws_cand = take((size_t)p->mask_words * 4);
-  p->ws_tile_start = take((size_t)(p->ntiles + 1) * 4);
+  p->ws_tile_start = take(p->flat_offsets ? (size_t)(p->ntiles + 1) * 4 : 0);
   const int64_t end_tiles = p->narrow ? p->I / (p->shape[N - 1] * p->shape[N - 2]) * p->end_tiles : 0;
   p->ws_end_start = p->own_offsets ? take((size_t)(end_tiles + 1) * 4) : p->ws_tile_start;
   const bool packed = p->fuse_next && !p->narrow;
@@ -279,7 +276,12 @@ void make_plan(const tgrad_config* c, Plan* p) {
     const size_t bytes = (size_t)p->hooi_gram_chunks[n] * p->shape[n] * p->shape[n] * 16;
     if (bytes > partial_max) partial_max = bytes;
   }
-  p->ws_partials = take(partial_max);
+  // The selection's counts and candidate mask lie where the partial Grams do: none of them outlives its own pass.
+  const size_t counts = align_up((size_t)p->nchunks * 4), select_bytes = 2 * counts + (size_t)p->mask_words * 4;
+  p->ws_partials = take(partial_max > select_bytes ? partial_max : select_bytes);
+  p->ws_chunk_gt = p->ws_partials;
+  p->ws_chunk_eq = p->ws_partials + counts;
+  p->ws_cand = p->ws_partials + 2 * counts;
   for (int n = 0; n < N; ++n) {
     const size_t mat = p->rank[n] < p->shape[n] ? (size_t)p->shape[n] * p->shape[n] * 16 : 0;
     p->ws_gram[n] = take(mat);
