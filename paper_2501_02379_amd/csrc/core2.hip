@@ -139,16 +139,9 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
         if (e0 + u * kThreads < n) dst[e0 + u * kThreads] = f[u];
     }
   };
-  auto u1_at = [&](int i1, int m1) -> float2 {                // zero outside the factor
-    const bool in = i1 < I1 && m1 < M1;
-    const float2 u = a.U1[in ? i1 * M1 + m1 : 0];
-    return in ? u : make_float2(0.f, 0.f);
-  };
-  auto u0_at = [&](int i0, int m0) -> float2 {
-    const bool in = i0 < I0 && m0 < M0;
-    const float2 u = a.U0[in ? i0 * M0 + m0 : 0];
-    return in ? u : make_float2(0.f, 0.f);
-  };
+  const FactorRef fU0 = factor_ref(a.U0, (int64_t)I0 * M0), fU1 = factor_ref(a.U1, (int64_t)I1 * M1);
+  auto u1_at = [&](int i1, int m1) -> float2 { return factor_entry(fU1, i1, m1, M1, i1 < I1 && m1 < M1); };
+  auto u0_at = [&](int i0, int m0) -> float2 { return factor_entry(fU0, i0, m0, M0, i0 < I0 && m0 < M0); };
   stage_table(sT1, nA, [&](int e) -> float2 {                 // U1[4 j + g][16 t1 + c]
     const int l = e & 63, t1 = (e >> 6) % NT1, j = (e >> 6) / NT1;
     return u1_at(4 * j + (l >> 4), 16 * t1 + (l & 15));
@@ -158,7 +151,7 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
     return u1_at(16 * q + (l & 15), 16 * t1 + 4 * (l >> 4) + r);
   });
   // the U0 operands of stage 2 (f2) and of stage 3 (f3) of the first row tile are requested here as well: asked for
-  // where they are used, each is a memory round trip in front of its stage (16x16x8x5: 10.2 us, now 8.4)
+  // where they are used, each is a memory round trip in front of its stage (16x16x8x5: 10.2 us, now 8.2)
   float2 f2[NT0][4], f3[NT0][4];
   auto fetch_f2 = [&](int t) {                                // U0[16 t + 4 g + r][16 t0 + c]
 #pragma unroll

@@ -46,6 +46,23 @@ __device__ __forceinline__ uint32_t select_key(float2 e) {
   return __float_as_uint(__fadd_rn(__fmul_rn(e.x, e.x), __fmul_rn(e.y, e.y)));
 }
 
+// Entries of a factor (row-major complex), zero where `in` is false: through a range-checked buffer, so that nothing
+// about the load is conditional.  (Written as a select, U[in ? i : 0] becomes a branch around the load and a wait right
+// behind it: a table of 32 entries per thread was 32 memory round trips.  k_mid with 128 x 64 factors 58 us, now 52; whole
+// steps 16x16x8x5 17.0 -> 15.7, 90x77x45x23 70.8 -> 66.4, 128x128x64x33 201 -> 192, in bf16 142 -> 132.)
+// The buffer starts at U and covers `entries` of it, at most 2 GB.
+typedef __amdgpu_buffer_rsrc_t FactorRef;
+__device__ __forceinline__ FactorRef factor_ref(const float2* U, int64_t entries) {
+  const int64_t bytes = entries * 8 < 0x7FFFFFF8 ? entries * 8 : 0x7FFFFFF8;
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float2*>(U), (short)0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ float2 factor_entry(const FactorRef& f, int row, int col, int cols, bool in) {
+  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+  const uint32_t off = in ? ((uint32_t)row * (uint32_t)cols + (uint32_t)col) * 8u : 0xFFFFFFF0u;
+  const u2 v = __builtin_amdgcn_raw_buffer_load_b64(f, off, 0, 0);
+  return make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
+}
+
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
 // Number of set bits of `b` strictly below this lane.

@@ -11,11 +11,11 @@
 // memory.  The steps of the first contraction are counted in fours of K, not up to the next of two sizes.
 //
 // Measured (rocprofv3, us; before: 32 x 32 tiles, or separate kernels per mode where slabs were ragged or few):
-//   first pass 64x64x32x17 15.7 -> 10.8, 32x32x32x32x17 (bf16) 84.5 -> 35.3, 128x128x64x33 91.7 -> 57 (4.9 TB/s), bf16
-//   87.7 -> 47.8, 64x64x64x32 32.4 -> 20.2, 90x77x45x23 26.6 + 8.9 -> 20.8;
-//   last pass 128x128x64x33 112 -> 108 (5.1 TB/s), bf16 weights 98.4 -> 66.2, 90x77x45x23 10.6 + 26.8 -> 29.1.
-// Whole step: 16x16x8x5 21.7 -> 17.2, 64x64x32x17 39.1 -> 33.3, 90x77x45x23 89.7 -> 70.4, five-way 156 -> 111, 128x128x64x33
-// 224 -> 201, with bf16 gradients and weights 200 -> 142.
+//   first pass 64x64x32x17 15.7 -> 9.9, 32x32x32x32x17 (bf16) 84.5 -> 34.8, 128x128x64x33 91.7 -> 56 (5.0 TB/s), bf16
+//   87.7 -> 46, 64x64x64x32 32.4 -> 20.2, 90x77x45x23 26.6 + 8.9 -> 19.8;
+//   last pass 128x128x64x33 112 -> 108 (5.1 TB/s), bf16 weights 98.4 -> 66, 90x77x45x23 10.6 + 26.8 -> 27.7.
+// Whole step: 16x16x8x5 21.7 -> 15.7, 64x64x32x17 39.1 -> 32.0, 90x77x45x23 89.7 -> 66.4, five-way 156 -> 107, 128x128x64x33
+// 224 -> 192, with bf16 gradients and weights 200 -> 132.
 //
 // Lanes: g = lane / 16, c = lane % 16.  A[i = c][k = g], B[k = g][j = c], D register r: D[i = 4 g + r][j = c].
 // Real columns are (m, p) = (re, im) parts interleaved: c = 2 m + p.
@@ -167,23 +167,22 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
   uint32_t cj0v, cj1v, nj0v, nj1v;
   range_of(slab, ts, cj0v, cj1v);
   range_of(nslab, nts, nj0v, nj1v);
+  const FactorRef fU3 = factor_ref(a.U3, (int64_t)K * M), fU2 = factor_ref(a.U2, (int64_t)I2 * M2);
   float2 creg[T4][NC];                                                   // conj(U3)[4 j + g][column]
 #pragma unroll
   for (int j = 0; j < T4; ++j)
 #pragma unroll
     for (int nc = 0; nc < NC; ++nc) {
       const int k = 4 * j + grp, m = (16 * nc + col) >> 1;
-      const bool in = k < K && m < M;
-      const float2 u = a.U3[in ? k * M + m : 0];
-      creg[j][nc] = in ? column_coef(make_float2(u.x, -u.y), col & 1) : make_float2(0.f, 0.f);
+      const float2 u = factor_entry(fU3, k, m, M, k < K && m < M);
+      creg[j][nc] = column_coef(make_float2(u.x, -u.y), col & 1);
     }
   for (int e = lane; e < slice; e += 64) sX[e] = 0.f;                    // pads stay finite
   stage_table(sT, ((I2 + 15) >> 4) * 4 * NM * 64, tid, (int)blockDim.x, [&](int e) -> float2 {
     const int l = e & 63, nm = (e >> 6) % NM, r = ((e >> 6) / NM) & 3, q = (e >> 6) / (4 * NM);
     const int i2 = 16 * q + 4 * (l >> 4) + r, m2 = 16 * nm + (l & 15);
-    const bool in = i2 < I2 && m2 < M2;
-    const float2 u = a.U2[in ? i2 * M2 + m2 : 0];
-    return in ? make_float2(u.x, -u.y) : make_float2(0.f, 0.f);
+    const float2 u = factor_entry(fU2, i2, m2, M2, i2 < I2 && m2 < M2);
+    return make_float2(u.x, -u.y);
   });
   int wofs[TB];                                                          // where the lane's pieces lie in the slice
 #pragma unroll
@@ -488,6 +487,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
   range_of(slab, ts, cj0v, cj1v);
   range_of(nslab, nts, nj0v, nj1v);
   fetch_y(slab < a.nslabs ? slab : 0);
+  const FactorRef fU3 = factor_ref(a.U3, (int64_t)M * K), fU2 = factor_ref(a.U2, (int64_t)I2 * K2);
   float2 cf[CT][NC][2], ct[NC][2];                                       // (c_alpha U3)[column][8 nc + 2 g + u]
 #pragma unroll
   for (int nc = 0; nc < NC; ++nc)
@@ -497,19 +497,16 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
 #pragma unroll
       for (int i = 0; i < CT; ++i) {
         const int m = (16 * i + col) >> 1;
-        const bool in = k < K && m < M;
-        const float2 f = a.U3[in ? m * K + k : 0];
-        cf[i][nc][u] = in ? column_coef(make_float2(a.c_alpha * f.x, a.c_alpha * f.y), part) : make_float2(0.f, 0.f);
+        const float2 f = factor_entry(fU3, m, k, K, k < K && m < M);
+        cf[i][nc][u] = column_coef(make_float2(a.c_alpha * f.x, a.c_alpha * f.y), part);
       }
-      const float2 f = a.U3[k < K ? (M - 1) * K + k : 0];
-      ct[nc][u] = k < K ? make_float2(a.c_alpha * f.x, a.c_alpha * f.y) : make_float2(0.f, 0.f);
+      const float2 f = factor_entry(fU3, M - 1, k, K, k < K);
+      ct[nc][u] = make_float2(a.c_alpha * f.x, a.c_alpha * f.y);
     }
   stage_table(sT, ((I2 + 15) >> 4) * SA * 64, tid, (int)blockDim.x, [&](int e) -> float2 {
     const int l = e & 63, s = (e >> 6) % SA, q = (e >> 6) / SA;
     const int i2 = 16 * q + (l & 15), m2 = 4 * s + (l >> 4);
-    const bool in = i2 < I2 && m2 < K2;
-    const float2 u = a.U2[in ? i2 * K2 + m2 : 0];
-    return in ? u : make_float2(0.f, 0.f);
+    return factor_entry(fU2, i2, m2, K2, i2 < I2 && m2 < K2);
   });
   uint32_t cj0 = __builtin_amdgcn_readfirstlane(cj0v), cj1 = __builtin_amdgcn_readfirstlane(cj1v);
   if (slab >= a.nslabs) cj1 = cj0;

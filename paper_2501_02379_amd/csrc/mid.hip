@@ -59,12 +59,11 @@ __device__ __forceinline__ void store_cols(float* o, const v4f* acc, int r) {
   else
     *reinterpret_cast<float4*>(o) = make_float4(acc[0][r], acc[1][r], acc[2][r], acc[3][r]);
 }
-// F[m, k] of the stage, zero outside (M, K)
+// F[m, k] of the stage, zero outside (M, K); U has rn columns
 template <bool PROJECT>
-__device__ __forceinline__ float2 factor_at(const float2* __restrict__ U, int rn, int m, int k, int M, int K) {
-  const bool in = m < M && k < K;
-  const float2 u = U[in ? (PROJECT ? (int64_t)k * rn + m : (int64_t)m * rn + k) : 0];
-  return in ? make_float2(u.x, PROJECT ? -u.y : u.y) : make_float2(0.f, 0.f);
+__device__ __forceinline__ float2 factor_at(const FactorRef& U, int rn, int m, int k, int M, int K) {
+  const float2 u = factor_entry(U, PROJECT ? k : m, PROJECT ? m : k, rn, m < M && k < K);
+  return make_float2(u.x, PROJECT ? -u.y : u.y);
 }
 
 constexpr int kThreads = 256, kWaves = 4;
@@ -106,7 +105,7 @@ __device__ __forceinline__ Cols columns_of(uint32_t cg, int c, uint32_t ncv, uin
 //   fetches the operands of its own rows straight into registers (no LDS table, no barrier in front of the
 //   matrix instructions) and the partial tiles meet in LDS, summed in a fixed order.
 template <int VEC, int MT, bool PROJECT, bool SPLIT>
-__global__ __launch_bounds__(kThreads) void k_mid(const float* __restrict__ x, const float2* __restrict__ U, int rn,
+__global__ __launch_bounds__(kThreads) void k_mid(const float* __restrict__ x, const float2* __restrict__ Up, int rn,
                                                   uint32_t ncv, uint32_t BV, int K, int M, float* __restrict__ out) {
   typedef typename ColVec<VEC>::type V;
   extern __shared__ float2 sF[];
@@ -118,6 +117,15 @@ __global__ __launch_bounds__(kThreads) void k_mid(const float* __restrict__ x, c
   const float* xp = x + (int64_t)cq.a * K * row + (int64_t)cq.b * VEC * 2;
   const int mbase = blockIdx.y * (16 * MT);
   const int J = (K + 3) >> 2;
+  // F[m, k] for k >= k0 = 4 j0 and the workgroup's rows: a full rank of an extent above 16384 does not fit one buffer
+  auto factor_from = [&](int j0) -> FactorRef {
+    const int64_t skip = PROJECT ? (int64_t)4 * j0 * rn : (int64_t)mbase * rn;
+    return factor_ref(Up + skip, (int64_t)(PROJECT ? K : M) * rn - skip);
+  };
+  auto factor_in = [&](const FactorRef& U, int j0, int m, int k) -> float2 {
+    const float2 u = factor_entry(U, PROJECT ? k - 4 * j0 : m - mbase, PROJECT ? m : k, rn, m < M && k < K);
+    return make_float2(u.x, PROJECT ? -u.y : u.y);
+  };
   auto load_x = [&](int j) -> V {                       // unconditional: rows past K meet zero factor entries
     const int k = 4 * j + grp;
     return *reinterpret_cast<const V*>(xp + (int64_t)(k < K ? k : K - 1) * row);
@@ -134,13 +142,14 @@ __global__ __launch_bounds__(kThreads) void k_mid(const float* __restrict__ x, c
     for (int j = j0; j < j1; j += kBatch) {
       V v[kBatch];
       float2 f[kBatch][MT];
+      const FactorRef U = factor_from(j);
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) v[u] = load_x(j + u);
 #pragma unroll
       for (int u = 0; u < kBatch; ++u)                  // (steps past the slice: zero coefficients)
 #pragma unroll
         for (int t = 0; t < MT; ++t)
-          f[u][t] = factor_at<PROJECT>(U, rn, mbase + 16 * t + col, j + u < j1 ? 4 * (j + u) + grp : K, M, K);
+          f[u][t] = factor_in(U, j, mbase + 16 * t + col, j + u < j1 ? 4 * (j + u) + grp : K);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
@@ -186,9 +195,10 @@ __global__ __launch_bounds__(kThreads) void k_mid(const float* __restrict__ x, c
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) cur[u] = load_x(jc0 + u);
       __syncthreads();                                  // previous chunk fully consumed
+      const FactorRef U = factor_from(jc0);
       stage_table(sF, jn * MT * 64, tid, [&](int e) -> float2 {
         const int l = e & 63, t = (e >> 6) % MT, j = (e >> 6) / MT;
-        return factor_at<PROJECT>(U, rn, mbase + 16 * t + (l & 15), 4 * (jc0 + j) + (l >> 4), M, K);
+        return factor_in(U, jc0, mbase + 16 * t + (l & 15), 4 * (jc0 + j) + (l >> 4));
       });
       __syncthreads();
       auto step = [&](const V& v, int j) {
@@ -231,11 +241,12 @@ __global__ __launch_bounds__(kThreads) void k_mid(const float* __restrict__ x, c
 // SHARE = true, for few columns: the 4 wavefronts share 16 column vectors and take one output tile each
 //   (tile 4 blockIdx.y + wave), operands straight from memory: no barrier at all.
 template <int VEC, int KS, bool SHARE>
-__global__ __launch_bounds__(kThreads) void k_expand(const float* __restrict__ x, const float2* __restrict__ U, int rn,
+__global__ __launch_bounds__(kThreads) void k_expand(const float* __restrict__ x, const float2* __restrict__ Up, int rn,
                                                      uint32_t ncv, uint32_t BV, int K, int M, int tiles,
                                                      float* __restrict__ out) {
   typedef typename ColVec<VEC>::type V;
   extern __shared__ float2 sF[];
+  const FactorRef U = factor_ref(Up, (int64_t)M * rn);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, grp = lane >> 4;
@@ -319,9 +330,10 @@ constexpr int kCoreThreads = 512, kCoreWaves = 8;
 constexpr int kCoreSteps = 4;             // steps of x per wavefront in flight: all of them for K <= 128
 
 template <int MT>
-__global__ __launch_bounds__(kCoreThreads) void k_core(const float* x, const float2* __restrict__ U, int rn, int K,
+__global__ __launch_bounds__(kCoreThreads) void k_core(const float* x, const float2* __restrict__ Up, int rn, int K,
                                                        int M, int64_t B, int groups, CoreAdam ad, float* z) {
   extern __shared__ float2 sF[];
+  const FactorRef U = factor_ref(Up, (int64_t)K * rn);
   constexpr int kPart = MT * 2 * 4 * 64;        // floats of one wavefront's partial tiles
   constexpr int kArea = kCoreWaves * kPart;     // [wave][tile][re / im][r][lane]; two of them take turns
   const int tid = threadIdx.x, lane = tid & 63;
