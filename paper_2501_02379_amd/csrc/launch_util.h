@@ -20,8 +20,8 @@ inline bool allow_lds(Kern kern, size_t bytes) {
 }
 
 // Workgroups of `kern` that are resident on one compute unit at a time (registers, LDS), asked of
-// the runtime once per kernel, workgroup and LDS size (`most` bounds the answer).  The tile loops are persistent (stride = grid size), so
-// the grid is exactly one resident set: more workgroups would run as a ragged second round.
+// the runtime once per kernel, workgroup and LDS size (`most` bounds the answer).  The tile loops are persistent
+// (stride = grid size), so the grid is exactly one resident set: more workgroups would run as a ragged second set.
 template <typename Kern>
 int resident_blocks(Kern kern, int threads, size_t lds, int most = 4) {
   static std::mutex mu;
