@@ -682,6 +682,26 @@ bool ends_kernel_fits(int K, int r, int I2, int r2) {
   return head_lds(kMaxWaves, K, I2, r2) <= kLdsLimit / 2 && tail_lds(kMaxWaves, K, I2, r2) <= kLdsLimit / 2;
 }
 
+// ... and which of those it pays for.  A tile costs a wavefront the same few round trips and whole 16-row halves of matrix
+// work however few rows it holds, and past 8192 slabs (two or more for every resident wavefront) the tiles of short slabs
+// follow each other; the separate kernels per mode take flat tiles of 32 rows wherever a slab ends, for one more launch
+// each way and one more trip of the mode-N result (r numbers per row) through memory.  (Slabs of whole 32-row tiles, which
+// the 32 x 32 kernels take as well, are not asked about: these are faster there whatever the rank.)  With S tiles of H halves in a slab
+// of I2 rows, both sides in the same units (fitted to 2400 measured pairs of whole steps; the worst choice loses 17 %).
+// Whole step, us, these kernels / the separate ones, slabs of I2 x K with ranks a quarter of that:
+//   16384 slabs: 4x5 41 / 32, 8x5 41 / 36, 16x5 42 / 42, 4x17 45 / 36, 8x17 47 / 46, 12x17 50 / 56, 4x65 89 / 71, 8x65 95 / 101;
+//   65536: 4x5 84 / 45, 8x5 88 / 60, 16x5 93 / 91, 24x5 114 / 118, 36x5 181 / 162, 8x9 93 / 74, 16x9 103 / 107, 8x17 108 / 96,
+//   12x17 118 / 123, 6x33 144 / 127, 8x33 153 / 151, 5x50 233 / 174;  262144: 4x3 252 / 96, 8x9 286 / 192, 28x2 341 / 367;
+//   4096 slabs: 4x5 24 / 27, 8x33 32 / 33, 36x5 31 / 33 (the saved launches win).
+// r: 65536 slabs of 12x9 with r = 1 95 / 82, r = 6 109 / 115, r = 9 126 / 143.
+bool ends_kernel_pays(int K, int r, int I2, int r2, int64_t nslabs) {
+  if (nslabs < 8192) return true;
+  const int R = end_tile_rows(K), S = (I2 + R - 1) / R, H = (I2 + 15) / 16;
+  const int row = 25 + (K < 17 ? K : 17) + 5 * r;
+  const int tiles = (nslabs < 16384 ? 35 : 50) * (6 * S + (r2 > 16 ? 9 : 5) * H);
+  return I2 * (row < 70 ? row : 70) >= tiles;
+}
+
 void launch_head(hipStream_t s, const void* g, int dtype, const int32_t* omega, const uint32_t* tile_start, float2* gs,
                  const float2* U3, int K, int M, const float2* U2, int I2, int M2, int64_t nslabs, float2* out) {
   const int R = end_tile_rows(K), S = (I2 + R - 1) / R;

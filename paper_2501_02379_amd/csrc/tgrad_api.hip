@@ -49,6 +49,7 @@ struct Plan {
   int64_t tile_elems = 0;
   bool fuse_next = false;        // the last-mode kernels also handle mode N-1 (see make_plan)
   bool narrow = false;           // ... and they are k_head / k_tail (ends.hip), on tiles that end with their slab
+  bool short_slabs = false;      // k_head / k_tail would fit, but separate kernels are faster
   int end_tiles = 0;             // k_head / k_tail: tiles per slab
   bool own_offsets = false;      // their tiles are not the flat tiles: support offsets of their own
   bool flat_offsets = true;      // some kernel walks the flat tiles with the support
@@ -138,7 +139,8 @@ int validate(const tgrad_config* c) {
   return TGRAD_OK;
 }
 
-void make_plan(const tgrad_config* c, Plan* p) {
+// `short_slabs_fused`: k_head / k_tail also where separate kernels are the faster ones (ends_kernel_pays).
+void make_plan(const tgrad_config* c, bool short_slabs_fused, Plan* p) {
   p->N = c->ndim;
   p->I = 1;
   p->C = 1;
@@ -197,6 +199,11 @@ void make_plan(const tgrad_config* c, Plan* p) {
       const bool full_tiles = p->rank[last] > 8 && p->rank[last - 1] > 16;
       p->narrow = p->tile_waves > 0 && !(wide && full_tiles) &&
                   ends_kernel_fits((int)p->shape[last], p->rank[last], (int)I2, p->rank[last - 1]);
+      if (p->narrow && !wide && !short_slabs_fused &&
+          !ends_kernel_pays((int)p->shape[last], p->rank[last], (int)I2, p->rank[last - 1], rows / I2)) {
+        p->narrow = false;
+        p->short_slabs = true;
+      }
       if (p->narrow) {
         const int R = end_tile_rows((int)p->shape[last]);
         p->end_tiles = (int)((I2 + R - 1) / R);
@@ -319,6 +326,17 @@ void make_plan(const tgrad_config* c, Plan* p) {
     p->ws_resid = take(p->order == TGRAD_ORDER_LR_US ? (size_t)p->I * 8 : 0);
   }
   p->workspace_bytes = o;
+}
+
+void make_plan(const tgrad_config* c, Plan* p) {
+  make_plan(c, false, p);
+  // The separate kernels keep the tensor after the first stage; where only the fused ones fit the fixed scratch of
+  // tgrad_step_static they are taken, so that the rule above refuses nothing there.
+  if (p->short_slabs && p->workspace_bytes > (size_t)TGRAD_STATIC_WORKSPACE_BYTES) {
+    Plan q;
+    make_plan(c, true, &q);
+    if (q.workspace_bytes <= (size_t)TGRAD_STATIC_WORKSPACE_BYTES) *p = q;
+  }
 }
 
 struct EventPair {

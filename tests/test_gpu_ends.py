@@ -53,3 +53,36 @@ def test_end_kernels_bf16_weights(shape, ranks, k, dt):
     for worst, frac in info["stats"]:
         assert worst <= 1
         assert frac <= max(5e-3, 2.0 / (2 * int(np.prod(shape))))
+
+
+# shape, ranks, fused: modes N-1 and N in one pass (False: separate kernels, 8192 slabs or more of few rows)
+SHORT_SLABS = [
+    ((91, 90, 4, 5), (9, 8, 2, 2), True),               # 8190 slabs
+    ((91, 91, 4, 5), (9, 8, 2, 2), False),              # 8281
+    ((128, 64, 8, 5), (9, 8, 3, 2), False),             # 8192, one tile in four filled
+    ((128, 64, 16, 5), (9, 8, 3, 2), True),             # ... half filled
+    ((128, 128, 9, 3), (9, 8, 3, 2), False),            # 16384: the further line
+    ((128, 128, 9, 9), (9, 8, 3, 9), True),             # ... a full last rank: its result is as long as the row
+    ((40, 30, 9, 36, 2), (4, 5, 3, 18, 1), False),      # 10800 slabs of one tile and four rows, two tiles of rank
+    ((32, 16, 16, 32, 3), (4, 5, 3, 18, 1), True),      # 8192 slabs of one whole tile
+]
+
+
+@pytest.mark.parametrize("shape,ranks,fused", SHORT_SLABS)
+def test_short_slabs_in_large_numbers(shape, ranks, fused):
+    """Both sides of the line from which on short slabs are left to separate kernels; launches and values."""
+    print("[case]", shape, ranks, fused, flush=True)
+    grads = [synth.small_case(shape, 350 + t, outlier_frac=(1, 100)) for t in range(2)]
+    rng = np.random.default_rng(7)
+    W0 = ((rng.standard_normal(shape) + 1j * rng.standard_normal(shape)) * 0.02).astype(np.complex64)
+    info = run_both(T, shape, ranks, int(np.prod(shape)) // 50, grads, W0, refresh_every=5, lr=2e-3, weight_decay=0.01)
+    assert all(info["omega_equal"])
+    check_parity(info, W0)
+    ctx = info["ctx"]
+    ctx.tgrad_set_profiling(True)
+    ctx.tgrad_step(T.to_device_weight(W0), T.to_device_grad(grads[0]))
+    times = ctx.tgrad_get_kernel_times()
+    between = len(shape) - 2 - (1 if fused else 0)       # stages between the first kernel and the core kernel, each way
+    if shape[0] * shape[1] <= 1600:                      # (small leading modes: two of them inside the core kernel)
+        between -= 1
+    assert times["project"]["launches"] == between and times["backproject"]["launches"] == between
