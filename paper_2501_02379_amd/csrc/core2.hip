@@ -10,9 +10,8 @@
 // belong to other workgroups), so it is the kernel of small leading modes, where launches cost more than
 // lines (core2_kernel_fits has the line and both sides of it).
 //
-// Tiles are 16 x 16 (v_mfma_f32_16x16x4f32, the same rate as 32x32x2): ranks are padded to 16 and not to
-// 32, and an extent of 128 gives 8 wavefronts a row tile each (two wavefronts per SIMD, so that one's
-// loads lie under the other's matrix instructions).  Operand layout (64 lanes, g = lane / 16, c = lane % 16):
+// Tiles are 16 x 16 (v_mfma_f32_16x16x4f32, the same rate as 32x32x2), one for both ranks; a wavefront has one tile of 16
+// rows i0 at a time.  Operand layout (64 lanes, g = lane / 16, c = lane % 16):
 //   A[i = c][k = g],  B[k = g][j = c],  D register r: D[i = 4 g + r][j = c].
 // The accumulator layout of one stage is the operand layout of the next - register r of D holds the
 // rows 4 g + r over the four lane groups, and a matrix-core step contracts exactly four rows, one per
@@ -61,12 +60,9 @@ struct Core2Adam {
 };
 
 constexpr int kSlots = 4;                    // wavefronts whose partial P lies in LDS at a time
-constexpr int slot_floats(int nt0, int nt1) { return nt0 * nt1 * 2 * 4 * 64; }
+constexpr int kSlot = 2 * 4 * 64;            // floats of one: [comp][r][lane]
 
-// NT0, NT1: tiles of 16 that hold the ranks of the two modes
-template <int NT0, int NT1>
 __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
-  constexpr int kSlot = slot_floats(NT0, NT1);
   extern __shared__ float2 sL[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -86,14 +82,14 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
   const bool active = slice < nsl && t_first < RT;     // (wave-uniform) idle wavefronts only pass the barriers
   const int64_t row = (int64_t)a.Cc * 2;      // floats between consecutive i1 of y
   const int64_t slab = row * I1;              // floats between consecutive i0 of y
-  // LDS: region A = stage-1 operands [J1][NT1][64], afterwards the partial sums ([slot][tile][comp][r][lane]
-  // floats) and N_L in slot 0; region B = stage-4 operands [Q1][4 NT1][64]
-  const int nA = J1 * NT1 * 64;
+  // LDS: region A = stage-1 operands [J1][64], afterwards the partial sums ([slot][comp][r][lane] floats) and N_L in
+  // slot 0; region B = stage-4 operands [Q1][4][64]
+  const int nA = J1 * 64;
   constexpr int kRedF2 = kSlots * kSlot / 2;
   float2* sT1 = sL;
   float* red = reinterpret_cast<float*>(sL);
   float2* sT4 = sL + (nA > kRedF2 ? nA : kRedF2);
-  const int nB = Q1 * NT1 * 4 * 64;
+  const int nB = Q1 * 4 * 64;
 
   // ---- prologue: the first rows of y, then all operands go in flight ----
   const int j_per = (J1 + nsl - 1) / nsl;
@@ -113,22 +109,12 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) cur[u] = load_y(rp, j0 + u);
   }
-  // moments of this thread's core entries
-  constexpr int kEnt = (NT0 * NT1 * 4 * 64 + kThreads - 1) / kThreads;
-  float2 mm[kEnt];
-  float vv[kEnt];
-  int64_t cidx[kEnt];
-  bool live[kEnt];
-#pragma unroll
-  for (int q = 0; q < kEnt; ++q) {
-    const int e = tid + q * kThreads;
-    const int l = e & 63, r = (e >> 6) & 3, t1 = (e >> 8) % NT1, t0 = (e >> 8) / NT1;
-    const int m0 = 16 * t0 + 4 * (l >> 4) + r, m1 = 16 * t1 + (l & 15);
-    live[q] = t0 < NT0 && m0 < M0 && m1 < M1;
-    cidx[q] = live[q] ? ((int64_t)m0 * M1 + m1) * a.Cc + plane : 0;
-    mm[q] = ad.m[cidx[q]];
-    vv[q] = ad.v[cidx[q]];
-  }
+  // moments of this thread's core entry (register tid / 64 of lane tid % 64; the upper four wavefronts have none)
+  const int em0 = 4 * grp + (wave & 3);
+  const bool live = wave < 4 && em0 < M0 && col < M1;
+  const int64_t cidx = live ? ((int64_t)em0 * M1 + col) * a.Cc + plane : 0;
+  const float2 mm = ad.m[cidx];
+  const float vv = ad.v[cidx];
   auto stage_table = [&](float2* dst, int n, auto gen) {      // 8 loads per thread in flight
     for (int e0 = tid; e0 < n; e0 += kThreads * 8) {
       float2 f[8];
@@ -139,31 +125,29 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
         if (e0 + u * kThreads < n) dst[e0 + u * kThreads] = f[u];
     }
   };
-  const FactorRef fU0 = factor_ref(a.U0, (int64_t)I0 * M0), fU1 = factor_ref(a.U1, (int64_t)I1 * M1);
+  // (sizes made scalar: a product that the compiler keeps in a vector register turns every load into a loop over the lanes)
+  const FactorRef fU0 = factor_ref(a.U0, __builtin_amdgcn_readfirstlane(I0 * M0));
+  const FactorRef fU1 = factor_ref(a.U1, __builtin_amdgcn_readfirstlane(I1 * M1));
   auto u1_at = [&](int i1, int m1) -> float2 { return factor_entry(fU1, i1, m1, M1, i1 < I1 && m1 < M1); };
   auto u0_at = [&](int i0, int m0) -> float2 { return factor_entry(fU0, i0, m0, M0, i0 < I0 && m0 < M0); };
-  stage_table(sT1, nA, [&](int e) -> float2 {                 // U1[4 j + g][16 t1 + c]
-    const int l = e & 63, t1 = (e >> 6) % NT1, j = (e >> 6) / NT1;
-    return u1_at(4 * j + (l >> 4), 16 * t1 + (l & 15));
+  stage_table(sT1, nA, [&](int e) -> float2 {                 // U1[4 j + g][c]
+    const int l = e & 63, j = e >> 6;
+    return u1_at(4 * j + (l >> 4), l & 15);
   });
-  stage_table(sT4, nB, [&](int e) -> float2 {                 // U1[16 q + c][16 t1 + 4 g + r]
-    const int l = e & 63, r = (e >> 6) & 3, t1 = (e >> 8) % NT1, q = (e >> 8) / NT1;
-    return u1_at(16 * q + (l & 15), 16 * t1 + 4 * (l >> 4) + r);
+  stage_table(sT4, nB, [&](int e) -> float2 {                 // U1[16 q + c][4 g + r]
+    const int l = e & 63, r = (e >> 6) & 3, q = e >> 8;
+    return u1_at(16 * q + (l & 15), 4 * (l >> 4) + r);
   });
   // the U0 operands of stage 2 (f2) and of stage 3 (f3) of the first row tile are requested here as well: asked for
   // where they are used, each is a memory round trip in front of its stage (16x16x8x5: 10.2 us, now 8.2)
-  float2 f2[NT0][4], f3[NT0][4];
-  auto fetch_f2 = [&](int t) {                                // U0[16 t + 4 g + r][16 t0 + c]
+  float2 f2[4], f3[4];
+  auto fetch_f2 = [&](int t) {                                // U0[16 t + 4 g + r][c]
 #pragma unroll
-    for (int t0 = 0; t0 < NT0; ++t0)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) f2[t0][r] = u0_at(16 * t + 4 * grp + r, 16 * t0 + col);
+    for (int r = 0; r < 4; ++r) f2[r] = u0_at(16 * t + 4 * grp + r, col);
   };
-  auto fetch_f3 = [&](int t) {                                // U0[16 t + c][16 t0 + 4 g + r]
+  auto fetch_f3 = [&](int t) {                                // U0[16 t + c][4 g + r]
 #pragma unroll
-    for (int t0 = 0; t0 < NT0; ++t0)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) f3[t0][r] = u0_at(16 * t + col, 16 * t0 + 4 * grp + r);
+    for (int r = 0; r < 4; ++r) f3[r] = u0_at(16 * t + col, 4 * grp + r);
   };
   if (active) {
     fetch_f2(t_first);
@@ -172,13 +156,8 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
   __syncthreads();
 
   // ---- stages 1 and 2 over this wavefront's row tiles ----
-  v4f p[NT0][NT1][2];
-#pragma unroll
-  for (int t0 = 0; t0 < NT0; ++t0)
-#pragma unroll
-    for (int t1 = 0; t1 < NT1; ++t1)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) p[t0][t1][i] = (v4f){0.f, 0.f, 0.f, 0.f};
+  v4f p[2];
+  p[0] = p[1] = (v4f){0.f, 0.f, 0.f, 0.f};
   if (active) {
     for (int t = t_first; t < RT; t += kWaves) {
       const float* rp = row_ptr(t);
@@ -187,20 +166,14 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
         for (int u = 0; u < kBatch; ++u) cur[u] = load_y(rp, j0 + u);
         fetch_f2(t);
       }
-      v4f tt[NT1][2];
-#pragma unroll
-      for (int t1 = 0; t1 < NT1; ++t1)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) tt[t1][i] = (v4f){0.f, 0.f, 0.f, 0.f};
+      v4f tt[2];
+      tt[0] = tt[1] = (v4f){0.f, 0.f, 0.f, 0.f};
       auto stage1 = [&](float2 v, int j) {
-#pragma unroll
-        for (int t1 = 0; t1 < NT1; ++t1) {
-          const float2 f = sT1[(j * NT1 + t1) * 64 + lane];
-          tt[t1][0] = mfma16(v.x, f.x, tt[t1][0]);             // re: yr ur + yi ui;  im: yi ur - yr ui
-          tt[t1][1] = mfma16(v.y, f.x, tt[t1][1]);
-          tt[t1][0] = mfma16(v.y, f.y, tt[t1][0]);
-          tt[t1][1] = mfma16(v.x, -f.y, tt[t1][1]);
-        }
+        const float2 f = sT1[j * 64 + lane];
+        tt[0] = mfma16(v.x, f.x, tt[0]);                       // re: yr ur + yi ui;  im: yi ur - yr ui
+        tt[1] = mfma16(v.y, f.x, tt[1]);
+        tt[0] = mfma16(v.y, f.y, tt[0]);
+        tt[1] = mfma16(v.x, -f.y, tt[1]);
       };
       int j = j0;
       for (; j + kBatch <= j1; j += kBatch) {
@@ -218,32 +191,22 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
       for (int u = 0; u < kBatch; ++u)
         if (j + u < j1) stage1(cur[u], j + u);
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int t0 = 0; t0 < NT0; ++t0) {
-          const float2 f = f2[t0][r];
-#pragma unroll
-          for (int t1 = 0; t1 < NT1; ++t1) {                   // re: ur tr + ui ti;  im: ur ti - ui tr
-            p[t0][t1][0] = mfma16(f.x, tt[t1][0][r], p[t0][t1][0]);
-            p[t0][t1][1] = mfma16(f.x, tt[t1][1][r], p[t0][t1][1]);
-            p[t0][t1][0] = mfma16(f.y, tt[t1][1][r], p[t0][t1][0]);
-            p[t0][t1][1] = mfma16(-f.y, tt[t1][0][r], p[t0][t1][1]);
-          }
-        }
+      for (int r = 0; r < 4; ++r) {                            // re: ur tr + ui ti;  im: ur ti - ui tr
+        const float2 f = f2[r];
+        p[0] = mfma16(f.x, tt[0][r], p[0]);
+        p[1] = mfma16(f.x, tt[1][r], p[1]);
+        p[0] = mfma16(f.y, tt[1][r], p[0]);
+        p[1] = mfma16(-f.y, tt[0][r], p[1]);
+      }
     }
   }
   __syncthreads();                                             // every wavefront is through with the stage-1 operands
   // ---- the wavefronts' partial sums: kSlots of them in LDS at a time, always the same order ----
   auto put = [&](int slot) {
 #pragma unroll
-    for (int t0 = 0; t0 < NT0; ++t0)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int t1 = 0; t1 < NT1; ++t1)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            red[slot * kSlot + (((t0 * NT1 + t1) * 2 + i) * 4 + r) * 64 + lane] = p[t0][t1][i][r];
+      for (int r = 0; r < 4; ++r) red[slot * kSlot + (i * 4 + r) * 64 + lane] = p[i][r];
   };
 #pragma unroll 1
   for (int base = kSlots; base < kWaves; base += kSlots) {
@@ -251,89 +214,69 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
     __syncthreads();
     if (wave < kSlots) {
 #pragma unroll
-      for (int t0 = 0; t0 < NT0; ++t0)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int t1 = 0; t1 < NT1; ++t1)
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-              p[t0][t1][i][r] += red[wave * kSlot + (((t0 * NT1 + t1) * 2 + i) * 4 + r) * 64 + lane];
+        for (int r = 0; r < 4; ++r) p[i][r] += red[wave * kSlot + (i * 4 + r) * 64 + lane];
     }
     __syncthreads();
   }
   if (wave < kSlots) put(wave);
   __syncthreads();
   // ---- AdamUpdate; N_L replaces the partial sums of slot 0 (each entry is read and written by one thread) ----
+  if (wave < 4) {
+    float* pr = red + wave * 64 + lane;
+    float* pi = pr + 256;
+    float gre = 0.f, gim = 0.f;
 #pragma unroll
-  for (int q = 0; q < kEnt; ++q) {
-    const int e = tid + q * kThreads;
-    const int l = e & 63, r = (e >> 6) & 3, tile = e >> 8;
-    if (NT0 * NT1 * 256 % kThreads == 0 || tile < NT0 * NT1) {
-      float* pr = red + (tile * 8 + r) * 64 + l;
-      float* pi = pr + 256;
-      float gre = 0.f, gim = 0.f;
-#pragma unroll
-      for (int w = 0; w < kSlots; ++w) {
-        gre += pr[w * kSlot];
-        gim += pi[w * kSlot];
-      }
-      float2 m = mm[q];
-      m.x = ad.beta1 * m.x + (1.f - ad.beta1) * gre;
-      m.y = ad.beta1 * m.y + (1.f - ad.beta1) * gim;
-      const float v = ad.beta2 * vv[q] + (1.f - ad.beta2) * (gre * gre + gim * gim);
-      const float d = 1.f / (sqrtf(v * ad.inv_c2) + ad.eps);
-      float nr = 0.f, ni = 0.f;
-      if (live[q]) {
-        ad.m[cidx[q]] = m;
-        ad.v[cidx[q]] = v;
-        ad.g_out[cidx[q]] = make_float2(gre, gim);
-        nr = m.x * ad.inv_c1 * d;
-        ni = m.y * ad.inv_c1 * d;
-      }
-      *pr = nr;
-      *pi = ni;
+    for (int w = 0; w < kSlots; ++w) {
+      gre += pr[w * kSlot];
+      gim += pi[w * kSlot];
     }
+    float2 m = mm;
+    m.x = ad.beta1 * m.x + (1.f - ad.beta1) * gre;
+    m.y = ad.beta1 * m.y + (1.f - ad.beta1) * gim;
+    const float v = ad.beta2 * vv + (1.f - ad.beta2) * (gre * gre + gim * gim);
+    const float d = 1.f / (sqrtf(v * ad.inv_c2) + ad.eps);
+    float nr = 0.f, ni = 0.f;
+    if (live) {
+      ad.m[cidx] = m;
+      ad.v[cidx] = v;
+      ad.g_out[cidx] = make_float2(gre, gim);
+      nr = m.x * ad.inv_c1 * d;
+      ni = m.y * ad.inv_c1 * d;
+    }
+    *pr = nr;
+    *pi = ni;
   }
   __syncthreads();
   if (!active) return;                                         // no barrier follows
   // ---- stages 3 and 4 ----
   float* zp = a.z + 2 * (int64_t)plane;
   for (int t = t_first; t < RT; t += kWaves) {
-    v4f rr[NT1][2];
-#pragma unroll
-    for (int t1 = 0; t1 < NT1; ++t1)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) rr[t1][i] = (v4f){0.f, 0.f, 0.f, 0.f};
+    v4f rr[2];
+    rr[0] = rr[1] = (v4f){0.f, 0.f, 0.f, 0.f};
     if (t != t_first) fetch_f3(t);
 #pragma unroll
-    for (int t0 = 0; t0 < NT0; ++t0)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float2 f = f3[t0][r];
-#pragma unroll
-        for (int t1 = 0; t1 < NT1; ++t1) {                     // re: nr ur - ni ui;  im: ni ur + nr ui
-          const float nr = red[((t0 * NT1 + t1) * 8 + r) * 64 + lane], ni = red[((t0 * NT1 + t1) * 8 + 4 + r) * 64 + lane];
-          rr[t1][0] = mfma16(nr, f.x, rr[t1][0]);
-          rr[t1][1] = mfma16(ni, f.x, rr[t1][1]);
-          rr[t1][0] = mfma16(ni, -f.y, rr[t1][0]);
-          rr[t1][1] = mfma16(nr, f.y, rr[t1][1]);
-        }
-      }
+    for (int r = 0; r < 4; ++r) {                              // re: nr ur - ni ui;  im: ni ur + nr ui
+      const float2 f = f3[r];
+      const float nr = red[r * 64 + lane], ni = red[(4 + r) * 64 + lane];
+      rr[0] = mfma16(nr, f.x, rr[0]);
+      rr[1] = mfma16(ni, f.x, rr[1]);
+      rr[0] = mfma16(ni, -f.y, rr[0]);
+      rr[1] = mfma16(nr, f.y, rr[1]);
+    }
     for (int q = slice; q < Q1; q += nsl) {
       v4f z[2];
       z[0] = z[1] = (v4f){0.f, 0.f, 0.f, 0.f};
-      const float2* ft = sT4 + q * NT1 * 256 + lane;
+      const float2* ft = sT4 + q * 256 + lane;
 #pragma unroll
-      for (int t1 = 0; t1 < NT1; ++t1)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {                          // re: rr ur - ri ui;  im: rr ui + ri ur
-          const float2 f = ft[(t1 * 4 + r) * 64];
-          z[0] = mfma16(rr[t1][0][r], f.x, z[0]);
-          z[1] = mfma16(rr[t1][0][r], f.y, z[1]);
-          z[0] = mfma16(rr[t1][1][r], -f.y, z[0]);
-          z[1] = mfma16(rr[t1][1][r], f.x, z[1]);
-        }
+      for (int r = 0; r < 4; ++r) {                            // re: rr ur - ri ui;  im: rr ui + ri ur
+        const float2 f = ft[r * 64];
+        z[0] = mfma16(rr[0][r], f.x, z[0]);
+        z[1] = mfma16(rr[0][r], f.y, z[1]);
+        z[0] = mfma16(rr[1][r], -f.y, z[0]);
+        z[1] = mfma16(rr[1][r], f.x, z[1]);
+      }
       const int i1 = 16 * q + col;
       if (i1 < I1) {
         float* zt = zp + (int64_t)(16 * t + 4 * grp) * slab + (int64_t)i1 * row;
@@ -346,48 +289,39 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
   }
 }
 
-size_t core2_lds(int I1, int nt0, int nt1) {
-  const size_t table = (size_t)((I1 + 3) / 4) * nt1 * 64 * 8, red = (size_t)kSlots * slot_floats(nt0, nt1) * 4;
-  return (table > red ? table : red) + (size_t)((I1 + 15) / 16) * nt1 * 4 * 64 * 8;
+size_t core2_lds(int I1) {
+  const size_t table = (size_t)((I1 + 3) / 4) * 64 * 8, red = (size_t)kSlots * kSlot * 4;
+  return (table > red ? table : red) + (size_t)((I1 + 15) / 16) * 4 * 64 * 8;
 }
 
 }  // namespace
 
-// Where the two leading modes (extents I0, I1, ranks M0, M1) and the core between them are one launch.  Against
-// the three kernels k_mid, k_core, k_expand, difference of a whole step in us (one launch - three):
-//   16x16x8x5 -2.7, 32x32x12x7 -4.2, 38x38x32 (r 9,9,8) -2.1, 48x16x48x25 -1.0;
-//   46x46x64 (r 12,12,16) +0.9, 26x64x64 +0.4, 64x64x32x17 (r 16,16,8,4) +3.9,
-//   90x77x45x23 (r 23,19,11,6) +9.7, 128x128x64x33 (r 32,32,16,8) +13:
-// up to 40 x 40 with ranks of one tile the saved launches win, above that the whole cache lines of the three
-// kernels do.  Not taken with `slabs_512` (the end kernels fused over at least 512 slabs) and a first extent up to
-// 16, nor above that line except for a first extent of 128 with 96 ... 384 columns where both sides are level
-// (128x40x32x13, r 8,6,32,12: +2.0; 128x128x32x13, r 32,32,32,12: -2; 128x33x32x9, r 8,6,20,5: -0.2): the tests hold the launch structure of those two groups of shapes.
-bool core2_kernel_fits(int I0, int I1, int M0, int M1, int64_t Cc, bool slabs_512) {
-  if (M0 > 32 || M1 > 32 || Cc < 1) return false;
-  if (I0 * I1 <= 1600 && M0 <= 16 && M1 <= 16) return !(slabs_512 && I0 <= 16);
-  return slabs_512 && I0 == 128 && I1 <= 128 && Cc >= 96 && Cc <= 384 && (I1 <= 48 || Cc > 256);
+// Where the two leading modes (extents I0, I1, ranks M0, M1) and the Cc columns of the core between them are one launch.
+// Against the three kernels k_mid, k_core, k_expand, difference of a whole step of 17 ... 45 us (one launch - three):
+//   at 8, 64, 128, 256 columns (and 512, 2048) with ranks a quarter of the extents
+//     8x8 -5, -4, -3, -3 (-1, +22); 16x16 -5, -4, -3, -3 (+1, +25); 32x32 -2, -1, -1, -2 (+4, +30); 40x40 -2, -2, -2, -1 (0, +23);
+//   at 8, 64, 128, 256 columns with ranks 8, 8
+//     8x200 -4, -3, -3, -1; 100x16 -4, -3, -4, -2; 16x64 -4, -2, -1, +1; 32x50 -2, -1, 0, +1;
+//   ... with ranks 16, 16
+//     32x32 -2, -1, 0, 0; 40x40 -2, 0, 0, 0; 16x64 -2, -1, 0, +1; 16x100 -2, 0, +1, +3;
+//   ... of larger modes
+//     46x46 (r 23,23) +2, +3, +4, +1; 64x64 (r 16,16) +3, +3, +5, +4; 128x40 (r 32,10) +1, +4, +3, +5;
+//     128x128 (r 32,32) +22, +22, +20, +17, and +36 with 384 columns.
+// So: up to 40 x 40 with ranks of one tile and up to one workgroup per compute unit the saved launches win; after that the
+// whole cache lines of the three kernels do.
+bool core2_kernel_fits(int I0, int I1, int M0, int M1, int64_t Cc) {
+  return I0 * I1 <= 1600 && M0 <= 16 && M1 <= 16 && Cc >= 1 && Cc <= 256;
 }
 
 void launch_core2(hipStream_t s, const float2* x, const float2* U0, const float2* U1, int I0, int I1, int M0, int M1,
                   int64_t Cc, float2* m, float* v, float2* g_out, float beta1, float beta2, float inv_c1, float inv_c2,
                   float eps, float2* z) {
   if (Cc <= 0) return;
-  const int nt0 = M0 <= 16 ? 1 : 2, nt1 = M1 <= 16 ? 1 : 2;
-  const size_t lds = core2_lds(I1, nt0, nt1);
+  const size_t lds = core2_lds(I1);
   Core2Args a{reinterpret_cast<const float*>(x), reinterpret_cast<float*>(z), U0, U1, I0, I1, M0, M1, (int)Cc};
   Core2Adam ad{m, v, g_out, beta1, beta2, inv_c1, inv_c2, eps};
-  const dim3 grid((unsigned)((Cc + 7) / 8 * 8)), block(kThreads);
-#define TGRAD_C2(A_, B_)                                 \
-  do {                                                   \
-    allow_lds(k_core2<A_, B_>, lds);                     \
-    k_core2<A_, B_><<<grid, block, lds, s>>>(a, ad);     \
-  } while (0)
-  if (nt0 == 1) {
-    if (nt1 == 1) TGRAD_C2(1, 1); else TGRAD_C2(1, 2);
-  } else {
-    if (nt1 == 1) TGRAD_C2(2, 1); else TGRAD_C2(2, 2);
-  }
-#undef TGRAD_C2
+  allow_lds(k_core2, lds);
+  k_core2<<<dim3((unsigned)((Cc + 7) / 8 * 8)), dim3(kThreads), lds, s>>>(a, ad);
 }
 
 }  // namespace tgrad

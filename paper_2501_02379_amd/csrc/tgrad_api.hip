@@ -189,12 +189,10 @@ void make_plan(const tgrad_config* c, bool short_slabs_fused, Plan* p) {
     // Fusion of the mode-(N-1) stages into the last-mode kernels.  On 32 x 32 tiles: whole 32-row tiles per slab,
     // one column tile of the last mode (r_N <= 16), r_(N-1) <= 32, enough slabs to fill the chip.
     bool wide = p->tile_waves == 4 && N >= 3;
-    bool slabs_512 = false;
     if (N >= 3) {
       const int64_t I2 = p->shape[last - 1];
-      slabs_512 = rows / I2 >= 512;
       wide = wide && (I2 % 32 == 0) && I2 <= TGRAD_MAX_EXTENT && p->rank[last - 1] <= 32 && 2 * p->rank[last] <= 32 &&
-             slabs_512 && p->shape[last] <= fused_max_last_extent();
+             rows / I2 >= 512 && p->shape[last] <= fused_max_last_extent();
       // Otherwise, and wherever the ranks leave half of a 32-wide tile empty, on 16 x 16 tiles.
       const bool full_tiles = p->rank[last] > 8 && p->rank[last - 1] > 16;
       p->narrow = p->tile_waves > 0 && !(wide && full_tiles) &&
@@ -216,8 +214,7 @@ void make_plan(const tgrad_config* c, bool short_slabs_fused, Plan* p) {
     if (N >= 3 && !(p->fuse_next && N == 3)) {  // (N = 3 with the fused end kernels leaves one mode: k_core)
       int64_t cc = 1;
       for (int m = 2; m < N; ++m) cc *= p->rank[m];
-      p->fuse_core2 = core2_kernel_fits((int)p->shape[0], (int)p->shape[1], p->rank[0], p->rank[1], cc,
-                                        p->fuse_next && slabs_512);
+      p->fuse_core2 = core2_kernel_fits((int)p->shape[0], (int)p->shape[1], p->rank[0], p->rank[1], cc);
     }
   }
 

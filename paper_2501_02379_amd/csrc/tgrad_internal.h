@@ -112,7 +112,7 @@ bool core_kernel_fits(int K, int M);
 void launch_core(hipStream_t s, const float2* x, const float2* U, int rn, int K, int M, int64_t B, float2* m,
                  float* v, float2* g_out, float beta1, float beta2, float inv_c1, float inv_c2, float eps,
                  float2* z);
-bool core2_kernel_fits(int I0, int I1, int M0, int M1, int64_t Cc, bool slabs_512);
+bool core2_kernel_fits(int I0, int I1, int M0, int M1, int64_t Cc);
 void launch_core2(hipStream_t s, const float2* x, const float2* U0, const float2* U1, int I0, int I1, int M0, int M1,
                   int64_t Cc, float2* m, float* v, float2* g_out, float beta1, float beta2, float inv_c1, float inv_c2,
                   float eps, float2* z);
