@@ -21,8 +21,8 @@
  *  - Every kernel launch is checked where it happens.  A HIP error that is already pending when
  *    `tgrad_step`, `tgrad_step_static` or `tgrad_refresh_factors` is entered belongs to the caller:
  *    the call returns TGRAD_ERR_HIP, launches nothing and leaves the error in place.
- *  - Which kernels serve a configuration is a function of the configuration alone (no environment
- *    switches): matrix-core kernels for the shapes they cover (last-mode rank <= 32 and last extent
+ *  - Which kernels serve a configuration is a function of the configuration and the entry point alone
+ *    (no environment switches): matrix-core kernels for the shapes they cover (last-mode rank <= 32 and last extent
  *    >= 2; two modes per pass when the shape allows), one-thread-per-output kernels for the rest.
  *  - A context is used from one host thread at a time.
  *  - Tensors are dense, row-major (last mode fastest).  TGRAD_C64 elements are
@@ -200,7 +200,8 @@ int tgrad_step(tgrad_ctx* ctx, void* weight_dev, const void* grad_dev);
  * context, and the scratch that `workspace_dev` provides elsewhere is a fixed array inside the
  * library, TGRAD_STATIC_WORKSPACE_BYTES per GPU, which every GPU that runs the library holds until
  * the process ends.  A configuration whose `tgrad_query_sizes` workspace exceeds that size is
- * rejected with TGRAD_ERR_UNSUPPORTED and nothing is launched.
+ * rejected with TGRAD_ERR_UNSUPPORTED and nothing is launched, unless (leading extents of 8192 and
+ * more in front of few rows) other kernels of this library, slower there, do with that size.
  *  cfg         host pointer; refresh_every must be >= 1 (INVALID_ARG otherwise).
  *  state_dev   device pointer, >= state_bytes of `tgrad_query_sizes`, 256-byte aligned: the optimizer
  *              state (Omega, M_S, V_S, M_L, V_L, U^(n)).  The caller zero-fills it before the call

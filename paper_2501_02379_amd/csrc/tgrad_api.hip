@@ -325,17 +325,6 @@ void make_plan(const tgrad_config* c, bool short_slabs_fused, Plan* p) {
   p->workspace_bytes = o;
 }
 
-void make_plan(const tgrad_config* c, Plan* p) {
-  make_plan(c, false, p);
-  // The separate kernels keep the tensor after the first stage; where only the fused ones fit the fixed scratch of
-  // tgrad_step_static they are taken, so that the rule above refuses nothing there.
-  if (p->short_slabs && p->workspace_bytes > (size_t)TGRAD_STATIC_WORKSPACE_BYTES) {
-    Plan q;
-    make_plan(c, true, &q);
-    if (q.workspace_bytes <= (size_t)TGRAD_STATIC_WORKSPACE_BYTES) *p = q;
-  }
-}
-
 struct EventPair {
   hipEvent_t a, b;
   int kid;
@@ -868,7 +857,7 @@ int tgrad_query_sizes(const tgrad_config* cfg, size_t* state_bytes, size_t* work
   int rc = validate(cfg);
   if (rc != TGRAD_OK) return rc;
   Plan p;
-  make_plan(cfg, &p);
+  make_plan(cfg, false, &p);
   *state_bytes = p.state_bytes;
   *workspace_bytes = p.workspace_bytes;
   return TGRAD_OK;
@@ -885,7 +874,7 @@ int tgrad_init(tgrad_ctx** out, const tgrad_config* cfg, void* state_dev, void* 
   tgrad_ctx* c = new (std::nothrow) tgrad_ctx();
   if (!c) return TGRAD_ERR_INVALID_ARG;
   c->cfg = *cfg;
-  make_plan(cfg, &c->plan);
+  make_plan(cfg, false, &c->plan);
   c->state = static_cast<char*>(state_dev);
   c->ws = static_cast<char*>(workspace_dev);
   c->stream = static_cast<hipStream_t>(hip_stream);
@@ -944,7 +933,9 @@ int tgrad_step_static(const tgrad_config* cfg, void* state_dev, int64_t t, void*
   if (cfg->refresh_every < 1) return TGRAD_ERR_INVALID_ARG;      // nobody else could refresh this state
   tgrad_ctx c;                                                    // on the stack: nothing is allocated
   c.cfg = *cfg;
-  make_plan(cfg, &c.plan);
+  make_plan(cfg, false, &c.plan);
+  // The separate kernels for short slabs keep one more tensor, the one after the first stage; the fused ones may still fit.
+  if (c.plan.short_slabs && c.plan.workspace_bytes > (size_t)TGRAD_STATIC_WORKSPACE_BYTES) make_plan(cfg, true, &c.plan);
   if (c.plan.workspace_bytes > (size_t)TGRAD_STATIC_WORKSPACE_BYTES) return TGRAD_ERR_UNSUPPORTED;
   void* ws = nullptr;
   rc = static_workspace(&ws);

@@ -145,15 +145,6 @@ def test_static_step_argument_checks_need_no_gpu():
     assert lib.tgrad_step_static(C.byref(small), 256, 0, 512, 1024, None) == T.TGRAD_ERR_INVALID_ARG
 
 
-def test_short_slabs_keep_the_fixed_scratch():
-    """8568 slabs of 6 x 5 are left to separate kernels, which keep one more tensor; where only the fused kernels fit the
-    fixed scratch of `tgrad_step_static` they are taken, so such a configuration is accepted all the same."""
-    stage = 84 * 102 * 6 * 2 * 8                         # the mode-N result, the tensor in question
-    fits = T.make_config((84, 102, 6, 5), (10, 12, 1, 2), 2570, refresh_every=5)
-    rc, _, wb = T.tgrad_query_sizes(fits)
-    assert rc == T.TGRAD_OK and T.STATIC_WORKSPACE_BYTES - stage < wb <= T.STATIC_WORKSPACE_BYTES
-
-
 def test_bench_refuses_more_than_one_gpu():
     """This build runs on one GPU: the benchmark says so and exits instead of pretending to scale."""
     import os

@@ -21,6 +21,7 @@ EXTRA = [
     ((12, 10, 9, 7), (3, 4, 2, 3), 60, "cbf16", "bf16", 0),       # half-precision gradients and weights
     ((8, 7, 40), (2, 2, 36), 30, "c64", "c64", 0),                # generic last-mode kernels (support bitmask)
     ((16, 32, 32, 9), (4, 8, 8, 4), 300, "c64", "c64", 1),        # low rank first, fused tier
+    ((120, 70, 4, 3), (3, 4, 2, 2), 600, "c64", "c64", 0),        # 8400 slabs of 4 x 3: separate kernels
 ]
 ITEMS = [T.STATE_INDICES, T.STATE_CORE_M, T.STATE_CORE_V, T.STATE_SPARSE_M, T.STATE_SPARSE_V]
 
@@ -90,6 +91,30 @@ def test_static_step_other_tiers_interleaved(case):
         b.step()
         a.check()
         b.check()
+
+
+def test_static_step_on_short_slabs_beyond_the_workspace_of_a_context():
+    """8568 slabs of 6 x 5 are left to separate kernels, which keep one tensor more than the fixed array holds; the static
+    step then takes the fused kernels, which fit.  Both sum in float32 in their own order, and one step moves an entry by
+    lr times a number of order one."""
+    import torch
+    shape, ranks, k, lr = (84, 102, 6, 5), (10, 12, 1, 2), 2570, 2e-3
+    cfg = T.make_config(shape, ranks, k, lr=lr, weight_decay=0.01, refresh_every=3)
+    rc, sb, wb = T.tgrad_query_sizes(cfg)
+    assert rc == T.TGRAD_OK and wb > T.STATIC_WORKSPACE_BYTES
+    ctx = T.Context(cfg)
+    state = torch.zeros(sb, dtype=torch.uint8, device="cuda:0")
+    rng = np.random.default_rng(4500)
+    W0 = ((rng.standard_normal(shape) + 1j * rng.standard_normal(shape)) * 0.02).astype(np.complex64)
+    W_ctx, W_static = T.to_device_weight(W0), T.to_device_weight(W0)
+    for t in range(4):
+        gd = T.to_device_grad(synth.small_case(shape, 4500 + t))
+        ctx.tgrad_step(W_ctx, gd)
+        T.tgrad_step_static(cfg, state, t, W_static, gd)
+    torch.cuda.synchronize()
+    a, b = T.weight_to_host(W_static), T.weight_to_host(W_ctx)
+    assert np.max(np.abs(b - W0)) > lr / 2 and np.max(np.abs(a - b)) < 1e-2 * lr
+    assert np.linalg.norm(a - b) < 1e-5 * np.linalg.norm(b - W0)
 
 
 def test_static_step_rejects_what_it_cannot_serve():
