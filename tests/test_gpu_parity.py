@@ -134,11 +134,11 @@ def test_exact_low_rank_gradient_gives_planted_subspace():
 
 
 # ------------------------------------------------------------------ the three kernel tiers, small
-FUSED_SHAPES = [
+FUSED_SHAPES = [                                   # k_head / k_tail (more of their edges: test_gpu_ends.py)
     ((16, 32, 32, 9), (4, 8, 8, 4), 300),          # one tile per slab
     ((16, 32, 64, 5), (4, 8, 16, 2), 200),         # two tiles per slab
-    ((16, 32, 32, 33), (4, 8, 8, 8), 500),         # odd last extent, 9 pieces per lane and tile
-    ((8, 64, 32, 35), (4, 8, 8, 6), 500),          # odd last extent, the long-row variant (17 pieces, 33 row pairs)
+    ((16, 32, 32, 33), (4, 8, 8, 8), 500),         # the longest rows of 32-row tiles, lone last column
+    ((8, 64, 32, 35), (4, 8, 8, 6), 500),          # 16-row tiles
     ((16, 32, 32, 8), (4, 8, 8, 4), 300),          # even last extent: padded LDS rows
     ((16, 32, 32, 9), (4, 8, 8, 4), 45000),        # more than 64 support entries in every tile
     ((42, 39, 32, 9), (4, 8, 8, 4), 5000),         # leading modes too large for one core kernel
@@ -154,8 +154,8 @@ def _core_launches(shape, ranks):
 
 @pytest.mark.parametrize("shape,ranks,k", FUSED_SHAPES)
 def test_fused_tier_small_shapes(shape, ranks, k):
-    """Shapes that take the fused kernels (modes N-1 and N in one pass) at a size the oracle runs
-    whole; the launch counts prove which tier ran."""
+    """Shapes that take the fused kernels (modes N-1 and N in one pass) on 16 x 16 tiles at a size the oracle runs
+    whole; the launches prove which tier ran (only the 32 x 32 kernels have a factor packed for them)."""
     _announce("fused tier", shape, ranks, k)
     grads = [synth.small_case(shape, 500 + t, outlier_frac=(1, 200)) for t in range(6)]
     rng = np.random.default_rng(6)
@@ -172,6 +172,77 @@ def test_fused_tier_small_shapes(shape, ranks, k):
     assert times["core"]["launches"] == 1
     between = len(shape) - 2 - _core_launches(shape, ranks)
     assert _launches(times, "project") == between and _launches(times, "backproject") == between
+    assert _packed_factors(ctx, grads[0]) == 0
+
+
+def _packed_factors(ctx, g):
+    """Factor copies that a refresh on `g` makes (identity factors of uncompressed modes are counted under the same name)."""
+    ctx.tgrad_set_profiling(False)
+    ctx.tgrad_set_profiling(True)
+    ctx.tgrad_refresh_factors(T.to_device_grad(g))
+    return _launches(ctx.tgrad_get_kernel_times(), "factor_pack") - sum(r == i for r, i in zip(ctx.rank, ctx.shape))
+
+
+# Both ranks in the upper half of a 32-wide tile, whole 32-row tiles, 512 slabs: k_lproj_flat (odd last extent) or
+# k_lproj<FUSE> (even) and k_lupdate_fused.  Tile pieces per lane: 5 up to an extent of 20, 9 up to 36, 17 up to 66.
+WIDE_SHAPES = [
+    # shape, ranks, k, gradient dtype
+    ((32, 16, 32, 20), (4, 5, 20, 12), 900, "c64"),
+    ((32, 16, 32, 20), (4, 5, 20, 12), 900, "cbf16"),
+    ((32, 17, 32, 32), (4, 5, 17, 9), 1500, "c64"),        # the shortest ranks
+    ((32, 17, 32, 34), (4, 5, 20, 12), 1500, "cbf16"),
+    ((16, 32, 64, 36), (4, 5, 20, 12), 1500, "c64"),       # two tiles per slab, the long-row variant
+    ((32, 16, 32, 66), (4, 5, 32, 16), 40000, "cbf16"),    # longest rows, full ranks
+    ((32, 16, 32, 13), (4, 5, 20, 12), 900, "cbf16"),      # odd from here on
+    ((32, 16, 32, 21), (4, 5, 20, 12), 900, "c64"),
+    ((32, 17, 32, 33), (4, 5, 20, 12), 1500, "cbf16"),
+    ((32, 17, 32, 65), (4, 5, 32, 16), 40000, "cbf16"),
+    ((32, 16, 256, 13), (4, 5, 20, 5), 900, "c64"),        # a mode too long for the other kernels' table beside this rank
+]
+
+
+@pytest.mark.parametrize("shape,ranks,k,dt", WIDE_SHAPES)
+def test_fused_tier_on_32_wide_tiles(shape, ranks, k, dt):
+    _announce("32-wide tiles", shape, ranks, k, dt)
+    grads = [synth.small_case(shape, 520 + t, outlier_frac=(1, 200), dtype=dt) for t in range(3)]
+    rng = np.random.default_rng(16)
+    W0 = ((rng.standard_normal(shape) + 1j * rng.standard_normal(shape)) * 0.02).astype(np.complex64)
+    info = run_both(T, shape, ranks, k, grads, W0, refresh_every=2, lr=2e-3, weight_decay=0.01,
+                    grad_dtype=T.TGRAD_CBF16 if dt == "cbf16" else 0)
+    assert all(info["omega_equal"])
+    check_parity(info, W0)
+    assert _packed_factors(info["ctx"], grads[0]) == 1
+
+
+CORE_SHAPES = [                                            # first extent and rank of k_core
+    ((70, 41, 8, 9), (33, 7, 4, 3), 900),                  # the first rank of four tiles, nine of sixteen steps
+    ((128, 12, 9, 8), (64, 5, 4, 3), 900),                 # full tiles, every step and output tile in one go
+    ((129, 12, 9, 8), (64, 5, 4, 3), 900),                 # ... one row more: operands fetched again
+    ((200, 12, 9, 8), (40, 7, 5, 3), 900),
+    ((256, 10, 9, 8), (20, 5, 4, 3), 900),                 # two tiles of rank, two output tiles for every wavefront
+    ((150, 17, 9, 8), (9, 5, 4, 3), 900),                  # one tile of rank
+    ((130, 46, 23, 17), (40, 23, 23, 17), 20000),          # 8993 columns: 563 groups, three for some of 256 workgroups
+    ((80, 9, 9, 8), (66, 5, 4, 3), 900),                   # a rank beyond k_core: three kernels
+]
+
+
+@pytest.mark.parametrize("shape,ranks,k", CORE_SHAPES)
+def test_core_kernel_extents_and_ranks(shape, ranks, k):
+    """k_core at its largest ranks, with first extents on both sides of 128 (where a workgroup's operands no longer
+    stay in registers), and with more groups of columns than workgroups are resident."""
+    _announce("core kernel", shape, ranks, k)
+    grads = [synth.small_case(shape, 540 + t, outlier_frac=(1, 200)) for t in range(3)]
+    rng = np.random.default_rng(17)
+    W0 = ((rng.standard_normal(shape) + 1j * rng.standard_normal(shape)) * 0.02).astype(np.complex64)
+    info = run_both(T, shape, ranks, k, grads, W0, refresh_every=2, lr=2e-3, weight_decay=0.01)
+    assert all(info["omega_equal"])
+    check_parity(info, W0)
+    ctx = info["ctx"]
+    ctx.tgrad_set_profiling(True)
+    ctx.tgrad_step(T.to_device_weight(W0), T.to_device_grad(grads[0]))
+    times = ctx.tgrad_get_kernel_times()
+    assert _launches(times, "core") == (1 if ranks[0] <= 64 else 0)
+    assert _launches(times, "adam_core") == (0 if ranks[0] <= 64 else 1)
 
 
 CORE2_SHAPES = [                                              # both leading modes and AdamUpdate in one launch?
@@ -227,11 +298,18 @@ def _bf16_weights(shape, seed):
 
 BF16W_CASES = [
     # shape, ranks, k, gradient dtype            kernel tier
-    ((16, 16, 8, 5), (8, 8, 4, 3), 103, "c64"),      # matrix-core, unfused
+    ((16, 16, 8, 5), (8, 8, 4, 3), 103, "c64"),      # fused
     ((16, 32, 32, 9), (4, 8, 8, 4), 300, "c64"),     # fused
     ((16, 32, 64, 5), (4, 8, 16, 2), 200, "cbf16"),  # fused, half-precision gradients too
-    ((7, 5, 3), (3, 2, 2), 9, "c64"),                # last tile ragged: 3 rows x 3 elements
-    ((9, 7, 6), (3, 3, 2), 11, "c64"),               # tail of 2 elements after the whole pieces
+    ((7, 5, 3), (3, 2, 2), 9, "c64"),                # fused, slabs of 15 elements
+    ((9, 7, 6), (3, 3, 2), 11, "c64"),               # fused, tail of 2 elements after the whole pieces
+    ((12, 9, 3, 7), (3, 3, 2, 3), 30, "c64"),        # separate kernels (three rows per slab)
+    ((9, 8, 40, 9), (3, 3, 36, 3), 300, "cbf16"),    # ... (a rank of mode N-1 above 32)
+    ((8, 7, 40), (3, 3, 20), 30, "c64"),             # ... (a last rank above 16)
+    ((6, 5, 4, 70), (3, 3, 2, 9), 90, "cbf16"),      # ... (a last extent above 68)
+    ((7, 3, 3), (3, 2, 2), 9, "c64"),                # ... last tile ragged: 21 rows x 3 elements, 3 after the whole pieces
+    ((32, 16, 32, 20), (4, 5, 20, 12), 900, "cbf16"),  # fused on 32-wide tiles, even last extent
+    ((32, 16, 32, 65), (4, 5, 32, 16), 9000, "c64"),   # ... the longest
     ((8, 7, 40), (2, 2, 36), 30, "c64"),             # generic kernels (last-mode rank above 32)
     ((5, 4, 3, 1), (2, 2, 2, 1), 3, "c64"),          # generic kernels (last extent 1)
     ((128, 40, 32, 17), (8, 6, 32, 12), 4000, "c64"),  # fused, last extent 17 (compile-time stage B)
@@ -274,7 +352,7 @@ def test_bf16_weights_ten_free_running_steps():
 # ------------------------------------------------------------------ composition orders
 ORDER_CASES = [
     # shape, ranks, k, gradient dtype                 kernel tier
-    ((16, 16, 8, 5), (8, 8, 4, 3), 103, "c64"),       # matrix-core, unfused
+    ((16, 16, 8, 5), (8, 8, 4, 3), 103, "c64"),       # fused
     ((16, 32, 32, 9), (4, 8, 8, 4), 300, "c64"),      # fused
     ((6, 5, 4, 3, 5), (2, 2, 2, 2, 2), 18, "cbf16"),  # five modes, half-precision gradients
     ((8, 7, 40), (2, 2, 36), 30, "c64"),              # generic last-mode kernels

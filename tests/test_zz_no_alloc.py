@@ -15,12 +15,14 @@ pytestmark = pytest.mark.gpu
 CASES = [
     # shape, ranks, k, gradient dtype, weights, order            kernel tier
     ((16, 32, 64, 5), (4, 8, 16, 2), 200, "c64", "c64", 0),       # fused
-    ((16, 16, 8, 5), (8, 8, 4, 3), 103, "c64", "c64", 0),         # matrix-core, unfused (the smaller input)
+    ((16, 16, 8, 5), (8, 8, 4, 3), 103, "c64", "c64", 0),         # fused (the smaller input)
 ]
 EXTRA = [
     ((12, 10, 9, 7), (3, 4, 2, 3), 60, "cbf16", "bf16", 0),       # half-precision gradients and weights
     ((8, 7, 40), (2, 2, 36), 30, "c64", "c64", 0),                # generic last-mode kernels (support bitmask)
     ((16, 32, 32, 9), (4, 8, 8, 4), 300, "c64", "c64", 1),        # low rank first, fused tier
+    ((32, 16, 32, 17), (4, 5, 20, 12), 900, "c64", "c64", 0),     # fused on 32-wide tiles: factor copies rebuilt in every call
+    ((9, 8, 40, 9), (3, 3, 36, 3), 300, "c64", "bf16", 2),        # separate kernels
     ((120, 70, 4, 3), (3, 4, 2, 2), 600, "c64", "c64", 0),        # 8400 slabs of 4 x 3: separate kernels
 ]
 ITEMS = [T.STATE_INDICES, T.STATE_CORE_M, T.STATE_CORE_V, T.STATE_SPARSE_M, T.STATE_SPARSE_V]
