@@ -1501,32 +1501,27 @@ void launch_lupdate_fused(hipStream_t s, const float2* y1, const float2* ut, int
                                     (int)(k > 0 ? k - 1 : 0));
   FusedPrev fz{y1, ut, S, K2};
   const int up = (M + 3) / 4 <= 5 ? 5 : (M + 3) / 4 <= 9 ? 9 : kUpdPrefetch;
-#define TGRAD_LUF_M(JT2_, UP_, MS_)                                                                      \
+  constexpr int kJT2 = 16;                     // (K2 in 17 .. 32: smaller ranks go to ends.hip)
+#define TGRAD_LUF_M(UP_, MS_)                                                                            \
   do {                                                                                                   \
     if (wdtype == TGRAD_C64) {                                                                           \
-      allow_lds(k_lupdate_fused<TGRAD_C64, W, MS_, JT2_, UP_>, lds);                                     \
-      grid.x = (unsigned)grid_for_tiles(ngroups, resident_blocks(k_lupdate_fused<TGRAD_C64, W, MS_, JT2_, UP_>, 64 * W, lds)); \
-      k_lupdate_fused<TGRAD_C64, W, MS_, JT2_, UP_><<<grid, block, lds, s>>>(U, A, K, M, ntiles, w, decay, c_alpha, sp, fz); \
+      allow_lds(k_lupdate_fused<TGRAD_C64, W, MS_, kJT2, UP_>, lds);                                     \
+      grid.x = (unsigned)grid_for_tiles(ngroups, resident_blocks(k_lupdate_fused<TGRAD_C64, W, MS_, kJT2, UP_>, 64 * W, lds)); \
+      k_lupdate_fused<TGRAD_C64, W, MS_, kJT2, UP_><<<grid, block, lds, s>>>(U, A, K, M, ntiles, w, decay, c_alpha, sp, fz); \
     } else {                                                                                             \
-      allow_lds(k_lupdate_fused<TGRAD_CBF16, W, MS_, JT2_, UP_>, lds);                                   \
-      grid.x = (unsigned)grid_for_tiles(ngroups, resident_blocks(k_lupdate_fused<TGRAD_CBF16, W, MS_, JT2_, UP_>, 64 * W, lds)); \
-      k_lupdate_fused<TGRAD_CBF16, W, MS_, JT2_, UP_><<<grid, block, lds, s>>>(U, A, K, M, ntiles, w, decay, c_alpha, sp, fz); \
+      allow_lds(k_lupdate_fused<TGRAD_CBF16, W, MS_, kJT2, UP_>, lds);                                   \
+      grid.x = (unsigned)grid_for_tiles(ngroups, resident_blocks(k_lupdate_fused<TGRAD_CBF16, W, MS_, kJT2, UP_>, 64 * W, lds)); \
+      k_lupdate_fused<TGRAD_CBF16, W, MS_, kJT2, UP_><<<grid, block, lds, s>>>(U, A, K, M, ntiles, w, decay, c_alpha, sp, fz); \
     }                                                                                                    \
   } while (0)
   // the half-spectrum extents of FNO layers (2^m + 1) get a stage B with the extent as a compile-time constant
-#define TGRAD_LUF_U(JT2_, UP_, MS_)                                                                      \
+#define TGRAD_LUF(UP_, MS_)                                                                              \
   do {                                                                                                   \
-    if (M == MS_) TGRAD_LUF_M(JT2_, UP_, MS_); else TGRAD_LUF_M(JT2_, UP_, 0);                           \
+    if (M == MS_) TGRAD_LUF_M(UP_, MS_); else TGRAD_LUF_M(UP_, 0);                                       \
   } while (0)
-#define TGRAD_LUF(JT2_)                                                                                  \
-  do {                                                                                                   \
-    if (up == 5) TGRAD_LUF_U(JT2_, 5, 17); else if (up == 9) TGRAD_LUF_U(JT2_, 9, 33);                   \
-    else TGRAD_LUF_U(JT2_, kUpdPrefetch, 65);                                                            \
-  } while (0)
-  TGRAD_LUF(16);                               // (K2 <= 16 goes to ends.hip)
-#undef TGRAD_LUF_U
-#undef TGRAD_LUF_M
+  if (up == 5) TGRAD_LUF(5, 17); else if (up == 9) TGRAD_LUF(9, 33); else TGRAD_LUF(kUpdPrefetch, 65);
 #undef TGRAD_LUF
+#undef TGRAD_LUF_M
 }
 
 }  // namespace tgrad

@@ -32,12 +32,6 @@ namespace tgrad {
 
 namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ v4f mfma16(float a, float b, v4f c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
 constexpr int kBatch = 8;                    // steps of y per lane in flight (twice that while a batch is computed)
@@ -115,26 +109,16 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
   const int64_t cidx = live ? ((int64_t)em0 * M1 + col) * a.Cc + plane : 0;
   const float2 mm = ad.m[cidx];
   const float vv = ad.v[cidx];
-  auto stage_table = [&](float2* dst, int n, auto gen) {      // 8 loads per thread in flight
-    for (int e0 = tid; e0 < n; e0 += kThreads * 8) {
-      float2 f[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) f[u] = gen(e0 + u * kThreads < n ? e0 + u * kThreads : e0);
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (e0 + u * kThreads < n) dst[e0 + u * kThreads] = f[u];
-    }
-  };
   // (sizes made scalar: a product that the compiler keeps in a vector register turns every load into a loop over the lanes)
   const FactorRef fU0 = factor_ref(a.U0, __builtin_amdgcn_readfirstlane(I0 * M0));
   const FactorRef fU1 = factor_ref(a.U1, __builtin_amdgcn_readfirstlane(I1 * M1));
   auto u1_at = [&](int i1, int m1) -> float2 { return factor_entry(fU1, i1, m1, M1, i1 < I1 && m1 < M1); };
   auto u0_at = [&](int i0, int m0) -> float2 { return factor_entry(fU0, i0, m0, M0, i0 < I0 && m0 < M0); };
-  stage_table(sT1, nA, [&](int e) -> float2 {                 // U1[4 j + g][c]
+  stage_table(sT1, nA, tid, kThreads, [&](int e) -> float2 {                 // U1[4 j + g][c]
     const int l = e & 63, j = e >> 6;
     return u1_at(4 * j + (l >> 4), l & 15);
   });
-  stage_table(sT4, nB, [&](int e) -> float2 {                 // U1[16 q + c][4 g + r]
+  stage_table(sT4, nB, tid, kThreads, [&](int e) -> float2 {                 // U1[16 q + c][4 g + r]
     const int l = e & 63, r = (e >> 6) & 3, q = e >> 8;
     return u1_at(16 * q + (l & 15), 4 * (l >> 4) + r);
   });

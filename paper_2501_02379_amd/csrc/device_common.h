@@ -63,6 +63,25 @@ __device__ __forceinline__ float2 factor_entry(const FactorRef& f, int row, int 
   return make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
 }
 
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ v4f mfma16(float a, float b, v4f c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// dst[0 .. n) = gen(e) by a workgroup, 8 loads per thread in flight
+template <typename Gen>
+__device__ __forceinline__ void stage_table(float2* dst, int n, int tid, int nthreads, Gen gen) {
+  for (int e0 = tid; e0 < n; e0 += nthreads * 8) {
+    float2 f[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) f[u] = gen(e0 + u * nthreads < n ? e0 + u * nthreads : e0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (e0 + u * nthreads < n) dst[e0 + u * nthreads] = f[u];
+  }
+}
+
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
 // Number of set bits of `b` strictly below this lane.

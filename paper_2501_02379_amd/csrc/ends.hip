@@ -32,30 +32,11 @@ namespace tgrad {
 
 namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ v4f mfma16(float a, float b, v4f c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
 constexpr int kMaxWaves = 4;
 
 // v of the neighbouring lane (c ^ 1): the other part of the same complex column
 __device__ __forceinline__ float swap_parts(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true));
-}
-
-// dst[0 .. n) = gen(e), 8 loads per thread in flight
-template <typename Gen>
-__device__ __forceinline__ void stage_table(float2* dst, int n, int tid, int nthreads, Gen gen) {
-  for (int e0 = tid; e0 < n; e0 += nthreads * 8) {
-    float2 f[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) f[u] = gen(e0 + u * nthreads < n ? e0 + u * nthreads : e0);
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (e0 + u * nthreads < n) dst[e0 + u * nthreads] = f[u];
-  }
 }
 
 // ---- k_head -------------------------------------------------------------------------------------
@@ -675,8 +656,8 @@ int end_tile_rows(int K) { return K <= 33 ? 32 : 16; }
 // Slabs of fewer than four rows would leave seven eighths of every tile empty (and need a support offset for every few
 // entries): they stay with the kernels that cut the tensor into tiles of 32 rows wherever a slab ends.
 // (With both ranks in the upper half of a 32-wide tile, whole 32-row tiles and at least 512 slabs the 32 x 32 kernels are
-// the better ones - make_plan prefers them: whole step 128x128x128x65, r 32,32,32,16: 747 us against 787 with these;
-// 128x128x64x33, r 64,64,32,16: 413 against 431.)
+// the better ones - make_plan prefers them: whole step 128x128x128x65, r 32,32,32,16: 738 us against 758 with these;
+// 128x128x64x33, r 64,64,32,16: 351 against 377, r 32,32,17,9: 245 against 273.)
 bool ends_kernel_fits(int K, int r, int I2, int r2) {
   if (K < 2 || K > 68 || r > 16 || r2 > 32 || I2 < 4 || I2 > TGRAD_MAX_EXTENT) return false;
   return head_lds(kMaxWaves, K, I2, r2) <= kLdsLimit / 2 && tail_lds(kMaxWaves, K, I2, r2) <= kLdsLimit / 2;

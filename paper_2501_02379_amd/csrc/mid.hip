@@ -22,12 +22,6 @@ namespace tgrad {
 
 namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ v4f mfma16(float a, float b, v4f c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
 template <int VEC> struct ColVec;
 template <> struct ColVec<1> { typedef float2 type; };
 template <> struct ColVec<2> { typedef float4 type; };
@@ -69,19 +63,6 @@ __device__ __forceinline__ float2 factor_at(const FactorRef& U, int rn, int m, i
 constexpr int kThreads = 256, kWaves = 4;
 constexpr int kBatch = 8;                 // steps (4 rows each) of x per lane in flight
 constexpr int kChunk = 32;                // steps of the factor staged in LDS at a time
-
-// dst[0 .. n) = gen(e), 8 loads per thread in flight
-template <typename Gen>
-__device__ __forceinline__ void stage_table(float2* dst, int n, int tid, Gen gen) {
-  for (int e0 = tid; e0 < n; e0 += kThreads * 8) {
-    float2 f[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) f[u] = gen(e0 + u * kThreads < n ? e0 + u * kThreads : e0);
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (e0 + u * kThreads < n) dst[e0 + u * kThreads] = f[u];
-  }
-}
 
 // The 16 column vectors of a wavefront: group `cg` of 16, lane column c; lanes past the end work on the
 // last column and store nothing.
@@ -196,7 +177,7 @@ __global__ __launch_bounds__(kThreads) void k_mid(const float* __restrict__ x, c
       for (int u = 0; u < kBatch; ++u) cur[u] = load_x(jc0 + u);
       __syncthreads();                                  // previous chunk fully consumed
       const FactorRef U = factor_from(jc0);
-      stage_table(sF, jn * MT * 64, tid, [&](int e) -> float2 {
+      stage_table(sF, jn * MT * 64, tid, kThreads, [&](int e) -> float2 {
         const int l = e & 63, t = (e >> 6) % MT, j = (e >> 6) / MT;
         return factor_in(U, jc0, mbase + 16 * t + (l & 15), 4 * (jc0 + j) + (l >> 4));
       });
@@ -288,7 +269,7 @@ __global__ __launch_bounds__(kThreads) void k_expand(const float* __restrict__ x
   } else {
     const int q0 = blockIdx.y * tiles, Q = (M + 15) >> 4;
     const int nq = Q - q0 < tiles ? Q - q0 : tiles;
-    stage_table(sF, nq * KS * 64, tid, [&](int e) -> float2 {
+    stage_table(sF, nq * KS * 64, tid, kThreads, [&](int e) -> float2 {
       const int l = e & 63, j = (e >> 6) % KS, q = (e >> 6) / KS;
       return factor_at<false>(U, rn, 16 * (q0 + q) + (l & 15), 4 * j + (l >> 4), M, K);
     });

@@ -79,8 +79,6 @@ void launch_gram_batch(hipStream_t s, int njobs, const void* g, int dtype, const
                        const int* In, const int64_t* B, const int* nchunks, double* const* partials);
 void launch_gram_reduce(hipStream_t s, int njobs, const int* In, const int* nchunks, double* const* partials,
                         double* const* gram);
-void launch_eig(hipStream_t s, const double* gram, double* work_a, double* work_v, int In, int r,
-                float* U);
 
 // step
 void launch_gather(hipStream_t s, const void* g, int dtype, const int32_t* omega, int64_t k,
