@@ -474,6 +474,14 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(const float* x, const flo
 // 90x77x66: 6.8 us shared, where 93 workgroups of one group per wavefront would leave 163 compute units idle).
 constexpr int64_t kOwnColumns = 1024;
 
+// k_expand's KS: steps of four rows of x, rounded up to the next variant.  Padded to 4, 8 or 16 steps a rank of a few was
+// matrix work for nothing: 12M columns of one row 284 us, now 105; 3M from 2 rows to 4 78, now 34; 500000 from 20 to 24 43,
+// now 36.
+static int expand_steps(int K) {
+  const int j = (K + 3) / 4;
+  return j <= 6 ? j : j <= 8 ? 8 : j <= 10 ? 10 : j <= 12 ? 12 : 16;
+}
+
 void launch_mid(hipStream_t s, const float2* x, const float2* U, int rn, bool project, const Stage& st,
                 float2* out) {
   const int64_t A = st.A, B = st.B;
@@ -489,7 +497,7 @@ void launch_mid(hipStream_t s, const float2* x, const float2* U, int rn, bool pr
   const dim3 block(kThreads);
   const int Q = (M + 15) / 16;
   if (!project && K <= 64) {
-    const int ks = K <= 16 ? 4 : K <= 32 ? 8 : 16;
+    const int ks = expand_steps(K);
     const int tiles = own ? (Q < 64 / ks * 2 ? Q : 64 / ks * 2) : 1;          // operands of `tiles` tiles: at most 64 KB
     const size_t lds = own ? (size_t)tiles * ks * 512 : 0;
     const dim3 grid((unsigned)(own ? (groups + kWaves - 1) / kWaves : groups),
@@ -501,7 +509,18 @@ void launch_mid(hipStream_t s, const float2* x, const float2* U, int rn, bool pr
   } while (0)
 #define TGRAD_EX_K(V_, S_)                                                                           \
   do {                                                                                               \
-    if (ks == 4) TGRAD_EX(V_, 4, S_); else if (ks == 8) TGRAD_EX(V_, 8, S_); else TGRAD_EX(V_, 16, S_); \
+    switch (ks) {                                                                                    \
+      case 1: TGRAD_EX(V_, 1, S_); break;                                                            \
+      case 2: TGRAD_EX(V_, 2, S_); break;                                                            \
+      case 3: TGRAD_EX(V_, 3, S_); break;                                                            \
+      case 4: TGRAD_EX(V_, 4, S_); break;                                                            \
+      case 5: TGRAD_EX(V_, 5, S_); break;                                                            \
+      case 6: TGRAD_EX(V_, 6, S_); break;                                                            \
+      case 8: TGRAD_EX(V_, 8, S_); break;                                                            \
+      case 10: TGRAD_EX(V_, 10, S_); break;                                                          \
+      case 12: TGRAD_EX(V_, 12, S_); break;                                                          \
+      default: TGRAD_EX(V_, 16, S_); break;                                                          \
+    }                                                                                                \
   } while (0)
     if (vec == 2) TGRAD_EX_K(2, false);
     else if (own) TGRAD_EX_K(1, false);

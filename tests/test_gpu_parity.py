@@ -245,6 +245,22 @@ def test_core_kernel_extents_and_ranks(shape, ranks, k):
     assert _launches(times, "adam_core") == (0 if ranks[0] <= 64 else 1)
 
 
+@pytest.mark.parametrize("rank", [2, 7, 12, 16, 19, 23, 31, 37, 45, 60])
+def test_middle_expansion_ranks(rank):
+    """k_expand's variants by rank (1 ... 6, 8, 10, 12 and 16 steps of four), each with a group of columns per wavefront
+    - pairs of columns (96 x 360) or single ones (96 x 351) - and with the wavefronts sharing one (20 x 54)."""
+    for first, tail in ((96, (40, 9)), (96, (39, 9)), (20, (6, 9))):
+        shape, ranks = (first, rank + 3) + tail, (4, rank) + tail
+        _announce("expansion", shape, ranks)
+        grads = [synth.small_case(shape, 560 + t) for t in range(2)]
+        rng = np.random.default_rng(18)
+        W0 = ((rng.standard_normal(shape) + 1j * rng.standard_normal(shape)) * 0.02).astype(np.complex64)
+        info = run_both(T, shape, ranks, 200, grads, W0, refresh_every=4, lr=2e-3, weight_decay=0.01)
+        assert all(info["omega_equal"])
+        check_parity(info, W0)
+        info["ctx"].tgrad_destroy()
+
+
 CORE2_SHAPES = [                                              # both leading modes and AdamUpdate in one launch?
     ((128, 40, 32, 13), (8, 6, 32, 12), 4000, "us_lr"),      # no: 5120 pairs of leading indices, 384 columns
     ((128, 41, 32, 13), (32, 32, 32, 12), 4000, "us_lr"),    # no
