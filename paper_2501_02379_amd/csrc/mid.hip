@@ -289,11 +289,13 @@ __global__ __launch_bounds__(kThreads) void k_expand(const float* __restrict__ x
 //   z[i, b]   = sum_m U[i, m] N_L[m, b]                 first reconstruction stage
 // so the core gradient and the core update never travel through memory between kernels (g_L is
 // still written out: it is part of the readable state).
-// A workgroup of 8 wavefronts owns 16 columns.  Wavefront w contracts the steps of rows w, w + 8, .. (4 rows
+// A workgroup of W = 8 wavefronts owns 16 columns (4 where the rank takes more than one tile and the extent fits them, up
+// to 64 rows: half of the partial tiles, so twice the workgroups per compute unit; 23 rows, rank 17, 340000 columns 211 us
+// with 8, 141 with 4; 64 rows, rank 32, 100 columns 6.3 and 5.9; 44 rows, rank 33, 20000 columns 27 and 24).  Wavefront w contracts the steps of rows w, w + W, .. (4 rows
 // each); the partial tiles are summed through LDS in a fixed order; AdamUpdate is spread over all threads
 // and leaves N_L in LDS in accumulator layout, which IS the B operand layout of the expansion (register r
 // of D holds rows 4 g + r: step r contracts exactly those); wavefront w then expands the output tiles
-// w, w + 8, ...  Every operand goes from memory straight into the registers of the one wavefront that
+// w, w + W, ...  Every operand goes from memory straight into the registers of the one wavefront that
 // uses it, and all of them (x, both factor operands, moments) are requested up front: one memory
 // round trip, three barriers.
 // A workgroup stays for several groups of columns where there are more of them than the chip holds: the factor operands
@@ -307,22 +309,23 @@ struct CoreAdam {
   float2* g_out;        // compressed gradient, written for the state accessors
   float beta1, beta2, inv_c1, inv_c2, eps;
 };
-constexpr int kCoreThreads = 512, kCoreWaves = 8;
-constexpr int kCoreSteps = 4;             // steps of x per wavefront in flight: all of them for K <= 128
+constexpr int kCoreSteps = 4;             // steps of x per wavefront in flight: all of them for K <= 16 waves
 
-template <int MT>
-__global__ __launch_bounds__(kCoreThreads) void k_core(const float* x, const float2* __restrict__ Up, int rn, int K,
+// MT: tiles of 16 that hold the rank; W: wavefronts of a workgroup
+template <int MT, int W>
+__global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* __restrict__ Up, int rn, int K,
                                                        int M, int64_t B, int groups, CoreAdam ad, float* z) {
   extern __shared__ float2 sF[];
   const FactorRef U = factor_ref(Up, (int64_t)K * rn);
+  constexpr int kThr = 64 * W;
   constexpr int kPart = MT * 2 * 4 * 64;        // floats of one wavefront's partial tiles
-  constexpr int kArea = kCoreWaves * kPart;     // [wave][tile][re / im][r][lane]; two of them take turns
+  constexpr int kArea = W * kPart;     // [wave][tile][re / im][r][lane]; two of them take turns
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, grp = lane >> 4;
   const int64_t row = B * 2;
   const int J = (K + 3) >> 2, Q = (K + 15) >> 4;
-  const bool once = J <= kCoreWaves * kCoreSteps;              // (K <= 128) one batch of steps, one output tile each
+  const bool once = J <= W * kCoreSteps;                       // (K <= 16 W) one batch of steps, one output tile each
   // operands of the compression: steps wave + 8 (s0 + u); past the end: zero coefficients
   float2 xv[kCoreSteps], fc[kCoreSteps][MT];
   auto fetch_x = [&](int g, int s0) {
@@ -330,24 +333,24 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(const float* x, const flo
     const float* xp = x + (b_raw < B ? b_raw : B - 1) * 2;
 #pragma unroll
     for (int u = 0; u < kCoreSteps; ++u) {
-      const int k = 4 * (wave + kCoreWaves * (s0 + u)) + grp;
+      const int k = 4 * (wave + W * (s0 + u)) + grp;
       xv[u] = *reinterpret_cast<const float2*>(xp + (int64_t)(k < K ? k : K - 1) * row);
     }
   };
   auto fetch_in = [&](int s0) {
 #pragma unroll
     for (int u = 0; u < kCoreSteps; ++u) {
-      const int k = 4 * (wave + kCoreWaves * (s0 + u)) + grp;
+      const int k = 4 * (wave + W * (s0 + u)) + grp;
 #pragma unroll
       for (int t = 0; t < MT; ++t) fc[u][t] = factor_at<true>(U, rn, 16 * t + col, k, M, K);
     }
   };
   // moments of this thread's core entries
-  constexpr int kEnt = (MT * 256 + kCoreThreads - 1) / kCoreThreads;
+  constexpr int kEnt = (MT * 256 + kThr - 1) / kThr;
   float2 mm[kEnt];
   float vv[kEnt];
   auto entry = [&](int g, int q, int64_t& idx) -> bool {
-    const int e = tid + q * kCoreThreads;
+    const int e = tid + q * kThr;
     const int l = e & 63, r = (e >> 6) & 3, t = e >> 8;
     const int m = 16 * t + 4 * (l >> 4) + r;
     const int64_t bb = (int64_t)g * 16 + (l & 15);
@@ -390,7 +393,7 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(const float* x, const flo
 #pragma unroll
         for (int t = 0; t < MT; ++t) cmac<1>(acc[t], fc[u][t], xs);
       }
-      if (kCoreWaves * (s0 + kCoreSteps) >= J) break;          // (the same for every wavefront)
+      if (W * (s0 + kCoreSteps) >= J) break;          // (the same for every wavefront)
       fetch_x(g, s0 + kCoreSteps);
       fetch_in(s0 + kCoreSteps);
     }
@@ -409,14 +412,14 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(const float* x, const flo
     // AdamUpdate; N_L replaces wavefront 0's partial sums (each entry is read and written by one thread)
 #pragma unroll
     for (int q = 0; q < kEnt; ++q) {
-      const int e = tid + q * kCoreThreads;
+      const int e = tid + q * kThr;
       const int l = e & 63, r = (e >> 6) & 3, t = e >> 8;
-      if (MT * 256 % kCoreThreads == 0 || t < MT) {
+      if (MT * 256 % kThr == 0 || t < MT) {
         float* pr = red + (t * 8 + r) * 64 + l;
         float* pi = pr + 256;
         float gre = 0.f, gim = 0.f;
 #pragma unroll
-        for (int w = 0; w < kCoreWaves; ++w) {
+        for (int w = 0; w < W; ++w) {
           gre += pr[w * kPart];
           gim += pi[w * kPart];
         }
@@ -443,7 +446,7 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(const float* x, const flo
     // expansion
     const int64_t b = (int64_t)g * 16 + col;
     float* op = z + b * 2;
-    for (int q = wave; q < Q; q += kCoreWaves) {
+    for (int q = wave; q < Q; q += W) {
       if (!once && (q != wave || it > 0)) fetch_out(q);
       v4f o[2];
       o[0] = o[1] = (v4f){0.f, 0.f, 0.f, 0.f};
@@ -566,16 +569,18 @@ void launch_core(hipStream_t s, const float2* x, const float2* U, int rn, int K,
   const float* xf = reinterpret_cast<const float*>(x);
   float* zf = reinterpret_cast<float*>(z);
   const int64_t groups = (B + 15) / 16;
-  const dim3 block(kCoreThreads);
-  const int mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
-  const size_t lds = (size_t)2 * kCoreWaves * mt * 2048;
-#define TGRAD_CORE(MT_)                                                                                      \
+#define TGRAD_CORE(MT_, W_)                                                                                  \
   do {                                                                                                       \
-    allow_lds(k_core<MT_>, lds);                                                                             \
-    const int64_t cap = (int64_t)compute_units() * resident_blocks(k_core<MT_>, kCoreThreads, lds);          \
-    k_core<MT_><<<dim3((unsigned)(groups < cap ? groups : cap)), block, lds, s>>>(xf, U, rn, K, M, B, (int)groups, ad, zf); \
+    const size_t lds = (size_t)2 * W_ * MT_ * 2048;                                                          \
+    allow_lds(k_core<MT_, W_>, lds);                                                                         \
+    const int64_t cap = (int64_t)compute_units() * resident_blocks(k_core<MT_, W_>, 64 * W_, lds);           \
+    k_core<MT_, W_><<<dim3((unsigned)(groups < cap ? groups : cap)), dim3(64 * W_), lds, s>>>(xf, U, rn, K, M, B, (int)groups, ad, zf); \
   } while (0)
-  if (mt == 1) TGRAD_CORE(1); else if (mt == 2) TGRAD_CORE(2); else TGRAD_CORE(4);
+  if (M <= 16) TGRAD_CORE(1, 8);
+  else if (M <= 32 && K <= 64) TGRAD_CORE(2, 4);
+  else if (M <= 32) TGRAD_CORE(2, 8);
+  else if (K <= 64) TGRAD_CORE(4, 4);
+  else TGRAD_CORE(4, 8);
 #undef TGRAD_CORE
 }
 

@@ -222,6 +222,10 @@ CORE_SHAPES = [                                            # first extent and ra
     ((256, 10, 9, 8), (20, 5, 4, 3), 900),                 # two tiles of rank, two output tiles for every wavefront
     ((150, 17, 9, 8), (9, 5, 4, 3), 900),                  # one tile of rank
     ((130, 46, 23, 17), (40, 23, 23, 17), 20000),          # 8993 columns: 563 groups, three for some of 256 workgroups
+    ((40, 41, 9, 8), (17, 7, 4, 3), 900),                  # two tiles of rank, four wavefronts
+    ((64, 12, 9, 8), (32, 5, 4, 3), 900),                  # ... the longest, full tiles
+    ((65, 12, 9, 8), (32, 5, 4, 3), 900),                  # ... eight wavefronts again
+    ((24, 40, 40, 23), (20, 40, 40, 23), 9000),            # 36800 columns: 2300 groups, three for some of 1024 workgroups
     ((80, 9, 9, 8), (66, 5, 4, 3), 900),                   # a rank beyond k_core: three kernels
 ]
 
