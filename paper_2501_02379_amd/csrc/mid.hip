@@ -557,7 +557,18 @@ void launch_mid(hipStream_t s, const float2* x, const float2* U, int rn, bool pr
 #undef TGRAD_MID
 }
 
-bool core_kernel_fits(int K, int M) { return M >= 1 && M <= 64 && K >= 1 && K <= TGRAD_MAX_EXTENT; }
+// Where mode 1 (extent K, rank M) and the core's B columns are one launch.  Up to two tiles of rank it always is the better
+// one.  Three or four tiles put one or two workgroups on a compute unit, and from some number of columns on the
+// separate k_mid, k_adam_core and k_expand, which stream, are: the more matrix work per column, the later (they repeat
+// none of it, but move the core twice more).  Three kernels / one, us:
+//   33 rows, rank 33: 20000 columns 23 / 24, 80000 60 / 82, 220000 139 / 212;    56, 44: 50000 58 / 57, 80000 79 / 85;
+//   64, 64: 20000 41 / 28, 80000 100 / 91, 120000 140 / 141;                     72, 52: 40000 68 / 63, 65000 79 / 97;
+//   128, 64: 30000 69 / 54, 120000 222 / 212;  96, 33: 40000 58 / 59, 120000 131 / 165;
+//   200, 64 (operands fetched per group): 20000 82 / 75, 30000 98 / 117;  160, 33: 10000 28 / 36.
+bool core_kernel_fits(int K, int M, int64_t B) {
+  if (M > 64 || K > TGRAD_MAX_EXTENT) return false;
+  return M <= 32 || B <= (int64_t)K * M * (K <= 64 ? 24 : K <= 128 ? 14 : 2);
+}
 
 // Last compression stage + AdamUpdate on the core + first reconstruction stage (mode 1: the tensor
 // before is (K, B), the tensor after is (K, B) again, the core in between (M, B)).

@@ -210,7 +210,7 @@ void make_plan(const tgrad_config* c, bool short_slabs_fused, Plan* p) {
       }
     }
     p->fuse_next = wide || p->narrow;
-    p->fuse_core = core_kernel_fits((int)p->shape[0], p->rank[0]);
+    p->fuse_core = core_kernel_fits((int)p->shape[0], p->rank[0], p->C / p->rank[0]);
     if (N >= 3 && !(p->fuse_next && N == 3)) {  // (N = 3 with the fused end kernels leaves one mode: k_core)
       int64_t cc = 1;
       for (int m = 2; m < N; ++m) cc *= p->rank[m];

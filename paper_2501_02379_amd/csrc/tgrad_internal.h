@@ -106,7 +106,7 @@ void launch_tile_offsets(hipStream_t s, const int32_t* omega, int64_t k, int64_t
                          int64_t slab_elems, int64_t ntiles, uint32_t* tile_start);
 void launch_mid(hipStream_t s, const float2* x, const float2* U, int rn, bool project, const Stage& st,
                 float2* out);
-bool core_kernel_fits(int K, int M);
+bool core_kernel_fits(int K, int M, int64_t B);
 void launch_core(hipStream_t s, const float2* x, const float2* U, int rn, int K, int M, int64_t B, float2* m,
                  float* v, float2* g_out, float beta1, float beta2, float inv_c1, float inv_c2, float eps,
                  float2* z);
