@@ -326,7 +326,7 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
   const int64_t row = B * 2;
   const int J = (K + 3) >> 2, Q = (K + 15) >> 4;
   const bool once = J <= W * kCoreSteps;                       // (K <= 16 W) one batch of steps, one output tile each
-  // operands of the compression: steps wave + 8 (s0 + u); past the end: zero coefficients
+  // operands of the compression: steps wave + W (s0 + u); past the end: zero coefficients
   float2 xv[kCoreSteps], fc[kCoreSteps][MT];
   auto fetch_x = [&](int g, int s0) {
     const int64_t b_raw = (int64_t)g * 16 + col;
