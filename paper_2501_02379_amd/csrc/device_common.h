@@ -69,6 +69,120 @@ __device__ __forceinline__ v4f mfma16(float a, float b, v4f c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// ---- float32 products on the bf16 matrix instructions -------------------------------------------
+// x = h + m + l with h = bf16(x), m = bf16(x - h), l = bf16(x - h - m): three times 8 bits hold all 24 of a float32,
+// and a x b = hh + hm + mh + hl + lh + mm leaves out products below 2^-25 of it.  Six v_mfma_f32_16x16x32_bf16 do the
+// work of eight v_mfma_f32_16x16x4f32 in 96 cycles instead of 256, and, unlike those, beside vector instructions of
+// another wavefront.  They add 32 products per rounding instead of 4, so sums come out closer to 64 bits than before:
+// relative error of a sum of K products of normal numbers, float32 instructions / these: K = 32 1.0e-7 / 3.7e-8,
+// 128 2.0e-7 / 1.5e-7 (6.4e-8 with the five small terms summed apart), 1024 5.7e-7 / 4.9e-7.
+// Parts of numbers below 2^-110 are subnormal in bf16 and may be lost; an infinity becomes NaN (inf - inf).
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32v4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32v2 __attribute__((ext_vector_type(2)));
+
+// Two float32 -> bf16 pairs (first in the low half), rounded to nearest, ties to even, NaN to a quiet NaN: one
+// v_cvt_pk_bf16_f32.  (In integer arithmetic it was 14 vector instructions per pair, and with bf16 weights those
+// bounded the update: k_tail at 128x128x64x33 81 us, now 66.)
+__device__ __forceinline__ uint32_t bf16_pack(float re, float im) {
+  f32x2 v;
+  v.x = re;
+  v.y = im;
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
+// Eight real numbers of a lane as an operand: four dwords of two neighbouring numbers, for each of the three parts.
+struct Split8 {
+  u32v4 h, m, l;
+};
+// One dword of each part from a pair of numbers.  x - h is exact, and one v_dot2c_f32_bf16 per number: dot2(h, (-1, 0), x).
+// (The constants are kept in registers: as an inline constant of the instruction, (-1, 0) would be read as a float32.)
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
+  uint32_t lo = 0x0000BF80u, hi = 0xBF800000u;
+  asm("" : "+s"(lo), "+s"(hi));
+  const bf16x2 n0 = __builtin_bit_cast(bf16x2, lo), n1 = __builtin_bit_cast(bf16x2, hi);
+  h = bf16_pack(a, b);
+  const bf16x2 hv = __builtin_bit_cast(bf16x2, h);
+  a = __builtin_amdgcn_fdot2_f32_bf16(hv, n0, a, false);
+  b = __builtin_amdgcn_fdot2_f32_bf16(hv, n1, b, false);
+  m = bf16_pack(a, b);
+  const bf16x2 mv = __builtin_bit_cast(bf16x2, m);
+  a = __builtin_amdgcn_fdot2_f32_bf16(mv, n0, a, false);
+  b = __builtin_amdgcn_fdot2_f32_bf16(mv, n1, b, false);
+  l = bf16_pack(a, b);
+}
+__device__ __forceinline__ void split_at(Split8& s, int d, float2 v) {   // numbers 2 d, 2 d + 1
+  uint32_t h, m, l;
+  split_pair(v.x, v.y, h, m, l);
+  s.h[d] = h;
+  s.m[d] = m;
+  s.l[d] = l;
+}
+// (re, im) pairs -> (im, re), and -> (re, -im): the second operands of a complex product
+__device__ __forceinline__ u32v4 swap_pairs(u32v4 v) {
+#pragma unroll
+  for (int d = 0; d < 4; ++d) v[d] = __builtin_amdgcn_alignbit(v[d], v[d], 16);
+  return v;
+}
+__device__ __forceinline__ u32v4 conj_pairs(u32v4 v) { return v ^ 0x80000000u; }
+__device__ __forceinline__ Split8 swap_pairs(const Split8& s) { return Split8{swap_pairs(s.h), swap_pairs(s.m), swap_pairs(s.l)}; }
+__device__ __forceinline__ Split8 conj_pairs(const Split8& s) { return Split8{conj_pairs(s.h), conj_pairs(s.m), conj_pairs(s.l)}; }
+
+// D[i = 4 g + r][j = c] += sum over the 32 slots (g, s): A[c][(g, s)] B[(g, s)][c]; which index of the sum a slot stands
+// for is the caller's choice, the same for both operands.
+__device__ __forceinline__ v4f mfma_bf(u32v4 a, u32v4 b, v4f c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+// N independent products with the same A: the six terms, smallest first
+template <int N>
+__device__ __forceinline__ void mfma_split(v4f* acc, const Split8& a, const Split8* b) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) acc[i] = mfma_bf(a.l, b[i].h, acc[i]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) acc[i] = mfma_bf(a.h, b[i].l, acc[i]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) acc[i] = mfma_bf(a.m, b[i].m, acc[i]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) acc[i] = mfma_bf(a.m, b[i].h, acc[i]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) acc[i] = mfma_bf(a.h, b[i].m, acc[i]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) acc[i] = mfma_bf(a.h, b[i].h, acc[i]);
+}
+
+// ... with the same B
+template <int N>
+__device__ __forceinline__ void mfma_split_b(v4f* acc, const Split8* a, const Split8& b) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) acc[i] = mfma_bf(a[i].l, b.h, acc[i]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) acc[i] = mfma_bf(a[i].h, b.l, acc[i]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) acc[i] = mfma_bf(a[i].m, b.m, acc[i]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) acc[i] = mfma_bf(a[i].m, b.h, acc[i]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) acc[i] = mfma_bf(a[i].h, b.m, acc[i]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) acc[i] = mfma_bf(a[i].h, b.h, acc[i]);
+}
+// One product over 16 slots (dwords 0 and 1 of the operands)
+__device__ __forceinline__ v4f mfma_bf_half(u32v4 a, u32v4 b, v4f c) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  const u32v2 al = {a.x, a.y}, bl = {b.x, b.y};
+  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, al), __builtin_bit_cast(s16x4, bl), c, 0, 0, 0);
+}
+__device__ __forceinline__ void mfma_split_half(v4f& acc, const Split8& a, const Split8& b) {
+  acc = mfma_bf_half(a.l, b.h, acc);
+  acc = mfma_bf_half(a.h, b.l, acc);
+  acc = mfma_bf_half(a.m, b.m, acc);
+  acc = mfma_bf_half(a.m, b.h, acc);
+  acc = mfma_bf_half(a.h, b.m, acc);
+  acc = mfma_bf_half(a.h, b.h, acc);
+}
+
 // dst[0 .. n) = gen(e) by a workgroup, 8 loads per thread in flight
 template <typename Gen>
 __device__ __forceinline__ void stage_table(float2* dst, int n, int tid, int nthreads, Gen gen) {

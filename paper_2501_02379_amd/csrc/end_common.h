@@ -106,18 +106,6 @@ __device__ __forceinline__ void sparse_adam_entry(const SparseAdam& sp, uint32_t
   sD[2 * e + 1] += d * mm.y;
 }
 
-// Two float32 -> bf16 pairs (re in the low half), rounded to nearest, ties to even, NaN to a quiet NaN: one
-// v_cvt_pk_bf16_f32.  (In integer arithmetic it was 14 vector instructions per pair, and with bf16 weights those
-// bounded the update: k_tail at 128x128x64x33 81 us, now 66.)
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t bf16_pack(float re, float im) {
-  f32x2 v;
-  v.x = re;
-  v.y = im;
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-
 // How the weight tensor is stored (section "Mixed precision training": weights may be kept in half
 // precision while the optimizer states stay in full precision).  A "piece" is 16 bytes of the W tile:
 // 2 complex64 elements, or 4 elements stored as bf16 (re, im) pairs.  apply() returns

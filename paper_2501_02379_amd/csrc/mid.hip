@@ -281,6 +281,172 @@ __global__ __launch_bounds__(kThreads) void k_expand(const float* __restrict__ x
   }
 }
 
+// ---- the same two for tensors that fill the chip, on split bf16 operands ---------------------------
+// A quad is 16 rows k of the contraction: slot 2 j + part of lane (c, g) is part `part` of row 16 quad + 4 j + g.
+// A operand: (Fr, Fi) of 16 output rows, from the table in LDS [quad][tile][h, m, l][lane]; B operands from one
+// split of the column's (xr, xi): (xr, -xi) gives the real part of F x, (xi, xr) the imaginary part.
+constexpr int kSplitItem = 3 * 64;        // u32v4 of one quad and tile of the table
+constexpr int kChunkQuads = 8;            // quads staged at a time: 96 KB with four tiles
+
+// table[(quad - q0) * tiles + tile] for quads q0 .. q0 + nq and output rows m0 .. m0 + 16 tiles
+template <bool PROJECT>
+__device__ __forceinline__ void stage_split(u32v4* table, const float2* Up, int rn, int M, int K, int m0, int tiles,
+                                            int q0, int nq, int tid, int nthreads) {
+  // (a full rank of an extent above 16384 does not fit one buffer: the buffer starts at the first row that is needed)
+  const int64_t skip = PROJECT ? (int64_t)16 * q0 * rn : (int64_t)m0 * rn;
+  const FactorRef U = factor_ref(Up + skip, (int64_t)(PROJECT ? K : M) * rn - skip);
+  const int n = nq * tiles * 64;
+  for (int e = tid; e < n; e += nthreads) {
+    const int l = e & 63, it = e >> 6, t = it % tiles, q = it / tiles;
+    const int m = 16 * t + (l & 15), k = 16 * q + (l >> 4);              // from m0 and 16 q0
+    float2 f[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool in = m0 + m < M && 16 * q0 + k + 4 * j < K;
+      f[j] = PROJECT ? factor_entry(U, k + 4 * j, m0 + m, rn, in) : factor_entry(U, m, 16 * q0 + k + 4 * j, rn, in);
+      if (PROJECT) f[j].y = -f[j].y;
+    }
+    Split8 s;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) split_at(s, j, f[j]);
+    u32v4* d = table + it * kSplitItem + l;
+    d[0] = s.h;
+    d[64] = s.m;
+    d[128] = s.l;
+  }
+}
+__device__ __forceinline__ Split8 split_item(const u32v4* p) { return Split8{p[0], p[64], p[128]}; }
+
+// The operands of the VEC columns of four row vectors of a lane: [column][re, im]
+template <int VEC>
+__device__ __forceinline__ void split_rows(const typename ColVec<VEC>::type* v, Split8* b) {
+  Split8 s[VEC];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float x[2 * VEC];
+    parts<VEC>(v[j], x);
+#pragma unroll
+    for (int c = 0; c < VEC; ++c) split_at(s[c], j, make_float2(x[2 * c], x[2 * c + 1]));
+  }
+#pragma unroll
+  for (int c = 0; c < VEC; ++c) {
+    b[2 * c] = conj_pairs(s[c]);
+    b[2 * c + 1] = swap_pairs(s[c]);
+  }
+}
+
+template <int VEC, int MT, bool PROJECT, int W>
+__global__ __launch_bounds__(64 * W) void k_mid_split(const float* __restrict__ x, const float2* __restrict__ Up, int rn,
+                                                      uint32_t ncv, uint32_t BV, int K, int M, int groups,
+                                                      float* __restrict__ out) {
+  typedef typename ColVec<VEC>::type V;
+  extern __shared__ u32v4 sQ[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 15, grp = lane >> 4;
+  const int64_t row = (int64_t)BV * VEC * 2;
+  const int m0 = blockIdx.y * (16 * MT), Q = (K + 15) >> 4;
+  const bool whole = Q <= kChunkQuads;                  // the table holds the whole factor
+  for (int g0 = (int)blockIdx.x * W; g0 < groups; g0 += (int)gridDim.x * W) {   // (the same trips for every wavefront)
+    const Cols cq = columns_of((uint32_t)(g0 + wave), col, ncv, BV);
+    const float* xp = x + (int64_t)cq.a * K * row + (int64_t)cq.b * VEC * 2;
+    auto load_x = [&](int k) -> V { return *reinterpret_cast<const V*>(xp + (int64_t)(k < K ? k : K - 1) * row); };
+    V nxt[4];
+    auto fetch = [&](int q) {                           // rows past K meet zero factor entries
+#pragma unroll
+      for (int j = 0; j < 4; ++j) nxt[j] = load_x(16 * q + 4 * j + grp);
+    };
+    fetch(0);
+    v4f acc[MT][2 * VEC];
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int i = 0; i < 2 * VEC; ++i) acc[t][i] = (v4f){0.f, 0.f, 0.f, 0.f};
+    for (int q0 = 0; q0 < Q; q0 += kChunkQuads) {
+      const int nq = Q - q0 < kChunkQuads ? Q - q0 : kChunkQuads;
+      if (!whole || g0 == (int)blockIdx.x * W) {
+        __syncthreads();                                // the chunk before is consumed
+        stage_split<PROJECT>(sQ, Up, rn, M, K, m0, MT, q0, nq, tid, 64 * W);
+        __syncthreads();
+      }
+      for (int q = 0; q < nq; ++q) {
+        Split8 b[2 * VEC];
+        split_rows<VEC>(nxt, b);
+        fetch(q0 + q + 1);
+        __builtin_amdgcn_sched_barrier(0);              // the loads stay in front of the quad they overlap
+        const u32v4* ft = sQ + q * MT * kSplitItem + lane;
+#pragma unroll
+        for (int t = 0; t < MT; ++t) mfma_split<2 * VEC>(acc[t], split_item(ft + t * kSplitItem), b);
+      }
+    }
+    if (cq.valid) {
+      float* op = out + ((int64_t)cq.a * M) * row + (int64_t)cq.b * VEC * 2;
+#pragma unroll
+      for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = m0 + 16 * t + 4 * grp + r;
+          if (m < M) store_cols<VEC>(op + (int64_t)m * row, acc[t], r);
+        }
+    }
+  }
+}
+
+// Expansion of up to 16 KQ rows: their operands stay in registers while the tiles of 16 output rows go by.
+template <int VEC, int KQ, int W>
+__global__ __launch_bounds__(64 * W) void k_expand_split(const float* __restrict__ x, const float2* __restrict__ Up,
+                                                         int rn, uint32_t ncv, uint32_t BV, int K, int M, int tiles,
+                                                         int groups, float* __restrict__ out) {
+  typedef typename ColVec<VEC>::type V;
+  extern __shared__ u32v4 sQ[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 15, grp = lane >> 4;
+  const int64_t row = (int64_t)BV * VEC * 2;
+  const int t0 = blockIdx.y * tiles, T = (M + 15) >> 4, nt = T - t0 < tiles ? T - t0 : tiles;
+  const int stride = (int)gridDim.x * W;
+  V v[KQ][4];
+  Cols nq = columns_of((uint32_t)((int)blockIdx.x * W + wave), col, ncv, BV);
+  auto fetch = [&](const Cols& c) {
+    const float* xp = x + (int64_t)c.a * K * row + (int64_t)c.b * VEC * 2;
+#pragma unroll
+    for (int q = 0; q < KQ; ++q)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int k = 16 * q + 4 * j + grp;
+        v[q][j] = *reinterpret_cast<const V*>(xp + (int64_t)(k < K ? k : K - 1) * row);
+      }
+  };
+  fetch(nq);
+  stage_split<false>(sQ, Up, rn, M, K, 16 * t0, nt, 0, KQ, tid, 64 * W);
+  __syncthreads();
+  for (int g = (int)blockIdx.x * W + wave; g < groups; g += stride) {
+    const Cols cq = nq;
+    Split8 b[KQ][2 * VEC];
+#pragma unroll
+    for (int q = 0; q < KQ; ++q) split_rows<VEC>(v[q], b[q]);
+    if (g + stride < groups) {                          // the next columns go in flight
+      nq = columns_of((uint32_t)(g + stride), col, ncv, BV);
+      fetch(nq);
+    }
+    float* op = out + ((int64_t)cq.a * M) * row + (int64_t)cq.b * VEC * 2;
+    for (int t = 0; t < nt; ++t) {
+      v4f acc[2 * VEC];
+#pragma unroll
+      for (int i = 0; i < 2 * VEC; ++i) acc[i] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int q = 0; q < KQ; ++q) mfma_split<2 * VEC>(acc, split_item(sQ + (q * nt + t) * kSplitItem + lane), b[q]);
+      if (cq.valid) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = 16 * (t0 + t) + 4 * grp + r;
+          if (m < M) store_cols<VEC>(op + (int64_t)m * row, acc, r);
+        }
+      }
+    }
+  }
+}
+
 // -------------------------------------------------------------------------------------------
 // k_core: the three steps around the Tucker core in one kernel, for mode 1 (the slowest index):
 //   g_L[m, b] = sum_k conj(U[k, m]) x[k, b]            last compression stage (K = I_1, M = r_1)
@@ -309,7 +475,7 @@ struct CoreAdam {
   float2* g_out;        // compressed gradient, written for the state accessors
   float beta1, beta2, inv_c1, inv_c2, eps;
 };
-constexpr int kCoreSteps = 4;             // steps of x per wavefront in flight: all of them for K <= 16 waves
+constexpr int kCoreSteps = 4;             // steps of four rows of x per wavefront: one operand, all of them for K <= 16 waves
 
 // MT: tiles of 16 that hold the rank; W: wavefronts of a workgroup
 template <int MT, int W>
@@ -319,7 +485,7 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
   const FactorRef U = factor_ref(Up, (int64_t)K * rn);
   constexpr int kThr = 64 * W;
   constexpr int kPart = MT * 2 * 4 * 64;        // floats of one wavefront's partial tiles
-  constexpr int kArea = W * kPart;     // [wave][tile][re / im][r][lane]; two of them take turns
+  constexpr int kArea = W * kPart;     // [wave][tile][re / im][r][lane], then N_L as B operands [tile][h, m, l][lane]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, grp = lane >> 4;
@@ -327,7 +493,8 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
   const int J = (K + 3) >> 2, Q = (K + 15) >> 4;
   const bool once = J <= W * kCoreSteps;                       // (K <= 16 W) one batch of steps, one output tile each
   // operands of the compression: steps wave + W (s0 + u); past the end: zero coefficients
-  float2 xv[kCoreSteps], fc[kCoreSteps][MT];
+  float2 xv[kCoreSteps];
+  Split8 fc[MT];
   auto fetch_x = [&](int g, int s0) {
     const int64_t b_raw = (int64_t)g * 16 + col;
     const float* xp = x + (b_raw < B ? b_raw : B - 1) * 2;
@@ -338,12 +505,19 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
     }
   };
   auto fetch_in = [&](int s0) {
+    float2 f[MT][kCoreSteps];
 #pragma unroll
     for (int u = 0; u < kCoreSteps; ++u) {
       const int k = 4 * (wave + W * (s0 + u)) + grp;
 #pragma unroll
-      for (int t = 0; t < MT; ++t) fc[u][t] = factor_at<true>(U, rn, 16 * t + col, k, M, K);
+      for (int t = 0; t < MT; ++t) f[t][u] = factor_at<true>(U, rn, 16 * t + col, k, M, K);
     }
+    return [=](Split8* to) {
+#pragma unroll
+      for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int u = 0; u < kCoreSteps; ++u) split_at(to[t], u, f[t][u]);
+    };
   };
   // moments of this thread's core entries
   constexpr int kEnt = (MT * 256 + kThr - 1) / kThr;
@@ -368,39 +542,55 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
     }
   };
   // operands of an output tile of the expansion
-  float2 fe[MT][4];
+  Split8 fe[MT];
   auto fetch_out = [&](int q) {
+    float2 f[MT][4];
 #pragma unroll
     for (int t = 0; t < MT; ++t)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) fe[t][r] = factor_at<false>(U, rn, 16 * q + col, 16 * t + 4 * grp + r, K, M);
+      for (int r = 0; r < 4; ++r) f[t][r] = factor_at<false>(U, rn, 16 * q + col, 16 * t + 4 * grp + r, K, M);
+    return [=](Split8* to) {
+#pragma unroll
+      for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) split_at(to[t], r, f[t][r]);
+    };
   };
   int g = blockIdx.x;
   fetch_x(g, 0);
-  fetch_in(0);
-  fetch_moments(g);
-  fetch_out(wave);
+  {
+    const auto in = fetch_in(0);
+    fetch_moments(g);
+    if constexpr (MT == 4) {                                   // (both sets of operands at once do not fit the registers)
+      in(fc);
+      __builtin_amdgcn_sched_barrier(0);
+      fetch_out(wave)(fe);
+    } else {
+      const auto out = fetch_out(wave);
+      __builtin_amdgcn_sched_barrier(0);                       // (everything requested)
+      in(fc);
+      out(fe);
+    }
+  }
   float* red = reinterpret_cast<float*>(sF);
-  for (int it = 0; g < groups; g += gridDim.x, ++it, red = reinterpret_cast<float*>(sF) + (it & 1) * kArea) {
+  uint32_t* sN = reinterpret_cast<uint32_t*>(red + kArea);
+  for (int it = 0; g < groups; g += gridDim.x, ++it) {
     v4f acc[MT][2];
 #pragma unroll
     for (int t = 0; t < MT; ++t) acc[t][0] = acc[t][1] = (v4f){0.f, 0.f, 0.f, 0.f};
-    __builtin_amdgcn_sched_barrier(0);
     for (int s0 = 0;; s0 += kCoreSteps) {
+      Split8 b[2];
+      split_rows<1>(xv, b);
 #pragma unroll
-      for (int u = 0; u < kCoreSteps; ++u) {
-        const float xs[2] = {xv[u].x, xv[u].y};
-#pragma unroll
-        for (int t = 0; t < MT; ++t) cmac<1>(acc[t], fc[u][t], xs);
-      }
+      for (int t = 0; t < MT; ++t) mfma_split<2>(acc[t], fc[t], b);
       if (W * (s0 + kCoreSteps) >= J) break;          // (the same for every wavefront)
       fetch_x(g, s0 + kCoreSteps);
-      fetch_in(s0 + kCoreSteps);
+      fetch_in(s0 + kCoreSteps)(fc);
     }
     const int gn = g + gridDim.x;
     if (gn < groups) {                                         // the next group's columns go in flight
       fetch_x(gn, 0);
-      if (!once) fetch_in(0);
+      if (!once) fetch_in(0)(fc);
     }
 #pragma unroll
     for (int t = 0; t < MT; ++t)
@@ -409,14 +599,14 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
 #pragma unroll
         for (int r = 0; r < 4; ++r) red[wave * kPart + ((t * 2 + i) * 4 + r) * 64 + lane] = acc[t][i][r];
     __syncthreads();
-    // AdamUpdate; N_L replaces wavefront 0's partial sums (each entry is read and written by one thread)
+    // AdamUpdate; N_L goes to LDS as a B operand: row 16 t + 4 g + r is dword r of lane (c, g), tile t
 #pragma unroll
     for (int q = 0; q < kEnt; ++q) {
       const int e = tid + q * kThr;
       const int l = e & 63, r = (e >> 6) & 3, t = e >> 8;
       if (MT * 256 % kThr == 0 || t < MT) {
-        float* pr = red + (t * 8 + r) * 64 + l;
-        float* pi = pr + 256;
+        const float* pr = red + (t * 8 + r) * 64 + l;
+        const float* pi = pr + 256;
         float gre = 0.f, gim = 0.f;
 #pragma unroll
         for (int w = 0; w < W; ++w) {
@@ -437,8 +627,12 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
           nr = m.x * ad.inv_c1 * d;
           ni = m.y * ad.inv_c1 * d;
         }
-        *pr = nr;
-        *pi = ni;
+        uint32_t h, m3, l3;
+        split_pair(nr, ni, h, m3, l3);
+        uint32_t* pn = sN + (t * 192 + l) * 4 + r;
+        pn[0] = h;
+        pn[256] = m3;
+        pn[512] = l3;
       }
     }
     if (gn < groups) fetch_moments(gn);
@@ -447,16 +641,15 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
     const int64_t b = (int64_t)g * 16 + col;
     float* op = z + b * 2;
     for (int q = wave; q < Q; q += W) {
-      if (!once && (q != wave || it > 0)) fetch_out(q);
+      if (!once && (q != wave || it > 0)) fetch_out(q)(fe);
       v4f o[2];
       o[0] = o[1] = (v4f){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int t = 0; t < MT; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float n[2] = {red[(t * 8 + r) * 64 + lane], red[(t * 8 + 4 + r) * 64 + lane]};
-          cmac<1>(o, fe[t][r], n);
-        }
+      for (int t = 0; t < MT; ++t) {
+        const Split8 n = split_item(reinterpret_cast<const u32v4*>(sN) + t * 192 + lane);
+        const Split8 b2[2] = {conj_pairs(n), swap_pairs(n)};
+        mfma_split<2>(o, fe[t], b2);
+      }
       if (b < B) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -476,6 +669,8 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
 // below, the wavefronts of a workgroup share a group so that the stage still spreads over the chip (372 groups,
 // 90x77x66: 6.8 us shared, where 93 workgroups of one group per wavefront would leave 163 compute units idle).
 constexpr int64_t kOwnColumns = 1024;
+// Rows above which those stages take the split bf16 operands: below, a quad is mostly empty.
+constexpr int kSplitRows = 8;
 
 // k_expand's KS: steps of four rows of x, rounded up to the next variant.  Padded to 4, 8 or 16 steps a rank of a few was
 // matrix work for nothing: 12M columns of one row 284 us, now 105; 3M from 2 rows to 4 78, now 34; 500000 from 20 to 24 43,
@@ -492,13 +687,63 @@ void launch_mid(hipStream_t s, const float2* x, const float2* U, int rn, bool pr
   if (A * M * B <= 0) return;
   const float* xf = reinterpret_cast<const float*>(x);
   float* of = reinterpret_cast<float*>(out);
-  const int vec = B % 2 == 0 && A * (B / 2) / 16 >= kOwnColumns ? 2 : 1;
+  // (two columns per lane, except where the operands of more than 32 rows would not stay in registers)
+  const bool rows_fit = project || K <= 32 || K > 64;
+  const int vec = rows_fit && B % 2 == 0 && A * (B / 2) / 16 >= kOwnColumns ? 2 : 1;
   const int64_t ncv64 = A * (B / vec);
   const uint32_t ncv = (uint32_t)ncv64, BV = (uint32_t)(B / vec);
   const int64_t groups = (ncv64 + 15) / 16;
   const bool own = groups >= kOwnColumns;
   const dim3 block(kThreads);
   const int Q = (M + 15) / 16;
+  if (own && K > kSplitRows) {
+    const int kq = (K + 15) / 16;
+    if (!project && K <= 64) {
+      // operands of `tiles` tiles: at most 96 KB
+      const int most = 32 / kq, tiles = Q < most ? Q : most;
+      const size_t lds = (size_t)tiles * kq * kSplitItem * 16;
+      const unsigned ny = (unsigned)((Q + tiles - 1) / tiles);
+#define TGRAD_EXS(V_, KQ_, W_)                                                                       \
+  do {                                                                                               \
+    allow_lds(k_expand_split<V_, KQ_, W_>, lds);                                                     \
+    const int64_t most_ = (int64_t)compute_units() * resident_blocks(k_expand_split<V_, KQ_, W_>, 64 * W_, lds); \
+    const int64_t need_ = (groups + W_ - 1) / W_;                                                    \
+    k_expand_split<V_, KQ_, W_><<<dim3((unsigned)(need_ < most_ ? need_ : most_), ny), dim3(64 * W_), lds, s>>>( \
+        xf, U, rn, ncv, BV, K, M, tiles, (int)groups, of);                                           \
+  } while (0)
+#define TGRAD_EXS_K(V_, W_)                                                                          \
+  do {                                                                                               \
+    if (kq == 1) TGRAD_EXS(V_, 1, W_); else TGRAD_EXS(V_, 2, W_);                                    \
+  } while (0)
+      if (kq == 3) { if (lds > 48 * 1024) TGRAD_EXS(1, 3, 8); else TGRAD_EXS(1, 3, 4); }
+      else if (kq == 4) { if (lds > 48 * 1024) TGRAD_EXS(1, 4, 8); else TGRAD_EXS(1, 4, 4); }
+      else if (lds > 48 * 1024) { if (vec == 2) TGRAD_EXS_K(2, 8); else TGRAD_EXS_K(1, 8); }
+      else { if (vec == 2) TGRAD_EXS_K(2, 4); else TGRAD_EXS_K(1, 4); }
+#undef TGRAD_EXS_K
+#undef TGRAD_EXS
+      return;
+    }
+    const int mt = Q >= 4 ? 4 : Q >= 2 ? 2 : 1;
+    const size_t lds = (size_t)(kq < kChunkQuads ? kq : kChunkQuads) * mt * kSplitItem * 16;
+    const unsigned ny = (unsigned)((Q + mt - 1) / mt);
+#define TGRAD_MIDS(V_, MT_, P_, W_)                                                                  \
+  do {                                                                                               \
+    allow_lds(k_mid_split<V_, MT_, P_, W_>, lds);                                                    \
+    const int64_t most_ = (int64_t)compute_units() * resident_blocks(k_mid_split<V_, MT_, P_, W_>, 64 * W_, lds); \
+    const int64_t need_ = (groups + W_ - 1) / W_;                                                    \
+    k_mid_split<V_, MT_, P_, W_><<<dim3((unsigned)(need_ < most_ ? need_ : most_), ny), dim3(64 * W_), lds, s>>>( \
+        xf, U, rn, ncv, BV, K, M, (int)groups, of);                                                  \
+  } while (0)
+#define TGRAD_MIDS_T(V_, P_)                                                                         \
+  do {                                                                                               \
+    if (mt == 4) TGRAD_MIDS(V_, 4, P_, 8); else if (mt == 2) TGRAD_MIDS(V_, 2, P_, 4); else TGRAD_MIDS(V_, 1, P_, 4); \
+  } while (0)
+    if (project) { if (vec == 2) TGRAD_MIDS_T(2, true); else TGRAD_MIDS_T(1, true); }
+    else { if (vec == 2) TGRAD_MIDS_T(2, false); else TGRAD_MIDS_T(1, false); }
+#undef TGRAD_MIDS_T
+#undef TGRAD_MIDS
+    return;
+  }
   if (!project && K <= 64) {
     const int ks = expand_steps(K);
     const int tiles = own ? (Q < 64 / ks * 2 ? Q : 64 / ks * 2) : 1;          // operands of `tiles` tiles: at most 64 KB
@@ -582,7 +827,7 @@ void launch_core(hipStream_t s, const float2* x, const float2* U, int rn, int K,
   const int64_t groups = (B + 15) / 16;
 #define TGRAD_CORE(MT_, W_)                                                                                  \
   do {                                                                                                       \
-    const size_t lds = (size_t)2 * W_ * MT_ * 2048;                                                          \
+    const size_t lds = (size_t)W_ * MT_ * 2048 + (size_t)MT_ * 3072;                                                          \
     allow_lds(k_core<MT_, W_>, lds);                                                                         \
     const int64_t cap = (int64_t)compute_units() * resident_blocks(k_core<MT_, W_>, 64 * W_, lds);           \
     k_core<MT_, W_><<<dim3((unsigned)(groups < cap ? groups : cap)), dim3(64 * W_), lds, s>>>(xf, U, rn, K, M, B, (int)groups, ad, zf); \
