@@ -24,6 +24,8 @@
 // first load to the last store and are staged in LDS private to it, as in contract_mfma.hip.  A wavefront walks
 // whole slabs where there are enough of them to occupy the chip; with fewer (SPLIT) the wavefronts of a
 // workgroup share a slab (k_head: partial sums added through LDS in a fixed order), or take any tile (k_tail).
+#include <type_traits>
+
 #include "device_common.h"
 #include "end_common.h"
 #include "launch_util.h"
@@ -32,7 +34,7 @@ namespace tgrad {
 
 namespace {
 
-constexpr int kMaxWaves = 4;
+constexpr int kMaxWaves = 8;
 
 // v of the neighbouring lane (c ^ 1): the other part of the same complex column
 __device__ __forceinline__ float swap_parts(float v) {
@@ -40,20 +42,34 @@ __device__ __forceinline__ float swap_parts(float v) {
 }
 
 // ---- k_head -------------------------------------------------------------------------------------
-// Steps of four elements of K (T4) and rows per tile; pieces of two elements per lane that cover a tile.
-constexpr int head_rows(int T4) { return T4 <= 9 ? 32 : 16; }
-constexpr int head_pieces(int T4) { return T4 <= 9 ? T4 : (T4 + 1) / 2; }
-// floats of LDS per wavefront.  Rows of an even K are padded by one element, so that neighbouring rows do not
-// share banks; everything a commit writes and everything the steps past K read lies inside, and so do the
-// partial sums of a shared slab.
-__host__ __device__ constexpr int head_slice(int K, int T4) {
-  const int pad = (K & 1) ? 0 : 2;
-  const int committed = head_pieces(T4) * 64 * 4;                        // floats of G that a commit writes
-  const int a = committed + pad * (committed / (2 * K) + 1);
-  const int b = head_rows(T4) * (2 * K + pad);
-  const int c = (a > b ? a : b) + 8 * T4;                                // + what the last row's steps read past its end
+// Stage 1  y[row, (m3, p)] = sum_i3 conj(U3) G: quads of 16 elements of a row on split bf16 operands (device_common.h; slot
+//   2 j + p of lane (c, g) is part p of element 16 quad + 4 j + g), a remainder of up to four elements - half-spectrum modes
+//   have one - as a float32 step.  G in bf16 is its own first part and needs no others: three products instead of six, and no
+//   vector arithmetic to prepare them.
+// Stage 2  sums over 32 rows of the slab at a time: register r of y is row 4 g + r of its 16, so the eight values of two
+//   16-row halves are the slots of a B operand as they stand; conj(U2) comes split from the table in LDS.
+// T4: steps of four elements of K (class of K); quads and remainder steps that do them.
+constexpr int head_quads(int T4) { return T4 / 4 + (T4 % 4 >= 2 ? 1 : 0); }
+constexpr int head_rest(int T4) { return T4 % 4 == 1 ? 1 : 0; }
+constexpr int head_rows(int T4) { return T4 <= 9 ? 32 : 16; }            // rows per tile
+constexpr int head_pieces(int T4) { return T4 <= 9 ? T4 : (T4 + 1) / 2; }   // pieces of two elements per lane that cover a tile
+// dwords of LDS per wavefront; an element takes ES of them (2, or 1 in bf16).  Rows of an even K are padded by one element,
+// so that neighbouring rows do not share banks; everything a commit writes and everything the steps past K read lies
+// inside, and so do the partial sums of a shared slab.
+__host__ __device__ constexpr int head_slice(int ES, int K, int T4) {
+  const int pad = (K & 1) ? 0 : 1;
+  const int committed = head_pieces(T4) * 64 * 2;                        // elements that a commit writes
+  const int a = committed + pad * (committed / K + 1);
+  const int b = head_rows(T4) * (K + pad);
+  const int c = ES * ((a > b ? a : b) + 16 * head_quads(T4) + 4);        // + what the last row's steps read past its end
   return ((c > 1024 ? c : 1024) + 3) & ~3;                               // 1024: partial sums of two by two tiles
 }
+// Tiles in flight per wavefront.  What a compute unit has in flight decides what it streams (64-row slabs of 33 elements:
+// loads alone 4.5 TB/s with 67 KB, 5.3 with 100 KB); registers hold more of it than LDS would.
+constexpr int head_ahead(int T4, int NC) { return T4 >= 9 && NC == 2 ? 2 : T4 >= 13 ? 2 : 1; }
+// Coefficients of more than two operands' worth are kept in LDS (a tile reads them once), fewer in registers.
+constexpr bool head_coef_lds(int T4, int NC) { return head_quads(T4) * NC > 2; }
+constexpr int kHeadItem = 6 * 64;         // u32v4 of the table per 32 rows and tile of M2: (Fr, Fi) x (h, m, l) x lane
 
 struct HeadArgs {
   const void* g;
@@ -74,16 +90,18 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
   typedef typename BufPair<DT>::type Raw;
   constexpr int R = head_rows(T4), TB = head_pieces(T4);
   constexpr int kPiece = (int)sizeof(Raw), kElem = kPiece / 2;           // bytes of two elements, of one
+  constexpr int ES = kElem / 4;                                          // dwords of an element in LDS
+  constexpr int QN = head_quads(T4), REST = head_rest(T4), kAhead = head_ahead(T4, NC);
   extern __shared__ float smem[];
   const int K = a.K, M = a.M, I2 = a.I2, M2 = a.M2, S = a.S;
-  const int pad = (K & 1) ? 0 : 2, stride = 2 * K + pad;
-  const int slice = head_slice(K, T4);
+  const int pad = (K & 1) ? 0 : 1, stride = ES * (K + pad);
+  const int slice = head_slice(ES, K, T4);
   const int W = (int)blockDim.x >> 6;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, grp = lane >> 4;
   float* sX = smem + wave * slice;
-  float2* sT = reinterpret_cast<float2*>(smem + W * slice);              // conj(U2) in operand order [16 rows][r][nm][lane]
+  u32v4* sT = reinterpret_cast<u32v4*>(smem + W * slice);                // conj(U2) in operand order [32 rows][nm]
   const bool split = a.split != 0;
   const int nw = (int)gridDim.x * W;
   int slab = split ? (int)blockIdx.x : (int)blockIdx.x * W + wave, ts = split ? wave : 0;
@@ -100,8 +118,8 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
     }
   };
   const uint32_t slab_elems = (uint32_t)(I2 * K);
-  Raw raw[TB];
-  u32x2 lone = {0u, 0u};                                                 // last element of a tile with an odd count
+  Raw raw[kAhead][TB];                                                   // the tiles in flight
+  u32x2 lone[kAhead];                                                    // last element of a tile with an odd count
   int32_t my_om = 0;
   // the tile being fetched (scalar): address, bytes in whole pieces (0: no tile), elements
   const char* f_base = reinterpret_cast<const char*>(a.g);
@@ -114,17 +132,17 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
     f_base = reinterpret_cast<const char*>(a.g) +
              (ok ? ((uint64_t)(uint32_t)sl * slab_elems + (uint32_t)(t * R * K)) * (uint64_t)kElem : 0ull);
   };
-  auto issue_piece = [&](int i) {
+  auto issue_piece = [&](Raw* to, int i) {
     const int k = i / 4, left = f_bytes - k * 4 * 64 * kPiece;           // a descriptor per 4 pieces: immediates reach 4 KB
     const __amdgpu_buffer_rsrc_t r = raw_buffer(f_base + k * 4 * 64 * kPiece, (uint32_t)(left > 0 ? left : 0));
-    raw[i] = BufPair<DT>::load(r, lane * kPiece + (i - 4 * k) * 64 * kPiece);
+    to[i] = BufPair<DT>::load(r, lane * kPiece + (i - 4 * k) * 64 * kPiece);
   };
-  auto issue_lone = [&]() {
+  auto issue_lone = [&](u32x2& to) {
     const __amdgpu_buffer_rsrc_t r = raw_buffer(f_base + f_bytes, (f_n & 1) ? kElem : 0);
     if constexpr (DT == TGRAD_C64) {
-      lone = __builtin_amdgcn_raw_buffer_load_b64(r, lane * kElem, 0, 2);
+      to = __builtin_amdgcn_raw_buffer_load_b64(r, lane * kElem, 0, 2);
     } else {
-      lone.x = __builtin_amdgcn_raw_buffer_load_b32(r, lane * kElem, 0, 2);
+      to.x = __builtin_amdgcn_raw_buffer_load_b32(r, lane * kElem, 0, 2);
     }
   };
   auto issue_support = [&](uint32_t j0, uint32_t j1) {
@@ -132,48 +150,93 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
     const __amdgpu_buffer_rsrc_t ro = raw_buffer(a.omega + j0, (cnt < 64u ? cnt : 64u) * 4u);
     my_om = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(ro, lane * 4, 0, 0);
   };
-  // ---- prologue: the first tile, then the operands go in flight ----
-  set_fetch(slab, ts);
+  // ---- prologue: the first tiles, then the operands go in flight ----
+  int s1 = slab, t1 = ts;                                                // the tile after this one, the one after that
+  if (slab < a.nslabs) advance(s1, t1);
+  int s2 = s1, t2 = t1;
+  if (s1 < a.nslabs) advance(s2, t2);
+  auto issue_tile = [&](Raw* to, u32x2& last, int sl, int t) {
+    set_fetch(sl, t);
 #pragma unroll
-  for (int i = 0; i < TB; ++i) issue_piece(i);
-  issue_lone();
+    for (int i = 0; i < TB; ++i) issue_piece(to, i);
+    last = (u32x2){0u, 0u};
+    issue_lone(last);
+  };
+  issue_tile(raw[0], lone[0], slab, ts);
   const uint32_t vzero = (uint32_t)opaque_zero();
   auto range_of = [&](int sl, int t, uint32_t& j0, uint32_t& j1) {       // per-lane loads, made scalar when used
     const uint32_t* tsb = a.tile_start + (sl < a.nslabs ? (int64_t)sl * S + t : 0);
     j0 = tsb[vzero];
     j1 = tsb[vzero + 1];
   };
-  int nslab = slab, nts = ts;
-  if (slab < a.nslabs) advance(nslab, nts);
   uint32_t cj0v, cj1v, nj0v, nj1v;
   range_of(slab, ts, cj0v, cj1v);
-  range_of(nslab, nts, nj0v, nj1v);
+  range_of(s1, t1, nj0v, nj1v);
   const FactorRef fU3 = factor_ref(a.U3, (int64_t)K * M), fU2 = factor_ref(a.U2, (int64_t)I2 * M2);
-  float2 creg[T4][NC];                                                   // conj(U3)[4 j + g][column]
+  constexpr bool kInLds = head_coef_lds(T4, NC);
+  Split8 cq[kInLds ? 1 : QN][NC];                                        // conj(U3)[16 q + 4 j + g][column]
+  u32v4* sC = sT + ((I2 + 31) >> 5) * (NM * kHeadItem);
+  float2 crest[NC];
+  auto coef = [&](int k, int nc) -> float2 {
+    const int m = (16 * nc + col) >> 1;
+    const float2 u = factor_entry(fU3, k, m, M, k < K && m < M);
+    return column_coef(make_float2(u.x, -u.y), col & 1);
+  };
 #pragma unroll
-  for (int j = 0; j < T4; ++j)
+  for (int nc = 0; nc < NC; ++nc) {
+    if constexpr (!kInLds) {
 #pragma unroll
-    for (int nc = 0; nc < NC; ++nc) {
-      const int k = 4 * j + grp, m = (16 * nc + col) >> 1;
-      const float2 u = factor_entry(fU3, k, m, M, k < K && m < M);
-      creg[j][nc] = column_coef(make_float2(u.x, -u.y), col & 1);
+      for (int q = 0; q < QN; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) split_at(cq[q][nc], j, coef(16 * q + 4 * j + grp, nc));
     }
+    if constexpr (REST > 0) crest[nc] = coef(16 * QN + grp, nc);
+  }
+  if constexpr (kInLds) {
+    for (int i = wave; i < QN * NC; i += W) {                            // [q][nc][h, m, l][lane]
+      const int q = i / NC, nc = i % NC;
+      float2 f[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) f[j] = coef(16 * q + 4 * j + grp, nc);
+      Split8 c;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) split_at(c, j, f[j]);
+      u32v4* p = sC + i * 192 + lane;
+      p[0] = c.h;
+      p[64] = c.m;
+      p[128] = c.l;
+    }
+  }
   for (int e = lane; e < slice; e += 64) sX[e] = 0.f;                    // pads stay finite
-  stage_table(sT, ((I2 + 15) >> 4) * 4 * NM * 64, tid, (int)blockDim.x, [&](int e) -> float2 {
-    const int l = e & 63, nm = (e >> 6) % NM, r = ((e >> 6) / NM) & 3, q = (e >> 6) / (4 * NM);
-    const int i2 = 16 * q + 4 * (l >> 4) + r, m2 = 16 * nm + (l & 15);
-    const float2 u = factor_entry(fU2, i2, m2, M2, i2 < I2 && m2 < M2);
-    return make_float2(u.x, -u.y);
-  });
+  for (int e = tid; e < ((I2 + 31) >> 5) * NM * 64; e += (int)blockDim.x) {
+    const int l = e & 63, nm = (e >> 6) % NM, q = (e >> 6) / NM;
+    const int m2 = 16 * nm + (l & 15);
+    float2 u[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int i2 = 32 * q + 16 * (i >> 2) + 4 * (l >> 4) + (i & 3);
+      u[i] = factor_entry(fU2, i2, m2, M2, i2 < I2 && m2 < M2);
+    }
+    Split8 fr, fi;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      split_at(fr, d, make_float2(u[2 * d].x, u[2 * d + 1].x));
+      split_at(fi, d, make_float2(-u[2 * d].y, -u[2 * d + 1].y));
+    }
+    u32v4* p = sT + (e >> 6) * kHeadItem + l;
+    p[0] = fr.h; p[64] = fr.m; p[128] = fr.l;
+    p[192] = fi.h; p[256] = fi.m; p[320] = fi.l;
+  }
   int wofs[TB];                                                          // where the lane's pieces lie in the slice
 #pragma unroll
   for (int i = 0; i < TB; ++i) {
     const int pi = lane + 64 * i;
-    wofs[i] = 4 * pi + (pad ? pad * (int)div_magic(2u * (uint32_t)pi, a.magicK) : 0);
+    wofs[i] = ES * (2 * pi + (pad ? (int)div_magic(2u * (uint32_t)pi, a.magicK) : 0));
   }
   uint32_t cj0 = __builtin_amdgcn_readfirstlane(cj0v), cj1 = __builtin_amdgcn_readfirstlane(cj1v);
   if (slab >= a.nslabs) cj1 = cj0;
   issue_support(cj0, cj1);
+  if constexpr (kAhead > 1) issue_tile(raw[kAhead - 1], lone[kAhead - 1], s1, t1);   // (the loop's order of requests)
   __syncthreads();                                                       // (the only barrier unless the slab is shared)
   if (!split && slab >= a.nslabs) return;
 
@@ -203,6 +266,9 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), ro, ofs[nc], 0, 0);
   };
   clear();
+  v4f held[NC];                                                          // (tiles of 16 rows) y of an even tile
+#pragma unroll
+  for (int nc = 0; nc < NC; ++nc) held[nc] = (v4f){0.f, 0.f, 0.f, 0.f};
   bool pending = false;
   int pending_slab = 0;
   auto store_slab = [&]() {
@@ -214,30 +280,34 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
         for (int r = 0; r < 4; ++r) store_at(pending_slab, nm, nc, r, value(nm, nc, r));
     clear();
   };
-  while (slab < a.nslabs) {
+  // One tile, from the registers of set `set`; its tile of kAhead tiles later goes in flight under it.  Loads retire in
+  // order, so what the next tile waits for (its support) is requested before those.
+  auto tile = [&](auto set) {
+    constexpr int D = decltype(set)::value;
     const uint32_t e_base = (uint32_t)slab * slab_elems + (uint32_t)(ts * R * K);   // I < 2^31
-    const int n_e = f_n, rows = I2 - ts * R;
+    const int rows = I2 - ts * R, n_e = (rows < R ? rows : R) * K;
     wave_sync();                                                         // previous tile's LDS reads are done
-    asm volatile("" : "+v"(my_om), "+v"(lone));
+    asm volatile("" : "+v"(my_om), "+v"(lone[D]));
 #pragma unroll
-    for (int i = 0; i < TB; ++i) asm volatile("" : "+v"(raw[i]));        // one wait for the whole batch
+    for (int i = 0; i < TB; ++i) asm volatile("" : "+v"(raw[D][i]));     // one wait for the whole batch
 #pragma unroll
     for (int i = 0; i < TB; ++i) {
-      float2* d = reinterpret_cast<float2*>(sX + wofs[i]);
       if constexpr (DT == TGRAD_C64) {
-        d[0] = make_float2(__uint_as_float(raw[i].x), __uint_as_float(raw[i].y));
-        d[1] = make_float2(__uint_as_float(raw[i].z), __uint_as_float(raw[i].w));
-      } else {                                                           // a bf16 is the upper half of a float32
-        d[0] = make_float2(__uint_as_float(raw[i].x << 16), __uint_as_float(raw[i].x & 0xFFFF0000u));
-        d[1] = make_float2(__uint_as_float(raw[i].y << 16), __uint_as_float(raw[i].y & 0xFFFF0000u));
+        float2* d = reinterpret_cast<float2*>(sX + wofs[i]);
+        d[0] = make_float2(__uint_as_float(raw[D][i].x), __uint_as_float(raw[D][i].y));
+        d[1] = make_float2(__uint_as_float(raw[D][i].z), __uint_as_float(raw[D][i].w));
+      } else {
+        uint32_t* d = reinterpret_cast<uint32_t*>(sX + wofs[i]);
+        d[0] = raw[D][i].x;
+        d[1] = raw[D][i].y;
       }
     }
     if (n_e & 1) {                                                       // (K is odd: no padding in the slice)
       wave_sync();
       if (lane == 0) {
-        float2* d = reinterpret_cast<float2*>(sX + 2 * (n_e - 1));
-        if constexpr (DT == TGRAD_C64) *d = make_float2(__uint_as_float(lone.x), __uint_as_float(lone.y));
-        else *d = make_float2(__uint_as_float(lone.x << 16), __uint_as_float(lone.x & 0xFFFF0000u));
+        float* d = sX + ES * (n_e - 1);
+        if constexpr (DT == TGRAD_C64) *reinterpret_cast<float2*>(d) = make_float2(__uint_as_float(lone[D].x), __uint_as_float(lone[D].y));
+        else *reinterpret_cast<uint32_t*>(d) = lone[D].x;
       }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -246,18 +316,19 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
       pending = false;
     }
     const int32_t cur_om = my_om;
-    set_fetch(nslab, nts);
-    int nnslab = nslab, nnts = nts;
-    if (nslab < a.nslabs) advance(nnslab, nnts);
+    set_fetch(kAhead == 1 ? s1 : s2, kAhead == 1 ? t1 : t2);
     const uint32_t nj0 = __builtin_amdgcn_readfirstlane(nj0v);
-    const uint32_t nj1 = nslab < a.nslabs ? __builtin_amdgcn_readfirstlane(nj1v) : nj0;
+    const uint32_t nj1 = s1 < a.nslabs ? __builtin_amdgcn_readfirstlane(nj1v) : nj0;
+    issue_support(nj0, nj1);
+    range_of(s2, t2, nj0v, nj1v);
     wave_sync();
     {                                                                    // Sparse(G, Omega): hand the values over, then remove them
       auto take = [&](uint32_t j, int32_t oj) {
         const uint32_t e = (uint32_t)oj - e_base;
-        float2* p = reinterpret_cast<float2*>(sX + 2 * e + (pad ? (uint32_t)pad * div_magic(e, a.magicK) : 0u));
-        a.gs[cj0 + j] = *p;
-        *p = make_float2(0.f, 0.f);
+        float* p = sX + ES * (e + (pad ? div_magic(e, a.magicK) : 0u));
+        a.gs[cj0 + j] = load_elem<DT>(p, 0);
+        if constexpr (DT == TGRAD_C64) *reinterpret_cast<float2*>(p) = make_float2(0.f, 0.f);
+        else *reinterpret_cast<uint32_t*>(p) = 0u;
       };
       const uint32_t cnt = cj1 - cj0;
       if ((uint32_t)lane < cnt) take((uint32_t)lane, cur_om);
@@ -266,67 +337,138 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
     }
     wave_sync();
     __builtin_amdgcn_s_setprio(1);
-    // The next tile's loads go between the steps of the first contraction: a load waits at issue until the memory
+    // The next tile's loads go between the products of the first contraction: a load waits at issue until the memory
     // pipeline takes it, and there that wait lies under matrix instructions.
+    constexpr int kTerms = DT == TGRAD_C64 ? 6 : 3, kSlots = QN * kTerms, kPer = (TB + kSlots - 1) / kSlots;
+    constexpr int H = R / 16;
+    v4f y[H][NC];
+    auto issue_at = [&](int slot) {
 #pragma unroll
-    for (int h = 0; h < R / 16; ++h) {
-      if (h == 0 || rows > 16 * h) {                                     // (wave-uniform)
-        v4f y[NC], yi[NC];                                               // two chains: half the depth and the rounding of one
-#pragma unroll
-        for (int nc = 0; nc < NC; ++nc) y[nc] = yi[nc] = (v4f){0.f, 0.f, 0.f, 0.f};
-        const float* xa = sX + (16 * h + col) * stride + 2 * grp;
-        constexpr int kFetch = 4;                                        // operands fetched ahead
-        float2 x[kFetch];
-#pragma unroll
-        for (int u = 0; u < kFetch && u < T4; ++u) x[u] = *reinterpret_cast<const float2*>(xa + 8 * u);
-#pragma unroll
-        for (int j = 0; j < T4; ++j) {
-          const float2 xv = x[j % kFetch];
-          if (j + kFetch < T4) x[j % kFetch] = *reinterpret_cast<const float2*>(xa + 8 * (j + kFetch));
-#pragma unroll
-          for (int nc = 0; nc < NC; ++nc) {
-            y[nc] = mfma16(xv.x, creg[j][nc].x, y[nc]);
-            yi[nc] = mfma16(xv.y, creg[j][nc].y, yi[nc]);
-          }
-          if (h == 0 && j < TB) {
-            __builtin_amdgcn_sched_barrier(0);
-            issue_piece(j);
-            __builtin_amdgcn_sched_barrier(0);
-          }
+      for (int i = 0; i < kPer; ++i)
+        if (slot * kPer + i < TB) {
+          __builtin_amdgcn_sched_barrier(0);
+          issue_piece(raw[D], slot * kPer + i);
+          __builtin_amdgcn_sched_barrier(0);
         }
-        const float2* ft = sT + (size_t)(ts * (R / 16) + h) * (4 * NM * 64) + lane;
+    };
+    // (The loads lie in the first half, which every tile has: a load on one of two paths would make the compiler wait for it
+    // wherever they meet.)
 #pragma unroll
-        for (int nc = 0; nc < NC; ++nc) y[nc] += yi[nc];
+    for (int h = 0; h < H; ++h) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+      for (int nc = 0; nc < NC; ++nc) y[h][nc] = (v4f){0.f, 0.f, 0.f, 0.f};
+      if (h == 0 || rows > 16 * h) {                                     // (wave-uniform)
+        v4f yl[NC];                                                      // the small terms have sums of their own
 #pragma unroll
-          for (int nm = 0; nm < NM; ++nm) {
-            const float2 f = ft[(r * NM + nm) * 64];
+        for (int nc = 0; nc < NC; ++nc) yl[nc] = (v4f){0.f, 0.f, 0.f, 0.f};
+        const float* xa = sX + (16 * h + col) * stride + ES * grp;
+#pragma unroll
+        for (int q = 0; q < QN; ++q) {
+          Split8 x;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float* p = xa + ES * (16 * q + 4 * j);
+            if constexpr (DT == TGRAD_C64) split_at(x, j, *reinterpret_cast<const float2*>(p));
+            else x.h[j] = *reinterpret_cast<const uint32_t*>(p);
+          }
+          const u32v4* cp = sC + q * (NC * 192) + lane;
+          u32v4 c[NC];
+          auto operand = [&](int k) {
 #pragma unroll
             for (int nc = 0; nc < NC; ++nc) {
-              da[nm][nc] = mfma16(f.x, y[nc][r], da[nm][nc]);
-              db[nm][nc] = mfma16(f.y, y[nc][r], db[nm][nc]);
+              if constexpr (kInLds) c[nc] = cp[nc * 192 + k * 64];
+              else c[nc] = k == 0 ? cq[q][nc].h : k == 1 ? cq[q][nc].m : cq[q][nc].l;
             }
+          };
+          auto product = [&](int slot, const u32v4& xv, v4f* to) {
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) to[nc] = mfma_bf(xv, c[nc], to[nc]);
+            if (h == 0) issue_at(kTerms * q + slot);
+          };
+          operand(2);
+          product(0, x.h, yl);
+          operand(1);
+          if constexpr (DT == TGRAD_C64) {
+            product(1, x.m, yl);
+            product(2, x.h, yl);
+            operand(0);
+            product(3, x.l, yl);
+            product(4, x.m, yl);
+            product(5, x.h, y[h]);
+          } else {
+            product(1, x.h, yl);
+            operand(0);
+            product(2, x.h, y[h]);
           }
+        }
+        if constexpr (REST > 0) {
+          const float2 xv = load_elem<DT>(xa + 16 * ES * QN, 0);
+#pragma unroll
+          for (int nc = 0; nc < NC; ++nc) {
+            y[h][nc] = mfma16(xv.x, crest[nc].x, y[h][nc]);
+            yl[nc] = mfma16(xv.y, crest[nc].y, yl[nc]);
+          }
+        }
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) y[h][nc] += yl[nc];
       }
     }
-    issue_lone();
-    issue_support(nj0, nj1);
-    uint32_t nnj0v, nnj1v;
-    range_of(nnslab, nnts, nnj0v, nnj1v);
+    auto second = [&](const v4f* lo, const v4f* hi) {
+      Split8 b[NC];
+#pragma unroll
+      for (int nc = 0; nc < NC; ++nc)
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+          split_at(b[nc], d, make_float2(lo[nc][2 * d], lo[nc][2 * d + 1]));
+          split_at(b[nc], 2 + d, make_float2(hi[nc][2 * d], hi[nc][2 * d + 1]));
+        }
+      const u32v4* ft = sT + (size_t)(R == 32 ? ts : ts >> 1) * (NM * kHeadItem) + lane;
+#pragma unroll
+      for (int nm = 0; nm < NM; ++nm) {
+        const u32v4* p = ft + nm * kHeadItem;
+        mfma_split<NC>(da[nm], Split8{p[0], p[64], p[128]}, b);
+        mfma_split<NC>(db[nm], Split8{p[192], p[256], p[320]}, b);
+      }
+    };
+    if constexpr (R == 32) {
+      second(y[0], y[1]);
+    } else {
+      // tiles of 16 rows: an even one of a slab that is walked waits for its neighbour
+      const bool odd = ts & 1, paired = odd && !split;
+      if (odd || split || ts == S - 1) {                                 // (wave-uniform)
+        v4f lo[NC], hi[NC];
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) {
+          const v4f none = (v4f){0.f, 0.f, 0.f, 0.f};
+          lo[nc] = paired ? held[nc] : odd ? none : y[0][nc];
+          hi[nc] = odd ? y[0][nc] : none;
+        }
+        second(lo, hi);
+      } else {
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) held[nc] = y[0][nc];
+      }
+    }
+    issue_lone(lone[D]);
     __builtin_amdgcn_s_setprio(0);
     if (!split && ts == S - 1) {
       pending = true;
       pending_slab = slab;
     }
-    slab = nslab;
-    ts = nts;
-    nslab = nnslab;
-    nts = nnts;
+    slab = s1;
+    ts = t1;
+    s1 = s2;
+    t1 = t2;
+    if (s2 < a.nslabs) advance(s2, t2);
     cj0 = nj0;
     cj1 = nj1;
-    nj0v = nnj0v;
-    nj1v = nnj1v;
+  };
+  while (slab < a.nslabs) {
+    tile(std::integral_constant<int, 0>());
+    if constexpr (kAhead > 1) {
+      if (slab >= a.nslabs) break;                                       // (out of the loop: no path on which set 0 was just requested)
+      tile(std::integral_constant<int, kAhead - 1>());
+    }
   }
   if (pending) store_slab();
   if (split) {                                                           // the wavefronts' parts of the slab, in order
@@ -357,9 +499,17 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
 // Stage B  tile[i2, column] = sum_m3 D'[.., i2] (c_alpha U3)[column, m3], 16 columns at a time, coefficients in
 //   registers; the flat image of the tile in LDS then takes the sparse entries and is streamed into W.
 // A last mode of 8 m + 1 complex columns has its last column done by vector arithmetic, not by a tile of its own.
+// Both on split bf16 operands (device_common.h).  Stage A: slot 2 j + u of lane (c, g) is part u of m2 = 16 q + 4 j + g;
+// stage B: slot 4 nc + r is register r of D' tile nc.
 constexpr int tail_rows(int CT) { return CT <= 4 ? 32 : 16; }
+// Coefficients of more than four operands' worth of columns leave no registers for the rest: they are then kept in LDS,
+// which the kernel has to spare (a tile reads CT x 3 KB of them per 16 rows).
+constexpr bool tail_coef_lds(int CT, int NC) { return CT * NC > 4; }
 constexpr int tail_pieces(int CT) { return CT == 2 ? 5 : CT == 3 ? 7 : 9; }   // complex64 pieces per lane of a tile
 __host__ __device__ constexpr int tail_slice(int M, int R) { return (R * 2 * M + 3) & ~3; }
+
+// Tiles in flight per wavefront: two where the registers hold them (see head_ahead)
+constexpr int tail_ahead(int CT, int NC, int SA) { return SA == 8 && NC == 2 ? 1 : CT == 9 || NC == 2 ? 2 : 1; }
 
 struct TailArgs {
   const float2* y1;             // (nslabs, K2, K) complex
@@ -387,7 +537,8 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, grp = lane >> 4, part = lane & 1;
   float* sD = smem + wave * slice;
-  float2* sT = reinterpret_cast<float2*>(smem + W * slice);              // U2 in operand order [16 rows][step][lane]
+  u32v4* sT = reinterpret_cast<u32v4*>(smem + W * slice);                // U2 in operand order [16 rows][quad][h, m, l][lane]
+  constexpr int KA = SA > 4 ? 2 : 1;                                     // quads of K2
   const bool vtail = (N2 & 15) == 2;
   const int NT = vtail ? N2 >> 4 : (N2 + 15) >> 4;                       // column tiles (<= CT: host)
   const bool split = a.split != 0;
@@ -407,13 +558,14 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
     }
   };
   const uint32_t slab_elems = (uint32_t)(I2 * M);
-  wraw wpre[kPre];
-  uint32_t wl0 = 0, wl1 = 0;                                             // elements past the last whole piece of the tile
+  constexpr int kAhead = tail_ahead(CT, NC, SA);
+  wraw wpre[kAhead][kPre];                                               // the tiles in flight
+  uint32_t wl0[kAhead], wl1[kAhead];                                     // elements past the last whole piece of a tile
   auto tile_elems = [&](int t) -> int { return (I2 - t * R < R ? I2 - t * R : R) * M; };
   auto tile_addr = [&](int sl, int t) -> char* {
     return reinterpret_cast<char*>(a.w) + ((uint64_t)(uint32_t)sl * slab_elems + (uint32_t)(t * R * M)) * (uint64_t)kElem;
   };
-  auto issue_w = [&](int sl, int t) {                                    // (no tile: empty descriptors)
+  auto issue_w = [&](wraw* to, uint32_t& l0, uint32_t& l1, int sl, int t) {                                    // (no tile: empty descriptors)
     const bool ok = sl < a.nslabs;
     const int n = ok ? tile_elems(t) : 0, n4 = n / WS::kElems;
     const char* base = ok ? tile_addr(sl, t) : reinterpret_cast<const char*>(a.w);
@@ -422,15 +574,15 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
       const int left = n4 * 16 - k * 4096;
       const __amdgpu_buffer_rsrc_t r = raw_buffer(base + k * 4096, (uint32_t)(left > 0 ? left : 0));
 #pragma unroll
-      for (int i = 4 * k; i < 4 * k + 4 && i < kPre; ++i) buffer_piece_load(wpre[i], r, lane * 16 + (i - 4 * k) * 1024);
+      for (int i = 4 * k; i < 4 * k + 4 && i < kPre; ++i) buffer_piece_load(to[i], r, lane * 16 + (i - 4 * k) * 1024);
     }
     const __amdgpu_buffer_rsrc_t rl = raw_buffer(base + n4 * 16, (uint32_t)((n - n4 * WS::kElems) * kElem));
     if constexpr (WDT == TGRAD_C64) {
       const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rl, lane * kElem, 0, 0);
-      wl0 = v.x;
-      wl1 = v.y;
+      l0 = v.x;
+      l1 = v.y;
     } else {
-      wl0 = __builtin_amdgcn_raw_buffer_load_b32(rl, lane * kElem, 0, 0);
+      l0 = __builtin_amdgcn_raw_buffer_load_b32(rl, lane * kElem, 0, 0);
     }
   };
   int32_t my_om = 0;
@@ -461,15 +613,23 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
     j1 = tsb[vzero + 1];
   };
   // ---- prologue: the first tile of W, its operands and the tables go in flight ----
-  issue_w(slab, ts);
-  int nslab = slab, nts = ts;
+  int nslab = slab, nts = ts;                                            // the tile after this one, the one after that
   if (slab < a.nslabs) advance(nslab, nts);
+  int s2 = nslab, t2 = nts;
+  if (nslab < a.nslabs) advance(s2, t2);
+#pragma unroll
+  for (int d = 0; d < kAhead; ++d) wl0[d] = wl1[d] = 0;
+  issue_w(wpre[0], wl0[0], wl1[0], slab, ts);
   uint32_t cj0v, cj1v, nj0v, nj1v;
   range_of(slab, ts, cj0v, cj1v);
   range_of(nslab, nts, nj0v, nj1v);
   fetch_y(slab < a.nslabs ? slab : 0);
   const FactorRef fU3 = factor_ref(a.U3, (int64_t)M * K), fU2 = factor_ref(a.U2, (int64_t)I2 * K2);
-  float2 cf[CT][NC][2], ct[NC][2];                                       // (c_alpha U3)[column][8 nc + 2 g + u]
+  // (c_alpha U3)[column][8 nc + 2 g + u], dword 2 nc + u
+  constexpr bool kInLds = tail_coef_lds(CT, NC);
+  Split8 cf[kInLds ? 1 : CT];
+  u32v4* sC = sT + ((I2 + 15) >> 4) * (KA * 192);
+  float2 ct[NC][2];
 #pragma unroll
   for (int nc = 0; nc < NC; ++nc)
 #pragma unroll
@@ -478,34 +638,68 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
 #pragma unroll
       for (int i = 0; i < CT; ++i) {
         const int m = (16 * i + col) >> 1;
-        const float2 f = factor_entry(fU3, m, k, K, k < K && m < M);
-        cf[i][nc][u] = column_coef(make_float2(a.c_alpha * f.x, a.c_alpha * f.y), part);
+        if constexpr (!kInLds) {
+          const float2 f = factor_entry(fU3, m, k, K, k < K && m < M);
+          split_at(cf[i], 2 * nc + u, column_coef(make_float2(a.c_alpha * f.x, a.c_alpha * f.y), part));
+        }
       }
       const float2 f = factor_entry(fU3, M - 1, k, K, k < K);
       ct[nc][u] = make_float2(a.c_alpha * f.x, a.c_alpha * f.y);
     }
-  stage_table(sT, ((I2 + 15) >> 4) * SA * 64, tid, (int)blockDim.x, [&](int e) -> float2 {
-    const int l = e & 63, s = (e >> 6) % SA, q = (e >> 6) / SA;
-    const int i2 = 16 * q + (l & 15), m2 = 4 * s + (l >> 4);
-    return factor_entry(fU2, i2, m2, K2, i2 < I2 && m2 < K2);
-  });
+  for (int e = tid; e < ((I2 + 15) >> 4) * KA * 64; e += (int)blockDim.x) {
+    const int l = e & 63, q = (e >> 6) % KA, i2 = 16 * ((e >> 6) / KA) + (l & 15);
+    float2 u[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int m2 = 16 * q + 4 * j + (l >> 4);
+      u[j] = factor_entry(fU2, i2, m2, K2, i2 < I2 && m2 < K2);
+    }
+    Split8 f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) split_at(f, j, u[j]);
+    u32v4* p = sT + (e >> 6) * 192 + l;
+    p[0] = f.h;
+    p[64] = f.m;
+    p[128] = f.l;
+  }
+  if constexpr (kInLds) {
+    for (int i = wave; i < CT; i += W) {
+      const int m = (16 * i + col) >> 1;
+      float2 f[2 * NC];
+#pragma unroll
+      for (int d = 0; d < 2 * NC; ++d) {
+        const int k = 8 * (d >> 1) + 2 * grp + (d & 1);
+        f[d] = factor_entry(fU3, m, k, K, k < K && m < M);
+      }
+      Split8 c = {};
+#pragma unroll
+      for (int d = 0; d < 2 * NC; ++d) split_at(c, d, column_coef(make_float2(a.c_alpha * f[d].x, a.c_alpha * f[d].y), part));
+      u32v4* p = sC + i * 192 + lane;
+      p[0] = c.h;
+      p[64] = c.m;
+      p[128] = c.l;
+    }
+  }
   uint32_t cj0 = __builtin_amdgcn_readfirstlane(cj0v), cj1 = __builtin_amdgcn_readfirstlane(cj1v);
   if (slab >= a.nslabs) cj1 = cj0;
   issue_sparse(cj0, cj1);
+  if constexpr (kAhead > 1) issue_w(wpre[kAhead - 1], wl0[kAhead - 1], wl1[kAhead - 1], nslab, nts);
   __syncthreads();                                                       // the only workgroup barrier
   bool fresh = true;                                                     // y as loaded, not yet in operand form
-  while (slab < a.nslabs) {
+  Split8 ya[KA][NC];
+  auto tile = [&](auto set) {
+    constexpr int D = decltype(set)::value;
     const uint32_t w_base = (uint32_t)slab * slab_elems + (uint32_t)(ts * R * M);
     const int n_w = tile_elems(ts), n4 = n_w / WS::kElems, rows = I2 - ts * R;
     char* w_tile = tile_addr(slab, ts);
     if (fresh) {
       // row (m3, p): re(u y) = ur yr - ui yi, im(u y) = ur yi + ui yr
 #pragma unroll
-      for (int s = 0; s < SA; ++s)
+      for (int s = 0; s < 4 * KA; ++s)
 #pragma unroll
         for (int nc = 0; nc < NC; ++nc) {
-          const float2 v = y[s][nc];
-          y[s][nc] = part ? make_float2(v.y, v.x) : make_float2(v.x, -v.y);
+          const float2 v = s < SA ? y[s < SA ? s : 0][nc] : make_float2(0.f, 0.f);
+          split_at(ya[s >> 2][nc], s & 3, part ? make_float2(v.y, v.x) : make_float2(v.x, -v.y));
         }
       fresh = false;
     }
@@ -513,33 +707,27 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
 #pragma unroll
     for (int h = 0; h < R / 16; ++h) {
       if (h == 0 || rows > 16 * h) {                                     // (wave-uniform)
-        v4f dz[NC], dzi[NC];                                             // two chains (see k_head)
+        v4f dz[NC];
 #pragma unroll
-        for (int nc = 0; nc < NC; ++nc) dz[nc] = dzi[nc] = (v4f){0.f, 0.f, 0.f, 0.f};
-        const float2* ft = sT + (size_t)(ts * (R / 16) + h) * (SA * 64) + lane;
+        for (int nc = 0; nc < NC; ++nc) dz[nc] = (v4f){0.f, 0.f, 0.f, 0.f};
+        const u32v4* ft = sT + (size_t)(ts * (R / 16) + h) * (KA * 192) + lane;
 #pragma unroll
-        for (int s = 0; s < SA; ++s) {
-          const float2 f = ft[s * 64];
+        for (int q = 0; q < KA; ++q)
+          mfma_split_b<NC>(dz, ya[q], Split8{ft[q * 192], ft[q * 192 + 64], ft[q * 192 + 128]});
+        Split8 za;
 #pragma unroll
-          for (int nc = 0; nc < NC; ++nc) {
-            dz[nc] = mfma16(y[s][nc].x, f.x, dz[nc]);
-            dzi[nc] = mfma16(y[s][nc].y, f.y, dzi[nc]);
-          }
-        }
+        for (int nc = 0; nc < NC; ++nc)
 #pragma unroll
-        for (int nc = 0; nc < NC; ++nc) dz[nc] += dzi[nc];
+          for (int u = 0; u < 2; ++u) split_at(za, 2 * nc + u, make_float2(dz[nc][2 * u], dz[nc][2 * u + 1]));
         float* sR = sD + (16 * h + 4 * grp) * N2 + col;
 #pragma unroll
         for (int i = 0; i < CT; ++i) {
           if (i < NT) {                                                  // (wave-uniform)
             v4f o = (v4f){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int nc = 0; nc < NC; ++nc)
-#pragma unroll
-              for (int u = 0; u < 2; ++u) {
-                o = mfma16(dz[nc][2 * u], cf[i][nc][u].x, o);
-                o = mfma16(dz[nc][2 * u + 1], cf[i][nc][u].y, o);
-              }
+            const Split8 b = kInLds ? Split8{sC[i * 192 + lane], sC[i * 192 + lane + 64], sC[i * 192 + lane + 128]}
+                                    : cf[kInLds ? 0 : i];
+            if constexpr (NC == 1) mfma_split_half(o, za, b);
+            else mfma_split<1>(&o, za, &b);
             if (16 * i + col < N2) {
 #pragma unroll
               for (int r = 0; r < 4; ++r) sR[r * N2 + 16 * i] = o[r];   // (rows past the slab's end: written, not streamed)
@@ -584,7 +772,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
     wave_sync();
     // ---- stream the tile into W ----
 #pragma unroll
-    for (int i = 0; i < kPre; ++i) claim_raw(wpre[i]);
+    for (int i = 0; i < kPre; ++i) claim_raw(wpre[D][i]);
 #pragma unroll
     for (int k = 0; k < (kPre + 3) / 4; ++k) {
       const int left = n4 * 16 - k * 4096;
@@ -592,7 +780,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
 #pragma unroll
       for (int i = 4 * k; i < 4 * k + 4 && i < kPre; ++i) {
         const int q = lane + i * 64;                                     // (the LDS read stays inside the slice)
-        buffer_piece_store(WS::apply(wpre[i], sD, q < n4 ? q : 0, a.decay), r, lane * 16 + (i - 4 * k) * 1024);
+        buffer_piece_store(WS::apply(wpre[D][i], sD, q < n4 ? q : 0, a.decay), r, lane * 16 + (i - 4 * k) * 1024);
       }
     }
     {                                                                    // elements past the last whole piece
@@ -600,24 +788,30 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
       if (e < n_w) {
         if constexpr (WDT == TGRAD_C64)
           *reinterpret_cast<float2*>(w_tile + (int64_t)e * kElem) =
-              make_float2(a.decay * __uint_as_float(wl0) + sD[2 * e], a.decay * __uint_as_float(wl1) + sD[2 * e + 1]);
+              make_float2(a.decay * __uint_as_float(wl0[D]) + sD[2 * e], a.decay * __uint_as_float(wl1[D]) + sD[2 * e + 1]);
         else
           *reinterpret_cast<uint32_t*>(w_tile + (int64_t)e * kElem) =
-              WStore<TGRAD_CBF16>::one(wl0, sD[2 * e], sD[2 * e + 1], a.decay);
+              WStore<TGRAD_CBF16>::one(wl0[D], sD[2 * e], sD[2 * e + 1], a.decay);
       }
     }
-    // ---- the next tile goes in flight ----
-    issue_w(nslab, nts);
-    int nnslab = nslab, nnts = nts;
-    if (nslab < a.nslabs) advance(nnslab, nnts);
+    // ---- the next tiles go in flight: the support first, which the next tile waits for (loads retire in order) ----
     cj0 = __builtin_amdgcn_readfirstlane(nj0v);
     cj1 = nslab < a.nslabs ? __builtin_amdgcn_readfirstlane(nj1v) : cj0;
     issue_sparse(cj0, cj1);
-    range_of(nnslab, nnts, nj0v, nj1v);
+    range_of(s2, t2, nj0v, nj1v);
+    issue_w(wpre[D], wl0[D], wl1[D], kAhead == 1 ? nslab : s2, kAhead == 1 ? nts : t2);
     slab = nslab;
     ts = nts;
-    nslab = nnslab;
-    nts = nnts;
+    nslab = s2;
+    nts = t2;
+    if (s2 < a.nslabs) advance(s2, t2);
+  };
+  while (slab < a.nslabs) {
+    tile(std::integral_constant<int, 0>());
+    if constexpr (kAhead > 1) {
+      if (slab >= a.nslabs) break;                                       // (out of the loop: no path on which set 0 was just requested)
+      tile(std::integral_constant<int, kAhead - 1>());
+    }
   }
 }
 
@@ -631,11 +825,14 @@ int steps_class(int K) {                        // k_head's T4
 int columns_class(int M) { return M <= 17 ? 2 : M <= 25 ? 3 : M <= 33 ? 4 : 9; }   // k_tail's CT
 int step_class(int K2) { return K2 <= 8 ? 2 : K2 <= 16 ? 4 : 8; }                  // k_tail's SA
 
-size_t head_lds(int W, int K, int I2, int M2) {
-  return (size_t)W * head_slice(K, steps_class(K)) * 4 + (size_t)((I2 + 15) / 16) * 4 * ((M2 + 15) / 16) * 512;
+size_t head_lds(int W, int ES, int K, int M, int I2, int M2) {
+  const int t4 = steps_class(K), nc = M <= 8 ? 1 : 2;
+  return (head_coef_lds(t4, nc) ? (size_t)head_quads(t4) * nc * 3072 : 0) + (size_t)W * head_slice(ES, K, t4) * 4 + (size_t)((I2 + 31) / 32) * ((M2 + 15) / 16) * kHeadItem * 16;
 }
-size_t tail_lds(int W, int M, int I2, int K2) {
-  return (size_t)W * tail_slice(M, end_tile_rows(M)) * 4 + (size_t)((I2 + 15) / 16) * step_class(K2) * 512;
+size_t tail_lds(int W, int M, int I2, int K2, int K) {
+  const int ct = columns_class(M);
+  return (size_t)W * tail_slice(M, end_tile_rows(M)) * 4 + (size_t)((I2 + 15) / 16) * (K2 > 16 ? 2 : 1) * 3072 +
+         (tail_coef_lds(ct, K <= 8 ? 1 : 2) ? (size_t)ct * 3072 : 0);
 }
 
 // From this many slabs on a wavefront takes whole ones (one wavefront per SIMD of the chip).
@@ -655,12 +852,20 @@ int end_tile_rows(int K) { return K <= 33 ? 32 : 16; }
 // Which shapes take the two kernels: K = extent of the last mode, r its rank, I2 / r2 extent and rank of mode N-1.
 // Slabs of fewer than four rows would leave seven eighths of every tile empty (and need a support offset for every few
 // entries): they stay with the kernels that cut the tensor into tiles of 32 rows wherever a slab ends.
-// (With both ranks in the upper half of a 32-wide tile, whole 32-row tiles and at least 512 slabs the 32 x 32 kernels are
-// the better ones - make_plan prefers them: whole step 128x128x128x65, r 32,32,32,16: 738 us against 758 with these;
-// 128x128x64x33, r 64,64,32,16: 351 against 377, r 32,32,17,9: 245 against 273.)
 bool ends_kernel_fits(int K, int r, int I2, int r2) {
   if (K < 2 || K > 68 || r > 16 || r2 > 32 || I2 < 4 || I2 > TGRAD_MAX_EXTENT) return false;
-  return head_lds(kMaxWaves, K, I2, r2) <= kLdsLimit / 2 && tail_lds(kMaxWaves, K, I2, r2) <= kLdsLimit / 2;
+  return head_lds(4, 2, K, r, I2, r2) <= kLdsLimit && tail_lds(4, K, I2, r2, r) <= kLdsLimit;
+}
+
+// Where the 32 x 32 kernels, if the shape suits them (512 slabs of whole 32-row tiles), are the better ones: both ranks in the
+// upper half of a 32-wide tile, or a table of conj(U2) that leaves one workgroup per compute unit, and not yet the slabs for
+// these kernels to fill the chip with.  Whole step, us, those / these: r 32,16 or 17,9 behind 8,8
+//   512 slabs: 32x17 21.1 / 21.6, 32x33 26.0 / 29.3, 128x65 60.5 / 57.3;  1024: 32x33 30.0 / 31.1, 128x65 71.6 / 82.5;
+//   2048: 32x17 32.5 / 31.2, 32x33 48.7 / 43.5, 128x65 117 / 115;  4096: 49 / 42, 66 / 60, 200 / 200;
+//   16384: 123 / 90, 158 / 139, 706 / 699;      256x13, r 20,5: 1024 slabs 60 / 52, 4096 166 / 97.
+bool wide_tiles_pay(int r, int I2, int r2, int64_t nslabs) {
+  if (r > 8 && r2 > 16) return nslabs < 2048;
+  return nslabs < 1024 && ((I2 + 31) / 32) * ((r2 + 15) / 16) * kHeadItem * 16 > (int)kLdsLimit / 2;
 }
 
 // ... and which of those it pays for.  A tile costs a wavefront the same few round trips and whole 16-row halves of matrix
@@ -676,6 +881,10 @@ bool ends_kernel_fits(int K, int r, int I2, int r2) {
 //   4096 slabs: 4x5 24 / 27, 8x33 32 / 33, 36x5 31 / 33 (the saved launches win).
 // r: 65536 slabs of 12x9 with r = 1 95 / 82, r = 6 109 / 115, r = 9 126 / 143.
 bool ends_kernel_pays(int K, int r, int I2, int r2, int64_t nslabs) {
+  // (A table that leaves room for one workgroup per compute unit is not staged for the sake of a few slabs: 16 slabs of
+  // 250x65, r 32,16, 45 / 40; 64 of 256x33 36 / 31; but 128 of 250x65 40 / 45, 2048 of 250x33 113 / 147.)
+  const size_t table = (size_t)((I2 + 15) / 16) * ((r2 + 15) / 16) * 2048;
+  if (nslabs < 128 && 16 * (size_t)head_slice(2, K, steps_class(K)) + table > kLdsLimit / 2) return false;
   if (nslabs < 8192) return true;
   const int R = end_tile_rows(K), S = (I2 + R - 1) / R, H = (I2 + 15) / 16;
   const int row = 25 + (K < 17 ? K : 17) + 5 * r;
@@ -687,8 +896,10 @@ void launch_head(hipStream_t s, const void* g, int dtype, const int32_t* omega, 
                  const float2* U3, int K, int M, const float2* U2, int I2, int M2, int64_t nslabs, float2* out) {
   const int R = end_tile_rows(K), S = (I2 + R - 1) / R;
   const bool split = nslabs < kWholeSlabs && S > 1;
-  const int W = split ? (S < kMaxWaves ? S : kMaxWaves) : nslabs >= kWholeSlabs ? kMaxWaves : 1;
-  const size_t lds = head_lds(W, K, I2, M2);
+  const int es = dtype == TGRAD_C64 ? 2 : 1;
+  const int full = head_lds(4, es, K, M, I2, M2) <= kLdsLimit / 2 ? 4 : head_lds(8, es, K, M, I2, M2) <= kLdsLimit ? 8 : 4;
+  const int W = split ? (S < 4 ? S : 4) : nslabs >= kWholeSlabs ? full : 1;
+  const size_t lds = head_lds(W, es, K, M, I2, M2);
   HeadArgs a{g, omega, tile_start, gs, U3, U2, K, M, I2, M2, S, (int)nslabs, split ? 1 : 0, magic_for(K),
              reinterpret_cast<float*>(out)};
   const int t4 = steps_class(K), nc = M <= 8 ? 1 : 2, nm = M2 <= 16 ? 1 : 2;
@@ -721,8 +932,9 @@ void launch_tail(hipStream_t s, const float2* y1, const float2* U3, int K, int M
   const int R = end_tile_rows(M), S = (I2 + R - 1) / R;
   const bool split = nslabs < kWholeSlabs;
   const int64_t units = split ? nslabs * S : nslabs;
-  const int W = units >= kWholeSlabs ? kMaxWaves : 1;
-  const size_t lds = tail_lds(W, M, I2, K2);
+  const int full = tail_lds(4, M, I2, K2, K) <= kLdsLimit / 2 ? 4 : tail_lds(8, M, I2, K2, K) <= kLdsLimit ? 8 : 4;
+  const int W = units >= kWholeSlabs ? full : 1;
+  const size_t lds = tail_lds(W, M, I2, K2, K);
   TailArgs a{y1, U2, U3, w, K, M, I2, K2, S, (int)nslabs, split ? 1 : 0, decay, c_alpha};
   const SparseAdam sp = sparse_adam(omega, tile_start, gs, ms, vs, beta1, beta2, inv_c1, inv_c2, eps, c_lambda, 0);
   const int ct = columns_class(M), nc = K <= 8 ? 1 : 2, sa = step_class(K2);

@@ -193,10 +193,9 @@ void make_plan(const tgrad_config* c, bool short_slabs_fused, Plan* p) {
       const int64_t I2 = p->shape[last - 1];
       wide = wide && (I2 % 32 == 0) && I2 <= TGRAD_MAX_EXTENT && p->rank[last - 1] <= 32 && 2 * p->rank[last] <= 32 &&
              rows / I2 >= 512 && p->shape[last] <= fused_max_last_extent();
-      // Otherwise, and wherever the ranks leave half of a 32-wide tile empty, on 16 x 16 tiles.
-      const bool full_tiles = p->rank[last] > 8 && p->rank[last - 1] > 16;
-      p->narrow = p->tile_waves > 0 && !(wide && full_tiles) &&
-                  ends_kernel_fits((int)p->shape[last], p->rank[last], (int)I2, p->rank[last - 1]);
+      // Otherwise, and wherever the 32-wide tiles are not the better ones, on 16 x 16 tiles.
+      p->narrow = p->tile_waves > 0 && ends_kernel_fits((int)p->shape[last], p->rank[last], (int)I2, p->rank[last - 1]) &&
+                  !(wide && wide_tiles_pay(p->rank[last], (int)I2, p->rank[last - 1], rows / I2));
       if (p->narrow && !wide && !short_slabs_fused &&
           !ends_kernel_pays((int)p->shape[last], p->rank[last], (int)I2, p->rank[last - 1], rows / I2)) {
         p->narrow = false;

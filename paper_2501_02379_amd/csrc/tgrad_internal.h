@@ -131,6 +131,7 @@ void launch_lupdate_fused(hipStream_t s, const float2* y1, const float2* ut, int
 // modes N-1 and N in one pass on 16 x 16 tiles (ends.hip)
 int end_tile_rows(int K);
 bool ends_kernel_fits(int K, int r, int I2, int r2);
+bool wide_tiles_pay(int r, int I2, int r2, int64_t nslabs);
 bool ends_kernel_pays(int K, int r, int I2, int r2, int64_t nslabs);
 void launch_head(hipStream_t s, const void* g, int dtype, const int32_t* omega, const uint32_t* tile_start, float2* gs,
                  const float2* U3, int K, int M, const float2* U2, int I2, int M2, int64_t nslabs, float2* out);

@@ -1,0 +1,108 @@
+"""The kernels whose float32 products run on split bf16 operands, one step or two per shape against the oracle, at the edges
+of their operands (16 rows or elements at a time), their tables and the lines between them and the kernels beside them."""
+import numpy as np
+import pytest
+
+from oracle import tgrad_oracle as O
+from paper_2501_02379_amd import synth
+from paper_2501_02379_amd import tgrad as T
+from helpers import check_parity, run_both, run_both_bf16_weights
+
+pytestmark = pytest.mark.gpu
+
+
+def _weights(shape, seed):
+    rng = np.random.default_rng(seed)
+    return (rng.standard_normal(shape) + 1j * rng.standard_normal(shape)) * 0.02
+
+
+MID_SHAPES = [
+    ((96, 140, 20, 9), (4, 70, 20, 9), 900),       # nine quads: two chunks of the table; a rank of five tiles, two launch rows
+    ((96, 256, 20, 9), (4, 60, 20, 9), 900),       # sixteen quads; an expansion whose table is cut after eight tiles
+    ((96, 128, 20, 9), (4, 16, 20, 9), 900),       # the table of one tile, all of it at once
+    ((250, 17, 16, 9), (4, 9, 16, 9), 900),        # one element past the last whole quad
+    ((250, 30, 29, 16), (4, 28, 29, 16), 900),     # 3625 groups of column pairs: several for some workgroups
+]
+
+
+@pytest.mark.parametrize("shape,ranks,k", MID_SHAPES)
+def test_middle_stages(shape, ranks, k):
+    print("[case]", shape, ranks, flush=True)
+    grads = [synth.small_case(shape, 700 + t, outlier_frac=(1, 200)) for t in range(2)]
+    W0 = _weights(shape, 21).astype(np.complex64)
+    info = run_both(T, shape, ranks, k, grads, W0, refresh_every=4, lr=2e-3, weight_decay=0.01)
+    assert all(info["omega_equal"])
+    check_parity(info, W0)
+
+
+# shape, ranks, k, gradient dtype, packed: whether the 32 x 32 kernels (which have a factor packed for them) serve it
+END_SHAPES = [
+    ((64, 32, 32, 17), (4, 4, 17, 9), 6000, "c64", False),      # 2048 slabs: the first with full ranks
+    ((89, 23, 32, 17), (4, 4, 17, 9), 6000, "c64", True),       # ... 2047
+    ((46, 45, 40, 33), (4, 4, 20, 12), 9000, "c64", False),     # coefficients in LDS, two tiles in flight, half a tile last
+    ((46, 45, 40, 33), (4, 4, 20, 12), 200000, "cbf16", False), # ... more than 64 support entries in a tile
+    ((46, 45, 24, 65), (3, 4, 17, 16), 9000, "c64", False),     # 16-row tiles in pairs
+    ((46, 45, 40, 65), (3, 4, 17, 16), 9000, "cbf16", False),   # ... three to a slab: the last alone
+    ((20, 20, 40, 50), (3, 4, 9, 9), 3000, "c64", False),       # ... shared by the wavefronts of a workgroup: never in pairs
+    ((33, 32, 24, 42), (3, 4, 9, 6), 3000, "cbf16", False),     # three quads, no remainder
+    ((33, 32, 21, 25), (3, 4, 9, 8), 3000, "c64", False),       # two quads, the second of nine elements
+    ((13, 10, 250, 34), (3, 4, 20, 10), 9000, "c64", False),    # a table that leaves one workgroup to a compute unit
+    ((40, 30, 230, 20), (3, 4, 18, 7), 9000, "c64", False),     # ... with whole slabs: eight wavefronts
+    ((10, 10, 250, 34), (3, 4, 20, 10), 9000, "c64", False),    # ... too few slabs for it: separate kernels
+    ((32, 32, 256, 13), (4, 5, 20, 5), 9000, "c64", False),     # 1024 slabs, whole 32-row tiles
+]
+
+
+@pytest.mark.parametrize("shape,ranks,k,dt,packed", END_SHAPES)
+def test_end_kernels(shape, ranks, k, dt, packed):
+    print("[case]", shape, ranks, dt, flush=True)
+    grads = [synth.small_case(shape, 720 + t, outlier_frac=(1, 200), dtype=dt) for t in range(2)]
+    W0 = _weights(shape, 22).astype(np.complex64)
+    info = run_both(T, shape, ranks, k, grads, W0, refresh_every=4, lr=2e-3, weight_decay=0.01,
+                    grad_dtype=T.TGRAD_CBF16 if dt == "cbf16" else T.TGRAD_C64)
+    assert all(info["omega_equal"])
+    check_parity(info, W0)
+    ctx = info["ctx"]
+    ctx.tgrad_set_profiling(True)
+    ctx.tgrad_refresh_factors(T.to_device_grad(grads[0]))
+    assert ("factor_pack" in ctx.tgrad_get_kernel_times()) == packed
+
+
+@pytest.mark.parametrize("shape,ranks,k", [(s, r, k) for s, r, k, dt, _ in END_SHAPES if dt == "cbf16"])
+def test_end_kernels_bf16_weights(shape, ranks, k):
+    """(Bounds as in test_bf16_weights_single_steps.)"""
+    print("[case]", shape, ranks, flush=True)
+    grads = [synth.small_case(shape, 740 + t, outlier_frac=(1, 200), dtype="cbf16") for t in range(2)]
+    info = run_both_bf16_weights(T, shape, ranks, k, grads, O.complex_to_bf16_pairs(_weights(shape, 23)), resync=True,
+                                 refresh_every=4, lr=2e-3, weight_decay=0.01, grad_dtype=T.TGRAD_CBF16)
+    for worst, frac in info["stats"]:
+        assert worst <= 1
+        assert frac <= max(5e-3, 2.0 / (2 * int(np.prod(shape))))
+
+
+def test_products_keep_float32_accuracy():
+    """A step's core gradient at entries of G between 2^-60 and 2^60, against 64 bits: every part of a float32 counts, so the
+    error stays that of float32 sums (16 roundings of 2^-24 at the depth of these chains), where two parts of three would
+    leave 2^-17."""
+    shape, ranks = (24, 20, 40, 33), (4, 5, 9, 8)
+    rng = np.random.default_rng(24)
+    for scale in (2.0 ** -60, 1.0, 2.0 ** 60):
+        g = ((rng.standard_normal(shape) + 1j * rng.standard_normal(shape)) * scale).astype(np.complex64)
+        ctx = T.Context(T.make_config(shape, ranks, 1, lr=1e-3, refresh_every=0), device="cuda:0")
+        ctx.tgrad_set_state(T.STATE_STEP, 3)
+        ctx.tgrad_set_state(T.STATE_INDICES, np.zeros(1, np.int32))
+        us = []
+        for n, (i, r) in enumerate(zip(shape, ranks)):
+            u = np.linalg.qr(rng.standard_normal((i, r)) + 1j * rng.standard_normal((i, r)))[0].astype(np.complex64)
+            ctx.tgrad_set_state(T.STATE_FACTOR0 + n, u)
+            us.append(u.astype(np.complex128))
+        ctx.tgrad_step(T.to_device_weight(np.zeros(shape, np.complex64)), T.to_device_grad(g))
+        x = g.astype(np.complex128)
+        x.reshape(-1)[0] = 0
+        for n, u in enumerate(us):
+            x = np.moveaxis(np.tensordot(u.conj(), x, axes=([0], [n])), 0, n)
+        m = ctx.tgrad_get_state(T.STATE_CORE_M).reshape(ranks).astype(np.complex128) / float(np.float32(1) - np.float32(0.9))
+        err = np.linalg.norm(m - x) / np.linalg.norm(x)
+        print("scale %g error %.2e" % (scale, err), flush=True)
+        assert err < 16 * 2.0 ** -24
+        ctx.tgrad_destroy()
