@@ -1,5 +1,7 @@
-// First and last kernel of a step on 16 x 16 matrix-core tiles, for narrow ranks and any extent of mode N-1:
+// First and last kernel of a step on 16 x 16 matrix-core tiles, for any extent of mode N-1:
 //   k_head  g_S <- G[Omega];  out[slab, m2, m3] = sum_{i2, i3} conj(U2[i2, m2]) conj(U3[i3, m3]) (G - Sparse(G, Omega))[slab, i2, i3]
+//           (or of G itself, in the two orders in which the low-rank part sees the full gradient: a gather kernel of its own
+//           took 8 us at 64x64x64x32 with 5 % of the entries, whole step 89 -> 80)
 //   k_tail  W <- (1 - lr wd) W - lr (alpha z x_(N-1) U2 x_N U3 + lambda scatter(AdamUpdate(g_S)))
 // with modes N-1 (extent I2, rank M2 <= 32) and N (extent K, rank M <= 16) in one pass over G and one over W; a
 // slab is the I2 x K block of one set of leading indices.  (contract_mfma.hip has the same two passes on 32 x 32
@@ -80,6 +82,7 @@ struct HeadArgs {
   const float2* U2;             // (I2, M2)
   int K, M, I2, M2, S, nslabs;  // S: tiles per slab
   int split;
+  int keep;                     // 1: the support is handed over, but not removed
   uint32_t magicK;
   float* out;                   // (nslabs, M2, M) complex
 };
@@ -102,7 +105,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
   const int col = lane & 15, grp = lane >> 4;
   float* sX = smem + wave * slice;
   u32v4* sT = reinterpret_cast<u32v4*>(smem + W * slice);                // conj(U2) in operand order [32 rows][nm]
-  const bool split = a.split != 0;
+  const bool split = a.split != 0, keep = a.keep != 0;
   const int nw = (int)gridDim.x * W;
   int slab = split ? (int)blockIdx.x : (int)blockIdx.x * W + wave, ts = split ? wave : 0;
   if (ts >= S) slab = a.nslabs;                                          // (a shared slab with fewer tiles than wavefronts)
@@ -327,6 +330,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
         const uint32_t e = (uint32_t)oj - e_base;
         float* p = sX + ES * (e + (pad ? div_magic(e, a.magicK) : 0u));
         a.gs[cj0 + j] = load_elem<DT>(p, 0);
+        if (keep) return;
         if constexpr (DT == TGRAD_C64) *reinterpret_cast<float2*>(p) = make_float2(0.f, 0.f);
         else *reinterpret_cast<uint32_t*>(p) = 0u;
       };
@@ -893,14 +897,14 @@ bool ends_kernel_pays(int K, int r, int I2, int r2, int64_t nslabs) {
 }
 
 void launch_head(hipStream_t s, const void* g, int dtype, const int32_t* omega, const uint32_t* tile_start, float2* gs,
-                 const float2* U3, int K, int M, const float2* U2, int I2, int M2, int64_t nslabs, float2* out) {
+                 const float2* U3, int K, int M, const float2* U2, int I2, int M2, int64_t nslabs, bool keep, float2* out) {
   const int R = end_tile_rows(K), S = (I2 + R - 1) / R;
   const bool split = nslabs < kWholeSlabs && S > 1;
   const int es = dtype == TGRAD_C64 ? 2 : 1;
   const int full = head_lds(4, es, K, M, I2, M2) <= kLdsLimit / 2 ? 4 : head_lds(8, es, K, M, I2, M2) <= kLdsLimit ? 8 : 4;
   const int W = split ? (S < 4 ? S : 4) : nslabs >= kWholeSlabs ? full : 1;
   const size_t lds = head_lds(W, es, K, M, I2, M2);
-  HeadArgs a{g, omega, tile_start, gs, U3, U2, K, M, I2, M2, S, (int)nslabs, split ? 1 : 0, magic_for(K),
+  HeadArgs a{g, omega, tile_start, gs, U3, U2, K, M, I2, M2, S, (int)nslabs, split ? 1 : 0, keep ? 1 : 0, magic_for(K),
              reinterpret_cast<float*>(out)};
   const int t4 = steps_class(K), nc = M <= 8 ? 1 : 2, nm = M2 <= 16 ? 1 : 2;
 #define TGRAD_HEAD(DT_, T_, C_, M_)                                                                          \

@@ -175,16 +175,29 @@ __global__ void k_residual_gather(float2* __restrict__ gs, const int32_t* __rest
                                   const float2* __restrict__ z, const float2* __restrict__ U, int rn, int M) {
   int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= k) return;
-  const int64_t o = omega[j];
-  const int m = (int)(o % M);
-  const int64_t a = o / M;
-  float2 acc = make_float2(0.f, 0.f);
-  for (int kk = 0; kk < rn; ++kk) {
-    float2 p = cmul(U[(int64_t)m * rn + kk], z[a * rn + kk]);
-    acc.x += p.x;
-    acc.y += p.y;
-  }
+  const uint32_t o = (uint32_t)omega[j], a = o / (uint32_t)M, m = o - a * (uint32_t)M;
+  const float2* zr = z + (int64_t)a * rn;
+  const float2* ur = U + (int64_t)m * rn;
   const float2 gv = gs[j];
+  float2 acc = make_float2(0.f, 0.f);
+  // four of both rows in flight (one after the other, and found by a 64-bit division, 419000 entries at rank 6 took 8.2 us)
+  for (int k0 = 0; k0 < rn; k0 += 4) {
+    float2 u[4], v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int kk = k0 + i < rn ? k0 + i : rn - 1;
+      u[i] = ur[kk];
+      v[i] = zr[kk];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (k0 + i < rn) {
+        const float2 p = cmul(u[i], v[i]);
+        acc.x += p.x;
+        acc.y += p.y;
+      }
+    }
+  }
   gs[j] = make_float2(gv.x - acc.x, gv.y - acc.y);
 }
 

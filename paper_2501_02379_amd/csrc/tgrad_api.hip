@@ -653,8 +653,9 @@ int do_step(tgrad_ctx* c, void* weight, const void* g) {
   const uint32_t* in_mask = remove_support ? mask : nullptr;
 
   // g_S <- Sparse(G, Omega);  g_L <- (G - g_S) x_N UN^H ... x_1 U1^H
-  // (the matrix-core first stage gathers the values it removes; otherwise a gather kernel does)
-  if (!mfma_last || !remove_support) { Scope sc_(c, KID_GATHER); launch_gather(s, g, cf.grad_dtype, omega, p.k, gs); }
+  // (k_head gathers in every order, the other matrix-core first stages the values that they remove; otherwise a gather
+  // kernel does)
+  if (!p.narrow && (!mfma_last || !remove_support)) { Scope sc_(c, KID_GATHER); launch_gather(s, g, cf.grad_dtype, omega, p.k, gs); }
   const float2* src = nullptr;
   float2* last = nullptr;                                      // the buffer `src` lies in
   for (int st = 0; st < N; ++st) {
@@ -665,8 +666,8 @@ int do_step(tgrad_ctx* c, void* weight, const void* g) {
       float2* dst1 = (N == 2) ? core_g : buf[1];
       Scope sc_(c, KID_PROJECT_FIRST);
       if (p.narrow)
-        launch_head(s, g, cf.grad_dtype, omega, in_ts, gs, U, sg.K, sg.M, c->st<float2>(p.st_U[N - 2]),
-                    (int)p.shape[N - 2], p.rank[N - 2], nslabs, dst1);
+        launch_head(s, g, cf.grad_dtype, omega, tile_start, gs, U, sg.K, sg.M, c->st<float2>(p.st_U[N - 2]),
+                    (int)p.shape[N - 2], p.rank[N - 2], nslabs, !remove_support, dst1);
       else
         launch_lproj(s, g, cf.grad_dtype, omega, in_ts, gs, U, p.rank[sg.mode], sg, p.tile_waves, dst1,
                      (int)p.shape[N - 2], p.rank[N - 2], c->w<float2>(p.ws_fpad));

@@ -134,7 +134,7 @@ bool ends_kernel_fits(int K, int r, int I2, int r2);
 bool wide_tiles_pay(int r, int I2, int r2, int64_t nslabs);
 bool ends_kernel_pays(int K, int r, int I2, int r2, int64_t nslabs);
 void launch_head(hipStream_t s, const void* g, int dtype, const int32_t* omega, const uint32_t* tile_start, float2* gs,
-                 const float2* U3, int K, int M, const float2* U2, int I2, int M2, int64_t nslabs, float2* out);
+                 const float2* U3, int K, int M, const float2* U2, int I2, int M2, int64_t nslabs, bool keep, float2* out);
 void launch_tail(hipStream_t s, const float2* y1, const float2* U3, int K, int M, const float2* U2, int I2, int K2,
                  int64_t nslabs, void* w, int wdtype, float decay, float c_alpha, const int32_t* omega,
                  const uint32_t* tile_start, const float2* gs, float2* ms, float* vs, float beta1, float beta2,
