@@ -195,38 +195,53 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
     }
     if constexpr (REST > 0) crest[nc] = coef(16 * QN + grp, nc);
   }
-  if constexpr (kInLds) {
-    for (int i = wave; i < QN * NC; i += W) {                            // [q][nc][h, m, l][lane]
-      const int q = i / NC, nc = i % NC;
-      float2 f[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) f[j] = coef(16 * q + 4 * j + grp, nc);
-      Split8 c;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) split_at(c, j, f[j]);
-      u32v4* p = sC + i * 192 + lane;
-      p[0] = c.h;
-      p[64] = c.m;
-      p[128] = c.l;
-    }
-  }
-  for (int e = lane; e < slice; e += 64) sX[e] = 0.f;                    // pads stay finite
-  for (int e = tid; e < ((I2 + 31) >> 5) * NM * 64; e += (int)blockDim.x) {
+  const int items = ((I2 + 31) >> 5) * NM * 64;
+  auto table_load = [&](int e, float2* u) {                              // (past the end: zeros)
     const int l = e & 63, nm = (e >> 6) % NM, q = (e >> 6) / NM;
     const int m2 = 16 * nm + (l & 15);
-    float2 u[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int i2 = 32 * q + 16 * (i >> 2) + 4 * (l >> 4) + (i & 3);
       u[i] = factor_entry(fU2, i2, m2, M2, i2 < I2 && m2 < M2);
     }
+  };
+  float2 tu[8];
+  if constexpr (kInLds) table_load(tid, tu);                             // in flight under the coefficients
+  if constexpr (kInLds) {
+    // [q][nc][h, m, l][lane]; a wavefront's next operands are requested together (a round trip each was 2 us of the 18 that
+    // a step of 42x42x44 takes)
+    constexpr int kItems = QN * NC < 4 ? QN * NC : 4;
+    for (int i0 = wave; i0 < QN * NC; i0 += kItems * W) {
+      float2 f[kItems][4];
+#pragma unroll
+      for (int u = 0; u < kItems; ++u) {
+        const int i = i0 + u * W < QN * NC ? i0 + u * W : i0, q = i / NC, nc = i % NC;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f[u][j] = coef(16 * q + 4 * j + grp, nc);
+      }
+#pragma unroll
+      for (int u = 0; u < kItems; ++u)
+        if (i0 + u * W < QN * NC) {
+          Split8 c;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) split_at(c, j, f[u][j]);
+          u32v4* p = sC + (i0 + u * W) * 192 + lane;
+          p[0] = c.h;
+          p[64] = c.m;
+          p[128] = c.l;
+        }
+    }
+  }
+  for (int e = lane; e < slice; e += 64) sX[e] = 0.f;                    // pads stay finite
+  for (int e = tid; e < items; e += (int)blockDim.x) {
+    if (!kInLds || e != tid) table_load(e, tu);
     Split8 fr, fi;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-      split_at(fr, d, make_float2(u[2 * d].x, u[2 * d + 1].x));
-      split_at(fi, d, make_float2(-u[2 * d].y, -u[2 * d + 1].y));
+      split_at(fr, d, make_float2(tu[2 * d].x, tu[2 * d + 1].x));
+      split_at(fi, d, make_float2(-tu[2 * d].y, -tu[2 * d + 1].y));
     }
-    u32v4* p = sT + (e >> 6) * kHeadItem + l;
+    u32v4* p = sT + (e >> 6) * kHeadItem + (e & 63);
     p[0] = fr.h; p[64] = fr.m; p[128] = fr.l;
     p[192] = fi.h; p[256] = fi.m; p[320] = fi.l;
   }
@@ -467,32 +482,60 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
     cj0 = nj0;
     cj1 = nj1;
   };
-  while (slab < a.nslabs) {
-    tile(std::integral_constant<int, 0>());
-    if constexpr (kAhead > 1) {
-      if (slab >= a.nslabs) break;                                       // (out of the loop: no path on which set 0 was just requested)
-      tile(std::integral_constant<int, kAhead - 1>());
-    }
-  }
-  if (pending) store_slab();
-  if (split) {                                                           // the wavefronts' parts of the slab, in order
-    __syncthreads();
-    constexpr int kPart = NM * NC * 4 * 64;
-#pragma unroll
-    for (int nm = 0; nm < NM; ++nm)
-#pragma unroll
-      for (int nc = 0; nc < NC; ++nc)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sX[((nm * NC + nc) * 4 + r) * 64 + lane] = value(nm, nc, r);
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < NM * NC * 4; ++e)
-      if (e % W == wave) {
-        float v = 0.f;
-        for (int w = 0; w < W; ++w) v += smem[w * slice + e * 64 + lane];
-        store_at((int)blockIdx.x, e / (4 * NC), (e >> 2) % NC, e & 3, v);
+  for (int base = (int)blockIdx.x;;) {
+    while (slab < a.nslabs) {
+      tile(std::integral_constant<int, 0>());
+      if constexpr (kAhead > 1) {
+        if (slab >= a.nslabs) break;                                       // (out of the loop: no path on which set 0 was just requested)
+        tile(std::integral_constant<int, kAhead - 1>());
       }
-    static_assert(kPart <= 1024, "head_slice");
+    }
+    if (pending) store_slab();
+    if (split) {                                                           // the wavefronts' parts of the slab, in order
+      __syncthreads();
+      constexpr int kPart = NM * NC * 4 * 64;
+#pragma unroll
+      for (int nm = 0; nm < NM; ++nm)
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) sX[((nm * NC + nc) * 4 + r) * 64 + lane] = value(nm, nc, r);
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < NM * NC * 4; ++e)
+        if (e % W == wave) {
+          float v = 0.f;
+          for (int w = 0; w < W; ++w) v += smem[w * slice + e * 64 + lane];
+          store_at(base, e / (4 * NC), (e >> 2) % NC, e & 3, v);
+        }
+      static_assert(kPart <= 1024, "head_slice");
+    }
+    // With coefficients in LDS a workgroup stays for several shared slabs: its tables leave few of its kind to a compute unit
+    // (43x16x99x50, r 32,16: 66.7 us with a workgroup per slab, 60.7).  Where they are light the code for it costs more than
+    // it saves (16x16x8x5 15.4 -> 15.9).
+    if constexpr (!kInLds) {
+      break;
+    } else {
+      base += (int)gridDim.x;
+      if (!split || base >= a.nslabs) break;
+      slab = wave < S ? base : a.nslabs;
+      ts = wave;
+      s1 = slab;
+      t1 = ts;
+      if (slab < a.nslabs) advance(s1, t1);
+      s2 = s1;
+      t2 = t1;
+      if (s1 < a.nslabs) advance(s2, t2);
+      __syncthreads();                                                       // the sums are read
+      issue_tile(raw[0], lone[0], slab, ts);
+      range_of(slab, ts, cj0v, cj1v);
+      range_of(s1, t1, nj0v, nj1v);
+      cj0 = __builtin_amdgcn_readfirstlane(cj0v);
+      cj1 = slab < a.nslabs ? __builtin_amdgcn_readfirstlane(cj1v) : cj0;
+      issue_support(cj0, cj1);
+      if constexpr (kAhead > 1) issue_tile(raw[kAhead - 1], lone[kAhead - 1], s1, t1);
+      clear();
+    }
   }
 }
 
@@ -667,21 +710,30 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
     p[128] = f.l;
   }
   if constexpr (kInLds) {
-    for (int i = wave; i < CT; i += W) {
-      const int m = (16 * i + col) >> 1;
-      float2 f[2 * NC];
+    constexpr int kItems = 3;                                            // (as in k_head)
+    for (int i0 = wave; i0 < CT; i0 += kItems * W) {
+      float2 f[kItems][2 * NC];
 #pragma unroll
-      for (int d = 0; d < 2 * NC; ++d) {
-        const int k = 8 * (d >> 1) + 2 * grp + (d & 1);
-        f[d] = factor_entry(fU3, m, k, K, k < K && m < M);
+      for (int u = 0; u < kItems; ++u) {
+        const int m = (16 * (i0 + u * W) + col) >> 1;
+#pragma unroll
+        for (int d = 0; d < 2 * NC; ++d) {
+          const int k = 8 * (d >> 1) + 2 * grp + (d & 1);
+          f[u][d] = factor_entry(fU3, m, k, K, k < K && m < M);
+        }
       }
-      Split8 c = {};
 #pragma unroll
-      for (int d = 0; d < 2 * NC; ++d) split_at(c, d, column_coef(make_float2(a.c_alpha * f[d].x, a.c_alpha * f[d].y), part));
-      u32v4* p = sC + i * 192 + lane;
-      p[0] = c.h;
-      p[64] = c.m;
-      p[128] = c.l;
+      for (int u = 0; u < kItems; ++u)
+        if (i0 + u * W < CT) {
+          Split8 c = {};
+#pragma unroll
+          for (int d = 0; d < 2 * NC; ++d)
+            split_at(c, d, column_coef(make_float2(a.c_alpha * f[u][d].x, a.c_alpha * f[u][d].y), part));
+          u32v4* p = sC + (i0 + u * W) * 192 + lane;
+          p[0] = c.h;
+          p[64] = c.m;
+          p[128] = c.l;
+        }
     }
   }
   uint32_t cj0 = __builtin_amdgcn_readfirstlane(cj0v), cj1 = __builtin_amdgcn_readfirstlane(cj1v);
@@ -902,7 +954,7 @@ void launch_head(hipStream_t s, const void* g, int dtype, const int32_t* omega, 
   const bool split = nslabs < kWholeSlabs && S > 1;
   const int es = dtype == TGRAD_C64 ? 2 : 1;
   const int full = head_lds(4, es, K, M, I2, M2) <= kLdsLimit / 2 ? 4 : head_lds(8, es, K, M, I2, M2) <= kLdsLimit ? 8 : 4;
-  const int W = split ? (S < 4 ? S : 4) : nslabs >= kWholeSlabs ? full : 1;
+  const int W = split ? (S < full ? S : full) : nslabs >= kWholeSlabs || head_coef_lds(steps_class(K), M <= 8 ? 1 : 2) ? full : 1;
   const size_t lds = head_lds(W, es, K, M, I2, M2);
   HeadArgs a{g, omega, tile_start, gs, U3, U2, K, M, I2, M2, S, (int)nslabs, split ? 1 : 0, keep ? 1 : 0, magic_for(K),
              reinterpret_cast<float*>(out)};
@@ -910,7 +962,8 @@ void launch_head(hipStream_t s, const void* g, int dtype, const int32_t* omega, 
 #define TGRAD_HEAD(DT_, T_, C_, M_)                                                                          \
   do {                                                                                                       \
     allow_lds(k_head<DT_, T_, C_, M_>, lds);                                                                 \
-    const unsigned grid = split ? (unsigned)nslabs : end_grid(k_head<DT_, T_, C_, M_>, W, lds, nslabs);      \
+    const unsigned grid = split && !head_coef_lds(T_, C_) ? (unsigned)nslabs                                 \
+                              : end_grid(k_head<DT_, T_, C_, M_>, W, lds, split ? nslabs * W : nslabs);      \
     k_head<DT_, T_, C_, M_><<<dim3(grid), dim3(64 * W), lds, s>>>(a);                                        \
   } while (0)
 #define TGRAD_HEAD_M(DT_, T_)                                                                                \
@@ -937,7 +990,8 @@ void launch_tail(hipStream_t s, const float2* y1, const float2* U3, int K, int M
   const bool split = nslabs < kWholeSlabs;
   const int64_t units = split ? nslabs * S : nslabs;
   const int full = tail_lds(4, M, I2, K2, K) <= kLdsLimit / 2 ? 4 : tail_lds(8, M, I2, K2, K) <= kLdsLimit ? 8 : 4;
-  const int W = units >= kWholeSlabs ? full : 1;
+  // (few tiles: a wavefront each, unless the coefficients in LDS are worth sharing; 42x42x44 19.6 us with single ones, 18.5)
+  const int W = units >= kWholeSlabs || tail_coef_lds(columns_class(M), K <= 8 ? 1 : 2) ? full : 1;
   const size_t lds = tail_lds(W, M, I2, K2, K);
   TailArgs a{y1, U2, U3, w, K, M, I2, K2, S, (int)nslabs, split ? 1 : 0, decay, c_alpha};
   const SparseAdam sp = sparse_adam(omega, tile_start, gs, ms, vs, beta1, beta2, inv_c1, inv_c2, eps, c_lambda, 0);
