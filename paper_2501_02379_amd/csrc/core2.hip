@@ -53,8 +53,7 @@ struct Core2Adam {
   float beta1, beta2, inv_c1, inv_c2, eps;
 };
 
-constexpr int kSlots = 4;                    // wavefronts whose partial P lies in LDS at a time
-constexpr int kSlot = 2 * 4 * 64;            // floats of one: [comp][r][lane]
+constexpr int kSlot = 2 * 4 * 64;            // floats of a wavefront's partial P in LDS: [comp][r][lane]
 
 __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
   extern __shared__ float2 sL[];
@@ -76,13 +75,12 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
   const bool active = slice < nsl && t_first < RT;     // (wave-uniform) idle wavefronts only pass the barriers
   const int64_t row = (int64_t)a.Cc * 2;      // floats between consecutive i1 of y
   const int64_t slab = row * I1;              // floats between consecutive i0 of y
-  // LDS: region A = stage-1 operands [J1][64], afterwards the partial sums ([slot][comp][r][lane] floats) and N_L in
-  // slot 0; region B = stage-4 operands [Q1][4][64]
+  // LDS: the partial sums of the eight wavefronts ([wave][comp][r][lane] floats; N_L in the first), the stage-1 operands
+  // [J1][64], the stage-4 operands [Q1][4][64], each in a place of its own: three barriers are enough
+  // (with the sums in two rounds in the place of the operands there were six; static step 32x32x12x7 21.2 us, now 20.7)
   const int nA = J1 * 64;
-  constexpr int kRedF2 = kSlots * kSlot / 2;
-  float2* sT1 = sL;
   float* red = reinterpret_cast<float*>(sL);
-  float2* sT4 = sL + (nA > kRedF2 ? nA : kRedF2);
+  float2* sT1 = sL + kWaves * kSlot / 2;
   const int nB = Q1 * 4 * 64;
 
   // ---- prologue: the first rows of y, then all operands go in flight ----
@@ -114,14 +112,6 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
   const FactorRef fU1 = factor_ref(a.U1, __builtin_amdgcn_readfirstlane(I1 * M1));
   auto u1_at = [&](int i1, int m1) -> float2 { return factor_entry(fU1, i1, m1, M1, i1 < I1 && m1 < M1); };
   auto u0_at = [&](int i0, int m0) -> float2 { return factor_entry(fU0, i0, m0, M0, i0 < I0 && m0 < M0); };
-  stage_table(sT1, nA, tid, kThreads, [&](int e) -> float2 {                 // U1[4 j + g][c]
-    const int l = e & 63, j = e >> 6;
-    return u1_at(4 * j + (l >> 4), l & 15);
-  });
-  stage_table(sT4, nB, tid, kThreads, [&](int e) -> float2 {                 // U1[16 q + c][4 g + r]
-    const int l = e & 63, r = (e >> 6) & 3, q = e >> 8;
-    return u1_at(16 * q + (l & 15), 4 * (l >> 4) + r);
-  });
   // the U0 operands of stage 2 (f2) and of stage 3 (f3) of the first row tile are requested here as well: asked for
   // where they are used, each is a memory round trip in front of its stage (16x16x8x5: 10.2 us, now 8.2)
   float2 f2[4], f3[4];
@@ -137,6 +127,12 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
     fetch_f2(t_first);
     fetch_f3(t_first);
   }
+  // both tables in one go, behind those requests: staged one after the other they were two memory round trips
+  stage_table(sT1, nA + nB, tid, kThreads, [&](int e) -> float2 {            // U1[4 j + g][c], then U1[16 q + c][4 g + r]
+    const int l = e & 63, n = (e >> 6) - J1, r = n & 3, q = n >> 2;
+    const bool first = n < 0;
+    return u1_at(first ? 4 * (n + J1) + (l >> 4) : 16 * q + (l & 15), first ? l & 15 : 4 * (l >> 4) + r);
+  });
   __syncthreads();
 
   // ---- stages 1 and 2 over this wavefront's row tiles ----
@@ -184,27 +180,11 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
       }
     }
   }
-  __syncthreads();                                             // every wavefront is through with the stage-1 operands
-  // ---- the wavefronts' partial sums: kSlots of them in LDS at a time, always the same order ----
-  auto put = [&](int slot) {
+  // ---- the wavefronts' partial sums, always added in the same order ----
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) red[slot * kSlot + (i * 4 + r) * 64 + lane] = p[i][r];
-  };
-#pragma unroll 1
-  for (int base = kSlots; base < kWaves; base += kSlots) {
-    if (wave >= base && wave < base + kSlots) put(wave - base);
-    __syncthreads();
-    if (wave < kSlots) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) p[i][r] += red[wave * kSlot + (i * 4 + r) * 64 + lane];
-    }
-    __syncthreads();
-  }
-  if (wave < kSlots) put(wave);
+    for (int r = 0; r < 4; ++r) red[wave * kSlot + (i * 4 + r) * 64 + lane] = p[i][r];
   __syncthreads();
   // ---- AdamUpdate; N_L replaces the partial sums of slot 0 (each entry is read and written by one thread) ----
   if (wave < 4) {
@@ -212,7 +192,7 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
     float* pi = pr + 256;
     float gre = 0.f, gim = 0.f;
 #pragma unroll
-    for (int w = 0; w < kSlots; ++w) {
+    for (int w = 0; w < kWaves; ++w) {
       gre += pr[w * kSlot];
       gim += pi[w * kSlot];
     }
@@ -252,7 +232,7 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
     for (int q = slice; q < Q1; q += nsl) {
       v4f z[2];
       z[0] = z[1] = (v4f){0.f, 0.f, 0.f, 0.f};
-      const float2* ft = sT4 + q * 256 + lane;
+      const float2* ft = sT1 + nA + q * 256 + lane;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {                            // re: rr ur - ri ui;  im: rr ui + ri ur
         const float2 f = ft[r * 64];
@@ -274,8 +254,7 @@ __global__ __launch_bounds__(kThreads) void k_core2(Core2Args a, Core2Adam ad) {
 }
 
 size_t core2_lds(int I1) {
-  const size_t table = (size_t)((I1 + 3) / 4) * 64 * 8, red = (size_t)kSlots * kSlot * 4;
-  return (table > red ? table : red) + (size_t)((I1 + 15) / 16) * 4 * 64 * 8;
+  return (size_t)kWaves * kSlot * 4 + (size_t)((I1 + 3) / 4) * 64 * 8 + (size_t)((I1 + 15) / 16) * 4 * 64 * 8;
 }
 
 }  // namespace
