@@ -7,17 +7,16 @@
 // slab is the I2 x K block of one set of leading indices.  (contract_mfma.hip has the same two passes on 32 x 32
 // tiles, for ranks that fill them: ends_kernel_fits has the line.)
 //
-// Why 16 x 16 (v_mfma_f32_16x16x4f32): a rank is padded to the tile, so a last-mode rank of 4 or 8 - which most
-// layers have - and a rank up to 16 of mode N-1 cost a half to a quarter of the matrix work of 32-wide tiles, and
-// fp32 matrix instructions occupy the SIMD's vector ALU: on 32-wide tiles both passes were bound by them, not by
-// memory.  The steps of the first contraction are counted in fours of K, not up to the next of two sizes.
+// Why 16 x 16: a rank is padded to the tile, so a last-mode rank of 4 or 8 - which most layers have - and a rank up to 16 of
+// mode N-1 cost a half to a quarter of the matrix work of 32-wide tiles.  Why split bf16 operands (device_common.h): in
+// float32 instructions both passes were bound by them where ranks fill the tiles or elements are bf16 (70 to 80 % of the
+// kernel's cycles), now they take 15 to 35 %, and memory, or the instructions around a small tile, bounds the pass.
 //
-// Measured (rocprofv3, us; before: 32 x 32 tiles, or separate kernels per mode where slabs were ragged or few):
-//   first pass 64x64x32x17 15.7 -> 9.9, 32x32x32x32x17 (bf16) 84.5 -> 34.8, 128x128x64x33 91.7 -> 56 (5.0 TB/s), bf16
-//   87.7 -> 46, 64x64x64x32 32.4 -> 20.2, 90x77x45x23 26.6 + 8.9 -> 19.8;
-//   last pass 128x128x64x33 112 -> 108 (5.1 TB/s), bf16 weights 98.4 -> 66, 90x77x45x23 10.6 + 26.8 -> 27.7.
-// Whole step: 16x16x8x5 21.7 -> 15.7, 64x64x32x17 39.1 -> 32.0, 90x77x45x23 89.7 -> 66.4, five-way 156 -> 107, 128x128x64x33
-// 224 -> 192, with bf16 gradients and weights 200 -> 132.
+// Measured (rocprofv3, us; 32 x 32 tiles or separate kernels -> 16 x 16 in float32 -> split operands):
+//   first pass 64x64x32x17 15.7 -> 9.9 -> 9, 32x32x32x32x17 (bf16) 84.5 -> 34.8 -> 24, 128x128x64x33 91.7 -> 56 -> 55 (5.0 TB/s;
+//   its loads alone 52.6), bf16 87.7 -> 46 -> 35, r 32,16 102 (32 x 32) -> 73, 128x128x128x65 243 (32 x 32) -> 222;
+//   last pass 128x128x64x33 112 -> 108 -> 105 (5.3 TB/s), bf16 weights 98 -> 66 -> 60, r 32,16 140 (32 x 32) -> 109,
+//   90x77x45x23 10.6 + 26.8 -> 28 -> 26.5, 128x128x128x65 434 (32 x 32) -> 440.
 //
 // Lanes: g = lane / 16, c = lane % 16.  A[i = c][k = g], B[k = g][j = c], D register r: D[i = 4 g + r][j = c].
 // Real columns are (m, p) = (re, im) parts interleaved: c = 2 m + p.

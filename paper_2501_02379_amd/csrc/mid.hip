@@ -282,6 +282,10 @@ __global__ __launch_bounds__(kThreads) void k_expand(const float* __restrict__ x
 }
 
 // ---- the same two for tensors that fill the chip, on split bf16 operands ---------------------------
+// In float32 matrix instructions these stages ran at half of those instructions' rate; in split operands (device_common.h) a
+// product takes 96 cycles for 256.  128x128x64x33, r 64,64,32,16: compression 51 -> 28 us, expansion 56 -> 34, k_core 65 -> 48;
+// 128x128x128x65, r 32,32,32,16: 27 -> 18, 29 -> 20, 20 -> 16.  Workgroups stay for several groups of columns, so that the
+// factor is cut into its parts once for them (up to 96 KB of LDS).
 // A quad is 16 rows k of the contraction: slot 2 j + part of lane (c, g) is part `part` of row 16 quad + 4 j + g.
 // A operand: (Fr, Fi) of 16 output rows, from the table in LDS [quad][tile][h, m, l][lane]; B operands from one
 // split of the column's (xr, xi): (xr, -xi) gives the real part of F x, (xi, xr) the imaginary part.
