@@ -774,8 +774,9 @@ void launch_mid(hipStream_t s, const float2* x, const float2* U, int rn, bool pr
       default: TGRAD_EX(V_, 16, S_); break;                                                          \
     }                                                                                                \
   } while (0)
-    if (vec == 2) TGRAD_EX_K(2, false);
-    else if (own) TGRAD_EX_K(1, false);
+    // (with columns of their own the wavefronts have at most kSplitRows rows here: one or two steps)
+    if (own && vec == 2) { if (ks == 1) TGRAD_EX(2, 1, false); else TGRAD_EX(2, 2, false); }
+    else if (own) { if (ks == 1) TGRAD_EX(1, 1, false); else TGRAD_EX(1, 2, false); }
     else TGRAD_EX_K(1, true);
 #undef TGRAD_EX_K
 #undef TGRAD_EX
@@ -798,8 +799,9 @@ void launch_mid(hipStream_t s, const float2* x, const float2* U, int rn, bool pr
   do {                                                                                               \
     if (project) TGRAD_MID_T(V_, true, S_); else TGRAD_MID_T(V_, false, S_);                         \
   } while (0)
-  if (vec == 2) TGRAD_MID_P(2, false);
-  else if (own) TGRAD_MID_P(1, false);
+  // (with columns of their own the wavefronts have at most kSplitRows rows here, so no more than that of rank, and compress)
+  if (own && vec == 2) TGRAD_MID(2, 1, true, false);
+  else if (own) TGRAD_MID(1, 1, true, false);
   else TGRAD_MID_P(1, true);
 #undef TGRAD_MID_P
 #undef TGRAD_MID_T
