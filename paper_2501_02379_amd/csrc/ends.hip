@@ -526,6 +526,12 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
       t2 = t1;
       if (s1 < a.nslabs) advance(s2, t2);
       __syncthreads();                                                       // the sums are read
+      // Commits leave the pads of the rows out: zeros again where the sums lay.  (A float32 read as a bf16 pair is an
+      // infinity or NaN once in 256, which the zero coefficients it meets would not take out of the product.)
+      if (pad) {
+#pragma unroll
+        for (int e = 0; e < NM * NC * 4; ++e) sX[e * 64 + lane] = 0.f;
+      }
       issue_tile(raw[0], lone[0], slab, ts);
       range_of(slab, ts, cj0v, cj1v);
       range_of(s1, t1, nj0v, nj1v);

@@ -80,6 +80,51 @@ def test_end_kernels_bf16_weights(shape, ranks, k):
         assert frac <= max(5e-3, 2.0 / (2 * int(np.prod(shape))))
 
 
+# Slabs of several tiles, fewer than 1024 of them but more than the chip has places for: a workgroup of the first kernel stays
+# for several of them.  Rows of an even number of elements are padded in LDS, and what lies there meets zero coefficients: it
+# has to be a finite number in the gradient's type, after the wavefronts have exchanged their sums through the same place too.
+# shape, ranks, k, gradient dtype, order
+SHARED_SLABS = [
+    ((24, 24, 64, 64), (6, 6, 16, 16), 9000, "cbf16", T.TGRAD_ORDER_US_LR),
+    ((43, 16, 99, 50), (14, 5, 32, 16), 9000, "cbf16", T.TGRAD_ORDER_US_LR),
+    ((43, 16, 99, 50), (14, 5, 32, 16), 9000, "c64", T.TGRAD_ORDER_US_LR),
+    ((43, 16, 99, 49), (14, 5, 32, 16), 9000, "cbf16", T.TGRAD_ORDER_US_LR),     # nothing to pad
+    ((30, 30, 48, 48), (8, 8, 12, 12), 9000, "cbf16", T.TGRAD_ORDER_US_LR),
+    ((30, 30, 48, 48), (8, 8, 12, 12), 9000, "cbf16", T.TGRAD_ORDER_SUM),
+    ((30, 30, 72, 32), (8, 8, 20, 9), 9000, "cbf16", T.TGRAD_ORDER_US_LR),       # 32-row tiles, a remainder step past the end
+    ((30, 30, 72, 32), (8, 8, 20, 9), 9000, "cbf16", T.TGRAD_ORDER_LR_US),
+    ((30, 30, 72, 26), (8, 8, 20, 12), 9000, "cbf16", T.TGRAD_ORDER_US_LR),      # ... two quads and no remainder
+]
+
+
+def _head_lds(K, r, I2, r2, elem_dwords):
+    """LDS bytes of a workgroup of the first kernel for shared slabs (coefficients, staging slices, table of conj(U))."""
+    steps = next(t for t in (3, 5, 7, 9, 13, 17) if t >= (K + 3) // 4)
+    quads = steps // 4 + (steps % 4 >= 2)
+    rows, pieces = (32, steps) if steps <= 9 else (16, (steps + 1) // 2)
+    pad = 1 - K % 2
+    elems = max(pieces * 128 + pad * (pieces * 128 // K + 1), rows * (K + pad)) + 16 * quads + 4
+    piece_slice = 4 * (-(-max(elem_dwords * elems, 1024) // 4) * 4)
+    fixed = quads * (1 if r <= 8 else 2) * 3072 + -(-I2 // 32) * (1 if r2 <= 16 else 2) * 6144
+    lds = lambda W: fixed + W * piece_slice
+    most = 4 if lds(4) <= 80 * 1024 or lds(8) > 160 * 1024 else 8
+    return lds(min(most, -(-I2 // rows)))
+
+
+@pytest.mark.parametrize("shape,ranks,k,dt,order", SHARED_SLABS)
+def test_workgroups_that_stay_for_several_slabs(shape, ranks, k, dt, order):
+    import torch
+    print("[case]", shape, ranks, dt, order, flush=True)
+    places = (160 * 1024) // _head_lds(shape[3], ranks[3], shape[2], ranks[2], 1 if dt == "cbf16" else 2)
+    assert shape[0] * shape[1] > places * torch.cuda.get_device_properties(0).multi_processor_count
+    grads = [synth.small_case(shape, 760 + t, outlier_frac=(1, 200), dtype=dt) for t in range(2)]
+    W0 = _weights(shape, 25).astype(np.complex64)
+    info = run_both(T, shape, ranks, k, grads, W0, refresh_every=4, lr=2e-3, weight_decay=0.01, order=order,
+                    grad_dtype=T.TGRAD_CBF16 if dt == "cbf16" else T.TGRAD_C64)
+    assert all(info["omega_equal"])
+    check_parity(info, W0)
+
+
 def test_products_keep_float32_accuracy():
     """A step's core gradient at entries of G between 2^-60 and 2^60, against 64 bits: every part of a float32 counts, so the
     error stays that of float32 sums (16 roundings of 2^-24 at the depth of these chains), where two parts of three would
