@@ -68,7 +68,8 @@ __host__ __device__ constexpr int head_slice(int ES, int K, int T4) {
 // Tiles in flight per wavefront.  What a compute unit has in flight decides what it streams (64-row slabs of 33 elements:
 // loads alone 4.5 TB/s with 67 KB, 5.3 with 100 KB); registers hold more of it than LDS would.
 constexpr int head_ahead(int T4, int NC) { return T4 >= 9 && NC == 2 ? 2 : T4 >= 13 ? 2 : 1; }
-// Coefficients of more than two operands' worth are kept in LDS (a tile reads them once), fewer in registers.
+// Coefficients of more than two operands' worth are kept in LDS (a tile reads them once) where a wavefront has many tiles
+// (HEAD_MANY), fewer in registers.
 constexpr bool head_coef_lds(int T4, int NC) { return head_quads(T4) * NC > 2; }
 constexpr int kHeadItem = 6 * 64;         // u32v4 of the table per 32 rows and tile of M2: (Fr, Fi) x (h, m, l) x lane
 
@@ -86,14 +87,23 @@ struct HeadArgs {
   float* out;                   // (nslabs, M2, M) complex
 };
 
+// What a launch of a class with many coefficients (head_coef_lds) looks like; the other classes are always HEAD_MANY.
+// Staging the coefficients, a second tile in flight and the waits between an operand in LDS and its product are worth their
+// while where a wavefront has many tiles.  Where it has one or two they were 1.0 to 1.7 us of 7 to 8 (head_mode has the lines).
+//   HEAD_MANY  wavefronts that walk whole slabs, workgroups that stay for several shared slabs
+//   HEAD_FEW   shared slabs, coefficients in registers, one tile in flight
+//   HEAD_ONE   one tile per wavefront: all of its operands in registers, no table, no next tile
+enum HeadMode { HEAD_MANY, HEAD_FEW, HEAD_ONE };
+
 // NC: tiles of 16 real columns (2 M), NM: tiles of 16 rows (M2)
-template <int DT, int T4, int NC, int NM>
+template <int DT, int T4, int NC, int NM, int MODE>
 __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
   typedef typename BufPair<DT>::type Raw;
   constexpr int R = head_rows(T4), TB = head_pieces(T4);
   constexpr int kPiece = (int)sizeof(Raw), kElem = kPiece / 2;           // bytes of two elements, of one
   constexpr int ES = kElem / 4;                                          // dwords of an element in LDS
-  constexpr int QN = head_quads(T4), REST = head_rest(T4), kAhead = head_ahead(T4, NC);
+  constexpr int QN = head_quads(T4), REST = head_rest(T4), kAhead = MODE == HEAD_MANY ? head_ahead(T4, NC) : 1;
+  constexpr bool ONE = MODE == HEAD_ONE;
   extern __shared__ float smem[];
   const int K = a.K, M = a.M, I2 = a.I2, M2 = a.M2, S = a.S;
   const int pad = (K & 1) ? 0 : 1, stride = ES * (K + pad);
@@ -173,9 +183,9 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
   };
   uint32_t cj0v, cj1v, nj0v, nj1v;
   range_of(slab, ts, cj0v, cj1v);
-  range_of(s1, t1, nj0v, nj1v);
+  if constexpr (!ONE) range_of(s1, t1, nj0v, nj1v);
   const FactorRef fU3 = factor_ref(a.U3, (int64_t)K * M), fU2 = factor_ref(a.U2, (int64_t)I2 * M2);
-  constexpr bool kInLds = head_coef_lds(T4, NC);
+  constexpr bool kInLds = MODE == HEAD_MANY && head_coef_lds(T4, NC);
   Split8 cq[kInLds ? 1 : QN][NC];                                        // conj(U3)[16 q + 4 j + g][column]
   u32v4* sC = sT + ((I2 + 31) >> 5) * (NM * kHeadItem);
   float2 crest[NC];
@@ -186,7 +196,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
   };
 #pragma unroll
   for (int nc = 0; nc < NC; ++nc) {
-    if constexpr (!kInLds) {
+    if constexpr (!kInLds && !ONE) {
 #pragma unroll
       for (int q = 0; q < QN; ++q)
 #pragma unroll
@@ -204,6 +214,43 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
       u[i] = factor_entry(fU2, i2, m2, M2, i2 < I2 && m2 < M2);
     }
   };
+  auto table_split = [&](const float2* u, Split8& fr, Split8& fi) {      // conj(U2): (Fr, Fi)
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      split_at(fr, d, make_float2(u[2 * d].x, u[2 * d + 1].x));
+      split_at(fi, d, make_float2(-u[2 * d].y, -u[2 * d + 1].y));
+    }
+  };
+  uint32_t cj0, cj1;
+  auto first_support = [&]() {
+    cj0 = __builtin_amdgcn_readfirstlane(cj0v);
+    cj1 = slab < a.nslabs ? __builtin_amdgcn_readfirstlane(cj1v) : cj0;
+    issue_support(cj0, cj1);
+  };
+  Split8 own_r[ONE ? NM : 1], own_i[ONE ? NM : 1];                       // (ONE) the table's rows of this wavefront's tile
+  if constexpr (ONE) {
+    float2 f[QN][NC][4], u[NM][8];
+#pragma unroll
+    for (int q = 0; q < QN; ++q)
+#pragma unroll
+      for (int nc = 0; nc < NC; ++nc)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f[q][nc][j] = coef(16 * q + 4 * j + grp, nc);
+#pragma unroll
+    for (int nm = 0; nm < NM; ++nm) table_load(((R == 32 ? ts : ts >> 1) * NM + nm) * 64 + lane, u[nm]);
+    for (int e = lane; e < slice; e += 64) sX[e] = 0.f;                  // pads stay finite
+    __builtin_amdgcn_sched_barrier(0);
+    first_support();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < QN; ++q)
+#pragma unroll
+      for (int nc = 0; nc < NC; ++nc)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) split_at(cq[q][nc], j, f[q][nc][j]);
+#pragma unroll
+    for (int nm = 0; nm < NM; ++nm) table_split(u[nm], own_r[nm], own_i[nm]);
+  }
   float2 tu[8];
   if constexpr (kInLds) table_load(tid, tu);                             // in flight under the coefficients
   if constexpr (kInLds) {
@@ -231,18 +278,16 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
         }
     }
   }
-  for (int e = lane; e < slice; e += 64) sX[e] = 0.f;                    // pads stay finite
-  for (int e = tid; e < items; e += (int)blockDim.x) {
-    if (!kInLds || e != tid) table_load(e, tu);
-    Split8 fr, fi;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      split_at(fr, d, make_float2(tu[2 * d].x, tu[2 * d + 1].x));
-      split_at(fi, d, make_float2(-tu[2 * d].y, -tu[2 * d + 1].y));
+  if constexpr (!ONE) {
+    for (int e = lane; e < slice; e += 64) sX[e] = 0.f;                  // pads stay finite
+    for (int e = tid; e < items; e += (int)blockDim.x) {
+      if (!kInLds || e != tid) table_load(e, tu);
+      Split8 fr, fi;
+      table_split(tu, fr, fi);
+      u32v4* p = sT + (e >> 6) * kHeadItem + (e & 63);
+      p[0] = fr.h; p[64] = fr.m; p[128] = fr.l;
+      p[192] = fi.h; p[256] = fi.m; p[320] = fi.l;
     }
-    u32v4* p = sT + (e >> 6) * kHeadItem + (e & 63);
-    p[0] = fr.h; p[64] = fr.m; p[128] = fr.l;
-    p[192] = fi.h; p[256] = fi.m; p[320] = fi.l;
   }
   int wofs[TB];                                                          // where the lane's pieces lie in the slice
 #pragma unroll
@@ -250,11 +295,9 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
     const int pi = lane + 64 * i;
     wofs[i] = ES * (2 * pi + (pad ? (int)div_magic(2u * (uint32_t)pi, a.magicK) : 0));
   }
-  uint32_t cj0 = __builtin_amdgcn_readfirstlane(cj0v), cj1 = __builtin_amdgcn_readfirstlane(cj1v);
-  if (slab >= a.nslabs) cj1 = cj0;
-  issue_support(cj0, cj1);
+  if constexpr (!ONE) first_support();
   if constexpr (kAhead > 1) issue_tile(raw[kAhead - 1], lone[kAhead - 1], s1, t1);   // (the loop's order of requests)
-  __syncthreads();                                                       // (the only barrier unless the slab is shared)
+  if constexpr (!ONE) __syncthreads();                                   // (the only barrier unless the slab is shared)
   if (!split && slab >= a.nslabs) return;
 
   // second-stage sums, unswapped: da = sum fr y, db = sum fi y (db of the other part is exchanged once per slab)
@@ -333,11 +376,14 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
       pending = false;
     }
     const int32_t cur_om = my_om;
-    set_fetch(kAhead == 1 ? s1 : s2, kAhead == 1 ? t1 : t2);
-    const uint32_t nj0 = __builtin_amdgcn_readfirstlane(nj0v);
-    const uint32_t nj1 = s1 < a.nslabs ? __builtin_amdgcn_readfirstlane(nj1v) : nj0;
-    issue_support(nj0, nj1);
-    range_of(s2, t2, nj0v, nj1v);
+    uint32_t nj0 = 0, nj1 = 0;
+    if constexpr (!ONE) {
+      set_fetch(kAhead == 1 ? s1 : s2, kAhead == 1 ? t1 : t2);
+      nj0 = __builtin_amdgcn_readfirstlane(nj0v);
+      nj1 = s1 < a.nslabs ? __builtin_amdgcn_readfirstlane(nj1v) : nj0;
+      issue_support(nj0, nj1);
+      range_of(s2, t2, nj0v, nj1v);
+    }
     wave_sync();
     {                                                                    // Sparse(G, Omega): hand the values over, then remove them
       auto take = [&](uint32_t j, int32_t oj) {
@@ -401,7 +447,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
           auto product = [&](int slot, const u32v4& xv, v4f* to) {
 #pragma unroll
             for (int nc = 0; nc < NC; ++nc) to[nc] = mfma_bf(xv, c[nc], to[nc]);
-            if (h == 0) issue_at(kTerms * q + slot);
+            if (!ONE && h == 0) issue_at(kTerms * q + slot);
           };
           operand(2);
           product(0, x.h, yl);
@@ -444,8 +490,8 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
 #pragma unroll
       for (int nm = 0; nm < NM; ++nm) {
         const u32v4* p = ft + nm * kHeadItem;
-        mfma_split<NC>(da[nm], Split8{p[0], p[64], p[128]}, b);
-        mfma_split<NC>(db[nm], Split8{p[192], p[256], p[320]}, b);
+        mfma_split<NC>(da[nm], ONE ? own_r[ONE ? nm : 0] : Split8{p[0], p[64], p[128]}, b);
+        mfma_split<NC>(db[nm], ONE ? own_i[ONE ? nm : 0] : Split8{p[192], p[256], p[320]}, b);
       }
     };
     if constexpr (R == 32) {
@@ -467,7 +513,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
         for (int nc = 0; nc < NC; ++nc) held[nc] = y[0][nc];
       }
     }
-    issue_lone(lone[D]);
+    if constexpr (!ONE) issue_lone(lone[D]);
     __builtin_amdgcn_s_setprio(0);
     if (!split && ts == S - 1) {
       pending = true;
@@ -484,6 +530,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
   for (int base = (int)blockIdx.x;;) {
     while (slab < a.nslabs) {
       tile(std::integral_constant<int, 0>());
+      if constexpr (ONE) break;
       if constexpr (kAhead > 1) {
         if (slab >= a.nslabs) break;                                       // (out of the loop: no path on which set 0 was just requested)
         tile(std::integral_constant<int, kAhead - 1>());
@@ -510,8 +557,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
       static_assert(kPart <= 1024, "head_slice");
     }
     // With coefficients in LDS a workgroup stays for several shared slabs: its tables leave few of its kind to a compute unit
-    // (43x16x99x50, r 32,16: 66.7 us with a workgroup per slab, 60.7).  Where they are light the code for it costs more than
-    // it saves (16x16x8x5 15.4 -> 15.9).
+    // (head_mode).  Where they are light the code for it costs more than it saves (16x16x8x5 15.4 -> 15.9).
     if constexpr (!kInLds) {
       break;
     } else {
@@ -535,9 +581,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
       issue_tile(raw[0], lone[0], slab, ts);
       range_of(slab, ts, cj0v, cj1v);
       range_of(s1, t1, nj0v, nj1v);
-      cj0 = __builtin_amdgcn_readfirstlane(cj0v);
-      cj1 = slab < a.nslabs ? __builtin_amdgcn_readfirstlane(cj1v) : cj0;
-      issue_support(cj0, cj1);
+      first_support();
       if constexpr (kAhead > 1) issue_tile(raw[kAhead - 1], lone[kAhead - 1], s1, t1);
       clear();
     }
@@ -554,8 +598,8 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
 // Both on split bf16 operands (device_common.h).  Stage A: slot 2 j + u of lane (c, g) is part u of m2 = 16 q + 4 j + g;
 // stage B: slot 4 nc + r is register r of D' tile nc.
 constexpr int tail_rows(int CT) { return CT <= 4 ? 32 : 16; }
-// Coefficients of more than four operands' worth of columns leave no registers for the rest: they are then kept in LDS,
-// which the kernel has to spare (a tile reads CT x 3 KB of them per 16 rows).
+// Coefficients of more than four operands' worth of columns leave no registers for a next tile: they are then kept in LDS,
+// which the kernel has to spare (a tile reads CT x 3 KB of them per 16 rows), unless there is no next tile (ONE).
 constexpr bool tail_coef_lds(int CT, int NC) { return CT * NC > 4; }
 constexpr int tail_pieces(int CT) { return CT == 2 ? 5 : CT == 3 ? 7 : 9; }   // complex64 pieces per lane of a tile
 __host__ __device__ constexpr int tail_slice(int M, int R) { return (R * 2 * M + 3) & ~3; }
@@ -573,7 +617,9 @@ struct TailArgs {
   float decay, c_alpha;
 };
 
-template <int WDT, int CT, int NC, int SA>
+// ONE: a workgroup is one wavefront with one tile
+// (of a class with many coefficients, tail_coef_lds): no table, no next tile
+template <int WDT, int CT, int NC, int SA, bool ONE>
 __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAdam sp) {
   typedef WStore<WDT> WS;
   typedef typename WS::raw wraw;
@@ -610,7 +656,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
     }
   };
   const uint32_t slab_elems = (uint32_t)(I2 * M);
-  constexpr int kAhead = tail_ahead(CT, NC, SA);
+  constexpr int kAhead = ONE ? 1 : tail_ahead(CT, NC, SA);
   wraw wpre[kAhead][kPre];                                               // the tiles in flight
   uint32_t wl0[kAhead], wl1[kAhead];                                     // elements past the last whole piece of a tile
   auto tile_elems = [&](int t) -> int { return (I2 - t * R < R ? I2 - t * R : R) * M; };
@@ -674,11 +720,11 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
   issue_w(wpre[0], wl0[0], wl1[0], slab, ts);
   uint32_t cj0v, cj1v, nj0v, nj1v;
   range_of(slab, ts, cj0v, cj1v);
-  range_of(nslab, nts, nj0v, nj1v);
+  if constexpr (!ONE) range_of(nslab, nts, nj0v, nj1v);
   fetch_y(slab < a.nslabs ? slab : 0);
   const FactorRef fU3 = factor_ref(a.U3, (int64_t)M * K), fU2 = factor_ref(a.U2, (int64_t)I2 * K2);
   // (c_alpha U3)[column][8 nc + 2 g + u], dword 2 nc + u
-  constexpr bool kInLds = tail_coef_lds(CT, NC);
+  constexpr bool kInLds = !ONE && tail_coef_lds(CT, NC);
   Split8 cf[kInLds ? 1 : CT];
   u32v4* sC = sT + ((I2 + 15) >> 4) * (KA * 192);
   float2 ct[NC][2];
@@ -698,21 +744,39 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
       const float2 f = factor_entry(fU3, M - 1, k, K, k < K);
       ct[nc][u] = make_float2(a.c_alpha * f.x, a.c_alpha * f.y);
     }
-  for (int e = tid; e < ((I2 + 15) >> 4) * KA * 64; e += (int)blockDim.x) {
+  auto table_load = [&](int e, float2* u) {
     const int l = e & 63, q = (e >> 6) % KA, i2 = 16 * ((e >> 6) / KA) + (l & 15);
-    float2 u[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int m2 = 16 * q + 4 * j + (l >> 4);
       u[j] = factor_entry(fU2, i2, m2, K2, i2 < I2 && m2 < K2);
     }
-    Split8 f;
+  };
+  Split8 own[ONE ? R / 16 : 1][ONE ? KA : 1];                            // (ONE) the table's rows of the tile
+  if constexpr (ONE) {
+    float2 u[R / 16][KA][4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) split_at(f, j, u[j]);
-    u32v4* p = sT + (e >> 6) * 192 + l;
-    p[0] = f.h;
-    p[64] = f.m;
-    p[128] = f.l;
+    for (int h = 0; h < R / 16; ++h)
+#pragma unroll
+      for (int q = 0; q < KA; ++q) table_load(((ts * (R / 16) + h) * KA + q) * 64 + lane, u[h][q]);
+#pragma unroll
+    for (int h = 0; h < R / 16; ++h)
+#pragma unroll
+      for (int q = 0; q < KA; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) split_at(own[h][q], j, u[h][q][j]);
+  } else {
+    for (int e = tid; e < ((I2 + 15) >> 4) * KA * 64; e += (int)blockDim.x) {
+      float2 u[4];
+      table_load(e, u);
+      Split8 f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) split_at(f, j, u[j]);
+      u32v4* p = sT + (e >> 6) * 192 + (e & 63);
+      p[0] = f.h;
+      p[64] = f.m;
+      p[128] = f.l;
+    }
   }
   if constexpr (kInLds) {
     constexpr int kItems = 3;                                            // (as in k_head)
@@ -745,7 +809,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
   if (slab >= a.nslabs) cj1 = cj0;
   issue_sparse(cj0, cj1);
   if constexpr (kAhead > 1) issue_w(wpre[kAhead - 1], wl0[kAhead - 1], wl1[kAhead - 1], nslab, nts);
-  __syncthreads();                                                       // the only workgroup barrier
+  if constexpr (!ONE) __syncthreads();                                   // the only workgroup barrier
   bool fresh = true;                                                     // y as loaded, not yet in operand form
   Split8 ya[KA][NC];
   auto tile = [&](auto set) {
@@ -774,7 +838,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
         const u32v4* ft = sT + (size_t)(ts * (R / 16) + h) * (KA * 192) + lane;
 #pragma unroll
         for (int q = 0; q < KA; ++q)
-          mfma_split_b<NC>(dz, ya[q], Split8{ft[q * 192], ft[q * 192 + 64], ft[q * 192 + 128]});
+          mfma_split_b<NC>(dz, ya[q], ONE ? own[ONE ? h : 0][ONE ? q : 0] : Split8{ft[q * 192], ft[q * 192 + 64], ft[q * 192 + 128]});
         Split8 za;
 #pragma unroll
         for (int nc = 0; nc < NC; ++nc)
@@ -814,7 +878,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
         }
       }
     }
-    if (nslab < a.nslabs && nslab != slab) {                             // (wave-uniform) the next tile opens another slab
+    if (!ONE && nslab < a.nslabs && nslab != slab) {                             // (wave-uniform) the next tile opens another slab
       fetch_y(nslab);
       fresh = true;
     }
@@ -855,6 +919,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
               WStore<TGRAD_CBF16>::one(wl0[D], sD[2 * e], sD[2 * e + 1], a.decay);
       }
     }
+    if constexpr (ONE) return;
     // ---- the next tiles go in flight: the support first, which the next tile waits for (loads retire in order) ----
     cj0 = __builtin_amdgcn_readfirstlane(nj0v);
     cj1 = nslab < a.nslabs ? __builtin_amdgcn_readfirstlane(nj1v) : cj0;
@@ -869,6 +934,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
   };
   while (slab < a.nslabs) {
     tile(std::integral_constant<int, 0>());
+    if constexpr (ONE) break;
     if constexpr (kAhead > 1) {
       if (slab >= a.nslabs) break;                                       // (out of the loop: no path on which set 0 was just requested)
       tile(std::integral_constant<int, kAhead - 1>());
@@ -886,12 +952,15 @@ int steps_class(int K) {                        // k_head's T4
 int columns_class(int M) { return M <= 17 ? 2 : M <= 25 ? 3 : M <= 33 ? 4 : 9; }   // k_tail's CT
 int step_class(int K2) { return K2 <= 8 ? 2 : K2 <= 16 ? 4 : 8; }                  // k_tail's SA
 
-size_t head_lds(int W, int ES, int K, int M, int I2, int M2) {
+size_t head_lds(int mode, int W, int ES, int K, int M, int I2, int M2) {
   const int t4 = steps_class(K), nc = M <= 8 ? 1 : 2;
-  return (head_coef_lds(t4, nc) ? (size_t)head_quads(t4) * nc * 3072 : 0) + (size_t)W * head_slice(ES, K, t4) * 4 + (size_t)((I2 + 31) / 32) * ((M2 + 15) / 16) * kHeadItem * 16;
+  const size_t slices = (size_t)W * head_slice(ES, K, t4) * 4;
+  if (mode == HEAD_ONE) return slices;
+  return (mode == HEAD_MANY && head_coef_lds(t4, nc) ? (size_t)head_quads(t4) * nc * 3072 : 0) + slices + (size_t)((I2 + 31) / 32) * ((M2 + 15) / 16) * kHeadItem * 16;
 }
-size_t tail_lds(int W, int M, int I2, int K2, int K) {
+size_t tail_lds(int W, int M, int I2, int K2, int K, bool one = false) {
   const int ct = columns_class(M);
+  if (one) return (size_t)tail_slice(M, end_tile_rows(M)) * 4;
   return (size_t)W * tail_slice(M, end_tile_rows(M)) * 4 + (size_t)((I2 + 15) / 16) * (K2 > 16 ? 2 : 1) * 3072 +
          (tail_coef_lds(ct, K <= 8 ? 1 : 2) ? (size_t)ct * 3072 : 0);
 }
@@ -915,7 +984,7 @@ int end_tile_rows(int K) { return K <= 33 ? 32 : 16; }
 // entries): they stay with the kernels that cut the tensor into tiles of 32 rows wherever a slab ends.
 bool ends_kernel_fits(int K, int r, int I2, int r2) {
   if (K < 2 || K > 68 || r > 16 || r2 > 32 || I2 < 4 || I2 > TGRAD_MAX_EXTENT) return false;
-  return head_lds(4, 2, K, r, I2, r2) <= kLdsLimit && tail_lds(4, K, I2, r2, r) <= kLdsLimit;
+  return head_lds(HEAD_MANY, 4, 2, K, r, I2, r2) <= kLdsLimit && tail_lds(4, K, I2, r2, r) <= kLdsLimit;
 }
 
 // Where the 32 x 32 kernels, if the shape suits them (512 slabs of whole 32-row tiles), are the better ones: both ranks in the
@@ -953,24 +1022,76 @@ bool ends_kernel_pays(int K, int r, int I2, int r2, int64_t nslabs) {
   return I2 * (row < 70 ? row : 70) >= tiles;
 }
 
+namespace {
+
+// (One class more: where slabs of four tiles meet two tiles of rank, its table leaves a compute unit one workgroup of four
+// wavefronts.  390 slabs of 118x30, r 23,5 13.5 us, now 9.0; 780 of 100x29, r 32,8 25.6, now 14.3.)
+constexpr bool head_has_one(int DT, int T4, int NC, int NM) {
+  return head_coef_lds(T4, NC) || (DT == TGRAD_C64 && T4 == 9 && NC == 1 && NM == 2);
+}
+
+// Which of the three HEAD_ modes, while slabs are too few for a wavefront to walk whole ones (us, k_head alone, r: ranks of
+// the two modes; the last figure is the kernel on float32 instructions that these took the place of):
+//   HEAD_ONE for slabs of up to four tiles, and of up to eight if all of them are resident at once (a workgroup of 5 to 8
+//     wavefronts has two on some SIMD, so it is asked about as one of 8).  ONE / FEW / MANY / float32: 11x9x29, r 2,9
+//     5.3 / 5.9 / 7.1 / 5.9; 42x42x44, r 13,14 6.6 / 7.4 / 8.7 / 7.3; 900 slabs of 42x44, r 32,12 16 / 22 / 20 / 18; 400 of 78x30,
+//     r 27,12 11.9 / 12.6 / 14.0 / 13.8; but 306 slabs of six tiles, 82x49, r 6,9 15.5 / 13.0 / 13.5 / 12.6;
+//   HEAD_FEW for complex64 G where two workgroups fit a compute unit, and for rows of up to 52 elements no more than three
+//     slabs per compute unit.  FEW / MANY / float32: 380 slabs of 86x61, r 19,5 12.6 / 15.7 / 12.4; 484 of 79x39, r 19,9
+//     14.4 / 17.8 / 13.9; 841 of 90x67, r 4,12 26.3 / 29.6 / 26.7; 688 of 99x50, r 32,16 25.2 / 28.7 / 27.0; but 936 of 100x43,
+//     r 15,14 23.7 / 22.4 / 22.7; with one workgroup, 552 of 99x55, r 19,12 36 / 28 / 27; with bf16 G, which takes half the LDS
+//     and three products of six, 784 of 77x63, r 22,11 24.3 / 22.4 / 29.1;
+//   HEAD_MANY for the rest.
+template <int DT, int T4, int NC, int NM>
+int head_mode(int64_t nslabs, int S, int es, int K, int M, int I2, int M2) {
+  if (!head_has_one(DT, T4, NC, NM) || nslabs >= kWholeSlabs) return HEAD_MANY;
+  if (!head_coef_lds(T4, NC)) return S == 4 && head_lds(HEAD_MANY, 4, es, K, M, I2, M2) > kLdsLimit / 2 ? HEAD_ONE : HEAD_MANY;
+  if (S <= 4) return HEAD_ONE;
+  if constexpr (head_coef_lds(T4, NC)) {
+    const auto one = k_head<DT, T4, NC, NM, HEAD_ONE>;
+    const size_t lds = head_lds(HEAD_ONE, S, es, K, M, I2, M2);
+    if (S <= kMaxWaves && allow_lds(one, lds) &&
+        nslabs <= (int64_t)compute_units() * resident_blocks(one, 64 * kMaxWaves, lds))
+      return HEAD_ONE;
+  }
+  const bool few = DT == TGRAD_C64 && (T4 == 17 || nslabs <= 3 * (int64_t)compute_units());
+  return few && head_lds(HEAD_FEW, 4, es, K, M, I2, M2) <= kLdsLimit / 2 ? HEAD_FEW : HEAD_MANY;
+}
+
+template <int DT, int T4, int NC, int NM, int MODE>
+void launch_head_as(hipStream_t s, const HeadArgs& a, int W, size_t lds, int64_t nslabs) {
+  const auto kern = k_head<DT, T4, NC, NM, MODE>;
+  allow_lds(kern, lds);
+  const bool stay = MODE == HEAD_MANY && (!a.split || head_coef_lds(T4, NC));
+  const unsigned grid = stay ? end_grid(kern, W, lds, a.split ? nslabs * W : nslabs) : (unsigned)nslabs;
+  kern<<<dim3(grid), dim3(64 * W), lds, s>>>(a);
+}
+
+template <int DT, int T4, int NC, int NM>
+void launch_head_of(hipStream_t s, const HeadArgs& a, int64_t nslabs) {
+  constexpr int es = DT == TGRAD_C64 ? 2 : 1;
+  const int mode = head_mode<DT, T4, NC, NM>(nslabs, a.S, es, a.K, a.M, a.I2, a.M2);
+  auto lds = [&](int W) { return head_lds(mode, W, es, a.K, a.M, a.I2, a.M2); };
+  const int full = mode == HEAD_FEW || lds(4) <= kLdsLimit / 2 ? 4 : lds(8) <= kLdsLimit ? 8 : 4;
+  const int W = mode == HEAD_ONE ? a.S : a.split ? (a.S < full ? a.S : full) : nslabs >= kWholeSlabs ? full : 1;
+  if constexpr (head_has_one(DT, T4, NC, NM)) {
+    if (mode == HEAD_ONE) return launch_head_as<DT, T4, NC, NM, HEAD_ONE>(s, a, W, lds(W), nslabs);
+    if constexpr (DT == TGRAD_C64 && head_coef_lds(T4, NC))
+      if (mode == HEAD_FEW) return launch_head_as<DT, T4, NC, NM, HEAD_FEW>(s, a, W, lds(W), nslabs);
+  }
+  launch_head_as<DT, T4, NC, NM, HEAD_MANY>(s, a, W, lds(W), nslabs);
+}
+
+}  // namespace
+
 void launch_head(hipStream_t s, const void* g, int dtype, const int32_t* omega, const uint32_t* tile_start, float2* gs,
                  const float2* U3, int K, int M, const float2* U2, int I2, int M2, int64_t nslabs, bool keep, float2* out) {
   const int R = end_tile_rows(K), S = (I2 + R - 1) / R;
   const bool split = nslabs < kWholeSlabs && S > 1;
-  const int es = dtype == TGRAD_C64 ? 2 : 1;
-  const int full = head_lds(4, es, K, M, I2, M2) <= kLdsLimit / 2 ? 4 : head_lds(8, es, K, M, I2, M2) <= kLdsLimit ? 8 : 4;
-  const int W = split ? (S < full ? S : full) : nslabs >= kWholeSlabs || head_coef_lds(steps_class(K), M <= 8 ? 1 : 2) ? full : 1;
-  const size_t lds = head_lds(W, es, K, M, I2, M2);
   HeadArgs a{g, omega, tile_start, gs, U3, U2, K, M, I2, M2, S, (int)nslabs, split ? 1 : 0, keep ? 1 : 0, magic_for(K),
              reinterpret_cast<float*>(out)};
   const int t4 = steps_class(K), nc = M <= 8 ? 1 : 2, nm = M2 <= 16 ? 1 : 2;
-#define TGRAD_HEAD(DT_, T_, C_, M_)                                                                          \
-  do {                                                                                                       \
-    allow_lds(k_head<DT_, T_, C_, M_>, lds);                                                                 \
-    const unsigned grid = split && !head_coef_lds(T_, C_) ? (unsigned)nslabs                                 \
-                              : end_grid(k_head<DT_, T_, C_, M_>, W, lds, split ? nslabs * W : nslabs);      \
-    k_head<DT_, T_, C_, M_><<<dim3(grid), dim3(64 * W), lds, s>>>(a);                                        \
-  } while (0)
+#define TGRAD_HEAD(DT_, T_, C_, M_) launch_head_of<DT_, T_, C_, M_>(s, a, nslabs)
 #define TGRAD_HEAD_M(DT_, T_)                                                                                \
   do {                                                                                                       \
     if (nc == 1) { if (nm == 1) TGRAD_HEAD(DT_, T_, 1, 1); else TGRAD_HEAD(DT_, T_, 1, 2); }                 \
@@ -995,17 +1116,28 @@ void launch_tail(hipStream_t s, const float2* y1, const float2* U3, int K, int M
   const bool split = nslabs < kWholeSlabs;
   const int64_t units = split ? nslabs * S : nslabs;
   const int full = tail_lds(4, M, I2, K2, K) <= kLdsLimit / 2 ? 4 : tail_lds(8, M, I2, K2, K) <= kLdsLimit ? 8 : 4;
-  // (few tiles: a wavefront each, unless the coefficients in LDS are worth sharing; 42x42x44 19.6 us with single ones, 18.5)
-  const int W = units >= kWholeSlabs || tail_coef_lds(columns_class(M), K <= 8 ? 1 : 2) ? full : 1;
-  const size_t lds = tail_lds(W, M, I2, K2, K);
+  // Few tiles: a wavefront each.  Where coefficients go to LDS (tail_coef_lds) it then takes its operands straight into
+  // registers; while all such tiles are resident that is the faster one for up to 8 columns of rank, beyond that up to
+  // three per compute unit.  Us, those / LDS / float32 operands as before: 42x42x44, r 13,14 5.8 / 7.4 / 6.9; 108x58x67, r 17,16 8.0 /
+  // 10.7 / 10.0; 380 slabs of 86x61, r 19,5 11.0 / 13.9 / 14.4; 552 of 82x54, r 22,8 14.3 / 13.6 / 16.1; 324 of 65x58, r 21,14
+  // 12.9 / 11.4 / 15.0.
+  const bool one = tail_coef_lds(columns_class(M), K <= 8 ? 1 : 2) && split && units <= (K <= 8 ? 3 * kWholeSlabs : 768);
+  const int W = units >= kWholeSlabs && !one ? full : 1;
+  const size_t lds = tail_lds(W, M, I2, K2, K, one);
   TailArgs a{y1, U2, U3, w, K, M, I2, K2, S, (int)nslabs, split ? 1 : 0, decay, c_alpha};
   const SparseAdam sp = sparse_adam(omega, tile_start, gs, ms, vs, beta1, beta2, inv_c1, inv_c2, eps, c_lambda, 0);
   const int ct = columns_class(M), nc = K <= 8 ? 1 : 2, sa = step_class(K2);
 #define TGRAD_TAIL(WD_, T_, C_, A_)                                                                          \
   do {                                                                                                       \
-    allow_lds(k_tail<WD_, T_, C_, A_>, lds);                                                                 \
-    const unsigned grid = end_grid(k_tail<WD_, T_, C_, A_>, W, lds, units);                                  \
-    k_tail<WD_, T_, C_, A_><<<dim3(grid), dim3(64 * W), lds, s>>>(a, sp);                                    \
+    if constexpr (tail_coef_lds(T_, C_)) {                                                                   \
+      if (one) {                                                                                             \
+        k_tail<WD_, T_, C_, A_, true><<<dim3((unsigned)units), dim3(64), lds, s>>>(a, sp);                   \
+        break;                                                                                               \
+      }                                                                                                      \
+    }                                                                                                        \
+    allow_lds(k_tail<WD_, T_, C_, A_, false>, lds);                                                          \
+    const unsigned grid = end_grid(k_tail<WD_, T_, C_, A_, false>, W, lds, units);                           \
+    k_tail<WD_, T_, C_, A_, false><<<dim3(grid), dim3(64 * W), lds, s>>>(a, sp);                             \
   } while (0)
 #define TGRAD_TAIL_A(WD_, T_, C_)                                                                            \
   do {                                                                                                       \

@@ -80,20 +80,72 @@ def test_end_kernels_bf16_weights(shape, ranks, k):
         assert frac <= max(5e-3, 2.0 / (2 * int(np.prod(shape))))
 
 
-# Slabs of several tiles, fewer than 1024 of them but more than the chip has places for: a workgroup of the first kernel stays
-# for several of them.  Rows of an even number of elements are padded in LDS, and what lies there meets zero coefficients: it
-# has to be a finite number in the gradient's type, after the wavefronts have exchanged their sums through the same place too.
+# Fewer than 1024 slabs whose last mode has many coefficients: one tile per wavefront while slabs have four tiles at most or
+# all of them are resident, coefficients in registers for complex64 beyond that; last kernel: one tile per wavefront up to
+# 768 tiles (rank above 8) or 3072.
+# shape, ranks, k, gradient dtype
+FEW_TILES = [
+    ((11, 9, 29), (4, 2, 9), 60, "c64"),                    # one tile of nine rows
+    ((40, 33, 22), (6, 32, 10), 800, "cbf16"),              # 32 + 1 rows, two tiles of rank each
+    ((9, 10, 37), (4, 2, 16), 90, "cbf16"),                 # 16-row tiles, one to a slab
+    ((12, 17, 34), (5, 16, 9), 200, "c64"),                 # 16 + 1 rows: an even tile and an odd one, padded rows
+    ((7, 64, 52), (3, 17, 8), 500, "c64"),                  # four tiles, three quads and a remainder step
+    ((7, 65, 68), (3, 9, 16), 500, "cbf16"),                # ... five, the last of one row
+    ((6, 128, 53), (3, 32, 5), 900, "c64"),                 # ... eight
+    ((6, 129, 53), (3, 20, 5), 900, "c64"),                 # ... nine: one more than that takes
+    ((9, 150, 26), (3, 20, 12), 900, "c64"),                # five tiles of 32 rows (9 x 26 > 150: a Gram matrix of full rank)
+    ((31, 33, 20, 33), (4, 5, 7, 12), 3000, "c64"),         # 1023 slabs of one tile
+    ((32, 32, 20, 33), (4, 5, 7, 12), 3000, "c64"),         # 1024: whole slabs
+    ((24, 32, 12, 44), (4, 5, 5, 9), 3000, "cbf16"),        # 768 tiles for the last kernel
+    ((27, 29, 12, 44), (4, 5, 5, 9), 3000, "cbf16"),        # ... 783
+    ((24, 32, 60, 34), (4, 5, 9, 6), 9000, "c64"),          # 3072 tiles, rank 6
+    ((25, 31, 60, 34), (4, 5, 9, 6), 9000, "c64"),          # ... 3100
+    ((19, 20, 86, 61), (4, 5, 19, 5), 9000, "c64"),         # 380 slabs of six tiles: coefficients in registers, shared slabs
+    ((21, 21, 97, 53), (5, 5, 7, 11), 9000, "c64"),         # ... of seven, one tile of rank
+    ((17, 18, 82, 36), (4, 4, 6, 9), 9000, "c64"),          # ... no remainder
+    ((13, 30, 118, 30), (3, 7, 23, 5), 9000, "c64"),        # the class whose table alone leaves one workgroup to a compute unit
+    ((13, 30, 118, 30), (3, 7, 23, 5), 9000, "cbf16"),      # ... in bf16 there is room
+]
+
+
+@pytest.mark.parametrize("shape,ranks,k,dt", FEW_TILES)
+def test_few_tiles_of_many_coefficients(shape, ranks, k, dt):
+    print("[case]", shape, ranks, dt, flush=True)
+    grads = [synth.small_case(shape, 780 + t, outlier_frac=(1, 200), dtype=dt) for t in range(2)]
+    W0 = _weights(shape, 26).astype(np.complex64)
+    info = run_both(T, shape, ranks, k, grads, W0, refresh_every=4, lr=2e-3, weight_decay=0.01,
+                    grad_dtype=T.TGRAD_CBF16 if dt == "cbf16" else T.TGRAD_C64)
+    assert all(info["omega_equal"])
+    check_parity(info, W0)
+
+
+@pytest.mark.parametrize("shape,ranks,k", [(s, r, k) for s, r, k, dt in FEW_TILES if dt == "cbf16"])
+def test_few_tiles_bf16_weights(shape, ranks, k):
+    """(Bounds as in test_bf16_weights_single_steps.)"""
+    print("[case]", shape, ranks, flush=True)
+    grads = [synth.small_case(shape, 790 + t, outlier_frac=(1, 200), dtype="cbf16") for t in range(2)]
+    info = run_both_bf16_weights(T, shape, ranks, k, grads, O.complex_to_bf16_pairs(_weights(shape, 27)), resync=True,
+                                 refresh_every=4, lr=2e-3, weight_decay=0.01, grad_dtype=T.TGRAD_CBF16)
+    for worst, frac in info["stats"]:
+        assert worst <= 1
+        assert frac <= max(5e-3, 2.0 / (2 * int(np.prod(shape))))
+
+
+# Slabs of five to eight tiles, fewer than 1024 of them but more than the chip has places for: a workgroup of the first kernel
+# stays for several of them (bf16 gradients, or a table too large for two workgroups).  Rows of an even number of elements are
+# padded in LDS, and what lies there meets zero coefficients: it has to be a finite number in the gradient's type, after the
+# wavefronts have exchanged their sums through the same place too.
 # shape, ranks, k, gradient dtype, order
 SHARED_SLABS = [
-    ((24, 24, 64, 64), (6, 6, 16, 16), 9000, "cbf16", T.TGRAD_ORDER_US_LR),
+    ((28, 28, 80, 64), (6, 6, 16, 16), 9000, "cbf16", T.TGRAD_ORDER_US_LR),
     ((43, 16, 99, 50), (14, 5, 32, 16), 9000, "cbf16", T.TGRAD_ORDER_US_LR),
-    ((43, 16, 99, 50), (14, 5, 32, 16), 9000, "c64", T.TGRAD_ORDER_US_LR),
     ((43, 16, 99, 49), (14, 5, 32, 16), 9000, "cbf16", T.TGRAD_ORDER_US_LR),     # nothing to pad
-    ((30, 30, 48, 48), (8, 8, 12, 12), 9000, "cbf16", T.TGRAD_ORDER_US_LR),
-    ((30, 30, 48, 48), (8, 8, 12, 12), 9000, "cbf16", T.TGRAD_ORDER_SUM),
-    ((30, 30, 72, 32), (8, 8, 20, 9), 9000, "cbf16", T.TGRAD_ORDER_US_LR),       # 32-row tiles, a remainder step past the end
-    ((30, 30, 72, 32), (8, 8, 20, 9), 9000, "cbf16", T.TGRAD_ORDER_LR_US),
-    ((30, 30, 72, 26), (8, 8, 20, 12), 9000, "cbf16", T.TGRAD_ORDER_US_LR),      # ... two quads and no remainder
+    ((24, 23, 114, 54), (6, 5, 32, 5), 9000, "c64", T.TGRAD_ORDER_US_LR),
+    ((30, 30, 80, 48), (8, 8, 12, 12), 9000, "cbf16", T.TGRAD_ORDER_US_LR),
+    ((30, 30, 80, 48), (8, 8, 12, 12), 9000, "cbf16", T.TGRAD_ORDER_SUM),
+    ((24, 24, 136, 32), (6, 6, 20, 9), 9000, "cbf16", T.TGRAD_ORDER_US_LR),      # 32-row tiles, a remainder step past the end
+    ((24, 24, 136, 32), (6, 6, 20, 9), 9000, "cbf16", T.TGRAD_ORDER_LR_US),
+    ((24, 24, 136, 26), (6, 6, 20, 12), 9000, "cbf16", T.TGRAD_ORDER_US_LR),     # ... two quads and no remainder
 ]
 
 
@@ -116,7 +168,8 @@ def test_workgroups_that_stay_for_several_slabs(shape, ranks, k, dt, order):
     import torch
     print("[case]", shape, ranks, dt, order, flush=True)
     places = (160 * 1024) // _head_lds(shape[3], ranks[3], shape[2], ranks[2], 1 if dt == "cbf16" else 2)
-    assert shape[0] * shape[1] > places * torch.cuda.get_device_properties(0).multi_processor_count
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    assert shape[0] * shape[1] > max(places, 2) * units          # (2: the most that one tile per wavefront gets in)
     grads = [synth.small_case(shape, 760 + t, outlier_frac=(1, 200), dtype=dt) for t in range(2)]
     W0 = _weights(shape, 25).astype(np.complex64)
     info = run_both(T, shape, ranks, k, grads, W0, refresh_every=4, lr=2e-3, weight_decay=0.01, order=order,
