@@ -459,15 +459,19 @@ __global__ __launch_bounds__(64 * W) void k_expand_split(const float* __restrict
 //   z[i, b]   = sum_m U[i, m] N_L[m, b]                 first reconstruction stage
 // so the core gradient and the core update never travel through memory between kernels (g_L is
 // still written out: it is part of the readable state).
-// A workgroup of W = 8 wavefronts owns 16 columns (4 where the rank takes more than one tile and the extent fits them, up
-// to 64 rows: half of the partial tiles, so twice the workgroups per compute unit; 23 rows, rank 17, 340000 columns 211 us
-// with 8, 141 with 4; 64 rows, rank 32, 100 columns 6.3 and 5.9; 44 rows, rank 33, 20000 columns 27 and 24).  Wavefront w contracts the steps of rows w, w + W, .. (4 rows
+// A workgroup of W = 8 wavefronts owns 16 columns (4 where the extent fits them, up to 64 rows: half of the partial tiles, so
+// twice the workgroups per compute unit; 23 rows, rank 17, 340000 columns 211 us with 8, 141 with 4; 16 rows, rank 16, 65536
+// columns 24 and 17, 30 columns 3.7 and 3.0; launch_core has the lines).  Wavefront w contracts the steps of rows w, w + W, .. (4 rows
 // each); the partial tiles are summed through LDS in a fixed order; AdamUpdate is spread over all threads
 // and leaves N_L in LDS in accumulator layout, which IS the B operand layout of the expansion (register r
 // of D holds rows 4 g + r: step r contracts exactly those); wavefront w then expands the output tiles
 // w, w + W, ...  Every operand goes from memory straight into the registers of the one wavefront that
 // uses it, and all of them (x, both factor operands, moments) are requested up front: one memory
-// round trip, three barriers.
+// round trip, two barriers for a group of columns.
+// Registers are what bounds it beside that: with indices in 64 bits the split operands made it 134 of them at one tile of
+// rank, one workgroup per compute unit instead of two (16 rows, rank 16, 65536 columns 27 us in float32 instructions, then 32,
+// now 17; 200 rows, rank 8, 20480 columns 22, then 26, now 20), and 176 bytes of scratch per lane at four (128 rows, rank 64,
+// 48 columns 10.5, then 11, now 9.3; 65536 columns 102, then 82, now 72).
 // A workgroup stays for several groups of columns where there are more of them than the chip holds: the factor operands
 // are then fetched once per workgroup instead of once per 16 columns (ranks up to 64: 128 KB each, which the L2 caches
 // delivered in 105 us for 128 x 32768 columns at rank 64, now 68), and a group's columns and moments arrive under the group before it.
@@ -499,13 +503,25 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
   // operands of the compression: steps wave + W (s0 + u); past the end: zero coefficients
   float2 xv[kCoreSteps];
   Split8 fc[MT];
+  // Eight wavefronts with four tiles of rank: the third parts of both sets of operands wait in LDS, a slot per lane
+  // (registers for all parts there are not)
+  constexpr bool kPark = MT == 4 && W == 8;
+  u32v4* park = reinterpret_cast<u32v4*>(sF) + (kArea + MT * 768) / 4 + wave * (2 * MT * 64) + lane;
+  auto set_low = [&](Split8* f, int set) {
+    if constexpr (kPark) {
+#pragma unroll
+      for (int t = 0; t < MT; ++t) park[(set * MT + t) * 64] = f[t].l;
+    }
+  };
+  auto operand = [&](const Split8* f, int set, int t) -> Split8 {
+    return Split8{f[t].h, f[t].m, kPark ? park[(set * MT + t) * 64] : f[t].l};
+  };
   auto fetch_x = [&](int g, int s0) {
-    const int64_t b_raw = (int64_t)g * 16 + col;
-    const float* xp = x + (b_raw < B ? b_raw : B - 1) * 2;
+    const uint32_t Bu = (uint32_t)B, b_raw = (uint32_t)g * 16u + (uint32_t)col, b = b_raw < Bu ? b_raw : Bu - 1u;
 #pragma unroll
     for (int u = 0; u < kCoreSteps; ++u) {
       const int k = 4 * (wave + W * (s0 + u)) + grp;
-      xv[u] = *reinterpret_cast<const float2*>(xp + (int64_t)(k < K ? k : K - 1) * row);
+      xv[u] = reinterpret_cast<const float2*>(x)[(uint32_t)(k < K ? k : K - 1) * Bu + b];   // (K B <= I < 2^31)
     }
   };
   auto fetch_in = [&](int s0) {
@@ -521,25 +537,26 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
       for (int t = 0; t < MT; ++t)
 #pragma unroll
         for (int u = 0; u < kCoreSteps; ++u) split_at(to[t], u, f[t][u]);
+      set_low(to, 0);
     };
   };
   // moments of this thread's core entries
   constexpr int kEnt = (MT * 256 + kThr - 1) / kThr;
   float2 mm[kEnt];
   float vv[kEnt];
-  auto entry = [&](int g, int q, int64_t& idx) -> bool {
+  auto entry = [&](int g, int q, uint32_t& idx) -> bool {
     const int e = tid + q * kThr;
     const int l = e & 63, r = (e >> 6) & 3, t = e >> 8;
     const int m = 16 * t + 4 * (l >> 4) + r;
-    const int64_t bb = (int64_t)g * 16 + (l & 15);
-    const bool live = t < MT && m < M && bb < B;
-    idx = live ? (int64_t)m * B + bb : 0;
+    const uint32_t Bu = (uint32_t)B, bb = (uint32_t)g * 16u + (uint32_t)(l & 15);
+    const bool live = t < MT && m < M && bb < Bu;
+    idx = live ? (uint32_t)m * Bu + bb : 0u;
     return live;
   };
   auto fetch_moments = [&](int g) {
 #pragma unroll
     for (int q = 0; q < kEnt; ++q) {
-      int64_t idx;
+      uint32_t idx;
       entry(g, q, idx);
       mm[q] = ad.m[idx];
       vv[q] = ad.v[idx];
@@ -558,6 +575,7 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
       for (int t = 0; t < MT; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) split_at(to[t], r, f[t][r]);
+      set_low(to, 1);
     };
   };
   int g = blockIdx.x;
@@ -586,7 +604,7 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
       Split8 b[2];
       split_rows<1>(xv, b);
 #pragma unroll
-      for (int t = 0; t < MT; ++t) mfma_split<2>(acc[t], fc[t], b);
+      for (int t = 0; t < MT; ++t) mfma_split<2>(acc[t], operand(fc, 0, t), b);
       if (W * (s0 + kCoreSteps) >= J) break;          // (the same for every wavefront)
       fetch_x(g, s0 + kCoreSteps);
       fetch_in(s0 + kCoreSteps)(fc);
@@ -623,7 +641,7 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
         const float v = ad.beta2 * vv[q] + (1.f - ad.beta2) * (gre * gre + gim * gim);
         const float d = 1.f / (sqrtf(v * ad.inv_c2) + ad.eps);
         float nr = 0.f, ni = 0.f;
-        int64_t idx;
+        uint32_t idx;
         if (entry(g, q, idx)) {
           ad.m[idx] = m;
           ad.v[idx] = v;
@@ -652,14 +670,14 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
       for (int t = 0; t < MT; ++t) {
         const Split8 n = split_item(reinterpret_cast<const u32v4*>(sN) + t * 192 + lane);
         const Split8 b2[2] = {conj_pairs(n), swap_pairs(n)};
-        mfma_split<2>(o, fe[t], b2);
+        mfma_split<2>(o, operand(fe, 1, t), b2);
       }
       if (b < B) {
+        const int i0 = 16 * q + 4 * grp;
+        float* oi = op + (int64_t)i0 * row;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = 16 * q + 4 * grp + r;
-          if (i < K) store_cols<1>(op + (int64_t)i * row, o, r);
-        }
+        for (int r = 0; r < 4; ++r, oi += row)
+          if (i0 + r < K) store_cols<1>(oi, o, r);
       }
     }
   }
@@ -811,11 +829,13 @@ void launch_mid(hipStream_t s, const float2* x, const float2* U, int rn, bool pr
 // Where mode 1 (extent K, rank M) and the core's B columns are one launch.  Up to two tiles of rank it always is the better
 // one.  Three or four tiles put one or two workgroups on a compute unit, and from some number of columns on the
 // separate k_mid, k_adam_core and k_expand, which stream, are: the more matrix work per column, the later (they repeat
-// none of it, but move the core twice more).  Three kernels / one, us:
-//   33 rows, rank 33: 20000 columns 23 / 24, 80000 60 / 82, 220000 139 / 212;    56, 44: 50000 58 / 57, 80000 79 / 85;
-//   64, 64: 20000 41 / 28, 80000 100 / 91, 120000 140 / 141;                     72, 52: 40000 68 / 63, 65000 79 / 97;
-//   128, 64: 30000 69 / 54, 120000 222 / 212;  96, 33: 40000 58 / 59, 120000 131 / 165;
-//   200, 64 (operands fetched per group): 20000 82 / 75, 30000 98 / 117;  160, 33: 10000 28 / 36.
+// none of it, but move the core twice more).  All stages but the first and the last, three kernels / one, us (modes 2 and 3
+// not compressed beside it):
+//   33 rows, rank 33: 20000 columns 70 / 66, 40960 85 / 88, 65536 108 / 119;    56, 44: 51200 109 / 107, 65536 120 / 120,
+//   81920 159 / 162;    64, 64: 65536 132 / 126, 81920 171 / 170, 120832 236 / 252;
+//   72, 52: 40960 110 / 105, 65536 151 / 152;    96, 33: 40960 116 / 114, 65536 152 / 157;
+//   128, 64: 65536 197 / 185, 102400 339 / 345;  128, 33: 40960 136 / 130, 65536 178 / 182;
+//   160, 33 (operands fetched per group): 10000 50 / 47;  200, 64: 12800 86 / 80, 20480 99 / 116;  250, 40: 16000 103 / 96.
 bool core_kernel_fits(int K, int M, int64_t B) {
   if (M > 64 || K > TGRAD_MAX_EXTENT) return false;
   return M <= 32 || B <= (int64_t)K * M * (K <= 64 ? 24 : K <= 128 ? 14 : 2);
@@ -833,12 +853,15 @@ void launch_core(hipStream_t s, const float2* x, const float2* U, int rn, int K,
   const int64_t groups = (B + 15) / 16;
 #define TGRAD_CORE(MT_, W_)                                                                                  \
   do {                                                                                                       \
-    const size_t lds = (size_t)W_ * MT_ * 2048 + (size_t)MT_ * 3072;                                                          \
+    const size_t lds = (size_t)W_ * MT_ * 2048 + (size_t)MT_ * 3072 + (MT_ == 4 && W_ == 8 ? W_ * MT_ * 2048 : 0); \
     allow_lds(k_core<MT_, W_>, lds);                                                                         \
     const int64_t cap = (int64_t)compute_units() * resident_blocks(k_core<MT_, W_>, 64 * W_, lds);           \
     k_core<MT_, W_><<<dim3((unsigned)(groups < cap ? groups : cap)), dim3(64 * W_), lds, s>>>(xf, U, rn, K, M, B, (int)groups, ad, zf); \
   } while (0)
-  if (M <= 16) TGRAD_CORE(1, 8);
+  // (one tile of rank: four wavefronts as well where eight do not hold the rows either and there is more than a group per
+  // compute unit, 140 rows, 32768 columns 32 us with 8, 28 with 4; but 128 rows 19.4 / 22.2, and 120 groups of 250 7.5 / 8.7)
+  if (M <= 16 && (K <= 64 || (K > 128 && groups > compute_units()))) TGRAD_CORE(1, 4);
+  else if (M <= 16) TGRAD_CORE(1, 8);
   else if (M <= 32 && K <= 64) TGRAD_CORE(2, 4);
   else if (M <= 32) TGRAD_CORE(2, 8);
   else if (K <= 64) TGRAD_CORE(4, 4);

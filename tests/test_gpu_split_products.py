@@ -35,6 +35,30 @@ def test_middle_stages(shape, ranks, k):
     check_parity(info, W0)
 
 
+# The core kernel: four wavefronts or eight, tiles of rank, rows in one batch or several, one group of 16 columns or several
+# for a workgroup.
+CORE_SHAPES = [
+    ((20, 40, 40, 12), (7, 40, 40, 12)),           # one tile of rank, four wavefronts; 1200 groups: two for some workgroups
+    ((64, 42, 40, 5), (16, 42, 40, 5)),            # ... as many rows as these hold
+    ((65, 42, 40, 5), (16, 42, 40, 5)),            # ... eight
+    ((140, 16, 16, 15), (16, 16, 16, 15)),         # ... more rows than these hold: 240 groups
+    ((140, 16, 16, 17), (16, 16, 16, 17)),         # ... 272 groups: four
+    ((100, 30, 20, 9), (50, 30, 20, 9)),           # four tiles, eight wavefronts: operands partly in LDS, 338 groups
+    ((200, 24, 20, 9), (64, 24, 20, 9)),           # ... in several batches, fetched again for every group
+    ((256, 12, 12, 9), (33, 12, 12, 9)),           # ... the longest
+]
+
+
+@pytest.mark.parametrize("shape,ranks", CORE_SHAPES)
+def test_core_kernel(shape, ranks):
+    print("[case]", shape, ranks, flush=True)
+    grads = [synth.small_case(shape, 800 + t, outlier_frac=(1, 200)) for t in range(2)]
+    W0 = _weights(shape, 28).astype(np.complex64)
+    info = run_both(T, shape, ranks, 900, grads, W0, refresh_every=4, lr=2e-3, weight_decay=0.01)
+    assert all(info["omega_equal"])
+    check_parity(info, W0)
+
+
 # shape, ranks, k, gradient dtype, packed: whether the 32 x 32 kernels (which have a factor packed for them) serve it
 END_SHAPES = [
     ((64, 32, 32, 17), (4, 4, 17, 9), 6000, "c64", False),      # 2048 slabs: the first with full ranks
