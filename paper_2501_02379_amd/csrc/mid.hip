@@ -548,9 +548,9 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
     const int e = tid + q * kThr;
     const int l = e & 63, r = (e >> 6) & 3, t = e >> 8;
     const int m = 16 * t + 4 * (l >> 4) + r;
-    const uint32_t Bu = (uint32_t)B, bb = (uint32_t)g * 16u + (uint32_t)(l & 15);
-    const bool live = t < MT && m < M && bb < Bu;
-    idx = live ? (uint32_t)m * Bu + bb : 0u;
+    const int64_t bb = (int64_t)g * 16 + (l & 15);             // (in 32 bits 128 rows, rank 32, 256 groups took 8.3 us, not 7.7)
+    const bool live = t < MT && m < M && bb < B;
+    idx = live ? (uint32_t)((int64_t)m * B + bb) : 0u;
     return live;
   };
   auto fetch_moments = [&](int g) {
