@@ -70,13 +70,16 @@ __device__ __forceinline__ v4f mfma16(float a, float b, v4f c) {
 }
 
 // ---- float32 products on the bf16 matrix instructions -------------------------------------------
-// x = h + m + l with h = bf16(x), m = bf16(x - h), l = bf16(x - h - m): three times 8 bits hold all 24 of a float32,
-// and a x b = hh + hm + mh + hl + lh + mm leaves out products below 2^-25 of it.  Six v_mfma_f32_16x16x32_bf16 do the
-// work of eight v_mfma_f32_16x16x4f32 in 96 cycles instead of 256, and, unlike those, beside vector instructions of
-// another wavefront.  They add 32 products per rounding instead of 4, so sums come out closer to 64 bits than before:
-// relative error of a sum of K products of normal numbers, float32 instructions / these: K = 32 1.0e-7 / 3.7e-8,
-// 128 2.0e-7 / 1.5e-7 (6.4e-8 with the five small terms summed apart), 1024 5.7e-7 / 4.9e-7.
-// Parts of numbers below 2^-110 are subnormal in bf16 and may be lost; an infinity becomes NaN (inf - inf).
+// x = h + m + l with h the upper 8 bits of x, m = bf16(x - h), l = bf16(x - h - m): three times 8 bits hold all 24 of a
+// float32, and a x b = hh + hm + mh + hl + lh + mm leaves out products below 2^-23 of it (ml, lm, ll: typically 2^-26).  Six
+// v_mfma_f32_16x16x32_bf16 do the work of eight v_mfma_f32_16x16x4f32 in 96 cycles instead of 256, and, unlike those, beside
+// vector instructions of another wavefront.  They add 32 products per rounding instead of 4, so sums come out closer to 64
+// bits than before: relative error of a sum of K products of normal numbers, float32 instructions / these: K = 32 1.0e-7 /
+// 4.4e-8, 128 2.1e-7 / 1.6e-7 (6.9e-8 with the five small terms summed apart), 1024 5.7e-7 / 4.8e-7.
+// What float32 instructions did and these do not: numbers below 2^-110 lose their last bits (parts below 2^-133, the smallest
+// bf16, are lost: an error of 8e-7 at 2^-114, 2e-4 at 2^-122; their squares are zero in float32, so AdamUpdate divides such a
+// gradient by eps alone and the weights do not show it); an infinity becomes NaN, in both parts of its complex number (inf - inf; two complex products
+// with finite factors made NaN of it before as well, and every step has more).
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -99,11 +102,13 @@ struct Split8 {
 };
 // One dword of each part from a pair of numbers.  x - h is exact, and one v_dot2c_f32_bf16 per number: dot2(h, (-1, 0), x).
 // (The constants are kept in registers: as an inline constant of the instruction, (-1, 0) would be read as a float32.)
+// h is cut off, not rounded: to nearest, a number above 3.39e38 would be an infinity and the rest NaN, and limiting every
+// number first cost 2 to 3 % of a step (128x128x128x65 743 us, 763).
 __device__ __forceinline__ void split_pair(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
   uint32_t lo = 0x0000BF80u, hi = 0xBF800000u;
   asm("" : "+s"(lo), "+s"(hi));
   const bf16x2 n0 = __builtin_bit_cast(bf16x2, lo), n1 = __builtin_bit_cast(bf16x2, hi);
-  h = bf16_pack(a, b);
+  h = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);   // the upper halves
   const bf16x2 hv = __builtin_bit_cast(bf16x2, h);
   a = __builtin_amdgcn_fdot2_f32_bf16(hv, n0, a, false);
   b = __builtin_amdgcn_fdot2_f32_bf16(hv, n1, b, false);

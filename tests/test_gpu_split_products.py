@@ -202,6 +202,77 @@ def test_workgroups_that_stay_for_several_slabs(shape, ranks, k, dt, order):
     check_parity(info, W0)
 
 
+# Every kernel whose operands are split, in its variants: first and last kernel with coefficients in registers, in LDS, for one
+# tile, for shared slabs; compressions and expansions of one, two and four tiles, with one column per lane and two; the core
+# kernel of one, two and four tiles on four wavefronts and eight.
+EXACT_SHAPES = [
+    ((24, 20, 40, 33), (4, 5, 9, 8), "c64"),
+    ((42, 42, 44), (13, 13, 14), "c64"),                   # one tile per wavefront; core (1, 4)
+    ((19, 20, 86, 61), (4, 5, 19, 5), "c64"),              # shared slabs, registers
+    ((28, 28, 80, 64), (6, 6, 16, 16), "cbf16"),           # ... LDS
+    ((48, 44, 40, 34), (30, 20, 20, 12), "c64"),           # whole slabs, LDS; core (2, 4)
+    ((48, 44, 40, 34), (12, 20, 20, 12), "cbf16"),
+    ((110, 60, 40, 16), (12, 50, 30, 15), "c64"),          # compression and expansion of four tiles, one column; core (1, 8)
+    ((96, 80, 40, 16), (40, 24, 30, 14), "c64"),           # ... of two, two columns; core (4, 8)
+    ((100, 96, 20, 16), (20, 12, 18, 14), "c64"),          # ... of one; core (2, 8)
+    ((64, 140, 20, 10), (44, 70, 18, 8), "c64"),           # expansion of more rows than registers hold; core (4, 4)
+]
+
+
+@pytest.mark.parametrize("shape,ranks,dt", EXACT_SHAPES)
+def test_selecting_factors_are_exact(shape, ranks, dt):
+    """Factors of one unit entry (1, i, -1 or -i) per column select entries of G: every product is exact, so is the core
+    gradient, bit for bit, up to the largest float32 (whose nearest bf16 is infinite).  The way back multiplies each entry of
+    N once: 16 roundings of 2^-24 are more than AdamUpdate and the products make, and where the third part of an operand is
+    lost 2^-17 remain."""
+    print("[case]", shape, ranks, dt, flush=True)
+    rng = np.random.default_rng(29)
+    bits = rng.integers(0, 1 << 24, shape + (2,), dtype=np.uint32)                  # sign and 23 bits of mantissa
+    expo = rng.integers(-100, 128, shape + (2,)).astype(np.int64) + 127
+    g = (((bits >> np.uint32(23)) << np.uint32(31)) | (expo.astype(np.uint32) << np.uint32(23)) |
+         (bits & np.uint32(0x7FFFFF))).view(np.float32)
+    if dt == "cbf16":
+        g = (g.view(np.uint32) & np.uint32(0xFFFF0000)).view(np.float32)
+    g = g.reshape(-1).view(np.complex64).reshape(shape)
+    g.reshape(-1)[:4] = np.finfo(np.float32).max * np.complex64(1 - 1j) if dt == "c64" else 1.0
+    lr, eps, tau = 1e-3, 1e-8, 4
+    ctx = T.Context(T.make_config(shape, ranks, 1, lr=lr, eps=eps, refresh_every=0,
+                                  grad_dtype=T.TGRAD_CBF16 if dt == "cbf16" else T.TGRAD_C64))
+    ctx.tgrad_set_state(T.STATE_STEP, tau - 1)
+    ctx.tgrad_set_state(T.STATE_INDICES, np.zeros(1, np.int64))
+    rows, phases = [], []
+    for n, (i, r) in enumerate(zip(shape, ranks)):
+        # (row 0 of the last mode's neighbours of the support is among the selected ones)
+        rows.append(np.concatenate([[0], 1 + rng.permutation(i - 1)[:r - 1]]) if n < len(shape) - 1 else
+                    np.concatenate([[1, 2, 3], 4 + rng.permutation(i - 4)[:r - 3]]))
+        phases.append(np.array([1, 1j, -1, -1j], np.complex64)[rng.integers(0, 4, r)])
+        u = np.zeros((i, r), np.complex64)
+        u[rows[n], np.arange(r)] = phases[n]
+        ctx.tgrad_set_state(T.STATE_FACTOR0 + n, u)
+    gd = g if dt == "c64" else O.complex_to_bf16_pairs(g)
+    W = T.to_device_weight(np.zeros(shape, np.complex64))
+    ctx.tgrad_step(W, T.to_device_grad(gd))
+    phase = phases[0]
+    for p in phases[1:]:
+        phase = np.multiply.outer(phase, p)
+    want = g[np.ix_(*rows)] * phase.conj()
+    assert np.array_equal(ctx.tgrad_get_state(T.STATE_CORE_G), want)
+    m, v = ctx.tgrad_get_state(T.STATE_CORE_M), ctx.tgrad_get_state(T.STATE_CORE_V)
+    with np.errstate(over="ignore"):
+        d = 1.0 / (np.sqrt(np.float32(1 / (1 - float(np.float32(0.999)) ** tau)) * v) + np.float32(eps)).astype(np.float64)
+    N = m.astype(np.complex128) / (1 - float(np.float32(0.9)) ** tau) * d * phase
+    got = T.weight_to_host(W).astype(np.complex128)
+    back = got[np.ix_(*rows)]
+    for a, b in ((back.real, N.real), (back.imag, N.imag)):
+        worst = np.max(np.abs(a + float(np.float32(lr)) * b) / (float(np.float32(lr)) * np.abs(b) + 1e-30))
+        print("way back: %.2e" % worst, flush=True)
+        assert worst < 16 * 2.0 ** -24
+    got[np.ix_(*rows)] = 0
+    got.reshape(-1)[0] = 0
+    assert not got.any()
+    ctx.tgrad_destroy()
+
+
 def test_products_keep_float32_accuracy():
     """A step's core gradient at entries of G between 2^-60 and 2^60, against 64 bits: every part of a float32 counts, so the
     error stays that of float32 sums (16 roundings of 2^-24 at the depth of these chains), where two parts of three would
