@@ -203,7 +203,7 @@ int tgrad_step(tgrad_ctx* ctx, void* weight_dev, const void* grad_dev);
  * library, TGRAD_STATIC_WORKSPACE_BYTES per GPU, which every GPU that runs the library holds until
  * the process ends.  A configuration whose `tgrad_query_sizes` workspace exceeds that size is
  * rejected with TGRAD_ERR_UNSUPPORTED and nothing is launched, unless (leading extents of 8192 and
- * more in front of few rows) other kernels of this library, slower there, do with that size.
+ * more in front of few rows; sizes within 1 % of the limit) other kernels of this library, slower there, do with that size.
  *  cfg         host pointer; refresh_every must be >= 1 (INVALID_ARG otherwise).
  *  state_dev   device pointer, >= state_bytes of `tgrad_query_sizes`, 256-byte aligned: the optimizer
  *              state (Omega, M_S, V_S, M_L, V_L, U^(n)).  The caller zero-fills it before the call

@@ -50,6 +50,7 @@ struct Plan {
   bool fuse_next = false;        // the last-mode kernels also handle mode N-1 (see make_plan)
   bool narrow = false;           // ... and they are k_head / k_tail (ends.hip), on tiles that end with their slab
   bool short_slabs = false;      // k_head / k_tail would fit, but separate kernels are faster
+  bool wide_fits = false;        // they were chosen before the 32 x 32 kernels, which would fit
   int end_tiles = 0;             // k_head / k_tail: tiles per slab
   bool own_offsets = false;      // their tiles are not the flat tiles: support offsets of their own
   bool flat_offsets = true;      // some kernel walks the flat tiles with the support
@@ -139,8 +140,13 @@ int validate(const tgrad_config* c) {
   return TGRAD_OK;
 }
 
-// `short_slabs_fused`: k_head / k_tail also where separate kernels are the faster ones (ends_kernel_pays).
-void make_plan(const tgrad_config* c, bool short_slabs_fused, Plan* p) {
+// The kernels for the last two modes: the fastest; or, where the workspace of those is too large, k_head / k_tail also for
+// short slabs that separate kernels are the faster ones for (ends_kernel_pays: one tensor less); or the 32 x 32 kernels
+// wherever they fit (no support offsets per slab).
+enum EndTier { END_FASTEST, END_SHORT_FUSED, END_WIDE };
+
+void make_plan(const tgrad_config* c, EndTier tier, Plan* p) {
+  *p = Plan();
   p->N = c->ndim;
   p->I = 1;
   p->C = 1;
@@ -195,8 +201,9 @@ void make_plan(const tgrad_config* c, bool short_slabs_fused, Plan* p) {
              rows / I2 >= 512 && p->shape[last] <= fused_max_last_extent();
       // Otherwise, and wherever the 32-wide tiles are not the better ones, on 16 x 16 tiles.
       p->narrow = p->tile_waves > 0 && ends_kernel_fits((int)p->shape[last], p->rank[last], (int)I2, p->rank[last - 1]) &&
-                  !(wide && wide_tiles_pay(p->rank[last], (int)I2, p->rank[last - 1], rows / I2));
-      if (p->narrow && !wide && !short_slabs_fused &&
+                  !(wide && (tier == END_WIDE || wide_tiles_pay(p->rank[last], (int)I2, p->rank[last - 1], rows / I2)));
+      p->wide_fits = p->narrow && wide;
+      if (p->narrow && !wide && tier != END_SHORT_FUSED &&
           !ends_kernel_pays((int)p->shape[last], p->rank[last], (int)I2, p->rank[last - 1], rows / I2)) {
         p->narrow = false;
         p->short_slabs = true;
@@ -857,7 +864,7 @@ int tgrad_query_sizes(const tgrad_config* cfg, size_t* state_bytes, size_t* work
   int rc = validate(cfg);
   if (rc != TGRAD_OK) return rc;
   Plan p;
-  make_plan(cfg, false, &p);
+  make_plan(cfg, END_FASTEST, &p);
   *state_bytes = p.state_bytes;
   *workspace_bytes = p.workspace_bytes;
   return TGRAD_OK;
@@ -874,7 +881,7 @@ int tgrad_init(tgrad_ctx** out, const tgrad_config* cfg, void* state_dev, void* 
   tgrad_ctx* c = new (std::nothrow) tgrad_ctx();
   if (!c) return TGRAD_ERR_INVALID_ARG;
   c->cfg = *cfg;
-  make_plan(cfg, false, &c->plan);
+  make_plan(cfg, END_FASTEST, &c->plan);
   c->state = static_cast<char*>(state_dev);
   c->ws = static_cast<char*>(workspace_dev);
   c->stream = static_cast<hipStream_t>(hip_stream);
@@ -933,9 +940,11 @@ int tgrad_step_static(const tgrad_config* cfg, void* state_dev, int64_t t, void*
   if (cfg->refresh_every < 1) return TGRAD_ERR_INVALID_ARG;      // nobody else could refresh this state
   tgrad_ctx c;                                                    // on the stack: nothing is allocated
   c.cfg = *cfg;
-  make_plan(cfg, false, &c.plan);
+  make_plan(cfg, END_FASTEST, &c.plan);
   // The separate kernels for short slabs keep one more tensor, the one after the first stage; the fused ones may still fit.
-  if (c.plan.short_slabs && c.plan.workspace_bytes > (size_t)TGRAD_STATIC_WORKSPACE_BYTES) make_plan(cfg, true, &c.plan);
+  // The 16 x 16 kernels keep support offsets per slab, where the 32 x 32 ones need none.
+  if ((c.plan.short_slabs || c.plan.wide_fits) && c.plan.workspace_bytes > (size_t)TGRAD_STATIC_WORKSPACE_BYTES)
+    make_plan(cfg, c.plan.short_slabs ? END_SHORT_FUSED : END_WIDE, &c.plan);
   if (c.plan.workspace_bytes > (size_t)TGRAD_STATIC_WORKSPACE_BYTES) return TGRAD_ERR_UNSUPPORTED;
   void* ws = nullptr;
   rc = static_workspace(&ws);

@@ -119,6 +119,29 @@ def test_static_step_on_short_slabs_beyond_the_workspace_of_a_context():
     assert np.linalg.norm(a - b) < 1e-5 * np.linalg.norm(b - W0)
 
 
+def test_static_step_where_support_offsets_per_slab_do_not_fit():
+    """4620 slabs of 32 x 56 take the 16 x 16 kernels, whose support offsets are what the fixed array is too short for; the
+    static step then takes the 32 x 32 ones, which need none.  (Bounds as above.)"""
+    import torch
+    shape, ranks, lr = (70, 66, 32, 56), (1, 1, 17, 9), 2e-3
+    cfg = T.make_config(shape, ranks, 0, lr=lr, weight_decay=0.01, refresh_every=3, grad_dtype=T.TGRAD_CBF16)
+    rc, sb, wb = T.tgrad_query_sizes(cfg)
+    assert rc == T.TGRAD_OK and wb > T.STATIC_WORKSPACE_BYTES
+    ctx = T.Context(cfg)
+    state = torch.zeros(sb, dtype=torch.uint8, device="cuda:0")
+    rng = np.random.default_rng(4600)
+    W0 = ((rng.standard_normal(shape) + 1j * rng.standard_normal(shape)) * 0.02).astype(np.complex64)
+    W_ctx, W_static = T.to_device_weight(W0), T.to_device_weight(W0)
+    for t in range(4):
+        gd = T.to_device_grad(synth.small_case(shape, 4600 + t, dtype="cbf16"))
+        ctx.tgrad_step(W_ctx, gd)
+        T.tgrad_step_static(cfg, state, t, W_static, gd)
+    torch.cuda.synchronize()
+    a, b = T.weight_to_host(W_static), T.weight_to_host(W_ctx)
+    assert np.max(np.abs(b - W0)) > lr / 2 and np.max(np.abs(a - b)) < 1e-2 * lr
+    assert np.linalg.norm(a - b) < 1e-5 * np.linalg.norm(b - W0)
+
+
 def test_static_step_rejects_what_it_cannot_serve():
     import ctypes as C
     import torch
