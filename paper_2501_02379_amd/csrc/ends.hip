@@ -70,7 +70,8 @@ __host__ __device__ constexpr int head_slice(int ES, int K, int T4) {
 constexpr int head_ahead(int T4, int NC) { return T4 >= 9 && NC == 2 ? 2 : T4 >= 13 ? 2 : 1; }
 // Coefficients of more than two operands' worth are kept in LDS (a tile reads them once) where a wavefront has many tiles
 // (HEAD_MANY), fewer in registers.
-constexpr bool head_coef_lds(int T4, int NC) { return head_quads(T4) * NC > 2; }
+constexpr bool head_many_coefs(int T4, int NC) { return head_quads(T4) * NC > 2; }
+constexpr bool head_coef_lds(int T4, int NC) { return NC == 2 && head_many_coefs(T4, NC); }
 constexpr int kHeadItem = 6 * 64;         // u32v4 of the table per 32 rows and tile of M2: (Fr, Fi) x (h, m, l) x lane
 
 struct HeadArgs {
@@ -558,7 +559,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_head(HeadArgs a) {
     }
     // With coefficients in LDS a workgroup stays for several shared slabs: its tables leave few of its kind to a compute unit
     // (head_mode).  Where they are light the code for it costs more than it saves (16x16x8x5 15.4 -> 15.9).
-    if constexpr (!kInLds) {
+    if constexpr (MODE != HEAD_MANY || !head_many_coefs(T4, NC)) {
       break;
     } else {
       base += (int)gridDim.x;
@@ -1011,10 +1012,15 @@ bool wide_tiles_pay(int r, int I2, int r2, int64_t nslabs) {
 //   4096 slabs: 4x5 24 / 27, 8x33 32 / 33, 36x5 31 / 33 (the saved launches win).
 // r: 65536 slabs of 12x9 with r = 1 95 / 82, r = 6 109 / 115, r = 9 126 / 143.
 bool ends_kernel_pays(int K, int r, int I2, int r2, int64_t nslabs) {
-  // (A table that leaves room for one workgroup per compute unit is not staged for the sake of a few slabs: 16 slabs of
-  // 250x65, r 32,16, 45 / 40; 64 of 256x33 36 / 31; but 128 of 250x65 40 / 45, 2048 of 250x33 113 / 147.)
-  const size_t table = (size_t)((I2 + 15) / 16) * ((r2 + 15) / 16) * 2048;
-  if (nslabs < 128 && 16 * (size_t)head_slice(2, K, steps_class(K)) + table > kLdsLimit / 2) return false;
+  // (Few slabs of the longest: eight tiles of 32 rows and two tiles of the first rank per wavefront of k_head, or thirteen
+  // and more of 16 with all operands doubled, are not worth it.  27 slabs of 232x15, r 32,2 26 / 24, 76 of 246x30, r 21,8
+  // 34 / 32, 96 of 204x56, r 27,16 48 / 44; but 84 of 188x20, r 30,7 26 / 30, 68 of 206x67, r 32,11 47 / 47, 39 of 146x62,
+  // r 18,7 25 / 37, 126 of 242x26, r 25,15 34 / 40.)
+  if (nslabs < 128 && r2 > 16 && (K <= 33 ? K > 12 && r <= 8 && I2 > 224 : K > 52 && r > 8 && I2 > 192)) return false;
+  // (... nor with four wavefronts for all of a compute unit while a fourth round is begun and not filled: 816 slabs of 247x60,
+  // r 26,12 135 / 130, 900 of 220x50 122 / 119, 909 of 236x51, r 30,12 127 / 122; but 625 of 250x65, r 32,16 115 / 121, 1600
+  // of 220x50 156 / 165.)
+  if (nslabs >= 768 && nslabs < kWholeSlabs && r > 8 && head_lds(HEAD_MANY, 8, 2, K, r, I2, r2) > kLdsLimit) return false;
   if (nslabs < 8192) return true;
   const int R = end_tile_rows(K), S = (I2 + R - 1) / R, H = (I2 + 15) / 16;
   const int row = 25 + (K < 17 ? K : 17) + 5 * r;
@@ -1027,7 +1033,7 @@ namespace {
 // (One class more: where slabs of four tiles meet two tiles of rank, its table leaves a compute unit one workgroup of four
 // wavefronts.  390 slabs of 118x30, r 23,5 13.5 us, now 9.0; 780 of 100x29, r 32,8 25.6, now 14.3.)
 constexpr bool head_has_one(int DT, int T4, int NC, int NM) {
-  return head_coef_lds(T4, NC) || (DT == TGRAD_C64 && T4 == 9 && NC == 1 && NM == 2);
+  return head_many_coefs(T4, NC) || (DT == TGRAD_C64 && T4 >= 5 && NC == 1 && NM == 2);
 }
 
 // Which of the three HEAD_ modes, while slabs are too few for a wavefront to walk whole ones (us, k_head alone, r: ranks of
@@ -1045,16 +1051,16 @@ constexpr bool head_has_one(int DT, int T4, int NC, int NM) {
 template <int DT, int T4, int NC, int NM>
 int head_mode(int64_t nslabs, int S, int es, int K, int M, int I2, int M2) {
   if (!head_has_one(DT, T4, NC, NM) || nslabs >= kWholeSlabs) return HEAD_MANY;
-  if (!head_coef_lds(T4, NC)) return S == 4 && head_lds(HEAD_MANY, 4, es, K, M, I2, M2) > kLdsLimit / 2 ? HEAD_ONE : HEAD_MANY;
+  if (!head_many_coefs(T4, NC) && head_lds(HEAD_MANY, 4, es, K, M, I2, M2) <= kLdsLimit / 2) return HEAD_MANY;
   if (S <= 4) return HEAD_ONE;
-  if constexpr (head_coef_lds(T4, NC)) {
+  if constexpr (head_has_one(DT, T4, NC, NM)) {
     const auto one = k_head<DT, T4, NC, NM, HEAD_ONE>;
     const size_t lds = head_lds(HEAD_ONE, S, es, K, M, I2, M2);
     if (S <= kMaxWaves && allow_lds(one, lds) &&
         nslabs <= (int64_t)compute_units() * resident_blocks(one, 64 * kMaxWaves, lds))
       return HEAD_ONE;
   }
-  const bool few = DT == TGRAD_C64 && (T4 == 17 || nslabs <= 3 * (int64_t)compute_units());
+  const bool few = DT == TGRAD_C64 && head_coef_lds(T4, NC) && (T4 == 17 || nslabs <= 3 * (int64_t)compute_units());
   return few && head_lds(HEAD_FEW, 4, es, K, M, I2, M2) <= kLdsLimit / 2 ? HEAD_FEW : HEAD_MANY;
 }
 
@@ -1062,7 +1068,7 @@ template <int DT, int T4, int NC, int NM, int MODE>
 void launch_head_as(hipStream_t s, const HeadArgs& a, int W, size_t lds, int64_t nslabs) {
   const auto kern = k_head<DT, T4, NC, NM, MODE>;
   allow_lds(kern, lds);
-  const bool stay = MODE == HEAD_MANY && (!a.split || head_coef_lds(T4, NC));
+  const bool stay = MODE == HEAD_MANY && (!a.split || head_many_coefs(T4, NC));
   const unsigned grid = stay ? end_grid(kern, W, lds, a.split ? nslabs * W : nslabs) : (unsigned)nslabs;
   kern<<<dim3(grid), dim3(64 * W), lds, s>>>(a);
 }
@@ -1113,7 +1119,15 @@ void launch_tail(hipStream_t s, const float2* y1, const float2* U3, int K, int M
                  const uint32_t* tile_start, const float2* gs, float2* ms, float* vs, float beta1, float beta2,
                  double inv_c1, double inv_c2, float eps, float c_lambda) {
   const int R = end_tile_rows(M), S = (I2 + R - 1) / R;
-  const bool split = nslabs < kWholeSlabs;
+  // Single tiles are dealt to the wavefronts, and a slab's part of z fetched for every one of them, while slabs are few; of
+  // five tiles and more also where whole ones leave most of the last round idle (2511 slabs for 2048 wavefronts), and for
+  // complex64 W, up to 8 columns of rank and more than 17 of W, where such a fetch is little beside the tile.  Whole / dealt
+  // (float32 operands, whole), us: 2511 slabs of 113x38, r 31,8 56 / 43 (48); 2304 of 110x35, r 5,15 44 / 34 (46); 2401 of
+  // 84x53, r 25,11, bf16 W 41 / 37 (47); 6400 of 256x20, r 13,4 112 / 98 (112); 8991 of 192x28, r 17,6 163 / 153 (157); but
+  // 3660 of 163x51, r 23,15, bf16 W 78 / 91; 8100 of 90x50, r 20,12 121 / 127; 6561 of 150x14, r 25,3 55 / 58; 12800 of
+  // 250x12, r 20,4 142 / 156.
+  const bool split = nslabs < kWholeSlabs ||
+                     (S >= 5 && nslabs < (wdtype == TGRAD_C64 && K <= 8 && M > 17 ? 9 * kWholeSlabs : 5 * kWholeSlabs / 2));
   const int64_t units = split ? nslabs * S : nslabs;
   const int full = tail_lds(4, M, I2, K2, K) <= kLdsLimit / 2 ? 4 : tail_lds(8, M, I2, K2, K) <= kLdsLimit ? 8 : 4;
   // Few tiles: a wavefront each.  Where coefficients go to LDS (tail_coef_lds) it then takes its operands straight into
@@ -1121,8 +1135,9 @@ void launch_tail(hipStream_t s, const float2* y1, const float2* U3, int K, int M
   // three per compute unit.  Us, those / LDS / float32 operands as before: 42x42x44, r 13,14 5.8 / 7.4 / 6.9; 108x58x67, r 17,16 8.0 /
   // 10.7 / 10.0; 380 slabs of 86x61, r 19,5 11.0 / 13.9 / 14.4; 552 of 82x54, r 22,8 14.3 / 13.6 / 16.1; 324 of 65x58, r 21,14
   // 12.9 / 11.4 / 15.0.
-  const bool one = tail_coef_lds(columns_class(M), K <= 8 ? 1 : 2) && split && units <= (K <= 8 ? 3 * kWholeSlabs : 768);
-  const int W = units >= kWholeSlabs && !one ? full : 1;
+  const bool in_lds = tail_coef_lds(columns_class(M), K <= 8 ? 1 : 2);
+  const bool one = in_lds && split && units <= (K <= 8 ? 3 * kWholeSlabs : 768);
+  const int W = !one && (in_lds || units >= kWholeSlabs) ? full : 1;
   const size_t lds = tail_lds(W, M, I2, K2, K, one);
   TailArgs a{y1, U2, U3, w, K, M, I2, K2, S, (int)nslabs, split ? 1 : 0, decay, c_alpha};
   const SparseAdam sp = sparse_adam(omega, tile_start, gs, ms, vs, beta1, beta2, inv_c1, inv_c2, eps, c_lambda, 0);

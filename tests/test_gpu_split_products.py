@@ -72,7 +72,13 @@ END_SHAPES = [
     ((33, 32, 21, 25), (3, 4, 9, 8), 3000, "c64", False),       # two quads, the second of nine elements
     ((13, 10, 250, 34), (3, 4, 20, 10), 9000, "c64", False),    # a table that leaves one workgroup to a compute unit
     ((40, 30, 230, 20), (3, 4, 18, 7), 9000, "c64", False),     # ... with whole slabs: eight wavefronts
-    ((10, 10, 250, 34), (3, 4, 20, 10), 9000, "c64", False),    # ... too few slabs for it: separate kernels
+    ((10, 10, 250, 34), (3, 4, 20, 10), 9000, "c64", False),    # ... fewer slabs
+    ((9, 3, 232, 15), (3, 2, 32, 2), 900, "c64", False),        # ... too few for it: separate kernels
+    ((9, 3, 205, 54), (3, 2, 17, 9), 900, "c64", False),        # ... the other line of those
+    ((29, 29, 220, 50), (3, 3, 26, 12), 9000, "c64", False),    # four wavefronts per compute unit, 841 slabs: separate kernels
+    ((27, 93, 70, 38), (6, 23, 31, 8), 9000, "c64", False),     # five tiles to a slab, 2511: single tiles in the last kernel
+    ((20, 128, 70, 38), (6, 23, 31, 9), 9000, "c64", False),    # ... 2560: whole slabs
+    ((20, 128, 70, 38), (6, 23, 31, 8), 9000, "c64", False),    # ... up to eight columns of rank single ones
     ((32, 32, 256, 13), (4, 5, 20, 5), 9000, "c64", False),     # 1024 slabs, whole 32-row tiles
 ]
 
@@ -164,7 +170,8 @@ SHARED_SLABS = [
     ((28, 28, 80, 64), (6, 6, 16, 16), 9000, "cbf16", T.TGRAD_ORDER_US_LR),
     ((43, 16, 99, 50), (14, 5, 32, 16), 9000, "cbf16", T.TGRAD_ORDER_US_LR),
     ((43, 16, 99, 49), (14, 5, 32, 16), 9000, "cbf16", T.TGRAD_ORDER_US_LR),     # nothing to pad
-    ((24, 23, 114, 54), (6, 5, 32, 5), 9000, "c64", T.TGRAD_ORDER_US_LR),
+    ((24, 23, 114, 54), (6, 5, 32, 9), 9000, "c64", T.TGRAD_ORDER_US_LR),
+    ((31, 31, 141, 38), (7, 7, 24, 6), 9000, "cbf16", T.TGRAD_ORDER_US_LR),      # coefficients in registers
     ((30, 30, 80, 48), (8, 8, 12, 12), 9000, "cbf16", T.TGRAD_ORDER_US_LR),
     ((30, 30, 80, 48), (8, 8, 12, 12), 9000, "cbf16", T.TGRAD_ORDER_SUM),
     ((24, 24, 136, 32), (6, 6, 20, 9), 9000, "cbf16", T.TGRAD_ORDER_US_LR),      # 32-row tiles, a remainder step past the end
@@ -181,7 +188,7 @@ def _head_lds(K, r, I2, r2, elem_dwords):
     pad = 1 - K % 2
     elems = max(pieces * 128 + pad * (pieces * 128 // K + 1), rows * (K + pad)) + 16 * quads + 4
     piece_slice = 4 * (-(-max(elem_dwords * elems, 1024) // 4) * 4)
-    fixed = quads * (1 if r <= 8 else 2) * 3072 + -(-I2 // 32) * (1 if r2 <= 16 else 2) * 6144
+    fixed = (quads * 2 * 3072 if r > 8 else 0) + -(-I2 // 32) * (1 if r2 <= 16 else 2) * 6144
     lds = lambda W: fixed + W * piece_slice
     most = 4 if lds(4) <= 80 * 1024 or lds(8) > 160 * 1024 else 8
     return lds(min(most, -(-I2 // rows)))
