@@ -62,7 +62,11 @@ __device__ __forceinline__ float2 factor_at(const FactorRef& U, int rn, int m, i
 
 constexpr int kThreads = 256, kWaves = 4;
 constexpr int kBatch = 8;                 // steps (4 rows each) of x per lane in flight
-constexpr int kChunk = 32;                // steps of the factor staged in LDS at a time
+// Rows above which stages whose wavefronts have columns of their own take the split bf16 operands: below, a quad is mostly
+// empty.  Both compressions of 100x100xKx60 behind the last, ranks 20 and r, float32 / split, us: K = 5, r 2 10.6 / 11.4; 6, 6
+// 13.2 / 13.8; 8, 3 11.7 / 12.3; but 9, 4 13.5 / 12.5; 12, 5 15.4 / 14.2.
+constexpr int kSplitRows = 8;
+constexpr int kOwnSteps = kSplitRows / 4; // steps of those that do not
 
 // The 16 column vectors of a wavefront: group `cg` of 16, lane column c; lanes past the end work on the
 // last column and store nothing.
@@ -80,8 +84,8 @@ __device__ __forceinline__ Cols columns_of(uint32_t cg, int c, uint32_t ncv, uin
   return q;
 }
 
-// SPLIT = false: a wavefront owns 16 column vectors and MT tiles of 16 output rows (blockIdx.y: which);
-//   the factor goes through LDS, shared by the 4 wavefronts.
+// SPLIT = false, at most kSplitRows rows: a wavefront owns 16 column vectors and MT tiles of 16 output rows (blockIdx.y:
+//   which); the factor goes through LDS, shared by the 4 wavefronts.
 // SPLIT = true, for few columns: the 4 wavefronts share 16 column vectors and split the rows k; each
 //   fetches the operands of its own rows straight into registers (no LDS table, no barrier in front of the
 //   matrix instructions) and the partial tiles meet in LDS, summed in a fixed order.
@@ -170,39 +174,23 @@ __global__ __launch_bounds__(kThreads) void k_mid(const float* __restrict__ x, c
       }
     }
   } else {
-    for (int jc0 = 0; jc0 < J; jc0 += kChunk) {
-      const int jn = J - jc0 < kChunk ? J - jc0 : kChunk;
-      V cur[kBatch];                                    // the chunk's first rows go in flight before the factor is staged
+    V v[kOwnSteps];                                     // rows in flight before the factor is staged
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) cur[u] = load_x(jc0 + u);
-      __syncthreads();                                  // previous chunk fully consumed
-      const FactorRef U = factor_from(jc0);
-      stage_table(sF, jn * MT * 64, tid, kThreads, [&](int e) -> float2 {
-        const int l = e & 63, t = (e >> 6) % MT, j = (e >> 6) / MT;
-        return factor_in(U, jc0, mbase + 16 * t + (l & 15), 4 * (jc0 + j) + (l >> 4));
-      });
-      __syncthreads();
-      auto step = [&](const V& v, int j) {
+    for (int j = 0; j < kOwnSteps; ++j) v[j] = load_x(j);
+    const FactorRef U = factor_from(0);
+    stage_table(sF, J * MT * 64, tid, kThreads, [&](int e) -> float2 {
+      const int l = e & 63, t = (e >> 6) % MT, j = (e >> 6) / MT;
+      return factor_in(U, 0, mbase + 16 * t + (l & 15), 4 * j + (l >> 4));
+    });
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kOwnSteps; ++j) {
+      if (j < J) {
         float xs[2 * VEC];
-        parts<VEC>(v, xs);
+        parts<VEC>(v[j], xs);
 #pragma unroll
         for (int t = 0; t < MT; ++t) cmac<VEC>(acc[t], sF[(j * MT + t) * 64 + lane], xs);
-      };
-      int j = 0;
-      for (; j + kBatch <= jn; j += kBatch) {
-        V nxt[kBatch];
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) nxt[u] = load_x(jc0 + j + kBatch + u);
-        __builtin_amdgcn_sched_barrier(0);              // the loads stay in front of the batch they overlap
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) step(cur[u], j + u);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) cur[u] = nxt[u];
       }
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u)
-        if (j + u < jn) step(cur[u], j + u);
     }
     if (!cq.valid) return;
     float* op = out + ((int64_t)cq.a * M) * row + (int64_t)cq.b * VEC * 2;
@@ -691,8 +679,6 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
 // below, the wavefronts of a workgroup share a group so that the stage still spreads over the chip (372 groups,
 // 90x77x66: 6.8 us shared, where 93 workgroups of one group per wavefront would leave 163 compute units idle).
 constexpr int64_t kOwnColumns = 1024;
-// Rows above which those stages take the split bf16 operands: below, a quad is mostly empty.
-constexpr int kSplitRows = 8;
 
 // k_expand's KS: steps of four rows of x, rounded up to the next variant.  Padded to 4, 8 or 16 steps a rank of a few was
 // matrix work for nothing: 12M columns of one row 284 us, now 105; 3M from 2 rows to 4 78, now 34; 500000 from 20 to 24 43,
@@ -802,8 +788,7 @@ void launch_mid(hipStream_t s, const float2* x, const float2* U, int rn, bool pr
   }
   const int mt = Q >= 4 ? 4 : Q >= 2 ? 2 : 1;
   const dim3 grid((unsigned)(own ? (groups + kWaves - 1) / kWaves : groups), (unsigned)((Q + mt - 1) / mt));
-  const int jn = (K + 3) / 4 < kChunk ? (K + 3) / 4 : kChunk;
-  const size_t lds = own ? (size_t)jn * mt * 512 : (size_t)kWaves * mt * 2 * vec * 1024;
+  const size_t lds = own ? (size_t)((K + 3) / 4) * mt * 512 : (size_t)kWaves * mt * 2 * vec * 1024;
 #define TGRAD_MID(V_, MT_, P_, S_)                                                                   \
   do {                                                                                               \
     allow_lds(k_mid<V_, MT_, P_, S_>, lds);                                                          \
