@@ -960,8 +960,10 @@ int tgrad_step_static(const tgrad_config* cfg, void* state_dev, int64_t t, void*
   c.profiling = false;
   if (error_pending_on_entry()) return TGRAD_ERR_HIP;
   Plan& p = c.plan;
-  if (p.order != TGRAD_ORDER_US_LR) zero_u32(c.stream, c.w<uint32_t>(p.ws_tile_zero), p.zero_tiles);
-  if (t % cfg->refresh_every == 0) {
+  const bool refresh = t % cfg->refresh_every == 0;
+  // (k_head does not read them: it keeps the support where it is)
+  if (p.order != TGRAD_ORDER_US_LR && (refresh || !p.narrow)) zero_u32(c.stream, c.w<uint32_t>(p.ws_tile_zero), p.zero_tiles);
+  if (refresh) {
     rc = do_refresh(&c, grad_dev);
     if (rc != TGRAD_OK) return rc;
   } else {
