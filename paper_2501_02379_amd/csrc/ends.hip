@@ -1012,11 +1012,11 @@ bool wide_tiles_pay(int r, int I2, int r2, int64_t nslabs) {
 //   4096 slabs: 4x5 24 / 27, 8x33 32 / 33, 36x5 31 / 33 (the saved launches win).
 // r: 65536 slabs of 12x9 with r = 1 95 / 82, r = 6 109 / 115, r = 9 126 / 143.
 bool ends_kernel_pays(int K, int r, int I2, int r2, int64_t nslabs) {
-  // (Few slabs of the longest: eight tiles of 32 rows and two tiles of the first rank per wavefront of k_head, or thirteen
-  // and more of 16 with all operands doubled, are not worth it.  27 slabs of 232x15, r 32,2 26 / 24, 76 of 246x30, r 21,8
-  // 34 / 32, 96 of 204x56, r 27,16 48 / 44; but 84 of 188x20, r 30,7 26 / 30, 68 of 206x67, r 32,11 47 / 47, 39 of 146x62,
+  // (Few slabs of the longest, with two tiles of their rank: eight tiles of 32 rows with a workgroup for each slab or a table
+  // for few of them, or thirteen and more of 16 with two column tiles, are not worth it.  27 slabs of 232x15, r 32,2 26 / 24,
+  // 76 of 246x30, r 21,8 34 / 32, 120 of 232x13, r 24,9 49 / 44, 96 of 204x56, r 27,16 48 / 44; but 84 of 188x20, r 30,7 26 / 30, 68 of 206x67, r 32,11 47 / 47, 39 of 146x62,
   // r 18,7 25 / 37, 126 of 242x26, r 25,15 34 / 40.)
-  if (nslabs < 128 && r2 > 16 && (K <= 33 ? K > 12 && r <= 8 && I2 > 224 : K > 52 && r > 8 && I2 > 192)) return false;
+  if (nslabs < 128 && r2 > 16 && (K <= 33 ? I2 > 224 && K > 12 && (r <= 8 || K <= 20) : I2 > 192 && K > 52 && r > 8)) return false;
   // (... nor with four wavefronts for all of a compute unit while a fourth round is begun and not filled: 816 slabs of 247x60,
   // r 26,12 135 / 130, 900 of 220x50 122 / 119, 909 of 236x51, r 30,12 127 / 122; but 625 of 250x65, r 32,16 115 / 121, 1600
   // of 220x50 156 / 165.)
