@@ -24,6 +24,7 @@ import numpy as np
 HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 MFMA_FP32_PEAK_TF = 157.3      # dense fp32 matrix
 MFMA_FP64_PEAK_TF = 78.6       # dense fp64 matrix
+MFMA_SPLIT_PEAK_TF = 2500 / 6  # float32 products as six dense bf16 ones
 
 
 def log(*a):
@@ -78,7 +79,9 @@ def kernel_model(w, fused, weight_bytes=8, core_fused=0):
         by += b_
         fl += f_
     if proj_end > first_mid:
-        m["project"] = {"bytes": by, "flops": fl, "bound": "mfma", "launches_per_step": proj_end - first_mid}
+        A, K, M, B = stage_dims(True, first_mid)
+        m["project"] = {"bytes": by, "flops": fl, "bound": "mfma", "launches_per_step": proj_end - first_mid,
+                        "split": A * B >= 16384 and K > 8}
     last_mid = N - 2 if fused else N - 1                  # reconstruction stages 0 .. last_mid - 1 run alone
     back_start = core_fused
     by = fl = 0
@@ -87,11 +90,14 @@ def kernel_model(w, fused, weight_bytes=8, core_fused=0):
         by += b_
         fl += f_
     if last_mid > back_start:
-        m["backproject"] = {"bytes": by, "flops": fl, "bound": "mfma", "launches_per_step": last_mid - back_start}
+        A, K, M, B = stage_dims(False, last_mid - 1)
+        m["backproject"] = {"bytes": by, "flops": fl, "bound": "mfma", "launches_per_step": last_mid - back_start,
+                            "split": A * B >= 16384 and K > 8}
     if core_fused:
         A0, K0, M0, B0 = stage_dims(True, N - core_fused)    # the kernel's input: (A0, K0, B0), A0 = I_1 with two modes
         fl = sum(2 * vol(*stage_dims(True, s))[1] for s in range(N - core_fused, N))
-        m["core"] = {"bytes": 2 * A0 * K0 * B0 * 8 + C * (8 + 12 + 12), "flops": fl + 12 * C, "bound": "mfma"}
+        m["core"] = {"bytes": 2 * A0 * K0 * B0 * 8 + C * (8 + 12 + 12), "flops": fl + 12 * C, "bound": "mfma",
+                     "split": core_fused == 1}
     # last reconstruction stage fused with the sparse AdamUpdate, the scatter-add and the weight
     # update: reads its input tensor and W, writes W; per sparse entry its index, gathered value
     # and both moments are read and the moments written back
@@ -361,12 +367,14 @@ def main():
             elif mm["bound"] == "mfma64":
                 ent["frac_mfma_fp64_peak"] = round(tfl / MFMA_FP64_PEAK_TF, 4)
                 ent["frac_mfma_fp64_achievable"] = round(tfl / mfma_tf["fp64"], 4)
-            else:
-                ent["frac_mfma_fp32_peak"] = round(tfl / MFMA_FP32_PEAK_TF, 4)
-                ent["frac_mfma_fp32_achievable"] = round(tfl / mfma_tf["fp32"], 4)
-            if name == "project_first":          # straddles the ridge: both fractions
-                ent["frac_mfma_fp32_peak"] = round(tfl / MFMA_FP32_PEAK_TF, 4)
-                ent["frac_mfma_fp32_achievable"] = round(tfl / mfma_tf["fp32"], 4)
+            # matrix products, also of the first pass: on split bf16 operands (six products for one) or on float32
+            # instructions (the 32 x 32 end kernels, which have a factor packed, the two-mode core kernel, few columns)
+            if mm["bound"] == "mfma" or name == "project_first":
+                if mm.get("split", name == "project_first" and fused and "factor_pack" not in rtimes):
+                    ent["frac_mfma_split_bf16_peak"] = round(tfl / MFMA_SPLIT_PEAK_TF, 4)
+                else:
+                    ent["frac_mfma_fp32_peak"] = round(tfl / MFMA_FP32_PEAK_TF, 4)
+                    ent["frac_mfma_fp32_achievable"] = round(tfl / mfma_tf["fp32"], 4)
         kernels[name] = ent
     refresh_names = ("select", "gram", "eig", "mask", "factor", "hooi", "tile", "residual", "gather")
     step_kernels = [n for n in kernels if not n.startswith(refresh_names)]
@@ -379,7 +387,8 @@ def main():
         if mm["bound"] == "hbm":
             ach, peak, unit = mm["bytes"] / lp / avg_s / 1e9, HBM_PEAK_GBS, "GB/s"
         else:
-            ach, peak, unit = mm["flops"] / lp / avg_s / 1e12, MFMA_FP32_PEAK_TF, "TFLOP/s"
+            ach, unit = mm["flops"] / lp / avg_s / 1e12, "TFLOP/s"
+            peak = MFMA_SPLIT_PEAK_TF if mm.get("split") else MFMA_FP32_PEAK_TF
         traffic = measured_traffic(w.name, dom) if args.weights == "c64" else None
         roofline = {"kernel": dom, "bound": "hbm" if mm["bound"] == "hbm" else "mfma",
                     "achieved": round(ach, 2), "peak": peak, "unit": unit, "frac": round(ach / peak, 4),
