@@ -3,18 +3,19 @@
 //   k_mid      out[a, m, b] = sum_k F[m, k] x[a, k, b],  F = U^H (compression) or U
 //   k_expand   the same for a short k (a rank): x stays in registers while the output rows go by
 //   k_core     mode 1 both ways around AdamUpdate on the Tucker core, in one launch
+// k_core, and the two others where a tensor fills the chip (k_mid_split, k_expand_split), run on split bf16 operands
+// (device_common.h), k_mid and k_expand on float32 instructions.
 // Tiles are 16 x 16 (v_mfma_f32_16x16x4f32, the same rate as 32x32x2).  Lanes g = lane / 16, c = lane % 16:
 //   A[i = c][k = g] = F (row m = i),  B[k = g][j = c] = x (16 neighbouring columns: 128 or 256
 //   contiguous bytes per row),  D register r: D[i = 4 g + r][j = c].
-// re(F x) = Fr xr - Fi xi, im(F x) = Fr xi + Fi xr: four real matrix instructions per step, column and tile.
+// re(F x) = Fr xr - Fi xi, im(F x) = Fr xi + Fi xr: four real products per step, column and tile.
 // 16-wide tiles because ranks are padded to them (8 ... 24 in most layers: half the matrix work of 32-wide
 // tiles) and because a wavefront then needs 16 columns instead of 32 or 64: twice to four times as many
 // wavefronts in flight for the same tensor.  What bounds these stages is latency - a launch, one memory round
 // trip for operands, one for x - until a tensor fills the chip, matrix work and memory in about equal parts after that.
-// Measured (rocprofv3, us; before: 32x32x2 tiles, factor always through LDS): 64x64x32x17, r 16,16,8,4:
-// compression 10.0 -> 4.8, core 15.8 -> 4.2, expansion 6.2 -> 3.4; 90x77x45x23, r 23,19,11,6: compressions
-// 17.6 + 12.9 -> 9.0 + 6.8, core 22.6 -> 7.3, expansions 8.0 + 12.2 -> 7.1 + 9.3; 128x128x64x33, r 64,64,32,16:
-// compressions + core + expansions 239 -> 227.
+// Measured (rocprofv3, us; 32x32x2 tiles with the factor always through LDS -> 16 x 16 in float32 -> as they are):
+// 128x128x64x33, r 64,64,32,16: compressions + core + expansions 239 -> 147 -> 106; 128x128x128x65, r 32,32,32,16: 75 (16 x 16
+// in float32) -> 55.
 #include "device_common.h"
 #include "launch_util.h"
 
@@ -532,20 +533,23 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
   constexpr int kEnt = (MT * 256 + kThr - 1) / kThr;
   float2 mm[kEnt];
   float vv[kEnt];
-  auto entry = [&](int g, int q, uint32_t& idx) -> bool {
+  // (The first group's places in 64 bits: in 32 their products came in front of the other requests, 128 rows, rank 32, 256
+  // groups 8.3 us, not 7.7.  The following ones' in 32: in 64 those of 1024 groups took 17.1 us, not 16.4.)
+  auto entry = [&](int g, int q, auto wide, uint32_t& idx) -> bool {
+    typedef decltype(wide) Int;
     const int e = tid + q * kThr;
     const int l = e & 63, r = (e >> 6) & 3, t = e >> 8;
     const int m = 16 * t + 4 * (l >> 4) + r;
-    const int64_t bb = (int64_t)g * 16 + (l & 15);             // (in 32 bits 128 rows, rank 32, 256 groups took 8.3 us, not 7.7)
-    const bool live = t < MT && m < M && bb < B;
-    idx = live ? (uint32_t)((int64_t)m * B + bb) : 0u;
+    const Int bb = (Int)g * 16 + (Int)(l & 15);
+    const bool live = t < MT && m < M && bb < (Int)B;
+    idx = live ? (uint32_t)((Int)m * (Int)B + bb) : 0u;
     return live;
   };
-  auto fetch_moments = [&](int g) {
+  auto fetch_moments = [&](int g, auto wide) {
 #pragma unroll
     for (int q = 0; q < kEnt; ++q) {
       uint32_t idx;
-      entry(g, q, idx);
+      entry(g, q, wide, idx);
       mm[q] = ad.m[idx];
       vv[q] = ad.v[idx];
     }
@@ -570,7 +574,7 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
   fetch_x(g, 0);
   {
     const auto in = fetch_in(0);
-    fetch_moments(g);
+    fetch_moments(g, int64_t());
     if constexpr (MT == 4) {                                   // (both sets of operands at once do not fit the registers)
       in(fc);
       __builtin_amdgcn_sched_barrier(0);
@@ -630,7 +634,7 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
         const float d = 1.f / (sqrtf(v * ad.inv_c2) + ad.eps);
         float nr = 0.f, ni = 0.f;
         uint32_t idx;
-        if (entry(g, q, idx)) {
+        if (entry(g, q, uint32_t(), idx)) {
           ad.m[idx] = m;
           ad.v[idx] = v;
           ad.g_out[idx] = make_float2(gre, gim);
@@ -645,7 +649,7 @@ __global__ __launch_bounds__(64 * W) void k_core(const float* x, const float2* _
         pn[512] = l3;
       }
     }
-    if (gn < groups) fetch_moments(gn);
+    if (gn < groups) fetch_moments(gn, uint32_t());
     __syncthreads();
     // expansion
     const int64_t b = (int64_t)g * 16 + col;
