@@ -1,11 +1,11 @@
 // First and last kernel of a step on 16 x 16 matrix-core tiles, for any extent of mode N-1:
 //   k_head  g_S <- G[Omega];  out[slab, m2, m3] = sum_{i2, i3} conj(U2[i2, m2]) conj(U3[i3, m3]) (G - Sparse(G, Omega))[slab, i2, i3]
 //           (or of G itself, in the two orders in which the low-rank part sees the full gradient: a gather kernel of its own
-//           took 8 us at 64x64x64x32 with 5 % of the entries, whole step 89 -> 80)
+//           took 8 us at 64x64x64x32 with 5 % of the entries, whole step 89 -> 82)
 //   k_tail  W <- (1 - lr wd) W - lr (alpha z x_(N-1) U2 x_N U3 + lambda scatter(AdamUpdate(g_S)))
 // with modes N-1 (extent I2, rank M2 <= 32) and N (extent K, rank M <= 16) in one pass over G and one over W; a
 // slab is the I2 x K block of one set of leading indices.  (contract_mfma.hip has the same two passes on 32 x 32
-// tiles, for ranks that fill them: ends_kernel_fits has the line.)
+// tiles, for few slabs of ranks that fill them: wide_tiles_pay has the line.)
 //
 // Why 16 x 16: a rank is padded to the tile, so a last-mode rank of 4 or 8 - which most layers have - and a rank up to 16 of
 // mode N-1 cost a half to a quarter of the matrix work of 32-wide tiles.  Why split bf16 operands (device_common.h): in
@@ -66,10 +66,12 @@ __host__ __device__ constexpr int head_slice(int ES, int K, int T4) {
   return ((c > 1024 ? c : 1024) + 3) & ~3;                               // 1024: partial sums of two by two tiles
 }
 // Tiles in flight per wavefront.  What a compute unit has in flight decides what it streams (64-row slabs of 33 elements:
-// loads alone 4.5 TB/s with 67 KB, 5.3 with 100 KB); registers hold more of it than LDS would.
+// loads alone 4.5 TB/s with 67 KB, 5.3 with 100 KB); registers hold more of it than LDS would.  k_head with one / two: 6400
+// slabs of 100x36, r 16,8 51 / 48 us, 10000 of 64x65 66 / 64, 16384 of 128x65, r 32,16 239 / 237, of 64x33, r 16,8 56 / 56.
 constexpr int head_ahead(int T4, int NC) { return T4 >= 9 && NC == 2 ? 2 : T4 >= 13 ? 2 : 1; }
-// Coefficients of more than two operands' worth are kept in LDS (a tile reads them once) where a wavefront has many tiles
-// (HEAD_MANY), fewer in registers.
+// Coefficients of two column tiles and more than two operands' worth each way are kept in LDS (a tile reads them once) where a
+// wavefront has many tiles (HEAD_MANY), others in registers: with one column tile and rows of 34 to 68 elements LDS was up to
+// 23 % slower (16384 slabs of 80x34, r 20,6 95 / 88 us; 2511 of 113x38, r 31,8 38 / 31).
 constexpr bool head_many_coefs(int T4, int NC) { return head_quads(T4) * NC > 2; }
 constexpr bool head_coef_lds(int T4, int NC) { return NC == 2 && head_many_coefs(T4, NC); }
 constexpr int kHeadItem = 6 * 64;         // u32v4 of the table per 32 rows and tile of M2: (Fr, Fi) x (h, m, l) x lane
@@ -88,7 +90,7 @@ struct HeadArgs {
   float* out;                   // (nslabs, M2, M) complex
 };
 
-// What a launch of a class with many coefficients (head_coef_lds) looks like; the other classes are always HEAD_MANY.
+// What a launch of a class with many coefficients (head_many_coefs) looks like; the others are HEAD_MANY (but see head_has_one).
 // Staging the coefficients, a second tile in flight and the waits between an operand in LDS and its product are worth their
 // while where a wavefront has many tiles.  Where it has one or two they were 1.0 to 1.7 us of 7 to 8 (head_mode has the lines).
 //   HEAD_MANY  wavefronts that walk whole slabs, workgroups that stay for several shared slabs
@@ -605,7 +607,8 @@ constexpr bool tail_coef_lds(int CT, int NC) { return CT * NC > 4; }
 constexpr int tail_pieces(int CT) { return CT == 2 ? 5 : CT == 3 ? 7 : 9; }   // complex64 pieces per lane of a tile
 __host__ __device__ constexpr int tail_slice(int M, int R) { return (R * 2 * M + 3) & ~3; }
 
-// Tiles in flight per wavefront: two where the registers hold them (see head_ahead)
+// Tiles in flight per wavefront: two where the registers hold them (see head_ahead; 6400 slabs of 100x36, r 16,8 75 / 73 us,
+// the others of those the same)
 constexpr int tail_ahead(int CT, int NC, int SA) { return SA == 8 && NC == 2 ? 1 : CT == 9 || NC == 2 ? 2 : 1; }
 
 struct TailArgs {
