@@ -67,7 +67,7 @@ END_SHAPES = [
     ((46, 45, 40, 33), (4, 4, 20, 12), 200000, "cbf16", False), # ... more than 64 support entries in a tile
     ((46, 45, 24, 65), (3, 4, 17, 16), 9000, "c64", False),     # 16-row tiles in pairs
     ((46, 45, 40, 65), (3, 4, 17, 16), 9000, "cbf16", False),   # ... three to a slab: the last alone
-    ((20, 20, 40, 50), (3, 4, 9, 9), 3000, "c64", False),       # ... shared by the wavefronts of a workgroup: never in pairs
+    ((20, 20, 40, 50), (3, 4, 9, 9), 3000, "c64", False),       # ... a tile per wavefront: never in pairs
     ((33, 32, 24, 42), (3, 4, 9, 6), 3000, "cbf16", False),     # three quads, no remainder
     ((33, 32, 21, 25), (3, 4, 9, 8), 3000, "c64", False),       # two quads, the second of nine elements
     ((13, 10, 250, 34), (3, 4, 20, 10), 9000, "c64", False),    # a table that leaves one workgroup to a compute unit
