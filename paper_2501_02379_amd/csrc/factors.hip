@@ -1209,8 +1209,8 @@ __global__ __launch_bounds__(kEigThreads) void k_eig_finish(EigJobs jobs) {
 //   k_trid      (one workgroup per matrix) Householder tridiagonalisation  A = Q T Q^H; reflector i annihilates column
 //               i below the subdiagonal; T real symmetric tridiagonal
 //   k_trid_vec  (one wavefront per eigenvector)
-//               the k-th largest eigenvalue of T by multisection on Sturm counts (64 points per step: 10 steps from the
-//               Gershgorin interval down to rounding), its eigenvector by inverse iteration (Gaussian elimination
+//               the k-th largest eigenvalue of T by multisection on Sturm counts (64 points per step, from the
+//               Gershgorin interval), its eigenvector by inverse iteration (Gaussian elimination
 //               with partial pivoting on T - lambda I from both ends, three solves from a fixed pseudo-random vector), the
 //               back-transformation with the reflectors, the phase convention and the float32 factor.
 // A cyclic Jacobi sweep reads and writes the whole matrix in every one of its n - 1 rounds, about ten sweeps long;
@@ -1219,13 +1219,13 @@ __global__ __launch_bounds__(kEigThreads) void k_eig_finish(EigJobs jobs) {
 // within 1e-7 of the spectral radius of one of the r leading ones (exactly repeated eigenvalues, a zero matrix),
 // this path declines (status[2] = 1) and the Jacobi kernels, which handle clusters gracefully, solve the matrix.
 //
-// Everything here is a serial chain, so what bounds it is latency.  k_trid keeps the matrix in registers (32 x 32
-// threads, elements (ty + 32 a, tx + 32 b), both triangles) and passes two barriers per step: every wavefront
-// derives the reflector from the column in LDS by itself, and the sums run over lanes without LDS.  In LDS, with
-// eight barriers per step and one wavefront deriving the reflector, a step took 6 us at n = 128.
-// Measured, four modes at once, us, tridiagonalisation + vectors: 128,128,128,65 (r 32,32,32,16) 935 + 66 -> 337 + 106;
-// 64,64,32,17 (r 16,16,8,4) 338 + 34 -> 110 + 57.
-constexpr int kMultiSteps = 10;        // 65^10 > 2^60
+// Everything here is a serial chain of one wavefront's instructions (4.5 cycles each, also where one needs the result of
+// the one before; a sum over the lanes 156), so what counts is how many there are.  k_trid keeps the matrix in registers, passes
+// one barrier per step and has the rank-2 update and the next matrix-vector product in one pass with the broadcast of rows
+// inside the multiply-adds.  With two barriers, the update and the product apart and the rows' factors read from LDS a step took
+// 1.7 us at n = 64 and 2.7 at 128; it takes 1.1 and 1.8.
+// Measured, four modes at once, us, tridiagonalisation + vectors together: 128,128,128,65 (r 32,32,32,16) 433 -> 277;
+// 64,64,32,17 (r 16,16,8,4) 155 -> 91.
 constexpr double kClusterTol = 1e-7;
 
 // work buffer of a job: reflector factors, T, and the bounds of its spectrum
@@ -1290,196 +1290,224 @@ __device__ __forceinline__ uint32_t trid_mix(uint32_t x) {
   return x;
 }
 
-// W wavefronts; thread (ty, tx) of the 2 W x 32 grid holds elements (ty + 2 W a, tx + 32 b), a < NA, b < NB.  Few
-// wavefronts, because every one of them derives the reflector: with 16 the four on a SIMD spent two thirds of a step
-// on that (n = 128: 4.7 us a step, with 8 wavefronts 2.7).
+// acc + S x for one row: the row's value of every operand sits in lane `LANE` of each group of 16 lanes, and the matrix
+// column's in the lane's own registers.  S <- S - v w^H - w v^H first, then acc <- acc + conj(S) x (ay - az is the
+// imaginary part).  Written out because the broadcast is part of the multiply-add (v_fmac_f64_dpp: 4.9 cycles, 4.5 without),
+// where the compiler makes a move of each (a tridiagonalisation of 128 rows 16 % longer); s_nop 1: a DPP operand may not be
+// read within two states of its last write.
+template <int LANE>
+__device__ __forceinline__ void trid_row(double2& s, double& ax, double& ay, double& az, const double2& v, const double2& w,
+                                         const double2& x, const double2& nvc, const double2& nwc, double vcy, double wcy) {
+#define TGRAD_ROW(d, src, m) "v_fmac_f64_dpp %" #d ", %" #src ", %" #m " row_newbcast:%17 row_mask:0xf bank_mask:0xf\n\t"
+  asm("s_nop 1\n\t"
+      TGRAD_ROW(0, 5, 13) TGRAD_ROW(1, 5, 16) TGRAD_ROW(0, 6, 14) TGRAD_ROW(1, 6, 13)      // v_j conj(w_k)
+      TGRAD_ROW(0, 7, 11) TGRAD_ROW(1, 7, 15) TGRAD_ROW(0, 8, 12) TGRAD_ROW(1, 8, 11)      // w_j conj(v_k)
+      TGRAD_ROW(2, 9, 0) TGRAD_ROW(3, 10, 0) TGRAD_ROW(2, 10, 1) TGRAD_ROW(4, 9, 1)        // conj(S) x_j
+      : "+&v"(s.x), "+&v"(s.y), "+&v"(ax), "+&v"(ay), "+&v"(az)
+      : "v"(v.x), "v"(v.y), "v"(w.x), "v"(w.y), "v"(x.x), "v"(x.y), "v"(nvc.x), "v"(nvc.y), "v"(nwc.x), "v"(nwc.y), "v"(vcy),
+        "v"(wcy), "n"(LANE));
+#undef TGRAD_ROW
+}
+
+// Place of row j in the LDS vectors: index rho + 4 m of a group of 64 at 16 rho + m, so that lane (rho, m) = 16 rho + m of a
+// wavefront reads its row there and every group of 16 lanes a wavefront's columns.
+__device__ __forceinline__ int trid_pos(int j) { return (j & 64) + 16 * (j & 3) + ((j & 63) >> 2); }
+
+// Wavefront (ch, rg) holds columns 64 ch + rg + 4 m (m = lane % 16), lane (rho, m) of it rows 64 s + rho + 4 a, a < 16, s < NS.
+// A step is one barrier long: behind it, every wavefront has column i + 1 of S as it was before reflector i and y = S x (x: what
+// column i has below row i + 1), from which it derives S v = column + scale y, w and the next column z by itself, one row per
+// lane; its columns' entries of v and w come from other lanes (ds_bpermute).  The rank-2 update of S and the product of the new
+// S with the next column then are one pass over the registers.
 struct TridLds {
-  double2 col[kEigTriMaxN], v[kEigTriMaxN], p[kEigTriMaxN];
+  double2 col[2][kEigTriMaxN], y[2][kEigTriMaxN];   // by parity of the step: a slower wavefront still reads the other
   double d[kEigTriMaxN], e[kEigTriMaxN];
 };
 
 // Workgroup barrier that orders LDS only (a full one would also wait for the reflectors on their way to memory)
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-template <int W, int NA, int NB>
-__device__ __forceinline__ void tridiagonalise(const EigJob& jb, TridLds& lds) {
-  constexpr int T = 64 * W, RG = 2 * W;
-  static_assert(NA <= 8 && RG * NA == 32 * NB && 32 * NB <= kEigTriMaxN, "");
-  const int n = jb.n;
-  const int tid = threadIdx.x, lane = tid & 63, tx = tid & 31, ty = tid >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const double2* G = reinterpret_cast<const double2*>(jb.gram);
-  double2* Vg = reinterpret_cast<double2*>(jb.V);   // reflector i: Vg[i * n + row], rows i + 1 .. n - 1
-  double2* tauG = trid_tau(jb);
-  double2* scol = lds.col;
-  double2* sv = lds.v;
-  double2* sp = lds.p;
-  double* sd = lds.d;
-  double* se = lds.e;
+__device__ __forceinline__ double read_lane_d(double v, int lane) {
+  const int2 w = __builtin_bit_cast(int2, v);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(w.x, lane), __builtin_amdgcn_readlane(w.y, lane)));
+}
+__device__ __forceinline__ double permute_d(int from, double v) {   // from: 4 x lane
+  const int2 w = __builtin_bit_cast(int2, v);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_ds_bpermute(from, w.x), __builtin_amdgcn_ds_bpermute(from, w.y)));
+}
 
-  double2 S[NA][NB];
+template <int NS>
+__device__ __forceinline__ void tridiagonalise(const EigJob& jb, TridLds& lds) {
+  constexpr int T = 256 * NS;
+  const int n = jb.n;
+  const int tid = threadIdx.x, lane = tid & 63, rho = lane >> 4, m = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ch = wave >> 2, rg = wave & 3;
+  const double2* G = reinterpret_cast<const double2*>(jb.gram);
+  double2* Vg = reinterpret_cast<double2*>(jb.V);   // reflector i: Vg[i * n + row], zero up to row i
+  double2* tauG = trid_tau(jb);
+  const double2 zero = make_double2(0., 0.);
+  const int kc = 64 * ch + rg + 4 * m, pc = 64 * ch + 16 * rg + m;   // own column, its place
+  const int from = 4 * (16 * rg + m);            // the lane that has row kc, times 4
+  const bool writer = rg == 1 && ch == (n > 64 ? NS - 1 : 0);   // (a wavefront that takes part to the last step)
+  int jr[NS];                                    // own rows, of which a wavefront's 64 lanes have one each
 #pragma unroll
-  for (int a = 0; a < NA; ++a)
+  for (int s = 0; s < NS; ++s) jr[s] = 64 * s + rho + 4 * m;
+
+  double2 S[NS][16];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int row = ty + RG * a, c = tx + 32 * b;
-      S[a][b] = row < n && c < n ? G[row * n + c] : make_double2(0., 0.);
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int a = 0; a < 16; ++a) {
+      const int row = 64 * s + rho + 4 * a;
+      S[s][a] = row < n && kc < n ? G[row * n + kc] : zero;
     }
-  for (int j = tid; j < kEigTriMaxN; j += T) scol[j] = sv[j] = sp[j] = make_double2(0., 0.);
+  double2 x[NS], v[NS], w[NS];                   // column i below row i + 1; reflector and w of step i - 1, by rows
+  double2 vc = zero, wc = zero;                  // and by own column
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    x[s] = jr[s] > 1 && jr[s] < n ? G[jr[s] * n] : zero;
+    v[s] = w[s] = zero;
+  }
+  double2 alpha = n > 1 ? G[n] : zero;           // entry i + 1 of column i
+  double diag = G[0].x;
+  for (int j = tid; j < 2 * kEigTriMaxN; j += T) (&lds.col[0][0])[j] = (&lds.y[0][0])[j] = zero;   // (places past n stay zero)
   __syncthreads();
-  auto publish = [&](int c, auto b_c) {          // column c, of block column b_c, -> LDS
-    constexpr int b = decltype(b_c)::value;
-    if (tx == (c & 31)) {
-#pragma unroll
-      for (int a = 0; a < NA; ++a) scol[ty + RG * a] = S[a][b];
+
+  // Steps i0 .. i1 - 1, of which rows and columns below 64 s0 are finished.  Every multiply-add is written out: what the
+  // wavefronts derive from the LDS vectors each for itself has to have the same bits.
+  auto steps = [&](int i0, int i1, auto s0_c) __attribute__((always_inline)) {
+    constexpr int s0 = decltype(s0_c)::value;
+    if (ch < s0 || 64 * ch >= n) {               // nothing left of this wavefront's columns
+      for (int i = i0; i < i1; ++i) lds_barrier();
+      return;
     }
-  };
-  publish(0, std::integral_constant<int, 0>());
-  // Steps of block column P: rows and columns of the blocks before it are finished, which the code knows (a branch per
-  // block would put the LDS latency of its operands in front of every one of them).
-  auto block_column = [&](auto p_c) __attribute__((always_inline)) {
-    constexpr int P = decltype(p_c)::value, A0 = 32 * P / RG;
-    auto publish_next = [&](int c) {             // (the last step of a block column publishes the next one's first)
-      if (P + 1 < NB && c == 32 * (P + 1)) publish(c, std::integral_constant<int, (P + 1 < NB ? P + 1 : P)>());
-      else publish(c, p_c);
-    };
-    const int i_end = 32 * (P + 1) < n - 1 ? 32 * (P + 1) : n - 1;
-    for (int i = 32 * P; i < i_end; ++i) {
-      lds_barrier();
-      // the reflector of column i, by every wavefront: v = (0 .. 0, 1, scale x)
-      const double2 c0 = scol[lane], c1 = n > 64 ? scol[lane + 64] : make_double2(0., 0.), alpha = scol[i + 1];
-      double xn2 = lane > i + 1 ? c0.x * c0.x + c0.y * c0.y : 0.;
-      if (n > 64) xn2 += lane + 64 > i + 1 ? c1.x * c1.x + c1.y * c1.y : 0.;
+    for (int i = i0; i < i1; ++i) {
+      const int par = i & 1;
+      // the reflector of column i: v = (0 .. 0, 1, scale x)
+      double xn2 = 0.;
+#pragma unroll
+      for (int s = s0; s < NS; ++s) xn2 = fma(x[s].x, x[s].x, fma(x[s].y, x[s].y, xn2));
       xn2 = wave_sum_d(xn2);
-      double2 tau = make_double2(0., 0.), scale = make_double2(0., 0.);
+      double2 tau = zero, scale = zero;
       double beta = alpha.x;
-      const bool reflect = !(xn2 == 0. && alpha.y == 0.);        // (the same in every wavefront)
-      if (reflect) {
-        beta = -copysign(sqrt(alpha.x * alpha.x + alpha.y * alpha.y + xn2), alpha.x);
-        const double inv_beta = rcp_nr(beta);
+      if (!(xn2 == 0. && alpha.y == 0.)) {
+        // beta = -+ sqrt(t), 1 / beta: the hardware's reciprocal root and two Newton steps
+        const double t = fma(alpha.x, alpha.x, fma(alpha.y, alpha.y, xn2));
+        double r = __builtin_amdgcn_rsq(t);
+        r = fma(0.5 * r, fma(-t * r, r, 1.), r);
+        r = fma(0.5 * r, fma(-t * r, r, 1.), r);
+        const double root = t * r;
+        beta = -copysign(fma(fma(-root, root, t), 0.5 * r, root), alpha.x);
+        const double inv_beta = -copysign(r, alpha.x);
         tau = make_double2((beta - alpha.x) * inv_beta, -alpha.y * inv_beta);
         const double2 z = make_double2(alpha.x - beta, alpha.y);              // 1 / (alpha - beta)
-        const double inv = rcp_nr(z.x * z.x + z.y * z.y);
+        const double inv = rcp_nr(fma(z.x, z.x, z.y * z.y));
         scale = make_double2(z.x * inv, -z.y * inv);
       }
-      auto v_of = [&](int j, double2 x) -> double2 {
-        return j > i + 1 ? cmuld(x, scale) : make_double2(j == i + 1 ? 1. : 0., 0.);
-      };
-      const double2 v0 = v_of(lane, c0), v1 = n > 64 ? v_of(lane + 64, c1) : make_double2(0., 0.);
-      if (wave == 0) {
-        sv[lane] = v0;
-        sv[lane + 64] = v1;
-      } else if (wave == 1) {
-        if (lane > i && lane < n) Vg[(size_t)i * n + lane] = v0;
-        if (lane + 64 > i && lane + 64 < n) Vg[(size_t)i * n + lane + 64] = v1;
-      } else if (wave == 2 && lane == 0) {
-        tauG[i] = tau;
-        sd[i] = scol[i].x;
-        se[i] = beta;
+      double2 vn[NS];
+#pragma unroll
+      for (int s = s0; s < NS; ++s) {
+        vn[s].x = jr[s] == i + 1 ? 1. : fma(scale.x, x[s].x, -(scale.y * x[s].y));
+        vn[s].y = fma(scale.x, x[s].y, scale.y * x[s].x);
       }
-      if (!reflect) {
-        lds_barrier();
-        publish_next(i + 1);
-        continue;
+      const double2 vo = NS > 1 && s0 == 0 && ch > 0 ? vn[NS - 1] : vn[s0];
+      const double2 vnc = make_double2(permute_d(from, vo.x), permute_d(from, vo.y));
+      if (writer) {
+        if (lane == 0) {
+          lds.d[i] = diag;
+          lds.e[i] = beta;
+          tauG[i] = tau;
+        }
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+          if (jr[s] < n) Vg[(size_t)i * n + jr[s]] = s < s0 ? zero : vn[s];
       }
-      {                                            // S v, rows summed over the 32 threads that hold them
-        double2 acc[8];
+      double ax = 0., ay = 0., az = 0.;
+      const double2 nvc = make_double2(-vc.x, -vc.y), nwc = make_double2(-wc.x, -wc.y);
 #pragma unroll
-        for (int a = 0; a < 8; ++a) acc[a] = make_double2(0., 0.);
-#pragma unroll
-        for (int b = P; b < NB; ++b) {
-          const double2 v = v_of(tx + 32 * b, scol[tx + 32 * b]);
-#pragma unroll
-          for (int a = A0; a < NA; ++a) {
-            acc[a].x += S[a][b].x * v.x - S[a][b].y * v.y;
-            acc[a].y += S[a][b].x * v.y + S[a][b].y * v.x;
+      for (int s = s0; s < NS; ++s) {
+        auto group = [&](auto g_c) __attribute__((always_inline)) {          // 16 rows: all finished, or past the matrix
+          constexpr int g = decltype(g_c)::value;
+          if (64 * s + 16 * g + 16 <= i + 1 || 64 * s + 16 * g >= n) return;
+          trid_row<4 * g>(S[s][4 * g], ax, ay, az, v[s], w[s], x[s], nvc, nwc, vc.y, wc.y);
+          trid_row<4 * g + 1>(S[s][4 * g + 1], ax, ay, az, v[s], w[s], x[s], nvc, nwc, vc.y, wc.y);
+          trid_row<4 * g + 2>(S[s][4 * g + 2], ax, ay, az, v[s], w[s], x[s], nvc, nwc, vc.y, wc.y);
+          trid_row<4 * g + 3>(S[s][4 * g + 3], ax, ay, az, v[s], w[s], x[s], nvc, nwc, vc.y, wc.y);
+          if ((i + 1) >> 4 == 4 * s + g) {       // row i + 1 is column i + 1, conjugated
+            const int q = (i + 1) & 12;
+            const double2 lo = q & 4 ? S[s][4 * g + 1] : S[s][4 * g], hi = q & 4 ? S[s][4 * g + 3] : S[s][4 * g + 2];
+            const double2 r = q & 8 ? hi : lo;
+            if (rho == ((i + 1) & 3)) lds.col[par][pc] = make_double2(r.x, -r.y);
           }
-        }
-        // lane bits 4, 3, 2, 1 pick (row block, part): each step adds two lanes and keeps half of the values
-        auto halve = [&](double lo, double hi, bool up, auto ctrl) -> double {
-          return (up ? hi : lo) + dpp_d<decltype(ctrl)::value>(up ? lo : hi);
         };
-        using M16 = std::integral_constant<int, kMirror16>;
-        using M8 = std::integral_constant<int, kMirror8>;
-        using R4 = std::integral_constant<int, kReverse4>;
-        const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
-        double h[4][2];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          h[a][0] = add_rows16(acc[a].x, acc[a + 4].x);
-          h[a][1] = add_rows16(acc[a].y, acc[a + 4].y);
-        }
-        double m[2][2];
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-          m[a][0] = halve(h[a][0], h[a + 2][0], b3, M16());
-          m[a][1] = halve(h[a][1], h[a + 2][1], b3, M16());
-        }
-        const double qx = halve(m[0][0], m[1][0], b2, M8()), qy = halve(m[0][1], m[1][1], b2, M8());
-        double q = halve(qx, qy, b1, R4());
-        q += dpp_d<kSwap2>(q);
-        const int a = ((lane >> 4) & 1) * 4 + ((lane >> 3) & 1) * 2 + ((lane >> 2) & 1);
-        if ((lane & 1) == 0 && a >= A0 && a < NA) {
-          double* dst = reinterpret_cast<double*>(&sp[ty + RG * a]);
-          dst[(lane >> 1) & 1] = q;
-        }
+        group(std::integral_constant<int, 0>());
+        group(std::integral_constant<int, 1>());
+        group(std::integral_constant<int, 2>());
+        group(std::integral_constant<int, 3>());
       }
+      const double y = add_halves(add_rows16(ax, ay - az));                  // even rows of lanes: its real part, odd: imaginary
+      if (rho < 2) reinterpret_cast<double*>(&lds.y[par][pc])[rho] = y;
       lds_barrier();
-      // w = tau S v - 1/2 |tau|^2 (v^H S v) v;   S <- S - v w^H - w v^H
-      const double2 q0 = sp[lane];
-      double dot = lane > i ? v0.x * q0.x + v0.y * q0.y : 0.;
-      if (n > 64) {
-        const double2 q1 = sp[lane + 64];
-        dot += lane + 64 > i ? v1.x * q1.x + v1.y * q1.y : 0.;
+      // w = tau S v - 1/2 |tau|^2 (v^H S v) v;   S <- S - v w^H - w v^H, of which z is column i + 1
+      double2 c[NS], q[NS];
+      double dot = 0.;
+#pragma unroll
+      for (int s = s0; s < NS; ++s) {
+        c[s] = lds.col[par][64 * s + lane];
+        const double2 yl = lds.y[par][64 * s + lane];
+        q[s].x = fma(scale.x, yl.x, fma(-scale.y, yl.y, c[s].x));
+        q[s].y = fma(scale.x, yl.y, fma(scale.y, yl.x, c[s].y));
+        v[s] = vn[s];
+        dot = fma(v[s].x, q[s].x, fma(v[s].y, q[s].y, dot));
       }
-      const double rho = wave_sum_d(dot);
-      const double alpha2 = -0.5 * (tau.x * tau.x + tau.y * tau.y) * rho;
-      auto w_of = [&](int j, double2 v) -> double2 {               // (rows that are finished: v = 0, and their S v is stale)
-        const double2 t = cmuld(tau, sp[j]);
-        return j > i ? make_double2(t.x + alpha2 * v.x, t.y + alpha2 * v.y) : make_double2(0., 0.);
+      vc = vnc;
+      const double alpha2 = -0.5 * fma(tau.x, tau.x, tau.y * tau.y) * wave_sum_d(dot);
+#pragma unroll
+      for (int s = s0; s < NS; ++s) {
+        const bool in = jr[s] > i;               // (finished rows of the LDS vectors are stale)
+        w[s].x = in ? fma(alpha2, v[s].x, fma(tau.x, q[s].x, -(tau.y * q[s].y))) : 0.;
+        w[s].y = in ? fma(alpha2, v[s].y, fma(tau.x, q[s].y, tau.y * q[s].x)) : 0.;
+      }
+      const double2 wo = NS > 1 && s0 == 0 && ch > 0 ? w[NS - 1] : w[s0];
+      wc = make_double2(permute_d(from, wo.x), permute_d(from, wo.y));
+      // entry j of the vector t, which every wavefront has
+      auto entry = [&](const double2 (&t)[NS], int j) -> double2 {
+        const int at = trid_pos(j) & 63;
+        if (NS > 1 && s0 == 0 && j >= 64) return make_double2(read_lane_d(t[NS - 1].x, at), read_lane_d(t[NS - 1].y, at));
+        return make_double2(read_lane_d(t[s0].x, at), read_lane_d(t[s0].y, at));
       };
-      double2 vt[NB], wt[NB];
+      const double2 w1 = entry(w, i + 1);
+      double2 z[NS];
 #pragma unroll
-      for (int b = P; b < NB; ++b) {
-        vt[b] = sv[tx + 32 * b];
-        wt[b] = w_of(tx + 32 * b, vt[b]);
+      for (int s = s0; s < NS; ++s) {
+        z[s].x = fma(-v[s].x, w1.x, fma(-v[s].y, w1.y, c[s].x - w[s].x));
+        z[s].y = fma(-v[s].y, w1.x, fma(v[s].x, w1.y, c[s].y - w[s].y));
+        x[s].x = jr[s] > i + 2 ? z[s].x : 0.;
+        x[s].y = jr[s] > i + 2 ? z[s].y : 0.;
       }
-#pragma unroll
-      for (int a = A0; a < NA; ++a) {
-        const double2 vy = sv[ty + RG * a], wy = w_of(ty + RG * a, vy);
-#pragma unroll
-        for (int b = P; b < NB; ++b) {
-          double2 s = S[a][b];
-          s.x -= vy.x * wt[b].x + vy.y * wt[b].y;
-          s.y -= vy.y * wt[b].x - vy.x * wt[b].y;
-          s.x -= wy.x * vt[b].x + wy.y * vt[b].y;
-          s.y -= wy.y * vt[b].x - wy.x * vt[b].y;
-          S[a][b] = s;
-        }
-      }
-      publish_next(i + 1);
+      diag = entry(z, i + 1).x;
+      alpha = entry(z, i + 2 < 64 * NS ? i + 2 : i + 1);
     }
   };
-  block_column(std::integral_constant<int, 0>());
-  if constexpr (NB > 1) block_column(std::integral_constant<int, 1>());
-  if constexpr (NB > 2) block_column(std::integral_constant<int, 2>());
-  if constexpr (NB > 3) block_column(std::integral_constant<int, 3>());
-  __syncthreads();
-  if (tid == 0) {
-    sd[n - 1] = scol[n - 1].x;
-    se[n - 1] = 0.;
+  // step 63 has column 63 behind it: entries of its z below row 64 are not read any more
+  steps(0, NS > 1 && n > 64 ? 63 : n - 1, std::integral_constant<int, 0>());
+  if constexpr (NS > 1)
+    if (n > 64) steps(63, n - 1, std::integral_constant<int, 1>());
+  if (writer && lane == 0) {
+    lds.d[n - 1] = diag;
+    lds.e[n - 1] = 0.;
   }
   __syncthreads();
   for (int i = tid; i < n; i += T) {
-    trid_d(jb)[i] = sd[i];
-    trid_e(jb)[i] = se[i];
+    trid_d(jb)[i] = lds.d[i];
+    trid_e(jb)[i] = lds.e[i];
   }
   if (wave == 0) {                               // Gershgorin interval
     double lo = 1e300, hi = -1e300;
     for (int i = lane; i < n; i += 64) {
-      const double rad = (i > 0 ? fabs(se[i - 1]) : 0.) + (i + 1 < n ? fabs(se[i]) : 0.);
-      lo = fmin(lo, sd[i] - rad);
-      hi = fmax(hi, sd[i] + rad);
+      const double rad = (i > 0 ? fabs(lds.e[i - 1]) : 0.) + (i + 1 < n ? fabs(lds.e[i]) : 0.);
+      lo = fmin(lo, lds.d[i] - rad);
+      hi = fmax(hi, lds.d[i] + rad);
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
@@ -1497,18 +1525,11 @@ __device__ __forceinline__ void tridiagonalise(const EigJob& jb, TridLds& lds) {
   }
 }
 
-// One workgroup per matrix; the code for its own extent.
-template <int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W / 4))) void k_trid(EigJobs jobs) {
+// One workgroup per matrix.  NS: groups of 64 rows.
+template <int NS>
+__global__ __launch_bounds__(256 * NS) __attribute__((amdgpu_waves_per_eu(NS, NS))) void k_trid(EigJobs jobs) {
   __shared__ TridLds lds;
-  const EigJob jb = jobs.job[blockIdx.x];
-  constexpr int A = 16 / W;                      // row blocks per block of 32 columns
-  if (jb.n <= 32) tridiagonalise<W, A, 1>(jb, lds);
-  else if (jb.n <= 64) tridiagonalise<W, 2 * A, 2>(jb, lds);
-  else if constexpr (W == 8) {
-    if (jb.n <= 96) tridiagonalise<W, 3 * A, 3>(jb, lds);
-    else tridiagonalise<W, 4 * A, 4>(jb, lds);
-  }
+  tridiagonalise<NS>(jobs.job[blockIdx.x], lds);
 }
 
 // Eigenvector k of job blockIdx.y.  T is scaled by a power of two so that its spectral radius lies in [1, 2).
@@ -1516,217 +1537,314 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 4, W
 // the chain is one multiply-add per row (a quotient recurrence has a reciprocal in it).  Every eighth row the pair is
 // brought back to order one; e^2 has a floor of 1e-60 so that no two consecutive p vanish: a pair then shrinks by at most
 // 1e-240 between two such rows.
+// Six steps leave the eigenvalue in an interval of 4 / (65^5 64) < 6e-11 of the scaled T.  Inverse iteration needs no more: an
+// eigenvalue at least kClusterTol away loses a factor of 3e-4 or more against it in each of the three solves, 2e-11 together,
+// and the vector that they converge to is that of T, not of the shift.  (Ten steps, to the last bit of the eigenvalue, gave
+// factors equally far from 64 bits.)
+constexpr int kMultiSteps = 6;
 constexpr int kAheadRefl = 12;
+constexpr int kSideRows = kEigTriMaxN / 2 + 8;   // rows of one side, and what is read ahead of them
+
 __global__ __launch_bounds__(64) void k_trid_vec(EigJobs jobs) {
   const EigJob jb = jobs.job[blockIdx.y];
   const int n = jb.n, r = jb.r;
   const int k = blockIdx.x;
   if (k >= r) return;
   const int lane = threadIdx.x;
-  __shared__ double2 de[kEigTriMaxN + 8];        // (d_i, e_(i-1)^2), scaled; past n: rows that change no sign
-  __shared__ double sd[kEigTriMaxN + 2], se[kEigTriMaxN + 2];
-  __shared__ double2 slu[kEigTriMaxN + 2][2];    // (1 / pivot, first super-diagonal), (second, multiplier)
-  __shared__ double sy[kEigTriMaxN + 2], sz[kEigTriMaxN + 2];
+  const int r0 = lane, r1 = lane + 64;
+  __shared__ double2 de[kEigTriMaxN + 24];       // (d_i, e_(i-1)^2), scaled; past n: rows that change no sign
+  __shared__ double2 sde[2][kSideRows];          // (d, e towards the next row) in the order of each side
+  __shared__ double2 slu[2][kSideRows][2];       // (1 / pivot, first super-diagonal), (second, multiplier)
+  __shared__ double sy[2][kSideRows], sz[2][kSideRows];
+  __shared__ double2 stau[kEigTriMaxN];
+  const double2* tauG = trid_tau(jb);
+  const double* dG = trid_d(jb);
+  const double* eG = trid_e(jb);
+  // everything that the wavefront reads is requested together
+  const int q0 = r0 < n ? r0 : n - 1, q1 = r1 < n ? r1 : n - 1;
   const double gl = trid_bounds(jb)[0], gu = trid_bounds(jb)[1];
+  const double d0 = dG[q0], d1 = dG[q1], e0 = eG[q0], e1 = eG[q1], f0 = eG[q0 > 0 ? q0 - 1 : 0], f1 = eG[q1 > 0 ? q1 - 1 : 0];
+  const double2 tau0 = tauG[q0], tau1 = tauG[q1];
   const double tn = fmax(fabs(gl), fabs(gu));
+  // the first reflectors of the back-transformation go in flight: unconditional loads, so that no wait stands at the end of a
+  // branch; a lane without a row takes row 0, where every reflector is zero
+  const double2* V0 = reinterpret_cast<const double2*>(jb.V) + (r0 < n ? r0 : 0);
+  const double2* V1 = reinterpret_cast<const double2*>(jb.V) + (r1 < n ? r1 : 0);
+  double2 pv0[kAheadRefl], pv1[kAheadRefl];
+  auto issue = [&](int i, int slot) {
+    const size_t at = (size_t)(i >= 0 ? i : 0) * n;
+    pv0[slot] = V0[at];
+    if (n > 64) pv1[slot] = V1[at];
+  };
+#pragma unroll
+  for (int d = 0; d < kAheadRefl; ++d) issue(n - 2 - d, d);
   if (!(tn > 0.) || !(tn <= 1e300) || gl != gl || gu != gu) {            // zero matrix, inf or NaN
     if (lane == 0) jb.status[2] = 1;
     return;
   }
   const int ex = -ilogb(tn);
   auto scaled = [&](double v) { return ldexp(v, ex); };
-  for (int i = lane; i < kEigTriMaxN + 8; i += 64) {
-    const double d = i < n ? scaled(trid_d(jb)[i]) : 8.;                 // d - x > 0 and e = 0: p keeps its sign
-    const double e = i < n ? scaled(trid_e(jb)[i]) : 0.;
-    const double ep = i > 0 && i < n ? scaled(trid_e(jb)[i - 1]) : 0.;
-    de[i] = make_double2(d, i < n ? fmax(ep * ep, 1e-60) : 0.);
-    if (i < kEigTriMaxN + 2) {
-      sd[i] = i < n ? d : 0.;
-      se[i] = e;
+  const int mt = (n - 1) >> 1, mb = n - 2 - mt;  // rows eliminated from the top and from the bottom: mb is mt or one less
+  auto place = [&](int row, double d, double e, double f, double2 tau) {
+    const double ep = row > 0 ? scaled(f) : 0.;
+    if (row < n) {
+      de[row] = make_double2(scaled(d), fmax(ep * ep, 1e-60));
+      stau[row] = tau;
+      if (row < kSideRows) sde[0][row] = make_double2(scaled(d), row < n - 1 ? scaled(e) : 0.);
+      if (n - 1 - row < kSideRows) sde[1][n - 1 - row] = make_double2(scaled(d), ep);
+    } else if (row < kEigTriMaxN + 24) {
+      de[row] = make_double2(8., 0.);            // d - x > 0 and e = 0: p keeps its sign
     }
-  }
+  };
+  place(r0, d0, e0, f0, tau0);
+  place(r1, d1, e1, f1, tau1);
+  place(lane + 128, 0., 0., 0., tau0);
   __syncthreads();
   auto sturm_count = [&](double x) -> int {      // eigenvalues below x
     double p0 = 0., p1 = 1.;
     int c = 0;
-    for (int i0 = 0; i0 < n; i0 += 8) {
-      double2 t[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) t[u] = de[i0 + u];
+    uint32_t signs = 0u;                         // of the last rows, the newest in bit 0
+    auto rows = [&](const double2 (&t)[8]) __attribute__((always_inline)) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         const double p2 = fma(t[u].x - x, p1, -(t[u].y * p0));
-        c += (int)((uint32_t)(__double2hiint(p2) ^ __double2hiint(p1)) >> 31);
+        signs = __builtin_amdgcn_alignbit(signs, (uint32_t)__double2hiint(p2), 31);
         p0 = p1;
         p1 = p2;
       }
+      c += __popc((signs ^ (signs >> 1)) & 0xFFu);
       const int e = -__builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
       p0 = ldexp(p0, e);
       p1 = ldexp(p1, e);
+    };
+    double2 t[8], u[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) t[j] = de[j];
+    for (int i0 = 0; i0 < n; i0 += 16) {         // (up to 15 rows past n, of those that change no sign)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) u[j] = de[i0 + 8 + j];
+      rows(t);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) t[j] = de[i0 + 16 + j];
+      rows(u);
     }
     return c;
   };
   const double tnorm = scaled(tn);
   const int kasc = n - 1 - k;                    // k-th largest = kasc-th smallest (0-based)
   double lo = scaled(gl), hi = scaled(gu);
+  bool apart = true;
   for (int step = 0; step < kMultiSteps; ++step) {
+    const bool last = step == kMultiSteps - 1;
     const double h = (hi - lo) * (1. / 65.);
-    const bool above = sturm_count(lo + (lane + 1) * h) > kasc;          // more than kasc eigenvalues below the point
-    const uint64_t bal = __ballot(above);
-    const int jf = bal ? __builtin_ctzll(bal) : 64;                      // the eigenvalue lies below point jf and not below jf - 1
+    // the last lane of the last step looks whether the next eigenvalue (also the one behind the last kept one) is separated
+    const double x = last && lane == 63 ? 0.5 * (lo + hi) - kClusterTol * tnorm : lo + (lane + 1) * h;
+    const int c = sturm_count(x);
+    uint64_t bal = __ballot(c > kasc);           // more than kasc eigenvalues below the point
+    if (last) {
+      bal &= ~0ull >> 1;
+      apart = k + 1 >= n || __builtin_amdgcn_readlane(c, 63) == kasc;
+    }
+    const int points = last ? 63 : 64;
+    const int jf = bal ? __builtin_ctzll(bal) : points;                  // the eigenvalue lies below point jf and not below jf - 1
     const double nlo = jf == 0 ? lo : lo + jf * h;
-    const double nhi = jf == 64 ? hi : lo + (jf + 1) * h;
+    const double nhi = jf == points ? hi : lo + (jf + 1) * h;
     lo = nlo;
     hi = nhi;
   }
   const double lam = 0.5 * (lo + hi);
-  // the next eigenvalue (also the one behind the last kept one) must be separated
-  if (!(fabs(lam) <= 1e300) || (k + 1 < n && sturm_count(lam - kClusterTol * tnorm) != kasc)) {
+  if (!(fabs(lam) <= 1e300) || !apart) {
     if (lane == 0) jb.status[2] = 1;
     return;
   }
 
-  // ---- inverse iteration: a serial chain, so it burns at both ends: lanes 0 .. 31 eliminate from the first row down,
-  // lanes 32 .. 63 from the last row up (the same code on the reversed matrix), a 2 x 2 system is left in the middle, and
-  // the substitution runs outwards on both sides.  Within a side every lane computes the same; one writes. ----
+  // ---- inverse iteration: a serial chain, so it burns at both ends: lane 0 eliminates from the first row down, lane 32 from
+  // the last row up (the same code on the reversed matrix), a 2 x 2 system is left in the middle, and the substitution runs
+  // outwards on both sides.  Only these two lanes are active: their writes need no predicate. ----
   const double tol = 2.220446049250313e-16 * tnorm;
   const int side = lane >> 5;
-  const bool writer = (lane & 31) == 0;
-  const int mt = (n - 1) >> 1, mh = side ? n - 2 - mt : mt;              // rows eliminated from the top, from this side
-  auto row_at = [&](int j) -> int { return side ? n - 1 - j : j; };
-  auto d_at = [&](int j) -> double { return sd[row_at(j)] - lam; };
-  auto e_at = [&](int j) -> double { return se[side ? n - 2 - j : j]; };  // couples rows j and j + 1 of this side
-  auto clamped = [&](double p) -> double { return fabs(p) < tol ? (p < 0. ? -tol : tol) : p; };
+  const bool worker = (lane & 31) == 0;
+  const int mh = side ? mb : mt;                 // rows eliminated from this side
+  auto clamped = [&](double p) -> double { return fabs(p) < tol ? copysign(tol, p) : p; };
   uint64_t swaps = 0ull;                         // bit j: rows interchanged at step j (mt <= 63)
-  double ca, cu;                                 // the side's last row: ca x[mh] + cu x[mh + 1]
-  {
-    double a = d_at(0), du = e_at(0);
-    double sub = du, dn = n > 2 ? d_at(1) : 0., en = n > 2 ? e_at(1) : 0.;   // the next row is read one ahead
-    for (int j = 0; j < mt; ++j) {               // elimination with partial pivoting
-      const int jn = j + 2 < n - 1 ? j + 2 : n - 2;
-      const double ndn = d_at(jn), nen = e_at(jn);
+  double ca = 0., cu = 0.;                       // the side's last row: ca x[mh] + cu x[mh + 1]
+  if (worker) {
+    const double2* in = sde[side];
+    double a = in[0].x - lam, du = in[0].y, sub = du;
+    double2 nx = in[1];
+    auto step = [&](int j) __attribute__((always_inline)) {              // elimination with partial pivoting
+      const double2 ahead = in[j + 2];
+      const double dn = nx.x - lam, en = nx.y;
       const bool swap = fabs(a) < fabs(sub);
       const double rp = rcp_nr(clamped(swap ? sub : a));
       const double f = (swap ? a : sub) * rp;
-      if (writer && j < mh) {
-        slu[row_at(j)][0] = make_double2(rp, swap ? dn : du);
-        slu[row_at(j)][1] = make_double2(swap ? en : 0., f);
-      }
-      if (j < mh) {
-        swaps |= (uint64_t)swap << j;
-        a = swap ? du - f * dn : dn - f * du;
-        du = swap ? -f * en : en;
-      }
+      slu[side][j][0] = make_double2(rp, swap ? dn : du);
+      slu[side][j][1] = make_double2(swap ? en : 0., f);
+      swaps |= swap ? 1ull << j : 0ull;
+      a = swap ? fma(-f, dn, du) : fma(-f, du, dn);
+      du = swap ? -f * en : en;
       sub = en;
-      dn = ndn;
-      en = nen;
-    }
+      nx = ahead;
+    };
+    for (int j = 0; j < mb; ++j) step(j);
+    if (mb < mt && side == 0) step(mb);
     ca = a;
     cu = du;
   }
   // the middle: (top row) a1 xp + u1 xq = y1, (bottom row) u2 xp + a2 xq = y2, with pivoting
-  const double oa = __shfl_xor(ca, 32, 64), ou = __shfl_xor(cu, 32, 64);
-  const double a1 = side ? oa : ca, u1 = side ? ou : cu, a2 = side ? ca : oa, u2 = side ? cu : ou;
+  const double a1 = read_lane_d(ca, 0), u1 = read_lane_d(cu, 0), a2 = read_lane_d(ca, 32), u2 = read_lane_d(cu, 32);
   const bool mswap = fabs(a1) < fabs(u2);
   const double mp = mswap ? u2 : a1, mu = mswap ? a2 : u1;               // the pivot row
   const double mrp = rcp_nr(clamped(mp));
   const double mf = (mswap ? a1 : u2) * mrp;
   const double mrq = rcp_nr(clamped((mswap ? u1 : a2) - mf * mu));
-  const int r0 = lane, r1 = lane + 64;
-  // the first reflectors of the back-transformation go in flight
-  const double2* Vg = reinterpret_cast<const double2*>(jb.V);
-  const double2* tauG = trid_tau(jb);
-  double2 pv0[kAheadRefl], pv1[kAheadRefl], ptau[kAheadRefl];
-  auto issue = [&](int i, int slot) {
-    const double2 zero = make_double2(0., 0.);
-    const int ic = i >= 0 ? i : 0;
-    ptau[slot] = tauG[ic];
-    pv0[slot] = (i >= 0 && r0 > i && r0 < n) ? Vg[(size_t)ic * n + r0] : zero;
-    pv1[slot] = (i >= 0 && r1 > i && r1 < n) ? Vg[(size_t)ic * n + r1] : zero;
-  };
-#pragma unroll
-  for (int d = 0; d < kAheadRefl; ++d) issue(n - 2 - d, d);
   auto start = [&](int i) -> double {
     const uint32_t u = trid_mix((uint32_t)i * 0x9E3779B9u + (uint32_t)k * 0x85EBCA6Bu + 0x1234567u);
     return (double)u * (1. / 2147483648.) - 1.;
   };
+  // place of a row in the arrays of the sides
+  const int i0 = r0 <= mt ? r0 : kSideRows + n - 1 - r0, i1 = r1 <= mt ? r1 : kSideRows + n - 1 - r1;
+  double* yrow = &sy[0][0];
+  double* zrow = &sz[0][0];
   double z0 = 0., z1 = 0.;
   for (int it = 0; it < 3; ++it) {
     __syncthreads();                             // (one wavefront: orders the LDS accesses)
-    double y;
+    double y = 0.;
     if (it == 0) {                               // the first right-hand side is taken as already eliminated
-      if (r0 < n) sy[r0] = start(r0);
-      if (r1 < n) sy[r1] = start(r1);
-      y = start(row_at(mh));
+      if (r0 < n) yrow[i0] = start(r0);
+      if (r1 < n) yrow[i1] = start(r1);
+      y = start(side ? n - 1 - mh : mh);
     } else {
-      if (r0 < n) sz[r0] = z0;
-      if (r1 < n) sz[r1] = z1;
+      if (r0 < n) zrow[i0] = z0;
+      if (r1 < n) zrow[i1] = z1;
       __syncthreads();
-      y = sz[row_at(0)];
-      double f = slu[row_at(0)][1].y, rhs = sz[row_at(1)];
-      for (int j = 0; j < mt; ++j) {             // elimination of the right-hand side
-        const int jn = j + 2 < n ? j + 2 : n - 1;
-        const double nf = slu[row_at(j + 1)][1].y, nrhs = sz[row_at(jn)];
-        const bool swap = (swaps >> j) & 1ull;
-        if (writer && j < mh) sy[row_at(j)] = swap ? rhs : y;
-        if (j < mh) y = swap ? y - f * rhs : rhs - f * y;
-        f = nf;
-        rhs = nrhs;
+      if (worker) {                              // elimination of the right-hand side, operands four rows ahead
+        y = sz[side][0];
+        auto step = [&](int j, double f, double rhs) __attribute__((always_inline)) {
+          const bool swap = (swaps >> j) & 1ull;
+          const double keep = swap ? rhs : y, other = swap ? y : rhs;
+          sy[side][j] = keep;
+          y = fma(-f, keep, other);
+        };
+        double f[4], rhs[4];
+        auto fetch = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            f[u] = slu[side][j + u][1].y;
+            rhs[u] = sz[side][j + u + 1];
+          }
+        };
+        fetch(0);
+        int j = 0;
+        for (; j + 4 <= mb; j += 4) {
+          double f0[4], h0[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            f0[u] = f[u];
+            h0[u] = rhs[u];
+          }
+          fetch(j + 4);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) step(j + u, f0[u], h0[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (j + u < mh) step(j + u, f[u], rhs[u]);
       }
     }
     __syncthreads();
-    const double oy = __shfl_xor(y, 32, 64);
-    const double y1 = side ? oy : y, y2 = side ? y : oy;
+    const double y1 = read_lane_d(y, 0), y2 = read_lane_d(y, 32);
     const double yp = mswap ? y2 : y1, yq = mswap ? y1 : y2;
     const double xq = (yq - mf * yp) * mrq, xp = (yp - mu * xq) * mrp;
-    double zn1 = side ? xq : xp, zn2 = side ? xp : xq;
-    if (writer) sz[row_at(mh)] = zn1;
-    int j = mh - 1;
-    double2 p = slu[row_at(j > 0 ? j : 0)][0];
-    double s2 = slu[row_at(j > 0 ? j : 0)][1].x, yi = sy[row_at(j > 0 ? j : 0)];
-    for (int step = 0; step < mt; ++step, --j) { // back substitution, outwards
-      const int jn = j > 1 ? j - 1 : 0;
-      const double2 np = slu[row_at(jn)][0];
-      const double ns2 = slu[row_at(jn)][1].x, nyi = sy[row_at(jn)];
-      const double z = (yi - s2 * zn2 - p.y * zn1) * p.x;
-      if (writer && j >= 0) sz[row_at(j)] = z;
-      zn2 = zn1;
-      zn1 = z;
-      p = np;
-      s2 = ns2;
-      yi = nyi;
+    if (worker) {
+      double zn1 = side ? xq : xp, zn2 = side ? xp : xq;
+      sz[side][mh] = zn1;
+      auto step = [&](int j, double2 p, double s2, double yi) __attribute__((always_inline)) {   // back substitution, outwards
+        const double z = fma(-p.y, zn1, fma(-s2, zn2, yi)) * p.x;
+        sz[side][j] = z;
+        zn2 = zn1;
+        zn1 = z;
+      };
+      const int full = mb & ~3;                  // down to a multiple of four row by row, then four at a time
+#pragma unroll
+      for (int u = 3; u >= 0; --u)
+        if (full + u < mh) step(full + u, slu[side][full + u][0], slu[side][full + u][1].x, sy[side][full + u]);
+      double2 p[4];
+      double s2[4], yi[4];
+      auto fetch = [&](int j) __attribute__((always_inline)) {
+        const int at = j > 0 ? j : 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          p[u] = slu[side][at + u][0];
+          s2[u] = slu[side][at + u][1].x;
+          yi[u] = sy[side][at + u];
+        }
+      };
+      fetch(full - 4);
+      for (int j = full - 4; j >= 0; j -= 4) {
+        double2 p0[4];
+        double t0[4], w0[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          p0[u] = p[u];
+          t0[u] = s2[u];
+          w0[u] = yi[u];
+        }
+        fetch(j - 4);
+#pragma unroll
+        for (int u = 3; u >= 0; --u) step(j + u, p0[u], t0[u], w0[u]);
+      }
     }
     __syncthreads();
-    z0 = r0 < n ? sz[r0] : 0.;
-    z1 = r1 < n ? sz[r1] : 0.;
-    double zmax = fmax(fabs(z0), fabs(z1));
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) zmax = fmax(zmax, __shfl_xor(zmax, off, 64));
-    const double sc = zmax > 0. ? 1. / zmax : 1.;
-    z0 *= sc;
-    z1 *= sc;
+    z0 = r0 < n ? zrow[i0] : 0.;
+    z1 = r1 < n ? zrow[i1] : 0.;
+    const double size = wave_sum_d(fabs(z0) + fabs(z1));                 // back to order one, by a power of two
+    const int e = size > 0. && size <= 1.7e308 ? -__builtin_amdgcn_frexp_exp(size) : 0;
+    z0 = ldexp(z0, e);
+    z1 = ldexp(z1, e);
   }
   const double nrm2 = wave_sum_d(z0 * z0 + z1 * z1);
   const double inv = nrm2 > 0. ? rsqrt(nrm2) : 0.;
 
-  // ---- U[:, k] = H_0 H_1 .. H_(n-2) z, the reflectors read kAheadRefl ahead ----
+  // ---- U[:, k] = H_0 H_1 .. H_(n-2) z, the reflectors read kAheadRefl ahead; both parts of v^H x in one reduction ----
   double2 x0 = make_double2(z0 * inv, 0.), x1 = make_double2(z1 * inv, 0.);
-  for (int base = n - 2; base >= 0; base -= kAheadRefl) {
+  auto back = [&](auto two_c) __attribute__((always_inline)) {
+    constexpr bool two = decltype(two_c)::value;
+    for (int base = n - 2; base >= 0; base -= kAheadRefl) {
 #pragma unroll
-    for (int d = 0; d < kAheadRefl; ++d) {
-      const int i = base - d;
-      const double2 tau = ptau[d], v0 = pv0[d], v1 = pv1[d];
-      issue(i - kAheadRefl, d);
-      if (i >= 0) {
-        const double2 t0 = cmuld(conjd(v0), x0), t1 = cmuld(conjd(v1), x1);
-        const double dx = wave_sum_d(t0.x + t1.x), dy = wave_sum_d(t0.y + t1.y);
+      for (int d = 0; d < kAheadRefl; ++d) {
+        const int i = base - d;
+        const double2 v0 = pv0[d], v1 = two ? pv1[d] : make_double2(0., 0.);
+        issue(i - kAheadRefl, d);
+        if (i < 0) continue;
+        const double2 tau = stau[i];
+        double tx = fma(v0.x, x0.x, v0.y * x0.y), ty = fma(v0.x, x0.y, -(v0.y * x0.x));
+        if (two) {
+          tx = fma(v1.x, x1.x, fma(v1.y, x1.y, tx));
+          ty = fma(v1.x, x1.y, fma(-v1.y, x1.x, ty));
+        }
+        double t = add_halves(add_rows16(tx, ty));                       // even rows of lanes: real part, odd: imaginary
+        t += dpp_d<kMirror16>(t);
+        t += dpp_d<kMirror8>(t);
+        t += dpp_d<kReverse4>(t);
+        t += dpp_d<kSwap2>(t);
+        const int2 w = __builtin_bit_cast(int2, t);
+        const auto plo = __builtin_amdgcn_permlane16_swap((unsigned)w.x, (unsigned)w.x, false, false);
+        const auto phi = __builtin_amdgcn_permlane16_swap((unsigned)w.y, (unsigned)w.y, false, false);
+        const double dx = __builtin_bit_cast(double, make_int2((int)plo[0], (int)phi[0]));
+        const double dy = __builtin_bit_cast(double, make_int2((int)plo[1], (int)phi[1]));
         const double2 sfac = cmuld(tau, make_double2(dx, dy));
-        const double2 u0 = cmuld(sfac, v0), u1 = cmuld(sfac, v1);
-        x0 = make_double2(x0.x - u0.x, x0.y - u0.y);
-        x1 = make_double2(x1.x - u1.x, x1.y - u1.y);
+        x0.x = fma(-sfac.x, v0.x, fma(sfac.y, v0.y, x0.x));
+        x0.y = fma(-sfac.x, v0.y, fma(-sfac.y, v0.x, x0.y));
+        if (two) {
+          x1.x = fma(-sfac.x, v1.x, fma(sfac.y, v1.y, x1.x));
+          x1.y = fma(-sfac.x, v1.y, fma(-sfac.y, v1.x, x1.y));
+        }
       }
     }
-  }
+  };
+  if (n > 64) back(std::integral_constant<bool, true>());
+  else back(std::integral_constant<bool, false>());
   // unit phase that makes the largest-modulus entry (lowest row on ties) real and positive
   double best = r0 < n ? x0.x * x0.x + x0.y * x0.y : -1.;
   int brow = r0;
@@ -1912,8 +2030,8 @@ void launch_eig_batch(hipStream_t s, int njobs, const double* const* gram, doubl
       int rmax = 1;
       for (int i = 0; i < nsmall; ++i) rmax = small.job[i].r > rmax ? small.job[i].r : rmax;
       const dim3 grid((unsigned)nsmall);
-      if (nmax <= 64) k_trid<4><<<grid, dim3(256), 0, s>>>(small);
-      else k_trid<8><<<grid, dim3(512), 0, s>>>(small);
+      if (nmax <= 64) k_trid<1><<<grid, dim3(256), 0, s>>>(small);
+      else k_trid<2><<<grid, dim3(512), 0, s>>>(small);
       k_trid_vec<<<dim3((unsigned)rmax, (unsigned)nsmall), dim3(64), 0, s>>>(small);
     }
     k_eig_tri<<<dim3((unsigned)nsmall), dim3(kEigThreads), lds, s>>>(small);
