@@ -257,7 +257,7 @@ __global__ __launch_bounds__(kGramThreads) void k_gram(const void* __restrict__ 
 }
 
 // -------------------------------------------------------------------------------------------------
-// k_gram128: the Gram for extents In <= 128 (every mode of the FNO shapes), up to four modes per launch (blockIdx.y).
+// k_gram128: the Gram for extents In <= 128 (every mode of the FNO shapes), all modes of a tensor in one launch.
 // A complex Hermitian product in THREE real ones.  With P1 = Xr Xr^T, P2 = Xi Xi^T and P3 = (Xr + Xi)(Xr - Xi)^T,
 //   Re = P1 + P2,   Im = Xi Xr^T - Xr Xi^T = P3 - P1 + P2,
 // so a 16 x 16 tile takes three matrix instructions per four tensor columns instead of four.  The products of
@@ -298,13 +298,24 @@ struct GramJob {
   const void* x;
   const uint32_t* mask;
   double* partials;
-  int64_t A, B, cols_per_chunk;
-  int In, nchunks;
+  int64_t A, B;
+  int In;
   uint32_t magicB;
+  uint32_t start, weight, tiles;     // where its tiles lie on the line of all work, and how long each is
 };
 struct GramJobs {
+  uint32_t per, rem;                 // workgroup b has the line from gram_edge(b) to gram_edge(b + 1)
+  int njobs;
+  int first[kMaxNdim], nchunks[kMaxNdim];   // workgroups first .. first + nchunks - 1 have a part of a job
   GramJob job[kMaxNdim];
 };
+__host__ __device__ inline uint32_t gram_edge(uint32_t per, uint32_t rem, uint32_t b) { return b * per + (b < rem ? b : rem); }
+// tiles of a job that start before `at`
+__host__ __device__ inline uint32_t gram_tiles_before(uint32_t at, uint32_t start, uint32_t weight, uint32_t tiles) {
+  if (at <= start) return 0u;
+  const uint32_t t = (at - start + weight - 1) / weight;
+  return t < tiles ? t : tiles;
+}
 
 __host__ __device__ constexpr int gram_cols(int RT) { return 256 / RT; }            // tensor columns per staged tile
 __host__ __device__ constexpr int gram_plane(int RT) { return gram_cols(RT) * (16 * RT + 1); }   // doubles
@@ -318,7 +329,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gram_buffer(const void* base, 
 __device__ constexpr int tri_row(int t) { int a = 0; while ((a + 1) * (a + 2) / 2 <= t) ++a; return a; }
 
 template <int DT, int RT>
-__device__ __forceinline__ void gram_chunk(const GramJob& jb, double* sG) {
+__device__ __forceinline__ void gram_chunk(const GramJob& jb, uint32_t tile0, uint32_t tile1, int chunk, double* sG) {
   constexpr int TC = gram_cols(RT), Q = 16 * RT + 1, PL = gram_plane(RT);
   constexpr int kEs = DT == TGRAD_C64 ? 8 : 4;        // bytes per element
   constexpr uint32_t kNowhere = 0xFFFFFFF0u;          // an offset beyond every descriptor: the load returns zero
@@ -327,9 +338,9 @@ __device__ __forceinline__ void gram_chunk(const GramJob& jb, double* sG) {
   const int In = jb.In;
   const int64_t J = jb.A * jb.B;
   const uint32_t B = (uint32_t)jb.B;                  // the host takes this kernel only when In * B < 2^28
-  const int64_t c_begin = (int64_t)blockIdx.x * jb.cols_per_chunk;
-  const int64_t c_end = c_begin + jb.cols_per_chunk < J ? c_begin + jb.cols_per_chunk : J;
-  const bool empty = c_begin >= c_end;                // (workgroup-uniform) a trailing chunk without columns writes zeros
+  const int64_t c_begin = (int64_t)tile0 * TC;
+  const int64_t c_end = (int64_t)tile1 * TC < J ? (int64_t)tile1 * TC : J;
+  const bool empty = c_begin >= c_end;                // (workgroup-uniform) a chunk without columns writes zeros
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -524,11 +535,13 @@ __device__ __forceinline__ void gram_chunk(const GramJob& jb, double* sG) {
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  auto tail_row = [&](const double* b) {              // row 16 RT against every row; columns wave, wave + 8, ..
-    const int jl = lane < 16 * RT ? lane : 16 * RT - 1;
+  // row 16 RT against every row: lane groups of 16 RT rows take a column each
+  constexpr int LG = RT >= 4 ? 1 : 4 / RT;
+  auto tail_row = [&](const double* b) {
+    const int jl = lane % (16 * RT < 64 ? 16 * RT : 64), lg = LG > 1 ? lane / (16 * RT) : 0;
 #pragma unroll
-    for (int c = 0; c < TC / 8; ++c) {
-      const double* col = b + (wave + 8 * c) * Q;
+    for (int c = 0; c < TC / (8 * LG); ++c) {
+      const double* col = b + (LG * (wave + 8 * c) + lg) * Q;
       const double yr = col[16 * RT], yi = col[16 * RT + PL], xr = col[jl], xi = col[jl + PL];
       t_re += yr * xr + yi * xi;
       t_im += yi * xr - yr * xi;
@@ -614,7 +627,7 @@ __device__ __forceinline__ void gram_chunk(const GramJob& jb, double* sG) {
       hi = half;
     }
   }
-  double2* out = reinterpret_cast<double2*>(jb.partials) + (int64_t)blockIdx.x * In * In;
+  double2* out = reinterpret_cast<double2*>(jb.partials) + (int64_t)chunk * In * In;
   if (cg == 0) {
 #pragma unroll
     for (int k = 0; k < kTiles; ++k) {
@@ -637,11 +650,14 @@ __device__ __forceinline__ void gram_chunk(const GramJob& jb, double* sG) {
     if (wave == 0) {
       double re = 0., im = 0., dd = 0.;
 #pragma unroll
-      for (int w = 0; w < 8; ++w) {
-        re += area[(w * 3) * 64];
-        im += area[(w * 3 + 1) * 64];
-        dd += area[(w * 3 + 2) * 64];
-      }
+      for (int w = 0; w < 8; ++w)
+#pragma unroll
+        for (int g = 0; g < LG; ++g) {               // (lanes past the rows read on, and write nothing)
+          const int at = LG > 1 ? (lane % (16 * RT)) + g * 16 * RT - lane : 0;
+          re += area[(w * 3) * 64 + at];
+          im += area[(w * 3 + 1) * 64 + at];
+          dd += area[(w * 3 + 2) * 64 + at];
+        }
       if (lane < 16 * RT) out[(int64_t)(16 * RT) * In + lane] = make_double2(re, im);
       if (lane == 0) out[(int64_t)(16 * RT) * In + 16 * RT] = make_double2(dd, 0.);
     }
@@ -651,12 +667,23 @@ __device__ __forceinline__ void gram_chunk(const GramJob& jb, double* sG) {
 template <int DT>
 __global__ __launch_bounds__(kGram128Threads) void k_gram128(GramJobs jobs) {
   extern __shared__ double sG[];
-  const GramJob jb = jobs.job[blockIdx.y];
-  if ((int)blockIdx.x >= jb.nchunks) return;
-  if (jb.rt == 8) gram_chunk<DT, 8>(jb, sG);
-  else if (jb.rt == 4) gram_chunk<DT, 4>(jb, sG);
-  else if (jb.rt == 2) gram_chunk<DT, 2>(jb, sG);
-  else gram_chunk<DT, 1>(jb, sG);
+  const uint32_t at0 = gram_edge(jobs.per, jobs.rem, blockIdx.x), at1 = gram_edge(jobs.per, jobs.rem, blockIdx.x + 1);
+  uint32_t todo = 0u;
+#pragma unroll
+  for (int j = 0; j < kMaxNdim; ++j)
+    todo |= j < jobs.njobs && (uint32_t)((int)blockIdx.x - jobs.first[j]) < (uint32_t)jobs.nchunks[j] ? 1u << j : 0u;
+  for (; todo; todo &= todo - 1u) {
+    const int j = __builtin_ctz(todo);
+    const GramJob jb = jobs.job[j];
+    const int chunk = (int)blockIdx.x - jobs.first[j];
+    const uint32_t t0 = gram_tiles_before(at0, jb.start, jb.weight, jb.tiles);
+    const uint32_t t1 = gram_tiles_before(at1, jb.start, jb.weight, jb.tiles);
+    __syncthreads();                                  // (the LDS of the part of the job before)
+    if (jb.rt == 8) gram_chunk<DT, 8>(jb, t0, t1, chunk, sG);
+    else if (jb.rt == 4) gram_chunk<DT, 4>(jb, t0, t1, chunk, sG);
+    else if (jb.rt == 2) gram_chunk<DT, 2>(jb, t0, t1, chunk, sG);
+    else gram_chunk<DT, 1>(jb, t0, t1, chunk, sG);
+  }
 }
 
 // gram[i, j] = sum over chunks of partials[chunk][i, j] for i >= j; the upper triangle is the
@@ -1899,79 +1926,141 @@ static int64_t gram_tiles(int64_t A, int In, int64_t B) {
   return (A * B + tc - 1) / tc;
 }
 
-// Runs of tensor columns that one mode's Gram is summed over by a workgroup each: one per compute unit.
-int gram_num_chunks(int64_t A, int In, int64_t B) {
-  const int64_t tiles = gram_tiles(A, In, B);
-  return (int)(tiles < 256 ? (tiles < 1 ? 1 : tiles) : 256);
+// All modes of up to 128 entries in one launch: their staged tiles, each as long as it takes, one after the other on a line
+// of which every one of 256 workgroups (a compute unit holds one) has an equal part; where a part begins or ends inside a mode is
+// a chunk of it, with a partial sum of its own.  Longer modes have a launch each, of equal chunks.
+// Lengths in 0.1 us, measured by 256 workgroups of 1 to 16 tiles each; `lead` is the first round trip of a part and its partial
+// sum, which a workgroup with parts of two modes has twice.  Refreshes, us, before (two chunks per compute unit, dealt by work and
+// rounded to whole tiles in each mode) / now: 64x64x32x17 242 / 218, 128x128x32x17 796 / 605, 64x64x64x33 529 / 369,
+// 90x77x45x23 628 / 488; a launch per mode and its reduction, 128x128x128x65: 4564 / 4514.
+struct GramCost {
+  uint32_t tile, lead;
+};
+static GramCost gram_cost(int rt, int In) {
+  const int ntr = (In + 15) / 16, tiles = ntr * (ntr + 1) / 2;
+  const bool tail = In == 16 * rt + 1;
+  if (rt == 8) return {14u + 12u * (uint32_t)((tiles + 7) / 8), 70u};
+  if (rt == 4) return {tail ? 54u : ntr == 3 ? 33u : 47u, 50u};
+  if (rt == 2) return {tail ? 40u : 33u, 25u};
+  return {tail ? 32u : 27u, 15u};
 }
-// One launch for all modes of a small tensor: its Grams are a few staged tiles per compute unit, so what counts is
-// launches, the first round trip to memory and the partial sums (64x64x32x17: four Grams and four reductions of 256
-// partials 187 us, one launch per kernel variant 85, one for all 82).  From 16 tiles per compute unit and mode on,
-// a mode fills the chip by itself.
-bool gram_batched(int64_t I) { return I <= (int64_t)256 * 16 * 4096; }
 
-// Chunks of every mode where they share a launch: by their share of the work two workgroups per compute unit (of unequal
-// length, so that the last ones level it out), and partial sums that take no more memory together than those of the
-// largest mode alone would, one by one.
-void gram_num_chunks_batched(int njobs, const int64_t* A, const int* In, const int64_t* B, int* nchunks) {
-  double cap = 0., sum = 0., work = 0.;
-  auto cost = [&](int i) -> double {               // staged tiles times their matrix instructions and their fetch
+// The line of `njobs` modes, cut for `groups` workgroups.
+static void gram_line(int njobs, const int64_t* A, const int* In, const int64_t* B, int groups, GramJobs* jobs) {
+  uint64_t total = 0, tiles_all = 0;
+  jobs->njobs = njobs;
+  for (int i = 0; i < njobs; ++i) tiles_all += (uint64_t)gram_tiles(A[i], In[i], B[i]);
+  // lengths are brought down until the line fits in 32 bits; where every tile has a workgroup, all are of length one
+  for (int shift = tiles_all <= (uint64_t)groups ? 31 : 0; ; ++shift) {
+    total = 0;
+    for (int i = 0; i < njobs; ++i) {
+      GramJob& jb = jobs->job[i];
+      jb.rt = gram_rows(In[i], B[i]);
+      const GramCost c = gram_cost(jb.rt, In[i]);
+      jb.In = In[i];
+      jb.A = A[i];
+      jb.B = B[i];
+      jb.weight = (c.tile >> shift) > 0 ? c.tile >> shift : 1u;
+      jb.tiles = (uint32_t)gram_tiles(A[i], In[i], B[i]);
+      if (i > 0) total += c.lead >> shift;
+      jb.start = (uint32_t)total;
+      total += (uint64_t)jb.tiles * jb.weight;
+    }
+    if (total < 0x7FFFFFFFull || shift >= 31) break;
+  }
+  jobs->per = (uint32_t)(total / (uint64_t)groups);
+  jobs->rem = (uint32_t)(total % (uint64_t)groups);
+  auto owner = [&](uint64_t at) -> int {             // the workgroup whose part holds position `at`
+    const uint64_t head = (uint64_t)jobs->rem * (jobs->per + 1ull);
+    return (int)(at < head ? at / (jobs->per + 1ull) : jobs->rem + (at - head) / (jobs->per ? jobs->per : 1u));
+  };
+  for (int i = 0; i < njobs; ++i) {
+    const GramJob& jb = jobs->job[i];
+    jobs->first[i] = owner(jb.start);
+    jobs->nchunks[i] = owner(jb.start + (uint64_t)(jb.tiles - 1) * jb.weight) - jobs->first[i] + 1;
+  }
+}
+
+// Whether a mode shares its launch with others.
+bool gram_shared(int In, int64_t B) { return gram_rows(In, B) != 0; }
+
+// Chunks of every mode of a tensor, those that share a launch first; returns the workgroups of that launch.  Partial sums are
+// bounded in memory by 512 chunks dealt by work, and by 256 of the mode whose are largest (with more than 16.8 M numbers: by the
+// latter alone); a launch of 256 workgroups seldom comes near.
+int gram_num_chunks(int njobs, const int64_t* A, const int* In, const int64_t* B, int* nchunks) {
+  double largest = 0., by_work = 0., work = 0.;
+  int64_t tiles_all = 0, numbers = 0;
+  int together = 0;
+  auto cost = [&](int i) -> double {
     const int rt = gram_rows(In[i], B[i]);
     return (double)gram_tiles(A[i], In[i], B[i]) * (rt == 8 ? 3. : rt == 4 ? 1.7 : 1.);
   };
   for (int i = 0; i < njobs; ++i) work += cost(i);
   for (int i = 0; i < njobs; ++i) {
-    const int n = gram_num_chunks(A[i], In[i], B[i]);
-    int share = (int)(512. * cost(i) / work + 0.5);
-    if (share < 1) share = 1;
-    nchunks[i] = n < share ? n : share;
-    const double tiles = (double)((A[i] * B[i] + 15) / 16);
-    cap = fmax(cap, fmin(tiles, 256.) * In[i] * In[i]);
-    sum += (double)nchunks[i] * In[i] * In[i];
-  }
-  if (sum > cap)
-    for (int i = 0; i < njobs; ++i) {
-      const int n = (int)(nchunks[i] * (cap / sum));
-      nchunks[i] = n > 1 ? n : 1;
+    const int64_t tiles = gram_tiles(A[i], In[i], B[i]);
+    const int most = tiles < 256 ? (tiles < 1 ? 1 : (int)tiles) : 256, share = (int)(512. * cost(i) / work + 0.5);
+    nchunks[i] = most < share ? most : share < 1 ? 1 : share;
+    numbers = A[i] * In[i] * B[i];
+    largest = fmax(largest, fmin((double)((A[i] * B[i] + 15) / 16), 256.) * In[i] * In[i]);
+    by_work += (double)nchunks[i] * In[i] * In[i];
+    if (numbers > (int64_t)256 * 16 * 4096 || njobs == 1) nchunks[i] = most;
+    if (gram_shared(In[i], B[i])) {
+      ++together;
+      tiles_all += tiles;
     }
+  }
+  const bool large = numbers > (int64_t)256 * 16 * 4096 || njobs == 1;
+  const double cap = large || by_work > largest ? largest : by_work;
+  for (int i = together; i < njobs; ++i)
+    if (!large && by_work > largest) nchunks[i] = (int)fmax(1., nchunks[i] * (largest / by_work));
+  if (together == 0) return 0;
+  GramJobs jobs;
+  for (int groups = tiles_all < 256 ? (int)(tiles_all < 1 ? 1 : tiles_all) : 256; ; --groups) {
+    gram_line(together, A, In, B, groups, &jobs);
+    double sum = 0.;
+    for (int i = 0; i < together; ++i) sum += (double)jobs.nchunks[i] * In[i] * In[i];
+    if (sum > cap && groups > 1) continue;
+    for (int i = 0; i < together; ++i) nchunks[i] = jobs.nchunks[i];
+    return groups;
+  }
 }
 
-// Partial Grams of several modes of one tensor, nchunks[i] runs of columns each.
+// Partial Grams of the modes that share a launch of `groups` workgroups, or of one that does not, in nchunks[0] chunks.
 void launch_gram_batch(hipStream_t s, int njobs, const void* g, int dtype, const uint32_t* mask, const int64_t* A,
-                       const int* In, const int64_t* B, const int* nchunks, double* const* partials) {
-  GramJobs jobs;
-  int n = 0, chunks = 0;
-  size_t lds128 = 0;
-  for (int i = 0; i < njobs; ++i) {
-    const int rt = gram_rows(In[i], B[i]), tc = rt ? gram_cols(rt) : kTC;
-    const int64_t per = (gram_tiles(A[i], In[i], B[i]) + nchunks[i] - 1) / nchunks[i] * tc;
-    if (rt == 0) {
-      const int nsup = (In[i] + kSuper - 1) / kSuper;
-      const size_t lds = (size_t)2 * kSuper * kRowD * sizeof(double);   // 132 KB: more than the default limit
-      const dim3 grid((unsigned)nchunks[i], (unsigned)(nsup * nsup)), block(kGramThreads);
-      if (dtype == TGRAD_C64) {
-        allow_lds(k_gram<TGRAD_C64>, lds);
-        k_gram<TGRAD_C64><<<grid, block, lds, s>>>(g, mask, A[i], In[i], B[i], per, partials[i]);
-      } else {
-        allow_lds(k_gram<TGRAD_CBF16>, lds);
-        k_gram<TGRAD_CBF16><<<grid, block, lds, s>>>(g, mask, A[i], In[i], B[i], per, partials[i]);
-      }
-      continue;
+                       const int* In, const int64_t* B, int groups, const int* nchunks, double* const* partials) {
+  if (!gram_shared(In[0], B[0])) {
+    const int64_t tiles = (A[0] * B[0] + kTC - 1) / kTC, per = (tiles + nchunks[0] - 1) / nchunks[0] * kTC;
+    const int nsup = (In[0] + kSuper - 1) / kSuper;
+    const size_t lds = (size_t)2 * kSuper * kRowD * sizeof(double);     // 132 KB: more than the default limit
+    const dim3 grid((unsigned)nchunks[0], (unsigned)(nsup * nsup)), block(kGramThreads);
+    if (dtype == TGRAD_C64) {
+      allow_lds(k_gram<TGRAD_C64>, lds);
+      k_gram<TGRAD_C64><<<grid, block, lds, s>>>(g, mask, A[0], In[0], B[0], per, partials[0]);
+    } else {
+      allow_lds(k_gram<TGRAD_CBF16>, lds);
+      k_gram<TGRAD_CBF16><<<grid, block, lds, s>>>(g, mask, A[0], In[0], B[0], per, partials[0]);
     }
-    jobs.job[n++] = GramJob{rt, g, mask, partials[i], A[i], B[i], per, In[i], nchunks[i],
-                            B[i] <= 1 ? 0u : (uint32_t)((0x100000000ull + (uint64_t)B[i] - 1) / (uint64_t)B[i])};
-    chunks = nchunks[i] > chunks ? nchunks[i] : chunks;
-    const size_t lds = (size_t)4 * gram_plane(rt) * sizeof(double);
-    lds128 = lds > lds128 ? lds : lds128;
+    return;
   }
-  if (n == 0) return;
-  const dim3 grid((unsigned)chunks, (unsigned)n), block(kGram128Threads);
+  GramJobs jobs;
+  gram_line(njobs, A, In, B, groups, &jobs);
+  size_t lds = 0;
+  for (int i = 0; i < njobs; ++i) {
+    GramJob& jb = jobs.job[i];
+    jb.x = g;
+    jb.mask = mask;
+    jb.partials = partials[i];
+    jb.magicB = B[i] <= 1 ? 0u : (uint32_t)((0x100000000ull + (uint64_t)B[i] - 1) / (uint64_t)B[i]);
+    const size_t need = (size_t)4 * gram_plane(jb.rt) * sizeof(double);
+    lds = need > lds ? need : lds;
+  }
+  const dim3 grid((unsigned)groups), block(kGram128Threads);
   if (dtype == TGRAD_C64) {
-    allow_lds(k_gram128<TGRAD_C64>, lds128);
-    k_gram128<TGRAD_C64><<<grid, block, lds128, s>>>(jobs);
+    allow_lds(k_gram128<TGRAD_C64>, lds);
+    k_gram128<TGRAD_C64><<<grid, block, lds, s>>>(jobs);
   } else {
-    allow_lds(k_gram128<TGRAD_CBF16>, lds128);
-    k_gram128<TGRAD_CBF16><<<grid, block, lds128, s>>>(jobs);
+    allow_lds(k_gram128<TGRAD_CBF16>, lds);
+    k_gram128<TGRAD_CBF16><<<grid, block, lds, s>>>(jobs);
   }
 }
 

@@ -61,18 +61,18 @@ struct Plan {
   // byte offsets into workspace
   size_t ws_sel, ws_hist, ws_eig_status, ws_chunk_gt, ws_chunk_eq, ws_mask, ws_cand, ws_tile_start, ws_end_start, ws_fpad, ws_ut, ws_partials, ws_gram[kMaxNdim],
       ws_eig_a[kMaxNdim], ws_eig_v[kMaxNdim], ws_gs, ws_core_g, ws_core_n, ws_buf[2], workspace_bytes;
-  int gram_jobs = 0;               // the compressed modes, in order
+  int gram_jobs = 0;               // the compressed modes: those whose Grams share a launch, then the longer ones
+  int gram_together = 0, gram_groups = 0;   // (how many those are, and the workgroups of the launch)
   int gram_mode[kMaxNdim], gram_In[kMaxNdim], gram_chunks[kMaxNdim];
   int64_t gram_A[kMaxNdim], gram_B[kMaxNdim];
   size_t gram_partial[kMaxNdim];   // byte offset of the mode's partial sums in ws_partials
-  bool gram_batch = false;         // all modes in shared launches
   int order = 0;                   // TGRAD_ORDER_*
   int64_t zero_tiles = 0;
   size_t ws_tile_zero = 0;         // all-zero tile offsets: "no support" for the first-stage kernel
   size_t ws_resid = 0;             // low-rank-first order: the residual G - G~_L at refresh
   size_t ws_rbuf[2] = {0, 0};      // low-rank-first order: intermediates of the raw reconstruction chain
   int hooi_sweeps = 0;
-  int hooi_gram_chunks[kMaxNdim];  // Gram of the chain result of mode n
+  int hooi_gram_chunks[kMaxNdim], hooi_gram_groups[kMaxNdim];   // Gram of the chain result of mode n
 };
 
 // The stages of one HOOI projection chain: the residual compressed in every mode but `keep`
@@ -250,26 +250,29 @@ void make_plan(const tgrad_config* c, EndTier tier, Plan* p) {
   const bool packed = p->fuse_next && !p->narrow;
   p->ws_fpad = take(packed ? (size_t)p->shape[N - 2] * 32 * 8 : 0);
   p->ws_ut = take(packed ? (size_t)p->shape[N - 2] * 32 * 8 : 0);
-  // Partial Grams: of all modes side by side where they share launches, else of one mode at a time.
+  // Partial Grams: side by side where modes share a launch, then one longer mode at a time in the same place.
   size_t partial_max = 0;
   p->gram_jobs = 0;
-  for (int n = 0; n < N; ++n) {
-    if (p->rank[n] == p->shape[n]) continue;
-    const int j = p->gram_jobs++;
-    p->gram_mode[j] = n;
-    p->gram_In[j] = (int)p->shape[n];
-    p->gram_A[j] = 1;
-    for (int m = 0; m < n; ++m) p->gram_A[j] *= p->shape[m];
-    p->gram_B[j] = 1;
-    for (int m = n + 1; m < N; ++m) p->gram_B[j] *= p->shape[m];
-    p->gram_chunks[j] = gram_num_chunks(p->gram_A[j], p->gram_In[j], p->gram_B[j]);
+  for (int longer = 0; longer < 2; ++longer) {
+    for (int n = 0; n < N; ++n) {
+      int64_t A = 1, B = 1;
+      for (int m = 0; m < n; ++m) A *= p->shape[m];
+      for (int m = n + 1; m < N; ++m) B *= p->shape[m];
+      if (p->rank[n] == p->shape[n] || gram_shared((int)p->shape[n], B) != (longer == 0)) continue;
+      const int j = p->gram_jobs++;
+      p->gram_mode[j] = n;
+      p->gram_In[j] = (int)p->shape[n];
+      p->gram_A[j] = A;
+      p->gram_B[j] = B;
+    }
+    if (longer == 0) p->gram_together = p->gram_jobs;
   }
-  p->gram_batch = gram_batched(p->I);
-  if (p->gram_batch) gram_num_chunks_batched(p->gram_jobs, p->gram_A, p->gram_In, p->gram_B, p->gram_chunks);
+  if (p->gram_jobs > 0) p->gram_groups = gram_num_chunks(p->gram_jobs, p->gram_A, p->gram_In, p->gram_B, p->gram_chunks);
   for (int j = 0; j < p->gram_jobs; ++j) {
     const size_t bytes = (size_t)p->gram_chunks[j] * p->gram_In[j] * p->gram_In[j] * 16;
-    p->gram_partial[j] = p->gram_batch ? partial_max : 0;
-    partial_max = p->gram_batch ? partial_max + bytes : bytes > partial_max ? bytes : partial_max;
+    const bool together = j < p->gram_together;
+    p->gram_partial[j] = together ? partial_max : 0;
+    partial_max = together ? partial_max + bytes : bytes > partial_max ? bytes : partial_max;
   }
   p->hooi_sweeps = c->hooi_sweeps;
   size_t hooi_buf[2] = {0, 0};
@@ -282,7 +285,8 @@ void make_plan(const tgrad_config* c, EndTier tier, Plan* p) {
       const size_t b = (size_t)ch.out_elems[s] * 8;
       if (b > hooi_buf[s & 1]) hooi_buf[s & 1] = b;
     }
-    p->hooi_gram_chunks[n] = gram_num_chunks(ch.gram_A, (int)p->shape[n], ch.gram_B);
+    const int extent = (int)p->shape[n];
+    p->hooi_gram_groups[n] = gram_num_chunks(1, &ch.gram_A, &extent, &ch.gram_B, &p->hooi_gram_chunks[n]);
     const size_t bytes = (size_t)p->hooi_gram_chunks[n] * p->shape[n] * p->shape[n] * 16;
     if (bytes > partial_max) partial_max = bytes;
   }
@@ -534,9 +538,9 @@ void compute_factors(tgrad_ctx* c, const void* g, const uint32_t* tile_start, co
       Us[j] = c->st<float>(p.st_U[n]);
       stat[j] = c->w<int>(p.ws_eig_status) + 4 * n;
     }
-    const int group = p.gram_batch ? p.gram_jobs : 1;
-    for (int j = 0; j < p.gram_jobs; j += group) {
-      { Scope sc_(c, KID_GRAM); launch_gram_batch(s, group, g, dt, use_mask, p.gram_A + j, p.gram_In + j, p.gram_B + j, p.gram_chunks + j, partials + j); }
+    for (int j = 0, group; j < p.gram_jobs; j += group) {
+      group = j < p.gram_together ? p.gram_together : 1;
+      { Scope sc_(c, KID_GRAM); launch_gram_batch(s, group, g, dt, use_mask, p.gram_A + j, p.gram_In + j, p.gram_B + j, p.gram_groups, p.gram_chunks + j, partials + j); }
       { Scope sc_(c, KID_GRAM_REDUCE); launch_gram_reduce(s, group, p.gram_In + j, p.gram_chunks + j, partials + j, gram_out + j); }
     }
     Scope sc_(c, KID_EIG);
@@ -564,7 +568,7 @@ void compute_factors(tgrad_ctx* c, const void* g, const uint32_t* tile_start, co
       double* partials = c->w<double>(p.ws_partials);
       double* gram = c->w<double>(p.ws_gram[n]);
       const int i1[1] = {(int)p.shape[n]};
-      { Scope sc_(c, KID_GRAM); launch_gram_batch(s, 1, src, TGRAD_C64, nullptr, &ch.gram_A, i1, &ch.gram_B, &p.hooi_gram_chunks[n], &partials); }
+      { Scope sc_(c, KID_GRAM); launch_gram_batch(s, 1, src, TGRAD_C64, nullptr, &ch.gram_A, i1, &ch.gram_B, p.hooi_gram_groups[n], &p.hooi_gram_chunks[n], &partials); }
       { Scope sc_(c, KID_GRAM_REDUCE); launch_gram_reduce(s, 1, i1, &p.hooi_gram_chunks[n], &partials, &gram); }
       const double* g1[1] = {gram};
       double* a1[1] = {c->w<double>(p.ws_eig_a[n])};

@@ -71,12 +71,11 @@ void launch_mask_from_indices(hipStream_t s, const int32_t* omega, int64_t k, ui
                               int64_t mask_words);
 
 // factor refresh
-int gram_num_chunks(int64_t A, int In, int64_t B);
 size_t eig_work_bytes(int n);                      // size of launch_eig_batch's per-mode buffer work_a
-bool gram_batched(int64_t I);
-void gram_num_chunks_batched(int njobs, const int64_t* A, const int* In, const int64_t* B, int* nchunks);
+bool gram_shared(int In, int64_t B);
+int gram_num_chunks(int njobs, const int64_t* A, const int* In, const int64_t* B, int* nchunks);
 void launch_gram_batch(hipStream_t s, int njobs, const void* g, int dtype, const uint32_t* mask, const int64_t* A,
-                       const int* In, const int64_t* B, const int* nchunks, double* const* partials);
+                       const int* In, const int64_t* B, int groups, const int* nchunks, double* const* partials);
 void launch_gram_reduce(hipStream_t s, int njobs, const int* In, const int* nchunks, double* const* partials,
                         double* const* gram);
 
