@@ -1984,45 +1984,61 @@ static void gram_line(int njobs, const int64_t* A, const int* In, const int64_t*
 // Whether a mode shares its launch with others.
 bool gram_shared(int In, int64_t B) { return gram_rows(In, B) != 0; }
 
-// Chunks of every mode of a tensor, those that share a launch first; returns the workgroups of that launch.  Partial sums are
-// bounded in memory by 512 chunks dealt by work, and by 256 of the mode whose are largest (with more than 16.8 M numbers: by the
-// latter alone); a launch of 256 workgroups seldom comes near.
-int gram_num_chunks(int njobs, const int64_t* A, const int* In, const int64_t* B, int* nchunks) {
-  double largest = 0., by_work = 0., work = 0.;
-  int64_t tiles_all = 0, numbers = 0;
+// Chunks of every mode of a tensor, those that share a launch first; returns the workgroups of that launch.  `room`: bytes of the
+// partial sums, which are those of 512 chunks dealt by work, but not more than 256 of the mode whose are largest (with more than
+// 16.8 M numbers, or one mode: these).  A launch of 256 workgroups seldom comes near; where it would, it has fewer.
+int gram_num_chunks(int njobs, const int64_t* A, const int* In, const int64_t* B, int* nchunks, size_t* room) {
+  const bool by_work = njobs > 1 && A[0] * In[0] * B[0] <= (int64_t)256 * 16 * 4096;
+  double largest = 0., work = 0., sum = 0.;
+  int64_t tiles_all = 0;
   int together = 0;
+  auto most = [&](int i) -> int {
+    const int64_t tiles = gram_tiles(A[i], In[i], B[i]);
+    return tiles < 256 ? (tiles < 1 ? 1 : (int)tiles) : 256;
+  };
   auto cost = [&](int i) -> double {
     const int rt = gram_rows(In[i], B[i]);
     return (double)gram_tiles(A[i], In[i], B[i]) * (rt == 8 ? 3. : rt == 4 ? 1.7 : 1.);
   };
   for (int i = 0; i < njobs; ++i) work += cost(i);
   for (int i = 0; i < njobs; ++i) {
-    const int64_t tiles = gram_tiles(A[i], In[i], B[i]);
-    const int most = tiles < 256 ? (tiles < 1 ? 1 : (int)tiles) : 256, share = (int)(512. * cost(i) / work + 0.5);
-    nchunks[i] = most < share ? most : share < 1 ? 1 : share;
-    numbers = A[i] * In[i] * B[i];
-    largest = fmax(largest, fmin((double)((A[i] * B[i] + 15) / 16), 256.) * In[i] * In[i]);
-    by_work += (double)nchunks[i] * In[i] * In[i];
-    if (numbers > (int64_t)256 * 16 * 4096 || njobs == 1) nchunks[i] = most;
+    nchunks[i] = most(i);
+    if (by_work) {
+      const int share = (int)(512. * cost(i) / work + 0.5);
+      nchunks[i] = share < 1 ? 1 : share < nchunks[i] ? share : nchunks[i];
+    }
+    const double n2 = (double)In[i] * In[i];
+    largest = fmax(largest, (by_work ? fmin((double)((A[i] * B[i] + 15) / 16), 256.) : (double)nchunks[i]) * n2);
+    sum += nchunks[i] * n2;
     if (gram_shared(In[i], B[i])) {
       ++together;
-      tiles_all += tiles;
+      tiles_all += gram_tiles(A[i], In[i], B[i]);
     }
   }
-  const bool large = numbers > (int64_t)256 * 16 * 4096 || njobs == 1;
-  const double cap = large || by_work > largest ? largest : by_work;
-  for (int i = together; i < njobs; ++i)
-    if (!large && by_work > largest) nchunks[i] = (int)fmax(1., nchunks[i] * (largest / by_work));
-  if (together == 0) return 0;
-  GramJobs jobs;
-  for (int groups = tiles_all < 256 ? (int)(tiles_all < 1 ? 1 : tiles_all) : 256; ; --groups) {
-    gram_line(together, A, In, B, groups, &jobs);
-    double sum = 0.;
-    for (int i = 0; i < together; ++i) sum += (double)jobs.nchunks[i] * In[i] * In[i];
-    if (sum > cap && groups > 1) continue;
-    for (int i = 0; i < together; ++i) nchunks[i] = jobs.nchunks[i];
-    return groups;
+  double bound = largest;
+  if (by_work) {
+    const double part = sum > largest ? largest / sum : 1.;
+    bound = 0.;
+    for (int i = 0; i < njobs; ++i) {
+      if (part < 1.) nchunks[i] = (int)fmax(1., (int)(nchunks[i] * part));
+      bound += (double)nchunks[i] * In[i] * In[i];
+    }
   }
+  int groups = 0;
+  if (together > 0) {
+    GramJobs jobs;
+    groups = tiles_all < 256 ? (int)(tiles_all < 1 ? 1 : tiles_all) : 256;
+    for (;; --groups) {
+      gram_line(together, A, In, B, groups, &jobs);
+      sum = 0.;
+      for (int i = 0; i < together; ++i) sum += (double)jobs.nchunks[i] * In[i] * In[i];
+      if (sum <= bound || groups == 1) break;
+    }
+    for (int i = 0; i < together; ++i) nchunks[i] = jobs.nchunks[i];
+    bound = fmax(bound, sum);
+  }
+  *room = (size_t)bound * sizeof(double2);
+  return groups;
 }
 
 // Partial Grams of the modes that share a launch of `groups` workgroups, or of one that does not, in nchunks[0] chunks.

@@ -7,7 +7,8 @@
 // Method: most-significant-digit radix select on the 32-bit pattern of the float32 key (digits of
 // 12, 12 and 8 bits), arranged so that the gradient is streamed only TWICE:
 //   1. k_select_hist    reads G: histogram of the leading 12 key bits -> the bin b1 that holds the
-//                       k-th largest key.
+//                       k-th largest key (each digit's bin is picked by the workgroups of the kernel that needs it, from
+//                       the 16 KB of its histogram; on large tensors the first one by k_select_pick).
 //   2. k_select_split   reads G: one bit per element into two bitmasks: "sure" (leading digit above
 //                       b1: certainly in the support) and "cand" (leading digit equal to b1: the
 //                       candidates among which the remaining digits decide).
@@ -15,7 +16,7 @@
 //                       histograms of the middle 12 and the last 8 bits -> the key T of the k-th
 //                       largest entry and the number `need_eq` of entries equal to T that belong to
 //                       the support (the ones with the lowest indices).
-//   4. k_select_count / k_select_scan / k_select_emit walk the two masks (and the candidates' keys):
+//   4. k_select_count / k_select_emit walk the two masks (and the candidates' keys):
 //                       the position of entry i inside Omega is
 //                           #(key > T before i) + min(#(key == T before i), need_eq),
 //                       two exclusive prefix counts, so no atomics decide an output slot.  The emit
@@ -106,44 +107,58 @@ __global__ __launch_bounds__(kSelThreads) void k_select_hist(const KeySource g, 
     if (h[b]) atomicAdd(&hist[b], h[b]);
 }
 
-// One block of 1024 threads: find the digit bin that holds the `remaining`-th largest entry.
-__global__ __launch_bounds__(1024) void k_select_pick(int pass, uint32_t k, SelectScalars* sc,
-                                                      const uint32_t* __restrict__ hist) {
-  __shared__ uint32_t scan[1024];
-  const int t = threadIdx.x;
-  uint32_t c[4];
+// The bin of a digit's histogram that holds the `want`-th largest entry, and how many are to be taken inside it, by one
+// workgroup; every thread gets both.
+struct Picked {
+  uint32_t bin, remaining;
+};
+template <int BINS>
+__device__ __forceinline__ Picked pick_bin(const uint32_t* __restrict__ hist, uint32_t want) {
+  constexpr int PER = BINS / kSelThreads;
+  __shared__ uint32_t total[kWavesPerBlock];
+  __shared__ Picked found;
+  const int lane = lane_id(), wave = threadIdx.x / kWave;
+  uint32_t c[PER];
   uint32_t local = 0;
-  for (int b = 0; b < 4; ++b) {
-    c[b] = hist[4 * t + b];
+#pragma unroll
+  for (int b = 0; b < PER; ++b) {
+    c[b] = hist[PER * threadIdx.x + b];
     local += c[b];
   }
-  // inclusive scan over threads in DESCENDING bin order: slot j holds thread 1023 - j
-  scan[1023 - t] = local;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    uint32_t v = scan[t];
-    uint32_t add = t >= off ? scan[t - off] : 0u;
-    __syncthreads();
-    scan[t] = v + add;
-    __syncthreads();
+  uint32_t from = local;                             // entries in this thread's bins and in those of higher lanes
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const uint32_t up = __shfl_down(from, off, kWave);
+    if (lane + off < kWave) from += up;
   }
-  uint32_t above = scan[1023 - t] - local;           // entries in bins owned by higher threads
-  const uint32_t rem = pass == 0 ? k : sc->remaining;
-  const uint32_t prefix = pass == 0 ? 0u : sc->prefix;
-  __syncthreads();                                    // everyone has read sc before one thread writes
-  for (int b = 3; b >= 0; --b) {
-    if (above < rem && rem <= above + c[b]) {
-      uint32_t bin = 4u * t + b;
-      uint32_t np = pass == 0 ? bin : pass == 1 ? ((prefix << 12) | bin) : ((prefix << 8) | bin);
-      sc->prefix = np;
-      sc->remaining = rem - above;
-      if (pass == 2) {
-        sc->threshold = np;
-        sc->need_eq = rem - above;
-      }
-    }
+  if (lane == 0) total[wave] = from;
+  __syncthreads();
+  uint32_t above = from - local;
+#pragma unroll
+  for (int w = 0; w < kWavesPerBlock; ++w) above += w > wave ? total[w] : 0u;
+#pragma unroll
+  for (int b = PER - 1; b >= 0; --b) {
+    if (above < want && want <= above + c[b]) found = Picked{(uint32_t)(PER * threadIdx.x + b), want - above};
     above += c[b];
   }
+  __syncthreads();
+  return found;
+}
+
+// The first digit.  |g|^2 = inf or NaN has all exponent bits set: leading 12-bit digit 0x7F8 or above.
+__device__ __forceinline__ Picked pick_first(uint32_t k, SelectScalars* sc, const uint32_t* __restrict__ hist, bool write) {
+  const Picked p = pick_bin<kHistBins>(hist, k);
+  if (write && threadIdx.x == 0) {
+    sc->prefix[0] = p.bin;
+    sc->remaining[0] = p.remaining;
+    uint32_t n = 0;
+    for (int b = 0x7F8; b < 0x800; ++b) n += hist[b];
+    sc->nonfinite = n;
+  }
+  return p;
+}
+__global__ __launch_bounds__(kSelThreads) void k_select_pick(uint32_t k, SelectScalars* sc, const uint32_t* __restrict__ hist) {
+  pick_first(k, sc, hist, true);
 }
 
 // Keys of the (up to) two elements a lane holds in iteration `it` of segment `seg`.
@@ -175,15 +190,15 @@ __device__ __forceinline__ uint32_t spread16(uint32_t x) {
 // One bit per element into the two masks (bit b of word w = element 32 w + b): `sure` where the
 // leading key digit lies above the bin b1 of the first pick, `cand` where it equals b1.  Bits past
 // the end of the tensor are written as zero; every word that covers an element is written.
-template <int DT>
-__global__ __launch_bounds__(kSelThreads) void k_select_split(const KeySource g, int64_t I,
-                                                              const SelectScalars* __restrict__ sc,
-                                                              uint32_t* __restrict__ sure,
-                                                              uint32_t* __restrict__ cand, int64_t nseg) {
+// The leading digit of T is picked by every workgroup for itself (PICK), or has been by a launch of its own.
+template <int DT, bool PICK>
+__device__ __forceinline__ void split_segment(const KeySource& g, int64_t I, uint32_t k, SelectScalars* sc,
+                                              const uint32_t* __restrict__ hist, uint32_t* __restrict__ sure,
+                                              uint32_t* __restrict__ cand, int64_t nseg) {
   const int lane = lane_id();
   const int64_t seg = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x / kWave);
+  const uint32_t b1 = PICK ? pick_first(k, sc, hist, blockIdx.x == 0).bin : sc->prefix[0];
   if (seg >= nseg) return;                           // whole wave leaves together
-  const uint32_t b1 = sc->prefix;                    // after the first pick: the leading digit of T
   for (int it = 0; it < kSegIters; ++it) {
     int64_t i0;
     bool v0, v1;
@@ -198,20 +213,35 @@ __global__ __launch_bounds__(kSelThreads) void k_select_split(const KeySource g,
     }
   }
 }
+template <int DT>
+__global__ __launch_bounds__(kSelThreads) void k_select_split(const KeySource g, int64_t I, uint32_t k, int pick,
+                                                              SelectScalars* sc, const uint32_t* __restrict__ hist,
+                                                              uint32_t* __restrict__ sure, uint32_t* __restrict__ cand,
+                                                              int64_t nseg) {
+  if (pick) split_segment<DT, true>(g, I, k, sc, hist, sure, cand, nseg);
+  else split_segment<DT, false>(g, I, k, sc, hist, sure, cand, nseg);
+}
 
 // Histogram of the next digit over the candidates only (pass 1: bits 19..8 of the keys whose
 // leading digit is the picked one - every candidate; pass 2: bits 7..0 of the keys whose leading
-// 24 bits are the picked ones).  A lane owns one mask word per iteration and fetches the keys of
-// its set bits.
+// 24 bits are the picked ones: every workgroup picks the middle digit for itself).  A lane owns one mask word per iteration
+// and fetches the keys of its set bits.
 template <int DT>
-__global__ __launch_bounds__(kSelThreads) void k_select_hist_cand(const KeySource g, int pass,
-                                                                  const SelectScalars* __restrict__ sc,
+__global__ __launch_bounds__(kSelThreads) void k_select_hist_cand(const KeySource g, int pass, SelectScalars* sc,
                                                                   const uint32_t* __restrict__ cand,
                                                                   int64_t nwords, uint32_t* __restrict__ hist) {
   __shared__ uint32_t h[kHistBins];
   for (int b = threadIdx.x; b < kHistBins; b += kSelThreads) h[b] = 0;
+  uint32_t prefix = sc->prefix[0];
+  if (pass == 2) {
+    const Picked p = pick_bin<kHistBins>(hist - kHistBins, sc->remaining[0]);
+    prefix = (prefix << 12) | p.bin;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      sc->prefix[1] = prefix;
+      sc->remaining[1] = p.remaining;
+    }
+  }
   __syncthreads();
-  const uint32_t prefix = sc->prefix;
   const int64_t stride = (int64_t)gridDim.x * kSelThreads;
   for (int64_t w = (int64_t)blockIdx.x * kSelThreads + threadIdx.x; w < nwords; w += stride) {
     uint32_t c = cand[w];
@@ -251,15 +281,20 @@ __device__ __forceinline__ void classify_candidates(const KeySource& g, int64_t 
 // Per chunk of `chunk_words` mask words (one wavefront each): entries above T and entries equal to T.
 template <int DT>
 __global__ __launch_bounds__(kSelThreads) void k_select_count(const KeySource g,
-                                                              const SelectScalars* __restrict__ sc,
+                                                              SelectScalars* sc, const uint32_t* __restrict__ hist,
                                                               const uint32_t* __restrict__ sure,
                                                               const uint32_t* __restrict__ cand, int64_t nwords,
                                                               int chunk_words, uint32_t* __restrict__ chunk_gt,
                                                               uint32_t* __restrict__ chunk_eq, int64_t nchunks) {
   const int lane = lane_id();
   const int64_t chunk = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x / kWave);
+  const Picked p = pick_bin<256>(hist, sc->remaining[1]);                // the last digit
+  const uint32_t T = (sc->prefix[1] << 8) | p.bin;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    sc->prefix[2] = T;
+    sc->remaining[2] = p.remaining;
+  }
   if (chunk >= nchunks) return;
-  const uint32_t T = sc->threshold;
   uint32_t ngt = 0, neq = 0;
   for (int it = 0; it < chunk_words / kWave; ++it) {
     const int64_t w = chunk * chunk_words + (int64_t)it * kWave + lane;
@@ -278,10 +313,6 @@ __global__ __launch_bounds__(kSelThreads) void k_select_count(const KeySource g,
   }
 }
 
-// In-place exclusive prefix sums of both per-chunk count arrays; one block of 16 wavefronts.
-// Wavefront w owns the contiguous range [w * per, (w + 1) * per): it first adds the range up
-// (coalesced 64-entry reads), the 16 totals are scanned through LDS, then the range is walked again
-// and every 64-entry group is scanned with lane shuffles on top of the running offset.
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, int lane) {
 #pragma unroll
   for (int off = 1; off < kWave; off <<= 1) {
@@ -291,48 +322,12 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, int lane) {
   return v;
 }
 
-__global__ __launch_bounds__(1024) void k_select_scan(uint32_t* seg_gt, uint32_t* seg_eq, int64_t nseg) {
-  __shared__ uint32_t tot_g[16], tot_e[16];
-  const int lane = lane_id();
-  const int wave = threadIdx.x / kWave;
-  const int64_t per = ((nseg + 15) / 16 + kWave - 1) / kWave * kWave;       // a multiple of the group size
-  const int64_t lo = wave * per;
-  const int64_t hi = lo + per < nseg ? lo + per : nseg;
-  uint32_t a = 0, b = 0;
-  for (int64_t i = lo + lane; i < hi; i += kWave) {
-    a += seg_gt[i];
-    b += seg_eq[i];
-  }
-  a = wave_inclusive_scan(a, lane);
-  b = wave_inclusive_scan(b, lane);
-  if (lane == kWave - 1) {
-    tot_g[wave] = a;
-    tot_e[wave] = b;
-  }
-  __syncthreads();
-  uint32_t run_g = 0, run_e = 0;                      // entries in the ranges of lower wavefronts
-  for (int w = 0; w < wave; ++w) {
-    run_g += tot_g[w];
-    run_e += tot_e[w];
-  }
-  for (int64_t i0 = lo; i0 < hi; i0 += kWave) {
-    const int64_t i = i0 + lane;
-    const uint32_t cg = i < hi ? seg_gt[i] : 0u, ce = i < hi ? seg_eq[i] : 0u;
-    const uint32_t sg = wave_inclusive_scan(cg, lane), se = wave_inclusive_scan(ce, lane);
-    if (i < hi) {
-      seg_gt[i] = run_g + sg - cg;
-      seg_eq[i] = run_e + se - ce;
-    }
-    run_g += __shfl(sg, kWave - 1, kWave);
-    run_e += __shfl(se, kWave - 1, kWave);
-  }
-}
-
 // Ordered compaction: a wavefront walks its chunk of mask words in index order (lane = word inside
 // a group of 64, bits ascending inside a word) and writes every selected index to its final slot.
 // `sure` comes in as the mask of the entries whose leading digit lies above the picked bin and goes
 // out as the support bitmask (those, the candidates above T and the first need_eq candidates equal
-// to T).
+// to T).  A workgroup adds up the counts of all chunks before its own (at most some 4000: select_chunk_words), and the
+// histograms, which nobody reads any more, are left zero for the next selection.
 template <int DT>
 __global__ __launch_bounds__(kSelThreads) void k_select_emit(const KeySource g,
                                                              const SelectScalars* __restrict__ sc,
@@ -340,13 +335,39 @@ __global__ __launch_bounds__(kSelThreads) void k_select_emit(const KeySource g,
                                                              const uint32_t* __restrict__ chunk_eq,
                                                              int64_t nchunks, uint32_t* __restrict__ sure,
                                                              const uint32_t* __restrict__ cand, int64_t nwords,
-                                                             int chunk_words, int32_t* __restrict__ omega) {
-  const int lane = lane_id();
-  const int64_t chunk = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x / kWave);
+                                                             int chunk_words, uint32_t* __restrict__ hist,
+                                                             int32_t* __restrict__ omega) {
+  __shared__ uint32_t before[2][kWavesPerBlock];
+  const int lane = lane_id(), wave = threadIdx.x / kWave;
+  const int64_t chunk0 = (int64_t)blockIdx.x * kWavesPerBlock, chunk = chunk0 + wave;
+  for (int64_t b = (int64_t)blockIdx.x * kSelThreads + threadIdx.x; b < 3 * kHistBins; b += (int64_t)gridDim.x * kSelThreads)
+    hist[b] = 0u;
+  uint32_t run_gt = 0, run_eq = 0;                   // entries before this chunk
+#pragma unroll 4
+  for (int64_t c = threadIdx.x; c < chunk0; c += kSelThreads) {
+    run_gt += chunk_gt[c];
+    run_eq += chunk_eq[c];
+  }
+  run_gt = wave_sum(run_gt);
+  run_eq = wave_sum(run_eq);
+  if (lane == 0) {
+    before[0][wave] = run_gt;
+    before[1][wave] = run_eq;
+  }
+  __syncthreads();
+  run_gt = run_eq = 0;
+#pragma unroll
+  for (int w = 0; w < kWavesPerBlock; ++w) {
+    run_gt += before[0][w];
+    run_eq += before[1][w];
+  }
   if (chunk >= nchunks) return;
-  const uint32_t T = sc->threshold;
-  const uint32_t need = sc->need_eq;
-  uint32_t run_gt = chunk_gt[chunk], run_eq = chunk_eq[chunk];
+  for (int w = 0; w < wave; ++w) {
+    run_gt += chunk_gt[chunk0 + w];
+    run_eq += chunk_eq[chunk0 + w];
+  }
+  const uint32_t T = sc->prefix[2];
+  const uint32_t need = sc->remaining[2];
   for (int it = 0; it < chunk_words / kWave; ++it) {
     const int64_t w = chunk * chunk_words + (int64_t)it * kWave + lane;
     uint32_t take = 0u, equal = 0u;                   // bits taken for certain; bits equal to T
@@ -486,20 +507,25 @@ void launch_select_hist(hipStream_t s, const void* g, int dtype, const SelectKey
   TGRAD_SEL_DISPATCH(k_select_hist, grid, kSelThreads, src, I, hist);
 }
 
-void launch_select_pick(hipStream_t s, int pass, uint32_t k, SelectScalars* sc, const uint32_t* hist) {
-  k_select_pick<<<dim3(1), dim3(1024), 0, s>>>(pass, k, sc, hist);
+// The pick of the first digit in a launch of its own (4.7 us) where there are more workgroups of k_select_split than fit the chip
+// at a time: below that each has it done before its first key arrives (refresh of 64x64x32x17: 218 -> 207 us with the other
+// picks, the sums over chunks and the zeroing of histograms inside other launches, five fewer).
+bool select_pick_apart(int64_t I) { return (I + kSegElems * kWavesPerBlock - 1) / (kSegElems * kWavesPerBlock) > 2048; }
+
+void launch_select_pick(hipStream_t s, uint32_t k, SelectScalars* sc, const uint32_t* hist) {
+  k_select_pick<<<dim3(1), dim3(kSelThreads), 0, s>>>(k, sc, hist);
 }
 
-void launch_select_split(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I,
-                         const SelectScalars* sc, uint32_t* sure, uint32_t* cand) {
+void launch_select_split(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I, uint32_t k,
+                         SelectScalars* sc, const uint32_t* hist, uint32_t* sure, uint32_t* cand) {
   const int64_t nseg = (I + kSegElems - 1) / kSegElems;
   unsigned grid = (unsigned)((nseg + kWavesPerBlock - 1) / kWavesPerBlock);
   const KeySource src{g, keys.s0, keys.s1};
-  TGRAD_SEL_DISPATCH(k_select_split, grid, kSelThreads, src, I, sc, sure, cand, nseg);
+  TGRAD_SEL_DISPATCH(k_select_split, grid, kSelThreads, src, I, k, select_pick_apart(I) ? 0 : 1, sc, hist, sure, cand, nseg);
 }
 
 void launch_select_hist_cand(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I,
-                             int pass, const SelectScalars* sc, const uint32_t* cand, uint32_t* hist) {
+                             int pass, SelectScalars* sc, const uint32_t* cand, uint32_t* hist) {
   const int64_t nwords = (I + 31) / 32;
   int64_t want = (nwords + kSelThreads - 1) / kSelThreads;
   unsigned grid = (unsigned)(want < 1 ? 1 : want > 2048 ? 2048 : want);
@@ -507,36 +533,32 @@ void launch_select_hist_cand(hipStream_t s, const void* g, int dtype, const Sele
   TGRAD_SEL_DISPATCH(k_select_hist_cand, grid, kSelThreads, src, pass, sc, cand, nwords, hist);
 }
 
-// Mask words per chunk, the run one wavefront walks in order: as few as keep the counts to be scanned at a few
-// thousand (64x64x32x17 in runs of 1024 words, 17 workgroups: count and emit 19 us each, in runs of 64 words 5).
+// Mask words per chunk, the run one wavefront walks in order: as few as keep the counts, which every workgroup of
+// k_select_emit adds up, at a few thousand (64x64x32x17 in runs of 1024 words, 17 workgroups: count and emit 19 us each, in runs of 64 words 5).
 int select_chunk_words(int64_t I) {
   int words = kWave;
-  while (words < 1024 && I > (int64_t)words * 32 * 4224) words *= 2;
+  while (I > (int64_t)words * 32 * 4224) words *= 2;
   return words;
 }
 
 void launch_select_count(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I,
-                         const SelectScalars* sc, const uint32_t* sure, const uint32_t* cand,
+                         SelectScalars* sc, const uint32_t* hist, const uint32_t* sure, const uint32_t* cand,
                          uint32_t* chunk_gt, uint32_t* chunk_eq, int64_t nchunks) {
   const int64_t nwords = (I + 31) / 32;
   unsigned grid = (unsigned)((nchunks + kWavesPerBlock - 1) / kWavesPerBlock);
   const KeySource src{g, keys.s0, keys.s1};
-  TGRAD_SEL_DISPATCH(k_select_count, grid, kSelThreads, src, sc, sure, cand, nwords, select_chunk_words(I),
+  TGRAD_SEL_DISPATCH(k_select_count, grid, kSelThreads, src, sc, hist, sure, cand, nwords, select_chunk_words(I),
                      chunk_gt, chunk_eq, nchunks);
-}
-
-void launch_select_scan(hipStream_t s, uint32_t* chunk_gt, uint32_t* chunk_eq, int64_t nchunks) {
-  k_select_scan<<<dim3(1), dim3(1024), 0, s>>>(chunk_gt, chunk_eq, nchunks);
 }
 
 void launch_select_emit(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I,
                         const SelectScalars* sc, const uint32_t* chunk_gt, const uint32_t* chunk_eq,
-                        int64_t nchunks, uint32_t* sure, const uint32_t* cand, int32_t* omega) {
+                        int64_t nchunks, uint32_t* sure, const uint32_t* cand, uint32_t* hist, int32_t* omega) {
   const int64_t nwords = (I + 31) / 32;
   unsigned grid = (unsigned)((nchunks + kWavesPerBlock - 1) / kWavesPerBlock);
   const KeySource src{g, keys.s0, keys.s1};
   TGRAD_SEL_DISPATCH(k_select_emit, grid, kSelThreads, src, sc, chunk_gt, chunk_eq, nchunks, sure, cand, nwords,
-                     select_chunk_words(I), omega);
+                     select_chunk_words(I), hist, omega);
 }
 #undef TGRAD_SEL_DISPATCH
 

@@ -2,6 +2,7 @@
 // caller's state / workspace buffers, and the sequencing of kernels on the caller's stream for
 // the two branches of Algorithm 1 (refresh and step).
 #include <cmath>
+#include <cstddef>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -27,7 +28,7 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 const char* const kKernelNames[KID_COUNT] = {
-    "select_hist", "select_pick", "select_split", "select_hist_cand", "select_count", "select_scan", "select_emit",
+    "select_hist", "select_pick", "select_split", "select_hist_cand", "select_count", "select_emit",
     "mask_from_indices",
     "tile_offsets", "gram", "gram_reduce", "eig_jacobi", "factor_pack",
     "gather", "project_first", "project", "adam_core", "backproject", "update", "sparse_update",
@@ -267,12 +268,12 @@ void make_plan(const tgrad_config* c, EndTier tier, Plan* p) {
     }
     if (longer == 0) p->gram_together = p->gram_jobs;
   }
-  if (p->gram_jobs > 0) p->gram_groups = gram_num_chunks(p->gram_jobs, p->gram_A, p->gram_In, p->gram_B, p->gram_chunks);
+  if (p->gram_jobs > 0)
+    p->gram_groups = gram_num_chunks(p->gram_jobs, p->gram_A, p->gram_In, p->gram_B, p->gram_chunks, &partial_max);
+  size_t side = 0;
   for (int j = 0; j < p->gram_jobs; ++j) {
-    const size_t bytes = (size_t)p->gram_chunks[j] * p->gram_In[j] * p->gram_In[j] * 16;
-    const bool together = j < p->gram_together;
-    p->gram_partial[j] = together ? partial_max : 0;
-    partial_max = together ? partial_max + bytes : bytes > partial_max ? bytes : partial_max;
+    p->gram_partial[j] = j < p->gram_together ? side : 0;
+    side += (size_t)p->gram_chunks[j] * p->gram_In[j] * p->gram_In[j] * 16;
   }
   p->hooi_sweeps = c->hooi_sweeps;
   size_t hooi_buf[2] = {0, 0};
@@ -286,8 +287,8 @@ void make_plan(const tgrad_config* c, EndTier tier, Plan* p) {
       if (b > hooi_buf[s & 1]) hooi_buf[s & 1] = b;
     }
     const int extent = (int)p->shape[n];
-    p->hooi_gram_groups[n] = gram_num_chunks(1, &ch.gram_A, &extent, &ch.gram_B, &p->hooi_gram_chunks[n]);
-    const size_t bytes = (size_t)p->hooi_gram_chunks[n] * p->shape[n] * p->shape[n] * 16;
+    size_t bytes;
+    p->hooi_gram_groups[n] = gram_num_chunks(1, &ch.gram_A, &extent, &ch.gram_B, &p->hooi_gram_chunks[n], &bytes);
     if (bytes > partial_max) partial_max = bytes;
   }
   // The selection's counts and candidate mask lie where the partial Grams do: none of them outlives its own pass.
@@ -351,7 +352,8 @@ struct tgrad_ctx {
   int64_t t;
   bool have_indices;
   bool have_factor[kMaxNdim];
-  bool have_hist;                 // the leading-digit histogram of the last refresh's gradient is in the workspace
+  bool have_hist;                 // the last refresh has counted its gradient's non-finite entries
+  bool hist_zero;                 // the selection's histograms are zero when a refresh begins
   int launch_status;              // first failed kernel launch of the current call (TGRAD_OK = none)
   bool profiling;
   std::vector<EventPair> events;
@@ -471,19 +473,20 @@ void select_support(tgrad_ctx* c, const void* x, int dt) {
     keys.s1 = (uint32_t)(seed >> 32) + t32 + 0x7F4A7C15u;
   }
   if (p.k > 0) {
-    zero_u32(s, hist, 3 * kHistBins);
+    // the histograms are zero between selections (k_select_emit leaves them so), unless a launch has failed
+    if (!c->hist_zero) zero_u32(s, hist, 3 * kHistBins);
     // two streaming passes over x: leading-digit histogram, then the two bitmasks
     { Scope sc_(c, KID_SEL_HIST); launch_select_hist(s, x, dt, keys, p.I, hist); }
-    { Scope sc_(c, KID_SEL_PICK); launch_select_pick(s, 0, (uint32_t)p.k, sc, hist); }
-    { Scope sc_(c, KID_SEL_SPLIT); launch_select_split(s, x, dt, keys, p.I, sc, mask, cand); }
+    if (select_pick_apart(p.I)) { Scope sc_(c, KID_SEL_PICK); launch_select_pick(s, (uint32_t)p.k, sc, hist); }
+    { Scope sc_(c, KID_SEL_SPLIT); launch_select_split(s, x, dt, keys, p.I, (uint32_t)p.k, sc, hist, mask, cand); }
     // the remaining digits are decided among the candidates only
     for (int pass = 1; pass < 3; ++pass) {
-      { Scope sc_(c, KID_SEL_HIST_CAND); launch_select_hist_cand(s, x, dt, keys, p.I, pass, sc, cand, hist + pass * kHistBins); }
-      { Scope sc_(c, KID_SEL_PICK); launch_select_pick(s, pass, (uint32_t)p.k, sc, hist + pass * kHistBins); }
+      Scope sc_(c, KID_SEL_HIST_CAND);
+      launch_select_hist_cand(s, x, dt, keys, p.I, pass, sc, cand, hist + pass * kHistBins);
     }
-    { Scope sc_(c, KID_SEL_COUNT); launch_select_count(s, x, dt, keys, p.I, sc, mask, cand, chunk_gt, chunk_eq, p.nchunks); }
-    { Scope sc_(c, KID_SEL_SCAN); launch_select_scan(s, chunk_gt, chunk_eq, p.nchunks); }
-    { Scope sc_(c, KID_SEL_EMIT); launch_select_emit(s, x, dt, keys, p.I, sc, chunk_gt, chunk_eq, p.nchunks, mask, cand, omega); }
+    { Scope sc_(c, KID_SEL_COUNT); launch_select_count(s, x, dt, keys, p.I, sc, hist + 2 * kHistBins, mask, cand, chunk_gt, chunk_eq, p.nchunks); }
+    { Scope sc_(c, KID_SEL_EMIT); launch_select_emit(s, x, dt, keys, p.I, sc, chunk_gt, chunk_eq, p.nchunks, mask, cand, hist, omega); }
+    if (c->launch_status != TGRAD_OK) c->hist_zero = false;
   }
   c->have_hist = p.k > 0 && !keys.random;
   tile_offsets(c);
@@ -893,6 +896,7 @@ int tgrad_init(tgrad_ctx** out, const tgrad_config* cfg, void* state_dev, void* 
   c->have_indices = false;
   for (int n = 0; n < kMaxNdim; ++n) c->have_factor[n] = false;
   c->have_hist = false;
+  c->hist_zero = true;
   c->launch_status = TGRAD_OK;
   c->profiling = false;
   for (int i = 0; i < KID_COUNT; ++i) {
@@ -901,6 +905,7 @@ int tgrad_init(tgrad_ctx** out, const tgrad_config* cfg, void* state_dev, void* 
   }
   // no solve has hit its sweep limit yet (a factor injected with tgrad_set_state never does)
   zero_u32(c->stream, c->w<uint32_t>(c->plan.ws_eig_status), 4 * kMaxNdim);
+  zero_u32(c->stream, c->w<uint32_t>(c->plan.ws_hist), 3 * kHistBins);
   // moments <- 0 (and everything else in the state block), with a fill kernel
   zero_u32(c->stream, reinterpret_cast<uint32_t*>(c->state), (int64_t)(c->plan.state_bytes / 4));
   if (c->plan.order != TGRAD_ORDER_US_LR)
@@ -960,6 +965,7 @@ int tgrad_step_static(const tgrad_config* cfg, void* state_dev, int64_t t, void*
   c.have_indices = true;                                          // the caller's contract for t % T != 0
   for (int n = 0; n < kMaxNdim; ++n) c.have_factor[n] = true;
   c.have_hist = false;
+  c.hist_zero = false;               // (scratch of all calls)
   c.launch_status = TGRAD_OK;
   c.profiling = false;
   if (error_pending_on_entry()) return TGRAD_ERR_HIP;
@@ -1026,13 +1032,9 @@ int tgrad_check(tgrad_ctx* ctx, int64_t* nonfinite) {
   if (ctx->cfg.select_rule != TGRAD_SELECT_TOPK_MAG || p.k == 0) return TGRAD_ERR_UNSUPPORTED;
   if (!ctx->have_hist) return TGRAD_ERR_NOT_READY;
   if (hipStreamSynchronize(ctx->stream) != hipSuccess) return TGRAD_ERR_HIP;
-  // |g|^2 = inf or NaN has all exponent bits set: leading 12-bit digit 0x7F8 or above
-  constexpr int kFirst = 0x7F8;
-  uint32_t tail[kHistBins - kFirst];
-  if (hipMemcpy(tail, ctx->ws + p.ws_hist + (size_t)kFirst * 4, sizeof(tail), hipMemcpyDeviceToHost) != hipSuccess)
+  uint32_t n = 0;
+  if (hipMemcpy(&n, ctx->ws + p.ws_sel + offsetof(SelectScalars, nonfinite), sizeof(n), hipMemcpyDeviceToHost) != hipSuccess)
     return TGRAD_ERR_HIP;
-  int64_t n = 0;
-  for (uint32_t v : tail) n += v;
   *nonfinite = n;
   return TGRAD_OK;
 }

@@ -17,11 +17,11 @@ constexpr int kMaxNdim = TGRAD_MAX_NDIM;
 constexpr int kSegElems = 2048;
 constexpr int kHistBins = 4096;            // 12-bit digits; the three digits are 12 + 12 + 8 bits
 
-struct SelectScalars {                     // lives in workspace, written by the pick kernel
-  uint32_t prefix;                         // key bits fixed so far (high-aligned digits)
-  uint32_t remaining;                      // how many entries are still to take inside `prefix`
-  uint32_t threshold;                      // final: key of the k-th largest entry
-  uint32_t need_eq;                        // final: entries with key == threshold to take (lowest indices)
+struct SelectScalars {                     // lives in workspace; what the pick of each digit leaves for the kernels behind it
+  uint32_t prefix[3];                      // key bits fixed so far; after the last digit the key of the k-th largest entry
+  uint32_t remaining[3];                   // how many entries are still to take inside `prefix`; after the last digit the
+                                           // entries equal to the key that belong to the support (lowest indices)
+  uint32_t nonfinite;                      // entries whose |g|^2 is infinite or NaN
 };
 
 // ---- one mode-n product stage: Out[a, m, b] = sum_k F[m, k] X[a, k, b] ------------------------
@@ -35,7 +35,7 @@ struct Stage {
 
 // Names of the profiled kernels (index into the per-context timing table).
 enum KernelId {
-  KID_SEL_HIST = 0, KID_SEL_PICK, KID_SEL_SPLIT, KID_SEL_HIST_CAND, KID_SEL_COUNT, KID_SEL_SCAN, KID_SEL_EMIT,
+  KID_SEL_HIST = 0, KID_SEL_PICK, KID_SEL_SPLIT, KID_SEL_HIST_CAND, KID_SEL_COUNT, KID_SEL_EMIT,
   KID_MASK_FROM_IDX,
   KID_TILE_OFFSETS, KID_GRAM, KID_GRAM_REDUCE, KID_EIG, KID_FACTOR_PACK,
   KID_GATHER, KID_PROJECT_FIRST, KID_PROJECT, KID_ADAM_CORE, KID_BACKPROJECT, KID_UPDATE,
@@ -54,26 +54,26 @@ struct SelectKeys {
 };
 void launch_select_hist(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I,
                         uint32_t* hist);
-void launch_select_pick(hipStream_t s, int pass, uint32_t k, SelectScalars* sc, const uint32_t* hist);
-void launch_select_split(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I,
-                         const SelectScalars* sc, uint32_t* sure, uint32_t* cand);
+bool select_pick_apart(int64_t I);
+void launch_select_pick(hipStream_t s, uint32_t k, SelectScalars* sc, const uint32_t* hist);
+void launch_select_split(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I, uint32_t k,
+                         SelectScalars* sc, const uint32_t* hist, uint32_t* sure, uint32_t* cand);
 void launch_select_hist_cand(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I,
-                             int pass, const SelectScalars* sc, const uint32_t* cand, uint32_t* hist);
+                             int pass, SelectScalars* sc, const uint32_t* cand, uint32_t* hist);
 int select_chunk_words(int64_t I);
 void launch_select_count(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I,
-                         const SelectScalars* sc, const uint32_t* sure, const uint32_t* cand,
+                         SelectScalars* sc, const uint32_t* hist, const uint32_t* sure, const uint32_t* cand,
                          uint32_t* chunk_gt, uint32_t* chunk_eq, int64_t nchunks);
-void launch_select_scan(hipStream_t s, uint32_t* chunk_gt, uint32_t* chunk_eq, int64_t nchunks);
 void launch_select_emit(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I,
                         const SelectScalars* sc, const uint32_t* chunk_gt, const uint32_t* chunk_eq,
-                        int64_t nchunks, uint32_t* sure, const uint32_t* cand, int32_t* omega);
+                        int64_t nchunks, uint32_t* sure, const uint32_t* cand, uint32_t* hist, int32_t* omega);
 void launch_mask_from_indices(hipStream_t s, const int32_t* omega, int64_t k, uint32_t* mask,
                               int64_t mask_words);
 
 // factor refresh
 size_t eig_work_bytes(int n);                      // size of launch_eig_batch's per-mode buffer work_a
 bool gram_shared(int In, int64_t B);
-int gram_num_chunks(int njobs, const int64_t* A, const int* In, const int64_t* B, int* nchunks);
+int gram_num_chunks(int njobs, const int64_t* A, const int* In, const int64_t* B, int* nchunks, size_t* room);
 void launch_gram_batch(hipStream_t s, int njobs, const void* g, int dtype, const uint32_t* mask, const int64_t* A,
                        const int* In, const int64_t* B, int groups, const int* nchunks, double* const* partials);
 void launch_gram_reduce(hipStream_t s, int njobs, const int* In, const int* nchunks, double* const* partials,
