@@ -611,13 +611,17 @@ __host__ __device__ constexpr int tail_slice(int M, int R) { return (R * 2 * M +
 // the others of those the same)
 constexpr int tail_ahead(int CT, int NC, int SA) { return SA == 8 && NC == 2 ? 1 : CT == 9 || NC == 2 ? 2 : 1; }
 
+// Whether a kernel has the code for slabs that several wavefronts walk together (launch_tail has the rule).
+constexpr bool tail_shares(int WDT, int CT) { return WDT == TGRAD_C64 && CT > 2; }
+
 struct TailArgs {
   const float2* y1;             // (nslabs, K2, K) complex
   const float2* U2;             // (I2, K2)
   const float2* U3;             // (M, K)
   void* w;
   int K, M, I2, K2, S, nslabs;
-  int split;                    // 1: single tiles are dealt to the wavefronts; 0: whole slabs
+  int split;                    // 1: single tiles are dealt to the wavefronts; 0: whole slabs; 2, 4: slabs that many wavefronts walk
+                                // together, tile by tile in turn (divides W and S)
   float decay, c_alpha;
 };
 
@@ -643,20 +647,22 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
   constexpr int KA = SA > 4 ? 2 : 1;                                     // quads of K2
   const bool vtail = (N2 & 15) == 2;
   const int NT = vtail ? N2 >> 4 : (N2 + 15) >> 4;                       // column tiles (<= CT: host)
-  const bool split = a.split != 0;
+  constexpr bool kShare = tail_shares(WDT, CT);
+  const bool split = kShare ? a.split == 1 : a.split != 0;
   const int nw = (int)gridDim.x * W;
   const int first = (int)blockIdx.x * W + wave;
-  int slab = split ? first / S : first, ts = split ? first - slab * S : 0;
+  const int share = kShare ? a.split >> 1 : 0, every = kShare && share ? a.split : 1, ts0 = kShare ? wave & (every - 1) : 0;
+  int slab = split ? first / S : first >> share, ts = split ? first - slab * S : ts0;
   auto advance = [&](int& sl, int& t) {
     if (split) {
       t += nw;
       sl += t / S;
       t = t % S;
-    } else if (t + 1 < S) {
-      t += 1;
+    } else if (t + every < S) {
+      t += every;
     } else {
-      t = 0;
-      sl += nw;
+      t = ts0;
+      sl += nw >> share;
     }
   };
   const uint32_t slab_elems = (uint32_t)(I2 * M);
@@ -1131,7 +1137,18 @@ void launch_tail(hipStream_t s, const float2* y1, const float2* U3, int K, int M
   // 250x12, r 20,4 142 / 156.
   const bool split = nslabs < kWholeSlabs ||
                      (S >= 5 && nslabs < (wdtype == TGRAD_C64 && K <= 8 && M > 17 ? 9 * kWholeSlabs : 5 * kWholeSlabs / 2));
-  const int64_t units = split ? nslabs * S : nslabs;
+  // Slabs are walked by two or four wavefronts of a workgroup together, in turn, where a slab has as many tiles (or a multiple): what
+  // a workgroup has in flight then lies side by side, which is what the memory rewards (a stand-alone loop that updates 8 KB tiles
+  // in place: 5.6 TB/s with wavefronts on slabs of their own, 5.2 with 16 KB tiles, 5.8 with wavefronts on consecutive
+  // tiles).  Each of them fetches the slab's part of z, so for ranks of 17 and more in mode N-1 only slabs of many
+  // tiles are shared; bf16 W and rows of up to 17 elements gain nothing.  Alone / two / four, whole step, us:
+  // 128x128x64x33, r 16,8 behind 32,32 185.5 / 184.2 / -; 100x100x64x65, r 16,8 217 / 212 / 207; 128x128x128x33, r 16,8, bf16 G 296 /
+  // 299 / 284; 50x50x64x65 73.3 / 71.0 / 69.5; 128x128x128x65, r 32,16 741 / 725 / 732; 64x64x128x65, r 32,16 207 / 201 / 200;
+  // 100x100x96x40, r 30,6 221 / 217 / -; but 64x64x64x33, r 30,16 80.9 / 85.3 / -; 100x100x64x17, r 8,4 67.5 / 68.2 / -; 128x128x64x65,
+  // bf16 G and W 190.6 / 189.5 / 190.8.
+  const int many = K2 <= 16 ? (S % 4 == 0 ? 4 : 2) : S >= 6 || (K <= 8 && S >= 4) ? 2 : 1;
+  const int together = !split && tail_shares(wdtype, columns_class(M)) && S % many == 0 ? many : 1;
+  const int64_t units = split ? nslabs * S : nslabs * together;
   const int full = tail_lds(4, M, I2, K2, K) <= kLdsLimit / 2 ? 4 : tail_lds(8, M, I2, K2, K) <= kLdsLimit ? 8 : 4;
   // Few tiles: a wavefront each.  Where coefficients go to LDS (tail_coef_lds) it then takes its operands straight into
   // registers; while all such tiles are resident that is the faster one for up to 8 columns of rank, beyond that up to
@@ -1142,7 +1159,7 @@ void launch_tail(hipStream_t s, const float2* y1, const float2* U3, int K, int M
   const bool one = in_lds && split && units <= (K <= 8 ? 3 * kWholeSlabs : 768);
   const int W = !one && (in_lds || units >= kWholeSlabs) ? full : 1;
   const size_t lds = tail_lds(W, M, I2, K2, K, one);
-  TailArgs a{y1, U2, U3, w, K, M, I2, K2, S, (int)nslabs, split ? 1 : 0, decay, c_alpha};
+  TailArgs a{y1, U2, U3, w, K, M, I2, K2, S, (int)nslabs, split ? 1 : W % together || together == 1 ? 0 : together, decay, c_alpha};
   const SparseAdam sp = sparse_adam(omega, tile_start, gs, ms, vs, beta1, beta2, inv_c1, inv_c2, eps, c_lambda, 0);
   const int ct = columns_class(M), nc = K <= 8 ? 1 : 2, sa = step_class(K2);
 #define TGRAD_TAIL(WD_, T_, C_, A_)                                                                          \
