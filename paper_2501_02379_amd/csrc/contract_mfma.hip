@@ -10,7 +10,7 @@
 // i.e. 4 real multiply-adds per complex multiply-add on either layout below.
 //
 // The kernels:
-//  (the modes between: mid.hip, core2.hip; both ends on 16 x 16 tiles: ends.hip)
+//  (the modes between: mid.hip, core2.hip; both ends on 16 x 16 tiles: ends.hip; the last mode alone, up to 72 entries: rows.hip)
 //  k_lproj    contracts the LAST mode of the gradient itself (first compression stage): a
 //             flat tile of rows is staged in LDS, the entries of the support Omega that fall
 //             in the tile are handed to the sparse branch (gather) and zeroed (this is
@@ -1357,6 +1357,7 @@ void launch_lproj(hipStream_t s, const void* g, int dtype, const int32_t* omega,
   const int64_t A = st.A;
   const int K = st.K, M = st.M;
   if (A * M <= 0) return;
+  if (fused_I2 == 0 && rows_kernel_fits(K, M)) return launch_rows(s, g, dtype, omega, tile_start, gs, U, st, out);
   const int64_t ntiles = (A + kTileRows - 1) / kTileRows;
   const size_t lds = lproj_lds_bytes(W, K, M);
   const int NT = (2 * M + 31) / 32;
@@ -1388,15 +1389,9 @@ void launch_lproj(hipStream_t s, const void* g, int dtype, const int32_t* omega,
   do {                                                                                                   \
     if (K & 1) TGRAD_LP(DT_, W_, NTB_, true); else TGRAD_LP(DT_, W_, NTB_, false);                       \
   } while (0)
-#define TGRAD_LP_F4(DT_, NTB_)   /* 4 wavefronts: also the variants for narrow last modes */              \
-  do {                                                                                                   \
-    if (tb == kTileBatch) TGRAD_LP_F(DT_, 4, NTB_);                                                      \
-    else if (tb == 9) { if (K & 1) TGRAD_LP_C(DT_, 4, NTB_, true, false, 1, 9); else TGRAD_LP_C(DT_, 4, NTB_, false, false, 1, 9); } \
-    else { if (K & 1) TGRAD_LP_C(DT_, 4, NTB_, true, false, 1, 5); else TGRAD_LP_C(DT_, 4, NTB_, false, false, 1, 5); } \
-  } while (0)
 #define TGRAD_LP_W(DT_, NTB_)                                                                            \
   do {                                                                                                   \
-    if (W == 4) TGRAD_LP_F4(DT_, NTB_); else if (W == 2) TGRAD_LP_F(DT_, 2, NTB_); else TGRAD_LP_F(DT_, 1, NTB_); \
+    if (W == 4) TGRAD_LP_F(DT_, 4, NTB_); else if (W == 2) TGRAD_LP_F(DT_, 2, NTB_); else TGRAD_LP_F(DT_, 1, NTB_); \
   } while (0)
 #define TGRAD_LPF_C(DT_, CP_, TB_)                                                                       \
   do {                                                                                                   \
@@ -1428,7 +1423,6 @@ void launch_lproj(hipStream_t s, const void* g, int dtype, const int32_t* omega,
   }
 #undef TGRAD_LPF
 #undef TGRAD_LPF_C
-#undef TGRAD_LP_F4
 #undef TGRAD_LP_W
 #undef TGRAD_LP_F
 #undef TGRAD_LP_FUSED
@@ -1443,6 +1437,9 @@ void launch_lupdate(hipStream_t s, const float2* z, const float2* U, const Stage
   const int64_t A = st.A;
   const int K = st.K, M = st.M;
   if (A * M <= 0) return;
+  if (rows_update_pays(M, K, A))
+    return launch_rows_update(s, z, U, st, w, wdtype, decay, c_alpha, omega, tile_start, gs, ms, vs, beta1, beta2, inv_c1,
+                              inv_c2, eps, c_lambda);
   const int64_t ntiles = (A + kTileRows - 1) / kTileRows;
   const size_t lds = lupdate_lds_bytes(W, K, M);
   const int64_t ngroups = (ntiles + W - 1) / W;
@@ -1463,11 +1460,14 @@ void launch_lupdate(hipStream_t s, const float2* z, const float2* U, const Stage
       k_lupdate<TGRAD_CBF16, W_, 2, JT_, UP_><<<grid, block, lds, s>>>(zf, U, A, K, M, ntiles, w, decay, c_alpha, sp); \
     }                                                                                                    \
   } while (0)
-#define TGRAD_LU(W_, JT_)        /* 4 wavefronts: also the variants for narrow last modes */              \
+  // (narrow last modes of a rank above 8 are k_rows_update's: 4 wavefronts, variants of up to four operand pairs)
+#define TGRAD_LU(W_, JT_)                                                                                \
   do {                                                                                                   \
-    if (W_ == 4 && up == 5) TGRAD_LU_U(4, JT_, 5);                                                       \
-    else if (W_ == 4 && up == 9) TGRAD_LU_U(4, JT_, 9);                                                  \
-    else TGRAD_LU_U(W_, JT_, kUpdPrefetch);                                                              \
+    if constexpr (W_ == 4 && JT_ <= 4) {                                                                 \
+      if (up == 5) { TGRAD_LU_U(4, JT_, 5); break; }                                                     \
+      if (up == 9) { TGRAD_LU_U(4, JT_, 9); break; }                                                     \
+    }                                                                                                    \
+    TGRAD_LU_U(W_, JT_, kUpdPrefetch);                                                                   \
   } while (0)
 #define TGRAD_LU_J(W_)                                                                                   \
   do {                                                                                                   \

@@ -127,6 +127,15 @@ void launch_lupdate_fused(hipStream_t s, const float2* y1, const float2* ut, int
                           const uint32_t* tile_start, int64_t k, const float2* gs, float2* ms, float* vs,
                           float beta1, float beta2, double inv_c1, double inv_c2, float eps, float c_lambda);
 
+// the last mode alone, on split operands (rows.hip)
+bool rows_kernel_fits(int K, int r);
+bool rows_update_pays(int K, int r, int64_t rows);
+void launch_rows(hipStream_t s, const void* g, int dtype, const int32_t* omega, const uint32_t* tile_start, float2* gs,
+                 const float2* U, const Stage& st, float2* out);
+void launch_rows_update(hipStream_t s, const float2* z, const float2* U, const Stage& st, void* w, int wdtype, float decay,
+                        float c_alpha, const int32_t* omega, const uint32_t* tile_start, const float2* gs, float2* ms, float* vs,
+                        float beta1, float beta2, double inv_c1, double inv_c2, float eps, float c_lambda);
+
 // modes N-1 and N in one pass on 16 x 16 tiles (ends.hip)
 int end_tile_rows(int K);
 bool ends_kernel_fits(int K, int r, int I2, int r2);
