@@ -1357,7 +1357,7 @@ void launch_lproj(hipStream_t s, const void* g, int dtype, const int32_t* omega,
   const int64_t A = st.A;
   const int K = st.K, M = st.M;
   if (A * M <= 0) return;
-  if (fused_I2 == 0 && rows_kernel_fits(K, M)) return launch_rows(s, g, dtype, omega, tile_start, gs, U, st, out);
+  if (fused_I2 == 0 && rows_kernel_pays(K, M, A)) return launch_rows(s, g, dtype, omega, tile_start, gs, U, st, out);
   const int64_t ntiles = (A + kTileRows - 1) / kTileRows;
   const size_t lds = lproj_lds_bytes(W, K, M);
   const int NT = (2 * M + 31) / 32;
@@ -1391,7 +1391,9 @@ void launch_lproj(hipStream_t s, const void* g, int dtype, const int32_t* omega,
   } while (0)
 #define TGRAD_LP_W(DT_, NTB_)                                                                            \
   do {                                                                                                   \
-    if (W == 4) TGRAD_LP_F(DT_, 4, NTB_); else if (W == 2) TGRAD_LP_F(DT_, 2, NTB_); else TGRAD_LP_F(DT_, 1, NTB_); \
+    if (W == 4 && NTB_ == 1 && tb == 5) {   /* (the shortest rows: rows_kernel_pays) */                  \
+      if (K & 1) TGRAD_LP_C(DT_, 4, 1, true, false, 1, 5); else TGRAD_LP_C(DT_, 4, 1, false, false, 1, 5); \
+    } else if (W == 4) TGRAD_LP_F(DT_, 4, NTB_); else if (W == 2) TGRAD_LP_F(DT_, 2, NTB_); else TGRAD_LP_F(DT_, 1, NTB_); \
   } while (0)
 #define TGRAD_LPF_C(DT_, CP_, TB_)                                                                       \
   do {                                                                                                   \

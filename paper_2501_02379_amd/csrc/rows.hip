@@ -471,10 +471,16 @@ unsigned rows_grid(Kern kern, int W, size_t lds, int64_t units) {
 
 }  // namespace
 
-// Extent K and rank r of the last mode.  k_rows takes all of these from k_lproj; us, k_lproj / k_rows, rows x K, r: 12288x4, 1
-// 4.6 / 4.2; 12288x33, 8 7.8 / 5.3; 229376x4, 1 9.7 / 9.0; 229376x33, 8 26 / 18; 400000x20, 5 29 / 20; 160000x65, 8 34 / 23; 640000x12,
-// 10 34 / 32; 640000x65, 16 109 / 80; 640000x33, 17 86 / 58; 640000x72, 30 288 / 113.
-bool rows_kernel_fits(int K, int r) { return K >= 2 && K <= kRowsMaxExtent && r <= kRowsMaxRank; }
+// Extent K and rank r of the last mode.
+static bool rows_kernel_fits(int K, int r) { return K >= 2 && K <= kRowsMaxExtent && r <= kRowsMaxRank; }
+
+// k_rows takes nearly all of these from k_lproj; us, k_lproj / k_rows, rows x K, r: 12288x4, 1 4.6 / 4.2; 12288x33, 8 7.8 / 5.3; 229376x4, 1
+// 9.7 / 9.0; 229376x33, 8 26 / 18; 400000x20, 5 29 / 20; 160000x65, 8 34 / 23; 640000x12, 10 34 / 32; 640000x65, 16 109 / 80; 640000x33, 17 86 / 58;
+// 640000x72, 30 288 / 113.  Not rows of up to 6 elements where they are one or two units for each wavefront of the chip, half as many
+// tiles for k_lproj (whole step: 65536x3 27.7 / 29.4, 98304x4 29.6 / 30.8, 65536x5 28.4 / 29.5, 76800x5 30.3 / 30.7; but 204800x3 40.1 / 38.8).
+bool rows_kernel_pays(int K, int r, int64_t rows) {
+  return rows_kernel_fits(K, r) && (K > 6 || rows < 1024 * kUnit || rows >= 8192 * kUnit);
+}
 
 // k_rows_update leaves ranks up to 8 of many rows to k_lupdate, which has two matrix steps of four elements for them and half as
 // many units to go around: 229376x4, r 1 7.9 / 12.6; 400000x12, r 3 18.2 / 24.0; 400000x20, r 5 27.4 / 30.0; 160000x65, r 8 34.0 / 34.7;

@@ -128,7 +128,7 @@ void launch_lupdate_fused(hipStream_t s, const float2* y1, const float2* ut, int
                           float beta1, float beta2, double inv_c1, double inv_c2, float eps, float c_lambda);
 
 // the last mode alone, on split operands (rows.hip)
-bool rows_kernel_fits(int K, int r);
+bool rows_kernel_pays(int K, int r, int64_t rows);
 bool rows_update_pays(int K, int r, int64_t rows);
 void launch_rows(hipStream_t s, const void* g, int dtype, const int32_t* omega, const uint32_t* tile_start, float2* gs,
                  const float2* U, const Stage& st, float2* out);
