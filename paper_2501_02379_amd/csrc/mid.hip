@@ -308,6 +308,52 @@ __device__ __forceinline__ void stage_split(u32v4* table, const float2* Up, int 
     d[128] = s.l;
   }
 }
+
+// The same for an expansion's whole table, in two calls: the first BATCH items of a wavefront are requested before the columns
+// of x are, so that what is needed first does not wait behind them (128x128x64x33, r 32,32,16,8: 11.3 -> 10.3 us;
+// 128x128x128x65, r 32,32,32,16: 22.6 -> 20.9).  k_mid_split waits for its first rows of x alone beside the table, and the
+// registers cost it more than the order gave (128x128x64x33, r 64,64,32,16: 31.9 -> 33 us).
+template <int BATCH>
+struct ExpandTable {
+  FactorRef U;
+  int rn, M, K, tiles, items;             // output rows and items of the table: tile + tiles * quad
+  float2 f[BATCH][4];
+  __device__ __forceinline__ ExpandTable(const float2* Up, int rn_, int M_, int K_, int m0, int tiles_, int quads)
+      : U(factor_ref(Up + (int64_t)m0 * rn_, (int64_t)(M_ - m0) * rn_)), rn(rn_), M(M_ - m0), K(K_), tiles(tiles_),
+        items(quads * tiles_) {}
+  __device__ __forceinline__ void load(int it0, int waves, int l) {
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      const int it = it0 + u * waves, q = it / tiles, m = 16 * (it - q * tiles) + (l & 15), k = 16 * q + (l >> 4);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) f[u][j] = factor_entry(U, m, k + 4 * j, rn, it < items && m < M && k + 4 * j < K);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  __device__ __forceinline__ void store(u32v4* table, int it0, int waves, int l) {
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      const int it = it0 + u * waves;
+      if (it < items) {
+        Split8 s;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) split_at(s, j, f[u][j]);
+        u32v4* d = table + it * kSplitItem + l;
+        d[0] = s.h;
+        d[64] = s.m;
+        d[128] = s.l;
+      }
+    }
+  }
+  // everything, where `load(wave, ..)` has been called
+  __device__ __forceinline__ void stage(u32v4* table, int wave, int waves, int l) {
+    store(table, wave, waves, l);
+    for (int it0 = wave + BATCH * waves; it0 < items; it0 += BATCH * waves) {
+      load(it0, waves, l);
+      store(table, it0, waves, l);
+    }
+  }
+};
 __device__ __forceinline__ Split8 split_item(const u32v4* p) { return Split8{p[0], p[64], p[128]}; }
 
 // The operands of the VEC columns of four row vectors of a lane: [column][re, im]
@@ -410,8 +456,10 @@ __global__ __launch_bounds__(64 * W) void k_expand_split(const float* __restrict
         v[q][j] = *reinterpret_cast<const V*>(xp + (int64_t)(k < K ? k : K - 1) * row);
       }
   };
+  ExpandTable<(KQ <= 2 ? 4 : 2)> tab(Up, rn, M, K, 16 * t0, nt, 0, KQ);
+  tab.load(wave, W, lane);
   fetch(nq);
-  stage_split<false>(sQ, Up, rn, M, K, 16 * t0, nt, 0, KQ, tid, 64 * W);
+  tab.stage(sQ, wave, W, lane);
   __syncthreads();
   for (int g = (int)blockIdx.x * W + wave; g < groups; g += stride) {
     const Cols cq = nq;

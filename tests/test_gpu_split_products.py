@@ -35,6 +35,14 @@ def test_middle_stages(shape, ranks, k):
     check_parity(info, W0)
 
 
+@pytest.mark.parametrize("shape,ranks,k", [
+    ((96, 100, 20, 9), (4, 40, 20, 9), 900),       # 21 items of an expansion's table: a whole batch of the wavefronts and a part
+    ((96, 200, 20, 9), (4, 20, 20, 9), 900),       # 26
+])
+def test_expansion_tables_past_the_first_requests(shape, ranks, k):
+    test_middle_stages(shape, ranks, k)
+
+
 # The core kernel: four wavefronts or eight, tiles of rank, rows in one batch or several, one group of 16 columns or several
 # for a workgroup.
 CORE_SHAPES = [
