@@ -1,6 +1,7 @@
 // Host side of the C ABI (include/tgrad.h): argument validation, the launch plan, carving of the
 // caller's state / workspace buffers, and the sequencing of kernels on the caller's stream for
 // the two branches of Algorithm 1 (refresh and step).
+#include <algorithm>
 #include <cmath>
 #include <cstddef>
 #include <cstring>
@@ -587,12 +588,12 @@ void compute_factors(tgrad_ctx* c, const void* g, const uint32_t* tile_start, co
 }
 
 // z = (G~_L before its last expansion), (A, r_N): the core `core` expanded in modes 1 .. N-1 through the
-// buffers of the raw chain.  Returns where it lies.
-const float2* raw_expand(tgrad_ctx* c, const float2* core) {
+// buffers of the raw chain.  Returns where it lies.  (`first`: how many of its expansions `core` has behind it)
+const float2* raw_expand(tgrad_ctx* c, const float2* core, int first = 0) {
   Plan& p = c->plan;
   float2* rb[2] = {c->w<float2>(p.ws_rbuf[0]), c->w<float2>(p.ws_rbuf[1])};
   const float2* src = core;
-  for (int st = 0; st + 1 < p.N; ++st) {
+  for (int st = first; st + 1 < p.N; ++st) {
     const Stage& sg = p.back[st];
     float2* dst = rb[st & 1];
     Scope sc_(c, KID_RESIDUAL);
@@ -708,8 +709,31 @@ int do_step(tgrad_ctx* c, void* weight, const void* g) {
   const double tau = (double)(c->t + 1);
   const double corr1 = 1.0 / (1.0 - std::pow((double)cf.beta1, tau)), corr2 = 1.0 / (1.0 - std::pow((double)cf.beta2, tau));
   const float inv_c1 = (float)corr1, inv_c2 = (float)corr2;
+  const int nmid = (mfma_last && p.fuse_next) ? N - 2 : N - 1;   // reconstruction stages run by k_mid
+  const bool residual = p.order == TGRAD_ORDER_LR_US && p.k > 0;
+  // Low rank first, mode 1 in k_core: the update and the compressed gradient go through the expansions that both have side by
+  // side, as one tensor of twice the leading extent, while a launch of one of them leaves the chip idle (64x64x64x32, r 13,13,
+  // 13,6, 312 groups of 16 columns: 78.3 -> 73.1 us a step; 128x128x64x33, r 32,32,16,8, 1024 groups: 224 -> 218.5; from 2048
+  // on nothing is won, and what the last kernel reads is written long before it: r 32,32,16,16 276.5 / 276.5, r 64,64,32,16,
+  // 4096, 411.5 / 416).  They lie where a refresh keeps the residual, if they fit.
+  float2* pair[2] = {nullptr, nullptr};
+  if (residual && p.fuse_core && !p.fuse_core2 && nmid > 1) {
+    constexpr int64_t kPairColumns = 2048 * 16;
+    int64_t most[2] = {0, 0}, columns = 0;                     // complex numbers of the two that a launch writes
+    for (int st = 0; st < nmid; ++st) {
+      const Stage& sg = p.back[st];
+      most[st & 1] = std::max(most[st & 1], sg.A * sg.M * sg.B * 2);
+      columns = std::max(columns, sg.A * sg.B);
+    }
+    most[0] = (most[0] + 31) & ~(int64_t)31;
+    if (columns < kPairColumns && most[0] + most[1] <= p.I) {
+      pair[0] = c->w<float2>(p.ws_resid);
+      pair[1] = pair[0] + most[0];
+    }
+  }
   const float2* zsrc = core_n;
-  int first_back = 0;
+  int first_back = 0, raw_first = 0;
+  const float2* raw = core_g;
   if (p.fuse_core2) {
     // the last two compression stages, AdamUpdate on the core and the first two reconstruction stages
     Scope sc_(c, KID_CORE);
@@ -723,8 +747,8 @@ int do_step(tgrad_ctx* c, void* weight, const void* g) {
     const Stage& sg = p.proj[N - 1];
     Scope sc_(c, KID_CORE);
     launch_core(s, src, c->st<float2>(p.st_U[0]), p.rank[0], sg.K, sg.M, sg.B, c->st<float2>(p.st_ml),
-                c->st<float>(p.st_vl), core_g, cf.beta1, cf.beta2, inv_c1, inv_c2, cf.eps, last);
-    zsrc = last;
+                c->st<float>(p.st_vl), core_g, cf.beta1, cf.beta2, inv_c1, inv_c2, cf.eps, pair[1] ? pair[0] : last);
+    zsrc = pair[1] ? pair[0] : last;
     first_back = 1;
   } else {
     Scope sc_(c, KID_ADAM_CORE);
@@ -734,15 +758,32 @@ int do_step(tgrad_ctx* c, void* weight, const void* g) {
 
   // low rank first: the sparse part works on the residual of the low-rank approximation of THIS
   // gradient: g_S <- g_S - (g_L x_1 U1 ... x_N UN)[Omega]
-  if (p.order == TGRAD_ORDER_LR_US && p.k > 0) {
-    const float2* z = raw_expand(c, core_g);
+  if (pair[1]) {
+    const Stage& s0 = p.back[0];
+    const int64_t n0 = s0.A * s0.M * s0.B;
+    {
+      Scope sc_(c, KID_RESIDUAL);
+      launch_mid(s, core_g, c->st<float2>(p.st_U[s0.mode]), p.rank[s0.mode], false, s0, pair[0] + n0);
+    }
+    for (int st = 1; st < nmid; ++st) {
+      Stage two = p.back[st];
+      two.A *= 2;
+      Scope sc_(c, KID_BACKPROJECT);
+      launch_mid(s, pair[(st & 1) ^ 1], c->st<float2>(p.st_U[two.mode]), p.rank[two.mode], false, two, pair[st & 1]);
+    }
+    const Stage& sn = p.back[nmid - 1];
+    zsrc = pair[(nmid - 1) & 1];
+    raw = zsrc + sn.A * sn.M * sn.B;
+    first_back = raw_first = nmid;
+  }
+  if (residual) {
+    const float2* z = raw_expand(c, raw, raw_first);
     Scope sc_(c, KID_RESIDUAL);
     launch_residual_gather(s, gs, omega, p.k, z, c->st<float2>(p.st_U[N - 1]), p.rank[N - 1], (int)p.shape[N - 1]);
   }
 
   // D <- alpha (N_L x_1 U1 ... x_N UN); the last stage is fused with AdamUpdate on the sparse values,
   // D[Omega] += lambda N_S and W <- W (1 - lr wd) - lr D
-  const int nmid = (mfma_last && p.fuse_next) ? N - 2 : N - 1;   // reconstruction stages run by k_mid
   for (int st = first_back; st < nmid; ++st) {
     const Stage& sg = p.back[st];
     float2* dst = buf[(N - 2 - st) & 1];
