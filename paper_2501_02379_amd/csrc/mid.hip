@@ -456,7 +456,7 @@ __global__ __launch_bounds__(64 * W) void k_expand_split(const float* __restrict
         v[q][j] = *reinterpret_cast<const V*>(xp + (int64_t)(k < K ? k : K - 1) * row);
       }
   };
-  ExpandTable<(KQ <= 2 ? 4 : 2)> tab(Up, rn, M, K, 16 * t0, nt, 0, KQ);
+  ExpandTable<(KQ <= 2 ? 4 : 2)> tab(Up, rn, M, K, 16 * t0, nt, KQ);
   tab.load(wave, W, lane);
   fetch(nq);
   tab.stage(sQ, wave, W, lane);
