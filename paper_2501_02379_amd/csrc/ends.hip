@@ -16,7 +16,7 @@
 //   first pass 64x64x32x17 15.7 -> 9.9 -> 9, 32x32x32x32x17 (bf16) 84.5 -> 34.8 -> 24, 128x128x64x33 91.7 -> 56 -> 55 (5.0 TB/s;
 //   its loads alone 52.6), bf16 87.7 -> 46 -> 35, r 32,16 102 (32 x 32) -> 73, 128x128x128x65 243 (32 x 32) -> 222;
 //   last pass 128x128x64x33 112 -> 108 -> 105 (5.3 TB/s), bf16 weights 98 -> 66 -> 60, r 32,16 140 (32 x 32) -> 109,
-//   90x77x45x23 10.6 + 26.8 -> 28 -> 26.5, 128x128x128x65 434 (32 x 32) -> 440.
+//   90x77x45x23 10.6 + 26.8 -> 28 -> 26.5, 128x128x128x65 434 (32 x 32) -> 440, slabs shared 426.
 //
 // Lanes: g = lane / 16, c = lane % 16.  A[i = c][k = g], B[k = g][j = c], D register r: D[i = 4 g + r][j = c].
 // Real columns are (m, p) = (re, im) parts interleaved: c = 2 m + p.
