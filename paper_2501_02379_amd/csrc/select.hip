@@ -107,6 +107,12 @@ __global__ __launch_bounds__(kSelThreads) void k_select_hist(const KeySource g, 
     if (h[b]) atomicAdd(&hist[b], h[b]);
 }
 
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
+  return v;
+}
+
 // The bin of a digit's histogram that holds the `want`-th largest entry, and how many are to be taken inside it, by one
 // workgroup; every thread gets both.
 struct Picked {
@@ -145,15 +151,24 @@ __device__ __forceinline__ Picked pick_bin(const uint32_t* __restrict__ hist, ui
   return found;
 }
 
-// The first digit.  |g|^2 = inf or NaN has all exponent bits set: leading 12-bit digit 0x7F8 or above.
+// The first digit, and how many entries have a |g|^2 that is infinite or NaN: all exponent bits set, the sign bit either way
+// (a NaN keeps the sign it came with), so leading 12-bit digit 0x7F8 or above.  `write` is the same for a whole workgroup.
 __device__ __forceinline__ Picked pick_first(uint32_t k, SelectScalars* sc, const uint32_t* __restrict__ hist, bool write) {
+  __shared__ uint32_t nonfinite[kWavesPerBlock];
   const Picked p = pick_bin<kHistBins>(hist, k);
-  if (write && threadIdx.x == 0) {
-    sc->prefix[0] = p.bin;
-    sc->remaining[0] = p.remaining;
+  if (write) {
     uint32_t n = 0;
-    for (int b = 0x7F8; b < 0x800; ++b) n += hist[b];
-    sc->nonfinite = n;
+    for (int b = 0x7F8 + threadIdx.x; b < kHistBins; b += kSelThreads) n += hist[b];
+    n = wave_sum(n);
+    if (lane_id() == 0) nonfinite[threadIdx.x / kWave] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      sc->prefix[0] = p.bin;
+      sc->remaining[0] = p.remaining;
+      n = 0;
+      for (int w = 0; w < kWavesPerBlock; ++w) n += nonfinite[w];
+      sc->nonfinite = n;
+    }
   }
   return p;
 }
@@ -255,12 +270,6 @@ __global__ __launch_bounds__(kSelThreads) void k_select_hist_cand(const KeySourc
   __syncthreads();
   for (int b = threadIdx.x; b < kHistBins; b += kSelThreads)
     if (h[b]) atomicAdd(&hist[b], h[b]);
-}
-
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-  return v;
 }
 
 // Candidate bits of one mask word sorted by their key against the threshold T.
