@@ -149,7 +149,10 @@ typedef struct {
  *  state_bytes     host pointer, out: persistent optimizer state (Omega as int32, M_S, V_S, M_L,
  *                  V_L, U^(n); the quantity the paper's memory model counts).
  *  workspace_bytes host pointer, out: scratch that carries nothing from one step to the next
- *                  except kernel-ready copies of the factors and the support bitmask.
+ *                  except the support's bitmask and offsets and kernel-ready copies of the factors
+ *                  (a refresh writes all of them anew), what tgrad_get_state and tgrad_check report
+ *                  of the last call, and, for orders other than TGRAD_ORDER_US_LR, a table of zeros
+ *                  that tgrad_init writes.
  * Errors: INVALID_ARG, UNSUPPORTED.
  */
 int tgrad_query_sizes(const tgrad_config* cfg, size_t* state_bytes, size_t* workspace_bytes);

@@ -335,8 +335,7 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, int lane) {
 // a group of 64, bits ascending inside a word) and writes every selected index to its final slot.
 // `sure` comes in as the mask of the entries whose leading digit lies above the picked bin and goes
 // out as the support bitmask (those, the candidates above T and the first need_eq candidates equal
-// to T).  A workgroup adds up the counts of all chunks before its own (at most some 4000: select_chunk_words), and the
-// histograms, which nobody reads any more, are left zero for the next selection.
+// to T).  A workgroup adds up the counts of all chunks before its own (at most some 4000: select_chunk_words).
 template <int DT>
 __global__ __launch_bounds__(kSelThreads) void k_select_emit(const KeySource g,
                                                              const SelectScalars* __restrict__ sc,
@@ -344,13 +343,10 @@ __global__ __launch_bounds__(kSelThreads) void k_select_emit(const KeySource g,
                                                              const uint32_t* __restrict__ chunk_eq,
                                                              int64_t nchunks, uint32_t* __restrict__ sure,
                                                              const uint32_t* __restrict__ cand, int64_t nwords,
-                                                             int chunk_words, uint32_t* __restrict__ hist,
-                                                             int32_t* __restrict__ omega) {
+                                                             int chunk_words, int32_t* __restrict__ omega) {
   __shared__ uint32_t before[2][kWavesPerBlock];
   const int lane = lane_id(), wave = threadIdx.x / kWave;
   const int64_t chunk0 = (int64_t)blockIdx.x * kWavesPerBlock, chunk = chunk0 + wave;
-  for (int64_t b = (int64_t)blockIdx.x * kSelThreads + threadIdx.x; b < 3 * kHistBins; b += (int64_t)gridDim.x * kSelThreads)
-    hist[b] = 0u;
   uint32_t run_gt = 0, run_eq = 0;                   // entries before this chunk
 #pragma unroll 4
   for (int64_t c = threadIdx.x; c < chunk0; c += kSelThreads) {
@@ -517,8 +513,8 @@ void launch_select_hist(hipStream_t s, const void* g, int dtype, const SelectKey
 }
 
 // The pick of the first digit in a launch of its own (4.7 us) where there are more workgroups of k_select_split than fit the chip
-// at a time: below that each has it done before its first key arrives (refresh of 64x64x32x17: 218 -> 207 us with the other
-// picks, the sums over chunks and the zeroing of histograms inside other launches, five fewer).
+// at a time: below that each has it done before its first key arrives (refresh of 64x64x32x17: 218 -> 210 us with the other
+// picks and the sums over chunks inside other launches, four fewer).
 bool select_pick_apart(int64_t I) { return (I + kSegElems * kWavesPerBlock - 1) / (kSegElems * kWavesPerBlock) > 2048; }
 
 void launch_select_pick(hipStream_t s, uint32_t k, SelectScalars* sc, const uint32_t* hist) {
@@ -562,12 +558,12 @@ void launch_select_count(hipStream_t s, const void* g, int dtype, const SelectKe
 
 void launch_select_emit(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I,
                         const SelectScalars* sc, const uint32_t* chunk_gt, const uint32_t* chunk_eq,
-                        int64_t nchunks, uint32_t* sure, const uint32_t* cand, uint32_t* hist, int32_t* omega) {
+                        int64_t nchunks, uint32_t* sure, const uint32_t* cand, int32_t* omega) {
   const int64_t nwords = (I + 31) / 32;
   unsigned grid = (unsigned)((nchunks + kWavesPerBlock - 1) / kWavesPerBlock);
   const KeySource src{g, keys.s0, keys.s1};
   TGRAD_SEL_DISPATCH(k_select_emit, grid, kSelThreads, src, sc, chunk_gt, chunk_eq, nchunks, sure, cand, nwords,
-                     select_chunk_words(I), hist, omega);
+                     select_chunk_words(I), omega);
 }
 #undef TGRAD_SEL_DISPATCH
 

@@ -354,7 +354,6 @@ struct tgrad_ctx {
   bool have_indices;
   bool have_factor[kMaxNdim];
   bool have_hist;                 // the last refresh has counted its gradient's non-finite entries
-  bool hist_zero;                 // the selection's histograms are zero when a refresh begins
   int launch_status;              // first failed kernel launch of the current call (TGRAD_OK = none)
   bool profiling;
   std::vector<EventPair> events;
@@ -474,8 +473,8 @@ void select_support(tgrad_ctx* c, const void* x, int dt) {
     keys.s1 = (uint32_t)(seed >> 32) + t32 + 0x7F4A7C15u;
   }
   if (p.k > 0) {
-    // the histograms are zero between selections (k_select_emit leaves them so), unless a launch has failed
-    if (!c->hist_zero) zero_u32(s, hist, 3 * kHistBins);
+    // (here, and not by the last kernel of the selection before: the workspace is the caller's between calls)
+    zero_u32(s, hist, 3 * kHistBins);
     // two streaming passes over x: leading-digit histogram, then the two bitmasks
     { Scope sc_(c, KID_SEL_HIST); launch_select_hist(s, x, dt, keys, p.I, hist); }
     if (select_pick_apart(p.I)) { Scope sc_(c, KID_SEL_PICK); launch_select_pick(s, (uint32_t)p.k, sc, hist); }
@@ -486,8 +485,7 @@ void select_support(tgrad_ctx* c, const void* x, int dt) {
       launch_select_hist_cand(s, x, dt, keys, p.I, pass, sc, cand, hist + pass * kHistBins);
     }
     { Scope sc_(c, KID_SEL_COUNT); launch_select_count(s, x, dt, keys, p.I, sc, hist + 2 * kHistBins, mask, cand, chunk_gt, chunk_eq, p.nchunks); }
-    { Scope sc_(c, KID_SEL_EMIT); launch_select_emit(s, x, dt, keys, p.I, sc, chunk_gt, chunk_eq, p.nchunks, mask, cand, hist, omega); }
-    if (c->launch_status != TGRAD_OK) c->hist_zero = false;
+    { Scope sc_(c, KID_SEL_EMIT); launch_select_emit(s, x, dt, keys, p.I, sc, chunk_gt, chunk_eq, p.nchunks, mask, cand, omega); }
   }
   c->have_hist = p.k > 0 && !keys.random;
   tile_offsets(c);
@@ -937,7 +935,6 @@ int tgrad_init(tgrad_ctx** out, const tgrad_config* cfg, void* state_dev, void* 
   c->have_indices = false;
   for (int n = 0; n < kMaxNdim; ++n) c->have_factor[n] = false;
   c->have_hist = false;
-  c->hist_zero = true;
   c->launch_status = TGRAD_OK;
   c->profiling = false;
   for (int i = 0; i < KID_COUNT; ++i) {
@@ -946,7 +943,6 @@ int tgrad_init(tgrad_ctx** out, const tgrad_config* cfg, void* state_dev, void* 
   }
   // no solve has hit its sweep limit yet (a factor injected with tgrad_set_state never does)
   zero_u32(c->stream, c->w<uint32_t>(c->plan.ws_eig_status), 4 * kMaxNdim);
-  zero_u32(c->stream, c->w<uint32_t>(c->plan.ws_hist), 3 * kHistBins);
   // moments <- 0 (and everything else in the state block), with a fill kernel
   zero_u32(c->stream, reinterpret_cast<uint32_t*>(c->state), (int64_t)(c->plan.state_bytes / 4));
   if (c->plan.order != TGRAD_ORDER_US_LR)
@@ -1006,7 +1002,6 @@ int tgrad_step_static(const tgrad_config* cfg, void* state_dev, int64_t t, void*
   c.have_indices = true;                                          // the caller's contract for t % T != 0
   for (int n = 0; n < kMaxNdim; ++n) c.have_factor[n] = true;
   c.have_hist = false;
-  c.hist_zero = false;               // (scratch of all calls)
   c.launch_status = TGRAD_OK;
   c.profiling = false;
   if (error_pending_on_entry()) return TGRAD_ERR_HIP;

@@ -66,7 +66,7 @@ void launch_select_count(hipStream_t s, const void* g, int dtype, const SelectKe
                          uint32_t* chunk_gt, uint32_t* chunk_eq, int64_t nchunks);
 void launch_select_emit(hipStream_t s, const void* g, int dtype, const SelectKeys& keys, int64_t I,
                         const SelectScalars* sc, const uint32_t* chunk_gt, const uint32_t* chunk_eq,
-                        int64_t nchunks, uint32_t* sure, const uint32_t* cand, uint32_t* hist, int32_t* omega);
+                        int64_t nchunks, uint32_t* sure, const uint32_t* cand, int32_t* omega);
 void launch_mask_from_indices(hipStream_t s, const int32_t* omega, int64_t k, uint32_t* mask,
                               int64_t mask_words);
 

@@ -28,3 +28,30 @@ def test_check_counts_nan_of_either_sign(shape, ranks):
         ctx.tgrad_refresh_factors(T.to_device_grad(g))
         assert ctx.tgrad_check() == 7
     ctx.tgrad_destroy()
+
+
+@pytest.mark.parametrize("shape,ranks,rule", [
+    ((16, 16, 8, 5), (8, 8, 4, 3), T.TGRAD_SELECT_TOPK_MAG), ((40, 30, 13, 9), (9, 7, 5, 3), T.TGRAD_SELECT_TOPK_MAG),
+    ((40, 30, 13, 9), (9, 7, 5, 3), T.TGRAD_SELECT_RANDOM), ((20, 16, 36, 20), (5, 4, 34, 18), T.TGRAD_SELECT_TOPK_MAG)])
+def test_refresh_reads_nothing_that_an_earlier_call_left(shape, ranks, rule):
+    """Refreshing at every step, a context may find anything in its workspace: another one's scratch, or a fill."""
+    import torch
+    print("[case] workspace", shape, rule, flush=True)
+    k = int(np.prod(shape)) // 50
+    kw = dict(refresh_every=1, lr=2e-3, select_rule=rule, select_seed=5)
+    ctx, ref = (make_gpu_ctx(T, shape, ranks, k, **kw) for _ in range(2))
+    W0 = synth.small_case(shape, 40) * np.float32(0.02)
+    w, wref = T.to_device_weight(W0), T.to_device_weight(W0)
+    rng = np.random.default_rng(6)
+    for t, fill in enumerate((0x00, 0xFF, 0x01, None, 0x7F)):
+        g = T.to_device_grad(synth.small_case(shape, 50 + t, outlier_frac=(1, 100)))
+        if fill is None:
+            ctx.ws_buf.copy_(torch.from_numpy(rng.integers(0, 256, ctx.ws_buf.numel(), dtype=np.uint8)))
+        else:
+            ctx.ws_buf.fill_(fill)
+        ctx.tgrad_step(w, g)
+        ref.tgrad_step(wref, g)
+        assert np.array_equal(ctx.tgrad_get_state(T.STATE_INDICES), ref.tgrad_get_state(T.STATE_INDICES)), fill
+        assert torch.equal(ctx.state_buf, ref.state_buf) and torch.equal(w, wref), fill
+    ctx.tgrad_destroy()
+    ref.tgrad_destroy()
