@@ -335,7 +335,8 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, int lane) {
 // a group of 64, bits ascending inside a word) and writes every selected index to its final slot.
 // `sure` comes in as the mask of the entries whose leading digit lies above the picked bin and goes
 // out as the support bitmask (those, the candidates above T and the first need_eq candidates equal
-// to T).  A workgroup adds up the counts of all chunks before its own (at most some 4000: select_chunk_words).
+// to T).  A workgroup adds up the counts of all chunks before its own (up to 138 M numbers at most some 4000:
+// select_chunk_words).
 template <int DT>
 __global__ __launch_bounds__(kSelThreads) void k_select_emit(const KeySource g,
                                                              const SelectScalars* __restrict__ sc,
@@ -539,10 +540,12 @@ void launch_select_hist_cand(hipStream_t s, const void* g, int dtype, const Sele
 }
 
 // Mask words per chunk, the run one wavefront walks in order: as few as keep the counts, which every workgroup of
-// k_select_emit adds up, at a few thousand (64x64x32x17 in runs of 1024 words, 17 workgroups: count and emit 19 us each, in runs of 64 words 5).
+// k_select_emit adds up, at a few thousand (64x64x32x17 in runs of 1024 words, 17 workgroups: count and emit 19 us each, in runs
+// of 64 words 5), but not more than 1024: the chains of longer runs cost more than more counts to add up do (143 M numbers, runs
+// of 2048 / of 1024: count and emit 131 / 81 us; 1.07 G, 8192 / 1024, 32768 counts: 720 / 520; 2.1 G: 1380 / 1070).
 int select_chunk_words(int64_t I) {
   int words = kWave;
-  while (I > (int64_t)words * 32 * 4224) words *= 2;
+  while (words < 1024 && I > (int64_t)words * 32 * 4224) words *= 2;
   return words;
 }
 

@@ -55,3 +55,27 @@ def test_refresh_reads_nothing_that_an_earlier_call_left(shape, ranks, rule):
         assert torch.equal(ctx.state_buf, ref.state_buf) and torch.equal(w, wref), fill
     ctx.tgrad_destroy()
     ref.tgrad_destroy()
+
+
+def test_support_where_a_wavefront_walks_the_longest_run():
+    """143 M numbers: runs of 1024 words of the masks, more of them than the 4224 that shorter runs are limited to; keys of
+    bf16 numbers, so that entries equal to the last one taken are many."""
+    import torch
+    shape, ranks = (256, 256, 64, 34), (256, 256, 2, 2)
+    print("[case] long runs", shape, flush=True)
+    k = 100_003
+    g = torch.randn(shape + (2,), generator=torch.Generator(device="cuda:0").manual_seed(3), device="cuda:0").bfloat16()
+    ctx = make_gpu_ctx(T, shape, ranks, k, grad_dtype=T.TGRAD_CBF16, refresh_every=0)
+    ctx.tgrad_refresh_factors(g)
+    got = torch.from_numpy(ctx.tgrad_get_state(T.STATE_INDICES)).to("cuda:0")
+    ctx.tgrad_destroy()
+    del ctx
+    re, im = g.view(-1, 2).unbind(1)
+    key = re.float().square_()
+    key += im.float().square_()
+    least = key.topk(k).values[-1]
+    above = (key > least).nonzero().reshape(-1)
+    equal = (key == least).nonzero().reshape(-1)
+    assert equal.numel() > k - above.numel() > 0           # (a tie that the lower index decides)
+    want = torch.cat((above, equal[:k - above.numel()])).sort().values
+    assert torch.equal(got, want)
