@@ -9,7 +9,9 @@
 // The 32 x 32 kernels on float32 instructions (contract_mfma.hip), which have the longer rows, take units of 32 rows - two or three
 // rounds of them for the wavefronts of a layer of a few million numbers - with 17 KB of LDS each and pad a rank of 18 to 32.
 // Whole steps, us, with those / with these: 43x43x74x38, r 21,21,36,18 129 / 95, 24x24x128x65, r 8,8,40,32 128 / 92, 64x64x64x64,
-// r 20,20,20,20 221 / 141, in bf16 50x50x64x64, r 10,10,20,32 152 / 93 (rows_kernel_fits has the kernels alone).
+// r 20,20,20,20 221 / 141, in bf16 50x50x64x64, r 10,10,20,32 152 / 93 (rows_kernel_pays and rows_update_pays have the kernels
+// alone).  Relative error against 64 bits, those / these: k_rows with rows of 4, 16 and 72 elements 5.5e-8 / 3.9e-8, 1.0e-7 / 4.5e-8 and
+// 2.2e-7 / 7.3e-8; k_rows_update with ranks 4, 16, 20 and 32 5.4e-8 / 4.3e-8, 1.0e-7 / 4.4e-8, 1.15e-7 / 1.12e-7 and 1.44e-7 / 9.6e-8.
 //
 // Lanes: g = lane / 16, c = lane % 16; slot 2 j + p of lane (c, g) is part p of element 16 quad + 4 j + g of row or column c;
 // register r of a result is row 4 g + r, column c; real columns are (m, p) = (re, im) parts interleaved.
@@ -485,8 +487,12 @@ bool rows_kernel_pays(int K, int r, int64_t rows) {
 // k_rows_update leaves ranks up to 8 of many rows to k_lupdate, which has two matrix steps of four elements for them and half as
 // many units to go around: 229376x4, r 1 7.9 / 12.6; 400000x12, r 3 18.2 / 24.0; 400000x20, r 5 27.4 / 30.0; 160000x65, r 8 34.0 / 34.7;
 // but 640000x12, r 10 38.8 / 36.8; 640000x24, r 9 58 / 51; 640000x65, r 16 136 / 127; 640000x33, r 17 101 / 77; 640000x72, r 30 350 /
-// 153; and with a wavefront for every unit 12288x4, r 1 4.3 / 3.9; 12288x24, r 6 5.8 / 4.8.
-bool rows_update_pays(int K, int r, int64_t rows) { return rows_kernel_fits(K, r) && (r > 8 || rows < 1024 * kUnit); }
+// 153; and with a wavefront for every unit 12288x24, r 6 5.8 / 4.8.  Ranks 1 and 2 stay there in any number (12288x4, r 1 4.3 /
+// 3.9): what the six products of three parts leave out is more than two or four float32 multiply-adds round off (relative error
+// 3.1e-8 / 4.4e-8 at 2 columns of rank 1, 3.9e-8 / 4.1e-8 at 4 of rank 2; from rank 3 on 4.7e-8 / 4.2e-8 and less).
+bool rows_update_pays(int K, int r, int64_t rows) {
+  return rows_kernel_fits(K, r) && (r > 8 || (r > 2 && rows < 1024 * kUnit));
+}
 
 void launch_rows(hipStream_t s, const void* g, int dtype, const int32_t* omega, const uint32_t* tile_start, float2* gs,
                  const float2* U, const Stage& st, float2* out) {

@@ -5,7 +5,7 @@ from __future__ import annotations
 import numpy as np
 import pytest
 
-from helpers import check_parity, run_both, run_both_bf16_weights
+from helpers import check_parity, make_gpu_ctx, run_both, run_both_bf16_weights
 from oracle import tgrad_oracle as O
 from paper_2501_02379_amd import synth, tgrad as T
 
@@ -71,3 +71,50 @@ def test_rows_in_the_other_orders(order):
     info = run_both(T, shape, ranks, 120, grads, W0, refresh_every=3, lr=2e-3, order=order)
     assert all(info["omega_equal"])
     check_parity(info, W0)
+
+
+def _float32_products(x, c):
+    """Rows of x times c (complex) by chains of float32 multiply-adds, one rounding each."""
+    parts = []
+    for a, b in (((1, c.real), (-1, c.imag)), ((1, c.imag), (1, c.real))):
+        acc = np.zeros((x.shape[0], c.shape[1]), np.float32)
+        for k in range(x.shape[1]):
+            for (sign, f), v in ((a, x[:, k].real), (b, x[:, k].imag)):
+                acc = (acc + sign * v.astype(np.float64)[:, None] * f[k].astype(np.float64)).astype(np.float32)
+        parts.append(acc)
+    return parts[0] + 1j * parts[1]
+
+
+@pytest.mark.parametrize("K,r", [(2, 1), (3, 1), (4, 1), (4, 2), (5, 2), (3, 3), (8, 2), (8, 4), (16, 3), (16, 16), (17, 9),
+                                 (20, 20), (24, 18), (33, 32), (72, 20)])
+def test_no_further_from_64_bits_than_float32_multiply_adds(K, r):
+    """Both products of the last mode alone: modes 1 and 2 are left as they are (identity factors, whose products are exact), the
+    update divides by 1 (V = 0, eps = 1, no gradient) and starts from zero weights.  3 %: three times what the error of some
+    8000 rounded numbers scatters, and the order of a sum moves less."""
+    print("[case] rows, error", K, r, flush=True)
+    shape, ranks = (32, 64, K), (32, 64, r)
+    rng = np.random.default_rng(100 * K + r)
+    g, m = ((rng.standard_normal(s) + 1j * rng.standard_normal(s)).astype(np.complex64) for s in (shape, ranks))
+    U = np.linalg.qr(rng.standard_normal((K, r)) + 1j * rng.standard_normal((K, r)))[0].astype(np.complex64)
+
+    def step(grad, core_m):
+        ctx = make_gpu_ctx(T, shape, ranks, 0, lr=1.0, beta1=0.5, beta2=0.5, eps=1.0, refresh_every=0)
+        ctx.tgrad_set_state(T.STATE_STEP, 1000)
+        ctx.tgrad_set_state(T.STATE_INDICES, np.zeros(0))
+        for n, u in enumerate((np.eye(32), np.eye(64), U)):
+            ctx.tgrad_set_state(T.STATE_FACTOR0 + n, u)
+        ctx.tgrad_set_state(T.STATE_CORE_M, core_m)
+        w = T.to_device_weight(np.zeros(shape, np.complex64))
+        ctx.tgrad_step(w, T.to_device_grad(grad))
+        core = ctx.tgrad_get_state(T.STATE_CORE_G)
+        ctx.tgrad_destroy()
+        return core, T.weight_to_host(w)
+
+    def error(got, x, c):
+        want = x.astype(np.complex128) @ c.astype(np.complex128)
+        return np.linalg.norm(got.reshape(want.shape) - want) / np.linalg.norm(want)
+
+    x = g.reshape(-1, K)
+    assert error(step(g, np.zeros(ranks))[0], x, U.conj()) <= 1.03 * error(_float32_products(x, U.conj()), x, U.conj())
+    x = (np.float32(-0.5) * m).reshape(-1, r)              # what the core's half of M is expanded from
+    assert error(step(np.zeros(shape, np.complex64), m)[1], x, U.T) <= 1.03 * error(_float32_products(x, U.T), x, U.T)
