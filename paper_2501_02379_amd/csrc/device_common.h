@@ -39,11 +39,14 @@ __device__ __forceinline__ void load_pair(const void* g, int64_t p, float2& e0, 
   }
 }
 
-// Selection key |g|^2 = fl(fl(re*re) + fl(im*im)) in float32, one rounding per operation (the
-// _rn intrinsics are never contracted into a fused multiply-add).  Non-negative floats order
-// like their bit patterns, so the key is compared as an unsigned integer.
+// Selection key |g|^2 = fl(fl(re*re) + fl(im*im)) in float32, one rounding per operation: contraction into a fused multiply-add
+// is switched off here (it is the compiler's default, also for __fmul_rn and __fadd_rn, which are plain operators; a key with the
+// first square unrounded differs in the last bit for a sixth of all numbers, and ties and the last entries taken went by that).
+// Non-negative floats order like their bit patterns, so the key is compared as an unsigned integer.
 __device__ __forceinline__ uint32_t select_key(float2 e) {
-  return __float_as_uint(__fadd_rn(__fmul_rn(e.x, e.x), __fmul_rn(e.y, e.y)));
+#pragma clang fp contract(off)
+  const float rr = e.x * e.x, ii = e.y * e.y;
+  return __float_as_uint(rr + ii);
 }
 
 // Entries of a factor (row-major complex), zero where `in` is false: through a range-checked buffer, so that nothing

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from helpers import make_gpu_ctx
+from oracle import tgrad_oracle as O
 from paper_2501_02379_amd import synth, tgrad as T
 
 pytestmark = pytest.mark.gpu
@@ -79,3 +80,34 @@ def test_support_where_a_wavefront_walks_the_longest_run():
     assert equal.numel() > k - above.numel() > 0           # (a tie that the lower index decides)
     want = torch.cat((above, equal[:k - above.numel()])).sort().values
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("shape", [(16, 16, 8, 5), (31, 24, 5, 9)])
+def test_equal_keys_go_by_index(shape):
+    """Numbers on a circle whose |g|^2 = fl(fl(re re) + fl(im im)) is the same float32: with the first square unrounded it is not."""
+    print("[case] equal keys", shape, flush=True)
+    rng = np.random.default_rng(17)
+    n = int(np.prod(shape))
+    a = rng.uniform(0, 2 * np.pi, 40 * n)
+    z = (np.sqrt(2.4) * np.exp(1j * a)).astype(np.complex64)
+    key = O.selection_key(z)
+    z = z[key == np.float32(2.4)][:n]
+    assert z.size == n
+    fused = (z.real.astype(np.float64) ** 2 + np.multiply(z.imag, z.imag, dtype=np.float32)).astype(np.float32)
+    assert np.unique(fused).size > 1
+    ctx = make_gpu_ctx(T, shape, shape, n // 3, refresh_every=0)
+    ctx.tgrad_refresh_factors(T.to_device_grad(z.reshape(shape)))
+    assert np.array_equal(ctx.tgrad_get_state(T.STATE_INDICES), np.arange(n // 3))
+    ctx.tgrad_destroy()
+
+
+def test_last_entry_of_many():
+    """8 M numbers, 800 979 of them in the support, the last two with one key between them: the lower index has it."""
+    shape = (59, 59, 59, 39)
+    print("[case] last entry", shape, flush=True)
+    g = synth.small_case(shape, 710, outlier_frac=(1, 100))
+    k = int(np.ceil(0.1 * g.size))
+    ctx = make_gpu_ctx(T, shape, (2, 2, 2, 2), k, refresh_every=0)
+    ctx.tgrad_refresh_factors(T.to_device_grad(g))
+    assert np.array_equal(ctx.tgrad_get_state(T.STATE_INDICES), O.sparse_indices(g, k))
+    ctx.tgrad_destroy()
