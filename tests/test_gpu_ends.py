@@ -55,6 +55,30 @@ def test_end_kernels_bf16_weights(shape, ranks, k, dt):
         assert frac <= max(5e-3, 2.0 / (2 * int(np.prod(shape))))
 
 
+# shape, ranks: slabs that two or four wavefronts of the last kernel walk together, more of them than it has wavefronts for at a
+# time (2 to 4 workgroups of 4 a compute unit), in numbers that do not divide the grid; the last tile of every slab is a partial one
+SHARED_SLABS = [
+    ((46, 46, 126, 20), (3, 4, 5, 6)),                  # four wavefronts, four tiles of 32 rows
+    ((46, 45, 115, 33), (3, 4, 16, 8)),                 # ... lone last column
+    ((46, 46, 61, 40), (3, 4, 9, 12)),                  # ... tiles of 16 rows, two operands of the last rank
+    ((51, 51, 125, 34), (3, 4, 6, 10)),                 # ... eight tiles
+    ((46, 46, 63, 20), (3, 4, 5, 6)),                   # two wavefronts, two tiles
+    ((46, 46, 63, 34), (3, 4, 20, 8)),                  # ... four tiles, two operands of mode N-1's rank
+    ((51, 51, 95, 34), (3, 4, 20, 10)),                 # ... six tiles
+]
+
+
+@pytest.mark.parametrize("shape,ranks", SHARED_SLABS)
+def test_slabs_walked_by_several_wavefronts(shape, ranks):
+    print("[case] shared slabs", shape, ranks, flush=True)
+    grads = [synth.small_case(shape, 320 + t, outlier_frac=(1, 100)) for t in range(2)]
+    rng = np.random.default_rng(8)
+    W0 = ((rng.standard_normal(shape) + 1j * rng.standard_normal(shape)) * 0.02).astype(np.complex64)
+    info = run_both(T, shape, ranks, int(np.prod(shape)) // 40, grads, W0, refresh_every=3, lr=2e-3, weight_decay=0.01)
+    assert all(info["omega_equal"])
+    check_parity(info, W0)
+
+
 # shape, ranks, fused: modes N-1 and N in one pass (False: separate kernels, 8192 slabs or more of few rows)
 SHORT_SLABS = [
     ((91, 90, 4, 5), (9, 8, 2, 2), True),               # 8190 slabs

@@ -25,11 +25,18 @@ SHAPES = [
     ((6, 13, 57), (3, 5, 17), 0.05),                    # nine pieces
     ((5, 9, 69), (3, 4, 24), 0.02), ((5, 9, 72), (3, 4, 32), 0.2),
     ((5, 9, 73), (3, 4, 18), 0.02),                     # longer rows: the 32 x 32 kernels
-    ((33, 31, 17, 33), (4, 5, 6, 17), 0.01),            # several units per wavefront, the last of 15 rows and an odd count
+    ((33, 31, 17, 33), (4, 5, 6, 17), 0.01),            # workgroups of 4 wavefronts, a unit each; the last of 15 rows and an odd count
     ((40, 30, 40, 24), (4, 5, 34, 9), 0.01),            # rank 9 of many rows
     ((40, 30, 40, 12), (4, 5, 34, 8), 0.01),            # rank 8 of many rows: the update of the 32 x 32 kernels
     ((20, 20, 40, 13), (4, 5, 34, 6), 0.05),            # 16000 rows: a wavefront for every unit
 ]
+
+# The same where every wavefront takes more than three units: both sets of registers, each of them requested again, and support
+# ranges, rows of z and LDS slices handed on.  256 compute units hold what LDS has room for: 3 workgroups of 4 wavefronts at rows
+# of 39 and rank 20 (4 with bf16 gradients), 2 (3) at 55 and 17, one of 8 (2 of 4) from 69 on.  More than 64 entries of the
+# support in every 32 rows; the last unit has 3, 13, 13 and 13 rows, an odd number of elements where rows are odd.
+LONG = [((59, 59, 59, 39), (4, 5, 6, 20), 0.1), ((53, 53, 53, 55), (4, 5, 6, 17), 0.06), ((47, 47, 45, 69), (4, 5, 6, 24), 0.05),
+        ((47, 47, 45, 72), (4, 5, 6, 32), 0.05)]
 
 
 def _weights(shape, seed):
@@ -59,6 +66,28 @@ def test_rows_bf16_weights(shape, ranks, share):
     for worst, frac in info["stats"]:
         assert worst <= 1
         assert frac <= max(5e-3, 2.0 / (2 * int(np.prod(shape))))
+
+
+@pytest.mark.parametrize("dt", ["c64", "cbf16"])
+@pytest.mark.parametrize("shape,ranks,share", LONG)
+def test_rows_many_units(shape, ranks, share, dt):
+    print("[case] rows, many units", shape, ranks, dt, flush=True)
+    grads = [synth.small_case(shape, 610 + t, outlier_frac=(1, 100), dtype=dt) for t in range(2)]
+    W0 = _weights(shape, 11).astype(np.complex64)
+    info = run_both(T, shape, ranks, int(np.ceil(share * np.prod(shape))), grads, W0, refresh_every=3, lr=2e-3, weight_decay=0.01,
+                    grad_dtype=T.TGRAD_CBF16 if dt == "cbf16" else T.TGRAD_C64)
+    assert all(info["omega_equal"])
+    check_parity(info, W0)
+
+
+@pytest.mark.parametrize("shape,ranks,share", LONG)
+def test_rows_many_units_bf16_weights(shape, ranks, share):
+    print("[case] rows, many units, bf16 weights", shape, ranks, flush=True)
+    grads = [synth.small_case(shape, 710 + t, outlier_frac=(1, 100)) for t in range(2)]
+    info = run_both_bf16_weights(T, shape, ranks, int(np.ceil(share * np.prod(shape))), grads,
+                                 O.complex_to_bf16_pairs(_weights(shape, 12)), resync=True, refresh_every=3, lr=2e-3, weight_decay=0.01)
+    for worst, frac in info["stats"]:
+        assert worst <= 1 and frac <= 5e-3
 
 
 @pytest.mark.parametrize("order", [T.TGRAD_ORDER_LR_US, T.TGRAD_ORDER_SUM])
