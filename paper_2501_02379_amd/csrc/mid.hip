@@ -310,9 +310,9 @@ __device__ __forceinline__ void stage_split(u32v4* table, const float2* Up, int 
 }
 
 // The same for an expansion's whole table, in two calls: the first BATCH items of a wavefront are requested before the columns
-// of x are, so that what is needed first does not wait behind them (128x128x64x33, r 32,32,16,8: 11.3 -> 10.3 us;
-// 128x128x128x65, r 32,32,32,16: 22.6 -> 20.9).  k_mid_split waits for its first rows of x alone beside the table, and the
-// registers cost it more than the order gave (128x128x64x33, r 64,64,32,16: 31.9 -> 33 us).
+// of x are, so that what is needed first does not wait behind them (launch_mid has the line).  k_mid_split waits for its first
+// rows of x alone beside the table, and the registers cost it more than the order gave (128x128x64x33, r 64,64,32,16: 31.9 ->
+// 33 us).
 template <int BATCH>
 struct ExpandTable {
   FactorRef U;
@@ -431,8 +431,9 @@ __global__ __launch_bounds__(64 * W) void k_mid_split(const float* __restrict__ 
   }
 }
 
-// Expansion of up to 16 KQ rows: their operands stay in registers while the tiles of 16 output rows go by.
-template <int VEC, int KQ, int W>
+// Expansion of up to 16 KQ rows: their operands stay in registers while the tiles of 16 output rows go by.  AHEAD: items of the
+// table that a wavefront requests before its columns (0: all of them after).
+template <int VEC, int KQ, int W, int AHEAD>
 __global__ __launch_bounds__(64 * W) void k_expand_split(const float* __restrict__ x, const float2* __restrict__ Up,
                                                          int rn, uint32_t ncv, uint32_t BV, int K, int M, int tiles,
                                                          int groups, float* __restrict__ out) {
@@ -456,10 +457,15 @@ __global__ __launch_bounds__(64 * W) void k_expand_split(const float* __restrict
         v[q][j] = *reinterpret_cast<const V*>(xp + (int64_t)(k < K ? k : K - 1) * row);
       }
   };
-  ExpandTable<(KQ <= 2 ? 4 : 2)> tab(Up, rn, M, K, 16 * t0, nt, KQ);
-  tab.load(wave, W, lane);
-  fetch(nq);
-  tab.stage(sQ, wave, W, lane);
+  if constexpr (AHEAD > 0) {
+    ExpandTable<AHEAD> tab(Up, rn, M, K, 16 * t0, nt, KQ);
+    tab.load(wave, W, lane);
+    fetch(nq);
+    tab.stage(sQ, wave, W, lane);
+  } else {
+    fetch(nq);
+    stage_split<false>(sQ, Up, rn, M, K, 16 * t0, nt, 0, KQ, tid, 64 * W);
+  }
   __syncthreads();
   for (int g = (int)blockIdx.x * W + wave; g < groups; g += stride) {
     const Cols cq = nq;
@@ -763,22 +769,29 @@ void launch_mid(hipStream_t s, const float2* x, const float2* U, int rn, bool pr
       const int most = 32 / kq, tiles = Q < most ? Q : most;
       const size_t lds = (size_t)tiles * kq * kSplitItem * 16;
       const unsigned ny = (unsigned)((Q + tiles - 1) / tiles);
-#define TGRAD_EXS(V_, KQ_, W_)                                                                       \
+      // The table's first items before the columns where a wavefront has three or more of them and the rows are more than one quad:
+      // what it requests beyond its items only delays the columns.  A launch, us, columns first / four items of the table first (two of
+      // more than two quads): 128x128x128x65, r 32,32,32,16 23.0 / 20.5; 128x128x32x33, r 20,32,16,16 15.7 / 15.2, with 128 of rank 64
+      // 21.8 / 20.8; but with 64 of rank 16 10.3 / 10.7, 32 of rank 10 9.5 / 10.2, 64x32x32x33 with rank 10 6.7 / 7.2, 32 7.7 / 8.2, 64x64
+      // with 32 10.4 / 11.1; with 200 of rank 32 (eight wavefronts) 25.8 / 25.8, two items first 25.2.
+#define TGRAD_EXS(V_, KQ_, W_, AH_)                                                                  \
   do {                                                                                               \
-    allow_lds(k_expand_split<V_, KQ_, W_>, lds);                                                     \
-    const int64_t most_ = (int64_t)compute_units() * resident_blocks(k_expand_split<V_, KQ_, W_>, 64 * W_, lds); \
+    allow_lds(k_expand_split<V_, KQ_, W_, AH_>, lds);                                                \
+    const int64_t most_ = (int64_t)compute_units() * resident_blocks(k_expand_split<V_, KQ_, W_, AH_>, 64 * W_, lds); \
     const int64_t need_ = (groups + W_ - 1) / W_;                                                    \
-    k_expand_split<V_, KQ_, W_><<<dim3((unsigned)(need_ < most_ ? need_ : most_), ny), dim3(64 * W_), lds, s>>>( \
+    k_expand_split<V_, KQ_, W_, AH_><<<dim3((unsigned)(need_ < most_ ? need_ : most_), ny), dim3(64 * W_), lds, s>>>( \
         xf, U, rn, ncv, BV, K, M, tiles, (int)groups, of);                                           \
   } while (0)
-#define TGRAD_EXS_K(V_, W_)                                                                          \
+#define TGRAD_EXS_K(V_)                                                                              \
   do {                                                                                               \
-    if (kq == 1) TGRAD_EXS(V_, 1, W_); else TGRAD_EXS(V_, 2, W_);                                    \
+    if (kq == 1) { if (lds > 48 * 1024) TGRAD_EXS(V_, 1, 8, 0); else TGRAD_EXS(V_, 1, 4, 0); }       \
+    else if (lds > 48 * 1024) TGRAD_EXS(V_, 2, 8, 2);                                                \
+    else if (tiles > 4) TGRAD_EXS(V_, 2, 4, 4);                                                      \
+    else TGRAD_EXS(V_, 2, 4, 0);                                                                     \
   } while (0)
-      if (kq == 3) { if (lds > 48 * 1024) TGRAD_EXS(1, 3, 8); else TGRAD_EXS(1, 3, 4); }
-      else if (kq == 4) { if (lds > 48 * 1024) TGRAD_EXS(1, 4, 8); else TGRAD_EXS(1, 4, 4); }
-      else if (lds > 48 * 1024) { if (vec == 2) TGRAD_EXS_K(2, 8); else TGRAD_EXS_K(1, 8); }
-      else { if (vec == 2) TGRAD_EXS_K(2, 4); else TGRAD_EXS_K(1, 4); }
+      if (kq == 3) { if (lds > 48 * 1024) TGRAD_EXS(1, 3, 8, 2); else TGRAD_EXS(1, 3, 4, 2); }
+      else if (kq == 4) { if (lds > 48 * 1024) TGRAD_EXS(1, 4, 8, 2); else TGRAD_EXS(1, 4, 4, 2); }
+      else if (vec == 2) TGRAD_EXS_K(2); else TGRAD_EXS_K(1);
 #undef TGRAD_EXS_K
 #undef TGRAD_EXS
       return;

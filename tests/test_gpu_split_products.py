@@ -37,7 +37,11 @@ def test_middle_stages(shape, ranks, k):
 
 @pytest.mark.parametrize("shape,ranks,k", [
     ((96, 100, 20, 9), (4, 40, 20, 9), 900),       # 21 items of an expansion's table: a whole batch of the wavefronts and a part
-    ((96, 200, 20, 9), (4, 20, 20, 9), 900),       # 26
+    ((96, 200, 20, 9), (4, 20, 20, 9), 900),       # 26, for eight wavefronts
+    ((250, 144, 16, 9), (4, 20, 16, 9), 900),      # ... 18, pairs of columns
+    ((250, 70, 16, 16), (4, 20, 16, 16), 900),     # 10 for four: a part of a batch; pairs of columns
+    ((96, 128, 20, 9), (4, 32, 20, 9), 900),       # 16: a whole one
+    ((96, 64, 20, 9), (4, 20, 20, 9), 900),        # 8: columns first
 ])
 def test_expansion_tables_past_the_first_requests(shape, ranks, k):
     test_middle_stages(shape, ranks, k)
