@@ -478,10 +478,12 @@ static bool rows_kernel_fits(int K, int r) { return K >= 2 && K <= kRowsMaxExten
 
 // k_rows takes nearly all of these from k_lproj; us, k_lproj / k_rows, rows x K, r: 12288x4, 1 4.6 / 4.2; 12288x33, 8 7.8 / 5.3; 229376x4, 1
 // 9.7 / 9.0; 229376x33, 8 26 / 18; 400000x20, 5 29 / 20; 160000x65, 8 34 / 23; 640000x12, 10 34 / 32; 640000x65, 16 109 / 80; 640000x33, 17 86 / 58;
-// 640000x72, 30 288 / 113.  Not rows of up to 6 elements where they are one or two units for each wavefront of the chip, half as many
-// tiles for k_lproj (whole step: 65536x3 27.7 / 29.4, 98304x4 29.6 / 30.8, 65536x5 28.4 / 29.5, 76800x5 30.3 / 30.7; but 204800x3 40.1 / 38.8).
+// 640000x72, 30 288 / 113.  Not rows of up to 6 elements where they are one to six units for each wavefront of the chip, half as many
+// tiles for k_lproj (whole step: 65536x3 27.7 / 29.4, 98304x4 29.6 / 30.8, 65536x5 28.4 / 29.5, 76800x5 30.3 / 30.7, bf16 152047x3 36.8 /
+// 38.0; a launch, 151872 rows of 2 to 6: 7.4 .. 8.7 / 8.0 .. 9.0, in bf16 7.2 .. 8.6 / 8.6 .. 9.8; but 204800x3 40.1 / 38.8 and launches
+// of 375000 rows of 2 to 6 12.4 .. 15.8 / 12.2 .. 13.7).
 bool rows_kernel_pays(int K, int r, int64_t rows) {
-  return rows_kernel_fits(K, r) && (K > 6 || rows < 1024 * kUnit || rows >= 8192 * kUnit);
+  return rows_kernel_fits(K, r) && (K > 6 || rows < 1024 * kUnit || rows >= 12288 * kUnit);
 }
 
 // k_rows_update leaves ranks up to 8 of many rows to k_lupdate, which has two matrix steps of four elements for them and half as

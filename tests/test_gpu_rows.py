@@ -29,6 +29,8 @@ SHAPES = [
     ((40, 30, 40, 24), (4, 5, 34, 9), 0.01),            # rank 9 of many rows
     ((40, 30, 40, 12), (4, 5, 34, 8), 0.01),            # rank 8 of many rows: the update of the 32 x 32 kernels
     ((20, 20, 40, 13), (4, 5, 34, 6), 0.05),            # 16000 rows: a wavefront for every unit
+    ((64, 60, 51, 6), (4, 5, 34, 3), 0.05),             # 195840 short rows: the 32 x 32 kernels
+    ((64, 61, 51, 5), (4, 5, 34, 2), 0.05),             # 199104: several short units per wavefront
 ]
 
 # The same where every wavefront takes more than three units: both sets of registers, each of them requested again, and support
