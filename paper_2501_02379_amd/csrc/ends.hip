@@ -650,7 +650,13 @@ __global__ __launch_bounds__(64 * kMaxWaves, 2) void k_tail(TailArgs a, SparseAd
   constexpr bool kShare = tail_shares(WDT, CT);
   const bool split = kShare ? a.split == 1 : a.split != 0;
   const int nw = (int)gridDim.x * W;
-  const int first = (int)blockIdx.x * W + wave;
+  int block = (int)blockIdx.x;
+  if (kShare && a.split > 1 && W == 4 && (int)gridDim.x % (8 * a.split) == 0) {
+    // slabs on the XCD on which k_head has them, four to a workgroup: its L2 has the support's places and values (launch_tail)
+    const int in = block % (8 * a.split);
+    block += a.split * (in & 7) + (in >> 3) - in;
+  }
+  const int first = block * W + wave;
   const int share = kShare ? a.split >> 1 : 0, every = kShare && share ? a.split : 1, ts0 = kShare ? wave & (every - 1) : 0;
   int slab = split ? first / S : first >> share, ts = split ? first - slab * S : ts0;
   auto advance = [&](int& sl, int& t) {
@@ -1146,8 +1152,21 @@ void launch_tail(hipStream_t s, const float2* y1, const float2* U3, int K, int M
   // 299 / 284; 50x50x64x65 73.3 / 71.0 / 69.5; 128x128x128x65, r 32,16 741 / 725 / 732; 64x64x128x65, r 32,16 207 / 201 / 200;
   // 100x100x96x40, r 30,6 221 / 217 / -; but 64x64x64x33, r 30,16 80.9 / 85.3 / -; 100x100x64x17, r 8,4 67.5 / 68.2 / -; 128x128x64x65,
   // bf16 G and W 190.6 / 189.5 / 190.8.
+  // Where a workgroup then has fewer slabs than one of k_head, it takes them on the same XCD: the support's places and values that one
+  // of the kernels has written or read lie in the other's L2.  Alone / two, each on the next XCD / two, 1, 5 and 30 % in the
+  // support: 2106 slabs of 44x29, r 8,8, 30 % 45.1 / 46.8 / 44.5; 1600 of 64x33, r 16,8 35.6 / 35.3 / 34.7, 35.8 / 36.0 / 35.0 and
+  // 45.5 / 46.3 / 43.9; 2700 of 115x19, r 30,7 61.9 / 61.9 / 60.9, 62.4 / 63.2 / 61.5 and 79.3 / 76.5 / 76.1; where gs outgrows the
+  // L2s nothing changes.
+  // Slabs of two tiles are not shared from 2560 on to 3072 (a round of 2048 wavefronts and a part: with two for a slab two rounds and as
+  // large a part; alone / two: 2700 of 44x29, r 8,8 37.4 / 38.5, of 64x33, r 16,16 57.3 / 58.5, of 39x19, r 8,4 31.0 / 31.5; but 2401 of 44x22,
+  // r 11,12 39.7 / 37.5, 2100 of 39x19, r 16,11 37.3 / 35.6, 3540 of 64x33, r 16,16 68.1 / 65.0), nor from there on if the second has less than 12 rows of 32
+  // for its wavefront (16000 of 39x19, r 16,11 117.1 / 121.0, 30 % 136.9 / 149.6; 8010 74.7 / 76.6; but 5593 of 45x29, r 13,14 79.5 / 78.0,
+  // 9401 of 54x28, r 6,11 94.5 / 92.1).  Nor, for ranks of 17 and more in mode N-1, 1280 to 2047 slabs, one for each wavefront (1600 of
+  // 126x27, r 30,8 52.1 / 54.0, of 115x19, r 30,7 43.1 / 43.8; but 1122 of 126x27 47.5 / 44.8, 2100 70.2 / 64.3).
   const int many = K2 <= 16 ? (S % 4 == 0 ? 4 : 2) : S >= 6 || (K <= 8 && S >= 4) ? 2 : 1;
-  const int together = !split && tail_shares(wdtype, columns_class(M)) && S % many == 0 ? many : 1;
+  const bool levels = S == 2 ? nslabs < 5 * kWholeSlabs / 2 || (nslabs >= 3 * kWholeSlabs && 8 * (I2 - R) >= 3 * R)
+                             : K2 <= 16 || nslabs < 5 * kWholeSlabs / 4 || nslabs >= 2 * kWholeSlabs;
+  const int together = !split && levels && tail_shares(wdtype, columns_class(M)) && S % many == 0 ? many : 1;
   const int64_t units = split ? nslabs * S : nslabs * together;
   const int full = tail_lds(4, M, I2, K2, K) <= kLdsLimit / 2 ? 4 : tail_lds(8, M, I2, K2, K) <= kLdsLimit ? 8 : 4;
   // Few tiles: a wavefront each.  Where coefficients go to LDS (tail_coef_lds) it then takes its operands straight into

@@ -65,6 +65,12 @@ SHARED_SLABS = [
     ((46, 46, 63, 20), (3, 4, 5, 6)),                   # two wavefronts, two tiles
     ((46, 46, 63, 34), (3, 4, 20, 8)),                  # ... four tiles, two operands of mode N-1's rank
     ((51, 51, 95, 34), (3, 4, 20, 10)),                 # ... six tiles
+    ((34, 33, 39, 19), (3, 4, 16, 11)),                 # ... 561 workgroups: not whole rounds of the eight XCDs
+    ((34, 32, 39, 19), (3, 4, 16, 11)),                 # ... 544: whole ones
+    ((51, 51, 39, 19), (3, 4, 16, 11)),                 # a wavefront for every slab again: 2601 of two tiles
+    ((60, 60, 43, 18), (3, 4, 5, 6)),                   # ... 3600, a second tile of 11 rows
+    ((60, 60, 44, 18), (3, 4, 5, 6)),                   # two again: of 12
+    ((37, 37, 115, 19), (3, 4, 30, 7)),                 # ... ranks of 17 and more, 1369 slabs
 ]
 
 
