@@ -269,8 +269,9 @@ __global__ __launch_bounds__(kGramThreads) void k_gram(const void* __restrict__ 
 // What runs next to the f64 matrix instructions matters, because they occupy the SIMD's vector ALU:
 //  * RT tile rows (1, 2, 4 or 8) are held; a staged tile is 4096 elements whatever RT: 256 / RT columns, so a thread
 //    always has 8 loads in flight and a barrier is passed as rarely as the LDS allows.
-//  * LDS holds two planes (re, im) per staged tile, column by column, rows contiguous, an odd column stride: operand
-//    reads (16 rows x 4 columns) and commits are free of bank conflicts.  Xr +- Xi are formed in registers.
+//  * LDS holds two planes (re, im) per staged tile, column by column, rows contiguous, an odd column stride.  (Not free of
+//    bank conflicts: 1.13 cycles of them for every one of active LDS instructions; operands are requested three column
+//    pairs ahead.)  Xr +- Xi are formed in registers.
 //  * Fetch: the element and its support-mask word come through buffer descriptors (the tile's first column as
 //    base, scalar); lanes without an element use an offset that the range check answers with zero.
 //    The mask is applied at the commit, so nothing waits for the loads before the matrix phase.
